@@ -119,6 +119,7 @@ int enqueue_gemm_linear(const ddd_body* b, const void* W, int N, int K, const ui
   g.H = K;
   g.V = N;
   g.ngrp = 0;
+  g.ldl = N;
   g.reverse = 0;
   g.epi = epi;
   g.out16 = out16;

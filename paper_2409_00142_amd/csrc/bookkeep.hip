@@ -196,7 +196,7 @@ __global__ __launch_bounds__(256) void row_topk_kernel(RowTopkArgs a) {
   // ---- collect candidates >= T ------------------------------------------------------------------
   // Only groups whose max reaches T can hold one: usually k or a few more of them, so the row's
   // logits are read group by group (64 consecutive values, one per lane) rather than scanned.
-  const float* x = a.logits + (size_t)row * a.V;
+  const float* x = a.logits + (size_t)row * a.ldl;
   const float T = s_T;
   for (int g = tid; g < ngrp_valid; g += 256)
     if (gmax[g] >= T) {
@@ -222,8 +222,8 @@ __global__ __launch_bounds__(256) void row_topk_kernel(RowTopkArgs a) {
           if (p < kCandMax) s_cand[p] = row_key(xv[u], vv[u]);
         }
     }
-  } else if ((a.V & 3) == 0) {                                 // too many groups tie at T: scan the row
-    const int nchunk = a.V >> 2;
+  } else if ((a.ldl & 3) == 0) {                               // too many groups tie at T: scan the row
+    const int nchunk = (a.V + 3) >> 2;                         // the last piece may reach into the row's padding
     for (int c0 = tid; c0 < nchunk; c0 += 8 * 256) {
       float4 q[8];   // eight independent 16-byte loads in flight before any is consumed
 #pragma unroll
@@ -239,7 +239,7 @@ __global__ __launch_bounds__(256) void row_topk_kernel(RowTopkArgs a) {
         if (c < nchunk && fmaxf(fmaxf(xq[0], xq[1]), fmaxf(xq[2], xq[3])) >= T) {
 #pragma unroll
           for (int e = 0; e < 4; ++e)
-            if (xq[e] >= T) {
+            if (xq[e] >= T && 4 * c + e < a.V) {
               const int p = atomicAdd(&s_cnt, 1);
               if (p < kCandMax) s_cand[p] = row_key(xq[e], 4 * c + e);
             }

@@ -25,10 +25,10 @@ struct ddd_ctx {
   float* part_sum;      // [B*k][nslice] or [B*k]
   int32_t* row_list;    // [B*k] active rows of the current call (GEMM path)
   int32_t* n_act;       // [1]
-  float* logits;        // [B*k][V] fp32 logits of the GEMM path (null if B*k <= 16)
+  float* logits;        // [B*k][ldl] fp32 logits of the GEMM path (null if B*k <= 16)
   float* grp_max;       // [B*k][ngrp] per-group max / sum-exp of the GEMM path
   float* grp_sum;
-  int ngrp;
+  int ngrp, ldl;
   const void* pack_src; // W pointer whose tile-major copy is in pack (null: none)
   uint16_t* pack;       // [ceil(V/256)*256][H] tile-major copy for the GEMM path, owned
   hipGraph_t graph;
@@ -78,6 +78,9 @@ bool pick_split(int H, int* G, int* nw) {
   return false;
 }
 
+// Row pitch of the context's own logits: whole 128-byte lines.
+int logits_pitch(int V) { return (V + 31) & ~31; }
+
 bool state_ok(const ddd_state* s) {
   return s && s->logprobsum && s->beam_node && s->beam_token && s->beam_parent_slot && s->pool_token &&
          s->pool_parent && s->pool_depth && s->pool_score && s->n_nodes && s->steps && s->active && s->row_active &&
@@ -119,8 +122,8 @@ WideStepArgs wide_args(const ddd_ctx* c, const BeamArgs& beam) {
   return w;
 }
 
-// MFMA GEMM over the rows listed in the context's row list, logits into `out`.
-int enqueue_gemm(ddd_ctx* c, const void* W, const void* hid, int max_rows, float* out, int reverse, hipStream_t s) {
+// MFMA GEMM over the rows listed in the context's row list, logits into `out` (row pitch ldl).
+int enqueue_gemm(ddd_ctx* c, const void* W, const void* hid, int max_rows, float* out, int ldl, int reverse, hipStream_t s) {
   GemmArgs g;
   g.W = static_cast<const uint16_t*>(W);
   g.Wp = (c->pack_src != nullptr && c->pack_src == W) ? c->pack : nullptr;
@@ -133,6 +136,7 @@ int enqueue_gemm(ddd_ctx* c, const void* W, const void* hid, int max_rows, float
   g.H = c->cfg.H;
   g.V = c->cfg.V;
   g.ngrp = c->ngrp;
+  g.ldl = ldl;
   g.reverse = (c->cfg.flags & DDD_FLAG_FORWARD_SWEEPS) ? 0 : reverse;
   g.epi = kGemmLogits;
   g.out16 = nullptr;
@@ -154,14 +158,16 @@ int enqueue_stream(ddd_ctx* c, const void* W, const void* hid, int n_rows, const
                    int reverse, hipStream_t s, bool list_ready = false, int trace_step = -1, bool eager_loads = false) {
   if (gemm_path(c, n_rows)) {
     float* out = logits_dbg ? logits_dbg : c->logits;
+    const int ldl = logits_dbg ? c->cfg.V : c->ldl;
     if (!list_ready) DDD_HIP(launch_build_row_list(row_active, n_rows, c->row_list, c->n_act, s));
-    int rc = enqueue_gemm(c, W, hid, n_rows, out, reverse, s);
+    int rc = enqueue_gemm(c, W, hid, n_rows, out, ldl, reverse, s);
     if (rc != DDD_OK) return rc;
     RowTopkArgs t;
     t.logits = out;
     t.grp_max = c->grp_max;
     t.grp_sum = c->grp_sum;
     t.ngrp = c->ngrp;
+    t.ldl = ldl;
     t.row_active = row_active;
     t.part_key = c->part_key;
     t.part_sum = c->part_sum;
@@ -246,7 +252,7 @@ size_t ddd_scratch_bytes(const ddd_config* cfg) {
   const size_t rows = (size_t)cfg->B * cfg->k, max_slices = (cfg->k > DDD_KMAX) ? 1 : 512;
   size_t n = rows * max_slices * cfg->k * sizeof(uint64_t) + rows * max_slices * sizeof(float) + rows * 4 + 4;
   if (rows > DDD_STREAM_ROWS || cfg->k > DDD_KMAX)   // logits and per-group statistics of the GEMM path
-    n += rows * (size_t)cfg->V * sizeof(float) + 2 * rows * (size_t)(((cfg->V + 63) / 64 + 3) & ~3) * sizeof(float);
+    n += rows * (size_t)logits_pitch(cfg->V) * sizeof(float) + 2 * rows * (size_t)(((cfg->V + 63) / 64 + 3) & ~3) * sizeof(float);
   return n;
 }
 
@@ -284,6 +290,7 @@ int ddd_create(const ddd_config* cfg, ddd_ctx** out) {
   c->pack_src = nullptr;
   c->pack = nullptr;
   c->ngrp = ((cfg->V + 63) / 64 + 3) & ~3;
+  c->ldl = logits_pitch(cfg->V);
   const size_t rows = (size_t)cfg->B * cfg->k;
   const size_t ns = (cfg->k > DDD_KMAX) ? 1 : (size_t)c->nslice;   // wide beams only use the dense format
   c->part_key_bytes = rows * ns * cfg->k * sizeof(uint64_t);
@@ -294,7 +301,7 @@ int ddd_create(const ddd_config* cfg, ddd_ctx** out) {
   if (e == hipSuccess) e = hipMalloc(&c->row_list, rows * sizeof(int32_t));
   if (e == hipSuccess) e = hipMalloc(&c->n_act, sizeof(int32_t));
   if (e == hipSuccess && (rows > DDD_STREAM_ROWS || cfg->k > DDD_KMAX)) {
-    c->logits_bytes = rows * (size_t)cfg->V * sizeof(float);
+    c->logits_bytes = rows * (size_t)c->ldl * sizeof(float);
     c->grp_bytes = rows * (size_t)c->ngrp * sizeof(float);
     e = hipMalloc(&c->logits, c->logits_bytes);
     if (e == hipSuccess) e = hipMalloc(&c->grp_max, c->grp_bytes);
@@ -463,7 +470,7 @@ int ddd_profile_lmhead(ddd_ctx* c, const void* W, const void* hid, int32_t n_row
   for (int i = 0; i < iters && rc == DDD_OK; ++i) {
     if (hipEventRecord(ev[2 * i], s) != hipSuccess) rc = DDD_ERR_HIP;
     if (rc == DDD_OK)
-      rc = gemm ? enqueue_gemm(c, W, hid, n_rows, c->logits, i & 1, s) : enqueue_stream(c, W, hid, n_rows, nullptr, nullptr, i & 1, s);
+      rc = gemm ? enqueue_gemm(c, W, hid, n_rows, c->logits, c->ldl, i & 1, s) : enqueue_stream(c, W, hid, n_rows, nullptr, nullptr, i & 1, s);
     if (rc == DDD_OK && hipEventRecord(ev[2 * i + 1], s) != hipSuccess) rc = DDD_ERR_HIP;
   }
   if (rc == DDD_OK && hipEventSynchronize(ev[2 * (size_t)iters - 1]) != hipSuccess) rc = DDD_ERR_HIP;

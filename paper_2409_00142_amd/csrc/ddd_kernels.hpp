@@ -22,10 +22,11 @@ struct GemmArgs {
   const uint16_t* hid;        // bf16 [rows,H]
   const int32_t* row_list;    // [n_act] ids of the active rows, ascending
   const int32_t* n_act_ptr;   // device scalar
-  float* logits;              // fp32 [rows][V]: written for the active rows
+  float* logits;              // fp32 [rows][ldl]: written for the active rows (columns V .. ldl - 1 hold no logits)
   float* grp_max;             // fp32 [rows][ngrp]: max of each group of 64 consecutive vocabulary rows ...
   float* grp_sum;             // fp32 [rows][ngrp]: ... and sum of exp(logit - that max); ngrp = ceil(V/64) rounded up to 4
   int H, V, ngrp;
+  int ldl;                    // row pitch of logits (y), >= V; a multiple of 4 lets every row be stored 16 bytes at a time
   int reverse;                // hand the row tiles of W out from the last to the first
   // What happens to the sums (the same product serves the draft layer's linears: W = a weight matrix [N = V][K = H],
   // hid = the input rows, logits = y).  kGemmLogits needs grp_max / grp_sum; the other modes ignore them.
@@ -56,13 +57,13 @@ hipError_t launch_build_row_list(const uint8_t* row_active, int n_rows, int32_t*
 // Row reduction of materialised logits: lse and top-k keys of every active row, in the "dense"
 // partial format part_key[row][k] (final keys in order), part_sum[row] = lse.
 struct RowTopkArgs {
-  const float* logits;        // fp32 [n_rows][V]
+  const float* logits;        // fp32 [n_rows][ldl]
   const float* grp_max;       // fp32 [n_rows][ngrp] per-group statistics written by the GEMM
   const float* grp_sum;
   const uint8_t* row_active;  // [n_rows] or null
   uint64_t* part_key;         // [n_rows][k]
   float* part_sum;            // [n_rows]
-  int n_rows, V, k, ngrp;
+  int n_rows, V, k, ngrp, ldl;
 };
 hipError_t launch_row_topk(const RowTopkArgs& a, hipStream_t stream);
 

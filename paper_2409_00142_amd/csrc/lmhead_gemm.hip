@@ -215,7 +215,10 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, unsigned char* ldsb
   if (NB == 0) return;
   // accumulator register q*4+e of block (bm, bn): vocabulary row vb + bm*32 + q*8 + e, hidden row column l32
   const int vb = mt * C::BM + wm * 32 * AB + lh * 4;
-  const bool v_aligned = (a.V & 3) == 0;
+  // Rows that start on 16 bytes are stored 16 bytes at a time, the last piece into the columns between V and ldl: the
+  // context's own logits have such a pitch whatever V is; a caller's debug buffer has pitch V, and for an odd V the
+  // scalar stores (V = 32003, 170 rows: 94.8 us a ddd_lmhead_topk call with those, 84.8 with a padded pitch).
+  const bool v_aligned = (a.ldl & 3) == 0;
   static_assert(AB % 2 == 0, "a wave covers whole groups of 64 vocabulary rows");
   constexpr int NGW = AB / 2;                                  // groups per wave
   const int grp0 = (mt * C::BM + wm * 32 * AB) >> 6;
@@ -226,7 +229,7 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, unsigned char* ldsb
       const int n = col0 + bn * 32 + l32;
       if (n >= n_act) continue;
       const int orow_id = a.row_list[n];
-      float* orow = a.logits + (size_t)orow_id * a.V;
+      float* orow = a.logits + (size_t)orow_id * a.ldl;
       uint16_t* o16 = a.out16 ? a.out16 + (size_t)orow_id * a.ld16 : nullptr;
       uint16_t* o16b = a.out16b ? a.out16b + (size_t)orow_id * a.ld16 : nullptr;
 #pragma unroll
@@ -292,13 +295,13 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, unsigned char* ldsb
             a.grp_sum[(size_t)orow_id * a.ngrp + grp0 + gp] = gs[gp];
           }
       }
-      float* orow = a.logits + (size_t)orow_id * a.V;
+      float* orow = a.logits + (size_t)orow_id * a.ldl;
 #pragma unroll
       for (int bm = 0; bm < AB; ++bm)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const int v = vb + bm * 32 + q * 8;
-          if (v_aligned && v + 3 < a.V) {
+          if (v_aligned && v < a.V) {   // v and ldl are multiples of 4: v + 3 < ldl
             const f32x4 o = {acc[bm][bn][q * 4], acc[bm][bn][q * 4 + 1], acc[bm][bn][q * 4 + 2],
                              acc[bm][bn][q * 4 + 3]};
             *reinterpret_cast<f32x4*>(orow + v) = o;
