@@ -104,15 +104,17 @@ int enqueue_linear_ranges(const ddd_body* b, LinearArgs a, int K_range, hipStrea
   return DDD_OK;
 }
 
-// y (+)= x W^T over the rows in b->row_list through the MFMA GEMM (calls of more than kBodyRows rows).
-int enqueue_gemm_linear(const ddd_body* b, const void* W, int N, int K, const uint16_t* x, float* y, int epi,
+// y (+)= x W^T over the rows in b->row_list, or over all n_rows of them, through the MFMA GEMM (calls of more than
+// kBodyRows rows).
+int enqueue_gemm_linear(const ddd_body* b, int n_rows, bool all_rows, const void* W, int N, int K, const uint16_t* x, float* y, int epi,
                         uint16_t* out16, uint16_t* out16b, int ld16, hipStream_t s) {
   GemmArgs g;
   g.W = static_cast<const uint16_t*>(W);
   g.Wp = nullptr;
   g.hid = x;
-  g.row_list = b->row_list;
+  g.row_list = all_rows ? nullptr : b->row_list;
   g.n_act_ptr = b->n_act;
+  g.n_rows = n_rows;
   g.logits = y;
   g.grp_max = nullptr;
   g.grp_sum = nullptr;
@@ -235,8 +237,7 @@ int ddd_body_linear(ddd_body* b, const void* W, int32_t N, int32_t K, const void
   if (R > kBodyRows) {   // the MFMA path of calls with more rows, all R rows taken as active
     if (R > b->rows || N % 4 != 0) return DDD_ERR_INVALID_ARG;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    BODY_HIP(launch_build_row_list(nullptr, R, b->row_list, b->n_act, s));
-    return enqueue_gemm_linear(b, W, N, K, static_cast<const uint16_t*>(x), y, accumulate ? kGemmAccumulate : kGemmStore,
+    return enqueue_gemm_linear(b, R, true, W, N, K, static_cast<const uint16_t*>(x), y, accumulate ? kGemmAccumulate : kGemmStore,
                                nullptr, nullptr, 0, s);
   }
   LinearArgs a = linear_args(W, K, N, R, nullptr, y, N, accumulate ? kLinearAccumulate : kLinearStore);
@@ -294,7 +295,8 @@ int ddd_body_step(void* user, int32_t step, const ddd_state* st, void* hid_out, 
   if (gemm) {
     // More than kBodyRows rows: the same sequence of operations with every linear on the matrix cores, over the
     // compacted list of active rows; the FC's input rows are assembled first (the GEMM gathers whole rows).
-    BODY_HIP(launch_build_row_list(act, R, b->row_list, b->n_act, s));
+    const bool all = act == nullptr;
+    if (!all) BODY_HIP(launch_build_row_list(act, R, b->row_list, b->n_act, s));
     PackX0Args px;
     px.E = static_cast<const uint16_t*>(b->w.E);
     px.token = (step == 0) ? b->p.root_token : st->beam_token;
@@ -307,19 +309,19 @@ int ddd_body_step(void* user, int32_t step, const ddd_state* st, void* hid_out, 
     px.R = R;
     px.feat_mode = (step == 0) ? kGatherNone : (step == 1) ? kGatherBlock : kGatherInBlock;
     BODY_HIP(launch_pack_x0(px, s));
-    rc = enqueue_gemm_linear(b, b->w.Wfc, H, 2 * H, b->x0, b->r, kGemmStore, nullptr, nullptr, 0, s);
+    rc = enqueue_gemm_linear(b, R, all, b->w.Wfc, H, 2 * H, b->x0, b->r, kGemmStore, nullptr, nullptr, 0, s);
     if (rc != DDD_OK) return rc;
     BODY_HIP(launch_rmsnorm(n1, s));
-    rc = enqueue_gemm_linear(b, b->w.Wqkv, 3 * H, H, b->xn, b->qkv, kGemmStore, nullptr, nullptr, 0, s);
+    rc = enqueue_gemm_linear(b, R, all, b->w.Wqkv, 3 * H, H, b->xn, b->qkv, kGemmStore, nullptr, nullptr, 0, s);
     if (rc != DDD_OK) return rc;
     BODY_HIP(launch_body_attention(t, s));
-    rc = enqueue_gemm_linear(b, b->w.Wo, H, H, b->xn, b->r, kGemmAccumulate, nullptr, nullptr, 0, s);   // r1 = r0 + o Wo^T
+    rc = enqueue_gemm_linear(b, R, all, b->w.Wo, H, H, b->xn, b->r, kGemmAccumulate, nullptr, nullptr, 0, s);   // r1 = r0 + o Wo^T
     if (rc != DDD_OK) return rc;
     BODY_HIP(launch_rmsnorm(n2, s));
-    rc = enqueue_gemm_linear(b, b->w.Wgu, 2 * F, H, b->xn, nullptr, kGemmSiluPairs, b->act, nullptr, F, s);
+    rc = enqueue_gemm_linear(b, R, all, b->w.Wgu, 2 * F, H, b->xn, nullptr, kGemmSiluPairs, b->act, nullptr, F, s);
     if (rc != DDD_OK) return rc;
     // h = bf16(r1 + a Wd^T), written to the hidden rows and to this call's features
-    return enqueue_gemm_linear(b, b->w.Wd, H, F, b->act, b->r, kGemmAccumulate, static_cast<uint16_t*>(hid_out),
+    return enqueue_gemm_linear(b, R, all, b->w.Wd, H, F, b->act, b->r, kGemmAccumulate, static_cast<uint16_t*>(hid_out),
                                b->h_hist + hist, H, s);
   }
 

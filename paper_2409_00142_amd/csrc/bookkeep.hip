@@ -11,16 +11,6 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeArgs a) {
   const int row = blockIdx.x * 4 + wave;
   if (row >= a.n_rows) return;                                 // wave-uniform
   if (a.row_active != nullptr && !a.row_active[row]) return;   // wave-uniform
-  if (a.nslice == 0) {   // dense format: the keys are final (any k up to DDD_KWIDE_MAX)
-    const float lse = a.part_sum[row];
-    for (int j = lane; j < a.k; j += 64) {
-      const uint64_t key = a.part_key[(size_t)row * a.k + j];
-      a.topk_token[(size_t)row * a.k + j] = key_token(key);
-      a.topk_logprob[(size_t)row * a.k + j] = key_value(key) - lse;
-    }
-    if (lane == 0) a.lse[row] = lse;
-    return;
-  }
   uint64_t key;
   float lse;
   {
@@ -192,6 +182,22 @@ __global__ __launch_bounds__(256) void row_topk_kernel(RowTopkArgs a) {
   }
   __syncthreads();
   const float lse = M + __logf(s_red[4] + s_red[5] + s_red[6] + s_red[7]);
+  // The rank-j key of the row: to the bookkeeping that follows, or to the caller of a single LM-head call (which
+  // needs nothing else: the separate launch that turned keys into tokens and logprobs cost 5 us a call).
+  auto emit = [&](int j, uint64_t key) {
+    if (a.topk_token != nullptr) {
+      a.topk_token[(size_t)row * a.k + j] = key_token(key);
+      a.topk_logprob[(size_t)row * a.k + j] = key_value(key) - lse;
+    } else {
+      a.part_key[(size_t)row * a.k + j] = key;
+    }
+  };
+  if (tid == 0) {
+    if (a.topk_token != nullptr)
+      a.lse[row] = lse;
+    else
+      a.part_sum[row] = lse;
+  }
 
   // ---- collect candidates >= T ------------------------------------------------------------------
   // Only groups whose max reaches T can hold one: usually k or a few more of them, so the row's
@@ -265,19 +271,17 @@ __global__ __launch_bounds__(256) void row_topk_kernel(RowTopkArgs a) {
     for (int i = cnt + tid; i < n2; i += 256) s_cand[i] = 0ull;
     __syncthreads();
     block_sort_desc(s_cand, n2, tid, 256);
-    for (int j = tid; j < a.k; j += 256) a.part_key[(size_t)row * a.k + j] = s_cand[j];
-    if (tid == 0) a.part_sum[row] = lse;
+    for (int j = tid; j < a.k; j += 256) emit(j, s_cand[j]);
   } else if (cnt <= 256) {                                     // uniform: the usual case, a few more than k candidates
     // ---- exact top-k among the candidates: a candidate's rank is the number of larger keys (keys are distinct) ---
     if (tid < cnt) {
       const uint64_t mine = s_cand[tid];
       int rank = 0;
       for (int j = 0; j < cnt; ++j) rank += (s_cand[j] > mine) ? 1 : 0;
-      if (rank < a.k) a.part_key[(size_t)row * a.k + rank] = mine;
+      if (rank < a.k) emit(rank, mine);
     } else if (tid < a.k) {
-      a.part_key[(size_t)row * a.k + tid] = 0ull;              // fewer candidates than beams (V < k cannot happen; kept total)
+      emit(tid, 0ull);                                         // fewer candidates than beams (V < k cannot happen; kept total)
     }
-    if (tid == 0) a.part_sum[row] = lse;
   } else if (cnt <= kCandMax) {                                // uniform
     // ---- many candidates (ties at the threshold): wave 0, k rounds of wave max over its strided share ---
     if (wave == 0) {
@@ -292,9 +296,8 @@ __global__ __launch_bounds__(256) void row_topk_kernel(RowTopkArgs a) {
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
       }
-      if (lane < a.k) a.part_key[(size_t)row * a.k + lane] = mine[0];
-      if (lane + 64 < a.k) a.part_key[(size_t)row * a.k + lane + 64] = mine[1];
-      if (lane == 0) a.part_sum[row] = lse;
+      if (lane < a.k) emit(lane, mine[0]);
+      if (lane + 64 < a.k) emit(lane + 64, mine[1]);
     }
   } else {
     // ---- more than kCandMax elements tie at or above T (e.g. constant logits): exact but slow ------
@@ -314,8 +317,7 @@ __global__ __launch_bounds__(256) void row_topk_kernel(RowTopkArgs a) {
       prev = umax64(umax64(s_best[0], s_best[1]), umax64(s_best[2], s_best[3]));
       if (tid == round) mine = prev;
     }
-    if (tid < a.k) a.part_key[(size_t)row * a.k + tid] = mine;
-    if (tid == 0) a.part_sum[row] = lse;
+    if (tid < a.k) emit(tid, mine);
   }
 }
 
@@ -354,63 +356,11 @@ hipError_t launch_depth_continue(const BeamArgs& a, int steps_done, hipStream_t 
 // the weight stream separately): one workgroup per sequence ---------------------------------------
 __global__ __launch_bounds__(1024) void step_bookkeep_kernel(StepArgs a) {
   __shared__ StepSmem sm;
-  __shared__ int s_last;
-  __shared__ int s_word_base[DDD_BMAX / 64 + 1];
-  __shared__ unsigned long long s_words[DDD_BMAX / 64];
   const int b = blockIdx.x, tid = threadIdx.x;
   if (a.trace != nullptr && b == 0 && tid == 0) a.trace[0] = (uint64_t)wall_clock64();
   const bool active = step_bookkeep_block(a, b, tid, blockDim.x, sm);
   if (a.trace != nullptr && b == 0 && tid == 0) a.trace[5] = (uint64_t)wall_clock64();
-  if (a.call_count == nullptr) return;               // uniform
-  if (tid == 0) {
-    // What the last workgroup needs from this one travels in atomics alone (performed at the device's
-    // coherence point), so no fence is needed: the sequence's bit first, then - once that atomic has returned
-    // its value - one add: arrivals in the low half, active sequences in the high half.
-    uint32_t mine = 1u | (active ? 0x10000u : 0u);
-    if (a.active_mask != nullptr && active) {
-      const uint64_t before = __hip_atomic_fetch_or(a.active_mask + (b >> 6), 1ull << (b & 63), __ATOMIC_RELAXED,
-                                                    __HIP_MEMORY_SCOPE_AGENT);
-      // the arrival below is made to depend on the value the first atomic returned: it cannot be issued earlier
-      asm volatile("" : "+v"(mine) : "v"((uint32_t)before), "v"((uint32_t)(before >> 32)));
-    }
-    const uint32_t seen = __hip_atomic_fetch_add(a.call_count, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const bool last = (seen & 0xFFFFu) + 1u == gridDim.x;
-    if (last) {
-      __hip_atomic_store(a.call_count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next round
-      if (a.progress != nullptr) {
-        const uint32_t any = ((seen + mine) >> 16) != 0u ? 1u : 0u;
-        __hip_atomic_store(a.progress, (a.round_tag << 2) | 2u | any, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-      }
-    }
-    s_last = (last && a.active_mask != nullptr) ? 1 : 0;
-  }
-  __syncthreads();
-  if (!s_last) return;                               // uniform
-  // The last workgroup to arrive: the next call's active rows, ascending (rows b*k .. b*k+k-1 of every sequence
-  // that goes on), for the GEMM path.  Every other workgroup's bit is in the mask: its arrival came after it.
-  const int B = gridDim.x, k = a.beam.k, nwords = (B + 63) >> 6;
-  for (int w = tid; w < nwords; w += blockDim.x) {
-    s_words[w] = __hip_atomic_load(a.active_mask + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(a.active_mask + w, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next call
-  }
-  __syncthreads();
-  if (tid == 0) {
-    int t = 0;
-    for (int w = 0; w < nwords; ++w) {
-      s_word_base[w] = t;
-      t += __popcll(s_words[w]);
-    }
-    s_word_base[nwords] = t;
-    *a.next_n_act = t * k;
-  }
-  __syncthreads();
-  for (int q = tid; q < B; q += blockDim.x) {
-    const unsigned long long word = s_words[q >> 6];
-    if ((word >> (q & 63)) & 1ull) {
-      const int pos = s_word_base[q >> 6] + __popcll(word & ((1ull << (q & 63)) - 1ull));
-      for (int i = 0; i < k; ++i) a.next_row_list[pos * k + i] = q * k + i;
-    }
-  }
+  report_call(a.report, active, b, a.beam.k, tid, blockDim.x);
 }
 
 hipError_t launch_step_bookkeep(const StepArgs& a, hipStream_t stream) {

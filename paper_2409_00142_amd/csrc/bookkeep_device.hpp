@@ -429,4 +429,62 @@ __device__ __forceinline__ bool step_bookkeep_block(const StepArgs& a, int b, in
   return !sm.stopped;
 }
 
+// End of a bookkeeping launch (one workgroup per sequence): the report of the call, by the workgroup that arrives last.
+// Every thread of every workgroup calls it; active: whether sequence b goes on (the same value in every thread).
+__device__ __forceinline__ void report_call(const CallReport& r, bool active, int b, int k, int tid, int nthr) {
+  __shared__ int s_last;
+  __shared__ int s_word_base[DDD_BMAX / 64 + 1];
+  __shared__ unsigned long long s_words[DDD_BMAX / 64];
+  if (r.call_count == nullptr) return;               // uniform
+  if (tid == 0) {
+    // What the last workgroup needs from this one travels in atomics alone (performed at the device's
+    // coherence point), so no fence is needed: the sequence's bit first, then - once that atomic has returned
+    // its value - one add: arrivals in the low half, active sequences in the high half.
+    uint32_t mine = 1u | (active ? 0x10000u : 0u);
+    if (r.active_mask != nullptr && active) {
+      const uint64_t before = __hip_atomic_fetch_or(r.active_mask + (b >> 6), 1ull << (b & 63), __ATOMIC_RELAXED,
+                                                    __HIP_MEMORY_SCOPE_AGENT);
+      // the arrival below is made to depend on the value the first atomic returned: it cannot be issued earlier
+      asm volatile("" : "+v"(mine) : "v"((uint32_t)before), "v"((uint32_t)(before >> 32)));
+    }
+    const uint32_t seen = __hip_atomic_fetch_add(r.call_count, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const bool last = (seen & 0xFFFFu) + 1u == gridDim.x;
+    if (last) {
+      __hip_atomic_store(r.call_count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next round
+      if (r.progress != nullptr) {
+        const uint32_t any = ((seen + mine) >> 16) != 0u ? 1u : 0u;
+        __hip_atomic_store(r.progress, (r.round_tag << 2) | 2u | any, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      }
+    }
+    s_last = (last && r.active_mask != nullptr) ? 1 : 0;
+  }
+  __syncthreads();
+  if (!s_last) return;                               // uniform
+  // The last workgroup to arrive: the next call's active rows, ascending (rows b*k .. b*k+k-1 of every sequence
+  // that goes on), for the GEMM path.  Every other workgroup's bit is in the mask: its arrival came after it.
+  const int B = gridDim.x, nwords = (B + 63) >> 6;
+  for (int w = tid; w < nwords; w += nthr) {
+    s_words[w] = __hip_atomic_load(r.active_mask + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(r.active_mask + w, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next call
+  }
+  __syncthreads();
+  if (tid == 0) {
+    int t = 0;
+    for (int w = 0; w < nwords; ++w) {
+      s_word_base[w] = t;
+      t += __popcll(s_words[w]);
+    }
+    s_word_base[nwords] = t;
+    *r.next_n_act = t * k;
+  }
+  __syncthreads();
+  for (int q = tid; q < B; q += nthr) {
+    const unsigned long long word = s_words[q >> 6];
+    if ((word >> (q & 63)) & 1ull) {
+      const int pos = s_word_base[q >> 6] + __popcll(word & ((1ull << (q & 63)) - 1ull));
+      for (int i = 0; i < k; ++i) r.next_row_list[pos * k + i] = q * k + i;
+    }
+  }
+}
+
 }  // namespace ddd

@@ -116,20 +116,19 @@ WideStepArgs wide_args(const ddd_ctx* c, const BeamArgs& beam) {
   w.do_select = 0;
   w.do_stop = 0;
   w.steps_done = 0;
-  w.call_count = nullptr;
-  w.progress = nullptr;
-  w.round_tag = 0;
+  w.report = CallReport{};
   return w;
 }
 
-// MFMA GEMM over the rows listed in the context's row list, logits into `out` (row pitch ldl).
-int enqueue_gemm(ddd_ctx* c, const void* W, const void* hid, int max_rows, float* out, int ldl, int reverse, hipStream_t s) {
+// MFMA GEMM over the rows listed in the context's row list, or over all max_rows of them, logits into `out` (row pitch ldl).
+int enqueue_gemm(ddd_ctx* c, const void* W, const void* hid, int max_rows, bool all_rows, float* out, int ldl, int reverse, hipStream_t s) {
   GemmArgs g;
   g.W = static_cast<const uint16_t*>(W);
   g.Wp = (c->pack_src != nullptr && c->pack_src == W) ? c->pack : nullptr;
   g.hid = static_cast<const uint16_t*>(hid);
-  g.row_list = c->row_list;
+  g.row_list = all_rows ? nullptr : c->row_list;
   g.n_act_ptr = c->n_act;
+  g.n_rows = max_rows;
   g.logits = out;
   g.grp_max = c->grp_max;
   g.grp_sum = c->grp_sum;
@@ -153,14 +152,26 @@ int slices_for(const ddd_ctx* c, int n_rows) { return gemm_path(c, n_rows) ? 0 :
 
 // LM head over n_rows rows, partials into the context scratch: the weight stream for up to
 // DDD_STREAM_ROWS rows, the MFMA GEMM over the compacted active rows otherwise.
-// list_ready: the previous call's bookkeeping launch has already written the list of active rows (GEMM path).
+// GEMM path: `list` says where its list of active rows comes from, and with `out` the row reduction leaves the results
+// in the caller's form (topk_token, topk_logprob, lse) instead of the context scratch.
+enum RowListSource {
+  kListBuild,   // built here from row_active
+  kListReady,   // the previous call's bookkeeping launch has written it
+  kListAll      // none needed: every row is active (no flags, or the first call behind a reset)
+};
+struct LmheadOut {
+  int32_t* topk_token;
+  float* topk_logprob;
+  float* lse;
+};
 int enqueue_stream(ddd_ctx* c, const void* W, const void* hid, int n_rows, const uint8_t* row_active, float* logits_dbg,
-                   int reverse, hipStream_t s, bool list_ready = false, int trace_step = -1, bool eager_loads = false) {
+                   int reverse, hipStream_t s, RowListSource list, int trace_step = -1, bool eager_loads = false,
+                   const LmheadOut* results = nullptr) {
   if (gemm_path(c, n_rows)) {
     float* out = logits_dbg ? logits_dbg : c->logits;
     const int ldl = logits_dbg ? c->cfg.V : c->ldl;
-    if (!list_ready) DDD_HIP(launch_build_row_list(row_active, n_rows, c->row_list, c->n_act, s));
-    int rc = enqueue_gemm(c, W, hid, n_rows, out, ldl, reverse, s);
+    if (list == kListBuild) DDD_HIP(launch_build_row_list(row_active, n_rows, c->row_list, c->n_act, s));
+    int rc = enqueue_gemm(c, W, hid, n_rows, list == kListAll, out, ldl, reverse, s);
     if (rc != DDD_OK) return rc;
     RowTopkArgs t;
     t.logits = out;
@@ -171,6 +182,9 @@ int enqueue_stream(ddd_ctx* c, const void* W, const void* hid, int n_rows, const
     t.row_active = row_active;
     t.part_key = c->part_key;
     t.part_sum = c->part_sum;
+    t.topk_token = results ? results->topk_token : nullptr;
+    t.topk_logprob = results ? results->topk_logprob : nullptr;
+    t.lse = results ? results->lse : nullptr;
     t.n_rows = n_rows;
     t.V = c->cfg.V;
     t.k = c->cfg.k;
@@ -462,7 +476,6 @@ int ddd_profile_lmhead(ddd_ctx* c, const void* W, const void* hid, int32_t n_row
   if (n_rows < 1 || n_rows > c->cfg.B * c->cfg.k || iters < 1 || iters > 4096) return DDD_ERR_INVALID_ARG;
   hipStream_t s = static_cast<hipStream_t>(stream);
   const bool gemm = gemm_path(c, n_rows);
-  if (gemm) DDD_HIP(launch_build_row_list(nullptr, n_rows, c->row_list, c->n_act, s));
   std::vector<hipEvent_t> ev(2 * (size_t)iters, nullptr);
   int rc = DDD_OK;
   for (size_t i = 0; i < ev.size() && rc == DDD_OK; ++i)
@@ -470,7 +483,8 @@ int ddd_profile_lmhead(ddd_ctx* c, const void* W, const void* hid, int32_t n_row
   for (int i = 0; i < iters && rc == DDD_OK; ++i) {
     if (hipEventRecord(ev[2 * i], s) != hipSuccess) rc = DDD_ERR_HIP;
     if (rc == DDD_OK)
-      rc = gemm ? enqueue_gemm(c, W, hid, n_rows, c->logits, c->ldl, i & 1, s) : enqueue_stream(c, W, hid, n_rows, nullptr, nullptr, i & 1, s);
+      rc = gemm ? enqueue_gemm(c, W, hid, n_rows, true, c->logits, c->ldl, i & 1, s)
+                : enqueue_stream(c, W, hid, n_rows, nullptr, nullptr, i & 1, s, kListAll);
     if (rc == DDD_OK && hipEventRecord(ev[2 * i + 1], s) != hipSuccess) rc = DDD_ERR_HIP;
   }
   if (rc == DDD_OK && hipEventSynchronize(ev[2 * (size_t)iters - 1]) != hipSuccess) rc = DDD_ERR_HIP;
@@ -552,8 +566,9 @@ int ddd_lmhead_topk(ddd_ctx* c, const void* W, const void* hid, int32_t n_rows, 
     return DDD_ERR_INVALID_ARG;
   if (n_rows < 1 || n_rows > c->cfg.B * c->cfg.k) return DDD_ERR_INVALID_ARG;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  int rc = enqueue_stream(c, W, hid, n_rows, row_active, logits_dbg, 0, s);
-  if (rc != DDD_OK) return rc;
+  const LmheadOut out = {topk_token, topk_logprob, lse};
+  int rc = enqueue_stream(c, W, hid, n_rows, row_active, logits_dbg, 0, s, row_active ? kListBuild : kListAll, -1, false, &out);
+  if (rc != DDD_OK || gemm_path(c, n_rows)) return rc;
   MergeArgs m;
   m.part_key = c->part_key;
   m.part_sum = c->part_sum;
@@ -562,7 +577,7 @@ int ddd_lmhead_topk(ddd_ctx* c, const void* W, const void* hid, int32_t n_rows, 
   m.topk_logprob = topk_logprob;
   m.lse = lse;
   m.n_rows = n_rows;
-  m.nslice = slices_for(c, n_rows);
+  m.nslice = c->nslice;
   m.k = c->cfg.k;
   DDD_HIP(launch_merge(m, s));
   return DDD_OK;
@@ -627,17 +642,19 @@ int draft_step(ddd_ctx* c, int32_t step, const void* W, const void* hid, ddd_sta
     std::memset(&a.tree, 0, sizeof(a.tree));
   a.nslice = slices_for(c, n_rows);
   a.m = c->cfg.m;
-  // rows of the calls after the prompt call go through the GEMM path and beams are narrow: the lists chain
-  const bool chain = in_round && c->cfg.k <= DDD_KMAX && gemm_path(c, c->cfg.B * c->cfg.k);
-  a.call_count = (publish || chain) ? c->call_count + step : nullptr;
-  a.progress = publish ? c->progress_dev + step : nullptr;
-  a.round_tag = c->round_tag;
-  a.active_mask = chain ? c->active_mask : nullptr;
-  a.next_row_list = c->row_list;
-  a.next_n_act = c->n_act;
+  // rows of the calls after the prompt call go through the GEMM path: the lists chain
+  const bool chain = in_round && gemm_path(c, c->cfg.B * c->cfg.k);
+  a.report.call_count = (publish || chain) ? c->call_count + step : nullptr;
+  a.report.progress = publish ? c->progress_dev + step : nullptr;
+  a.report.round_tag = c->round_tag;
+  a.report.active_mask = chain ? c->active_mask : nullptr;
+  a.report.next_row_list = c->row_list;
+  a.report.next_n_act = c->n_act;
   a.trace = c->trace ? c->trace + (size_t)step * kTraceCallWords + DDD_STATIC_SLICES * kTraceStreamWords : nullptr;
+  // a round's first call comes right behind the reset: every sequence drafts
+  const RowListSource list = (in_round && step == 0) ? kListAll : chain ? kListReady : kListBuild;
   // publish = the host-paced round: it queues at most one call per round that every sequence skips
-  int rc = enqueue_stream(c, W, hid, n_rows, flags, logits_dbg, step & 1, s, chain && step >= 1, step, publish);
+  int rc = enqueue_stream(c, W, hid, n_rows, flags, logits_dbg, step & 1, s, list, step, publish);
   if (rc != DDD_OK) return rc;
   if (c->cfg.k > DDD_KMAX) {
     WideStepArgs w = wide_args(c, a.beam);
@@ -647,9 +664,7 @@ int draft_step(ddd_ctx* c, int32_t step, const void* W, const void* hid, ddd_sta
     w.tree = a.tree;
     w.do_select = 1;
     w.do_stop = 1;
-    w.call_count = publish ? c->call_count + step : nullptr;
-    w.progress = publish ? c->progress_dev + step : nullptr;
-    w.round_tag = c->round_tag;
+    w.report = a.report;
     DDD_HIP(launch_step_wide(w, s));
     return DDD_OK;
   }

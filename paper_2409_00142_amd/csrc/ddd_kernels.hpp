@@ -20,8 +20,9 @@ struct GemmArgs {
   const uint16_t* W;          // bf16 [V,H]
   const uint16_t* Wp;         // null, or the tile-major copy of W written by launch_pack_weights
   const uint16_t* hid;        // bf16 [rows,H]
-  const int32_t* row_list;    // [n_act] ids of the active rows, ascending
-  const int32_t* n_act_ptr;   // device scalar
+  const int32_t* row_list;    // [n_act] ids of the active rows, ascending, or null: rows 0 .. n_rows - 1, all of them
+  const int32_t* n_act_ptr;   // device scalar (with row_list)
+  int n_rows;                 // rows of the call (without row_list)
   float* logits;              // fp32 [rows][ldl]: written for the active rows (columns V .. ldl - 1 hold no logits)
   float* grp_max;             // fp32 [rows][ngrp]: max of each group of 64 consecutive vocabulary rows ...
   float* grp_sum;             // fp32 [rows][ngrp]: ... and sum of exp(logit - that max); ngrp = ceil(V/64) rounded up to 4
@@ -63,12 +64,14 @@ struct RowTopkArgs {
   const uint8_t* row_active;  // [n_rows] or null
   uint64_t* part_key;         // [n_rows][k]
   float* part_sum;            // [n_rows]
+  int32_t* topk_token;        // null, or [n_rows][k]: the results in the caller's form (part_key and part_sum are not
+  float* topk_logprob;        // [n_rows][k]            written then): tokens, logit - lse,
+  float* lse;                 // [n_rows]               and lse
   int n_rows, V, k, ngrp, ldl;
 };
 hipError_t launch_row_topk(const RowTopkArgs& a, hipStream_t stream);
 
 // ---- per-row merge, beam select, stop test (bookkeep.hip) -------------------------------------
-// nslice == 0 selects the dense format above (nothing to merge).
 struct MergeArgs {
   const uint64_t* part_key;   // [n_rows][k][nslice]: rank j of every slice together (the merge reads ranks 0..2)
   const float* part_sum;      // [n_rows][nslice]
@@ -91,6 +94,16 @@ struct BeamArgs {
 hipError_t launch_beam_select(const BeamArgs& a, hipStream_t stream);
 hipError_t launch_depth_continue(const BeamArgs& a, int steps_done, hipStream_t stream);
 
+// What the last workgroup of a bookkeeping launch leaves behind, once every sequence of the call has been looked at.
+struct CallReport {
+  uint32_t* call_count;       // null (no report), or this call's arrival word (device): the last workgroup to arrive ...
+  uint32_t* progress;         //   ... reports (round_tag << 2) | 2 | (some sequence still active) to this word in host
+  uint32_t round_tag;         //       memory (if progress is not null), and
+  uint64_t* active_mask;      //   ... if not null ([ceil(B/64)] device words, zero between calls: bit b = sequence b goes
+  int32_t* next_row_list;     //       on) writes the next call's list of active rows b*k+i, ascending, and their
+  int32_t* next_n_act;        //       number: what build_row_list_kernel would make of row_active after this launch
+};
+
 struct StepArgs {             // merge + beam select + stop test in one launch
   BeamArgs beam;              // topk_* unused
   const uint64_t* part_key;   // [B*k][k][nslice]
@@ -98,12 +111,7 @@ struct StepArgs {             // merge + beam select + stop test in one launch
   float* lse_dbg;             // [B*k] or null: lse of every merged row
   ddd_tree tree;              // tree.mask == null: do not build the final tree here
   int nslice, m;
-  uint32_t* call_count;       // null, or this call's arrival word (device): the last workgroup to arrive ...
-  uint32_t* progress;         //   ... reports (round_tag << 2) | 2 | (some sequence still active) to this word in host
-  uint32_t round_tag;         //       memory (if progress is not null), and
-  uint64_t* active_mask;      //   ... if not null ([ceil(B/64)] device words, zero between calls: bit b = sequence b goes
-  int32_t* next_row_list;     //       on) writes the next call's list of active rows b*k+i, ascending, and their
-  int32_t* next_n_act;        //       number: what build_row_list_kernel would make of row_active after this launch
+  CallReport report;
   uint64_t* trace;            // null, or [kTraceStepWords] device words: wall-clock stamps of workgroup 0's phases
 };
 hipError_t launch_step_bookkeep(const StepArgs& a, hipStream_t stream);
@@ -138,9 +146,7 @@ struct WideStepArgs {
   int do_select;              // run the beam update
   int do_stop;                // run the stop test (steps_done = beam.step + 1 after a beam update)
   int steps_done;             // draft calls made so far, for a stop test without a beam update
-  uint32_t* call_count;       // null, or this call's arrival word: the last workgroup to arrive reports
-  uint32_t* progress;         //   (round_tag << 2) | 2 | (some sequence still active) to this word in host memory
-  uint32_t round_tag;
+  CallReport report;
 };
 hipError_t prepare_wide();    // once per process: enables the kernels' LDS sizes
 hipError_t launch_step_wide(const WideStepArgs& a, hipStream_t stream);

@@ -55,6 +55,9 @@ struct GemmCfg {
   static_assert(kSB <= kSA && kLdsBytes <= 160 * 1024, "ring depths");
 };
 
+// Row of the n-th active row of the call.
+__device__ __forceinline__ int row_id(const GemmArgs& a, int n) { return a.row_list != nullptr ? a.row_list[n] : n; }
+
 // One work unit of one wave.  The column tile starts at active row tile_col0; this wave multiplies
 // NB blocks of 32 rows from block wblk0 of the tile on (0 <= NB <= BB; a wave with NB == 0 still
 // copies tiles and meets the barriers).  Every value of NB has its own fully unrolled loop, so the
@@ -98,7 +101,7 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, unsigned char* ldsb
   }
 #pragma unroll
   for (int i = 0; i < NBP; ++i)
-    bo[i] = ((uint32_t)a.row_list[min(tile_col0 + (i * 4 + wave) * 8 + prow, n_act - 1)] * (uint32_t)a.H + pc * 8) * 2u;
+    bo[i] = ((uint32_t)row_id(a, min(tile_col0 + (i * 4 + wave) * 8 + prow, n_act - 1)) * (uint32_t)a.H + pc * 8) * 2u;
   typedef const __attribute__((address_space(1))) void* gptr_t;
   typedef __attribute__((address_space(3))) void* lptr_t;
   const unsigned char* Hb = reinterpret_cast<const unsigned char*>(a.hid);
@@ -228,7 +231,7 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, unsigned char* ldsb
     for (int bn = 0; bn < NBR; ++bn) {
       const int n = col0 + bn * 32 + l32;
       if (n >= n_act) continue;
-      const int orow_id = a.row_list[n];
+      const int orow_id = row_id(a, n);
       float* orow = a.logits + (size_t)orow_id * a.ldl;
       uint16_t* o16 = a.out16 ? a.out16 + (size_t)orow_id * a.ld16 : nullptr;
       uint16_t* o16b = a.out16b ? a.out16b + (size_t)orow_id * a.ld16 : nullptr;
@@ -286,7 +289,7 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, unsigned char* ldsb
       gs[gp] += __shfl_xor(gs[gp], 32, 64);
     }
     if (n < n_act) {
-      const int orow_id = a.row_list[n];
+      const int orow_id = row_id(a, n);
       if (lh == 0) {
 #pragma unroll
         for (int gp = 0; gp < NGW; ++gp)
@@ -357,7 +360,7 @@ template <int AB, int BB>
 __global__ __launch_bounds__(256, 1) void lmhead_gemm_kernel(GemmArgs a) {
   extern __shared__ __align__(16) unsigned char lds[];     // the two tile rings of the chosen width
 
-  const int n_act = *a.n_act_ptr;
+  const int n_act = a.row_list != nullptr ? *a.n_act_ptr : a.n_rows;
   if (n_act <= 0) return;                                  // uniform
   const int nblk_all = (n_act + 31) >> 5;
   const int NT = (nblk_all + 2 * BB - 1) / (2 * BB);

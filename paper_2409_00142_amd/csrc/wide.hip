@@ -426,17 +426,7 @@ __device__ __forceinline__ bool step_wide_block(const WideStepArgs& a, unsigned 
 __global__ __launch_bounds__(kWideThreads) void step_wide_kernel(WideStepArgs a) {
   extern __shared__ __align__(16) unsigned char wsm_raw[];
   const bool active = step_wide_block(a, wsm_raw);
-  if (a.call_count != nullptr && threadIdx.x == 0) {
-    // report to the host that paces the round (see step_bookkeep_kernel): one atomic per sequence, arrivals in
-    // the low half, active sequences in the high half; the last arrival clears the word and writes the host word
-    const uint32_t mine = 1u | (active ? 0x10000u : 0u);
-    const uint32_t seen = __hip_atomic_fetch_add(a.call_count, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if ((seen & 0xFFFFu) + 1u == gridDim.x) {
-      __hip_atomic_store(a.call_count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const uint32_t any = ((seen + mine) >> 16) != 0u ? 1u : 0u;
-      __hip_atomic_store(a.progress, (a.round_tag << 2) | 2u | any, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    }
-  }
+  report_call(a.report, active, blockIdx.x, a.beam.k, threadIdx.x, blockDim.x);
 }
 
 __global__ __launch_bounds__(kWideThreads) void tree_finalize_wide_kernel(FinalizeArgs a) {
