@@ -19,6 +19,7 @@
 // Rows of stopped sequences are skipped; a launch whose rows are all inactive exits at once.
 #include "body_kernels.hpp"
 #include "ddd_device.hpp"
+#include "gemm_plan.hpp"
 #include "stream_tile.hpp"
 
 namespace ddd {
@@ -209,6 +210,118 @@ hipError_t launch_rmsnorm(const RmsNormArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
+// ---- partial sums of a split product added up by their reader --------------------------------------------------
+// What a thread needs to read the sums: every value is a few independent loads whose lines lie n_act * N floats apart.
+struct SumsView {
+  const float* part;
+  size_t stride;   // floats between two K ranges
+  int N, S;
+};
+__device__ __forceinline__ int sums_rows(const SplitSums& a) { return a.n_act_ptr != nullptr ? *a.n_act_ptr : a.n_rows; }
+// Called by all 64 lanes of a wave.
+__device__ __forceinline__ SumsView sums_view(const SplitSums& a, int n_act, int lane) {
+  const GemmPlan p = gemm_plan(a.shape, n_act, lane);
+  return SumsView{a.part, (size_t)n_act * a.shape.N, a.shape.N, p.S};
+}
+__device__ __forceinline__ f32x4 sums_at4(const SumsView& v, int n, int col) {   // in the order of the ranges
+  const float* p = v.part + (size_t)n * v.N + col;
+  f32x4 t[8];
+#pragma unroll
+  for (int s = 0; s < 8; ++s)
+    t[s] = s < v.S ? *reinterpret_cast<const f32x4*>(p + s * v.stride) : f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4 y = t[0];
+#pragma unroll
+  for (int s = 1; s < 8; ++s)
+    if (s < v.S) y += t[s];
+  return y;
+}
+__device__ __forceinline__ float sums_at(const SumsView& v, int n, int col) {
+  const float* p = v.part + (size_t)n * v.N + col;
+  float t[8];
+#pragma unroll
+  for (int s = 0; s < 8; ++s) t[s] = s < v.S ? p[s * v.stride] : 0.f;
+  float y = t[0];
+#pragma unroll
+  for (int s = 1; s < 8; ++s)
+    if (s < v.S) y += t[s];
+  return y;
+}
+
+// The residual stream behind a split product, and its norm: one workgroup per active row, 16 bytes per load.  Reads
+// 4 * (ranges + 1) bytes per element once; the separate accumulating epilogue and norm read and wrote them twice.
+__global__ __launch_bounds__(512) void sum_rmsnorm_kernel(SumRmsNormArgs a) {
+  __shared__ float part[8];
+  const int n = blockIdx.x, tid = threadIdx.x;
+  const int n_act = sums_rows(a.sums);
+  if (n >= n_act) return;                                        // uniform over the block
+  const int r = a.row_list != nullptr ? a.row_list[n] : n;
+  const SumsView v = sums_view(a.sums, n_act, tid & 63);
+  float* x = a.x + (size_t)r * a.H;
+  f32x4 xv[3];                                                   // H <= 5120, a multiple of 128
+  float ss = 0.f;
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+    const int i = (tid + 512 * j) * 4;
+    xv[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (i < a.H) {
+      const f32x4 s = sums_at4(v, n, i);
+      xv[j] = a.add ? *reinterpret_cast<const f32x4*>(x + i) + s : s;
+      *reinterpret_cast<f32x4*>(x + i) = xv[j];
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) ss += xv[j][e] * xv[j][e];
+  }
+  ss = wave_sum_f32(ss);
+  if ((tid & 63) == 0) part[tid >> 6] = ss;
+  __syncthreads();
+  float tot = 0.f;
+#pragma unroll
+  for (int w = 0; w < 8; ++w) tot += part[w];                   // fixed order
+  const float inv = 1.0f / sqrtf(tot / (float)a.H + 1e-6f);
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+    const int i = (tid + 512 * j) * 4;
+    if (i < a.H) {
+      const f32x4 g = *reinterpret_cast<const f32x4*>(a.g + i);
+      uint32_t o[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = f32_to_bf16_rne(xv[j][e] * inv * g[e]);
+      *reinterpret_cast<uint2*>(a.out + (size_t)r * a.H + i) = make_uint2(o[0] | (o[1] << 16), o[2] | (o[3] << 16));
+    }
+  }
+}
+
+hipError_t launch_sum_rmsnorm(const SumRmsNormArgs& a, hipStream_t stream) {
+  if (a.H > 3 * 512 * 4) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(sum_rmsnorm_kernel, dim3(a.R), dim3(512), 0, stream, a);
+  return hipGetLastError();
+}
+
+__global__ __launch_bounds__(256) void sum_rows_kernel(SumRowsArgs a) {
+  const int n = blockIdx.x, tid = threadIdx.x;
+  const int n_act = sums_rows(a.sums);
+  if (n >= n_act) return;                                        // uniform over the block
+  const int r = a.row_list != nullptr ? a.row_list[n] : n;
+  const SumsView v = sums_view(a.sums, n_act, tid & 63);
+  for (int i = tid * 4; i < v.N; i += 256 * 4) {                 // N is a multiple of 4
+    f32x4 y = sums_at4(v, n, i);
+    float* yp = a.y + (size_t)r * v.N + i;
+    if (a.add) y = *reinterpret_cast<const f32x4*>(yp) + y;
+    if (a.store) *reinterpret_cast<f32x4*>(yp) = y;
+    if (a.out16 != nullptr) {
+      const uint2 o = make_uint2(f32_to_bf16_rne(y[0]) | ((uint32_t)f32_to_bf16_rne(y[1]) << 16),
+                                 f32_to_bf16_rne(y[2]) | ((uint32_t)f32_to_bf16_rne(y[3]) << 16));
+      *reinterpret_cast<uint2*>(a.out16 + (size_t)r * v.N + i) = o;
+      if (a.out16b != nullptr) *reinterpret_cast<uint2*>(a.out16b + (size_t)r * v.N + i) = o;
+    }
+  }
+}
+
+hipError_t launch_sum_rows(const SumRowsArgs& a, hipStream_t stream) {
+  hipLaunchKernelGGL(sum_rows_kernel, dim3(a.R), dim3(256), 0, stream, a);
+  return hipGetLastError();
+}
+
 // ---- RoPE + key/value store + tree attention: one workgroup of 16 waves per (row, head) ----------
 // Every phase is a few dependent memory round trips deep at most: keys are dealt one per thread,
 // values to 8 groups of 128 threads (one per element of the head).
@@ -235,6 +348,29 @@ __device__ __forceinline__ float block_sum_f32(float x, float* red, int tid) {
   return s;
 }
 
+__device__ __forceinline__ SumsView qkv_view(const BodyAttnArgs& a, int lane) {   // by all 64 lanes of a wave
+  return a.sums.part != nullptr ? sums_view(a.sums, sums_rows(a.sums), lane) : SumsView{nullptr, 0, 0, 0};
+}
+// Elements p and p + 64 of the query, key and value of row r, head h.
+__device__ __forceinline__ void load_qkv_pair(const BodyAttnArgs& a, const SumsView& v, int r, int h, int p, float& q0, float& q1, float& k0,
+                                              float& k1, float& v0, float& v1) {
+  const int c = h * kHeadDim + p;
+  if (a.sums.part != nullptr) {                                  // uniform: a split product, added up here
+    const int n = a.row_pos != nullptr ? a.row_pos[r] : r;
+    q0 = sums_at(v, n, c);
+    q1 = sums_at(v, n, c + 64);
+    k0 = sums_at(v, n, a.H + c);
+    k1 = sums_at(v, n, a.H + c + 64);
+    v0 = sums_at(v, n, 2 * a.H + c);
+    v1 = sums_at(v, n, 2 * a.H + c + 64);
+    return;
+  }
+  const float* row = a.qkv + (size_t)r * 3 * a.H + c;
+  q0 = row[0], q1 = row[64];
+  k0 = row[a.H], k1 = row[a.H + 64];
+  v0 = row[2 * a.H], v1 = row[2 * a.H + 64];
+}
+
 __global__ __launch_bounds__(kAttnThreads) void body_attention_kernel(BodyAttnArgs a) {
   extern __shared__ __align__(16) float sm[];
   const int nh = a.H / kHeadDim;
@@ -242,6 +378,7 @@ __global__ __launch_bounds__(kAttnThreads) void body_attention_kernel(BodyAttnAr
   if (a.row_active != nullptr && a.row_active[r] == 0) return;   // uniform
   const int b = (a.step == 0) ? r : r / a.k;
   const int n_vis = a.L + a.step + 1;
+  const SumsView sv = qkv_view(a, tid & 63);
   float* qs = sm;                  // [128] rotated query
   float* ks = sm + 128;            // [128] own key as stored (bf16 values)
   float* vs = sm + 256;            // [128] own value as stored
@@ -255,10 +392,8 @@ __global__ __launch_bounds__(kAttnThreads) void body_attention_kernel(BodyAttnAr
     const float inv_freq = exp2f(-(float)(2 * tid) / (float)kHeadDim * 13.287712379549449f);   // log2(10000)
     float sn, cs;
     sincosf((float)(a.L + a.step) * inv_freq, &sn, &cs);
-    const float* row = a.qkv + (size_t)r * 3 * a.H + h * kHeadDim;
-    const float q0 = row[tid], q1 = row[tid + 64];
-    const float k0 = row[a.H + tid], k1 = row[a.H + tid + 64];
-    const float v0 = row[2 * a.H + tid], v1 = row[2 * a.H + tid + 64];
+    float q0, q1, k0, k1, v0, v1;
+    load_qkv_pair(a, sv, r, h, tid, q0, q1, k0, k1, v0, v1);
     qs[tid] = q0 * cs - q1 * sn;
     qs[tid + 64] = q1 * cs + q0 * sn;
     const uint16_t kb0 = f32_to_bf16_rne(k0 * cs - k1 * sn), kb1 = f32_to_bf16_rne(k1 * cs + k0 * sn);
@@ -351,6 +486,28 @@ __global__ __launch_bounds__(kAttnThreads) void body_attention_kernel(BodyAttnAr
 // ---- rows of [E[token], parent feature] for the GEMM path: one workgroup per row ------------------------------
 __global__ __launch_bounds__(256) void pack_x0_kernel(PackX0Args a) {
   const int r = blockIdx.x, tid = threadIdx.x;
+  if (r == a.R) {   // one more workgroup beside the rows' (with row_active): the list of active rows
+    __shared__ int cnt[4];
+    const int lane = tid & 63, wave = tid >> 6;
+    int base = 0;
+    for (int r0 = 0; r0 < a.R; r0 += 256) {
+      const int q = r0 + tid;
+      const bool on = q < a.R && a.row_active[q] != 0;
+      const unsigned long long m = __ballot(on);
+      if (lane == 0) cnt[wave] = __popcll(m);
+      __syncthreads();
+      int pos = base + __popcll(m & ((1ull << lane) - 1ull));
+      for (int w = 0; w < wave; ++w) pos += cnt[w];
+      if (on) {
+        a.row_list[pos] = q;
+        a.row_pos[q] = pos;
+      }
+      base += cnt[0] + cnt[1] + cnt[2] + cnt[3];
+      __syncthreads();                                           // the counts are used again
+    }
+    if (tid == 0) *a.n_act = base;
+    return;
+  }
   if (a.row_active != nullptr && a.row_active[r] == 0) return;   // uniform
   int fr = r;
   if (a.feat_mode == kGatherBlock) fr = r / a.k;
@@ -366,7 +523,7 @@ __global__ __launch_bounds__(256) void pack_x0_kernel(PackX0Args a) {
 }
 
 hipError_t launch_pack_x0(const PackX0Args& a, hipStream_t stream) {
-  hipLaunchKernelGGL(pack_x0_kernel, dim3(a.R), dim3(256), 0, stream, a);
+  hipLaunchKernelGGL(pack_x0_kernel, dim3(a.R + (a.row_active != nullptr ? 1 : 0)), dim3(256), 0, stream, a);
   return hipGetLastError();
 }
 
@@ -387,6 +544,7 @@ __global__ __launch_bounds__(kSeqThreads) void body_attention_seq_kernel(BodyAtt
   const int kk = (a.step == 0) ? 1 : a.k;                 // rows of this sequence
   const int r0 = (a.step == 0) ? b : b * a.k;
   if (a.row_active != nullptr && a.row_active[r0] == 0) return;   // uniform: a sequence's rows share their flag
+  const SumsView sv = qkv_view(a, tid & 63);
   const int n_vis = a.L + a.step + 1;
   float* qs = sm;                                  // [kSeqRows][128] rotated queries
   float* ks = qs + kSeqRows * kHeadDim;            // [kSeqRows][128] own keys as stored (bf16 values)
@@ -402,10 +560,8 @@ __global__ __launch_bounds__(kSeqThreads) void body_attention_seq_kernel(BodyAtt
     const float inv_freq = exp2f(-(float)(2 * p) / (float)kHeadDim * 13.287712379549449f);   // log2(10000)
     float sn, cs;
     sincosf((float)(a.L + a.step) * inv_freq, &sn, &cs);
-    const float* row = a.qkv + (size_t)r * 3 * a.H + h * kHeadDim;
-    const float q0 = row[p], q1 = row[p + 64];
-    const float k0 = row[a.H + p], k1 = row[a.H + p + 64];
-    const float v0 = row[2 * a.H + p], v1 = row[2 * a.H + p + 64];
+    float q0, q1, k0, k1, v0, v1;
+    load_qkv_pair(a, sv, r, h, p, q0, q1, k0, k1, v0, v1);
     qs[i * kHeadDim + p] = q0 * cs - q1 * sn;
     qs[i * kHeadDim + p + 64] = q1 * cs + q0 * sn;
     const uint16_t kb0 = f32_to_bf16_rne(k0 * cs - k1 * sn), kb1 = f32_to_bf16_rne(k1 * cs + k0 * sn);
@@ -588,6 +744,7 @@ __global__ __launch_bounds__(kMfThreads) void body_attention_mfma_kernel(BodyAtt
   const int kk = (a.step == 0) ? 1 : a.k;                 // rows of this sequence
   const int r0 = (a.step == 0) ? b : b * a.k;
   if (a.row_active != nullptr && a.row_active[r0] == 0) return;   // uniform: a sequence's rows share their flag
+  const SumsView sv = qkv_view(a, tid & 63);
   const int L = a.L, Lp = a.Lp, n_vis = L + a.step + 1;
   const int ppitch = Lp + 8;
   float* qs = reinterpret_cast<float*>(smb);        // [kSeqRows][128] rotated queries; later the prompt's part of the outputs
@@ -619,10 +776,8 @@ __global__ __launch_bounds__(kMfThreads) void body_attention_mfma_kernel(BodyAtt
     const float inv_freq = exp2f(-(float)(2 * p) / (float)kHeadDim * 13.287712379549449f);   // log2(10000)
     float sn, cs;
     sincosf((float)(L + a.step) * inv_freq, &sn, &cs);
-    const float* row = a.qkv + (size_t)r * 3 * a.H + h * kHeadDim;
-    const float q0 = row[p], q1 = row[p + 64];
-    const float k0 = row[a.H + p], k1 = row[a.H + p + 64];
-    const float v0 = row[2 * a.H + p], v1 = row[2 * a.H + p + 64];
+    float q0, q1, k0, k1, v0, v1;
+    load_qkv_pair(a, sv, r, h, p, q0, q1, k0, k1, v0, v1);
     qs[i * kHeadDim + p] = q0 * cs - q1 * sn;
     qs[i * kHeadDim + p + 64] = q1 * cs + q0 * sn;
     const uint16_t kb0 = f32_to_bf16_rne(k0 * cs - k1 * sn), kb1 = f32_to_bf16_rne(k1 * cs + k0 * sn);

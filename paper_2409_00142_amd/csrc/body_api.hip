@@ -28,6 +28,9 @@ struct ddd_body {
   // calls of more than kBodyRows rows go through the MFMA GEMM:
   uint16_t* x0;      // bf16 [rows][2H]  FC input rows, assembled (null if rows <= kBodyRows)
   int32_t* row_list; // [rows] ids of the active rows of the current call
+  int32_t* row_pos;  // [rows] every active row's position in row_list
+  float* part;       // fp32 [part_cap] partial sums of the split product in flight
+  long long part_cap;
   int32_t* n_act;    // [1]
   uint16_t* vt;      // bf16 [B][H][Lp] the prompt's values, keys contiguous (null if rows <= kBodyRows or L < 32);
   int Lp;            //   rewritten by the prompt call of every round
@@ -104,10 +107,23 @@ int enqueue_linear_ranges(const ddd_body* b, LinearArgs a, int K_range, hipStrea
   return DDD_OK;
 }
 
-// y (+)= x W^T over the rows in b->row_list, or over all n_rows of them, through the MFMA GEMM (calls of more than
-// kBodyRows rows).
-int enqueue_gemm_linear(const ddd_body* b, int n_rows, bool all_rows, const void* W, int N, int K, const uint16_t* x, float* y, int epi,
-                        uint16_t* out16, uint16_t* out16b, int ld16, hipStream_t s) {
+// The shape of a linear for calls of up to b->rows rows; smax: most K ranges its product may be split into.
+SplitShape split_shape(const ddd_body* b, int N, int K, int smax) {
+  SplitShape g;
+  g.bbmax = gemm_linear_bbmax(b->rows);
+  g.nmt = (N + 127) / 128;
+  g.kt = K / 64;
+  g.N = N;
+  g.grid = ((b->n_cu + 7) / 8) * 8;
+  g.smax = smax;
+  g.cap = b->part_cap;
+  return g;
+}
+
+// y = x W^T over the rows in b->row_list, or over all n_rows of them, through the MFMA GEMM (calls of more than
+// kBodyRows rows): partial sums in b->part (kGemmPartial), activations in out16 (kGemmSiluPairs), or in y.
+int enqueue_gemm_linear(const ddd_body* b, int n_rows, bool all_rows, const void* W, int N, int K, const uint16_t* x, float* y,
+                        int epi, uint16_t* out16, int ld16, hipStream_t s) {
   GemmArgs g;
   g.W = static_cast<const uint16_t*>(W);
   g.Wp = nullptr;
@@ -115,7 +131,7 @@ int enqueue_gemm_linear(const ddd_body* b, int n_rows, bool all_rows, const void
   g.row_list = all_rows ? nullptr : b->row_list;
   g.n_act_ptr = b->n_act;
   g.n_rows = n_rows;
-  g.logits = y;
+  g.logits = epi == kGemmPartial ? b->part : y;
   g.grp_max = nullptr;
   g.grp_sum = nullptr;
   g.H = K;
@@ -125,10 +141,20 @@ int enqueue_gemm_linear(const ddd_body* b, int n_rows, bool all_rows, const void
   g.reverse = 0;
   g.epi = epi;
   g.out16 = out16;
-  g.out16b = out16b;
   g.ld16 = ld16;
-  BODY_HIP(launch_gemm_linear(g, b->rows, ((b->n_cu + 7) / 8) * 8, s));
+  g.split = split_shape(b, N, K, epi == kGemmPartial ? 8 : 1);
+  BODY_HIP(launch_gemm_linear(g, b->rows, g.split.grid, s));
   return DDD_OK;
+}
+
+// How the reader of a kGemmPartial product adds it up.
+SplitSums split_sums(const ddd_body* b, int n_rows, bool all_rows, int N, int K) {
+  SplitSums v;
+  v.part = b->part;
+  v.shape = split_shape(b, N, K, 8);
+  v.n_act_ptr = all_rows ? nullptr : b->n_act;
+  v.n_rows = n_rows;
+  return v;
 }
 
 LinearArgs linear_args(const void* W, int ldw, int N, int R, const uint8_t* row_active, float* y, int ldy, int mode) {
@@ -191,6 +217,11 @@ int ddd_body_create(const ddd_body_config* cfg, ddd_body** out) {
   if (e == hipSuccess && b->rows > kBodyRows) {
     e = hipMalloc(&b->x0, R * 2 * H * sizeof(uint16_t));
     if (e == hipSuccess) e = prepare_lmhead_gemm();
+    if (e == hipSuccess) e = hipMalloc(&b->row_pos, R * sizeof(int32_t));
+    // room for the layer's products unsplit, and for one tile of every workgroup: a split fills the chip once
+    const long long grid = ((b->n_cu + 7) / 8) * 8, tile = 128LL * 64 * gemm_linear_bbmax(b->rows);
+    b->part_cap = (long long)R * 3 * H > grid * tile ? (long long)R * 3 * H : grid * tile;
+    if (e == hipSuccess) e = hipMalloc(&b->part, (size_t)b->part_cap * sizeof(float));
     b->Lp = (cfg->L + 31) & ~31;
     if (e == hipSuccess && cfg->L >= 32) e = hipMalloc(&b->vt, (size_t)cfg->B * H * b->Lp * sizeof(uint16_t));
   }
@@ -215,6 +246,8 @@ int ddd_body_destroy(ddd_body* b) {
   (void)hipFree(b->x0);
   (void)hipFree(b->vt);
   (void)hipFree(b->row_list);
+  (void)hipFree(b->row_pos);
+  (void)hipFree(b->part);
   (void)hipFree(b->n_act);
   delete b;
   return DDD_OK;
@@ -237,8 +270,22 @@ int ddd_body_linear(ddd_body* b, const void* W, int32_t N, int32_t K, const void
   if (R > kBodyRows) {   // the MFMA path of calls with more rows, all R rows taken as active
     if (R > b->rows || N % 4 != 0) return DDD_ERR_INVALID_ARG;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    return enqueue_gemm_linear(b, R, true, W, N, K, static_cast<const uint16_t*>(x), y, accumulate ? kGemmAccumulate : kGemmStore,
-                               nullptr, nullptr, 0, s);
+    const uint16_t* xr = static_cast<const uint16_t*>(x);
+    if ((long long)R * N > b->part_cap)   // more sums than the layer's own products have: straight to y, K not split
+      return enqueue_gemm_linear(b, R, true, W, N, K, xr, y, accumulate ? kGemmAccumulate : kGemmStore, nullptr, 0, s);
+    int rc = enqueue_gemm_linear(b, R, true, W, N, K, xr, nullptr, kGemmPartial, nullptr, 0, s);
+    if (rc != DDD_OK) return rc;
+    SumRowsArgs f;
+    f.sums = split_sums(b, R, true, N, K);
+    f.row_list = nullptr;
+    f.y = y;
+    f.out16 = nullptr;
+    f.out16b = nullptr;
+    f.R = R;
+    f.add = accumulate ? 1 : 0;
+    f.store = 1;
+    BODY_HIP(launch_sum_rows(f, s));
+    return DDD_OK;
   }
   LinearArgs a = linear_args(W, K, N, R, nullptr, y, N, accumulate ? kLinearAccumulate : kLinearStore);
   a.rg[0].x = static_cast<const uint16_t*>(x);
@@ -271,6 +318,8 @@ int ddd_body_step(void* user, int32_t step, const ddd_state* st, void* hid_out, 
   n1.R = R;
   BodyAttnArgs t;
   t.qkv = b->qkv;
+  t.sums = SplitSums{};
+  t.row_pos = nullptr;
   t.Kp = static_cast<const uint16_t*>(b->p.K);
   t.Vp = static_cast<const uint16_t*>(b->p.V);
   t.k_hist = b->k_hist;
@@ -296,7 +345,7 @@ int ddd_body_step(void* user, int32_t step, const ddd_state* st, void* hid_out, 
     // More than kBodyRows rows: the same sequence of operations with every linear on the matrix cores, over the
     // compacted list of active rows; the FC's input rows are assembled first (the GEMM gathers whole rows).
     const bool all = act == nullptr;
-    if (!all) BODY_HIP(launch_build_row_list(act, R, b->row_list, b->n_act, s));
+    const int32_t* list = all ? nullptr : b->row_list;
     PackX0Args px;
     px.E = static_cast<const uint16_t*>(b->w.E);
     px.token = (step == 0) ? b->p.root_token : st->beam_token;
@@ -304,25 +353,55 @@ int ddd_body_step(void* user, int32_t step, const ddd_state* st, void* hid_out, 
     px.parent_slot = st->beam_parent_slot;
     px.row_active = act;
     px.x0 = b->x0;
+    px.row_list = b->row_list;
+    px.row_pos = b->row_pos;
+    px.n_act = b->n_act;
     px.H = H;
     px.k = b->cfg.k;
     px.R = R;
     px.feat_mode = (step == 0) ? kGatherNone : (step == 1) ? kGatherBlock : kGatherInBlock;
     BODY_HIP(launch_pack_x0(px, s));
-    rc = enqueue_gemm_linear(b, R, all, b->w.Wfc, H, 2 * H, b->x0, b->r, kGemmStore, nullptr, nullptr, 0, s);
+    // r0 and its norm
+    rc = enqueue_gemm_linear(b, R, all, b->w.Wfc, H, 2 * H, b->x0, nullptr, kGemmPartial, nullptr, 0, s);
     if (rc != DDD_OK) return rc;
-    BODY_HIP(launch_rmsnorm(n1, s));
-    rc = enqueue_gemm_linear(b, R, all, b->w.Wqkv, 3 * H, H, b->xn, b->qkv, kGemmStore, nullptr, nullptr, 0, s);
+    SumRmsNormArgs sn;
+    sn.sums = split_sums(b, R, all, H, 2 * H);
+    sn.row_list = list;
+    sn.x = b->r;
+    sn.g = b->w.g1;
+    sn.out = b->xn;
+    sn.H = H;
+    sn.R = R;
+    sn.add = 0;
+    BODY_HIP(launch_sum_rmsnorm(sn, s));
+    rc = enqueue_gemm_linear(b, R, all, b->w.Wqkv, 3 * H, H, b->xn, nullptr, kGemmPartial, nullptr, 0, s);
     if (rc != DDD_OK) return rc;
+    t.sums = split_sums(b, R, all, 3 * H, H);
+    t.row_pos = all ? nullptr : b->row_pos;
     BODY_HIP(launch_body_attention(t, s));
-    rc = enqueue_gemm_linear(b, R, all, b->w.Wo, H, H, b->xn, b->r, kGemmAccumulate, nullptr, nullptr, 0, s);   // r1 = r0 + o Wo^T
+    // r1 = r0 + o Wo^T and its norm
+    rc = enqueue_gemm_linear(b, R, all, b->w.Wo, H, H, b->xn, nullptr, kGemmPartial, nullptr, 0, s);
     if (rc != DDD_OK) return rc;
-    BODY_HIP(launch_rmsnorm(n2, s));
-    rc = enqueue_gemm_linear(b, R, all, b->w.Wgu, 2 * F, H, b->xn, nullptr, kGemmSiluPairs, b->act, nullptr, F, s);
+    sn.sums = split_sums(b, R, all, H, H);
+    sn.g = b->w.g2;
+    sn.add = 1;
+    BODY_HIP(launch_sum_rmsnorm(sn, s));
+    rc = enqueue_gemm_linear(b, R, all, b->w.Wgu, 2 * F, H, b->xn, nullptr, kGemmSiluPairs, b->act, F, s);
     if (rc != DDD_OK) return rc;
     // h = bf16(r1 + a Wd^T), written to the hidden rows and to this call's features
-    return enqueue_gemm_linear(b, R, all, b->w.Wd, H, F, b->act, b->r, kGemmAccumulate, static_cast<uint16_t*>(hid_out),
-                               b->h_hist + hist, H, s);
+    rc = enqueue_gemm_linear(b, R, all, b->w.Wd, H, F, b->act, nullptr, kGemmPartial, nullptr, 0, s);
+    if (rc != DDD_OK) return rc;
+    SumRowsArgs f;
+    f.sums = split_sums(b, R, all, H, F);
+    f.row_list = list;
+    f.y = b->r;
+    f.out16 = static_cast<uint16_t*>(hid_out);
+    f.out16b = b->h_hist + hist;
+    f.R = R;
+    f.add = 1;
+    f.store = 0;
+    BODY_HIP(launch_sum_rows(f, s));
+    return DDD_OK;
   }
 
   // r0 = [E[token], parent feature] Wfc^T: one launch over two K ranges of H, the rows read where they are

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "ddd_kernels.hpp"
+
 namespace ddd {
 
 constexpr int kBodyRows = 16;      // most rows of a call that go through the weight stream (one pass); more: MFMA GEMM
@@ -54,10 +56,34 @@ struct RmsNormArgs {
 };
 hipError_t launch_rmsnorm(const RmsNormArgs& a, hipStream_t stream);
 
+// Calls that go through the MFMA GEMM: x = sum of the partial sums of a split product (+ x with `add`), written back to x,
+// and out as above.  Rows in list order (row_list null: rows 0 .. n_rows - 1).
+struct SumRmsNormArgs {
+  SplitSums sums;
+  const int32_t* row_list;
+  float* x;                   // fp32 [rows][H]
+  const float* g;
+  uint16_t* out;              // bf16 [rows][H]
+  int H, R, add;
+};
+hipError_t launch_sum_rmsnorm(const SumRmsNormArgs& a, hipStream_t stream);
+// y = sum of the partial sums (+ y with `add`): to y (fp32, if `store`), and rounded to out16 and out16b where not null.
+struct SumRowsArgs {
+  SplitSums sums;
+  const int32_t* row_list;
+  float* y;                   // fp32 [rows][N]
+  uint16_t* out16;            // null, or bf16 [rows][N]
+  uint16_t* out16b;           // null, or a second copy
+  int R, add, store;
+};
+hipError_t launch_sum_rows(const SumRowsArgs& a, hipStream_t stream);
+
 // RoPE of q and k at position L + step, k and v stored as bf16, attention of every row over the
 // prompt, its ancestors and itself.
 struct BodyAttnArgs {
-  const float* qkv;           // fp32 [R][3H]
+  const float* qkv;           // fp32 [R][3H]; not read if sums.part is given:
+  SplitSums sums;             //   the partial sums of q, k, v (N = 3H) and, if not null,
+  const int32_t* row_pos;     //   the position of every active row in the list of active rows
   const uint16_t* Kp;         // bf16 [B][L][H] keys of the prompt (as cached)
   const uint16_t* Vp;
   uint16_t* k_hist;           // bf16 [D][hist_rows][H]
@@ -76,7 +102,7 @@ hipError_t launch_body_attention(const BodyAttnArgs& a, hipStream_t stream);
 hipError_t launch_pack_prompt_values(const uint16_t* Vp, uint16_t* Vt, int B, int H, int L, int Lp, hipStream_t stream);
 
 // Input rows of the FC for calls that go through the MFMA GEMM: x0[r] = [E[token of r], feature of r's parent],
-// assembled once (the GEMM gathers whole rows of one matrix).
+// assembled once (the GEMM gathers whole rows of one matrix).  With row_active the same launch lists the active rows.
 struct PackX0Args {
   const uint16_t* E;          // bf16 [V][H]
   const int32_t* token;       // [R] token of every row (root tokens for the prompt call)
@@ -84,6 +110,9 @@ struct PackX0Args {
   const int32_t* parent_slot; // [R] or null
   const uint8_t* row_active;  // [R] or null
   uint16_t* x0;               // bf16 [R][2H]
+  int32_t* row_list;          // [R] ids of the active rows, ascending,
+  int32_t* row_pos;           // [R] every active row's position in it,
+  int32_t* n_act;             // [1] and their number (row_active not null)
   int H, k, R;
   int feat_mode;              // GatherMode of the feature row: kGatherNone (prompt call), kGatherBlock, kGatherInBlock
 };

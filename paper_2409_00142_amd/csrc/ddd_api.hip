@@ -139,7 +139,6 @@ int enqueue_gemm(ddd_ctx* c, const void* W, const void* hid, int max_rows, bool 
   g.reverse = (c->cfg.flags & DDD_FLAG_FORWARD_SWEEPS) ? 0 : reverse;
   g.epi = kGemmLogits;
   g.out16 = nullptr;
-  g.out16b = nullptr;
   g.ld16 = 0;
   DDD_HIP(launch_lmhead_gemm(g, max_rows, c->g_grid, s));
   return DDD_OK;

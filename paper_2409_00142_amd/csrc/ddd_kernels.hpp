@@ -16,6 +16,21 @@ constexpr int kTraceStepWords = 8;
 constexpr int kTraceCallWords = DDD_STATIC_SLICES * kTraceStreamWords + kTraceStepWords;   // one draft call
 
 // ---- LM-head MFMA GEMM for more than 16 rows (lmhead_gemm.hip) --------------------------------
+// A product y = x W^T of the draft layer whose sums are taken in up to `smax` ranges of K by different workgroups: the
+// GEMM leaves the ranges' partial sums, and whoever reads y adds them up (in order).  How many ranges depends on the
+// number of active rows, which only the device knows; the GEMM and its readers find it by the same rule (gemm_plan.hpp).
+struct SplitShape {
+  int bbmax;                  // the launch's widest column tile holds 64 * bbmax rows
+  int nmt, kt, N;             // row tiles of W (128 rows), k tiles (64 k), rows of W
+  int grid, smax;             // workgroups; most ranges (1: never split)
+  long long cap;              // floats `part` has room for
+};
+struct SplitSums {
+  const float* part;          // [ranges][n_act][N] partial sums, active rows in list order; null: not a split product
+  SplitShape shape;
+  const int32_t* n_act_ptr;   // device scalar, or null: n_rows rows
+  int n_rows;
+};
 struct GemmArgs {
   const uint16_t* W;          // bf16 [V,H]
   const uint16_t* Wp;         // null, or the tile-major copy of W written by launch_pack_weights
@@ -32,21 +47,23 @@ struct GemmArgs {
   // What happens to the sums (the same product serves the draft layer's linears: W = a weight matrix [N = V][K = H],
   // hid = the input rows, logits = y).  kGemmLogits needs grp_max / grp_sum; the other modes ignore them.
   int epi;                    // GemmEpilogue
-  uint16_t* out16;            // bf16 [rows][ld16]: the activations (kGemmSiluPairs), or null / the rounded result (kGemmAccumulate)
-  uint16_t* out16b;           // null, or a second copy of out16 (kGemmAccumulate)
+  uint16_t* out16;            // bf16 [rows][ld16]: the activations (kGemmSiluPairs)
   int ld16;
+  SplitShape split;           // every mode but kGemmLogits (smax > 1 in kGemmPartial only: logits = [ranges][n_act][N] there)
 };
 enum GemmEpilogue {
   kGemmLogits = 0,       // logits = sum, plus max and sum of exponentials of every group of 64 vocabulary rows
   kGemmStore = 1,        // y = sum
-  kGemmAccumulate = 2,   // y += sum; out16 / out16b (if not null) = bf16(y)
+  kGemmAccumulate = 2,   // y += sum
+  kGemmPartial = 4,      // partial sums of K ranges (GemmArgs::split)
   kGemmSiluPairs = 3     // rows of W come in (gate_i, up_i) pairs: out16[r][i] = bf16(silu(gate) * up); y unused
 };
 hipError_t prepare_lmhead_gemm();   // once per process: enables the kernels' LDS sizes
 // max_rows: the largest number of rows this call can have (picks the tile shape)
 hipError_t launch_lmhead_gemm(const GemmArgs& a, int max_rows, int grid, hipStream_t stream);
-// The same kernel for a linear of the draft layer: the tile shape is picked so that the launch has about as many
-// work units as workgroups (N = a.V is a few thousand rows, not a vocabulary).
+// The same kernel for a linear of the draft layer (N = a.V is a few thousand rows, not a vocabulary): the column tiles and
+// K ranges are picked on the device (a.split).  gemm_linear_bbmax: the SplitShape::bbmax of calls of up to max_rows rows.
+inline int gemm_linear_bbmax(int max_rows) { return max_rows > 192 ? 5 : max_rows > 128 ? 3 : 2; }
 hipError_t launch_gemm_linear(const GemmArgs& a, int max_rows, int grid, hipStream_t stream);
 // Tile-major copy of W for the GEMM: blocks of 256 vocabulary rows x 64 k, each 32 KB contiguous
 // ([row in block][64 bf16]), blocks ordered (row block, k block); rows past V repeat row V-1.

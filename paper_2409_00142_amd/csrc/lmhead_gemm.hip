@@ -24,6 +24,7 @@
 // through its L2.
 #include "ddd_device.hpp"
 #include "ddd_kernels.hpp"
+#include "gemm_plan.hpp"
 
 namespace ddd {
 
@@ -62,13 +63,15 @@ __device__ __forceinline__ int row_id(const GemmArgs& a, int n) { return a.row_l
 // NB blocks of 32 rows from block wblk0 of the tile on (0 <= NB <= BB; a wave with NB == 0 still
 // copies tiles and meets the barriers).  Every value of NB has its own fully unrolled loop, so the
 // accumulators stay in place (no data-dependent branches around the MFMAs).
-template <int AB, int BB, int NB>
+template <int AB, int BB, int NB, bool LIN>
 __device__ __forceinline__ void gemm_unit(const GemmArgs& a, unsigned char* ldsb, int mt, int tile_col0, int wblk0,
-                                          int n_act, int tid, int wm, int l32, int lh) {
+                                          int n_act, int split, int nsplit, int tid, int wm, int l32, int lh) {
   using C = GemmCfg<AB, BB>;
   constexpr int NBR = NB > 0 ? NB : 1;
   constexpr int NAP = C::NAP, NBP = C::NBP, kSA = C::kSA, kSB = C::kSB;
-  const int KT = a.H / kGK;
+  // this unit's range of k tiles: all of them unless the product is split (a linear's only)
+  const int KTall = a.H / kGK;
+  const int kt_lo = LIN ? KTall * split / nsplit : 0, KT = LIN ? KTall * (split + 1) / nsplit - kt_lo : KTall;
   const int col0 = tile_col0 + wblk0 * 32;
 
   f32x16 acc[AB][NBR];
@@ -90,13 +93,13 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, unsigned char* ldsb
   // row-major (a k tile of a row tile = BM pieces of 128 bytes, one per row) or from its tile-major
   // copy (the same pieces contiguous: 256 rows x 128 bytes per block, the next k tile 32 KB on)
   const bool packed = a.Wp != nullptr;
-  const unsigned char* Wb = reinterpret_cast<const unsigned char*>(packed ? a.Wp : a.W);
   const uint32_t a_tile_stride = packed ? 256u * kRowB : (uint32_t)kRowB;
+  const unsigned char* Wb = reinterpret_cast<const unsigned char*>(packed ? a.Wp : a.W) + (size_t)kt_lo * a_tile_stride;
   uint32_t ao[NAP], bo[NBP];
 #pragma unroll
   for (int i = 0; i < NAP; ++i) {
     const int vrow = mt * C::BM + (i * 4 + wave) * 8 + prow;
-    ao[i] = packed ? ((uint32_t)(vrow >> 8) * (uint32_t)KT * 256u + (uint32_t)(vrow & 255)) * kRowB + pc * 16
+    ao[i] = packed ? ((uint32_t)(vrow >> 8) * (uint32_t)KTall * 256u + (uint32_t)(vrow & 255)) * kRowB + pc * 16
                    : ((uint32_t)min(vrow, a.V - 1) * (uint32_t)a.H + pc * 8) * 2u;
   }
 #pragma unroll
@@ -104,7 +107,7 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, unsigned char* ldsb
     bo[i] = ((uint32_t)row_id(a, min(tile_col0 + (i * 4 + wave) * 8 + prow, n_act - 1)) * (uint32_t)a.H + pc * 8) * 2u;
   typedef const __attribute__((address_space(1))) void* gptr_t;
   typedef __attribute__((address_space(3))) void* lptr_t;
-  const unsigned char* Hb = reinterpret_cast<const unsigned char*>(a.hid);
+  const unsigned char* Hb = reinterpret_cast<const unsigned char*>(a.hid) + (size_t)kt_lo * kRowB;
   unsigned char* const ldsA = ldsb;
   unsigned char* const ldsB = ldsb + kSA * C::kABytes;
   // copy instruction i of a tile of W (A) / of the hidden rows (B)
@@ -225,16 +228,15 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, unsigned char* ldsb
   static_assert(AB % 2 == 0, "a wave covers whole groups of 64 vocabulary rows");
   constexpr int NGW = AB / 2;                                  // groups per wave
   const int grp0 = (mt * C::BM + wm * 32 * AB) >> 6;
-  if (a.epi != kGemmLogits) {
-    // ---- a linear of the draft layer: store, accumulate, or gate (V is a multiple of 4 there) ------------
+  if (LIN) {
+    // ---- a linear of the draft layer: partial sums, store, accumulate, or gate (V is a multiple of 4 there) ----
 #pragma unroll
     for (int bn = 0; bn < NBR; ++bn) {
       const int n = col0 + bn * 32 + l32;
       if (n >= n_act) continue;
       const int orow_id = row_id(a, n);
-      float* orow = a.logits + (size_t)orow_id * a.ldl;
-      uint16_t* o16 = a.out16 ? a.out16 + (size_t)orow_id * a.ld16 : nullptr;
-      uint16_t* o16b = a.out16b ? a.out16b + (size_t)orow_id * a.ld16 : nullptr;
+      float* orow = a.logits + (a.epi == kGemmPartial ? (size_t)split * n_act + n : (size_t)orow_id) * a.ldl;
+      uint16_t* o16 = a.epi == kGemmSiluPairs ? a.out16 + (size_t)orow_id * a.ld16 : nullptr;
 #pragma unroll
       for (int bm = 0; bm < AB; ++bm)
 #pragma unroll
@@ -249,11 +251,6 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, unsigned char* ldsb
           } else {
             if (a.epi == kGemmAccumulate) o += *reinterpret_cast<const f32x4*>(orow + v);
             *reinterpret_cast<f32x4*>(orow + v) = o;
-            if (o16 != nullptr) {
-              const uint32_t p0 = bf16_rne(o[0]) | (bf16_rne(o[1]) << 16), p1 = bf16_rne(o[2]) | (bf16_rne(o[3]) << 16);
-              *reinterpret_cast<uint2*>(o16 + v) = make_uint2(p0, p1);
-              if (o16b != nullptr) *reinterpret_cast<uint2*>(o16b + v) = make_uint2(p0, p1);
-            }
           }
         }
     }
@@ -322,32 +319,33 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, unsigned char* ldsb
 // active rows are dealt evenly: to the column tiles, and inside a tile to the two waves along the
 // hidden rows, so that 400 active rows cost 7 + 6 blocks in two tiles of (4, 3) and (3, 3) per
 // wave pair instead of 10 + 3 in tiles of (5, 5) and (3, 0).
-template <int AB, int BB>
-__device__ __forceinline__ void gemm_units(const GemmArgs& a, unsigned char* lds, int n_act, int NT, int bpt) {
+template <int AB, int BB, bool LIN>
+__device__ __forceinline__ void gemm_units(const GemmArgs& a, unsigned char* lds, int n_act, int NT, int bpt, int S) {
   using C = GemmCfg<AB, BB>;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int wm = wave % kWM, wn = wave / kWM;
   const int l32 = lane & 31, lh = lane >> 5;
   const int nmt = (a.V + C::BM - 1) / C::BM;
   const int nblk_all = (n_act + 31) >> 5;
-  const int nunits = nmt * NT;
+  const int nunits = nmt * S * NT;
   const int G = gridDim.x;
   const int vg = (blockIdx.x & 7) * (G >> 3) + (blockIdx.x >> 3);   // neighbours on one XCD get neighbouring units
 
   for (int u = vg; u < nunits; u += G) {
-    const int mu = u / NT, nt = u - mu * NT;
+    const int ms = u / NT, nt = u - ms * NT;
+    const int mu = LIN ? ms / S : ms, split = ms - mu * S;
     const int mt = a.reverse ? nmt - 1 - mu : mu;   // consecutive calls walk W in opposite directions (memory-side cache)
     const int nblk = min(bpt, nblk_all - nt * bpt);  // >= 1
     const int h0 = (nblk + 1) >> 1;
     const int wblk0 = wn ? h0 : 0, nb = wn ? nblk - h0 : h0;   // wave-uniform
     const int tc0 = nt * bpt * 32;
     switch (nb) {
-      case 0: gemm_unit<AB, BB, 0>(a, lds, mt, tc0, wblk0, n_act, tid, wm, l32, lh); break;
-      case 1: gemm_unit<AB, BB, 1>(a, lds, mt, tc0, wblk0, n_act, tid, wm, l32, lh); break;
-      case 2: gemm_unit<AB, BB, (BB >= 2 ? 2 : BB)>(a, lds, mt, tc0, wblk0, n_act, tid, wm, l32, lh); break;
-      case 3: gemm_unit<AB, BB, (BB >= 3 ? 3 : BB)>(a, lds, mt, tc0, wblk0, n_act, tid, wm, l32, lh); break;
-      case 4: gemm_unit<AB, BB, (BB >= 4 ? 4 : BB)>(a, lds, mt, tc0, wblk0, n_act, tid, wm, l32, lh); break;
-      default: gemm_unit<AB, BB, BB>(a, lds, mt, tc0, wblk0, n_act, tid, wm, l32, lh); break;
+      case 0: gemm_unit<AB, BB, 0, LIN>(a, lds, mt, tc0, wblk0, n_act, split, S, tid, wm, l32, lh); break;
+      case 1: gemm_unit<AB, BB, 1, LIN>(a, lds, mt, tc0, wblk0, n_act, split, S, tid, wm, l32, lh); break;
+      case 2: gemm_unit<AB, BB, (BB >= 2 ? 2 : BB), LIN>(a, lds, mt, tc0, wblk0, n_act, split, S, tid, wm, l32, lh); break;
+      case 3: gemm_unit<AB, BB, (BB >= 3 ? 3 : BB), LIN>(a, lds, mt, tc0, wblk0, n_act, split, S, tid, wm, l32, lh); break;
+      case 4: gemm_unit<AB, BB, (BB >= 4 ? 4 : BB), LIN>(a, lds, mt, tc0, wblk0, n_act, split, S, tid, wm, l32, lh); break;
+      default: gemm_unit<AB, BB, BB, LIN>(a, lds, mt, tc0, wblk0, n_act, split, S, tid, wm, l32, lh); break;
     }
   }
 }
@@ -355,27 +353,34 @@ __device__ __forceinline__ void gemm_units(const GemmArgs& a, unsigned char* lds
 // BB is the widest column tile the launch may need (64 * BB rows per workgroup).  The number of
 // active rows is only known on the device, so the kernel picks the column tiling itself: as few
 // tiles as BB allows, the blocks dealt evenly to them, and the narrowest tile that holds a share
-// (with 64 active rows a 320-row tile would still copy 320 repeated rows per K tile through LDS).
-template <int AB, int BB>
+// (with 64 active rows a 320-row tile would still copy 320 repeated rows per K tile through LDS).  LIN: a linear of the
+// draft layer (column tiles and K ranges by gemm_plan, the other epilogues) instead of the LM head.
+template <int AB, int BB, bool LIN>
 __global__ __launch_bounds__(256, 1) void lmhead_gemm_kernel(GemmArgs a) {
   extern __shared__ __align__(16) unsigned char lds[];     // the two tile rings of the chosen width
 
   const int n_act = a.row_list != nullptr ? *a.n_act_ptr : a.n_rows;
   if (n_act <= 0) return;                                  // uniform
   const int nblk_all = (n_act + 31) >> 5;
-  const int NT = (nblk_all + 2 * BB - 1) / (2 * BB);
-  const int bpt = (nblk_all + NT - 1) / NT;                // blocks per column tile, <= 2 * BB
+  int NT = (nblk_all + 2 * BB - 1) / (2 * BB), S = 1;
+  int bpt = (nblk_all + NT - 1) / NT;                      // blocks per column tile, <= 2 * BB
+  if (LIN) {
+    const GemmPlan p = gemm_plan(a.split, n_act, threadIdx.x & 63);
+    NT = p.NT;
+    bpt = p.bpt;
+    S = p.S;
+  }
   const int bb = (bpt + 1) >> 1;                           // blocks per wave, <= BB
   if (BB >= 5 && bb >= 5)
-    gemm_units<AB, (BB >= 5 ? 5 : BB)>(a, lds, n_act, NT, bpt);
+    gemm_units<AB, (BB >= 5 ? 5 : BB), LIN>(a, lds, n_act, NT, bpt, S);
   else if (BB >= 4 && bb == 4)
-    gemm_units<AB, (BB >= 4 ? 4 : BB)>(a, lds, n_act, NT, bpt);
+    gemm_units<AB, (BB >= 4 ? 4 : BB), LIN>(a, lds, n_act, NT, bpt, S);
   else if (BB >= 3 && bb == 3)
-    gemm_units<AB, (BB >= 3 ? 3 : BB)>(a, lds, n_act, NT, bpt);
+    gemm_units<AB, (BB >= 3 ? 3 : BB), LIN>(a, lds, n_act, NT, bpt, S);
   else if (BB >= 2 && bb == 2)
-    gemm_units<AB, (BB >= 2 ? 2 : BB)>(a, lds, n_act, NT, bpt);
+    gemm_units<AB, (BB >= 2 ? 2 : BB), LIN>(a, lds, n_act, NT, bpt, S);
   else
-    gemm_units<AB, 1>(a, lds, n_act, NT, bpt);
+    gemm_units<AB, 1, LIN>(a, lds, n_act, NT, bpt, S);
 }
 
 // ---- tile-major copy of W ------------------------------------------------------------------------
@@ -443,41 +448,44 @@ static int pick_shape(int max_rows, int V, int grid) {
   return ((V + 255) / 256 >= grid) ? 4 : 3;
 }
 
-template <int AB, int BB>
+template <int AB, int BB, bool LIN>
 static hipError_t prepare_shape() {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&lmhead_gemm_kernel<AB, BB>),
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&lmhead_gemm_kernel<AB, BB, LIN>),
                              hipFuncAttributeMaxDynamicSharedMemorySize, GemmCfg<AB, BB>::kLdsBytes);
 }
 
 hipError_t prepare_lmhead_gemm() {
-  hipError_t e = prepare_shape<2, 5>();
-  if (e == hipSuccess) e = prepare_shape<2, 3>();
-  if (e == hipSuccess) e = prepare_shape<2, 2>();
-  if (e == hipSuccess) e = prepare_shape<4, 2>();
+  hipError_t e = prepare_shape<2, 5, false>();
+  if (e == hipSuccess) e = prepare_shape<2, 3, false>();
+  if (e == hipSuccess) e = prepare_shape<2, 2, false>();
+  if (e == hipSuccess) e = prepare_shape<4, 2, false>();
+  if (e == hipSuccess) e = prepare_shape<2, 5, true>();
+  if (e == hipSuccess) e = prepare_shape<2, 3, true>();
+  if (e == hipSuccess) e = prepare_shape<2, 2, true>();
   return e;
 }
 
-template <int AB, int BB>
+template <int AB, int BB, bool LIN>
 static void launch_shape(const GemmArgs& a, int grid, hipStream_t stream) {
   constexpr int lds_bytes = GemmCfg<AB, BB>::kLdsBytes;
-  hipLaunchKernelGGL((lmhead_gemm_kernel<AB, BB>), dim3(grid), dim3(256), lds_bytes, stream, a);
+  hipLaunchKernelGGL((lmhead_gemm_kernel<AB, BB, LIN>), dim3(grid), dim3(256), lds_bytes, stream, a);
 }
 
 hipError_t launch_gemm_linear(const GemmArgs& a, int max_rows, int grid, hipStream_t stream) {
-  // work units of the widest tile that holds the rows; fewer than workgroups: take 128 x 128 tiles instead
-  const int mt = (a.V + 127) / 128;
-  const int wide = max_rows > 192 ? 320 : max_rows > 128 ? 192 : 128;
-  if (mt * ((max_rows + wide - 1) / wide) >= grid) return launch_lmhead_gemm(a, max_rows, grid, stream);
-  launch_shape<2, 2>(a, grid, stream);
+  switch (gemm_linear_bbmax(max_rows)) {   // the kernel picks the column tiles (and K ranges) itself
+    case 5: launch_shape<2, 5, true>(a, grid, stream); break;
+    case 3: launch_shape<2, 3, true>(a, grid, stream); break;
+    default: launch_shape<2, 2, true>(a, grid, stream); break;
+  }
   return hipGetLastError();
 }
 
 hipError_t launch_lmhead_gemm(const GemmArgs& a, int max_rows, int grid, hipStream_t stream) {
   switch (pick_shape(max_rows, a.V, grid)) {
-    case 1: launch_shape<2, 5>(a, grid, stream); break;
-    case 2: launch_shape<2, 3>(a, grid, stream); break;
-    case 4: launch_shape<4, 2>(a, grid, stream); break;
-    default: launch_shape<2, 2>(a, grid, stream); break;
+    case 1: launch_shape<2, 5, false>(a, grid, stream); break;
+    case 2: launch_shape<2, 3, false>(a, grid, stream); break;
+    case 4: launch_shape<4, 2, false>(a, grid, stream); break;
+    default: launch_shape<2, 2, false>(a, grid, stream); break;
   }
   return hipGetLastError();
 }

@@ -52,3 +52,33 @@ def test_logits_pitch_of_any_vocabulary(gpu, V, equal):
     want = np.argsort(-b[3], axis=1, kind="stable")[:, :k]     # ties: the lower token first
     assert np.array_equal(a[0], want)
     assert np.all(a[0] < V)
+
+
+@pytest.mark.parametrize("N,K", [(4, 256), (128, 2048), (1156, 2048), (4096, 512), (516, 11008)])
+@pytest.mark.parametrize("R", [17, 32, 33, 64, 65, 321, 640])
+def test_split_linear(gpu, N, K, R):
+    """ddd_body_linear on the MFMA path where few row tiles of W make it split K (1 to 8 ranges, uneven where the k tiles
+    do not divide), one block of rows more or less than a tile: against the product in 64 bits, and twice the same bits.
+
+    Tolerance: products of bf16 numbers are exact in fp32, and K sums of terms of size K^-0.5 round with relative error
+    2^-24 each: sqrt(K) * 2^-24 times a few, below 1e-5 for K <= 11008; 1e-4 leaves room for the largest of R * N."""
+    torch, D = gpu
+    print(f"[case] split_linear N={N} K={K} R={R}", flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N * 31 + K * 7 + R)
+    W = torch.empty(N, K, dtype=torch.bfloat16, device="cuda").normal_(0, K ** -0.5, generator=g)
+    x = torch.empty(R, K, dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=g)
+    want = x.double() @ W.double().T.contiguous()
+    body = D.ddd_body_create(D.ddd_body_config((R + 4) // 5, 5, 256, 256, 10, 2, 0))
+    try:
+        y = [torch.full((R, N), float("nan"), device="cuda") for _ in range(2)]
+        for t in y:
+            D.ddd_body_linear(body, W, N, K, x, R, t)
+        acc = y[0].clone()
+        D.ddd_body_linear(body, W, N, K, x, R, acc, accumulate=True)
+        torch.cuda.synchronize()
+    finally:
+        D.ddd_body_destroy(body)
+    assert torch.equal(y[0], y[1])
+    assert float((y[0].double() - want).abs().max()) <= 1e-4
+    assert float((acc.double() - 2 * want).abs().max()) <= 2e-4
