@@ -107,18 +107,7 @@ int enqueue_linear_ranges(const ddd_body* b, LinearArgs a, int K_range, hipStrea
   return DDD_OK;
 }
 
-// The shape of a linear for calls of up to b->rows rows; smax: most K ranges its product may be split into.
-SplitShape split_shape(const ddd_body* b, int N, int K, int smax) {
-  SplitShape g;
-  g.bbmax = gemm_linear_bbmax(b->rows);
-  g.nmt = (N + 127) / 128;
-  g.kt = K / 64;
-  g.N = N;
-  g.grid = ((b->n_cu + 7) / 8) * 8;
-  g.smax = smax;
-  g.cap = b->part_cap;
-  return g;
-}
+int body_grid(const ddd_body* b) { return ((b->n_cu + 7) / 8) * 8; }   // workgroups of the MFMA GEMM
 
 // y = x W^T over the rows in b->row_list, or over all n_rows of them, through the MFMA GEMM (calls of more than
 // kBodyRows rows): partial sums in b->part (kGemmPartial), activations in out16 (kGemmSiluPairs), or in y.
@@ -142,8 +131,8 @@ int enqueue_gemm_linear(const ddd_body* b, int n_rows, bool all_rows, const void
   g.epi = epi;
   g.out16 = out16;
   g.ld16 = ld16;
-  g.split = split_shape(b, N, K, epi == kGemmPartial ? 8 : 1);
-  BODY_HIP(launch_gemm_linear(g, b->rows, g.split.grid, s));
+  g.split = linear_shape(N, K, n_rows, body_grid(b), epi == kGemmPartial ? 8 : 1, b->part_cap);
+  BODY_HIP(launch_gemm_linear(g, g.split.grid, s));
   return DDD_OK;
 }
 
@@ -151,7 +140,7 @@ int enqueue_gemm_linear(const ddd_body* b, int n_rows, bool all_rows, const void
 SplitSums split_sums(const ddd_body* b, int n_rows, bool all_rows, int N, int K) {
   SplitSums v;
   v.part = b->part;
-  v.shape = split_shape(b, N, K, 8);
+  v.shape = linear_shape(N, K, n_rows, body_grid(b), 8, b->part_cap);
   v.n_act_ptr = all_rows ? nullptr : b->n_act;
   v.n_rows = n_rows;
   return v;
@@ -219,8 +208,8 @@ int ddd_body_create(const ddd_body_config* cfg, ddd_body** out) {
     if (e == hipSuccess) e = prepare_lmhead_gemm();
     if (e == hipSuccess) e = hipMalloc(&b->row_pos, R * sizeof(int32_t));
     // room for the layer's products unsplit, and for one tile of every workgroup: a split fills the chip once
-    const long long grid = ((b->n_cu + 7) / 8) * 8, tile = 128LL * 64 * gemm_linear_bbmax(b->rows);
-    b->part_cap = (long long)R * 3 * H > grid * tile ? (long long)R * 3 * H : grid * tile;
+    const long long sums = (long long)R * 3 * H, chip = (long long)body_grid(b) * 192 * (R < 320 ? (R + 63) / 64 * 64 : 320);
+    b->part_cap = sums > chip ? sums : chip;
     if (e == hipSuccess) e = hipMalloc(&b->part, (size_t)b->part_cap * sizeof(float));
     b->Lp = (cfg->L + 31) & ~31;
     if (e == hipSuccess && cfg->L >= 32) e = hipMalloc(&b->vt, (size_t)cfg->B * H * b->Lp * sizeof(uint16_t));

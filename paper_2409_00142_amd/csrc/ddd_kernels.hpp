@@ -20,8 +20,8 @@ constexpr int kTraceCallWords = DDD_STATIC_SLICES * kTraceStreamWords + kTraceSt
 // GEMM leaves the ranges' partial sums, and whoever reads y adds them up (in order).  How many ranges depends on the
 // number of active rows, which only the device knows; the GEMM and its readers find it by the same rule (gemm_plan.hpp).
 struct SplitShape {
-  int bbmax;                  // the launch's widest column tile holds 64 * bbmax rows
-  int nmt, kt, N;             // row tiles of W (128 rows), k tiles (64 k), rows of W
+  int ab, bbmax;              // tile: 64 * ab rows of W, at most 64 * bbmax active rows
+  int kt, N;                  // k tiles (64 k), rows of W
   int grid, smax;             // workgroups; most ranges (1: never split)
   long long cap;              // floats `part` has room for
 };
@@ -61,10 +61,10 @@ enum GemmEpilogue {
 hipError_t prepare_lmhead_gemm();   // once per process: enables the kernels' LDS sizes
 // max_rows: the largest number of rows this call can have (picks the tile shape)
 hipError_t launch_lmhead_gemm(const GemmArgs& a, int max_rows, int grid, hipStream_t stream);
-// The same kernel for a linear of the draft layer (N = a.V is a few thousand rows, not a vocabulary): the column tiles and
-// K ranges are picked on the device (a.split).  gemm_linear_bbmax: the SplitShape::bbmax of calls of up to max_rows rows.
-inline int gemm_linear_bbmax(int max_rows) { return max_rows > 192 ? 5 : max_rows > 128 ? 3 : 2; }
-hipError_t launch_gemm_linear(const GemmArgs& a, int max_rows, int grid, hipStream_t stream);
+// The same kernel for a linear of the draft layer (N = a.V is a few thousand rows, not a vocabulary): the tile is a.split's
+// (linear_shape, for calls of up to max_rows rows), the column tiles and K ranges are picked on the device.
+SplitShape linear_shape(int N, int K, int max_rows, int grid, int smax, long long cap);
+hipError_t launch_gemm_linear(const GemmArgs& a, int grid, hipStream_t stream);
 // Tile-major copy of W for the GEMM: blocks of 256 vocabulary rows x 64 k, each 32 KB contiguous
 // ([row in block][64 bf16]), blocks ordered (row block, k block); rows past V repeat row V-1.
 // Wp holds ceil(V/256)*256*H elements.

@@ -49,7 +49,7 @@ __device__ __forceinline__ uint32_t bf16_rne(float x) {   // finite inputs; the 
 template <int AB, int BB>
 struct GemmCfg {
   static constexpr int BM = 32 * AB * kWM, BN = 64 * BB;
-  static constexpr int kSA = (AB >= 4) ? 3 : 4, kSB = (BB >= 4) ? 2 : 3;   // ring depths, kSB <= kSA
+  static constexpr int kSA = (AB >= 3) ? 3 : 4, kSB = (BB >= 4) ? 2 : 3;   // ring depths, kSB <= kSA
   static constexpr int kABytes = BM * kRowB, kBBytes = BN * kRowB;
   static constexpr int kLdsBytes = kSA * kABytes + kSB * kBBytes;
   static constexpr int NAP = BM / 32, NBP = BN / 32;   // copy instructions per wave and tile (8 rows each)
@@ -225,8 +225,8 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, unsigned char* ldsb
   // context's own logits have such a pitch whatever V is; a caller's debug buffer has pitch V, and for an odd V the
   // scalar stores (V = 32003, 170 rows: 94.8 us a ddd_lmhead_topk call with those, 84.8 with a padded pitch).
   const bool v_aligned = (a.ldl & 3) == 0;
-  static_assert(AB % 2 == 0, "a wave covers whole groups of 64 vocabulary rows");
-  constexpr int NGW = AB / 2;                                  // groups per wave
+  static_assert(LIN || AB % 2 == 0, "a wave covers whole groups of 64 vocabulary rows");
+  constexpr int NGW = LIN ? 1 : AB / 2;                        // groups per wave
   const int grp0 = (mt * C::BM + wm * 32 * AB) >> 6;
   if (LIN) {
     // ---- a linear of the draft layer: partial sums, store, accumulate, or gate (V is a multiple of 4 there) ----
@@ -459,6 +459,7 @@ hipError_t prepare_lmhead_gemm() {
   if (e == hipSuccess) e = prepare_shape<2, 3, false>();
   if (e == hipSuccess) e = prepare_shape<2, 2, false>();
   if (e == hipSuccess) e = prepare_shape<4, 2, false>();
+  if (e == hipSuccess) e = prepare_shape<3, 5, true>();
   if (e == hipSuccess) e = prepare_shape<2, 5, true>();
   if (e == hipSuccess) e = prepare_shape<2, 3, true>();
   if (e == hipSuccess) e = prepare_shape<2, 2, true>();
@@ -471,12 +472,35 @@ static void launch_shape(const GemmArgs& a, int grid, hipStream_t stream) {
   hipLaunchKernelGGL((lmhead_gemm_kernel<AB, BB, LIN>), dim3(grid), dim3(256), lds_bytes, stream, a);
 }
 
-hipError_t launch_gemm_linear(const GemmArgs& a, int max_rows, int grid, hipStream_t stream) {
-  switch (gemm_linear_bbmax(max_rows)) {   // the kernel picks the column tiles (and K ranges) itself
-    case 5: launch_shape<2, 5, true>(a, grid, stream); break;
-    case 3: launch_shape<2, 3, true>(a, grid, stream); break;
-    default: launch_shape<2, 2, true>(a, grid, stream); break;
-  }
+// 128 rows of W per tile, or 192 where that is cheaper: fewer copies and fragment reads per MFMA, and with hundreds of
+// rows fewer half-empty passes over the workgroups (640 rows: 22016 rows of W are 344 tiles of 128 x 320 but 230 of
+// 192 x 320 for 256 workgroups, 167 -> 115.5 us; 12288 rows 192 tiles, or 128 with two ranges of K each, 85.5 -> 76 us).
+SplitShape linear_shape(int N, int K, int max_rows, int grid, int smax, long long cap) {
+  auto shape = [&](int ab, int bbmax) { return SplitShape{ab, bbmax, K / kGK, N, grid, smax, cap}; };
+  auto best = [&](const SplitShape& g) {
+    float least = 0.f;
+    const int t0 = plan_least_tiles(g, max_rows);
+    for (int i = 0; i < 64; ++i) {
+      const float p = plan_price(g, max_rows, t0 + (i & 7), (i >> 3) + 1);
+      if (p > 0.f && (least == 0.f || p < least)) least = p;
+    }
+    return least;
+  };
+  if (max_rows <= 128) return shape(2, 2);
+  if (max_rows <= 192) return shape(2, 3);
+  const SplitShape two = shape(2, 5), three = shape(3, 5);
+  return best(three) < best(two) ? three : two;
+}
+
+hipError_t launch_gemm_linear(const GemmArgs& a, int grid, hipStream_t stream) {
+  if (a.split.ab == 3)
+    launch_shape<3, 5, true>(a, grid, stream);
+  else if (a.split.bbmax == 5)
+    launch_shape<2, 5, true>(a, grid, stream);
+  else if (a.split.bbmax == 3)
+    launch_shape<2, 3, true>(a, grid, stream);
+  else
+    launch_shape<2, 2, true>(a, grid, stream);
   return hipGetLastError();
 }
 
