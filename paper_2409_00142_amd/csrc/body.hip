@@ -12,7 +12,7 @@
 //   body_attention_kernel  RoPE, bf16 key / value store, softmax over prompt + ancestors + self: one workgroup per
 //                          (row, head); batched rounds: one per (sequence, head), by ordinary arithmetic
 //                          (body_attention_seq_kernel) or with the prompt part on the matrix cores
-//                          (body_attention_mfma_kernel, pack_prompt_values_kernel)
+//                          (body_attention_mfma_kernel)
 //   pack_x0_kernel         the FC's input rows assembled for the MFMA path of calls with more than 16 rows
 //   The SiLU gate and the final bf16 rounding of the hidden rows ride in the epilogues of the
 //   linears that produce their inputs.
@@ -708,18 +708,42 @@ __global__ __launch_bounds__(kSeqThreads) void body_attention_seq_kernel(BodyAtt
 //   O[d][row]   = sum_key V[key][d] p[row][key]  (A = 16 d x 32 keys, B = 16 rows x 32 keys)
 // The fp32 operands (rotated queries, softmax weights) go in as two bf16 halves, x = hi + lo with |x - hi - lo| <=
 // 2^-17 |x| (two MFMAs per tile), so no rounding point is added to the layer's definition.  Both A operands come
-// straight from global memory, 16 bytes per lane: 8 consecutive d of one key for the first contraction (the cache's
-// own layout), 8 consecutive keys of one d for the second, which needs the values with the keys of an element
-// contiguous: pack_prompt_values_kernel writes that copy in the prompt call of every round.  No operand is staged in
-// LDS, which leaves room for three workgroups per CU: each is a chain of dependent steps, and the others' loads run
-// under it.  The rows' own keys and their ancestors' (at most 32 per row, different from row to row) are handled by
-// ordinary arithmetic.  (With one workgroup per (row, head) the launch took 510 us at the 7B shape with 640 rows, with
-// ordinary arithmetic per (sequence, head) 177 us.)
+// straight from global memory, 16 bytes per lane.  For the first that is 8 consecutive d of one key, the cache's own
+// layout.  The second wants 8 consecutive keys of one d: a lane loads 8 keys' pieces of the same 8 d and turns the
+// 8 x 8 block over in its registers (32 byte permutes), and the MFMA that takes its t-th d has the d 8m + t as its row
+// m - any 16 of the 128 will do.  A wave then holds all d of its keys, and the waves' sums meet in LDS.  (A copy of the
+// values with the keys of an element contiguous, written by every round's prompt call, cost 72 us a round at B = 64,
+// L = 256, H = 4096 and as much memory as the values.)  What bounds it: the 268 MB of prompt keys and values at 640 rows,
+// 55 us at the rate of a large copy: 62 us for one row per
+// sequence, 88 us for ten (which read 63 MB of partial sums too; 92 with the copied values).  No operand is staged in LDS, which leaves room for three workgroups per CU: each
+// is a chain of dependent steps, and the others' loads run under it.  The rows' own keys and their ancestors' (at most
+// 32 per row, different from row to row) are handled by ordinary arithmetic.  (With one workgroup per (row, head) the
+// launch took 510 us at the 7B shape with 640 rows, with ordinary arithmetic per (sequence, head) 177 us.)
 constexpr int kMfThreads = 256;
+constexpr int kMfLeast = 32;                 // shortest prompt (fewer keys leave most of the waves without a step of 32)
+constexpr int kMfWaves = kMfThreads / 64;
+constexpr int kMfOutPitch = kHeadDim + 4;    // floats of a row in a wave's outputs
 
-static size_t attention_mfma_lds(int Lp, int n_vis) {
-  return (size_t)(kSeqRows * kHeadDim + kSeqRows + kSeqRows * 32 + (size_t)n_vis * kSeqRows) * sizeof(float) +
-         (size_t)(2 * kSeqRows * kHeadDim + 2 * kSeqRows * (Lp + 8)) * sizeof(uint16_t);
+struct MfLds {              // offsets in bytes
+  int spitch, ppitch;       // floats of a row of scores, bf16 of a row of weights
+  size_t rsum, anc, ks, vs, aw, sct, ph, pl, total;
+};
+__host__ __device__ inline MfLds mf_lds(int L, int step) {
+  MfLds m;
+  m.spitch = ((L + 3) & ~3) + 4;
+  m.ppitch = ((L + 31) & ~31) + 8;
+  m.rsum = (size_t)kSeqRows * kHeadDim * 4;            // behind the rotated queries
+  m.anc = m.rsum + kSeqRows * 4;
+  m.ks = m.anc + kSeqRows * 32 * 4;
+  m.vs = m.ks + kSeqRows * kHeadDim * 2;
+  m.aw = m.vs + kSeqRows * kHeadDim * 2;               // [kSeqRows][step + 1] scores, then weights, past the prompt
+  m.sct = (m.aw + (size_t)kSeqRows * (step + 1) * 4 + 15) & ~(size_t)15;
+  m.ph = m.sct + (size_t)kSeqRows * m.spitch * 4;
+  m.pl = m.ph + (size_t)kSeqRows * m.ppitch * 2;
+  m.total = m.pl + (size_t)kSeqRows * m.ppitch * 2;
+  const size_t outs = m.sct + (size_t)kMfWaves * kSeqRows * kMfOutPitch * 4;   // the waves' outputs take the place of sct, ph, pl
+  if (outs > m.total) m.total = outs;
+  return m;
 }
 
 __device__ __forceinline__ void split_bf16x8(const float* x, bool on, bf16x8& hi, bf16x8& lo) {
@@ -736,7 +760,7 @@ __device__ __forceinline__ void split_bf16x8(const float* x, bool on, bf16x8& hi
   lo = __builtin_bit_cast(bf16x8, l);
 }
 
-__global__ __launch_bounds__(kMfThreads) void body_attention_mfma_kernel(BodyAttnArgs a) {
+__global__ __launch_bounds__(kMfThreads, 3) void body_attention_mfma_kernel(BodyAttnArgs a) {
   extern __shared__ __align__(16) unsigned char smb[];
   const int nh = a.H / kHeadDim;
   const int b = blockIdx.x / nh, h = blockIdx.x % nh, tid = threadIdx.x, lane = tid & 63;
@@ -745,16 +769,18 @@ __global__ __launch_bounds__(kMfThreads) void body_attention_mfma_kernel(BodyAtt
   const int r0 = (a.step == 0) ? b : b * a.k;
   if (a.row_active != nullptr && a.row_active[r0] == 0) return;   // uniform: a sequence's rows share their flag
   const SumsView sv = qkv_view(a, tid & 63);
-  const int L = a.L, Lp = a.Lp, n_vis = L + a.step + 1;
-  const int ppitch = Lp + 8;
-  float* qs = reinterpret_cast<float*>(smb);        // [kSeqRows][128] rotated queries; later the prompt's part of the outputs
-  float* rsum = qs + kSeqRows * kHeadDim;           // [kSeqRows] sums of the weights
-  int* anc = reinterpret_cast<int*>(rsum + kSeqRows);            // [kSeqRows][32] row of the ancestor in each earlier call
-  float* sct = reinterpret_cast<float*>(anc + kSeqRows * 32);    // [n_vis][kSeqRows] scores; weights of the keys past the prompt
-  uint16_t* ks = reinterpret_cast<uint16_t*>(sct + (size_t)n_vis * kSeqRows);   // [kSeqRows][128] own keys as stored
-  uint16_t* vs = ks + kSeqRows * kHeadDim;                                      // [kSeqRows][128] own values as stored
-  uint16_t* ph = vs + kSeqRows * kHeadDim;          // [kSeqRows][ppitch] weights of the prompt keys, high halves
-  uint16_t* pl = ph + kSeqRows * ppitch;            // ... low halves
+  const int L = a.L;
+  const MfLds m = mf_lds(L, a.step);
+  float* qs = reinterpret_cast<float*>(smb);                     // [kSeqRows][128] rotated queries
+  float* rsum = reinterpret_cast<float*>(smb + m.rsum);          // [kSeqRows] sums of the weights
+  int* anc = reinterpret_cast<int*>(smb + m.anc);                // [kSeqRows][32] row of the ancestor in each earlier call
+  uint16_t* ks = reinterpret_cast<uint16_t*>(smb + m.ks);        // [kSeqRows][128] own keys as stored
+  uint16_t* vs = reinterpret_cast<uint16_t*>(smb + m.vs);        // [kSeqRows][128] own values as stored
+  float* aw = reinterpret_cast<float*>(smb + m.aw);              // [kSeqRows][step + 1]
+  float* sct = reinterpret_cast<float*>(smb + m.sct);            // [kSeqRows][spitch] scores of the prompt keys
+  uint16_t* ph = reinterpret_cast<uint16_t*>(smb + m.ph);        // [kSeqRows][ppitch] their weights, high halves
+  uint16_t* pl = reinterpret_cast<uint16_t*>(smb + m.pl);        // ... low halves
+  float* outs = sct;                                             // [wave][kSeqRows][kMfOutPitch] the prompt's part of the outputs
 
   // ---- the first 256 prompt keys: requested now, multiplied once the queries are rotated ------------------------
   // lane (row, dq) of the A operand holds 8 consecutive d of key `row` of the tile; tile t belongs to wave t mod 4
@@ -771,26 +797,35 @@ __global__ __launch_bounds__(kMfThreads) void body_attention_mfma_kernel(BodyAtt
   };
   load_keys(0);
   // ---- own rows: rotate, store, ancestors (as in the kernels above) -----------------------------------------------
-  for (int t = tid; t < kk * 64; t += kMfThreads) {
-    const int i = t >> 6, p = t & 63, r = r0 + i;
+  {
+    const int p = tid & 63;                               // every row's pair (p, p + 64) turns by the same angle
     const float inv_freq = exp2f(-(float)(2 * p) / (float)kHeadDim * 13.287712379549449f);   // log2(10000)
     float sn, cs;
     sincosf((float)(L + a.step) * inv_freq, &sn, &cs);
-    float q0, q1, k0, k1, v0, v1;
-    load_qkv_pair(a, sv, r, h, p, q0, q1, k0, k1, v0, v1);
-    qs[i * kHeadDim + p] = q0 * cs - q1 * sn;
-    qs[i * kHeadDim + p + 64] = q1 * cs + q0 * sn;
-    const uint16_t kb0 = f32_to_bf16_rne(k0 * cs - k1 * sn), kb1 = f32_to_bf16_rne(k1 * cs + k0 * sn);
-    const uint16_t vb0 = f32_to_bf16_rne(v0), vb1 = f32_to_bf16_rne(v1);
-    const size_t slot = ((size_t)a.step * a.hist_rows + r) * a.H + h * kHeadDim;
-    a.k_hist[slot + p] = kb0;
-    a.k_hist[slot + p + 64] = kb1;
-    a.v_hist[slot + p] = vb0;
-    a.v_hist[slot + p + 64] = vb1;
-    ks[i * kHeadDim + p] = kb0;
-    ks[i * kHeadDim + p + 64] = kb1;
-    vs[i * kHeadDim + p] = vb0;
-    vs[i * kHeadDim + p + 64] = vb1;
+    for (int i0 = wave; i0 < kk; i0 += 2 * kMfWaves) {    // two rows' loads in flight
+      float q0[2], q1[2], k0[2], k1[2], v0[2], v1[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+        load_qkv_pair(a, sv, r0 + min(i0 + u * kMfWaves, kk - 1), h, p, q0[u], q1[u], k0[u], k1[u], v0[u], v1[u]);
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int i = i0 + u * kMfWaves;
+        if (i >= kk) break;                               // wave-uniform
+        qs[i * kHeadDim + p] = q0[u] * cs - q1[u] * sn;
+        qs[i * kHeadDim + p + 64] = q1[u] * cs + q0[u] * sn;
+        const uint16_t kb0 = f32_to_bf16_rne(k0[u] * cs - k1[u] * sn), kb1 = f32_to_bf16_rne(k1[u] * cs + k0[u] * sn);
+        const uint16_t vb0 = f32_to_bf16_rne(v0[u]), vb1 = f32_to_bf16_rne(v1[u]);
+        const size_t slot = ((size_t)a.step * a.hist_rows + r0 + i) * a.H + h * kHeadDim;
+        a.k_hist[slot + p] = kb0;
+        a.k_hist[slot + p + 64] = kb1;
+        a.v_hist[slot + p] = vb0;
+        a.v_hist[slot + p + 64] = vb1;
+        ks[i * kHeadDim + p] = kb0;
+        ks[i * kHeadDim + p + 64] = kb1;
+        vs[i * kHeadDim + p] = vb0;
+        vs[i * kHeadDim + p + 64] = vb1;
+      }
+    }
   }
   for (int t = tid; t < kk * 32; t += kMfThreads) {   // walk the parent slots back from row i to call number c
     const int i = t >> 5, c = t & 31;
@@ -803,7 +838,7 @@ __global__ __launch_bounds__(kMfThreads) void body_attention_mfma_kernel(BodyAtt
     anc[i * 32 + c] = cur;
   }
   if (h == 0 && a.step >= 1 && tid < kk) a.par_hist[a.step * a.hist_rows + r0 + tid] = a.beam_parent_slot[r0 + tid];
-  for (int e = tid; e < kSeqRows * ppitch / 2; e += kMfThreads) {   // rows and keys that do not exist weigh nothing
+  for (int e = tid; e < kSeqRows * m.ppitch / 2; e += kMfThreads) {   // rows and keys that do not exist weigh nothing
     reinterpret_cast<uint32_t*>(ph)[e] = 0u;
     reinterpret_cast<uint32_t*>(pl)[e] = 0u;
   }
@@ -829,25 +864,23 @@ __global__ __launch_bounds__(kMfThreads) void body_attention_mfma_kernel(BodyAtt
           acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kfr, qh[s4], acc, 0, 0, 0);
           acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kfr, ql[s4], acc, 0, 0, 0);
         }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {                                // accumulator e: key 4 * (lane >> 4) + e, row lane & 15
-          const int key = t * 16 + q4 * 4 + e;
-          if (key < L) sct[key * kSeqRows + row] = acc[e] * scale;
-        }
+        const int key = t * 16 + q4 * 4;                             // accumulator e: key + e of row lane & 15
+        if (key < L) *reinterpret_cast<f32x4*>(sct + row * m.spitch + key) = acc * scale;   // spitch holds the last piece
       }
     }
   }
-  // ---- the prompt's values for this wave's two d tiles (first 256 keys): on their way from here on ----------------
-  // lane (d, kq) of the A operand holds 8 consecutive keys of element d
-  const int nstep = Lp >> 5;
+  // ---- the prompt's values for this wave's first two steps of 32 keys: on their way from here on -----------------
+  // lane (m, kq) holds, for the 8 keys 32 st + 8 kq + j, the d 8m .. 8m + 7; step st belongs to wave st mod 4
+  const int nstep = (L + 31) >> 5;
   u32x4 vf[2][8];
   auto load_values = [&](int st0) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const uint16_t* vp = a.Vt + ((size_t)b * a.H + h * kHeadDim + (wave * 2 + j) * 16 + row) * Lp + q4 * 8;
+    for (int u = 0; u < 2; ++u)
 #pragma unroll
-      for (int u = 0; u < 8; ++u) vf[j][u] = *reinterpret_cast<const u32x4*>(vp + min(st0 + u, nstep - 1) * 32);
-    }
+      for (int j = 0; j < 8; ++j) {
+        const int key = min((st0 + wave + kMfWaves * u) * 32 + q4 * 8 + j, L - 1);
+        vf[u][j] = *reinterpret_cast<const u32x4*>(a.Vp + ((size_t)(b * L + key) * a.H + h * kHeadDim + row * 8));
+      }
   };
   load_values(0);
   // ---- the rows' ancestors and themselves: four threads per (row, key) pair, 32 elements each ---------------------
@@ -870,62 +903,77 @@ __global__ __launch_bounds__(kMfThreads) void body_attention_mfma_kernel(BodyAtt
       }
     dot += dpp_move_f32<0xB1>(dot);       // the four quarters of the key: lanes ^1, then ^2 (fixed order)
     dot += dpp_move_f32<0x4E>(dot);
-    if (qd == 0) sct[(L + c) * kSeqRows + i] = dot * scale;
+    if (qd == 0) aw[e] = dot * scale;
   }
   __syncthreads();
   // ---- softmax weights: wave w takes rows w, w + 4, ...; the prompt's weights as two bf16 halves ------------------
-  for (int i = wave; i < kk; i += kMfThreads / 64) {
-    float mx = -INFINITY;
-    for (int j = lane; j < n_vis; j += 64) mx = fmaxf(mx, sct[j * kSeqRows + i]);
+  for (int i = wave; i < kk; i += kMfWaves) {
+    const float* sr = sct + i * m.spitch;
+    float* ar = aw + i * (a.step + 1);
+    float mx = (lane <= a.step) ? ar[lane] : -INFINITY;              // at most DDD_DMAX of them
+    for (int j = lane; j < L; j += 64) mx = fmaxf(mx, sr[j]);
     mx = wave_max_f32(mx);
     float sum = 0.f;
-    for (int j = lane; j < n_vis; j += 64) {
-      const float p = __expf(sct[j * kSeqRows + i] - mx);
+    for (int j = lane; j < L; j += 64) {
+      const float p = __expf(sr[j] - mx);
       sum += p;
-      if (j < L) {
-        const uint16_t hi = f32_to_bf16_rne(p);
-        ph[i * ppitch + j] = hi;
-        pl[i * ppitch + j] = f32_to_bf16_rne(p - bf16_to_f32(hi));
-      } else {
-        sct[j * kSeqRows + i] = p;
-      }
+      const uint16_t hi = f32_to_bf16_rne(p);
+      ph[i * m.ppitch + j] = hi;
+      pl[i * m.ppitch + j] = f32_to_bf16_rne(p - bf16_to_f32(hi));
+    }
+    if (lane <= a.step) {
+      const float p = __expf(ar[lane] - mx);
+      sum += p;
+      ar[lane] = p;
     }
     sum = wave_sum_f32(sum);
     if (lane == 0) rsum[i] = sum;
   }
   __syncthreads();
-  // ---- the prompt's part of the outputs: wave w takes d tiles 2w and 2w + 1 --------------------------------------
+  // ---- the prompt's part of the outputs, this wave's keys ----------------------------------------------------------
   {
-    f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-    for (int st0 = 0; st0 < nstep; st0 += 8) {
+    f32x4 acc[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int st0 = 0; st0 < nstep; st0 += 2 * kMfWaves) {
       if (st0 > 0) load_values(st0);
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int st = st0 + u;
-        if (st >= nstep) continue;                                   // uniform
+      for (int u = 0; u < 2; ++u) {
+        const int st = st0 + wave + kMfWaves * u;
+        if (st >= nstep) continue;                                   // wave-uniform
         // B operand: weights of row `row`, keys 32 st + 8 q4 .. + 7
-        const bf16x8 bh = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(ph + row * ppitch + st * 32 + q4 * 8));
-        const bf16x8 bl = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(pl + row * ppitch + st * 32 + q4 * 8));
+        const bf16x8 bh = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(ph + row * m.ppitch + st * 32 + q4 * 8));
+        const bf16x8 bl = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(pl + row * m.ppitch + st * 32 + q4 * 8));
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const bf16x8 af = __builtin_bit_cast(bf16x8, vf[j][u]);
-          acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bh, acc[j], 0, 0, 0);
-          acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bl, acc[j], 0, 0, 0);
+        for (int t = 0; t < 8; ++t) {                                // element t of every key's piece: keys j, j + 1 in a word
+          u32x4 f;
+#pragma unroll
+          for (int x = 0; x < 4; ++x)
+            f[x] = __builtin_amdgcn_perm(vf[u][2 * x + 1][t >> 1], vf[u][2 * x][t >> 1], (t & 1) ? 0x07060302u : 0x05040100u);
+          const bf16x8 af = __builtin_bit_cast(bf16x8, f);
+          acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bh, acc[t], 0, 0, 0);
+          acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bl, acc[t], 0, 0, 0);
         }
       }
     }
-    // the queries are no longer needed: their place takes the outputs (accumulator e: d 4 * (lane >> 4) + e of the tile)
+    __syncthreads();                                                 // every wave is done with the scores and the weights
+    // accumulator e of tile t: row lane & 15, d = 8 (4 q4 + e) + t
+    float* o = outs + (wave * kSeqRows + row) * kMfOutPitch + q4 * 32;
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) qs[row * kHeadDim + (wave * 2 + j) * 16 + q4 * 4 + e] = acc[j][e];
+    for (int e = 0; e < 4; ++e) {
+      *reinterpret_cast<f32x4*>(o + e * 8) = f32x4{acc[0][e], acc[1][e], acc[2][e], acc[3][e]};
+      *reinterpret_cast<f32x4*>(o + e * 8 + 4) = f32x4{acc[4][e], acc[5][e], acc[6][e], acc[7][e]};
+    }
   }
   __syncthreads();
   // ---- ancestors and the row itself, normalisation: the values of four ancestors in flight ------------------------
   {
     const int d = tid & (kHeadDim - 1);
     for (int i = tid >> 7; i < kk; i += kMfThreads / kHeadDim) {
-      float o = qs[i * kHeadDim + d];
+      float o = 0.f;
+#pragma unroll
+      for (int w = 0; w < kMfWaves; ++w) o += outs[(w * kSeqRows + i) * kMfOutPitch + d];   // fixed order
+      const float* ar = aw + i * (a.step + 1);
       const uint16_t* vh = a.v_hist + (size_t)h * kHeadDim + d;
       int c = 0;
       for (; c + 3 < a.step; c += 4) {
@@ -933,49 +981,13 @@ __global__ __launch_bounds__(kMfThreads) void body_attention_mfma_kernel(BodyAtt
 #pragma unroll
         for (int u = 0; u < 4; ++u) v[u] = vh[((size_t)(c + u) * a.hist_rows + anc[i * 32 + c + u]) * a.H];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) o += sct[(L + c + u) * kSeqRows + i] * bf16_to_f32(v[u]);
+        for (int u = 0; u < 4; ++u) o += ar[c + u] * bf16_to_f32(v[u]);
       }
-      for (; c < a.step; ++c) o += sct[(L + c) * kSeqRows + i] * bf16_to_f32(vh[((size_t)c * a.hist_rows + anc[i * 32 + c]) * a.H]);
-      o += sct[(n_vis - 1) * kSeqRows + i] * bf16_to_f32(vs[i * kHeadDim + d]);
+      for (; c < a.step; ++c) o += ar[c] * bf16_to_f32(vh[((size_t)c * a.hist_rows + anc[i * 32 + c]) * a.H]);
+      o += ar[a.step] * bf16_to_f32(vs[i * kHeadDim + d]);
       a.o[(size_t)(r0 + i) * a.H + h * kHeadDim + d] = f32_to_bf16_rne(o / rsum[i]);
     }
   }
-}
-
-// Vt[b][e][key] = Vp[b][key][e]: one workgroup per (sequence, block of 128 elements, block of 128 keys); a thread
-// writes 64 keys of one element, a whole cache line.
-constexpr int kPackKeys = 128;
-__global__ __launch_bounds__(256) void pack_prompt_values_kernel(const uint16_t* __restrict__ Vp, uint16_t* __restrict__ Vt,
-                                                                 int H, int L, int Lp) {
-  __shared__ uint16_t tile[kPackKeys][kHeadDim + 8];
-  const int nhb = H / kHeadDim;
-  const int b = blockIdx.x / nhb, hb = blockIdx.x % nhb, k0 = blockIdx.y * kPackKeys, tid = threadIdx.x;
-  for (int c = tid; c < kPackKeys * 16; c += 256) {         // 16-byte pieces, whole rows of the cache
-    const int kin = c >> 4, pc = c & 15, key = k0 + kin;
-    u32x4 u = {0u, 0u, 0u, 0u};
-    if (key < L) u = *reinterpret_cast<const u32x4*>(Vp + ((size_t)(b * L + key) * H + hb * kHeadDim + pc * 8));
-    *reinterpret_cast<u32x4*>(&tile[kin][pc * 8]) = u;
-  }
-  __syncthreads();
-  const int d = tid & (kHeadDim - 1), kh = tid >> 7;          // keys k0 + 64 kh .. + 63 of element d
-  uint16_t* dst = Vt + ((size_t)b * H + hb * kHeadDim + d) * Lp + k0 + kh * 64;
-#pragma unroll
-  for (int g = 0; g < 8; ++g) {
-    if (k0 + kh * 64 + g * 8 >= Lp) break;                    // Lp is a multiple of 32
-    u32x4 o;
-#pragma unroll
-    for (int x = 0; x < 4; ++x) {
-      const uint32_t lo = tile[kh * 64 + g * 8 + 2 * x][d], hi = tile[kh * 64 + g * 8 + 2 * x + 1][d];
-      o[x] = lo | (hi << 16);
-    }
-    *reinterpret_cast<u32x4*>(dst + g * 8) = o;
-  }
-}
-
-hipError_t launch_pack_prompt_values(const uint16_t* Vp, uint16_t* Vt, int B, int H, int L, int Lp, hipStream_t stream) {
-  hipLaunchKernelGGL(pack_prompt_values_kernel, dim3(B * (H / kHeadDim), (Lp + kPackKeys - 1) / kPackKeys), dim3(256), 0,
-                     stream, Vp, Vt, H, L, Lp);
-  return hipGetLastError();
 }
 
 static size_t attention_seq_lds(int n_vis) {
@@ -986,7 +998,7 @@ static size_t attention_seq_lds(int n_vis) {
 hipError_t launch_body_attention(const BodyAttnArgs& a, hipStream_t stream) {
   const int n_vis = a.L + a.step + 1;
   // batched rounds with a prompt: one workgroup per (sequence, head), the prompt part on the matrix cores
-  if (a.R > kBodyRows && a.k <= kSeqRows && a.Vt != nullptr && attention_mfma_lds(a.Lp, n_vis) <= 150 * 1024) {
+  if (a.R > kBodyRows && a.k <= kSeqRows && a.L >= kMfLeast && mf_lds(a.L, a.step).total <= 150 * 1024) {
     static bool prepared_mf = false;
     if (!prepared_mf) {
       const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&body_attention_mfma_kernel),
@@ -996,7 +1008,7 @@ hipError_t launch_body_attention(const BodyAttnArgs& a, hipStream_t stream) {
     }
     const int n_seq = (a.step == 0) ? a.R : a.R / a.k;
     hipLaunchKernelGGL(body_attention_mfma_kernel, dim3(n_seq * (a.H / kHeadDim)), dim3(kMfThreads),
-                       attention_mfma_lds(a.Lp, n_vis), stream, a);
+                       mf_lds(a.L, a.step).total, stream, a);
     return hipGetLastError();
   }
   // ... without one (or with one too long for the LDS): the same by ordinary arithmetic

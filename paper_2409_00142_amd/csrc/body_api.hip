@@ -32,8 +32,6 @@ struct ddd_body {
   float* part;       // fp32 [part_cap] partial sums of the split product in flight
   long long part_cap;
   int32_t* n_act;    // [1]
-  uint16_t* vt;      // bf16 [B][H][Lp] the prompt's values, keys contiguous (null if rows <= kBodyRows or L < 32);
-  int Lp;            //   rewritten by the prompt call of every round
 };
 
 namespace {
@@ -211,8 +209,6 @@ int ddd_body_create(const ddd_body_config* cfg, ddd_body** out) {
     const long long sums = (long long)R * 3 * H, chip = (long long)body_grid(b) * 192 * (R < 320 ? (R + 63) / 64 * 64 : 320);
     b->part_cap = sums > chip ? sums : chip;
     if (e == hipSuccess) e = hipMalloc(&b->part, (size_t)b->part_cap * sizeof(float));
-    b->Lp = (cfg->L + 31) & ~31;
-    if (e == hipSuccess && cfg->L >= 32) e = hipMalloc(&b->vt, (size_t)cfg->B * H * b->Lp * sizeof(uint16_t));
   }
   if (e != hipSuccess) {
     ddd_body_destroy(b);
@@ -233,7 +229,6 @@ int ddd_body_destroy(ddd_body* b) {
   (void)hipFree(b->v_hist);
   (void)hipFree(b->par_hist);
   (void)hipFree(b->x0);
-  (void)hipFree(b->vt);
   (void)hipFree(b->row_list);
   (void)hipFree(b->row_pos);
   (void)hipFree(b->part);
@@ -323,10 +318,6 @@ int ddd_body_step(void* user, int32_t step, const ddd_state* st, void* hid_out, 
   t.step = step;
   t.R = R;
   t.hist_rows = (int)hist_rows;
-  t.Vt = b->vt;
-  t.Lp = b->Lp;
-  if (step == 0 && b->vt != nullptr)   // the round's prompt, laid out for the batched attention's second contraction
-    BODY_HIP(launch_pack_prompt_values(t.Vp, b->vt, b->cfg.B, H, b->cfg.L, b->Lp, s));
   RmsNormArgs n2 = n1;
   n2.g = b->w.g2;
 

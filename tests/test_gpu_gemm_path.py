@@ -82,3 +82,62 @@ def test_split_linear(gpu, N, K, R):
     assert torch.equal(y[0], y[1])
     assert float((y[0].double() - want).abs().max()) <= 1e-4
     assert float((acc.double() - 2 * want).abs().max()) <= 2e-4
+
+
+@pytest.mark.parametrize("L", [0, 5, 31, 32, 33, 64, 250, 257, 545])
+@pytest.mark.parametrize("k", [3, 10, 16])
+def test_batched_attention_of_any_prompt_length(gpu, L, k):
+    """Draft layer, several sequences per call (batched attention: the prompt on the matrix cores from 32 positions on,
+    whole steps of 32 keys or not) against the same sequences one at a time (at most 16 rows: the weight streams).
+    One sequence stops before the third call.
+
+    Tolerance: both sides round at the same five points of a call, what lies between them is summed in another order,
+    and a rounding that falls the other way moves a term by one bf16 ulp (2^-8): 2^-5 of the row's rms, as against the oracle."""
+    torch, D = gpu
+    print(f"[case] batched_attention L={L} k={k}", flush=True)
+    B, H, F, V, calls = 7, 256, 384, 300, 4
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1000 * k + L)
+
+    def normal(*shape, std=1.0, dtype=torch.bfloat16):
+        return torch.empty(shape, dtype=dtype, device="cuda").normal_(0, std, generator=g)
+
+    w = {"E": normal(V, H), "Wfc": normal(H, 2 * H, std=(2 * H) ** -0.5), "g1": normal(H, dtype=torch.float32),
+         "Wqkv": normal(3 * H, H, std=H ** -0.5), "Wo": normal(H, H, std=H ** -0.5), "g2": normal(H, dtype=torch.float32),
+         "Wgu": normal(2 * F, H, std=H ** -0.5), "Wd": normal(H, F, std=F ** -0.5)}
+    p = {"K": normal(B, max(L, 1), H), "V": normal(B, max(L, 1), H), "f_root": normal(B, H),
+         "root_token": torch.randint(0, V, (B,), generator=g, device="cuda", dtype=torch.int32)}
+    tok = torch.randint(0, V, (calls, B, k), generator=g, device="cuda", dtype=torch.int32)
+    slot = torch.randint(0, k, (calls, B, k), generator=g, device="cuda", dtype=torch.int32)
+    slot[1] = 0
+
+    def layer(seqs):
+        n = len(seqs)
+        body = D.ddd_body_create(D.ddd_body_config(n, k, H, F, V, calls, L))
+        pp = {name: t[seqs].contiguous() for name, t in p.items()}
+        D.ddd_body_bind(body, w, pp)
+        st, t = D.alloc_state(D.make_config(n, H, V, k, calls, 10, 0.0))
+        out = []
+        try:
+            for s in range(calls):
+                t["beam_token"].copy_(tok[s][seqs])
+                t["beam_parent_slot"].copy_(slot[s][seqs])
+                if s == 2 and n > 1:
+                    t["row_active"][2 * k:3 * k] = 0
+                h = torch.zeros(n if s == 0 else n * k, H, dtype=torch.bfloat16, device="cuda")
+                D.ddd_body_step(body, s, st, h)
+                torch.cuda.synchronize()
+                out.append(h.float().reshape(n, -1, H))
+        finally:
+            D.ddd_body_destroy(body)
+        return out
+
+    got = layer(list(range(B)))
+    for b in range(B):
+        want = layer([b])
+        for s in range(calls):
+            if b == 2 and s >= 2:
+                assert float(got[s][b].abs().max()) == 0.0
+                continue
+            rms = want[s][0].square().mean(-1, keepdim=True).sqrt()
+            assert float(((got[s][b] - want[s][0]).abs() / rms).max()) <= 2 ** -5, (b, s)
