@@ -45,6 +45,12 @@ struct ddd_ctx {
   ddd_round_stats stats;         // caller's statistics arrays (all null: none bound)
   bool stats_on;
   uint32_t* stats_sync;          // device [2]: arrivals and deepest sequence of the verify launch in flight (zero between)
+  // ddd_verify_sample of small batches: the sums of every row (null: the batch is too large for it).  The array belongs to
+  // the first stream that uses it: calls on one stream are ordered, calls on any other take the kernel without scratch.
+  void* sample_rows;
+  bool sample_owned;
+  hipStream_t sample_stream;
+  std::mutex sample_mutex;       // held over the two launches, so that two threads' calls do not interleave on the stream
   uint64_t* trace;               // null, or device [DDD_DMAX + 1][kTraceCallWords]: stamps of every draft call's kernels
   size_t part_key_bytes, part_sum_bytes, logits_bytes, grp_bytes;   // sizes of the scratch arrays (DDD_FLAG_POISON_SCRATCH)
 };
@@ -80,6 +86,12 @@ bool pick_split(int H, int* G, int* nw) {
 
 // Row pitch of the context's own logits: whole 128-byte lines.
 int logits_pitch(int V) { return (V + 31) & ~31; }
+
+// Whether ddd_verify_sample makes the sums of all rows first (tree.hip): the chip reads 128 MB of logits in about 26 us
+// and the walk behind it takes 8; a walk that makes the sums of its own three to five rows takes 40 to 60 us.
+bool rows_from_sums(const ddd_config& c) {
+  return (long long)c.B * (c.m + 1) * c.V * 4 <= (128LL << 20) && (long long)c.B * (c.m + 1) <= 8192;
+}
 
 bool state_ok(const ddd_state* s) {
   return s && s->logprobsum && s->beam_node && s->beam_token && s->beam_parent_slot && s->pool_token &&
@@ -263,7 +275,8 @@ size_t ddd_pool_capacity(const ddd_config* cfg) {
 size_t ddd_scratch_bytes(const ddd_config* cfg) {
   if (ddd_config_validate(cfg) != DDD_OK) return 0;
   const size_t rows = (size_t)cfg->B * cfg->k, max_slices = (cfg->k > DDD_KMAX) ? 1 : 512;
-  size_t n = rows * max_slices * cfg->k * sizeof(uint64_t) + rows * max_slices * sizeof(float) + rows * 4 + 4;
+  const size_t sample = rows_from_sums(*cfg) ? (size_t)cfg->B * (cfg->m + 1) * verify_sample_row_bytes() : 0;
+  size_t n = sample + rows * max_slices * cfg->k * sizeof(uint64_t) + rows * max_slices * sizeof(float) + rows * 4 + 4;
   if (rows > DDD_STREAM_ROWS || cfg->k > DDD_KMAX)   // logits and per-group statistics of the GEMM path
     n += rows * (size_t)logits_pitch(cfg->V) * sizeof(float) + 2 * rows * (size_t)(((cfg->V + 63) / 64 + 3) & ~3) * sizeof(float);
   return n;
@@ -327,6 +340,9 @@ int ddd_create(const ddd_config* cfg, ddd_ctx** out) {
   c->active_mask = nullptr;
   c->stats_sync = nullptr;
   c->stats_on = false;
+  c->sample_rows = nullptr;
+  c->sample_owned = false;
+  c->sample_stream = nullptr;
   c->stats = ddd_round_stats{nullptr, nullptr, nullptr, nullptr, nullptr};
   c->progress = nullptr;
   c->progress_dev = nullptr;
@@ -340,6 +356,8 @@ int ddd_create(const ddd_config* cfg, ddd_ctx** out) {
   if (e == hipSuccess) e = hipMemset(c->stats_sync, 0, 2 * sizeof(uint32_t));
   if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&c->active_mask), (DDD_BMAX / 64) * sizeof(uint64_t));
   if (e == hipSuccess) e = hipMemset(c->active_mask, 0, (DDD_BMAX / 64) * sizeof(uint64_t));
+  if (e == hipSuccess && rows_from_sums(*cfg))
+    e = hipMalloc(&c->sample_rows, (size_t)cfg->B * (cfg->m + 1) * verify_sample_row_bytes());
   void* host_words = nullptr;
   if (e == hipSuccess)
     e = hipHostMalloc(&host_words, (DDD_DMAX + 1) * sizeof(uint32_t), hipHostMallocMapped | hipHostMallocCoherent);
@@ -354,6 +372,7 @@ int ddd_create(const ddd_config* cfg, ddd_ctx** out) {
     if (c->call_count) (void)hipFree(c->call_count);
     if (c->active_mask) (void)hipFree(c->active_mask);
     if (c->stats_sync) (void)hipFree(c->stats_sync);
+    if (c->sample_rows) (void)hipFree(c->sample_rows);
     if (host_words) (void)hipHostFree(host_words);
     if (c->logits) (void)hipFree(c->logits);
     if (c->grp_max) (void)hipFree(c->grp_max);
@@ -385,6 +404,7 @@ int ddd_destroy(ddd_ctx* c) {
   (void)hipFree(c->call_count);
   (void)hipFree(c->active_mask);
   (void)hipFree(c->stats_sync);
+  if (c->sample_rows) (void)hipFree(c->sample_rows);
   (void)hipHostFree(const_cast<uint32_t*>(c->progress));
   delete c;
   return DDD_OK;
@@ -763,7 +783,25 @@ int ddd_verify_sample(ddd_ctx* c, const ddd_tree* tree, const float* target_logi
   a.m = c->cfg.m;
   a.D = c->cfg.max_depth;
   a.V = c->cfg.V;
-  DDD_HIP(launch_verify_sample(a, static_cast<hipStream_t>(stream)));
+  a.rows = nullptr;
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  std::unique_lock<std::mutex> lock(c->sample_mutex, std::defer_lock);
+  if (c->sample_rows != nullptr && s != hipStreamPerThread) {   // that handle is another stream in every thread
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &capture) != hipSuccess) {
+      (void)hipGetLastError();
+      capture = hipStreamCaptureStatusActive;
+    }
+    if (capture == hipStreamCaptureStatusNone) {   // a graph could be launched on another stream
+      lock.lock();
+      if (!c->sample_owned) {
+        c->sample_owned = true;
+        c->sample_stream = s;
+      }
+      if (c->sample_stream == s) a.rows = c->sample_rows;
+    }
+  }
+  DDD_HIP(launch_verify_sample(a, s));
   return DDD_OK;
 }
 

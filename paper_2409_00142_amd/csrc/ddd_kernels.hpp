@@ -220,7 +220,9 @@ struct VerifySampleArgs {
   int32_t* bonus_token;          // [B]
   float temperature;
   int B, m, D, V;
+  void* rows;                    // null, or scratch of verify_sample_row_bytes() per row of logits: the sums of all rows first
 };
+size_t verify_sample_row_bytes();
 hipError_t launch_verify_sample(const VerifySampleArgs& a, hipStream_t stream);
 
 // Tree attention over the final tree's mask (tree_attn.hip); heads of 128.

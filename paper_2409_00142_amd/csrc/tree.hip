@@ -101,52 +101,81 @@ hipError_t launch_verify_accept(const VerifyArgs& a, hipStream_t stream) {
 // accepted the bonus token is the first j whose prefix sum of the remaining weights exceeds
 // u_bonus[node] * rem.  Every decision is taken in fp64.
 //
-// One workgroup of 16 waves per sequence walks the accepted path.  Per node, one pass for the row
-// maximum and one for the weights: the row is cut into 128 blocks of consecutive tokens (8 per
-// wave, coalesced loads, fixed summation order) whose sums stay in LDS, so the bonus draw only has
-// to look inside the one block in which the prefix sum passes the threshold.
+// A row is cut into 128 blocks of consecutive tokens (coalesced loads, fixed summation order) whose sums of weights are
+// kept, so the bonus draw only has to look inside the one block in which the prefix sum passes the threshold.
+//
+// The walk is a chain - which row is next depends on the decision at this one - and a row of 32 000 fp64 exponentials
+// keeps one CU busy for about 8 us, so the two ways of doing it differ in where the rows' sums are made:
+//  * small batches (verify_sample_from_sums): a first launch makes the sums of every row of every tree with the whole
+//    chip (23 us for 62 MB: fp64 issue, 8 cycles an instruction), and the walk that follows looks numbers up: B = 8, V = 32000, 61 nodes,
+//    41 to 65 us a call by the depth of the accepted paths -> 30 us, B = 1 24 to 37 -> 15 us.  It reads m + 1 rows per sequence instead of two or three.
+//  * beyond that (verify_sample_kernel): one workgroup of 16 waves per sequence makes the sums of the rows it visits.
+// The line lies where the extra rows would cost what they save (rows_from_sums).
 constexpr int kVsWaves = 16;
 constexpr int kVsThreads = kVsWaves * kWave;
 constexpr int kVsSubPerWave = 8;
 constexpr int kVsSub = kVsWaves * kVsSubPerWave;     // 128 = two per lane of the wave that draws the bonus
 constexpr int kVsMaxRemoved = 128;                   // children of one node <= beam width <= 128
+constexpr int kVsChunk = 4 * kWave;                  // tokens one wave loads per instruction
 
-// exp(a) for a <= 0 to about 1e-14 relative: a = n ln2 + r, |r| <= ln2 / 2, Taylor polynomial of
-// degree 11 in r (remainder below 7e-15), scaled by 2^n.  Arguments below -800 give 0.  Every
-// instruction of a 64-wide wave costs four cycles here whatever its precision, and this function
-// is most of what the kernel executes, hence the short polynomial: the decisions need the weights
-// to about 1e-13, not to the last bit.
-__device__ __forceinline__ double exp_nonpos(double a) {
-  a = fmax(a, -800.0);
-  const double n = __builtin_rint(a * 1.4426950408889634074);
-  double r = fma(n, -6.93147180369123816490e-01, a);      // ln2, high part
-  r = fma(n, -1.90821492927058770002e-10, r);             // ln2, low part
-  double p = 1.0 / 39916800.0;
-  p = fma(p, r, 1.0 / 3628800.0);
-  p = fma(p, r, 1.0 / 362880.0);
-  p = fma(p, r, 1.0 / 40320.0);
-  p = fma(p, r, 1.0 / 5040.0);
-  p = fma(p, r, 1.0 / 720.0);
-  p = fma(p, r, 1.0 / 120.0);
-  p = fma(p, r, 1.0 / 24.0);
-  p = fma(p, r, 1.0 / 6.0);
-  p = fma(p, r, 0.5);
-  p = fma(p, r, 1.0);
-  p = fma(p, r, 1.0);
+// exp(d / T) for d = x - max <= 0 as 2^(d * beta2), beta2 = log2(e) / T: n = the nearest integer of the exponent, f the
+// exact rest, and a polynomial of degree 10 through the Chebyshev nodes of [-1/2, 1/2] (3e-16).  The difference from
+// the row maximum is taken first (exact for the logits that matter), so the weight of the maximum is 1 and the error of
+// the others 2e-15 at T = 1, that of a row's sum 1e-16 (a Taylor polynomial of degree 11 around exp(x / T - max / T), as before:
+// 9e-15 and 5e-16).  19 instructions of fp64 issue per token, most of what the kernels execute.  Exactly 0 for -inf.
+__device__ __forceinline__ double weight_of(double d, double beta2) {
+  const double t = fmax(d * beta2, -1200.0);
+  const double n = __builtin_rint(t);
+  const double f = t - n;
+  double p = 7.072585949269223e-09;
+  p = fma(p, f, 1.0208690299958306e-07);
+  p = fma(p, f, 1.321544258792169e-06);
+  p = fma(p, f, 1.5252657260200837e-05);
+  p = fma(p, f, 0.0001540353044173605);
+  p = fma(p, f, 0.0013333558230164974);
+  p = fma(p, f, 0.009618129107606888);
+  p = fma(p, f, 0.05550410866444772);
+  p = fma(p, f, 0.24022650695910097);
+  p = fma(p, f, 0.69314718055995);
+  p = fma(p, f, 1.0);
   return ldexp(p, (int)n);
 }
-
-__device__ __forceinline__ double wave_sum_f64(double x) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off, 64);
-  return x;
+__device__ __forceinline__ double weight4(const float4& v, double Md, double beta2) {
+  const double e0 = weight_of((double)v.x - Md, beta2), e1 = weight_of((double)v.y - Md, beta2);
+  const double e2 = weight_of((double)v.z - Md, beta2), e3 = weight_of((double)v.w - Md, beta2);
+  return (e0 + e1) + (e2 + e3);
 }
+
 __device__ __forceinline__ double wave_scan_f64(double x, int lane) {   // inclusive prefix over the lanes
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) {
     const double t = __shfl_up(x, off, 64);
     if (lane >= off) x += t;
   }
+  return x;
+}
+__device__ __forceinline__ double wave_sum_f64(double x) {
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off, 64);
+  return x;
+}
+// Sums over the wave of N values per lane at once (N = 4 or 8; N + 6 - log2 N - 1 exchanges instead of 6 N): the sum of
+// value i ends up in the lanes whose top log2 N lane bits are i.
+template <int N>
+__device__ __forceinline__ double wave_sums_f64(double (&v)[N], int lane) {
+  int off = 32;
+#pragma unroll
+  for (int n = N / 2; n >= 1; n >>= 1, off >>= 1) {
+    const bool up = (lane & off) != 0;
+#pragma unroll
+    for (int i = 0; i < n; ++i) {
+      const double keep = up ? v[i + n] : v[i], send = up ? v[i] : v[i + n];
+      v[i] = keep + __shfl_xor(send, off, 64);
+    }
+  }
+  double x = v[0];
+#pragma unroll
+  for (int o = 64 / N / 2; o >= 1; o >>= 1) x += __shfl_xor(x, o, 64);
   return x;
 }
 
@@ -162,37 +191,159 @@ __device__ __forceinline__ float4 load_logits4(const float* x, int j, int lim, b
   v.w = j + 3 < lim ? x[j + 3] : ninf;
   return v;
 }
+__device__ __forceinline__ float max4(float m, const float4& v) { return fmaxf(fmaxf(m, v.x), fmaxf(v.y, fmaxf(v.z, v.w))); }
+__device__ __forceinline__ int chunks_per_block(int V) { return (V + kVsSub * kVsChunk - 1) / (kVsSub * kVsChunk); }
+__device__ __forceinline__ bool rows_aligned(const VerifySampleArgs& a) {
+  return (a.V & 3) == 0 && (reinterpret_cast<uintptr_t>(a.logits) & 15) == 0;
+}
+__device__ __forceinline__ double beta2_of(const VerifySampleArgs& a) { return 1.4426950408889634 / (double)a.temperature; }
 
-constexpr int kVsChunk = 4 * kWave;     // tokens one wave loads per instruction
+// The sequence's tree, read once, and the tokens rejected at the current node.
+struct VsTree {
+  int par[DDD_MMAX + 1], tok[DDD_MMAX + 1];
+  double ua[DDD_MMAX + 1], ub[DDD_MMAX + 1];
+  int rm_tok[kVsMaxRemoved];
+  double rm_w[kVsMaxRemoved];
+};
+__device__ __forceinline__ void load_tree(const VerifySampleArgs& a, int b, int tid, VsTree& t) {
+  const int T = a.m + 1;
+  if (tid < T) {
+    t.par[tid] = a.tree.parent_idx[(size_t)b * T + tid];
+    t.tok[tid] = min(max(a.tree.tree_token[(size_t)b * T + tid], 0), a.V - 1);
+    t.ua[tid] = a.u_accept[(size_t)b * T + tid];
+    t.ub[tid] = a.u_bonus[(size_t)b * T + tid];
+  }
+}
 
+// The children tests of node `cur` by one wave, in tree-index order: lane = tree index base + lane.  kid / kw: whether that
+// index is a child and its token's weight, asked for 64 indices at a time.  Returns the accepted child or -1; rem and
+// nrm: the weight not rejected and the number of rejected tokens (listed in t).
+template <class KidFn>
+__device__ __forceinline__ int test_children(VsTree& t, int n, int lane, double& rem, int& nrm, KidFn kids_of) {
+  int nxt = -1;
+  for (int base = 1; base < n && nxt < 0; base += kWave) {
+    bool kid;
+    double kw, ku;
+    int ktok;
+    kids_of(base, kid, kw, ku, ktok);
+    uint64_t kids = __ballot(kid);
+    while (kids) {
+      const int l = __ffsll((unsigned long long)kids) - 1;
+      kids &= kids - 1;
+      const double w = __shfl(kw, l, 64);
+      const int tk = __shfl(ktok, l, 64);
+      if (__shfl(ku, l, 64) * rem < w) {
+        nxt = base + l;
+        break;
+      }
+      rem -= w;
+      if (lane == 0 && nrm < kVsMaxRemoved) {
+        t.rm_tok[nrm] = tk;
+        t.rm_w[nrm] = w;
+      }
+      ++nrm;
+    }
+  }
+  nrm = min(nrm, kVsMaxRemoved);
+  return nxt;
+}
+
+// Bonus token of a row by one wave: the block in which the prefix sum of the remaining weights passes the threshold (v0,
+// v1: the sums of blocks 2 lane and 2 lane + 1), then the token inside it; -1 if rounding leaves none.
+__device__ __forceinline__ int draw_bonus(const VsTree& t, int nrm, const float* x, double Md, double beta2, double thr, double v0,
+                                          double v1, int sb, int V, bool vec, int lane) {
+  for (int r = 0; r < nrm; ++r) {
+    const int blk = t.rm_tok[r] / sb;
+    if (blk == 2 * lane) v0 -= t.rm_w[r];
+    if (blk == 2 * lane + 1) v1 -= t.rm_w[r];
+  }
+  const double inc = wave_scan_f64(v0 + v1, lane);        // prefix up to and including block 2*lane+1
+  const double before = inc - (v0 + v1);
+  const uint64_t hit = __ballot(inc > thr);
+  if (hit == 0) return -1;
+  const int hl = __ffsll((unsigned long long)hit) - 1;
+  const double bef = __shfl(before, hl, 64), first = __shfl(v0, hl, 64);
+  const bool in_first = bef + first > thr;
+  double run = in_first ? bef : bef + first;
+  for (int jb = (2 * hl + (in_first ? 0 : 1)) * sb; jb < V; jb += kVsChunk) {   // ends inside the block but for rounding
+    const int j = jb + 4 * lane;
+    const float4 v = load_logits4(x, j, V, vec);
+    double w[4] = {weight_of((double)v.x - Md, beta2), weight_of((double)v.y - Md, beta2),
+                   weight_of((double)v.z - Md, beta2), weight_of((double)v.w - Md, beta2)};
+    for (int r = 0; r < nrm; ++r) {
+      const int d = t.rm_tok[r] - j;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (d == e) w[e] = 0.0;
+    }
+    const double c0 = w[0], c1 = c0 + w[1], c2 = c1 + w[2], c3 = c2 + w[3];
+    const double pre = run + (wave_scan_f64(c3, lane) - c3);     // remaining weight before this lane's tokens
+    const int e = pre + c0 > thr ? 0 : pre + c1 > thr ? 1 : pre + c2 > thr ? 2 : pre + c3 > thr ? 3 : 4;
+    const uint64_t over = __ballot(e < 4 && j + e < V);
+    if (over != 0) {
+      const int ol = __ffsll((unsigned long long)over) - 1;
+      return jb + 4 * ol + __shfl(e, ol, 64);
+    }
+    run = __shfl(pre + c3, 63, 64);
+  }
+  return -1;
+}
+
+// Rounding left no prefix above the threshold: the last token that still has weight, and if the children covered
+// everything the target's most likely token.  By the whole block.
+template <int WAVES>
+__device__ __forceinline__ int last_resort(const VsTree& t, int nrm, const float* x, double Md, float temperature, int V, int tid) {
+  __shared__ int s_last[WAVES];
+  __shared__ uint64_t s_key[WAVES];
+  const int lane = tid & 63, wv = tid >> 6;
+  const double beta = 1.0 / (double)temperature;
+  int last = -1;
+  uint64_t key = 0;
+  for (int j = tid; j < V; j += WAVES * kWave) {
+    key = umax64(key, row_key(x[j], j));
+    bool live = exp(((double)x[j] - Md) * beta) > 0.0;
+    for (int r = 0; r < nrm; ++r)
+      if (t.rm_tok[r] == j) live = false;
+    if (live) last = max(last, j);
+  }
+  key = wave_max_u64(key);
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) last = max(last, __shfl_xor(last, off, 64));
+  if (lane == 0) {
+    s_last[wv] = last;
+    s_key[wv] = key;
+  }
+  __syncthreads();
+  last = -1;
+  key = 0;
+#pragma unroll
+  for (int i = 0; i < WAVES; ++i) {
+    last = max(last, s_last[i]);
+    key = umax64(key, s_key[i]);
+  }
+  return last >= 0 ? last : key_token(key);
+}
+
+// ---- one workgroup per sequence makes the sums of the rows it visits --------------------------------------------
 __global__ __launch_bounds__(kVsThreads) void verify_sample_kernel(VerifySampleArgs a) {
   __shared__ float s_max[kVsWaves];
   __shared__ double s_sub[kVsSub];
-  __shared__ int s_rm_tok[kVsMaxRemoved];
-  __shared__ double s_rm_w[kVsMaxRemoved];
-  __shared__ int s_next, s_nrm, s_bonus, s_last[kVsWaves];
-  __shared__ uint64_t s_key[kVsWaves];
-  __shared__ int s_par[DDD_MMAX + 1], s_tok[DDD_MMAX + 1];     // the sequence's tree, read once
-  __shared__ double s_ua[DDD_MMAX + 1], s_ub[DDD_MMAX + 1];
+  __shared__ VsTree t;
+  __shared__ int s_next, s_nrm, s_bonus;
 
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int T = a.m + 1, V = a.V;
-  if (tid < T) {
-    s_par[tid] = a.tree.parent_idx[(size_t)b * T + tid];
-    s_tok[tid] = min(max(a.tree.tree_token[(size_t)b * T + tid], 0), V - 1);
-    s_ua[tid] = a.u_accept[(size_t)b * T + tid];
-    s_ub[tid] = a.u_bonus[(size_t)b * T + tid];
-  }
+  load_tree(a, b, tid, t);
   const int n = min(a.tree.n_sel[b], a.m) + 1;
   StatsPre sp{0, 0u};
   if (tid == 0) sp = stats_begin(a.stats, b, a.B);
   __syncthreads();
   int32_t* path = a.accept_path + (size_t)b * (a.D + 1);
-  const int cpb = (V + kVsSub * kVsChunk - 1) / (kVsSub * kVsChunk);      // chunks per block
+  const int cpb = chunks_per_block(V);
   const int sb = cpb * kVsChunk;                                          // tokens per block
-  const int j0 = wv * kVsSubPerWave * sb;                                 // may lie beyond V
-  const bool vec = (V & 3) == 0 && (reinterpret_cast<uintptr_t>(a.logits) & 15) == 0;
-  const double beta = 1.0 / (double)a.temperature;
+  const int j0 = wv * kVsSubPerWave * sb + 4 * lane;                      // may lie beyond V
+  const bool vec = rows_aligned(a);
+  const double beta2 = beta2_of(a);
 
   int cur = 0, len = 0, nrm = 0;
   double Md = 0.0, rem = 0.0;          // nrm, rem: meaningful in wave 0
@@ -202,24 +353,13 @@ __global__ __launch_bounds__(kVsThreads) void verify_sample_kernel(VerifySampleA
   for (int it = 0; it <= a.D; ++it) {
     x = a.logits + ((size_t)b * T + cur) * V;
     // wave 0: what the children tests will need (tree indices 1..64; larger trees fetch the rest
-    // when they get there), requested now so that it arrives behind the two passes
-    bool kid = false;
-    int ktok = 0;
+    // when they get there), requested now so that it arrives behind the sums
     float kx = 0.0f;
-    double ku = 0.0;
-    if (wv == 0 && 1 + lane < n) {
-      kid = s_par[1 + lane] == cur;
-      ktok = s_tok[1 + lane];
-      kx = x[ktok];
-      ku = s_ua[1 + lane];
-    }
+    if (wv == 0 && 1 + lane < n) kx = x[t.tok[1 + lane]];
     // row maximum
     float mx = -__builtin_inff();
 #pragma unroll 8
-    for (int c = 0; c < kVsSubPerWave * cpb; ++c) {
-      const float4 v = load_logits4(x, j0 + c * kVsChunk + 4 * lane, V, vec);
-      mx = fmaxf(fmaxf(mx, v.x), fmaxf(v.y, fmaxf(v.z, v.w)));
-    }
+    for (int c = 0; c < kVsSubPerWave * cpb; ++c) mx = max4(mx, load_logits4(x, j0 + c * kVsChunk, V, vec));
     mx = wave_max_f32(mx);
     if (lane == 0) s_max[wv] = mx;
     __syncthreads();
@@ -227,51 +367,33 @@ __global__ __launch_bounds__(kVsThreads) void verify_sample_kernel(VerifySampleA
 #pragma unroll
     for (int i = 1; i < kVsWaves; ++i) mx = fmaxf(mx, s_max[i]);
     Md = (double)mx;
-    const double mb = -Md * beta;
     // weights: one sum per block of sb consecutive tokens, in a fixed order
-#pragma unroll 2
-    for (int i = 0; i < kVsSubPerWave; ++i) {
-      double acc = 0.0;
-      for (int c = 0; c < cpb; ++c) {
-        const int j = j0 + (i * cpb + c) * kVsChunk + 4 * lane;
-        const float4 v = load_logits4(x, j, V, vec);
-        const double e0 = exp_nonpos(fma((double)v.x, beta, mb)), e1 = exp_nonpos(fma((double)v.y, beta, mb));
-        const double e2 = exp_nonpos(fma((double)v.z, beta, mb)), e3 = exp_nonpos(fma((double)v.w, beta, mb));
-        acc += (e0 + e1) + (e2 + e3);
+#pragma unroll 1
+    for (int i0 = 0; i0 < kVsSubPerWave; i0 += 4) {
+      double sums[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        double acc = 0.0;
+        for (int c = 0; c < cpb; ++c) acc += weight4(load_logits4(x, j0 + ((i0 + i) * cpb + c) * kVsChunk, V, vec), Md, beta2);
+        sums[i] = acc;
       }
-      acc = wave_sum_f64(acc);
-      if (lane == 0) s_sub[wv * kVsSubPerWave + i] = acc;
+      const double sum = wave_sums_f64<4>(sums, lane);
+      if ((lane & 15) == 0) s_sub[wv * kVsSubPerWave + i0 + (lane >> 4)] = sum;
     }
     __syncthreads();
     if (wv == 0) {
-      rem = 0.0;
-      for (int i = 0; i < kVsSub; ++i) rem += s_sub[i];
-      int nxt = -1;
+      rem = wave_sum_f64(s_sub[2 * lane] + s_sub[2 * lane + 1]);
       nrm = 0;
-      if (len < a.D) {
-        for (int base = 1; base < n && nxt < 0; base += kWave) {
-          if (base > 1) {
-            const int c = base + lane;
-            kid = c < n && s_par[c] == cur;
-            ktok = c < n ? s_tok[c] : 0;
-            kx = x[ktok];
-            ku = c < n ? s_ua[c] : 0.0;
-          }
-          const double kw = exp_nonpos(fma((double)kx, beta, mb));       // this lane's tree index: base + lane
-          uint64_t kids = __ballot(kid);
-          while (kids) {
-            const int l = __ffsll((unsigned long long)kids) - 1;
-            kids &= kids - 1;
-            const double w = __shfl(kw, l, 64);
-            const int tk = __shfl(ktok, l, 64);
-            if (__shfl(ku, l, 64) * rem < w) { nxt = base + l; break; }
-            rem -= w;
-            if (lane == 0 && nrm < kVsMaxRemoved) { s_rm_tok[nrm] = tk; s_rm_w[nrm] = w; }
-            ++nrm;
-          }
-        }
-      }
-      nrm = min(nrm, kVsMaxRemoved);
+      int nxt = -1;
+      if (len < a.D)
+        nxt = test_children(t, n, lane, rem, nrm, [&](int base, bool& kid, double& kw, double& ku, int& ktok) {
+          const int c = base + lane;
+          kid = c < n && t.par[c] == cur;
+          ktok = c < n ? t.tok[c] : 0;
+          if (base > 1) kx = x[ktok];
+          ku = c < n ? t.ua[c] : 0.0;
+          kw = weight_of((double)kx - Md, beta2);
+        });
       if (lane == 0) s_next = nxt;
     }
     __syncthreads();
@@ -282,77 +404,179 @@ __global__ __launch_bounds__(kVsThreads) void verify_sample_kernel(VerifySampleA
     if (tid == 0) path[len] = cur;
   }
 
-  // Bonus token at `cur` (x, Md, s_sub, s_rm_* describe that node): wave 0 finds the block in
-  // which the prefix sum of the remaining weights passes the threshold, then the token inside it.
+  // Bonus token at `cur` (x, Md, s_sub, the rejected tokens describe that node)
   if (wv == 0) {
-    const double thr = s_ub[cur] * rem;
-    double v0 = s_sub[2 * lane], v1 = s_sub[2 * lane + 1];
-    for (int r = 0; r < nrm; ++r) {
-      const int blk = s_rm_tok[r] / sb;
-      if (blk == 2 * lane) v0 -= s_rm_w[r];
-      if (blk == 2 * lane + 1) v1 -= s_rm_w[r];
+    const int bonus = draw_bonus(t, nrm, x, Md, beta2, t.ub[cur] * rem, s_sub[2 * lane], s_sub[2 * lane + 1], sb, V, vec, lane);
+    if (lane == 0) {
+      s_bonus = bonus;
+      s_nrm = nrm;
     }
-    const double inc = wave_scan_f64(v0 + v1, lane);        // prefix up to and including block 2*lane+1
-    const double before = inc - (v0 + v1);
-    const uint64_t hit = __ballot(inc > thr);
-    int bonus = -1;
-    if (hit != 0) {
-      const int hl = __ffsll((unsigned long long)hit) - 1;
-      const double bef = __shfl(before, hl, 64), first = __shfl(v0, hl, 64);
-      const bool in_first = bef + first > thr;
-      double run = in_first ? bef : bef + first;
-      for (int jb = (2 * hl + (in_first ? 0 : 1)) * sb; jb < V; jb += kVsChunk) {   // ends inside the block but for rounding
-        const int j = jb + 4 * lane;
-        const float4 v = load_logits4(x, j, V, vec);
-        const double mb = -Md * beta;
-        double w[4] = {exp_nonpos(fma((double)v.x, beta, mb)), exp_nonpos(fma((double)v.y, beta, mb)),
-                       exp_nonpos(fma((double)v.z, beta, mb)), exp_nonpos(fma((double)v.w, beta, mb))};
-        for (int r = 0; r < nrm; ++r) {
-          const int d = s_rm_tok[r] - j;
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (d == e) w[e] = 0.0;
-        }
-        const double c0 = w[0], c1 = c0 + w[1], c2 = c1 + w[2], c3 = c2 + w[3];
-        const double pre = run + (wave_scan_f64(c3, lane) - c3);     // remaining weight before this lane's tokens
-        const int e = pre + c0 > thr ? 0 : pre + c1 > thr ? 1 : pre + c2 > thr ? 2 : pre + c3 > thr ? 3 : 4;
-        const uint64_t over = __ballot(e < 4 && j + e < V);
-        if (over != 0) {
-          const int ol = __ffsll((unsigned long long)over) - 1;
-          bonus = jb + 4 * ol + __shfl(e, ol, 64);
-          break;
-        }
-        run = __shfl(pre + c3, 63, 64);
-      }
-    }
-    if (lane == 0) { s_bonus = bonus; s_nrm = nrm; }
   }
   __syncthreads();
   int bonus = s_bonus;
-  if (bonus < 0) {
-    // rounding left no prefix above the threshold: the last token that still has weight, and if
-    // the children covered everything the target's most likely token  (block-uniform branch)
-    const int n_removed = s_nrm;
-    int last = -1;
-    uint64_t key = 0;
-    for (int j = tid; j < V; j += kVsThreads) {
-      key = umax64(key, row_key(x[j], j));
-      bool live = exp(((double)x[j] - Md) * beta) > 0.0;
-      for (int r = 0; r < n_removed; ++r)
-        if (s_rm_tok[r] == j) live = false;
-      if (live) last = max(last, j);
-    }
-    key = wave_max_u64(key);
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) last = max(last, __shfl_xor(last, off, 64));
-    if (lane == 0) { s_last[wv] = last; s_key[wv] = key; }
-    __syncthreads();
-    last = -1;
-    key = 0;
-#pragma unroll
-    for (int i = 0; i < kVsWaves; ++i) { last = max(last, s_last[i]); key = umax64(key, s_key[i]); }
-    bonus = last >= 0 ? last : key_token(key);
+  if (bonus < 0) bonus = last_resort<kVsWaves>(t, s_nrm, x, Md, a.temperature, V, tid);   // block-uniform branch
+  if (tid == 0) {
+    for (int i = len + 1; i <= a.D; ++i) path[i] = -1;
+    a.accept_len[b] = len;
+    a.bonus_token[b] = bonus;
+    stats_end(a.stats, sp, a.B, len);
   }
+}
+
+// ---- small batches: the sums of all rows by the whole chip, then the walk -----------------------------------------
+// A row's 128 blocks belong to kVsParts workgroups of 16 blocks; each takes its weights relative to its own maximum, and
+// the walk scales them by exp((part's maximum - row's maximum) / T).
+constexpr int kVsParts = 8, kVsPartSub = kVsSub / kVsParts, kVsPartWaves = 4, kVsPartPerWave = kVsPartSub / kVsPartWaves;
+constexpr int kVsWalkThreads = 256, kVsWalkWaves = kVsWalkThreads / kWave;
+struct VsRow {
+  double sub[kVsSub];          // block sums, each relative to its part's maximum
+  double psum[kVsParts];       // the parts' sums
+  float pmax[kVsParts];        // and maxima
+  float pad[8];
+};
+static_assert(sizeof(VsRow) == 1152, "whole lines");
+static_assert(kVsWalkThreads >= DDD_MMAX + 1, "a thread per tree index");
+
+size_t verify_sample_row_bytes() { return sizeof(VsRow); }
+
+// CPB: chunks of 256 tokens per block, kept in registers between the maximum and the weights (1: V <= 32768, 2:
+// V <= 65536 ...); 0: any V, the logits read twice.
+template <int CPB>
+__global__ __launch_bounds__(kVsPartWaves * kWave) void verify_row_sums_kernel(VerifySampleArgs a) {
+  __shared__ float s_max[kVsPartWaves];
+  __shared__ double s_sub[kVsPartSub];
+  const int part = blockIdx.x, i = blockIdx.y, b = blockIdx.z, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int T = a.m + 1, V = a.V;
+  if (i > min(a.tree.n_sel[b], a.m)) return;                              // uniform: not a node of the tree
+  const float* x = a.logits + ((size_t)b * T + i) * V;
+  VsRow* out = static_cast<VsRow*>(a.rows) + (size_t)b * T + i;
+  const int cpb = CPB > 0 ? CPB : chunks_per_block(V);
+  const int sb = cpb * kVsChunk;
+  const int j0 = (part * kVsPartSub + wv * kVsPartPerWave) * sb + 4 * lane;   // may lie beyond V
+  const bool vec = rows_aligned(a);
+  const double beta2 = beta2_of(a);
+  constexpr int kKeep = CPB > 0 ? CPB : 1;
+  float4 xv[kVsPartPerWave][kKeep];
+  float mx = -__builtin_inff();
+  if (CPB > 0) {
+#pragma unroll
+    for (int q = 0; q < kVsPartPerWave; ++q)
+#pragma unroll
+      for (int c = 0; c < kKeep; ++c) xv[q][c] = load_logits4(x, j0 + (q * kKeep + c) * kVsChunk, V, vec);
+#pragma unroll
+    for (int q = 0; q < kVsPartPerWave; ++q)
+#pragma unroll
+      for (int c = 0; c < kKeep; ++c) mx = max4(mx, xv[q][c]);
+  } else {
+#pragma unroll 8
+    for (int c = 0; c < kVsPartPerWave * cpb; ++c) mx = max4(mx, load_logits4(x, j0 + c * kVsChunk, V, vec));
+  }
+  mx = wave_max_f32(mx);
+  if (lane == 0) s_max[wv] = mx;
+  __syncthreads();
+  mx = fmaxf(fmaxf(s_max[0], s_max[1]), fmaxf(s_max[2], s_max[3]));
+  const bool none = mx == -__builtin_inff();                              // nothing but -inf, or past the vocabulary: no weight
+  const double Md = none ? 0.0 : (double)mx;
+  double sums[kVsPartPerWave];
+#pragma unroll
+  for (int q = 0; q < kVsPartPerWave; ++q) {
+    double acc = 0.0;
+    if (CPB > 0) {
+#pragma unroll
+      for (int c = 0; c < kKeep; ++c) acc += weight4(xv[q][c], Md, beta2);
+    } else {
+      for (int c = 0; c < cpb; ++c) acc += weight4(load_logits4(x, j0 + (q * cpb + c) * kVsChunk, V, vec), Md, beta2);
+    }
+    sums[q] = acc;
+  }
+  const double sum = wave_sums_f64<kVsPartPerWave>(sums, lane);
+  constexpr int kLanes = kWave / kVsPartPerWave;                          // lanes that hold the same block's sum
+  if ((lane & (kLanes - 1)) == 0) {
+    out->sub[part * kVsPartSub + wv * kVsPartPerWave + lane / kLanes] = sum;
+    s_sub[wv * kVsPartPerWave + lane / kLanes] = sum;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    double total = 0.0;
+    for (int q = 0; q < kVsPartSub; ++q) total += s_sub[q];
+    out->psum[part] = total;
+    out->pmax[part] = mx;
+  }
+}
+
+__global__ __launch_bounds__(kVsWalkThreads) void verify_sample_from_sums_kernel(VerifySampleArgs a) {
+  __shared__ VsTree t;
+  __shared__ double s_rem[DDD_MMAX + 1], s_kw[DDD_MMAX + 1];
+  __shared__ float s_max[DDD_MMAX + 1];
+  __shared__ int s_cur, s_nrm, s_bonus;
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int T = a.m + 1, V = a.V;
+  const int n = min(a.tree.n_sel[b], a.m) + 1;
+  const VsRow* rows = static_cast<const VsRow*>(a.rows) + (size_t)b * T;
+  const double beta2 = beta2_of(a);
+  StatsPre sp{0, 0u};
+  if (tid == 0) sp = stats_begin(a.stats, b, a.B);
+  // thread i: the sums of tree index i's row, and its token's logit in its parent's row
+  load_tree(a, b, tid, t);
+  float kx = 0.0f;
+  if (tid >= 1 && tid < n) kx = a.logits[((size_t)b * T + min(max(t.par[tid], 0), T - 1)) * V + t.tok[tid]];
+  if (tid < n) {
+    float pm[kVsParts], mx = -__builtin_inff();
+    double ps[kVsParts], rem = 0.0;
+#pragma unroll
+    for (int p = 0; p < kVsParts; ++p) {
+      pm[p] = rows[tid].pmax[p];
+      ps[p] = rows[tid].psum[p];
+    }
+#pragma unroll
+    for (int p = 0; p < kVsParts; ++p) mx = fmaxf(mx, pm[p]);
+#pragma unroll
+    for (int p = 0; p < kVsParts; ++p) rem += ps[p] * weight_of((double)pm[p] - (double)mx, beta2);
+    s_max[tid] = mx;
+    s_rem[tid] = rem;
+  }
+  __syncthreads();
+  if (tid >= 1 && tid < n) s_kw[tid] = weight_of((double)kx - (double)s_max[min(max(t.par[tid], 0), T - 1)], beta2);
+  __syncthreads();
+  int32_t* path = a.accept_path + (size_t)b * (a.D + 1);
+  int cur = 0, len = 0, nrm = 0;
+  if (wv == 0) {
+    double rem = 0.0;
+    if (lane == 0) path[0] = 0;
+    for (int it = 0; it <= a.D; ++it) {
+      rem = s_rem[cur];
+      nrm = 0;
+      int nxt = -1;
+      if (len < a.D)
+        nxt = test_children(t, n, lane, rem, nrm, [&](int base, bool& kid, double& kw, double& ku, int& ktok) {
+          const int c = base + lane;
+          kid = c < n && t.par[c] == cur;
+          ktok = c < n ? t.tok[c] : 0;
+          ku = c < n ? t.ua[c] : 0.0;
+          kw = c < n ? s_kw[c] : 0.0;
+        });
+      if (nxt < 0) break;
+      cur = nxt;
+      ++len;
+      if (lane == 0) path[len] = cur;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");                // lane 0's list of rejected tokens
+    __builtin_amdgcn_wave_barrier();
+    const VsRow& r = rows[cur];
+    const double scale = weight_of((double)r.pmax[(2 * lane) / kVsPartSub] - (double)s_max[cur], beta2);
+    const int bonus = draw_bonus(t, nrm, a.logits + ((size_t)b * T + cur) * V, (double)s_max[cur], beta2, t.ub[cur] * rem,
+                                 r.sub[2 * lane] * scale, r.sub[2 * lane + 1] * scale, chunks_per_block(V) * kVsChunk, V,
+                                 rows_aligned(a), lane);
+    if (lane == 0) {
+      s_cur = cur;
+      s_nrm = nrm;
+      s_bonus = bonus;
+    }
+  }
+  __syncthreads();
+  int bonus = s_bonus;
+  if (bonus < 0)                                                          // block-uniform
+    bonus = last_resort<kVsWalkWaves>(t, s_nrm, a.logits + ((size_t)b * T + s_cur) * V, (double)s_max[s_cur], a.temperature, V, tid);
   if (tid == 0) {
     for (int i = len + 1; i <= a.D; ++i) path[i] = -1;
     a.accept_len[b] = len;
@@ -362,7 +586,25 @@ __global__ __launch_bounds__(kVsThreads) void verify_sample_kernel(VerifySampleA
 }
 
 hipError_t launch_verify_sample(const VerifySampleArgs& a, hipStream_t stream) {
-  if (a.m > DDD_MMAX) return hipErrorInvalidValue;      // the kernel keeps the tree in LDS
+  if (a.m > DDD_MMAX) return hipErrorInvalidValue;      // the kernels keep the tree in LDS
+  const int cpb = (a.V + kVsSub * kVsChunk - 1) / (kVsSub * kVsChunk);   // chunks of 256 tokens per block
+  if (a.rows != nullptr) {
+    const dim3 grid(kVsParts, a.m + 1, a.B), block(kVsPartWaves * kWave);
+    if (cpb == 1)
+      hipLaunchKernelGGL((verify_row_sums_kernel<1>), grid, block, 0, stream, a);
+    else if (cpb == 2)
+      hipLaunchKernelGGL((verify_row_sums_kernel<2>), grid, block, 0, stream, a);
+    else if (cpb == 3)
+      hipLaunchKernelGGL((verify_row_sums_kernel<3>), grid, block, 0, stream, a);
+    else if (cpb == 4)
+      hipLaunchKernelGGL((verify_row_sums_kernel<4>), grid, block, 0, stream, a);
+    else
+      hipLaunchKernelGGL((verify_row_sums_kernel<0>), grid, block, 0, stream, a);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(verify_sample_from_sums_kernel, dim3(a.B), dim3(kVsWalkThreads), 0, stream, a);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(verify_sample_kernel, dim3(a.B), dim3(kVsThreads), 0, stream, a);
   return hipGetLastError();
 }
