@@ -76,25 +76,47 @@ __device__ __forceinline__ uint32_t kth_largest_group_max(const float* gmax, int
   return T;
 }
 
-// Descending bitonic sort of n2 (a power of two) 64-bit keys in LDS by the whole block.
-__device__ __forceinline__ void block_sort_desc(uint64_t* keys, int n2, int tid, int nthr) {
-  for (int size = 2; size <= n2; size <<= 1)
-    for (int stride = size >> 1; stride > 0; stride >>= 1) {
-      for (int p = tid; p < (n2 >> 1); p += nthr) {
-        const int pos = 2 * stride * (p / stride) + (p % stride);
-        const int partner = pos + stride;
-        const bool desc = ((pos & size) == 0);
-        const uint64_t x = keys[pos], y = keys[partner];
-        if ((x < y) == desc) {
-          keys[pos] = y;
-          keys[partner] = x;
-        }
-      }
-      __syncthreads();
-    }
-}
+// The rank-j key of a row of logits, in the form the launch's caller wants it.  For a wide beam inside a draft call the row
+// also forms its candidates of the beam update (Algorithm 1's next summed logprobs) - with k * k of them per sequence that is
+// 160 KB of pool entries, which one workgroup per sequence spent most of its launch on - and leaves their keys.
+struct RowEmit {
+  const RowTopkArgs& a;
+  int row;
+  float lse;
+  float parent_lps;    // of this row's beam slot (a.form)
+  int parent_node;
 
-constexpr int kSortFromK = 17;   // beams wider than DDD_KMAX: sorts replace the k rounds of wave maxima
+  __device__ __forceinline__ RowEmit(const RowTopkArgs& args, int r) : a(args), row(r), lse(0.f), parent_lps(0.f), parent_node(0) {
+    if (a.form) {
+      parent_lps = a.beam.st.logprobsum[row];            // row b * k + i is slot i of sequence b
+      parent_node = a.beam.st.beam_node[row];
+    }
+  }
+  __device__ __forceinline__ void operator()(int j, uint64_t key) const {
+    if (a.topk_token != nullptr) {
+      // the results of a single LM-head call (a separate launch that turned keys into tokens and logprobs cost 5 us)
+      a.topk_token[(size_t)row * a.k + j] = key_token(key);
+      a.topk_logprob[(size_t)row * a.k + j] = key_value(key) - lse;
+    } else if (a.form) {
+      const int k = a.k, b = row / k, f = (row - b * k) * k + j, t = key_token(key);
+      const float sc = __fadd_rn(parent_lps, key_value(key) - lse);   // logprob = logit - lse, then one fp32 add
+      const size_t pn = (size_t)b * a.beam.nmax + 1 + k + (size_t)(a.beam.step - 1) * k * k + f;
+      a.beam.st.pool_token[pn] = t;
+      a.beam.st.pool_parent[pn] = parent_node;
+      a.beam.st.pool_depth[pn] = a.beam.step + 1;
+      a.beam.st.pool_score[pn] = sc;
+      a.part_key[(size_t)row * k + j] = wide_beam_key(sc, t, f);
+    } else {
+      a.part_key[(size_t)row * a.k + j] = key;
+    }
+  }
+  __device__ __forceinline__ void row_lse() const {       // by one thread
+    if (a.topk_token != nullptr)
+      a.lse[row] = lse;
+    else
+      a.part_sum[row] = lse;
+  }
+};
 
 __global__ __launch_bounds__(256) void row_topk_kernel(RowTopkArgs a) {
   __shared__ uint64_t s_cand[kCandMax];
@@ -105,6 +127,7 @@ __global__ __launch_bounds__(256) void row_topk_kernel(RowTopkArgs a) {
   __shared__ uint32_t s_bound[4];
   const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if (a.row_active != nullptr && !a.row_active[row]) return;   // uniform
+  RowEmit emit(a, row);
   const int ngrp_valid = (a.V + 63) >> 6;
   const float* gmax = a.grp_max + (size_t)row * a.ngrp;
   const float* gsum = a.grp_sum + (size_t)row * a.ngrp;
@@ -125,15 +148,7 @@ __global__ __launch_bounds__(256) void row_topk_kernel(RowTopkArgs a) {
     s_cnt = 0;
     s_ng = 0;
   }
-  if (a.k >= kSortFromK) {
-    // wide beams: sort the group maxima (at most 2048) and read off the k-th
-    int n2 = 64;
-    while (n2 < ngrp_valid) n2 <<= 1;
-    for (int g = tid; g < n2; g += 256) s_cand[g] = (g < ngrp_valid) ? (uint64_t)ord32(gmax[g]) : 0ull;
-    __syncthreads();
-    block_sort_desc(s_cand, n2, tid, 256);
-    if (tid == 0) s_T = (a.k <= ngrp_valid) ? unord32((uint32_t)s_cand[a.k - 1]) : -INFINITY;
-  } else {
+  {
     // Up to 2048 groups (V <= 131072), up to 8 per thread, as ordered keys.  A lower bound first: a quad of lanes
     // holds 4 to 32 groups, and the k-th largest of a wave's 16 quad maxima is reached by k distinct groups (k <= 16);
     // the best of the four waves' bounds is taken.  The group maxima at or above it - a few dozen - are ranked by
@@ -182,22 +197,8 @@ __global__ __launch_bounds__(256) void row_topk_kernel(RowTopkArgs a) {
   }
   __syncthreads();
   const float lse = M + __logf(s_red[4] + s_red[5] + s_red[6] + s_red[7]);
-  // The rank-j key of the row: to the bookkeeping that follows, or to the caller of a single LM-head call (which
-  // needs nothing else: the separate launch that turned keys into tokens and logprobs cost 5 us a call).
-  auto emit = [&](int j, uint64_t key) {
-    if (a.topk_token != nullptr) {
-      a.topk_token[(size_t)row * a.k + j] = key_token(key);
-      a.topk_logprob[(size_t)row * a.k + j] = key_value(key) - lse;
-    } else {
-      a.part_key[(size_t)row * a.k + j] = key;
-    }
-  };
-  if (tid == 0) {
-    if (a.topk_token != nullptr)
-      a.lse[row] = lse;
-    else
-      a.part_sum[row] = lse;
-  }
+  emit.lse = lse;
+  if (tid == 0) emit.row_lse();
 
   // ---- collect candidates >= T ------------------------------------------------------------------
   // Only groups whose max reaches T can hold one: usually k or a few more of them, so the row's
@@ -264,15 +265,7 @@ __global__ __launch_bounds__(256) void row_topk_kernel(RowTopkArgs a) {
   __syncthreads();
   const int cnt = s_cnt;
 
-  if (cnt <= kCandMax && a.k >= kSortFromK) {                  // uniform
-    // ---- wide beams: sort the candidates, the first k are the answer ------------------------------
-    int n2 = 64;
-    while (n2 < cnt) n2 <<= 1;
-    for (int i = cnt + tid; i < n2; i += 256) s_cand[i] = 0ull;
-    __syncthreads();
-    block_sort_desc(s_cand, n2, tid, 256);
-    for (int j = tid; j < a.k; j += 256) emit(j, s_cand[j]);
-  } else if (cnt <= 256) {                                     // uniform: the usual case, a few more than k candidates
+  if (cnt <= 256) {                                            // uniform: the usual case, a few more than k candidates
     // ---- exact top-k among the candidates: a candidate's rank is the number of larger keys (keys are distinct) ---
     if (tid < cnt) {
       const uint64_t mine = s_cand[tid];
@@ -285,19 +278,18 @@ __global__ __launch_bounds__(256) void row_topk_kernel(RowTopkArgs a) {
   } else if (cnt <= kCandMax) {                                // uniform
     // ---- many candidates (ties at the threshold): wave 0, k rounds of wave max over its strided share ---
     if (wave == 0) {
-      uint64_t mine[2] = {0ull, 0ull};                         // ranks lane and lane + 64
+      uint64_t mine = 0ull;
       for (int round = 0; round < a.k; ++round) {
         uint64_t loc = 0ull;
         for (int i = lane; i < cnt; i += 64) loc = umax64(loc, s_cand[i]);
         const uint64_t best = wave_max_u64(loc);
-        if (lane == (round & 63)) mine[round >> 6] = best;
+        if (lane == round) mine = best;
         for (int i = lane; i < cnt; i += 64)
           if (s_cand[i] == best) s_cand[i] = 0ull;
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
       }
-      if (lane < a.k) emit(lane, mine[0]);
-      if (lane + 64 < a.k) emit(lane + 64, mine[1]);
+      if (lane < a.k) emit(lane, mine);
     }
   } else {
     // ---- more than kCandMax elements tie at or above T (e.g. constant logits): exact but slow ------
@@ -321,8 +313,121 @@ __global__ __launch_bounds__(256) void row_topk_kernel(RowTopkArgs a) {
   }
 }
 
+// The same for wide beams (DDD_KMAX < k <= DDD_KWIDE_MAX), where a bound from quad maxima no longer holds k keys: 1024
+// threads rank the group maxima by counting (at most 2048: 32-bit compares against broadcast reads of LDS, several threads
+// per group), and then the candidates at or above the k-th of them.  (Bitonic sorts of both by 256 threads, a block
+// barrier per stage, took 28 us a launch at k = 100, V = 32000, whatever the number of rows; 14.5 us now.)
+constexpr int kWideRowThreads = 1024;
+constexpr int kWideGroups = 2048;   // V <= 2^17
+
+__global__ __launch_bounds__(kWideRowThreads) void row_topk_wide_kernel(RowTopkArgs a) {
+  __shared__ __align__(16) uint32_t s_gm[kWideGroups];       // group maxima as ordered keys
+  __shared__ int s_num[kWideGroups];                         // work area; later the groups that hold candidates
+  __shared__ uint64_t s_cand[kCandMax];
+  __shared__ int s_rank[kCandMax];
+  __shared__ float s_red[2][16];
+  __shared__ uint32_t s_min[16];
+  __shared__ int s_cnt, s_ng;
+  const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (a.row_active != nullptr && !a.row_active[row]) return;   // uniform
+  RowEmit emit(a, row);
+  const int ngrp = (a.V + 63) >> 6, ngrp4 = (ngrp + 3) >> 2;
+  float m = -INFINITY, mine_max[2] = {-INFINITY, -INFINITY}, mine_sum[2] = {0.f, 0.f};
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int g = tid + u * kWideRowThreads;
+    if (g < ngrp) {
+      mine_max[u] = a.grp_max[(size_t)row * a.ngrp + g];
+      mine_sum[u] = a.grp_sum[(size_t)row * a.ngrp + g];
+    }
+    if (g < 4 * ngrp4) s_gm[g] = (g < ngrp) ? ord32(mine_max[u]) : 0u;
+    m = fmaxf(m, mine_max[u]);
+  }
+  if (tid == 0) s_cnt = s_ng = 0;
+  for (int i = tid; i < kCandMax; i += kWideRowThreads) s_rank[i] = 0;
+  m = wave_max_f32(m);
+  if (lane == 0) s_red[0][wave] = m;
+  __syncthreads();
+  float M = s_red[0][0];
+#pragma unroll
+  for (int w = 1; w < 16; ++w) M = fmaxf(M, s_red[0][w]);
+  float acc = 0.f;
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+    if (tid + u * kWideRowThreads < ngrp) acc += mine_sum[u] * __expf(mine_max[u] - M);
+  acc = wave_sum_f32(acc);
+  if (lane == 0) s_red[1][wave] = acc;
+  // ---- T = k-th largest group max -----------------------------------------------------------------------------------
+  const uint32_t least = block_kth_largest_u32(s_gm, ngrp, min(a.k, ngrp), s_num, s_min, tid);   // its barriers publish s_red
+  const float T = (ngrp < a.k) ? -INFINITY : unord32(least);
+  float total = 0.f;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) total += s_red[1][w];            // fixed order
+  emit.lse = M + __logf(total);
+  if (tid == 0) emit.row_lse();
+  // ---- the groups that can hold a candidate, and the candidates >= T -------------------------------------------------
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int g = tid + u * kWideRowThreads;
+    if (g < ngrp && mine_max[u] >= T) s_num[atomicAdd(&s_ng, 1)] = g;
+  }
+  __syncthreads();
+  const float* x = a.logits + (size_t)row * a.ldl;
+  const int ng = s_ng;
+  for (int i0 = wave; i0 < ng; i0 += 16 * 8) {
+    float xv[8];
+    int vv[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {                               // eight groups' loads in flight
+      const int i = i0 + 16 * u;
+      vv[u] = (i < ng) ? s_num[i] * 64 + lane : a.V;
+      xv[u] = (vv[u] < a.V) ? x[vv[u]] : -INFINITY;
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const bool in = vv[u] < a.V && xv[u] >= T;
+      const unsigned long long bal = __ballot(in);
+      if (bal == 0ull) continue;                                // wave-uniform
+      int base = 0;
+      if (lane == 0) base = atomicAdd(&s_cnt, __popcll(bal));
+      const int p = __builtin_amdgcn_readfirstlane(base) + __popcll(bal & ((1ull << lane) - 1ull));
+      if (in && p < kCandMax) s_cand[p] = row_key(xv[u], vv[u]);
+    }
+  }
+  __syncthreads();
+  const int cnt = s_cnt;
+  if (cnt <= kCandMax) {                                        // uniform
+    count_larger_keys(s_cand, cnt, s_rank, tid, kWideRowThreads);
+    __syncthreads();
+    for (int i = tid; i < cnt; i += kWideRowThreads)
+      if (s_rank[i] < a.k) emit(s_rank[i], s_cand[i]);
+    return;
+  }
+  // ---- more than kCandMax elements tie at or above T (e.g. constant logits): exact but slow ---------------------------
+  uint64_t prev = ~0ull, mine = 0ull;
+  for (int round = 0; round < a.k; ++round) {
+    uint64_t loc = 0ull;
+    for (int v = tid; v < a.V; v += kWideRowThreads) {
+      const uint64_t key = row_key(x[v], v);
+      if (key < prev) loc = umax64(loc, key);
+    }
+    loc = wave_max_u64(loc);
+    __syncthreads();
+    if (lane == 0) s_cand[wave] = loc;
+    __syncthreads();
+    prev = s_cand[0];
+#pragma unroll
+    for (int w = 1; w < 16; ++w) prev = umax64(prev, s_cand[w]);
+    if (tid == round) mine = prev;
+  }
+  if (tid < a.k) emit(tid, mine);
+}
+
 hipError_t launch_row_topk(const RowTopkArgs& a, hipStream_t stream) {
-  hipLaunchKernelGGL(row_topk_kernel, dim3(a.n_rows), dim3(256), 0, stream, a);
+  if (a.k > DDD_KMAX)
+    hipLaunchKernelGGL(row_topk_wide_kernel, dim3(a.n_rows), dim3(kWideRowThreads), 0, stream, a);
+  else
+    hipLaunchKernelGGL(row_topk_kernel, dim3(a.n_rows), dim3(256), 0, stream, a);
   return hipGetLastError();
 }
 

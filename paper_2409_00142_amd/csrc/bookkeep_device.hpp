@@ -436,6 +436,17 @@ __device__ __forceinline__ void report_call(const CallReport& r, bool active, in
   __shared__ int s_word_base[DDD_BMAX / 64 + 1];
   __shared__ unsigned long long s_words[DDD_BMAX / 64];
   if (r.call_count == nullptr) return;               // uniform
+  if (gridDim.x == 1) {
+    // a single sequence has nobody to wait for: no atomics (two round trips to the device's coherence point)
+    if (tid == 0) {
+      if (r.progress != nullptr)
+        __hip_atomic_store(r.progress, (r.round_tag << 2) | 2u | (active ? 1u : 0u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      if (r.active_mask != nullptr) *r.next_n_act = active ? k : 0;
+    }
+    if (r.active_mask != nullptr && active)
+      for (int i = tid; i < k; i += nthr) r.next_row_list[i] = i;
+    return;
+  }
   if (tid == 0) {
     // What the last workgroup needs from this one travels in atomics alone (performed at the device's
     // coherence point), so no fence is needed: the sequence's bit first, then - once that atomic has returned

@@ -23,6 +23,7 @@ struct ddd_ctx {
   int nmax;
   uint64_t* part_key;   // [B*k][k][nslice] (weight stream: rank-major, the slices' j-th keys together) or [B*k][k] (GEMM path, dense)
   float* part_sum;      // [B*k][nslice] or [B*k]
+  void* small;          // the allocation that holds every device array of the context but part_key, logits, pack and trace
   int32_t* row_list;    // [B*k] active rows of the current call (GEMM path)
   int32_t* n_act;       // [1]
   float* logits;        // [B*k][ldl] fp32 logits of the GEMM path (null if B*k <= 16)
@@ -164,7 +165,8 @@ int slices_for(const ddd_ctx* c, int n_rows) { return gemm_path(c, n_rows) ? 0 :
 // LM head over n_rows rows, partials into the context scratch: the weight stream for up to
 // DDD_STREAM_ROWS rows, the MFMA GEMM over the compacted active rows otherwise.
 // GEMM path: `list` says where its list of active rows comes from, and with `out` the row reduction leaves the results
-// in the caller's form (topk_token, topk_logprob, lse) instead of the context scratch.
+// in the caller's form (topk_token, topk_logprob, lse) instead of the context scratch, with `form` (wide beams, calls after
+// the prompt call) the candidates of the beam update in the pool and their keys in the scratch.
 enum RowListSource {
   kListBuild,   // built here from row_active
   kListReady,   // the previous call's bookkeeping launch has written it
@@ -177,7 +179,7 @@ struct LmheadOut {
 };
 int enqueue_stream(ddd_ctx* c, const void* W, const void* hid, int n_rows, const uint8_t* row_active, float* logits_dbg,
                    int reverse, hipStream_t s, RowListSource list, int trace_step = -1, bool eager_loads = false,
-                   const LmheadOut* results = nullptr) {
+                   const LmheadOut* results = nullptr, const BeamArgs* form = nullptr) {
   if (gemm_path(c, n_rows)) {
     float* out = logits_dbg ? logits_dbg : c->logits;
     const int ldl = logits_dbg ? c->cfg.V : c->ldl;
@@ -199,6 +201,8 @@ int enqueue_stream(ddd_ctx* c, const void* W, const void* hid, int n_rows, const
     t.n_rows = n_rows;
     t.V = c->cfg.V;
     t.k = c->cfg.k;
+    t.form = form != nullptr ? 1 : 0;
+    t.beam = form != nullptr ? *form : BeamArgs{};
     DDD_HIP(launch_row_topk(t, s));
     return DDD_OK;
   }
@@ -276,7 +280,7 @@ size_t ddd_scratch_bytes(const ddd_config* cfg) {
   if (ddd_config_validate(cfg) != DDD_OK) return 0;
   const size_t rows = (size_t)cfg->B * cfg->k, max_slices = (cfg->k > DDD_KMAX) ? 1 : 512;
   const size_t sample = rows_from_sums(*cfg) ? (size_t)cfg->B * (cfg->m + 1) * verify_sample_row_bytes() : 0;
-  size_t n = sample + rows * max_slices * cfg->k * sizeof(uint64_t) + rows * max_slices * sizeof(float) + rows * 4 + 4;
+  size_t n = sample + rows * max_slices * cfg->k * sizeof(uint64_t) + rows * max_slices * sizeof(float) + rows * 4 + 4096;
   if (rows > DDD_STREAM_ROWS || cfg->k > DDD_KMAX)   // logits and per-group statistics of the GEMM path
     n += rows * (size_t)logits_pitch(cfg->V) * sizeof(float) + 2 * rows * (size_t)(((cfg->V + 63) / 64 + 3) & ~3) * sizeof(float);
   return n;
@@ -323,19 +327,15 @@ int ddd_create(const ddd_config* cfg, ddd_ctx** out) {
   c->part_sum_bytes = rows * ns * sizeof(float);
   c->logits_bytes = c->grp_bytes = 0;
   hipError_t e = hipMalloc(&c->part_key, c->part_key_bytes);
-  if (e == hipSuccess) e = hipMalloc(&c->part_sum, c->part_sum_bytes);
-  if (e == hipSuccess) e = hipMalloc(&c->row_list, rows * sizeof(int32_t));
-  if (e == hipSuccess) e = hipMalloc(&c->n_act, sizeof(int32_t));
   if (e == hipSuccess && (rows > DDD_STREAM_ROWS || cfg->k > DDD_KMAX)) {
     c->logits_bytes = rows * (size_t)c->ldl * sizeof(float);
     c->grp_bytes = rows * (size_t)c->ngrp * sizeof(float);
     e = hipMalloc(&c->logits, c->logits_bytes);
-    if (e == hipSuccess) e = hipMalloc(&c->grp_max, c->grp_bytes);
-    if (e == hipSuccess) e = hipMalloc(&c->grp_sum, c->grp_bytes);
     if (e == hipSuccess) e = prepare_lmhead_gemm();
     if (e == hipSuccess && cfg->k > DDD_KMAX) e = prepare_wide();
   }
   if (e == hipSuccess) e = prepare_tree_attention();
+  c->small = nullptr;
   c->call_count = nullptr;
   c->active_mask = nullptr;
   c->stats_sync = nullptr;
@@ -350,14 +350,32 @@ int ddd_create(const ddd_config* cfg, ddd_ctx** out) {
   c->run_rounds = c->run_waits = c->run_timeouts = 0;
   c->run_max_wait_us = 0.0;
   c->trace = nullptr;
-  if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&c->call_count), (DDD_DMAX + 1) * sizeof(uint32_t));
-  if (e == hipSuccess) e = hipMemset(c->call_count, 0, (DDD_DMAX + 1) * sizeof(uint32_t));
-  if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&c->stats_sync), 2 * sizeof(uint32_t));
-  if (e == hipSuccess) e = hipMemset(c->stats_sync, 0, 2 * sizeof(uint32_t));
-  if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&c->active_mask), (DDD_BMAX / 64) * sizeof(uint64_t));
-  if (e == hipSuccess) e = hipMemset(c->active_mask, 0, (DDD_BMAX / 64) * sizeof(uint64_t));
-  if (e == hipSuccess && rows_from_sums(*cfg))
-    e = hipMalloc(&c->sample_rows, (size_t)cfg->B * (cfg->m + 1) * verify_sample_row_bytes());
+  // all but the two large arrays share one allocation (each costs 10 to 50 us of a context's creation); the words that have
+  // to start at zero come first
+  {
+    auto aligned = [](size_t n) { return (n + 255) & ~(size_t)255; };
+    const size_t o_mask = aligned((DDD_DMAX + 1) * sizeof(uint32_t)), o_sync = o_mask + aligned((DDD_BMAX / 64) * sizeof(uint64_t));
+    const size_t o_act = o_sync + aligned(2 * sizeof(uint32_t)), o_list = o_act + aligned(sizeof(int32_t));
+    const size_t o_rows = o_list + aligned(rows * sizeof(int32_t));
+    const size_t n_rows = rows_from_sums(*cfg) ? (size_t)cfg->B * (cfg->m + 1) * verify_sample_row_bytes() : 0;
+    const size_t o_sum = o_rows + aligned(n_rows), o_gmax = o_sum + aligned(c->part_sum_bytes), o_gsum = o_gmax + aligned(c->grp_bytes);
+    if (e == hipSuccess) e = hipMalloc(&c->small, o_gsum + aligned(c->grp_bytes));
+    if (e == hipSuccess) e = hipMemset(c->small, 0, o_act);
+    if (e == hipSuccess) {
+      unsigned char* p = static_cast<unsigned char*>(c->small);
+      c->call_count = reinterpret_cast<uint32_t*>(p);
+      c->active_mask = reinterpret_cast<uint64_t*>(p + o_mask);
+      c->stats_sync = reinterpret_cast<uint32_t*>(p + o_sync);
+      c->n_act = reinterpret_cast<int32_t*>(p + o_act);
+      c->row_list = reinterpret_cast<int32_t*>(p + o_list);
+      if (n_rows) c->sample_rows = p + o_rows;
+      c->part_sum = reinterpret_cast<float*>(p + o_sum);
+      if (c->grp_bytes) {
+        c->grp_max = reinterpret_cast<float*>(p + o_gmax);
+        c->grp_sum = reinterpret_cast<float*>(p + o_gsum);
+      }
+    }
+  }
   void* host_words = nullptr;
   if (e == hipSuccess)
     e = hipHostMalloc(&host_words, (DDD_DMAX + 1) * sizeof(uint32_t), hipHostMallocMapped | hipHostMallocCoherent);
@@ -369,18 +387,10 @@ int ddd_create(const ddd_config* cfg, ddd_ctx** out) {
     c->progress_dev = static_cast<uint32_t*>(dev_words);
   }
   if (e != hipSuccess) {
-    if (c->call_count) (void)hipFree(c->call_count);
-    if (c->active_mask) (void)hipFree(c->active_mask);
-    if (c->stats_sync) (void)hipFree(c->stats_sync);
-    if (c->sample_rows) (void)hipFree(c->sample_rows);
+    if (c->small) (void)hipFree(c->small);
     if (host_words) (void)hipHostFree(host_words);
     if (c->logits) (void)hipFree(c->logits);
-    if (c->grp_max) (void)hipFree(c->grp_max);
-    if (c->grp_sum) (void)hipFree(c->grp_sum);
     if (c->part_key) (void)hipFree(c->part_key);
-    if (c->part_sum) (void)hipFree(c->part_sum);
-    if (c->row_list) (void)hipFree(c->row_list);
-    if (c->n_act) (void)hipFree(c->n_act);
     delete c;
     return hip_fail(e, "context scratch");
   }
@@ -393,18 +403,10 @@ int ddd_destroy(ddd_ctx* c) {
   if (c->graph_exec) (void)hipGraphExecDestroy(c->graph_exec);
   if (c->graph) (void)hipGraphDestroy(c->graph);
   (void)hipFree(c->part_key);
-  (void)hipFree(c->part_sum);
-  (void)hipFree(c->row_list);
-  (void)hipFree(c->n_act);
   if (c->logits) (void)hipFree(c->logits);
-  if (c->grp_max) (void)hipFree(c->grp_max);
-  if (c->grp_sum) (void)hipFree(c->grp_sum);
   if (c->pack) (void)hipFree(c->pack);
   if (c->trace) (void)hipFree(c->trace);
-  (void)hipFree(c->call_count);
-  (void)hipFree(c->active_mask);
-  (void)hipFree(c->stats_sync);
-  if (c->sample_rows) (void)hipFree(c->sample_rows);
+  (void)hipFree(c->small);
   (void)hipHostFree(const_cast<uint32_t*>(c->progress));
   delete c;
   return DDD_OK;
@@ -673,7 +675,8 @@ int draft_step(ddd_ctx* c, int32_t step, const void* W, const void* hid, ddd_sta
   // a round's first call comes right behind the reset: every sequence drafts
   const RowListSource list = (in_round && step == 0) ? kListAll : chain ? kListReady : kListBuild;
   // publish = the host-paced round: it queues at most one call per round that every sequence skips
-  int rc = enqueue_stream(c, W, hid, n_rows, flags, logits_dbg, step & 1, s, list, step, publish);
+  int rc = enqueue_stream(c, W, hid, n_rows, flags, logits_dbg, step & 1, s, list, step, publish, nullptr,
+                          c->cfg.k > DDD_KMAX && step >= 1 ? &a.beam : nullptr);
   if (rc != DDD_OK) return rc;
   if (c->cfg.k > DDD_KMAX) {
     WideStepArgs w = wide_args(c, a.beam);

@@ -31,6 +31,19 @@ __device__ __forceinline__ uint64_t beam_key(float score, int token, int flat) {
 }
 __device__ __forceinline__ int beam_key_flat(uint64_t key) { return (int)(0xFFu - ((uint32_t)key & 0xFFu)); }
 
+// Beam key of wide beams (DDD_KMAX < k): larger score, then lower token id (< 2^18), then lower flat index (< 2^14).
+constexpr int kFlatBits = 14;                      // k*k <= 16384 flat indices
+constexpr uint32_t kFlatMask = (1u << kFlatBits) - 1u;
+constexpr uint32_t kTokMaskW = (1u << (32 - kFlatBits)) - 1u;   // tokens below 2^18
+__device__ __forceinline__ uint64_t wide_beam_key(float score, int token, int flat) {
+  const uint32_t lo = ((kTokMaskW - (uint32_t)token) << kFlatBits) | (kFlatMask - (uint32_t)flat);
+  return ((uint64_t)ord32(score) << 32) | lo;
+}
+__device__ __forceinline__ int wide_key_flat(uint64_t key) { return (int)(kFlatMask - ((uint32_t)key & kFlatMask)); }
+__device__ __forceinline__ int wide_key_token(uint64_t key) {
+  return (int)(kTokMaskW - (((uint32_t)key >> kFlatBits) & kTokMaskW));
+}
+
 // ---- wave-wide max of a 64-bit key ----------------------------------------------------------
 // All of these must be called with all 64 lanes of the wave active; the result is the same in
 // every lane.  The cross-lane steps are DPP moves (quad swaps, half-row and row mirrors), the

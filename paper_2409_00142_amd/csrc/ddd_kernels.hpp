@@ -72,6 +72,15 @@ hipError_t launch_pack_weights(const uint16_t* W, uint16_t* Wp, int V, int H, hi
 hipError_t launch_build_row_list(const uint8_t* row_active, int n_rows, int32_t* row_list, int32_t* n_act,
                                  hipStream_t stream);
 
+struct BeamArgs {
+  ddd_state st;
+  const int32_t* topk_token;  // [B] or [B*k] rows of k
+  const float* topk_logprob;
+  int B, k, D, nmax, step;
+  float threshold;
+  uint32_t check_mask;
+};
+
 // Row reduction of materialised logits: lse and top-k keys of every active row, in the "dense"
 // partial format part_key[row][k] (final keys in order), part_sum[row] = lse.
 struct RowTopkArgs {
@@ -85,6 +94,8 @@ struct RowTopkArgs {
   float* topk_logprob;        // [n_rows][k]            written then): tokens, logit - lse,
   float* lse;                 // [n_rows]               and lse
   int n_rows, V, k, ngrp, ldl;
+  int form;                   // wide beams, calls after the prompt call: append the row's candidates to the pool (beam) and leave
+  BeamArgs beam;              //   their beam keys in part_key instead of the row's keys
 };
 hipError_t launch_row_topk(const RowTopkArgs& a, hipStream_t stream);
 
@@ -100,14 +111,6 @@ struct MergeArgs {
 };
 hipError_t launch_merge(const MergeArgs& a, hipStream_t stream);
 
-struct BeamArgs {
-  ddd_state st;
-  const int32_t* topk_token;  // [B] or [B*k] rows of k
-  const float* topk_logprob;
-  int B, k, D, nmax, step;
-  float threshold;
-  uint32_t check_mask;
-};
 hipError_t launch_beam_select(const BeamArgs& a, hipStream_t stream);
 hipError_t launch_depth_continue(const BeamArgs& a, int steps_done, hipStream_t stream);
 
@@ -155,7 +158,8 @@ hipError_t launch_lmhead_stream(const StreamArgs& a, int G, int nslice, hipStrea
 // the top-k token / logprob arrays of the stand-alone call.
 struct WideStepArgs {
   BeamArgs beam;
-  const uint64_t* part_key;   // [rows][k] final keys in order, or null: use beam.topk_token / topk_logprob
+  const uint64_t* part_key;   // [rows][k] final keys in order (the prompt call) or the candidates' beam keys (later calls: the
+                              //   row reduction has formed them), or null: use beam.topk_token / topk_logprob
   const float* part_lse;      // [rows] lse of each row (with part_key)
   float* lse_dbg;             // [rows] or null
   ddd_tree tree;              // tree.mask == null: do not build the final tree here

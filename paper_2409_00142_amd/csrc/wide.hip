@@ -1,14 +1,15 @@
 // Wide beams (DDD_KMAX < k <= DDD_KWIDE_MAX): beam update, stop test and final tree of one
 // sequence by one workgroup (Appendix, Table 2: draft speed against beam width).
 //
-// With up to 128 x 128 candidates per draft call and tens of thousands of pool nodes nothing fits
-// in registers any more: the k*k candidate keys (score desc, token asc, flat index asc) are built
-// in LDS and the k-th largest is found by a radix select (8-bit digits from the top: histogram in
-// LDS, the digit holding the wanted rank narrows the prefix); the keys at or above it are the new
-// beam, sorted by a small bitonic network.  The final rerank selects the m best pool nodes the
-// same way with keys computed on the fly from the pool scores in global memory (L2-resident).
-// Everything else (Eq. 1 in fp64 in index order, parents, ancestor rows, mask) is as for narrow
-// beams.
+// With up to 128 x 128 candidates per draft call and tens of thousands of pool nodes one workgroup must not do what many
+// can: inside a draft call the candidates' pool entries and beam keys (score desc, token asc, flat index asc) are written
+// by the row reduction, one workgroup per row, and this launch only reads the keys, sixteen per thread.  The beam: a lower
+// bound from the rows' first few candidates, the keys above it ranked by counting; many equal scores: a radix select
+// (8-bit digits from the top: histogram in LDS, the digit holding the wanted rank narrows the prefix).  The final rerank
+// selects the m best pool nodes the same way from the scores in global memory.  At k = 100, V = 32000, B = 1: 31 -> 16 us
+// a call, 73 -> 32 us for the call that builds the final tree (with the candidates formed here and the 64-bit radix
+// select and counting over 512 keys).  Everything else (Eq. 1 in fp64 in index order, parents, ancestor rows, mask) is as
+// for narrow beams.
 #include "bookkeep_device.hpp"
 #include "tree_device.hpp"
 
@@ -17,9 +18,6 @@ namespace ddd {
 constexpr int kKW = DDD_KWIDE_MAX;
 constexpr int kWideThreads = 1024;
 constexpr int kGlobalChunk = 8;                    // loads in flight per thread when the keys come from global memory
-constexpr int kFlatBits = 14;                      // k*k <= 16384 flat indices
-constexpr uint32_t kFlatMask = (1u << kFlatBits) - 1u;
-constexpr uint32_t kTokMaskW = (1u << (32 - kFlatBits)) - 1u;   // tokens below 2^18
 // final tree of a large pool: sample, candidates and their ranks (tree_finalize_wide_block)
 constexpr int kWSub = 512, kWCand = 1024;
 constexpr int kWideWorkBytes = kWSub * 8 + kWCand * 8 + kWCand * 4;
@@ -30,15 +28,6 @@ __host__ __device__ inline size_t wide_front_bytes(int k) {
   return keys > (size_t)kWideWorkBytes ? keys : (size_t)kWideWorkBytes;
 }
 
-__device__ __forceinline__ uint64_t wide_beam_key(float score, int token, int flat) {
-  const uint32_t lo = ((kTokMaskW - (uint32_t)token) << kFlatBits) | (kFlatMask - (uint32_t)flat);
-  return ((uint64_t)ord32(score) << 32) | lo;
-}
-__device__ __forceinline__ int wide_key_flat(uint64_t key) { return (int)(kFlatMask - ((uint32_t)key & kFlatMask)); }
-__device__ __forceinline__ int wide_key_token(uint64_t key) {
-  return (int)(kTokMaskW - (((uint32_t)key >> kFlatBits) & kTokMaskW));
-}
-
 struct WideSmem {
   unsigned hist[256];
   int digit, rem, alone, cnt, stopped;
@@ -46,7 +35,7 @@ struct WideSmem {
   float lps_old[kKW];
   int node_old[kKW];
   uint64_t sel[kKW];
-  double e[kKW];
+  uint32_t red[16];
   TreeEmitSmem te;
 };
 
@@ -205,11 +194,10 @@ __device__ __forceinline__ void sort_sel_desc_wave(WideSmem& sm, int lane) {
   }
 }
 
-// Final tree for a pool of any size.  The m best rerank keys are found as for narrow beams (tree_device.hpp): the
-// m-th best key of the first kWSub nodes is a lower bound of the tree's keys (summed logprobs fall with depth), one
-// sweep over the pool collects the keys at or above it, and the candidates are ranked by counting; a sweep over
-// 50 000 scores takes about 20 us on the one CU that runs it, and the radix select needs five or six of them.  While
-// more than kWCand keys pass the bound, the m-th best of kWSub of them tightens it (twice at most); after that the
+// Final tree for a pool of any size.  The m best rerank keys are found as for narrow beams (tree_device.hpp): the m-th
+// best score of the first 256 nodes is a lower bound of the tree's scores (summed logprobs fall with depth), one sweep over
+// the pool collects the nodes at or above it (up to kWCand), and they are ranked by counting.  If more pass the bound, the
+// same with whole keys, the first kWSub nodes and then kWSub of the candidates as the sample (three attempts); after that the
 // radix select takes over.  work: kWideWorkBytes of LDS.
 __device__ __forceinline__ void tree_finalize_wide_block(const ddd_state& st, const ddd_tree& tree, int b, int m, int nmax,
                                                          int tid, int nthr, WideSmem& sm, unsigned char* work) {
@@ -221,7 +209,41 @@ __device__ __forceinline__ void tree_finalize_wide_block(const ddd_state& st, co
   uint64_t* cand = sample + kWSub;                                   // [kWCand]
   int* rank = reinterpret_cast<int*>(cand + kWCand);                // [kWCand]
   bool ranked = false;
+  // First with 32-bit scores: the m-th best of the first 256 nodes, and one plain sweep over the scores.
   if (m_eff < N && nthr == kWideThreads) {                           // uniform
+    constexpr int kFirst = 256;
+    static_assert(kFirst >= DDD_MMAX && 2 * kFirst <= 2 * kWSub, "the sample holds m scores and lies in front of the candidates");
+    uint32_t* first = reinterpret_cast<uint32_t*>(work);             // [kFirst + 4]
+    int* cnt = reinterpret_cast<int*>(first + kFirst + 4);           // [kFirst]
+    const int n_first = min(N, kFirst);
+    for (int i = tid; i < ((n_first + 3) & ~3); i += nthr) first[i] = (i < n_first) ? ord32(psc[i + 1]) : 0u;
+    for (int i = tid; i < kWCand; i += nthr) rank[i] = 0;
+    if (tid == 0) sm.cnt = 0;
+    __syncthreads();
+    const float bound = unord32(block_kth_largest_u32(first, n_first, m_eff, cnt, sm.red, tid));
+    for (int i0 = tid; i0 < N; i0 += 16 * kWideThreads) {
+      float x[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) x[u] = (i0 + u * kWideThreads < N) ? psc[i0 + u * kWideThreads + 1] : -INFINITY;
+#pragma unroll
+      for (int u = 0; u < 16; ++u)
+        if (x[u] >= bound && i0 + u * kWideThreads < N) {
+          const int p = atomicAdd(&sm.cnt, 1);
+          if (p < kWCand) cand[p] = rerank_key(x[u], i0 + u * kWideThreads + 1);
+        }
+    }
+    __syncthreads();
+    const int C = sm.cnt;
+    if (C <= kWCand) {                                               // uniform
+      count_larger_keys(cand, C, rank, tid, nthr);
+      __syncthreads();
+      for (int c = tid; c < C; c += nthr)
+        if (rank[c] < m_eff) sm.te.pick[rank[c]] = (int)(0xFFFFFFFFu - (uint32_t)cand[c]);
+      ranked = true;
+    }
+    __syncthreads();
+  }
+  if (!ranked && m_eff < N && nthr == kWideThreads) {                           // uniform
     int n_sample = min(N, kWSub);
     for (int i = tid; i < n_sample; i += nthr) sample[i] = key_of(i);
     for (int attempt = 0; attempt < 3; ++attempt) {
@@ -282,7 +304,6 @@ __device__ __forceinline__ bool step_wide_block(const WideStepArgs& a, unsigned 
   const BeamArgs& g = a.beam;
   const int b = blockIdx.x, tid = threadIdx.x, nthr = blockDim.x;
   const int k = g.k, step = g.step;
-  uint64_t* keys = reinterpret_cast<uint64_t*>(wsm_raw);                       // [k*k]
   WideSmem& sm = *reinterpret_cast<WideSmem*>(wsm_raw + wide_front_bytes(k));
   if (!g.st.active[b]) return false;         // uniform over the workgroup
 
@@ -329,59 +350,107 @@ __device__ __forceinline__ bool step_wide_block(const WideStepArgs& a, unsigned 
         if (a.lse_dbg != nullptr && from_keys) a.lse_dbg[row0] = a.part_lse[row0];
       }
     } else {
-      const int base = 1 + k + (step - 1) * k * k;
-      for (int i = tid; i < k; i += nthr) {
-        sm.lps_old[i] = lps[i];
-        sm.node_old[i] = bnode[i];
-        if (a.lse_dbg != nullptr && from_keys) a.lse_dbg[row0 + i] = a.part_lse[row0 + i];
-      }
-      __syncthreads();
-      for (int f0 = 0; f0 < k * k; f0 += 4 * nthr) {      // four candidates per thread in flight
-        int t[4];
-        float lp[4];
+      const int base = 1 + k + (step - 1) * k * k, kk = k * k;
+      if (a.lse_dbg != nullptr && from_keys)
+        for (int i = tid; i < k; i += nthr) a.lse_dbg[row0 + i] = a.part_lse[row0 + i];
+      // every candidate's beam key, element f = tid + u * 1024: formed by the row reduction, or here from the caller's rows
+      constexpr int kPer = kKW * kKW / kWideThreads;
+      uint64_t kv[kPer];
+      if (from_keys) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int f = f0 + u * nthr + tid;
-          t[u] = 0;
-          lp[u] = 0.f;
-          if (f < k * k) {
-            const int i = f / k, j = f - i * k;
-            if (from_keys) {
-              const uint64_t key = a.part_key[(row0 + i) * k + j];
-              t[u] = key_token(key);
-              lp[u] = key_value(key) - a.part_lse[row0 + i];
-            } else {
-              t[u] = g.topk_token[(row0 + i) * k + j];
-              lp[u] = g.topk_logprob[(row0 + i) * k + j];
+        for (int u = 0; u < kPer; ++u) {
+          const int f = u * kWideThreads + tid;
+          kv[u] = (f < kk) ? a.part_key[row0 * k + f] : 0ull;
+        }
+      } else {
+        for (int i = tid; i < k; i += nthr) {
+          sm.lps_old[i] = lps[i];
+          sm.node_old[i] = bnode[i];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u0 = 0; u0 < kPer; u0 += 4) {            // four candidates per thread in flight
+          int t[4];
+          float lp[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int f = (u0 + u) * kWideThreads + tid;
+            t[u] = (f < kk) ? g.topk_token[row0 * k + f] : 0;
+            lp[u] = (f < kk) ? g.topk_logprob[row0 * k + f] : 0.f;
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int f = (u0 + u) * kWideThreads + tid;
+            kv[u0 + u] = 0ull;
+            if (f < kk) {
+              const int i = f / k;
+              const float sc = __fadd_rn(sm.lps_old[i], lp[u]);
+              ptok[base + f] = t[u];
+              ppar[base + f] = sm.node_old[i];
+              pdep[base + f] = step + 1;
+              psc[base + f] = sc;
+              kv[u0 + u] = wide_beam_key(sc, t[u], f);
             }
           }
         }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int f = f0 + u * nthr + tid;
-          if (f < k * k) {
-            const int i = f / k;
-            const float sc = __fadd_rn(sm.lps_old[i], lp[u]);
-            ptok[base + f] = t[u];
-            ppar[base + f] = sm.node_old[i];
-            pdep[base + f] = step + 1;
-            psc[base + f] = sc;
-            keys[f] = wide_beam_key(sc, t[u], f);
-          }
-        }
       }
-      __syncthreads();
-      const uint64_t kth = block_select_kth<8>(k * k, k - 1, [&](int i) { return keys[i]; }, sm, tid);
-      for (int i = tid; i < kKW; i += nthr) sm.sel[i] = 0ull;
+      // The new beam: the k-th best score of the rows' first few candidates is a lower bound of the beam's scores (a row's
+      // logprobs fall), the keys at or above it - k and a few more - are ranked by counting.  Three per row at k = 100: the
+      // comparisons of a larger sample cost more than the candidates it spares.
+      uint32_t* sample = reinterpret_cast<uint32_t*>(wsm_raw);   // [kWSub]
+      int* cnt = reinterpret_cast<int*>(sample + kWSub);         // [kWSub]
+      uint64_t* cand = reinterpret_cast<uint64_t*>(cnt + kWSub); // [kWCand]
+      int* rank = reinterpret_cast<int*>(cand + kWCand);         // [kWCand]
+      const int per_row = min(k, max(1, 320 / k)), n_sample = k * per_row;
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) {
+        const int f = u * kWideThreads + tid, i = f / k, j = f - i * k;
+        if (f < kk && j < per_row) sample[i * per_row + j] = (uint32_t)(kv[u] >> 32);
+      }
+      if (tid < 4) sample[n_sample + tid] = 0u;
+      for (int i = tid; i < kWCand; i += nthr) rank[i] = 0;
       if (tid == 0) sm.cnt = 0;
       __syncthreads();
-      for (int f = tid; f < k * k; f += nthr)
-        if (keys[f] >= kth) {
-          const int p = atomicAdd(&sm.cnt, 1);
-          if (p < kKW) sm.sel[p] = keys[f];     // exactly k of them: keys are distinct
-        }
+      const uint32_t bound = block_kth_largest_u32(sample, n_sample, k, cnt, sm.red, tid);
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) {
+        const bool in = kv[u] != 0ull && (uint32_t)(kv[u] >> 32) >= bound;
+        const unsigned long long bal = __ballot(in);
+        if (bal == 0ull) continue;                                // wave-uniform
+        int at = 0;
+        if ((tid & 63) == 0) at = atomicAdd(&sm.cnt, __popcll(bal));
+        const int p = __builtin_amdgcn_readfirstlane(at) + __popcll(bal & ((1ull << (tid & 63)) - 1ull));
+        if (in && p < kWCand) cand[p] = kv[u];
+      }
       __syncthreads();
-      if (tid < 64) sort_sel_desc_wave(sm, tid);
+      const int C = sm.cnt;
+      if (C <= kWCand) {                                          // uniform
+        count_larger_keys(cand, C, rank, tid, nthr);
+        __syncthreads();
+        for (int i = tid; i < C; i += nthr)
+          if (rank[i] < k) sm.sel[rank[i]] = cand[i];
+      } else {
+        // many equal or nearly equal scores: radix select over all keys
+        __syncthreads();                                          // everybody has the count; the keys take the work area's place
+        uint64_t* keys = reinterpret_cast<uint64_t*>(wsm_raw);
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+          const int f = u * kWideThreads + tid;
+          if (f < kk) keys[f] = kv[u];
+        }
+        __syncthreads();
+        const uint64_t kth = block_select_kth<8>(kk, k - 1, [&](int i) { return keys[i]; }, sm, tid);
+        for (int i = tid; i < kKW; i += nthr) sm.sel[i] = 0ull;
+        if (tid == 0) sm.cnt = 0;
+        __syncthreads();
+        for (int f = tid; f < kk; f += nthr)
+          if (keys[f] >= kth) {
+            const int p = atomicAdd(&sm.cnt, 1);
+            if (p < kKW) sm.sel[p] = keys[f];     // exactly k of them: keys are distinct
+          }
+        __syncthreads();
+        if (tid < 64) sort_sel_desc_wave(sm, tid);
+      }
       __syncthreads();
       for (int r = tid; r < k; r += nthr) {
         const uint64_t key = sm.sel[r];
@@ -401,16 +470,27 @@ __device__ __forceinline__ bool step_wide_block(const WideStepArgs& a, unsigned 
 
   if (tid == 0) sm.stopped = 0;
   if (a.do_stop) {
-    for (int i = tid; i < k; i += nthr) sm.e[i] = exp((double)lps[i]);
-    __syncthreads();
-    if (tid == 0) {
+    if (tid < 64) {                              // wave 0: lane l holds beam slots l and l + 64
+      const double e0 = (tid < k) ? exp((double)lps[tid]) : 0.0, e1 = (tid + 64 < k) ? exp((double)lps[tid + 64]) : 0.0;
+      const uint64_t b0 = (uint64_t)__double_as_longlong(e0), b1 = (uint64_t)__double_as_longlong(e1);
       double P = 0.0;
-      for (int i = 0; i < k; ++i) P += sm.e[i];   // index order
+      auto add8 = [&](uint64_t bits, int i0) {   // slots i0 .. i0 + 7 of 64 (those past k hold 0)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)bits, i0 + i);
+          const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(bits >> 32), i0 + i);
+          P += __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+        }
+      };
+      for (int i = 0; i < min(k, 64); i += 8) add8(b0, i);        // index order
+      for (int i = 0; i < k - 64; i += 8) add8(b1, i);
       bool cont = steps_done < g.D;
       if (cont && ((g.check_mask >> steps_done) & 1u) && P < (double)g.threshold) cont = false;
-      g.st.conf[b] = P;
-      g.st.active[b] = cont ? 1 : 0;
-      sm.stopped = cont ? 0 : 1;
+      if (tid == 0) {
+        g.st.conf[b] = P;
+        g.st.active[b] = cont ? 1 : 0;
+        sm.stopped = cont ? 0 : 1;
+      }
     }
     __syncthreads();
     const uint8_t on = sm.stopped ? 0 : 1;
