@@ -32,7 +32,9 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float x) {   // finite input
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
 // ---- y (+)= x W^T ----------------------------------------------------------------------------
-template <int G>
+// MULTI: several K ranges, the last of any number of units; otherwise one whole range, and the input rows stay in registers
+// for the whole kernel.
+template <int G, bool MULTI>
 __global__ __launch_bounds__(704) void linear_stream_kernel(LinearArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int NW = a.nw;
@@ -69,14 +71,17 @@ __global__ __launch_bounds__(704) void linear_stream_kernel(LinearArgs a) {
     const int woff = ks + c * 8;       // this lane's element offset inside a row of any range
     const uint16_t* wb0 = a.rg[0].W + woff;
     const int vlast = max(n1 - 1, 0);
+    // groups of 128 this wave has in the last range: a whole range unless K ends inside it (MULTI; wave-uniform)
+    const int n_last = MULTI ? min(max(a.last_units - wave * G, 0), G) : G;
 
     u32x4 ring[G][4];
     {
-      const int v0 = n0;
+      const int v0 = n0, n_first = (MULTI && NR == 1) ? n_last : G;
 #pragma unroll
       for (int g = 0; g < G; ++g)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
+          if (MULTI && g >= n_first) continue;
           const int row = min(v0 + i * 4 + lrow, vlast);
           ring[g][i] = *reinterpret_cast<const u32x4*>(wb0 + (size_t)row * a.ldw + g * 128);
         }
@@ -86,36 +91,40 @@ __global__ __launch_bounds__(704) void linear_stream_kernel(LinearArgs a) {
 #pragma unroll
     for (int r = 0; r < kLinearRanges; ++r) {
       const LinearRange& rg = a.rg[r < NR ? r : 0];
-      src[r] = n;
-      if (n < a.R) {
-        if (rg.gather_mode == kGatherIndex) src[r] = rg.gather_idx[n];
-        else if (rg.gather_mode == kGatherInBlock) src[r] = (n / a.gather_k) * a.gather_k + rg.gather_idx[n];
-        else if (rg.gather_mode == kGatherBlock) src[r] = n / a.gather_k;
-      }
+      const int nr = min(n, a.R - 1);   // operand columns past the last row repeat it: their sums are not written
+      src[r] = nr;
+      if (rg.gather_mode == kGatherIndex) src[r] = rg.gather_idx[nr];
+      else if (rg.gather_mode == kGatherInBlock) src[r] = (nr / a.gather_k) * a.gather_k + rg.gather_idx[nr];
+      else if (rg.gather_mode == kGatherBlock) src[r] = nr / a.gather_k;
     }
+    auto x_of = [&](int r) {           // this lane's source row in range r, at its first element
+      const LinearRange& rg = a.rg[r];
+      return rg.x + (size_t)(r == 0 ? src[0] : r == 1 ? src[1] : src[2]) * rg.ldx + ks + q * 8;
+    };
     bf16x8 bfrag[G][4];
+    {
+      const uint16_t* xp = x_of(0);
+#pragma unroll
+      for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          if (MULTI && NR == 1 && g >= n_last) continue;
+          bfrag[g][j] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(xp + g * 128 + j * 32));
+        }
+    }
 #pragma unroll 1
     for (int it = 0; it < total; ++it) {
       __builtin_amdgcn_sched_barrier(0);   // the previous step's operands are dead before the next ones are requested
-      const int r = it % NR;
-      if (NR > 1 || it == 0) {       // the input rows of this step's range
-        const LinearRange& rg = a.rg[r];
-        const uint16_t* xp = rg.x + (size_t)(r == 0 ? src[0] : r == 1 ? src[1] : src[2]) * rg.ldx + ks + q * 8;
-#pragma unroll
-        for (int g = 0; g < G; ++g)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            u32x4 u = {0u, 0u, 0u, 0u};
-            if (n < a.R) u = *reinterpret_cast<const u32x4*>(xp + g * 128 + j * 32);
-            bfrag[g][j] = __builtin_bit_cast(bf16x8, u);
-          }
-      }
+      const int r = it % NR, r1 = (it + 1) % NR;
       f32x4 acc;
+      const int n_cur = (MULTI && r == NR - 1) ? n_last : G;
       if (it + 1 < total) {          // refill the ring with the next step's tile while this one is consumed
-        const uint16_t* wn = a.rg[(it + 1) % NR].W + woff;
-        acc = stream_tile<G, true>(ring, bfrag, mystage, wr_off, rd_off, wn, a.ldw, n0 + ((it + 1) / NR) * 16 + lrow, vlast);
+        const uint16_t* wn = a.rg[r1].W + woff;
+        const int next_row0 = n0 + ((it + 1) / NR) * 16 + lrow, n_next = (MULTI && r1 == NR - 1) ? n_last : G;
+        acc = stream_tile<G, true, MULTI, MULTI>(ring, bfrag, mystage, wr_off, rd_off, wn, a.ldw, next_row0, vlast, n_cur, n_next,
+                                                  x_of(r1));
       } else {
-        acc = stream_tile<G, false>(ring, bfrag, mystage, wr_off, rd_off, wb0, a.ldw, 0, vlast);
+        acc = stream_tile<G, false, MULTI>(ring, bfrag, mystage, wr_off, rd_off, wb0, a.ldw, 0, vlast, n_cur);
       }
       *reinterpret_cast<f32x4*>(red + ((it & 1) * NW + wave) * 256 + lane * 4) = acc;
       __syncthreads();
@@ -163,7 +172,10 @@ template <int G>
 static hipError_t launch_linear_g(const LinearArgs& a, int nslice, hipStream_t stream) {
   const dim3 grid(nslice), block((a.nw + 1) * 64);
   const size_t lds = (size_t)2 * a.nw * 1024 + (size_t)a.nw * kStageBytes;
-  hipLaunchKernelGGL((linear_stream_kernel<G>), grid, block, lds, stream, a);
+  if (a.n_ranges > 1 || a.last_units < a.nw * G)
+    hipLaunchKernelGGL((linear_stream_kernel<G, true>), grid, block, lds, stream, a);
+  else
+    hipLaunchKernelGGL((linear_stream_kernel<G, false>), grid, block, lds, stream, a);
   return hipGetLastError();
 }
 

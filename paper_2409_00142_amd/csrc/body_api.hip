@@ -56,10 +56,24 @@ bool pick_range(int units, int* G, int* nw) {   // units = remaining K / 128
   return best > 0;
 }
 
+// The shortest range of at least `units` units (128 elements each): false if there is none.
+bool fit_range(int units, int* G, int* nw) {
+  int best = 0;
+  for (int g = 4; g >= 1; g >>= 1)
+    for (int w = 10; w >= 1; --w)
+      if (g * w >= units && (best == 0 || g * w < best)) {
+        best = g * w;
+        *G = g;
+        *nw = w;
+      }
+  return best > 0;
+}
+
 // One product y (+)= x W^T over K, cut into K ranges of 128 * G * nw elements; `a` describes the product: rg[0]
-// holds W, x and the gather of the whole K extent.  Consecutive ranges of the same length go into one launch (at
-// most kLinearRanges of them).  a.mode is the LinearMode of the whole product; a.out16 / a.out16b are written by
-// the launch that completes it.
+// holds W, x and the gather of the whole K extent.  Up to kLinearRanges ranges of the same length go into one launch, the
+// last of them shorter where K ends: a K of 11008 is 4096 + 4096 + 2816 in one launch (with ranges of whole length only,
+// 2 x 5120 and a second launch for 768: 34.5 -> 27.5 us at 4096 rows of W, with the gap).  a.mode is the LinearMode of the whole product;
+// a.out16 / a.out16b are written by the launch that completes it.
 int enqueue_linear(const ddd_body* b, LinearArgs a, int K, hipStream_t s) {
   a.ntiles = (a.N + 15) / 16;
   const int nslice = a.ntiles < b->n_cu ? a.ntiles : b->n_cu;
@@ -69,11 +83,15 @@ int enqueue_linear(const ddd_body* b, LinearArgs a, int K, hipStream_t s) {
   const int mode = a.mode;
   int k0 = 0;
   while (k0 < K) {
-    int G = 1, nw = 1;
-    pick_range((K - k0) / 128, &G, &nw);
+    const int units = (K - k0) / 128;
+    int G = 4, nw = 10, nr = kLinearRanges;                // what is left does not fit one launch: as much as goes in
+    for (int n = 1; n <= kLinearRanges; ++n)
+      if (fit_range((units + n - 1) / n, &G, &nw)) {       // fewest ranges, each as short as the grid of lengths allows
+        nr = n;
+        break;
+      }
     const int len = 128 * G * nw;
-    int nr = 1;
-    while (nr < kLinearRanges && k0 + (nr + 1) * len <= K) ++nr;
+    nr = (K - k0 + len - 1) / len < nr ? (K - k0 + len - 1) / len : nr;   // a length rounded up may need fewer
     const bool last = k0 + nr * len >= K;
     // the gate needs complete sums: such a product must fit one launch
     if (mode == kLinearSiluPairs && !(k0 == 0 && last)) return DDD_ERR_INVALID_ARG;
@@ -86,6 +104,7 @@ int enqueue_linear(const ddd_body* b, LinearArgs a, int K, hipStream_t s) {
     a.out16 = last ? out16 : nullptr;
     a.out16b = last ? out16b : nullptr;
     a.nw = nw;
+    a.last_units = last ? (K - k0 - (nr - 1) * len) / 128 : G * nw;
     a.mode = (k0 > 0) ? (int)kLinearAccumulate : mode;
     BODY_HIP(launch_linear_stream(a, G, nslice, s));
     k0 += nr * len;
@@ -100,6 +119,7 @@ int enqueue_linear_ranges(const ddd_body* b, LinearArgs a, int K_range, hipStrea
   if (!pick_range(K_range / 128, &G, &nw) || 128 * G * nw != K_range) return DDD_ERR_INVALID_ARG;
   a.ntiles = (a.N + 15) / 16;
   a.nw = nw;
+  a.last_units = G * nw;
   const int nslice = a.ntiles < b->n_cu ? a.ntiles : b->n_cu;
   BODY_HIP(launch_linear_stream(a, G, nslice, s));
   return DDD_OK;

@@ -33,8 +33,8 @@ struct LinearRange {
   int gather_mode, ldx;
 };
 constexpr int kLinearRanges = 3;
-// One launch covers n_ranges K ranges of the same length 128*G*nw and adds them up in order before
-// the epilogue runs: y (+)= sum_ranges x_range W_range^T.
+// One launch covers n_ranges K ranges of the same length 128*G*nw (the last may be shorter) and adds them up in order
+// before the epilogue runs: y (+)= sum_ranges x_range W_range^T.
 struct LinearArgs {
   LinearRange rg[kLinearRanges];
   int n_ranges, gather_k;
@@ -43,6 +43,7 @@ struct LinearArgs {
   uint16_t* out16;            // null, or bf16 [R] with row pitch ld16: the rounded result (modes 0/1), the activations (mode 2)
   uint16_t* out16b;           // null, or a second copy of out16 (same pitch)
   int ldw, ldy, ld16, N, R, ntiles, nw, mode;
+  int last_units;             // 128-element units of the last range (fewer than a whole range: the product's K ends there)
 };
 hipError_t launch_linear_stream(const LinearArgs& a, int G, int nslice, hipStream_t stream);
 
