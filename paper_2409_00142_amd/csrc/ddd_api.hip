@@ -334,7 +334,6 @@ int ddd_create(const ddd_config* cfg, ddd_ctx** out) {
     if (e == hipSuccess) e = prepare_lmhead_gemm();
     if (e == hipSuccess && cfg->k > DDD_KMAX) e = prepare_wide();
   }
-  if (e == hipSuccess) e = prepare_tree_attention();
   c->small = nullptr;
   c->call_count = nullptr;
   c->active_mask = nullptr;
@@ -431,15 +430,8 @@ int ddd_weights_pack(ddd_ctx* c, const void* W, void* stream) {
 }
 
 namespace {
-// Key splits of the tree attention: about two workgroups per CU, at least eight 32-key chunks per split.
 int attn_splits(const ddd_ctx* c, int n_heads, int L) {
-  const int T = c->cfg.m + 1, nqt = (T + 63) / 64;
-  const int nchunks = (L + 31) / 32 + (T + 31) / 32;
-  int ns = (2 * c->n_cu) / (c->cfg.B * n_heads * nqt);
-  const int cap = nchunks / 8 > 1 ? nchunks / 8 : 1;
-  if (ns > cap) ns = cap;
-  if (ns > 64) ns = 64;
-  return ns < 1 ? 1 : ns;
+  return tree_attention_splits(c->cfg.B, n_heads, c->cfg.m + 1, L, c->n_cu);
 }
 }  // namespace
 
@@ -484,7 +476,7 @@ int ddd_tree_attention(ddd_ctx* c, const ddd_tree* tree, const void* q, const vo
   a.L = L;
   a.Tp = (a.T + 31) & ~31;
   a.nsplit = attn_splits(c, n_heads, L);
-  DDD_HIP(launch_tree_attention(a, static_cast<hipStream_t>(stream)));
+  DDD_HIP(launch_tree_attention(a, c->n_cu, static_cast<hipStream_t>(stream)));
   return DDD_OK;
 }
 

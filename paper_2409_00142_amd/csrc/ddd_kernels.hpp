@@ -242,11 +242,11 @@ struct TreeAttnArgs {
   float* out;                 // fp32 [B][T][nh][128]
   int B, T, nh, L, Tp, nsplit;
 };
-hipError_t prepare_tree_attention();
 // k, v: bf16 [B][L][nh][128] -> the fragment-order cache the attention reads (each ceil(L/32)*32*nh*128*B elements)
 hipError_t launch_kv_pack(const uint16_t* k, const uint16_t* v, uint16_t* kp, uint16_t* vp, int B, int L, int nh,
                           hipStream_t stream);
 size_t tree_attention_part_floats();
-hipError_t launch_tree_attention(const TreeAttnArgs& a, hipStream_t stream);
+int tree_attention_splits(int B, int n_heads, int T, int L, int n_cu);   // TreeAttnArgs::nsplit
+hipError_t launch_tree_attention(const TreeAttnArgs& a, int n_cu, hipStream_t stream);
 
 }  // namespace ddd

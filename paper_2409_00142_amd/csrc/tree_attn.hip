@@ -5,18 +5,23 @@
 //   out[i] = sum_j softmax_j(q_i . k_j / sqrt(128)) v_j   over the L prompt keys and the tree keys
 //                                                         j with mask[i][j] = 1, per sequence and head
 //
-// The prompt's keys and values are read once (HBM-bound: 2 * L * 256 bytes per head), so the
-// kernel is a split-key ("flash decoding") pass: workgroup = 4 waves, every wave takes chunks of
-// 32 keys for a tile of 64 queries and keeps a running max / sum / output per query.
-// Both products run on v_mfma_f32_32x32x16_bf16 in transposed form, which puts one query in one
-// lane, so the softmax rescaling is a per-lane scalar:
+// The prompt's keys and values are read once (HBM-bound: 2 * L * 256 bytes per head), so the kernel is a split-key
+// ("flash decoding") pass for tiles of 64 queries.  A workgroup of NW = 4 or 8 waves takes NW chunks of 32 keys at a time: every
+// wave makes the scores of one chunk, the waves agree on each query's softmax reference through LDS and leave the weights
+// there, and then every wave sums its own tile of the output (32 elements of the head for 64 or 32 queries) over all the
+// chunks.  No wave's output is merged with another's and a wave holds 16 or 32 accumulators instead of 128: three workgroups
+// of four share a CU, so loads fly under other waves' products (64 users, L = 2048: 493 -> 426 us, 5.4 TB/s), and the code of a
+// pass is short where it runs once (one user, L = 1999: 27.5 -> 22.8 us).
+// Both products run on v_mfma_f32_32x32x16_bf16 in transposed form, which puts one
+// query in one lane, so the softmax rescaling is a per-lane scalar:
 //   S^T[key][query]  = K[key][d]   Q^T[d][query]     (A = 32 keys x 16 d from the key cache as stored)
 //   O^T[d][query]   += V^T[d][key] P^T[key][query]   (A = 32 d x 16 keys from the transposed value cache)
 // The accumulator of the first product holds, per lane, keys g*8 + 4*lh + 0..3 (g = 0..3), which is
 // not the 8 consecutive keys a B operand wants; the second product simply contracts over the keys
 // in that order, by loading V^T as two 4-key pieces per operand.
-// The four waves of a workgroup merge through LDS into one partial per workgroup; a second kernel
-// merges the workgroups' partials.
+// Where a head is split over workgroups, a second kernel merges their partials.
+#include <algorithm>
+
 #include "ddd_device.hpp"
 #include "ddd_kernels.hpp"
 
@@ -30,11 +35,21 @@ typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
 constexpr int kAD = 128;        // head dimension
 constexpr int kQT = 64;         // queries per tile
 constexpr int kPartFloats = kAD * kQT + 2 * kQT;   // one partial: O^T[128][64], m[64], l[64]
-constexpr int kLdsPitch = kQT + 1;                 // a wave's O^T in LDS: rows padded, so that reads along d are conflict-free too
-constexpr int kLdsPart = kAD * kLdsPitch + 2 * kQT + 2 * kQT;   // ... + m[64], l[64], weight[64], spare
+constexpr int kOutPitch = kAD + 4;                 // O[query][d] in LDS at the end: rows padded, 16 bytes aligned
+// Waves of a workgroup = chunks of 32 keys of a step: a wave of four sums a quarter of the head for all 64 queries, one of
+// eight for half of them.
+template <int NW>
+struct AttnCfg {
+  static constexpr int NQ = 8 / NW;                          // blocks of 32 queries of a wave's output
+  static constexpr int kLdsQ = 16 * 64, kLdsP = NW * 4 * 64;   // 16-byte pieces: the queries, the weights of a step
+  static constexpr int kTile = (kLdsQ + kLdsP) * 16 > kQT * kOutPitch * 4 ? (kLdsQ + kLdsP) * 16 : kQT * kOutPitch * 4;
+  static constexpr int kLdsBytes = kTile + NW * kQT * 4;     // ... and the chunks' maxima (in the end: sums) per query
+};
 constexpr float kLazy = 11.0f;  // how far (in powers of two) a score may exceed a query's softmax reference before it moves
 
 typedef __attribute__((ext_vector_type(2))) float f32x2;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef f32x4 f32x4_of_floats __attribute__((aligned(4)));   // the caller's output starts on any float
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {   // round to nearest even (one v_cvt_pk_bf16_f32)
@@ -42,288 +57,347 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {   // round
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2));
 }
 
-// Operands of one chunk of 32 keys for one wave.
-struct KeyOperands {
-  bf16x8 kf[8];      // keys as A operands: lane (l32, lh) holds d = s*16 + lh*8 .. +7 of key c0 + l32
+// Steps of a head: the prompt's whole ones, then the rest of its keys and the tree's (chunks of 32, the last of either ragged).
+struct AttnSteps {
+  int full, rest_prompt, rest, all;   // whole steps; chunks of the rest from the prompt, in all; steps in all
 };
-struct ValueOperands {
-  bf16x8 vf[4][2];   // transposed values as A operands: lane (l32, lh) holds, for d = db*32 + l32 and 16-key step t,
-                     // the keys c0 + 16t + 4*lh + 0..3 and c0 + 16t + 8 + 4*lh + 0..3 (the order the first product
-                     // leaves them in)
+__host__ __device__ __forceinline__ AttnSteps attn_steps(int L, int T, int nw) {
+  AttnSteps n;
+  n.full = L / (32 * nw);
+  n.rest_prompt = (L - n.full * 32 * nw + 31) / 32;
+  n.rest = n.rest_prompt + (T + 31) / 32;
+  n.all = n.full + (n.rest + nw - 1) / nw;
+  return n;
+}
+
+// Operands of one step for one wave.
+template <int NW>
+struct Operands {
+  bf16x8 kf[8];           // its chunk's keys as A operands: lane (l32, lh) holds d = s*16 + lh*8 .. +7 of key c0 + l32
+  bf16x8 vf[NW][2];       // every chunk's values for its quarter of the head as A operands: lane (l32, lh) holds, for
+                          // d = db*32 + l32 and 16-key step t, the keys c0 + 16t + 4*lh + 0..3 and
+                          // c0 + 16t + 8 + 4*lh + 0..3 (the order the first product leaves them in)
 };
 
-// Prompt chunks come from the packed cache (fragment order: every operand of a wave is 1 KB of consecutive
-// memory, 16 bytes per lane); the two tree chunks from the tree's own small arrays.
-__device__ __forceinline__ void load_keys(const TreeAttnArgs& a, int c, int ncp, int b, int h, int lane,
-                                          KeyOperands& x) {
-  const int l32 = lane & 31, lh = lane >> 5;
-  if (c < ncp) {
-    const u32x4* kp = reinterpret_cast<const u32x4*>(a.k_prompt) + ((((size_t)b * a.nh + h) * ncp + c) * 8) * 64 + lane;
+// Prompt chunks come from the packed cache (fragment order: every operand of a wave is 1 KB of consecutive memory, 16 bytes per
+// lane), 512 16-byte pieces of keys and as many of values per chunk.
+__device__ __forceinline__ const u32x4* prompt_chunk(const TreeAttnArgs& a, const uint16_t* base, int c, int b, int h) {
+  return reinterpret_cast<const u32x4*>(base) + (((size_t)b * a.nh + h) * ((a.L + 31) >> 5) + c) * 512;
+}
+
+// A step of prompt keys and tree keys that are not all there (the steps after the whole ones of the prompt).  Chunk ch
+// of the step is chunk i = first + ch of the rest: prompt chunks, then the tree's, then nothing.
+// vis: which of the lane's 16 keys of this wave's chunk count for its two queries, bit e as the accumulator registers go.
+template <int NW>
+__device__ __forceinline__ void load_rest(const TreeAttnArgs& a, int first, int c_rest, int n_prompt, int n_rest, int b, int h, int qt,
+                                          int wave, int lane, Operands<NW>& x, uint32_t (&vis)[2]) {
+  const int l32 = lane & 31, lh = lane >> 5, db = wave / (NW / 4);
+  const u32x4 zero = {0u, 0u, 0u, 0u};
+  const int i = first + wave;
+  vis[0] = vis[1] = 0u;
+  if (i < n_prompt) {
+    const u32x4* kp = prompt_chunk(a, a.k_prompt, c_rest + i, b, h);
 #pragma unroll
-    for (int s = 0; s < 8; ++s) x.kf[s] = __builtin_bit_cast(bf16x8, kp[s * 64]);
-  } else {
-    const int kj = min((c - ncp) * 32 + l32, a.T - 1);
+    for (int s = 0; s < 8; ++s) x.kf[s] = __builtin_bit_cast(bf16x8, kp[s * 64 + lane]);
+#pragma unroll
+    for (int e = 0; e < 16; ++e)
+      vis[0] |= ((c_rest + i) * 32 + (e >> 2) * 8 + lh * 4 + (e & 3) < a.L) ? (1u << e) : 0u;
+    vis[1] = vis[0];
+  } else if (i < n_rest) {
+    const int c0 = (i - n_prompt) * 32, kj = min(c0 + l32, a.T - 1);
     const uint16_t* kp = a.k_tree + (((size_t)b * a.T + kj) * a.nh + h) * kAD + lh * 8;
 #pragma unroll
     for (int s = 0; s < 8; ++s) x.kf[s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(kp + s * 16));
-  }
-}
-
-__device__ __forceinline__ void load_values(const TreeAttnArgs& a, int c, int ncp, int b, int h, int lane,
-                                            ValueOperands& x) {
-  const int l32 = lane & 31, lh = lane >> 5;
-  if (c < ncp) {
-    const u32x4* vp = reinterpret_cast<const u32x4*>(a.v_prompt) + ((((size_t)b * a.nh + h) * ncp + c) * 8) * 64 + lane;
 #pragma unroll
-    for (int db = 0; db < 4; ++db)
+    for (int qb = 0; qb < 2; ++qb) {
+      const int qi = qt * kQT + qb * 32 + l32;
+      const uint8_t* mrow = a.mask + ((size_t)b * a.T + min(qi, a.T - 1)) * a.T;
 #pragma unroll
-      for (int t = 0; t < 2; ++t) x.vf[db][t] = __builtin_bit_cast(bf16x8, vp[(db * 2 + t) * 64]);
+      for (int e = 0; e < 16; ++e) {
+        const int key = c0 + (e >> 2) * 8 + lh * 4 + (e & 3);
+        const uint8_t on = mrow[min(key, a.T - 1)];
+        vis[qb] |= (key < a.T && qi < a.T && on != 0) ? (1u << e) : 0u;
+      }
+    }
   } else {
-    const uint16_t* vp = a.vt_tree + (((size_t)b * a.nh + h) * kAD + l32) * a.Tp + (c - ncp) * 32 + lh * 4;
 #pragma unroll
-    for (int db = 0; db < 4; ++db)
+    for (int s = 0; s < 8; ++s) x.kf[s] = __builtin_bit_cast(bf16x8, zero);
+  }
+  const uint16_t* vt = a.vt_tree + (((size_t)b * a.nh + h) * kAD + db * 32 + l32) * a.Tp + lh * 4;
+#pragma unroll
+  for (int ch = 0; ch < NW; ++ch) {
+    const int j = first + ch;                                // uniform
+    if (j < n_prompt) {
+      const u32x4* vp = prompt_chunk(a, a.v_prompt, c_rest + j, b, h) + db * 128 + lane;
+#pragma unroll
+      for (int t = 0; t < 2; ++t) x.vf[ch][t] = __builtin_bit_cast(bf16x8, vp[t * 64]);
+    } else if (j < n_rest) {
+      const uint16_t* vp = vt + (j - n_prompt) * 32;
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
-        const u32x2 lo = *reinterpret_cast<const u32x2*>(vp + (size_t)db * 32 * a.Tp + t * 16);
-        const u32x2 hi = *reinterpret_cast<const u32x2*>(vp + (size_t)db * 32 * a.Tp + t * 16 + 8);
-        const u32x4 u = {lo[0], lo[1], hi[0], hi[1]};
-        x.vf[db][t] = __builtin_bit_cast(bf16x8, u);
+        const u32x2 lo = *reinterpret_cast<const u32x2*>(vp + t * 16), hi = *reinterpret_cast<const u32x2*>(vp + t * 16 + 8);
+        x.vf[ch][t] = __builtin_bit_cast(bf16x8, u32x4{lo[0], lo[1], hi[0], hi[1]});
       }
+    } else {
+      x.vf[ch][0] = x.vf[ch][1] = __builtin_bit_cast(bf16x8, zero);
+    }
   }
 }
 
-// Running softmax state of the wave's 64 queries (one per lane and query block) and their outputs.
+// LDS is exchanged, loads from global memory stay in flight (__syncthreads() would wait for them).
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// Softmax state of the queries: reference and this wave's share of the sum for the lane's query of both blocks (the
+// references are the same in every wave), and the wave's output tile (d = db*32 .., query qb*32 + l32).
+template <int NW>
 struct QueryState {
-  f32x16 o[4][2];
+  f32x16 o[AttnCfg<NW>::NQ];
   float m[2], l[2];
 };
 
-__device__ __forceinline__ void attend_chunk(const TreeAttnArgs& a, const KeyOperands& x, const ValueOperands& xv,
-                                             const bf16x8 (&qf)[2][8], int c,
-                                             int ncp, int b, int qt, int lane, QueryState& st) {
-  const int l32 = lane & 31, lh = lane >> 5;
-  const bool tree = c >= ncp;
-  const int c0 = (tree ? c - ncp : c) * 32;
-  const int nkeys = tree ? a.T : a.L;
+// One step.  NEXT: the operands of the next whole step are requested from kn and vn, each as soon as its register has been used.
+template <int NW, bool REST, bool NEXT>
+__device__ __forceinline__ void attend_step(Operands<NW>& x, const u32x4* qlds, u32x4* plds, float* cmax_lds, const uint32_t (&vis)[2],
+                                            const u32x4* kn, const u32x4* vn, int wave, int lane, QueryState<NW>& st) {
   // scores are kept in units of ln 2: exp(s - m) = exp2(s' - m') with s' = s * log2(e) / sqrt(128)
   const float scale = 0.08838834764831845f * 1.4426950408889634f;
-  const bool ragged = tree || c0 + 32 > nkeys;          // uniform: only such chunks have keys to hide
-  bf16x8 pf[2][2];
+  const int l32 = lane & 31;
+  float sv[2][16];
 #pragma unroll
   for (int qb = 0; qb < 2; ++qb) {
     f32x16 sacc;
 #pragma unroll
     for (int e = 0; e < 16; ++e) sacc[e] = 0.f;
 #pragma unroll
-    for (int s = 0; s < 8; ++s) sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x.kf[s], qf[qb][s], sacc, 0, 0, 0);
+    for (int s = 0; s < 8; ++s) {
+      sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x.kf[s], __builtin_bit_cast(bf16x8, qlds[(qb * 8 + s) * 64 + lane]), sacc, 0, 0, 0);
+      if (NEXT && qb == 1) x.kf[s] = __builtin_bit_cast(bf16x8, kn[s * 64 + lane]);
+    }
     // register e of the lane: key c0 + (e>>2)*8 + lh*4 + (e&3), query qb*32 + l32
-    float sv[16];
     float cmax = -INFINITY;
-    if (ragged) {
-      const int qi = qt * kQT + qb * 32 + l32;
-      const uint8_t* mrow = a.mask + ((size_t)b * a.T + min(qi, a.T - 1)) * a.T;
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int key = c0 + (e >> 2) * 8 + lh * 4 + (e & 3);
-        bool ok = key < nkeys;
-        if (tree) ok = ok && qi < a.T && mrow[min(key, a.T - 1)] != 0;
-        sv[e] = ok ? sacc[e] * scale : -INFINITY;
-        cmax = fmaxf(cmax, sv[e]);
-      }
-    } else {
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        sv[e] = sacc[e] * scale;
-        cmax = fmaxf(cmax, sv[e]);
-      }
+    for (int e = 0; e < 16; ++e) {
+      sv[qb][e] = (!REST || ((vis[qb] >> e) & 1u)) ? sacc[e] * scale : -INFINITY;
+      cmax = fmaxf(cmax, sv[qb][e]);
     }
     cmax = fmaxf(cmax, __shfl_xor(cmax, 32, 64));            // the other half of the query's keys
+    if (lane < 32) cmax_lds[wave * kQT + qb * 32 + l32] = cmax;
+  }
+  lds_barrier();
+  float alpha[2];
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb) {
+    float cmax = cmax_lds[qb * 32 + l32];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) cmax = fmaxf(cmax, cmax_lds[w * kQT + qb * 32 + l32]);
     // The reference m of a query only moves when a score exceeds it by more than kLazy: until then the
-    // weights 2^(s - m) may grow to 2^kLazy (harmless in fp32 and in bf16), and the 64 accumulators of the
-    // query need no rescaling, which for most chunks spares the whole wave the pass over its accumulators.
+    // weights 2^(s - m) may grow to 2^kLazy (harmless in fp32 and in bf16), and outputs need no rescaling.
     const float m_new = (cmax > st.m[qb] + kLazy || st.m[qb] == -INFINITY) ? cmax : st.m[qb];
-    const float alpha = (m_new == st.m[qb]) ? 1.f : exp2f(st.m[qb] - m_new);
+    alpha[qb] = (m_new == st.m[qb]) ? 1.f : exp2f(st.m[qb] - m_new);
     float psum = 0.f;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-      sv[e] = __builtin_amdgcn_exp2f(sv[e] - m_new);                           // exp2(-inf) = 0 for hidden keys; m_new is finite
-      psum += sv[e];                                          // whenever a key of the query has been seen
+      sv[qb][e] = __builtin_amdgcn_exp2f(sv[qb][e] - m_new);   // exp2(-inf) = 0 for hidden keys; m_new is finite
+      psum += sv[qb][e];                                       // whenever a key of the query has been seen
     }
-    if (m_new == -INFINITY) {                                 // nothing visible yet: all weights are zero, not NaN
+    if (m_new == -INFINITY) {                                  // nothing visible yet: all weights are zero, not NaN
 #pragma unroll
-      for (int e = 0; e < 16; ++e) sv[e] = 0.f;
+      for (int e = 0; e < 16; ++e) sv[qb][e] = 0.f;
       psum = 0.f;
     }
-    psum += __shfl_xor(psum, 32, 64);
-    st.l[qb] = st.l[qb] * alpha + psum;
+    st.l[qb] = st.l[qb] * alpha[qb] + psum;
     st.m[qb] = m_new;
-    if (__any(alpha != 1.f)) {                               // uniform
 #pragma unroll
-      for (int db = 0; db < 4; ++db)
+    for (int t = 0; t < 2; ++t)
+      plds[((wave * 2 + qb) * 2 + t) * 64 + lane] =
+          u32x4{pack_bf16x2(sv[qb][8 * t], sv[qb][8 * t + 1]), pack_bf16x2(sv[qb][8 * t + 2], sv[qb][8 * t + 3]),
+                pack_bf16x2(sv[qb][8 * t + 4], sv[qb][8 * t + 5]), pack_bf16x2(sv[qb][8 * t + 6], sv[qb][8 * t + 7])};
+  }
+  constexpr int NQ = AttnCfg<NW>::NQ;
 #pragma unroll
-        for (int e = 0; e < 16; ++e) st.o[db][qb][e] *= alpha;
+  for (int i = 0; i < NQ; ++i) {
+    const float al = (NQ == 2 ? i == 1 : (wave & 1) != 0) ? alpha[1] : alpha[0];
+    if (__any(al != 1.f)) {                                    // uniform
+#pragma unroll
+      for (int e = 0; e < 16; ++e) st.o[i][e] *= al;
     }
+  }
+  lds_barrier();
+#pragma unroll
+  for (int ch = 0; ch < NW; ++ch)
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-      const u32x4 u = {pack_bf16x2(sv[8 * t], sv[8 * t + 1]), pack_bf16x2(sv[8 * t + 2], sv[8 * t + 3]),
-                       pack_bf16x2(sv[8 * t + 4], sv[8 * t + 5]), pack_bf16x2(sv[8 * t + 6], sv[8 * t + 7])};
-      pf[qb][t] = __builtin_bit_cast(bf16x8, u);
+#pragma unroll
+      for (int i = 0; i < NQ; ++i) {
+        const int qb = NQ == 2 ? i : (wave & 1);
+        st.o[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+            x.vf[ch][t], __builtin_bit_cast(bf16x8, plds[((ch * 2 + qb) * 2 + t) * 64 + lane]), st.o[i], 0, 0, 0);
+      }
+      if (NEXT) x.vf[ch][t] = __builtin_bit_cast(bf16x8, vn[ch * 512 + t * 64 + lane]);
     }
-  }
-#pragma unroll
-  for (int t = 0; t < 2; ++t)
-#pragma unroll
-    for (int db = 0; db < 4; ++db)
-#pragma unroll
-      for (int qb = 0; qb < 2; ++qb)
-        st.o[db][qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xv.vf[db][t], pf[qb][t], st.o[db][qb], 0, 0, 0);
 }
 
-__global__ __launch_bounds__(256, 1) void tree_attn_partial_kernel(TreeAttnArgs a) {
-  extern __shared__ __align__(16) float lds[];   // [4][kLdsPart]: the waves' partials at the end
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l32 = lane & 31, lh = lane >> 5;
+template <int NW>
+__global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void tree_attn_partial_kernel(TreeAttnArgs a) {
+  using C = AttnCfg<NW>;
+  __shared__ __align__(16) unsigned char lds[C::kLdsBytes];
+  u32x4* qlds = reinterpret_cast<u32x4*>(lds);         // [qb * 8 + s][lane] queries as B operands
+  u32x4* plds = qlds + C::kLdsQ;                          // [chunk][qb][t][lane] weights as B operands
+  float* cmax_lds = reinterpret_cast<float*>(lds + C::kTile);   // [chunk][query]
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, lh = lane >> 5;
+  const int db = wave / (NW / 4);
   const int nqt = (a.T + kQT - 1) / kQT;
   const int split = blockIdx.x / nqt, qt = blockIdx.x - split * nqt, h = blockIdx.y, b = blockIdx.z;
-  const int gw = split * 4 + wave, ngw = a.nsplit * 4;
-  const int ncp = (a.L + 31) >> 5, nct = (a.T + 31) >> 5;   // chunks of prompt keys, of tree keys
-  const int nc = ncp + nct;
+  const AttnSteps n = attn_steps(a.L, a.T, NW);
 
-  // queries of this tile as B operands: lane (l32, lh) holds d = s*16 + lh*8 .. +7 of query qb*32 + l32
-  bf16x8 qf[2][8];
+  // the first step's operands are on their way while the queries are staged; the workgroup takes steps split, split + nsplit, ...
+  int sc = split;
+  Operands<NW> x;
+  const u32x4 *kp = nullptr, *vp = nullptr;
+  uint32_t vis[2];
+  if (sc < n.full) {
+    kp = prompt_chunk(a, a.k_prompt, sc * NW + wave, b, h);
+    vp = prompt_chunk(a, a.v_prompt, sc * NW, b, h) + db * 128;
 #pragma unroll
-  for (int qb = 0; qb < 2; ++qb) {
-    const int qi = qt * kQT + qb * 32 + l32;
-    const uint16_t* qp = a.q + (((size_t)b * a.T + min(qi, a.T - 1)) * a.nh + h) * kAD + lh * 8;
+    for (int s = 0; s < 8; ++s) x.kf[s] = __builtin_bit_cast(bf16x8, kp[s * 64 + lane]);
 #pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      u32x4 u = {0u, 0u, 0u, 0u};
-      if (qi < a.T) u = *reinterpret_cast<const u32x4*>(qp + s * 16);
-      qf[qb][s] = __builtin_bit_cast(bf16x8, u);
-    }
+    for (int ch = 0; ch < NW; ++ch)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) x.vf[ch][t] = __builtin_bit_cast(bf16x8, vp[ch * 512 + t * 64 + lane]);
   }
-  QueryState st;
+  {
+    // lane (l32, lh) holds d = s*16 + lh*8 .. +7 of query qb*32 + l32
+    u32x4 u[16 / NW];
 #pragma unroll
-  for (int db = 0; db < 4; ++db)
+    for (int i = 0; i < 16 / NW; ++i) {
+      const int f = wave * (16 / NW) + i, qi = qt * kQT + (f >> 3) * 32 + l32;
+      u[i] = u32x4{0u, 0u, 0u, 0u};
+      if (qi < a.T) u[i] = *reinterpret_cast<const u32x4*>(a.q + (((size_t)b * a.T + qi) * a.nh + h) * kAD + lh * 8 + (f & 7) * 16);
+    }
 #pragma unroll
-    for (int qb = 0; qb < 2; ++qb)
+    for (int i = 0; i < 16 / NW; ++i) qlds[(wave * (16 / NW) + i) * 64 + lane] = u[i];
+  }
+  QueryState<NW> st;
 #pragma unroll
-      for (int e = 0; e < 16; ++e) st.o[db][qb][e] = 0.f;
+  for (int i = 0; i < C::NQ; ++i)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) st.o[i][e] = 0.f;
   st.m[0] = st.m[1] = -INFINITY;
   st.l[0] = st.l[1] = 0.f;
+  lds_barrier();
 
-  for (int c = gw; c < nc; c += ngw) {   // chunks gw, gw + ngw, ...
-    KeyOperands k;
-    ValueOperands v;
-    load_keys(a, c, ncp, b, h, lane, k);
-    load_values(a, c, ncp, b, h, lane, v);
-    attend_chunk(a, k, v, qf, c, ncp, b, qt, lane, st);
-  }
-
-  // the four waves' partials meet in LDS ...
-  float* mine = lds + wave * kLdsPart;
-#pragma unroll
-  for (int db = 0; db < 4; ++db)
-#pragma unroll
-    for (int qb = 0; qb < 2; ++qb)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int d = db * 32 + (e >> 2) * 8 + lh * 4 + (e & 3);
-        mine[d * kLdsPitch + qb * 32 + l32] = st.o[db][qb][e];
-      }
-  if (lh == 0) {
-#pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
-      mine[kAD * kLdsPitch + qb * 32 + l32] = st.m[qb];
-      mine[kAD * kLdsPitch + kQT + qb * 32 + l32] = st.l[qb];
+  if (sc < n.full) {
+    const size_t stride = (size_t)a.nsplit * NW * 512;
+#pragma unroll 1
+    for (; sc + a.nsplit < n.full; sc += a.nsplit) {
+      kp += stride;
+      vp += stride;
+      attend_step<NW, false, true>(x, qlds, plds, cmax_lds, vis, kp, vp, wave, lane, st);
     }
+    attend_step<NW, false, false>(x, qlds, plds, cmax_lds, vis, nullptr, nullptr, wave, lane, st);
+    sc += a.nsplit;
   }
-  __syncthreads();
-  // ... and leave as one partial of the workgroup (fixed order): weight of every wave's partial per query first
-  if (tid < kQT) {
-    float M = -INFINITY;
+#pragma unroll 1
+  for (; sc < n.all; sc += a.nsplit) {
+    load_rest<NW>(a, (sc - n.full) * NW, n.full * NW, n.rest_prompt, n.rest, b, h, qt, wave, lane, x, vis);
+    attend_step<NW, true, false>(x, qlds, plds, cmax_lds, vis, nullptr, nullptr, wave, lane, st);
+  }
+
+  // the waves' shares of the queries' sums
+  lds_barrier();
 #pragma unroll
-    for (int w = 0; w < 4; ++w) M = fmaxf(M, lds[w * kLdsPart + kAD * kLdsPitch + tid]);
+  for (int q2 = 0; q2 < 2; ++q2) {
+    const float l = st.l[q2] + __shfl_xor(st.l[q2], 32, 64);
+    if (lane < 32) cmax_lds[wave * kQT + q2 * 32 + l32] = l;
+  }
+  lds_barrier();
+  float* ol = reinterpret_cast<float*>(lds);             // [query][d]
+#pragma unroll
+  for (int i = 0; i < C::NQ; ++i) {
+    const int qb = C::NQ == 2 ? i : (wave & 1), q = qb * 32 + l32;
     float lsum = 0.f;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const float mw = lds[w * kLdsPart + kAD * kLdsPitch + tid];
-      const float wg = (mw == -INFINITY) ? 0.f : exp2f(mw - M);
-      lsum += wg * lds[w * kLdsPart + kAD * kLdsPitch + kQT + tid];
-      lds[w * kLdsPart + kAD * kLdsPitch + 2 * kQT + tid] = wg;
+    for (int w = 0; w < NW; ++w) lsum += cmax_lds[w * kQT + q];   // fixed order
+    if (a.nsplit == 1) {
+      const float inv = 1.f / lsum;
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        *reinterpret_cast<f32x4*>(ol + q * kOutPitch + db * 32 + g * 8 + lh * 4) =
+            f32x4{st.o[i][g * 4] * inv, st.o[i][g * 4 + 1] * inv, st.o[i][g * 4 + 2] * inv, st.o[i][g * 4 + 3] * inv};
+    } else {
+      float* part = a.part + ((((size_t)b * a.nh + h) * nqt + qt) * a.nsplit + split) * kPartFloats + q;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) part[(db * 32 + (e >> 2) * 8 + lh * 4 + (e & 3)) * kQT] = st.o[i][e];
+      if (db == 0 && lane < 32) {
+        part[kAD * kQT] = qb != 0 ? st.m[1] : st.m[0];
+        part[kAD * kQT + kQT] = lsum;
+      }
     }
-    lds[kAD * kLdsPitch + 3 * kQT + tid] = M;             // spare slots of wave 0's area
-    lds[kLdsPart + kAD * kLdsPitch + 3 * kQT + tid] = lsum;   // ... and of wave 1's
   }
-  __syncthreads();
-  const float* wgt = lds + kAD * kLdsPitch + 2 * kQT;     // weight of wave w for query q at wgt[w * kLdsPart + q]
-  const float* sM = lds + kAD * kLdsPitch + 3 * kQT;
-  const float* sL = lds + kLdsPart + kAD * kLdsPitch + 3 * kQT;
   if (a.nsplit == 1) {
-    // the only partial of its queries: finish here, no merge pass; consecutive threads write consecutive d
-    const int d = tid & (kAD - 1);
-    for (int q = tid >> 7; q < kQT; q += 2) {
+    // the only partial of its queries: finish here, no merge pass; through LDS, so that whole rows are written
+    lds_barrier();
+    const int d = (tid & 31) * 4;
+#pragma unroll
+    for (int q = tid >> 5; q < kQT; q += 2 * NW) {
       const int qi = qt * kQT + q;
-      if (qi >= a.T) break;
-      float acc = 0.f;
-#pragma unroll
-      for (int w = 0; w < 4; ++w) acc += wgt[w * kLdsPart + q] * lds[w * kLdsPart + d * kLdsPitch + q];
-      // tree indices past n_sel are padding: zero rows
-      a.out[(((size_t)b * a.T + qi) * a.nh + h) * kAD + d] = (qi <= a.n_sel[b]) ? acc / sL[q] : 0.f;
+      f32x4 v = *reinterpret_cast<const f32x4*>(ol + q * kOutPitch + d);
+      if (qi < a.T) {
+        if (qi > a.n_sel[b]) v = f32x4{0.f, 0.f, 0.f, 0.f};   // tree indices past n_sel are padding: zero rows
+        *reinterpret_cast<f32x4_of_floats*>(a.out + (((size_t)b * a.T + qi) * a.nh + h) * kAD + d) = v;
+      }
     }
-    return;
-  }
-  float* part = a.part + ((((size_t)b * a.nh + h) * nqt + qt) * a.nsplit + split) * kPartFloats;
-  const int qx = tid & (kQT - 1);
-  for (int d = tid >> 6; d < kAD; d += 4) {
-    float acc = 0.f;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) acc += wgt[w * kLdsPart + qx] * lds[w * kLdsPart + d * kLdsPitch + qx];
-    part[d * kQT + qx] = acc;
-  }
-  if (tid < kQT) {
-    part[kAD * kQT + qx] = sM[qx];
-    part[kAD * kQT + kQT + qx] = sL[qx];
   }
 }
 
-// Merge of the workgroups' partials: one workgroup per (query tile x quarter of the head, head, sequence).
-constexpr int kMaxSplits = 64;
+// Merge of the workgroups' partials: one workgroup per (query tile x eighth of the head, head, sequence).  Every thread asks for
+// its partials eight at a time, the references and sums together with the outputs: one or two memory latencies in all.
+constexpr int kMergeD = 16;   // elements of the head per workgroup
 
 __global__ __launch_bounds__(256) void tree_attn_merge_kernel(TreeAttnArgs a) {
-  __shared__ float sw[kMaxSplits][kQT];   // weight of every partial for every query
-  __shared__ float sden[kQT];
   const int nqt = (a.T + kQT - 1) / kQT;
-  const int qt = blockIdx.x >> 2, dq0 = (blockIdx.x & 3) * 32, h = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
+  const int qt = blockIdx.x / (kAD / kMergeD), dq0 = (blockIdx.x % (kAD / kMergeD)) * kMergeD, h = blockIdx.y, b = blockIdx.z,
+            tid = threadIdx.x;
   const float* part = a.part + (((size_t)b * a.nh + h) * nqt + qt) * a.nsplit * kPartFloats;
   const int qx = tid & (kQT - 1), qi = qt * kQT + qx;
-  if (tid < kQT) {
-    float M = -INFINITY;
-    for (int p = 0; p < a.nsplit; ++p) M = fmaxf(M, part[p * kPartFloats + kAD * kQT + qx]);
-    float den = 0.f;
-    for (int p = 0; p < a.nsplit; ++p) {   // fixed order
-      const float mp = part[p * kPartFloats + kAD * kQT + qx];
-      const float w = (mp == -INFINITY) ? 0.f : exp2f(mp - M);
-      sw[p][qx] = w;
-      den += w * part[p * kPartFloats + kAD * kQT + kQT + qx];
-    }
-    sden[qx] = den;
-  }
-  __syncthreads();
   if (qi >= a.T) return;
-  const bool live = qi <= a.n_sel[b];     // tree indices past n_sel are padding: zero rows
-  const float den = sden[qx];
-  float* orow = a.out + (((size_t)b * a.T + qi) * a.nh + h) * kAD;
-  float num[8];
+  const float* pm = part + kAD * kQT + qx;                         // reference of partial p at pm[p * kPartFloats], its sum kQT on
+  const float* po = part + (size_t)(dq0 + (tid >> 6)) * kQT + qx;
+  constexpr int kRows = kMergeD / 4;
+  float M = -INFINITY, den = 0.f, num[kRows];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) num[i] = 0.f;
-  for (int p = 0; p < a.nsplit; ++p) {     // fixed order; the eight elements of a thread are independent loads
-    const float w = sw[p][qx];
-    const float* pp = part + (size_t)p * kPartFloats + (size_t)(dq0 + (tid >> 6)) * kQT + qx;
+  for (int i = 0; i < kRows; ++i) num[i] = 0.f;
+  for (int p0 = 0; p0 < a.nsplit; p0 += 8) {                       // fixed order
+    float m8[8], l8[8], o8[8][kRows];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) num[i] += w * pp[(size_t)4 * i * kQT];
+    for (int j = 0; j < 8; ++j) {
+      const size_t at = (size_t)min(p0 + j, a.nsplit - 1) * kPartFloats;
+      m8[j] = pm[at];
+      l8[j] = pm[at + kQT];
+#pragma unroll
+      for (int i = 0; i < kRows; ++i) o8[j][i] = po[at + (size_t)4 * i * kQT];
+      if (p0 + j >= a.nsplit) m8[j] = -INFINITY;
+    }
+    float M2 = M;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) M2 = fmaxf(M2, m8[j]);
+    const float w = (M == -INFINITY) ? 0.f : exp2f(M - M2);
+    M = M2;
+    den *= w;
+#pragma unroll
+    for (int i = 0; i < kRows; ++i) num[i] *= w;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const float wj = (m8[j] == -INFINITY) ? 0.f : exp2f(m8[j] - M);
+      den += wj * l8[j];
+#pragma unroll
+      for (int i = 0; i < kRows; ++i) num[i] += wj * o8[j][i];
+    }
   }
+  const bool live = qi <= a.n_sel[b];     // tree indices past n_sel are padding: zero rows
+  float* orow = a.out + (((size_t)b * a.T + qi) * a.nh + h) * kAD;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) orow[dq0 + (tid >> 6) + 4 * i] = live ? num[i] / den : 0.f;
+  for (int i = 0; i < kRows; ++i) orow[dq0 + (tid >> 6) + 4 * i] = live ? num[i] / den : 0.f;
 }
 
 // Prompt cache in fragment order: per (sequence, head, chunk of 32 keys) 8 KB of keys, [s][lane] x 8 bf16 =
@@ -364,20 +438,32 @@ hipError_t launch_kv_pack(const uint16_t* k, const uint16_t* v, uint16_t* kp, ui
   return hipGetLastError();
 }
 
-hipError_t prepare_tree_attention() {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&tree_attn_partial_kernel),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, 4 * kLdsPart * (int)sizeof(float));
-}
-
 size_t tree_attention_part_floats() { return (size_t)kPartFloats; }
 
-hipError_t launch_tree_attention(const TreeAttnArgs& a, hipStream_t stream) {
+// Waves per workgroup.  Few tiles (one to four users): eight, one workgroup per CU - a step is 256 keys, so a head needs half as many
+// splits and partials.  Otherwise four: three workgroups fit a CU, and every value is read by one wave instead of two.
+// 32 heads, L = 1999 / 1500 / 700 / 2048 with 1 / 4 / 9 / 64 users, eight against four: 22.8 / 34.9 / 41.9 / 441 us against
+// 24.9 / 35.8 / 32.3 / 426 (27.5 / 49.9 / 57.7 / 493 with a whole output tile per wave and merges through LDS).
+static int attn_waves(long long tiles, int n_cu) { return 2 * tiles <= n_cu ? 8 : 4; }
+static long long attn_tiles(int B, int n_heads, int T) { return (long long)B * n_heads * ((T + kQT - 1) / kQT); }
+
+// Splits of a head's keys over workgroups: one workgroup of eight waves or two of four per CU, a step each at least.
+int tree_attention_splits(int B, int n_heads, int T, int L, int n_cu) {
+  const long long tiles = attn_tiles(B, n_heads, T);
+  const int nw = attn_waves(tiles, n_cu), most = std::min(attn_steps(L, T, nw).all, 64);
+  return (int)std::min<long long>(std::max<long long>((nw == 8 ? 1 : 2) * n_cu / tiles, 1), most);
+}
+
+hipError_t launch_tree_attention(const TreeAttnArgs& a, int n_cu, hipStream_t stream) {
   const int nqt = (a.T + kQT - 1) / kQT;
-  hipLaunchKernelGGL(tree_attn_partial_kernel, dim3(a.nsplit * nqt, a.nh, a.B), dim3(256),
-                     4 * kLdsPart * sizeof(float), stream, a);
+  const dim3 grid(a.nsplit * nqt, a.nh, a.B);
+  if (attn_waves(attn_tiles(a.B, a.nh, a.T), n_cu) == 8)
+    hipLaunchKernelGGL(tree_attn_partial_kernel<8>, grid, dim3(64 * 8), 0, stream, a);
+  else
+    hipLaunchKernelGGL(tree_attn_partial_kernel<4>, grid, dim3(64 * 4), 0, stream, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.nsplit == 1) return e;
-  hipLaunchKernelGGL(tree_attn_merge_kernel, dim3(nqt * 4, a.nh, a.B), dim3(256), 0, stream, a);
+  hipLaunchKernelGGL(tree_attn_merge_kernel, dim3(nqt * (kAD / kMergeD), a.nh, a.B), dim3(256), 0, stream, a);
   return hipGetLastError();
 }
 

@@ -68,6 +68,20 @@ def test_tree_attention_random_shapes(gpu):
         _check_case(gpu, name, B, m, nh, L, n_sels, seed=500 + i)
 
 
+# More tiles of 64 queries than half of the CUs: workgroups of four waves, 128 keys a step - prompts around whole steps, one
+# split per head and several, one query tile and two, trees that end inside a chunk, users without a tree.
+@pytest.mark.parametrize("B,m,nh,L", [(5, 20, 32, L) for L in (0, 1, 95, 96, 127, 128, 129, 257)] +
+                         [(5, 127, 16, 160), (9, 40, 32, 200), (9, 63, 32, 33), (17, 64, 16, 130), (9, 5, 64, 384)])
+def test_tree_attention_many_tiles(gpu, B, m, nh, L):
+    _check_case(gpu, "many_tiles", B, m, nh, L, [(m * i) // (B - 1) for i in range(B)], seed=1000 + B + m + nh + L)
+
+
+# At most half as many tiles as CUs: eight waves, 256 keys a step, as many splits as steps.
+@pytest.mark.parametrize("L", [160, 192, 193, 223, 224, 255, 256, 257, 480, 511, 513, 769])
+def test_tree_attention_few_tiles(gpu, L):
+    _check_case(gpu, "few_tiles", 1, 60, 3, L, [60], seed=2000 + L)
+
+
 def _check_case(gpu, name, B, m, nh, L, n_sels, seed):
     torch, D, SD = gpu
     T, d = m + 1, 128
