@@ -334,10 +334,12 @@ hipError_t launch_sum_rows(const SumRowsArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// ---- RoPE + key/value store + tree attention: one workgroup of 16 waves per (row, head) ----------
-// Every phase is a few dependent memory round trips deep at most: keys are dealt one per thread,
-// values to 8 groups of 128 threads (one per element of the head).
-constexpr int kAttnThreads = 1024;
+// ---- RoPE + key/value store + tree attention: one workgroup of 8 waves per (row, head) ----------
+// A chain of memory round trips: the first 256 keys and values are in flight while the query is rotated and the ancestors are
+// looked up, sixteen threads read a key or value of 256 bytes together (one key per thread, 64 rows in a wave's
+// load, and 2-byte reads of the values took 15.3 us for ten rows, 32 heads, L = 256, now 9.4).
+constexpr int kAttnThreads = 512;
+constexpr int kAttnKeys = 8;     // keys of a thread in flight
 
 __device__ __forceinline__ float block_max_f32(float x, float* red, int tid) {
   x = wave_max_f32(x);
@@ -383,21 +385,55 @@ __device__ __forceinline__ void load_qkv_pair(const BodyAttnArgs& a, const SumsV
   v0 = row[2 * a.H], v1 = row[2 * a.H + 64];
 }
 
-__global__ __launch_bounds__(kAttnThreads) void body_attention_kernel(BodyAttnArgs a) {
+__device__ __forceinline__ float row16_sum_f32(float x) {   // over the 16 lanes of a DPP row, the same in all of them
+  x += dpp_move_f32<0xB1>(x);
+  x += dpp_move_f32<0x4E>(x);
+  x += dpp_move_f32<0x141>(x);
+  x += dpp_move_f32<0x140>(x);
+  return x;
+}
+__device__ __forceinline__ void unpack_bf16x8(const u32x4& u, float (&f)[8]) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    f[2 * e] = __uint_as_float(u[e] << 16);
+    f[2 * e + 1] = __uint_as_float(u[e] & 0xFFFF0000u);
+  }
+}
+
+constexpr int kAttnLdsFloats = 400 + (kAttnThreads / 64) * kHeadDim;   // in front of the scores
+
+// LDS is exchanged, loads from global memory stay in flight (__syncthreads() would wait for them).
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+__global__ __launch_bounds__(kAttnThreads, 4) void body_attention_kernel(BodyAttnArgs a) {
   extern __shared__ __align__(16) float sm[];
   const int nh = a.H / kHeadDim;
   const int r = blockIdx.x / nh, h = blockIdx.x % nh, tid = threadIdx.x;
-  if (a.row_active != nullptr && a.row_active[r] == 0) return;   // uniform
   const int b = (a.step == 0) ? r : r / a.k;
   const int n_vis = a.L + a.step + 1;
-  const SumsView sv = qkv_view(a, tid & 63);
   float* qs = sm;                  // [128] rotated query
   float* ks = sm + 128;            // [128] own key as stored (bf16 values)
   float* vs = sm + 256;            // [128] own value as stored
-  float* red = sm + 384;           // [16] block reductions
+  float* red = sm + 384;           // [8] block reductions
   float* part = sm + 400;          // [8][128] partial outputs
-  float* sc = sm + 400 + 8 * kHeadDim;                            // [n_vis] scores, then weights
+  float* sc = sm + kAttnLdsFloats;                                // [n_vis] scores, then weights
   int* anc = reinterpret_cast<int*>(sc + ((n_vis + 3) & ~3));    // [step] row of the ancestor in each earlier call
+
+  // thread (kg, sub): elements sub*8 .. +7 of keys kg, kg + kGroups, ...; the first 256 keys are requested before anything else
+  constexpr int kGroups = kAttnThreads / 16;
+  const int kg = tid >> 4, sub = tid & 15;
+  const size_t at0 = (size_t)b * a.L * a.H + h * kHeadDim + sub * 8;
+  u32x4 kb[kAttnKeys], vb[kAttnKeys];
+  auto load_block = [&](const uint16_t* base, int j0, u32x4 (&u)[kAttnKeys]) {
+#pragma unroll
+    for (int i = 0; i < kAttnKeys; ++i) {
+      const int j = j0 + kGroups * i + kg;
+      if (j < a.L) u[i] = *reinterpret_cast<const u32x4*>(base + at0 + (size_t)j * a.H);
+    }
+  };
+  load_block(a.Kp, 0, kb);
+  if (a.row_active != nullptr && a.row_active[r] == 0) return;   // uniform
+  const SumsView sv = qkv_view(a, tid & 63);
 
   if (tid < 64) {
     // pair (tid, tid + 64) of the head rotates by pos * base^(-2*tid/128)
@@ -431,66 +467,92 @@ __global__ __launch_bounds__(kAttnThreads) void body_attention_kernel(BodyAttnAr
   } else if (tid == 128 && h == 0 && a.step >= 1) {
     a.par_hist[a.step * a.hist_rows + r] = a.beam_parent_slot[r];
   }
-  __syncthreads();
+  __builtin_amdgcn_sched_barrier(0);
+  load_block(a.Vp, 0, vb);         // ... the values behind the query's registers
+  lds_barrier();                   // the loads stay in flight
 
-  // scores: one key per thread
+  // scores: sixteen threads per key
   const float scale = 0.08838834764831845f;   // 1 / sqrt(128)
-  float mx = -INFINITY;
-  for (int j = tid; j < n_vis; j += kAttnThreads) {
-    float dot = 0.f;
-    if (j == n_vis - 1) {
-      for (int i = 0; i < kHeadDim; ++i) dot += qs[i] * ks[i];
-    } else {
-      const uint16_t* kp = (j < a.L) ? a.Kp + ((size_t)(b * a.L + j) * a.H + h * kHeadDim)
-                                     : a.k_hist + (((size_t)(j - a.L) * a.hist_rows + anc[j - a.L]) * a.H + h * kHeadDim);
-      u32x4 u[kHeadDim / 8];
+  float q8[8];
 #pragma unroll
-      for (int c = 0; c < kHeadDim / 8; ++c) u[c] = *reinterpret_cast<const u32x4*>(kp + c * 8);
+  for (int e = 0; e < 8; ++e) q8[e] = qs[sub * 8 + e];
+  // ancestor kg (or, as the last, the row itself): at most DDD_DMAX + 1 of them, one per group of sixteen threads
+  static_assert(DDD_DMAX + 1 <= kGroups, "one pass over the ancestors");
+  float ke[8], ve[8];
 #pragma unroll
-      for (int c = 0; c < kHeadDim / 8; ++c)
+  for (int e = 0; e < 8; ++e) ke[e] = ve[e] = 0.f;
+  if (kg < a.step) {
+    const size_t at = ((size_t)kg * a.hist_rows + anc[kg]) * a.H + h * kHeadDim + sub * 8;
+    unpack_bf16x8(*reinterpret_cast<const u32x4*>(a.k_hist + at), ke);
+    unpack_bf16x8(*reinterpret_cast<const u32x4*>(a.v_hist + at), ve);
+  } else if (kg == a.step) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          dot += qs[c * 8 + 2 * e] * __uint_as_float(u[c][e] << 16);
-          dot += qs[c * 8 + 2 * e + 1] * __uint_as_float(u[c][e] & 0xFFFF0000u);
-        }
-    }
-    dot *= scale;
-    sc[j] = dot;
-    mx = fmaxf(mx, dot);
+    for (int e = 0; e < 8; ++e) ke[e] = ks[sub * 8 + e], ve[e] = vs[sub * 8 + e];
   }
-  mx = block_max_f32(mx, red, tid);
+  float mx = -INFINITY;
+  auto score = [&](const float (&f)[8], int j, bool on) {
+    float dot = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) dot += q8[e] * f[e];
+    dot = row16_sum_f32(dot) * scale;
+    if (on) {
+      if (sub == 0) sc[j] = dot;
+      mx = fmaxf(mx, dot);
+    }
+  };
+  for (int j0 = 0; j0 < a.L; j0 += kGroups * kAttnKeys) {
+    if (j0 > 0) load_block(a.Kp, j0, kb);
+#pragma unroll
+    for (int i = 0; i < kAttnKeys; ++i) {
+      const int j = j0 + kGroups * i + kg;
+      float f[8];
+      unpack_bf16x8(kb[i], f);
+      score(f, j, j < a.L);
+    }
+  }
+  score(ke, a.L + kg, kg <= a.step);
+  mx = block_max_f32(mx, red, tid);            // its barriers also publish the scores
   float sum = 0.f;
   for (int j = tid; j < n_vis; j += kAttnThreads) {
     const float p = __expf(sc[j] - mx);
     sc[j] = p;
     sum += p;
   }
-  sum = block_sum_f32(sum, red, tid);   // its barriers also publish the weights
+  sum = block_sum_f32(sum, red, tid);          // ... and these the weights
 
-  // values: element d of the head, keys grp, grp + 8, ...
-  const int d = tid & (kHeadDim - 1), grp = tid >> 7;
-  float o = 0.f;
-  {
-    const uint16_t* vbase = a.Vp + ((size_t)b * a.L * a.H + h * kHeadDim + d);
-    int j = grp;
-    for (; j + 8 * 15 < a.L; j += 8 * 16) {   // sixteen keys of this group in flight
-      float v[16];
+  // values: the thread's eight elements over its keys, then over the groups
+  float o[8];
+  const float pe = kg <= a.step ? sc[a.L + kg] : 0.f;
 #pragma unroll
-      for (int i = 0; i < 16; ++i) v[i] = bf16_to_f32(vbase[(size_t)(j + 8 * i) * a.H]);
+  for (int e = 0; e < 8; ++e) o[e] = pe * ve[e];
+  for (int j0 = 0; j0 < a.L; j0 += kGroups * kAttnKeys) {
+    if (j0 > 0) load_block(a.Vp, j0, vb);
 #pragma unroll
-      for (int i = 0; i < 16; ++i) o += sc[j + 8 * i] * v[i];
+    for (int i = 0; i < kAttnKeys; ++i) {
+      const int j = j0 + kGroups * i + kg;
+      if (j < a.L) {
+        float f[8];
+        unpack_bf16x8(vb[i], f);
+        const float p = sc[j];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] += p * f[e];
+      }
     }
-    for (; j < a.L; j += 8) o += sc[j] * bf16_to_f32(vbase[(size_t)j * a.H]);
-    for (int c = grp; c < a.step; c += 8)
-      o += sc[a.L + c] * bf16_to_f32(a.v_hist[((size_t)c * a.hist_rows + anc[c]) * a.H + h * kHeadDim + d]);
-    if (grp == 0) o += sc[n_vis - 1] * vs[d];
   }
-  part[grp * kHeadDim + d] = o;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    o[e] += __shfl_xor(o[e], 16, 64);
+    o[e] += __shfl_xor(o[e], 32, 64);
+  }
+  if ((tid & 63) < 16) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) part[(tid >> 6) * kHeadDim + sub * 8 + e] = o[e];
+  }
   __syncthreads();
   if (tid < kHeadDim) {
     float t = 0.f;
 #pragma unroll
-    for (int g = 0; g < 8; ++g) t += part[g * kHeadDim + tid];   // fixed order
+    for (int g = 0; g < kAttnThreads / 64; ++g) t += part[g * kHeadDim + tid];   // fixed order
     a.o[(size_t)r * a.H + h * kHeadDim + tid] = f32_to_bf16_rne(t / sum);
   }
 }

@@ -151,6 +151,49 @@ def test_body_steps_with_scripted_beams(gpu, B, k):
         D.ddd_body_destroy(body)
 
 
+def _rows_within(got_bits, want_bits):
+    """The derived bound of _rows_close alone: how many elements round alike depends on the shape (with one prompt key a row's
+    attention is one value, and a tie in it moves the whole head)."""
+    g = synth.bf16_bits_to_f32(got_bits).astype(np.float64)
+    w = synth.bf16_bits_to_f32(want_bits).astype(np.float64)
+    rms = np.sqrt(np.mean(w * w, axis=1, keepdims=True))
+    err = np.abs(g - w) - (ROW_ATOL_RMS * rms + ROW_RTOL * np.abs(w))
+    assert np.all(err <= 0.0), float(err.max())
+
+
+# Prompts around the attention's blocks (32 groups of keys, 256 keys in flight), none, and several blocks; one and two users;
+# H = 384: K ranges of three units, F = 1408: a K that ends inside the last range.
+@pytest.mark.parametrize("B,L", [(1, 0), (1, 1), (2, 31), (1, 32), (1, 33), (2, 255), (1, 256), (1, 257), (2, 289), (1, 600)])
+def test_body_few_rows_prompt_lengths(gpu, B, L):
+    torch, D, SD = gpu
+    H, F, V, k, Dm = 384, 1408, 60, 4, 4
+    print(f"[case] body few rows B={B} k={k} H={H} F={F} L={L}", flush=True)
+    dev_w, dev_p, ow, op = _body_inputs(torch, SD, V, H, F, L, B)
+    st, st_t = D.alloc_state(D.make_config(B, H, V, k, Dm, 8, 0.3))
+    rng = np.random.default_rng(500 + 10 * L + B)
+    body = D.ddd_body_create(D.ddd_body_config(B, k, H, F, V, Dm, L))
+    obodies = [OB.StandInBody(ow, op[b], root_token=3) for b in range(B)]
+    try:
+        D.ddd_body_bind(body, dev_w, dev_p)
+        hid = torch.zeros(B * k, H, dtype=torch.bfloat16, device="cuda")
+        for s in range(Dm):
+            beams = [(rng.integers(0, V, k).tolist(), [0] * k if s == 1 else rng.integers(0, k, k).tolist()) for b in range(B)]
+            if s >= 1:
+                for name, i in (("beam_token", 0), ("beam_parent_slot", 1)):
+                    st_t[name].copy_(torch.tensor([t for bm in beams for t in bm[i]], dtype=torch.int32).view_as(st_t[name]))
+                st_t["row_active"].fill_(1)
+            D.ddd_body_step(body, s, st, hid)
+            torch.cuda.synchronize()
+            got = _bits(hid)
+            for b in range(B):
+                if s == 0:
+                    _rows_within(got[b:b + 1], obodies[b](0, None, None))
+                else:
+                    _rows_within(got[b * k:(b + 1) * k], obodies[b](s, _Beam(*beams[b]), None))
+    finally:
+        D.ddd_body_destroy(body)
+
+
 @pytest.mark.parametrize("shape", [("tiny", 1, 4, 256, 384, 500, 9, 5), ("k10_h1024", 1, 10, 1024, 2816, 3000, 33, 6),
                                    # the shape the benchmark's --body layer times: 7B sizes, 32 heads, 256 prompt positions
                                    ("7b_full_shape", 1, 10, 4096, 11008, 32000, 256, 3),
