@@ -10,8 +10,8 @@
 // wave makes the scores of one chunk, the waves agree on each query's softmax reference through LDS and leave the weights
 // there, and then every wave sums its own tile of the output (32 elements of the head for 64 or 32 queries) over all the
 // chunks.  No wave's output is merged with another's and a wave holds 16 or 32 accumulators instead of 128: three workgroups
-// of four share a CU, so loads fly under other waves' products (64 users, L = 2048: 493 -> 426 us, 5.4 TB/s), and the code of a
-// pass is short where it runs once (one user, L = 1999: 27.5 -> 22.8 us).
+// of four share a CU, so loads fly under other waves' products (64 users, L = 2048: 495 -> 428 us, 5.4 TB/s), and the code of a
+// pass is short where it runs once (one user, L = 1999: 27.3 -> 23.8 us).
 // Both products run on v_mfma_f32_32x32x16_bf16 in transposed form, which puts one
 // query in one lane, so the softmax rescaling is a per-lane scalar:
 //   S^T[key][query]  = K[key][d]   Q^T[d][query]     (A = 32 keys x 16 d from the key cache as stored)
@@ -41,7 +41,7 @@ constexpr int kOutPitch = kAD + 4;                 // O[query][d] in LDS at the 
 template <int NW>
 struct AttnCfg {
   static constexpr int NQ = 8 / NW;                          // blocks of 32 queries of a wave's output
-  static constexpr int kLdsQ = 16 * 64, kLdsP = NW * 4 * 64;   // 16-byte pieces: the queries, the weights of a step
+  static constexpr int kLdsQ = 16 * 64, kLdsP = NW * 8 * 64;   // 16-byte pieces: the queries, the weights of a step (two halves)
   static constexpr int kTile = (kLdsQ + kLdsP) * 16 > kQT * kOutPitch * 4 ? (kLdsQ + kLdsP) * 16 : kQT * kOutPitch * 4;
   static constexpr int kLdsBytes = kTile + NW * kQT * 4;     // ... and the chunks' maxima (in the end: sums) per query
 };
@@ -194,24 +194,30 @@ __device__ __forceinline__ void attend_step(Operands<NW>& x, const u32x4* qlds, 
     // weights 2^(s - m) may grow to 2^kLazy (harmless in fp32 and in bf16), and outputs need no rescaling.
     const float m_new = (cmax > st.m[qb] + kLazy || st.m[qb] == -INFINITY) ? cmax : st.m[qb];
     alpha[qb] = (m_new == st.m[qb]) ? 1.f : exp2f(st.m[qb] - m_new);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) sv[qb][e] = __builtin_amdgcn_exp2f(sv[qb][e] - m_new);   // exp2(-inf) = 0 for hidden keys; m_new
+    if (m_new == -INFINITY) {                                  // is finite whenever a key of the query has been seen
+#pragma unroll
+      for (int e = 0; e < 16; ++e) sv[qb][e] = 0.f;            // nothing visible yet: all weights are zero, not NaN
+    }
+    // the weights go in as two bf16 halves, hi + lo to 2^-17 relative: rounded to one, relative to a reference that a step's
+    // chunks share, they were up to a sixth further from 64 bits than relative to every chunk's own (1.35e-3 against 1.15e-3)
     float psum = 0.f;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      sv[qb][e] = __builtin_amdgcn_exp2f(sv[qb][e] - m_new);   // exp2(-inf) = 0 for hidden keys; m_new is finite
-      psum += sv[qb][e];                                       // whenever a key of the query has been seen
-    }
-    if (m_new == -INFINITY) {                                  // nothing visible yet: all weights are zero, not NaN
+    for (int t = 0; t < 2; ++t) {
+      u32x4 hi, lo;
 #pragma unroll
-      for (int e = 0; e < 16; ++e) sv[qb][e] = 0.f;
-      psum = 0.f;
+      for (int i = 0; i < 4; ++i) {
+        const float p0 = sv[qb][8 * t + 2 * i], p1 = sv[qb][8 * t + 2 * i + 1];
+        psum += p0 + p1;
+        hi[i] = pack_bf16x2(p0, p1);
+        lo[i] = pack_bf16x2(p0 - __uint_as_float(hi[i] << 16), p1 - __uint_as_float(hi[i] & 0xFFFF0000u));
+      }
+      plds[((wave * 2 + qb) * 4 + t) * 64 + lane] = hi;
+      plds[((wave * 2 + qb) * 4 + 2 + t) * 64 + lane] = lo;
     }
     st.l[qb] = st.l[qb] * alpha[qb] + psum;
     st.m[qb] = m_new;
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-      plds[((wave * 2 + qb) * 2 + t) * 64 + lane] =
-          u32x4{pack_bf16x2(sv[qb][8 * t], sv[qb][8 * t + 1]), pack_bf16x2(sv[qb][8 * t + 2], sv[qb][8 * t + 3]),
-                pack_bf16x2(sv[qb][8 * t + 4], sv[qb][8 * t + 5]), pack_bf16x2(sv[qb][8 * t + 6], sv[qb][8 * t + 7])};
   }
   constexpr int NQ = AttnCfg<NW>::NQ;
 #pragma unroll
@@ -230,8 +236,10 @@ __device__ __forceinline__ void attend_step(Operands<NW>& x, const u32x4* qlds, 
 #pragma unroll
       for (int i = 0; i < NQ; ++i) {
         const int qb = NQ == 2 ? i : (wave & 1);
-        st.o[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-            x.vf[ch][t], __builtin_bit_cast(bf16x8, plds[((ch * 2 + qb) * 2 + t) * 64 + lane]), st.o[i], 0, 0, 0);
+#pragma unroll
+        for (int half = 0; half < 2; ++half)
+          st.o[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+              x.vf[ch][t], __builtin_bit_cast(bf16x8, plds[((ch * 2 + qb) * 4 + half * 2 + t) * 64 + lane]), st.o[i], 0, 0, 0);
       }
       if (NEXT) x.vf[ch][t] = __builtin_bit_cast(bf16x8, vn[ch * 512 + t * 64 + lane]);
     }
@@ -242,7 +250,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void tree_attn_partial_ke
   using C = AttnCfg<NW>;
   __shared__ __align__(16) unsigned char lds[C::kLdsBytes];
   u32x4* qlds = reinterpret_cast<u32x4*>(lds);         // [qb * 8 + s][lane] queries as B operands
-  u32x4* plds = qlds + C::kLdsQ;                          // [chunk][qb][t][lane] weights as B operands
+  u32x4* plds = qlds + C::kLdsQ;                          // [chunk][qb][half][t][lane] weights as B operands
   float* cmax_lds = reinterpret_cast<float*>(lds + C::kTile);   // [chunk][query]
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, lh = lane >> 5;
   const int db = wave / (NW / 4);
@@ -443,7 +451,8 @@ size_t tree_attention_part_floats() { return (size_t)kPartFloats; }
 // Waves per workgroup.  Few tiles (one to four users): eight, one workgroup per CU - a step is 256 keys, so a head needs half as many
 // splits and partials.  Otherwise four: three workgroups fit a CU, and every value is read by one wave instead of two.
 // 32 heads, L = 1999 / 1500 / 700 / 2048 with 1 / 4 / 9 / 64 users, eight against four: 22.8 / 34.9 / 41.9 / 441 us against
-// 24.9 / 35.8 / 32.3 / 426 (27.5 / 49.9 / 57.7 / 493 with a whole output tile per wave and merges through LDS).
+// 24.9 / 35.8 / 32.3 / 426 (27.5 / 49.9 / 57.7 / 493 with a whole output tile per wave and merges through LDS); all without the
+// weights' low halves, which cost one user 1.6 us and 64 users nothing.
 static int attn_waves(long long tiles, int n_cu) { return 2 * tiles <= n_cu ? 8 : 4; }
 static long long attn_tiles(int B, int n_heads, int T) { return (long long)B * n_heads * ((T + kQT - 1) / kQT); }
 
