@@ -220,14 +220,16 @@ __device__ __forceinline__ void tree_finalize_wide_block(const ddd_state& st, co
     for (int i = tid; i < kWCand; i += nthr) rank[i] = 0;
     if (tid == 0) sm.cnt = 0;
     __syncthreads();
-    const float bound = unord32(block_kth_largest_u32(first, n_first, m_eff, cnt, sm.red, tid));
+    // Compared as ordered bits, a total order: at least the m_eff scores of the sample that made the bound pass it, whatever
+    // they are (a NaN, from a row whose largest logit is infinite, would fail every comparison of floats).
+    const uint32_t bound = block_kth_largest_u32(first, n_first, m_eff, cnt, sm.red, tid);
     for (int i0 = tid; i0 < N; i0 += 16 * kWideThreads) {
       float x[16];
 #pragma unroll
       for (int u = 0; u < 16; ++u) x[u] = (i0 + u * kWideThreads < N) ? psc[i0 + u * kWideThreads + 1] : -INFINITY;
 #pragma unroll
       for (int u = 0; u < 16; ++u)
-        if (x[u] >= bound && i0 + u * kWideThreads < N) {
+        if (i0 + u * kWideThreads < N && ord32(x[u]) >= bound) {
           const int p = atomicAdd(&sm.cnt, 1);
           if (p < kWCand) cand[p] = rerank_key(x[u], i0 + u * kWideThreads + 1);
         }

@@ -100,3 +100,109 @@ def test_draft_step_equals_its_parts(gpu, B, k, kind):
                 assert np.array_equal(got["logprobsum"][q], sc[order])
     finally:
         D.ddd_destroy(ctx)
+
+
+def _ordered(scores):
+    """fp32 scores as unsigned integers in the total order of the rerank and beam keys (both zeros alike, a positive NaN above
+    +inf)."""
+    u = (np.ascontiguousarray(scores, dtype=np.float32) + np.float32(0.0)).view(np.uint32)
+    return np.where(u >> 31, ~u, u | np.uint32(0x80000000)).astype(np.int64)
+
+
+def _check_tree(tree, pool, n, m, b):
+    """The final tree of sequence b against a sort of its pool's nodes 1 .. n - 1 by (score desc, node id asc)."""
+    key = _ordered(pool["pool_score"][b, 1:n])
+    best = np.sort(np.lexsort((np.arange(n - 1), -key))[:m] + 1)
+    assert tree["n_sel"][b] == len(best)
+    assert np.array_equal(tree["sel_node"][b][: len(best)], best)
+    for got, want in (("tree_token", "pool_token"), ("pos", "pool_depth")):
+        assert np.array_equal(tree[got][b][1 : len(best) + 1], pool[want][b][best])
+    parent = pool["pool_parent"][b][best]
+    at = np.searchsorted(best, parent)
+    known = (at < len(best)) & (best[np.minimum(at, len(best) - 1)] == parent)
+    assert np.array_equal(tree["parent_idx"][b][1 : len(best) + 1], np.where(parent == 0, 0, np.where(known, at + 1, -1)))
+
+
+@pytest.mark.parametrize("special", ["none", "nan_first", "nan_all_of_the_first", "nan_negative", "nan_later", "inf", "minus_inf", "zeros"])
+@pytest.mark.parametrize("k,calls,m", [(100, 4, 60), (17, 31, 127), (128, 2, 128)])
+def test_final_tree_of_any_scores(gpu, k, calls, m, special):
+    """ddd_tree_finalize over pools of several thousand nodes whose scores are not all finite: a NaN (a row whose largest logit
+    is infinite has no finite logprob) has its place in the order like any other score."""
+    torch, D = gpu
+    print(f"[case] wide_tree k={k} calls={calls} m={m} {special}", flush=True)
+    B, rng = 2, np.random.default_rng(k + calls)
+    n = 1 + k + (calls - 1) * k * k
+    depth = np.concatenate([[0], np.ones(k), np.repeat(np.arange(2, calls + 1), k * k)]).astype(np.int32)
+    parent = np.concatenate([[-1], np.zeros(k), 1 + np.repeat(np.arange(n - 1 - k) // k, 1) % k]).astype(np.int32)
+    score = (-rng.gamma(2.0, 1.0, (B, n)) - depth).astype(np.float32)
+    at = {"nan_first": slice(3, 90), "nan_all_of_the_first": slice(1, 257), "nan_negative": slice(1, 257),
+          "nan_later": slice(n - 300, n), "inf": slice(40, 50), "minus_inf": slice(10, n), "zeros": slice(5, 250)}
+    if special != "none":
+        value = {"inf": np.inf, "minus_inf": -np.inf, "zeros": 0.0}.get(special, np.nan)
+        bits = np.float32(value).view(np.uint32) | np.uint32(0x80000000 if special == "nan_negative" else 0)
+        score.view(np.uint32)[:, at[special]] = bits
+        if special == "zeros":
+            score[:, 5:250:2] = -0.0
+    cfg = D.make_config(B, 128, 4000, k, calls, m, 0.0, 0)
+    ctx = D.ddd_create(cfg)
+    try:
+        st, t = D.alloc_state(cfg)
+        tree, tt = D.alloc_tree(cfg)
+        tok = rng.integers(0, 4000, (B, n)).astype(np.int32)
+        for name, v in (("pool_score", score), ("pool_token", tok), ("pool_parent", np.tile(parent, (B, 1))),
+                        ("pool_depth", np.tile(depth, (B, 1)))):
+            t[name][:, :n].copy_(torch.from_numpy(v))
+        t["n_nodes"].fill_(n)
+        D.ddd_tree_finalize(ctx, st, tree)
+        torch.cuda.synchronize()
+        got, pool = {x: v.cpu().numpy() for x, v in tt.items()}, {x: v.cpu().numpy() for x, v in t.items()}
+    finally:
+        D.ddd_destroy(ctx)
+    for b in range(B):
+        _check_tree(got, pool, n, m, b)
+
+
+@pytest.mark.parametrize("B,k", [(1, 17), (2, 100), (1, 128)])
+def test_wide_round_with_an_infinite_logit(gpu, B, k):
+    """One hidden row of the second call meets a row of W whose product exceeds fp32 (+inf logit): its logprobs are NaN, and the
+    beam, the later calls and the final tree follow the order of the keys like with any other scores."""
+    torch, D = gpu
+    print(f"[case] wide_infinite_logit B={B} k={k}", flush=True)
+    H, V, calls, m = 128, 3000, 4, 40
+    rng = np.random.default_rng(k)
+    W = _bits(torch, synth.make_lm_head(V, H, 0.2, 1))
+    W[:, 0] = 0.0
+    W[5, 0] = 3e38
+    cfg = D.make_config(B, H, V, k, calls, m, 0.0, 0)
+    ctx = D.ddd_create(cfg)
+    try:
+        st, t = D.alloc_state(cfg)
+        tree, tt = D.alloc_tree(cfg)
+        D.ddd_round_reset(ctx, st)
+        for s in range(calls):
+            R = B if s == 0 else B * k
+            hid = torch.from_numpy(rng.standard_normal((R, H)).astype(np.float32) * 2).cuda().to(torch.bfloat16)
+            hid[:, 0] = 0.0
+            if s == 1:
+                hid[3, 0] = 100.0
+            lps = t["logprobsum"].cpu().numpy().copy()
+            D.ddd_draft_step(ctx, s, W, hid, st, tree)
+            torch.cuda.synchronize()
+            if s == 0:
+                continue
+            got = {n: v.cpu().numpy() for n, v in t.items()}
+            base, kk = 1 + k + (s - 1) * k * k, k * k
+            for b in range(B):
+                sc, tok = got["pool_score"][b, base:base + kk], got["pool_token"][b, base:base + kk]
+                assert tok.min() >= 0 and tok.max() < V
+                bad = np.isnan(sc.reshape(k, k)).all(axis=1)
+                assert np.array_equal(bad, np.isnan(lps[b]) | ((s == 1) & (b == 0) & (np.arange(k) == 3)))
+                order = np.lexsort((np.arange(kk), tok, -_ordered(sc)))[:k]
+                assert np.array_equal(got["beam_node"][b], base + order)
+                assert np.array_equal(got["beam_parent_slot"][b], order // k)
+                assert np.array_equal(got["beam_token"][b], tok[order])
+        tree_np = {n: v.cpu().numpy() for n, v in tt.items()}
+        for b in range(B):
+            _check_tree(tree_np, got, 1 + k + (calls - 1) * k * k, m, b)
+    finally:
+        D.ddd_destroy(ctx)
