@@ -401,6 +401,7 @@ __global__ __launch_bounds__(kWideRowThreads) void row_topk_wide_kernel(RowTopkA
     __syncthreads();
     for (int i = tid; i < cnt; i += kWideRowThreads)
       if (s_rank[i] < a.k) emit(s_rank[i], s_cand[i]);
+    for (int j = cnt + tid; j < a.k; j += kWideRowThreads) emit(j, 0ull);   // fewer candidates than beams: no number in the row
     return;
   }
   // ---- more than kCandMax elements tie at or above T (e.g. constant logits): exact but slow ---------------------------

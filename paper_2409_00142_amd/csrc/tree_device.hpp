@@ -141,9 +141,10 @@ __device__ __forceinline__ void bitonic_sort_desc(uint64_t* keys, int n2, int ti
   if (n2 < 128) __syncthreads();
 }
 
-// rank[i] = number of keys[0..n) larger than keys[i] (keys distinct, rank zeroed beforehand), by every thread of the block: with fewer keys than threads the comparisons of a key are shared
-// by nthr / n threads.  No barrier inside.
+// rank[i] = number of keys[0..n) larger than keys[i] (keys distinct, rank zeroed beforehand), by every thread of the block:
+// with fewer keys than threads the comparisons of a key are shared by nthr / n threads.  No barrier inside.
 __device__ __forceinline__ void count_larger_keys(const uint64_t* keys, int n, int* rank, int tid, int nthr) {
+  if (n <= 0) return;                                            // uniform: nothing to rank (and nothing to divide by)
   if (n <= nthr) {                                               // uniform
     const int P = nthr / n, part = tid / n, i = tid - part * n;
     if (part < P) {

@@ -206,3 +206,39 @@ def test_wide_round_with_an_infinite_logit(gpu, B, k):
             _check_tree(tree_np, got, 1 + k + (calls - 1) * k * k, m, b)
     finally:
         D.ddd_destroy(ctx)
+
+
+@pytest.mark.parametrize("k,V", [(17, 128), (100, 3000), (128, 70001)])
+def test_row_without_candidates(gpu, k, V):
+    """A hidden row that holds no number has no logit above any bound: all k of its results are "no token" (-1), not what an
+    earlier call left, and a draft call with such a row stays inside its beam and pool."""
+    torch, D = gpu
+    print(f"[case] wide_no_candidates k={k} V={V}", flush=True)
+    H, bad = 128, 2
+    rng = np.random.default_rng(k)
+    W = _bits(torch, synth.make_lm_head(V, H, 0.2, 1))
+    cfg = D.make_config(1, H, V, k, 4, 20, 0.0, 0)
+    ctx = D.ddd_create(cfg)
+    try:
+        st, t = D.alloc_state(cfg)
+        D.ddd_round_reset(ctx, st)
+        for s in range(3):                                       # numbers in the first two calls: the scratch holds their keys
+            hid = torch.from_numpy(rng.standard_normal((1 if s == 0 else k, H)).astype(np.float32)).cuda().to(torch.bfloat16)
+            if s == 2:
+                hid[bad] = float("nan")
+            D.ddd_draft_step(ctx, s, W, hid, st)
+        tok = torch.full((k, k), -7, dtype=torch.int32, device="cuda")
+        lp, lse = torch.zeros(k, k, device="cuda"), torch.zeros(k, device="cuda")
+        D.ddd_lmhead_topk(ctx, W, hid, k, None, tok, lp, lse)
+        torch.cuda.synchronize()
+        got, tok = {n: v.cpu().numpy()[0] for n, v in t.items() if n != "row_active"}, tok.cpu().numpy()
+    finally:
+        D.ddd_destroy(ctx)
+    assert np.all(tok[bad] == -1)
+    rest = np.delete(tok, bad, axis=0)
+    assert rest.min() >= 0 and rest.max() < V
+    base, kk = 1 + k + k * k, k * k
+    assert np.array_equal(got["pool_token"][base:base + kk].reshape(k, k), tok)
+    assert np.all(got["pool_depth"][base:base + kk] == 3)
+    assert len(set(got["beam_node"])) == k and got["beam_node"].min() >= base and got["beam_node"].max() < base + kk
+    assert np.array_equal(got["beam_parent_slot"], (got["beam_node"] - base) // k)
