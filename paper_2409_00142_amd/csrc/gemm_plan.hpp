@@ -11,19 +11,20 @@ struct GemmPlan {
   int S;     // K ranges
 };
 
-// What a product costs with NT column tiles and S ranges of K, in steps of 0.14 us (fitted to the LM head's launches of
-// 32 to 640 rows): a k tile of a unit costs ab * bb / 2 + 2.5 (its MFMAs, and the copies they do not cover), the unit's
-// ramp and stores 25 + 6 ab bb, and every partial sum is read once more by whoever adds them up (4 bytes at 5 TB/s).
-// Returns 0 where the combination does not exist.
-__host__ __device__ inline float plan_price(const SplitShape& g, int n_act, int NT, int S) {
+// What a product costs with NT column tiles and S ranges of K, in ns (fitted to the LM head's launches of
+// 32 to 640 rows): a k tile of a unit costs 140 ns times ab * bb / 2 + 2.5 (its MFMAs, and the copies they do not cover), the
+// unit's ramp and stores 140 ns times 25 + 6 ab bb, and every partial sum is read once more by whoever adds them up (4 bytes at
+// 5 TB/s).  Returns 0 where the combination does not exist.  Integers: the GEMM and every reader of its sums must come to the same
+// number of ranges, whatever the compiler fuses in each of them.
+__host__ __device__ inline uint32_t plan_price(const SplitShape& g, int n_act, int NT, int S) {
   const int nblk = (n_act + 31) >> 5, nmt = (g.N + 64 * g.ab - 1) / (64 * g.ab);
   const int bpt = (nblk + NT - 1) / NT, bb = (bpt + 1) >> 1;
   const long long sums = (long long)S * n_act * g.N;
-  if (NT > nblk || (NT - 1) * bpt >= nblk || S > g.smax || (S > 1 && (g.kt < 4 * S || sums > g.cap))) return 0.f;
-  const int waves = (nmt * NT * S + g.grid - 1) / g.grid;
-  const float area = (float)(g.ab * bb);
-  return (float)waves * ((0.5f * area + 2.5f) * (float)((g.kt + S - 1) / S) + 25.f + 6.f * area) +
-         (float)sums * (1.f / 171875.f);
+  if (NT > nblk || (NT - 1) * bpt >= nblk || S > g.smax || (S > 1 && (g.kt < 4 * S || sums > g.cap))) return 0u;
+  const uint32_t waves = (uint32_t)((nmt * NT * S + g.grid - 1) / g.grid), area = (uint32_t)(g.ab * bb);
+  const uint32_t ns = 70u * ((area + 5u) * (uint32_t)((g.kt + S - 1) / S) + 50u + 12u * area);   // of one unit
+  const uint64_t price = (uint64_t)waves * ns + (((uint64_t)sums * 3498460u) >> 32);              // sums / 1227.7
+  return price < 0xFFFFFFFFu ? (uint32_t)price : 0xFFFFFFFEu;
 }
 __host__ __device__ inline int plan_least_tiles(const SplitShape& g, int n_act) {
   const int nblk = (n_act + 31) >> 5;
@@ -38,8 +39,8 @@ __host__ __device__ inline int plan_least_tiles(const SplitShape& g, int n_act) 
 __device__ __forceinline__ GemmPlan gemm_plan(const SplitShape& g, int n_act, int lane) {
   const int nblk = (n_act + 31) >> 5;
   const int S = (lane >> 3) + 1, NT = plan_least_tiles(g, n_act) + (lane & 7), bpt = (nblk + NT - 1) / NT;
-  const float price = plan_price(g, n_act, NT, S);
-  const uint32_t key = price > 0.f ? ~__float_as_uint(price) : 0u;      // prices are positive: their bits order like them
+  const uint32_t price = plan_price(g, n_act, NT, S);
+  const uint32_t key = price != 0u ? ~price : 0u;
   const uint32_t best = wave_max_u32(key);
   const int l = __ffsll((unsigned long long)__ballot(key == best)) - 1;
   GemmPlan p;

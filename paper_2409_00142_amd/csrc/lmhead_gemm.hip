@@ -478,11 +478,11 @@ static void launch_shape(const GemmArgs& a, int grid, hipStream_t stream) {
 SplitShape linear_shape(int N, int K, int max_rows, int grid, int smax, long long cap) {
   auto shape = [&](int ab, int bbmax) { return SplitShape{ab, bbmax, K / kGK, N, grid, smax, cap}; };
   auto best = [&](const SplitShape& g) {
-    float least = 0.f;
+    uint32_t least = 0u;
     const int t0 = plan_least_tiles(g, max_rows);
     for (int i = 0; i < 64; ++i) {
-      const float p = plan_price(g, max_rows, t0 + (i & 7), (i >> 3) + 1);
-      if (p > 0.f && (least == 0.f || p < least)) least = p;
+      const uint32_t p = plan_price(g, max_rows, t0 + (i & 7), (i >> 3) + 1);
+      if (p != 0u && (least == 0u || p < least)) least = p;
     }
     return least;
   };
