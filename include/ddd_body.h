@@ -82,7 +82,8 @@ int ddd_body_step(void* user, int32_t step, const ddd_state* st, void* hid_out_b
 
 /* y[r,n] = sum_k x[r,k] W[n,k]: one linear of the layer on its own (K a multiple of 128, N >= 1; W bf16 [N,K],
  * x bf16 [R,K], y fp32 [R,N], all device): the weight stream for R <= 16 rows, the MFMA path for
- * 16 < R <= B*k rows (N a multiple of 4 there).  accumulate != 0 adds to y. */
+ * 16 < R <= B*k rows (N a multiple of 4 there).  accumulate != 0 adds to y.  Nothing is kept in the body: calls on
+ * several streams may overlap each other and the steps of a round. */
 int ddd_body_linear(ddd_body* body, const void* W, int32_t N, int32_t K, const void* x, int32_t R, float* y,
                     int32_t accumulate, void* stream);
 

@@ -316,16 +316,11 @@ __global__ __launch_bounds__(256) void sum_rows_kernel(SumRowsArgs a) {
   const int r = a.row_list != nullptr ? a.row_list[n] : n;
   const SumsView v = sums_view(a.sums, n_act, tid & 63);
   for (int i = tid * 4; i < v.N; i += 256 * 4) {                 // N is a multiple of 4
-    f32x4 y = sums_at4(v, n, i);
-    float* yp = a.y + (size_t)r * v.N + i;
-    if (a.add) y = *reinterpret_cast<const f32x4*>(yp) + y;
-    if (a.store) *reinterpret_cast<f32x4*>(yp) = y;
-    if (a.out16 != nullptr) {
-      const uint2 o = make_uint2(f32_to_bf16_rne(y[0]) | ((uint32_t)f32_to_bf16_rne(y[1]) << 16),
-                                 f32_to_bf16_rne(y[2]) | ((uint32_t)f32_to_bf16_rne(y[3]) << 16));
-      *reinterpret_cast<uint2*>(a.out16 + (size_t)r * v.N + i) = o;
-      if (a.out16b != nullptr) *reinterpret_cast<uint2*>(a.out16b + (size_t)r * v.N + i) = o;
-    }
+    const f32x4 y = *reinterpret_cast<const f32x4*>(a.y + (size_t)r * v.N + i) + sums_at4(v, n, i);
+    const uint2 o = make_uint2(f32_to_bf16_rne(y[0]) | ((uint32_t)f32_to_bf16_rne(y[1]) << 16),
+                               f32_to_bf16_rne(y[2]) | ((uint32_t)f32_to_bf16_rne(y[3]) << 16));
+    *reinterpret_cast<uint2*>(a.out16 + (size_t)r * v.N + i) = o;
+    *reinterpret_cast<uint2*>(a.out16b + (size_t)r * v.N + i) = o;
   }
 }
 

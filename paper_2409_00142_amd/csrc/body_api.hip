@@ -274,22 +274,10 @@ int ddd_body_linear(ddd_body* b, const void* W, int32_t N, int32_t K, const void
   if (R > kBodyRows) {   // the MFMA path of calls with more rows, all R rows taken as active
     if (R > b->rows || N % 4 != 0) return DDD_ERR_INVALID_ARG;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const uint16_t* xr = static_cast<const uint16_t*>(x);
-    if ((long long)R * N > b->part_cap)   // more sums than the layer's own products have: straight to y, K not split
-      return enqueue_gemm_linear(b, R, true, W, N, K, xr, y, accumulate ? kGemmAccumulate : kGemmStore, nullptr, 0, s);
-    int rc = enqueue_gemm_linear(b, R, true, W, N, K, xr, nullptr, kGemmPartial, nullptr, 0, s);
-    if (rc != DDD_OK) return rc;
-    SumRowsArgs f;
-    f.sums = split_sums(b, R, true, N, K);
-    f.row_list = nullptr;
-    f.y = y;
-    f.out16 = nullptr;
-    f.out16b = nullptr;
-    f.R = R;
-    f.add = accumulate ? 1 : 0;
-    f.store = 1;
-    BODY_HIP(launch_sum_rows(f, s));
-    return DDD_OK;
+    // straight to y, K not split: the body's room for partial sums belongs to the stream of its steps, and calls of this
+    // function on several streams may overlap
+    return enqueue_gemm_linear(b, R, true, W, N, K, static_cast<const uint16_t*>(x), y, accumulate ? kGemmAccumulate : kGemmStore,
+                               nullptr, 0, s);
   }
   LinearArgs a = linear_args(W, K, N, R, nullptr, y, N, accumulate ? kLinearAccumulate : kLinearStore);
   a.rg[0].x = static_cast<const uint16_t*>(x);
@@ -398,8 +386,6 @@ int ddd_body_step(void* user, int32_t step, const ddd_state* st, void* hid_out, 
     f.out16 = static_cast<uint16_t*>(hid_out);
     f.out16b = b->h_hist + hist;
     f.R = R;
-    f.add = 1;
-    f.store = 0;
     BODY_HIP(launch_sum_rows(f, s));
     return DDD_OK;
   }

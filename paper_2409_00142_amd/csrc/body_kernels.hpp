@@ -68,14 +68,14 @@ struct SumRmsNormArgs {
   int H, R, add;
 };
 hipError_t launch_sum_rmsnorm(const SumRmsNormArgs& a, hipStream_t stream);
-// y = sum of the partial sums (+ y with `add`): to y (fp32, if `store`), and rounded to out16 and out16b where not null.
+// bf16(y + sum of the partial sums), to out16 and out16b.
 struct SumRowsArgs {
   SplitSums sums;
   const int32_t* row_list;
-  float* y;                   // fp32 [rows][N]
-  uint16_t* out16;            // null, or bf16 [rows][N]
-  uint16_t* out16b;           // null, or a second copy
-  int R, add, store;
+  const float* y;             // fp32 [rows][N]
+  uint16_t* out16;            // bf16 [rows][N]
+  uint16_t* out16b;           // a second copy
+  int R;
 };
 hipError_t launch_sum_rows(const SumRowsArgs& a, hipStream_t stream);
 

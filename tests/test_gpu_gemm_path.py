@@ -56,9 +56,9 @@ def test_logits_pitch_of_any_vocabulary(gpu, V, equal):
 
 @pytest.mark.parametrize("N,K", [(4, 256), (128, 2048), (1156, 2048), (4096, 512), (516, 11008)])
 @pytest.mark.parametrize("R", [17, 32, 33, 64, 65, 321, 640])
-def test_split_linear(gpu, N, K, R):
-    """ddd_body_linear on the MFMA path where few row tiles of W make it split K (1 to 8 ranges, uneven where the k tiles
-    do not divide), one block of rows more or less than a tile: against the product in 64 bits, and twice the same bits.
+def test_linear_of_any_rows(gpu, N, K, R):
+    """ddd_body_linear on the MFMA path, one block of rows more or less than a tile: against the product in 64 bits, and twice
+    the same bits.
 
     Tolerance: products of bf16 numbers are exact in fp32, and K sums of terms of size K^-0.5 round with relative error
     2^-24 each: sqrt(K) * 2^-24 times a few, below 1e-5 for K <= 11008; 1e-4 leaves room for the largest of R * N."""
@@ -84,6 +84,32 @@ def test_split_linear(gpu, N, K, R):
     assert float((acc.double() - 2 * want).abs().max()) <= 2e-4
 
 
+def test_linears_on_two_streams(gpu):
+    """ddd_body_linear keeps nothing in the body: calls of one body on two streams may overlap.  Tolerance as above."""
+    torch, D = gpu
+    print("[case] linears_on_two_streams", flush=True)
+    N, K, R = 1024, 8192, 200
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    W = [torch.empty(N, K, dtype=torch.bfloat16, device="cuda").normal_(0, K ** -0.5, generator=g) for _ in range(2)]
+    x = [torch.empty(R, K, dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=g) for _ in range(2)]
+    y = [[torch.full((R, N), float("nan"), device="cuda") for _ in range(20)] for _ in range(2)]
+    body = D.ddd_body_create(D.ddd_body_config(50, 4, 256, 256, 10, 2, 0))
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+    try:
+        for i in range(20):
+            for q in range(2):
+                D.ddd_body_linear(body, W[q], N, K, x[q], R, y[q][i], stream=streams[q].cuda_stream)
+        torch.cuda.synchronize()
+    finally:
+        D.ddd_body_destroy(body)
+    for q in range(2):
+        want = x[q].double() @ W[q].double().T.contiguous()
+        for t in y[q]:
+            assert float((t.double() - want).abs().max()) <= 1e-4
+
+
 @pytest.mark.parametrize("L", [0, 5, 31, 32, 33, 64, 250, 257, 545])
 @pytest.mark.parametrize("k", [3, 10, 16])
 def test_batched_attention_of_any_prompt_length(gpu, L, k):
@@ -93,11 +119,26 @@ def test_batched_attention_of_any_prompt_length(gpu, L, k):
 
     Tolerance: both sides round at the same five points of a call, what lies between them is summed in another order,
     and a rounding that falls the other way moves a term by one bf16 ulp (2^-8): 2^-5 of the row's rms, as against the oracle."""
-    torch, D = gpu
     print(f"[case] batched_attention L={L} k={k}", flush=True)
-    B, H, F, V, calls = 7, 256, 384, 300, 4
+    _batch_against_single(gpu, 7, k, 256, 384, L, range(7), 1000 * k + L)
+
+
+# Row counts around the blocks of 32 rows and the column tiles; few rows of W for 256 workgroups, so that every product but
+# gate/up is split: K = 11008 (172 k tiles) into up to eight uneven ranges, K = 2048 and 1024 into up to eight and four.
+@pytest.mark.parametrize("B,k,H,F", [(6, 3, 256, 11008), (8, 4, 256, 2944), (11, 3, 1024, 1408), (13, 5, 256, 11008), (43, 3, 512, 1024),
+                                     (65, 5, 256, 11008), (64, 10, 1024, 2816)])
+def test_split_products_of_the_layer(gpu, B, k, H, F):
+    """Draft layer with more than 16 rows: partial sums of K ranges, added up by the norms, the attention and the last launch,
+    against the same sequences one at a time (at most 16 rows: whole sums in the weight streams).  Tolerance as above."""
+    print(f"[case] split_products B={B} k={k} H={H} F={F}", flush=True)
+    _batch_against_single(gpu, B, k, H, F, 33, sorted({0, 2, B // 2, B - 1}), B + F)
+
+
+def _batch_against_single(gpu, B, k, H, F, L, check, seed):
+    torch, D = gpu
+    V, calls = 300, 4
     g = torch.Generator(device="cuda")
-    g.manual_seed(1000 * k + L)
+    g.manual_seed(seed)
 
     def normal(*shape, std=1.0, dtype=torch.bfloat16):
         return torch.empty(shape, dtype=dtype, device="cuda").normal_(0, std, generator=g)
@@ -133,7 +174,7 @@ def test_batched_attention_of_any_prompt_length(gpu, L, k):
         return out
 
     got = layer(list(range(B)))
-    for b in range(B):
+    for b in check:
         want = layer([b])
         for s in range(calls):
             if b == 2 and s >= 2:
