@@ -63,9 +63,10 @@ def _bits(t):
 LINEAR_CASES = [
     # name, N, K, R
     ("one_range", 300, 256, 5),
-    ("two_ranges_1408", 1000, 1408, 16),          # 128*11 = 1280 + 128
-    ("k8192", 520, 8192, 10),                      # 5120 + 3072
-    ("k11008_ragged_N", 1037, 11008, 3),           # 5120 + 5120 + 768; N not a multiple of 16
+    ("one_short_range_1408", 1000, 1408, 16),          # eleven units of 128 in one range of twelve
+    ("two_ranges_8192", 520, 8192, 10),            # 2 x 4096
+    ("k11008_ragged_N", 1037, 11008, 3),           # three ranges, the last shorter; N not a multiple of 16
+    ("k16000_two_launches", 300, 16000, 7),        # 3 x 5120, and a second launch for the rest
     # more than 16 rows: the MFMA path (128 x 128 tiles when the product has few of them, wider ones otherwise)
     ("gemm_rows40", 512, 1024, 40),
     ("gemm_rows130_k8192", 520, 8192, 130),
@@ -105,11 +106,12 @@ class _Beam:
         self.token, self.parent_slot = np.asarray(token), np.asarray(parent_slot)
 
 
-@pytest.mark.parametrize("B,k", [(2, 3), (6, 3), (20, 2)], ids=lambda v: str(v))
+@pytest.mark.parametrize("B,k", [(2, 3), (6, 3), (20, 2), (3, 20)], ids=lambda v: str(v))
 def test_body_steps_with_scripted_beams(gpu, B, k):
     """Four calls with scripted beams (seeded tokens and parent slots); some sequences stop after call 1 or 2, and
     their rows must be left untouched from then on.  B*k <= 16: every linear is a weight stream; more rows: the
-    MFMA path (B = 6: from the second call on; B = 20: for the prompt call as well)."""
+    MFMA path (B = 6: from the second call on; B = 20: for the prompt call as well).  k = 20: more rows per sequence than the
+    batched attention takes, one workgroup per row and head adds the partial sums of its q, k and v up."""
     torch, D, SD = gpu
     H, F, V, L, Dm = 256, 384, 60, 7, 4
     print(f"[case] body scripted beams B={B} k={k} H={H} F={F} L={L}", flush=True)

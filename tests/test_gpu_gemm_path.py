@@ -110,12 +110,12 @@ def test_linears_on_two_streams(gpu):
             assert float((t.double() - want).abs().max()) <= 1e-4
 
 
-@pytest.mark.parametrize("L", [0, 5, 31, 32, 33, 64, 250, 257, 545])
+@pytest.mark.parametrize("L", [0, 5, 31, 32, 33, 64, 250, 257, 545, 1024, 1100])
 @pytest.mark.parametrize("k", [3, 10, 16])
 def test_batched_attention_of_any_prompt_length(gpu, L, k):
     """Draft layer, several sequences per call (batched attention: the prompt on the matrix cores from 32 positions on,
-    whole steps of 32 keys or not) against the same sequences one at a time (at most 16 rows: the weight streams).
-    One sequence stops before the third call.
+    whole steps of 32 keys or not; one too long for that: one workgroup per row and head) against the same sequences one at a
+    time (at most 16 rows: the weight streams).  One sequence stops before the third call.
 
     Tolerance: both sides round at the same five points of a call, what lies between them is summed in another order,
     and a rounding that falls the other way moves a term by one bf16 ulp (2^-8): 2^-5 of the row's rms, as against the oracle."""
@@ -123,10 +123,11 @@ def test_batched_attention_of_any_prompt_length(gpu, L, k):
     _batch_against_single(gpu, 7, k, 256, 384, L, range(7), 1000 * k + L)
 
 
-# Row counts around the blocks of 32 rows and the column tiles; few rows of W for 256 workgroups, so that every product but
-# gate/up is split: K = 11008 (172 k tiles) into up to eight uneven ranges, K = 2048 and 1024 into up to eight and four.
+# Row counts around the blocks of 32 rows and the column tiles, few rows of W for 256 workgroups: K = 11008 (172 k tiles) in
+# eight uneven ranges, 2816 in six or eight, 2048 in six or eight, 1408 in five, 1024 in two or four, 512 in one or two, 256 in
+# one.  H = 4096 with 640 rows: tiles of 192 rows of W, whole and split.
 @pytest.mark.parametrize("B,k,H,F", [(6, 3, 256, 11008), (8, 4, 256, 2944), (11, 3, 1024, 1408), (13, 5, 256, 11008), (43, 3, 512, 1024),
-                                     (65, 5, 256, 11008), (64, 10, 1024, 2816)])
+                                     (65, 5, 256, 11008), (64, 10, 1024, 2816), (64, 10, 4096, 1408)])
 def test_split_products_of_the_layer(gpu, B, k, H, F):
     """Draft layer with more than 16 rows: partial sums of K ranges, added up by the norms, the attention and the last launch,
     against the same sequences one at a time (at most 16 rows: whole sums in the weight streams).  Tolerance as above."""
