@@ -17,6 +17,7 @@
 //   The SiLU gate and the final bf16 rounding of the hidden rows ride in the epilogues of the
 //   linears that produce their inputs.
 // Rows of stopped sequences are skipped; a launch whose rows are all inactive exits at once.
+#include "attn_plan.hpp"
 #include "body_kernels.hpp"
 #include "ddd_device.hpp"
 #include "gemm_plan.hpp"
@@ -603,7 +604,6 @@ hipError_t launch_pack_x0(const PackX0Args& a, hipStream_t stream) {
 // read once and multiplied with all k queries (four threads per key, 32 elements each), each value once and
 // weighted into all k outputs.  The arithmetic per row is that of body_attention_kernel (the same products and
 // weights; sums in a different but fixed order).
-constexpr int kSeqRows = 16;          // most rows per sequence (k) this kernel handles
 constexpr int kSeqThreads = 1024;
 
 __global__ __launch_bounds__(kSeqThreads) void body_attention_seq_kernel(BodyAttnArgs a) {
@@ -788,33 +788,6 @@ __global__ __launch_bounds__(kSeqThreads) void body_attention_seq_kernel(BodyAtt
 // is a chain of dependent steps, and the others' loads run under it.  The rows' own keys and their ancestors' (at most
 // 32 per row, different from row to row) are handled by ordinary arithmetic.  (With one workgroup per (row, head) the
 // launch took 510 us at the 7B shape with 640 rows, with ordinary arithmetic per (sequence, head) 177 us.)
-constexpr int kMfThreads = 256;
-constexpr int kMfLeast = 32;                 // shortest prompt (fewer keys leave most of the waves without a step of 32)
-constexpr int kMfWaves = kMfThreads / 64;
-constexpr int kMfOutPitch = kHeadDim + 4;    // floats of a row in a wave's outputs
-
-struct MfLds {              // offsets in bytes
-  int spitch, ppitch;       // floats of a row of scores, bf16 of a row of weights
-  size_t rsum, anc, ks, vs, aw, sct, ph, pl, total;
-};
-__host__ __device__ inline MfLds mf_lds(int L, int step) {
-  MfLds m;
-  m.spitch = ((L + 3) & ~3) + 4;
-  m.ppitch = ((L + 31) & ~31) + 8;
-  m.rsum = (size_t)kSeqRows * kHeadDim * 4;            // behind the rotated queries
-  m.anc = m.rsum + kSeqRows * 4;
-  m.ks = m.anc + kSeqRows * 32 * 4;
-  m.vs = m.ks + kSeqRows * kHeadDim * 2;
-  m.aw = m.vs + kSeqRows * kHeadDim * 2;               // [kSeqRows][step + 1] scores, then weights, past the prompt
-  m.sct = (m.aw + (size_t)kSeqRows * (step + 1) * 4 + 15) & ~(size_t)15;
-  m.ph = m.sct + (size_t)kSeqRows * m.spitch * 4;
-  m.pl = m.ph + (size_t)kSeqRows * m.ppitch * 2;
-  m.total = m.pl + (size_t)kSeqRows * m.ppitch * 2;
-  const size_t outs = m.sct + (size_t)kMfWaves * kSeqRows * kMfOutPitch * 4;   // the waves' outputs take the place of sct, ph, pl
-  if (outs > m.total) m.total = outs;
-  return m;
-}
-
 __device__ __forceinline__ void split_bf16x8(const float* x, bool on, bf16x8& hi, bf16x8& lo) {
   u32x4 h, l;
 #pragma unroll
@@ -1067,11 +1040,11 @@ static size_t attention_seq_lds(int n_vis) {
 hipError_t launch_body_attention(const BodyAttnArgs& a, hipStream_t stream) {
   const int n_vis = a.L + a.step + 1;
   // batched rounds with a prompt: one workgroup per (sequence, head), the prompt part on the matrix cores
-  if (a.R > kBodyRows && a.k <= kSeqRows && a.L >= kMfLeast && mf_lds(a.L, a.step).total <= 150 * 1024) {
+  if (attention_on_matrix_cores(a.R, a.k, a.L, a.step)) {
     static bool prepared_mf = false;
     if (!prepared_mf) {
       const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&body_attention_mfma_kernel),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024);
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, kMfLdsMost);
       if (e != hipSuccess) return e;
       prepared_mf = true;
     }
@@ -1080,7 +1053,7 @@ hipError_t launch_body_attention(const BodyAttnArgs& a, hipStream_t stream) {
                        mf_lds(a.L, a.step).total, stream, a);
     return hipGetLastError();
   }
-  // ... without one (or with one too long for the LDS): the same by ordinary arithmetic
+  // ... with a shorter one or none: the same by ordinary arithmetic
   if (a.R > kBodyRows && a.k <= kSeqRows && attention_seq_lds(n_vis) <= 150 * 1024) {
     static bool prepared = false;
     if (!prepared) {
@@ -1094,7 +1067,8 @@ hipError_t launch_body_attention(const BodyAttnArgs& a, hipStream_t stream) {
                        attention_seq_lds(n_vis), stream, a);
     return hipGetLastError();
   }
-  const size_t lds = (size_t)(400 + 8 * kHeadDim + ((n_vis + 3) & ~3) + 32) * sizeof(float);
+  // few rows, wider beams, or a prompt too long for the LDS: one workgroup per (row, head)
+  const size_t lds = (size_t)(kAttnLdsFloats + ((n_vis + 3) & ~3) + 32) * sizeof(float);
   hipLaunchKernelGGL(body_attention_kernel, dim3(a.R * (a.H / kHeadDim)), dim3(kAttnThreads), lds, stream, a);
   return hipGetLastError();
 }
