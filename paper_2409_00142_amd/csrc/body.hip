@@ -32,6 +32,9 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float x) {   // finite input
 }
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
+typedef u32x4 u32x4_of_halves __attribute__((aligned(2)));   // the caller's prompt values start on any element,
+typedef f32x4 f32x4_of_floats __attribute__((aligned(4)));   // its norm weights on any float
+
 // ---- y (+)= x W^T ----------------------------------------------------------------------------
 // MULTI: several K ranges, the last of any number of units; otherwise one whole range, and the input rows stay in registers
 // for the whole kernel.
@@ -295,7 +298,7 @@ __global__ __launch_bounds__(512) void sum_rmsnorm_kernel(SumRmsNormArgs a) {
   for (int j = 0; j < 3; ++j) {
     const int i = (tid + 512 * j) * 4;
     if (i < a.H) {
-      const f32x4 g = *reinterpret_cast<const f32x4*>(a.g + i);
+      const f32x4 g = *reinterpret_cast<const f32x4_of_floats*>(a.g + i);
       uint32_t o[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) o[e] = f32_to_bf16_rne(xv[j][e] * inv * g[e]);
@@ -424,7 +427,7 @@ __global__ __launch_bounds__(kAttnThreads, 4) void body_attention_kernel(BodyAtt
 #pragma unroll
     for (int i = 0; i < kAttnKeys; ++i) {
       const int j = j0 + kGroups * i + kg;
-      if (j < a.L) u[i] = *reinterpret_cast<const u32x4*>(base + at0 + (size_t)j * a.H);
+      if (j < a.L) u[i] = *reinterpret_cast<const u32x4_of_halves*>(base + at0 + (size_t)j * a.H);
     }
   };
   load_block(a.Kp, 0, kb);

@@ -196,6 +196,42 @@ def test_body_few_rows_prompt_lengths(gpu, B, L):
         D.ddd_body_destroy(body)
 
 
+@pytest.mark.parametrize("B", [1, 6])
+def test_body_weights_off_alignment(gpu, B):
+    """The caller's norm weights start on any float and, with few rows, the prompt's values on any element: the same bits."""
+    torch, D, SD = gpu
+    H, F, V, k, L = 384, 1408, 60, 4, 70
+    print(f"[case] body off alignment B={B}", flush=True)
+    dev_w, dev_p, _, _ = _body_inputs(torch, SD, V, H, F, L, B)
+
+    def shifted(t):                                              # a copy whose first element is the second of an allocation
+        buf = torch.empty(t.numel() + 1, dtype=t.dtype, device="cuda")
+        buf[1:].copy_(t.reshape(-1))
+        return buf[1:].view(t.shape)
+
+    def steps(w, p):
+        st, st_t = D.alloc_state(D.make_config(B, H, V, k, 4, 8, 0.3))
+        rng = np.random.default_rng(3)
+        body = D.ddd_body_create(D.ddd_body_config(B, k, H, F, V, 4, L))
+        out = []
+        try:
+            D.ddd_body_bind(body, w, p)
+            for s in range(3):
+                st_t["beam_token"].copy_(torch.from_numpy(rng.integers(0, V, (B, k)).astype(np.int32)))
+                hid = torch.zeros(B * k, H, dtype=torch.bfloat16, device="cuda")
+                D.ddd_body_step(body, s, st, hid)
+                torch.cuda.synchronize()
+                out.append(_bits(hid))
+        finally:
+            D.ddd_body_destroy(body)
+        return out
+
+    off_w = {n: shifted(t) if n in ("g1", "g2") else t for n, t in dev_w.items()}
+    off_p = {n: shifted(t) if n == "V" and B == 1 else t for n, t in dev_p.items()}
+    for a, b in zip(steps(dev_w, dev_p), steps(off_w, off_p)):
+        assert np.array_equal(a, b)
+
+
 @pytest.mark.parametrize("shape", [("tiny", 1, 4, 256, 384, 500, 9, 5), ("k10_h1024", 1, 10, 1024, 2816, 3000, 33, 6),
                                    # the shape the benchmark's --body layer times: 7B sizes, 32 heads, 256 prompt positions
                                    ("7b_full_shape", 1, 10, 4096, 11008, 32000, 256, 3),
