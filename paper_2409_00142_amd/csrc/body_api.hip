@@ -19,7 +19,7 @@ struct ddd_body {
   bool bound;
   float* r;          // fp32 [rows][H]   residual stream
   uint16_t* xn;      // bf16 [rows][H]   normalised rows / attention output
-  float* qkv;        // fp32 [rows][3H]
+  float* qkv;        // fp32 [kBodyRows][3H]: calls of more rows leave partial sums in part instead
   uint16_t* act;     // bf16 [rows][F]
   uint16_t* h_hist;  // bf16 [D][rows][H]
   uint16_t* k_hist;
@@ -209,7 +209,7 @@ int ddd_body_create(const ddd_body_config* cfg, ddd_body** out) {
   const size_t H = cfg->H, F = cfg->F, D = cfg->max_depth, R = b->rows > kBodyRows ? b->rows : kBodyRows;
   hipError_t e = hipMalloc(&b->r, R * H * sizeof(float));
   if (e == hipSuccess) e = hipMalloc(&b->xn, R * H * sizeof(uint16_t));
-  if (e == hipSuccess) e = hipMalloc(&b->qkv, R * 3 * H * sizeof(float));
+  if (e == hipSuccess) e = hipMalloc(&b->qkv, (size_t)kBodyRows * 3 * H * sizeof(float));
   if (e == hipSuccess) e = hipMalloc(&b->act, R * F * sizeof(uint16_t));
   if (e == hipSuccess) e = hipMalloc(&b->h_hist, D * R * H * sizeof(uint16_t));
   if (e == hipSuccess) e = hipMalloc(&b->k_hist, D * R * H * sizeof(uint16_t));

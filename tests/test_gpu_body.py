@@ -232,6 +232,25 @@ def test_body_weights_off_alignment(gpu, B):
         assert np.array_equal(a, b)
 
 
+def test_body_memory(gpu):
+    """What a body of 640 rows holds: residual stream, norms, activations, FC inputs, three histories, and partial sums of three
+    hidden sizes per row or one tile of 192 x 320 for every CU - and q, k, v of 16 rows, not of 640."""
+    torch, D, SD = gpu
+    B, k, H, F, calls = 64, 10, 4096, 11008, 3
+    print("[case] body memory", flush=True)
+    R, chip = B * k, torch.cuda.get_device_properties(0).multi_processor_count * 192 * 320
+    want = R * H * (4 + 2 + 4) + R * F * 2 + 3 * calls * R * H * 2 + 4 * max(R * 3 * H, chip) + 16 * 3 * H * 4
+    D.ddd_body_destroy(D.ddd_body_create(D.ddd_body_config(B, k, H, F, 1000, calls, 64)))   # the kernels are loaded
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    body = D.ddd_body_create(D.ddd_body_config(B, k, H, F, 1000, calls, 64))
+    try:
+        used = free - torch.cuda.mem_get_info()[0]
+    finally:
+        D.ddd_body_destroy(body)
+    assert used <= want + 12 * (2 << 20), (used, want)            # a dozen allocations, rounded up to 2 MB at most
+
+
 @pytest.mark.parametrize("shape", [("tiny", 1, 4, 256, 384, 500, 9, 5), ("k10_h1024", 1, 10, 1024, 2816, 3000, 33, 6),
                                    # the shape the benchmark's --body layer times: 7B sizes, 32 heads, 256 prompt positions
                                    ("7b_full_shape", 1, 10, 4096, 11008, 32000, 256, 3),
