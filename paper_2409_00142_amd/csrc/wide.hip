@@ -226,10 +226,10 @@ __device__ __forceinline__ void tree_finalize_wide_block(const ddd_state& st, co
     for (int i0 = tid; i0 < N; i0 += 16 * kWideThreads) {
       float x[16];
 #pragma unroll
-      for (int u = 0; u < 16; ++u) x[u] = (i0 + u * kWideThreads < N) ? psc[i0 + u * kWideThreads + 1] : -INFINITY;
+      for (int u = 0; u < 16; ++u) x[u] = psc[min(i0 + u * kWideThreads, N - 1) + 1];   // no branch: all in flight
 #pragma unroll
       for (int u = 0; u < 16; ++u)
-        if (i0 + u * kWideThreads < N && ord32(x[u]) >= bound) {
+        if (ord32(x[u]) >= bound && i0 + u * kWideThreads < N) {
           const int p = atomicAdd(&sm.cnt, 1);
           if (p < kWCand) cand[p] = rerank_key(x[u], i0 + u * kWideThreads + 1);
         }
