@@ -365,8 +365,8 @@ __device__ __forceinline__ SumsView qkv_view(const BodyAttnArgs& a, int lane) { 
   return a.sums.part != nullptr ? sums_view(a.sums, sums_rows(a.sums), lane) : SumsView{nullptr, 0, 0, 0};
 }
 // Elements p and p + 64 of the query, key and value of row r, head h.
-__device__ __forceinline__ void load_qkv_pair(const BodyAttnArgs& a, const SumsView& v, int r, int h, int p, float& q0, float& q1, float& k0,
-                                              float& k1, float& v0, float& v1) {
+__device__ __forceinline__ void load_qkv_pair(const BodyAttnArgs& a, const SumsView& v, int r, int h, int p, float& q0, float& q1,
+                                              float& k0, float& k1, float& v0, float& v1) {
   const int c = h * kHeadDim + p;
   if (a.sums.part != nullptr) {                                  // uniform: a split product, added up here
     const int n = a.row_pos != nullptr ? a.row_pos[r] : r;
@@ -786,9 +786,10 @@ __global__ __launch_bounds__(kSeqThreads) void body_attention_seq_kernel(BodyAtt
 // m - any 16 of the 128 will do.  A wave then holds all d of its keys, and the waves' sums meet in LDS.  (A copy of the
 // values with the keys of an element contiguous, written by every round's prompt call, cost 72 us a round at B = 64,
 // L = 256, H = 4096 and as much memory as the values.)  What bounds it: the 268 MB of prompt keys and values at 640 rows,
-// 55 us at the rate of a large copy: 62 us for one row per
-// sequence, 88 us for ten (which read 63 MB of partial sums too; 92 with the copied values).  No operand is staged in LDS, which leaves room for three workgroups per CU: each
-// is a chain of dependent steps, and the others' loads run under it.  The rows' own keys and their ancestors' (at most
+// 55 us at the rate of a large copy: 62 us for one row per sequence, 88 us for ten (which read 63 MB of partial sums too; 92
+// with the copied values).  No operand is staged in LDS, but scores and weights of the whole prompt are: three workgroups share a
+// CU up to L = 256, two up to 480, one beyond (attn_plan.hpp).  Each is a chain of dependent steps, and the others' loads run
+// under it.  The rows' own keys and their ancestors' (at most
 // 32 per row, different from row to row) are handled by ordinary arithmetic.  (With one workgroup per (row, head) the
 // launch took 510 us at the 7B shape with 640 rows, with ordinary arithmetic per (sequence, head) 177 us.)
 __device__ __forceinline__ void split_bf16x8(const float* x, bool on, bf16x8& hi, bf16x8& lo) {

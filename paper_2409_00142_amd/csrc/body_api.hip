@@ -72,8 +72,8 @@ bool fit_range(int units, int* G, int* nw) {
 // One product y (+)= x W^T over K, cut into K ranges of 128 * G * nw elements; `a` describes the product: rg[0]
 // holds W, x and the gather of the whole K extent.  Up to kLinearRanges ranges of the same length go into one launch, the
 // last of them shorter where K ends: a K of 11008 is 4096 + 4096 + 2816 in one launch (with ranges of whole length only,
-// 2 x 5120 and a second launch for 768: 34.5 -> 27.5 us at 4096 rows of W, with the gap).  a.mode is the LinearMode of the whole product;
-// a.out16 / a.out16b are written by the launch that completes it.
+// 2 x 5120 and a second launch for 768: 34.5 -> 27.5 us at 4096 rows of W, with the gap).  a.mode is the LinearMode of the
+// whole product; a.out16 / a.out16b are written by the launch that completes it.
 int enqueue_linear(const ddd_body* b, LinearArgs a, int K, hipStream_t s) {
   a.ntiles = (a.N + 15) / 16;
   const int nslice = a.ntiles < b->n_cu ? a.ntiles : b->n_cu;

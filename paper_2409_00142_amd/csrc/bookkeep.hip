@@ -78,7 +78,9 @@ __device__ __forceinline__ uint32_t kth_largest_group_max(const float* gmax, int
 
 // The rank-j key of a row of logits, in the form the launch's caller wants it.  For a wide beam inside a draft call the row
 // also forms its candidates of the beam update (Algorithm 1's next summed logprobs) - with k * k of them per sequence that is
-// 160 KB of pool entries, which one workgroup per sequence spent most of its launch on - and leaves their keys.
+// 160 KB of pool entries, which one workgroup per sequence spent most of its launch on - and leaves their keys.  WIDE: whether the
+// kernel serves such beams.
+template <bool WIDE>
 struct RowEmit {
   const RowTopkArgs& a;
   int row;
@@ -87,7 +89,7 @@ struct RowEmit {
   int parent_node;
 
   __device__ __forceinline__ RowEmit(const RowTopkArgs& args, int r) : a(args), row(r), lse(0.f), parent_lps(0.f), parent_node(0) {
-    if (a.form) {
+    if (WIDE && a.form) {
       parent_lps = a.beam.st.logprobsum[row];            // row b * k + i is slot i of sequence b
       parent_node = a.beam.st.beam_node[row];
     }
@@ -97,7 +99,7 @@ struct RowEmit {
       // the results of a single LM-head call (a separate launch that turned keys into tokens and logprobs cost 5 us)
       a.topk_token[(size_t)row * a.k + j] = key_token(key);
       a.topk_logprob[(size_t)row * a.k + j] = key_value(key) - lse;
-    } else if (a.form) {
+    } else if (WIDE && a.form) {
       const int k = a.k, b = row / k, f = (row - b * k) * k + j, t = key_token(key);
       const float sc = __fadd_rn(parent_lps, key_value(key) - lse);   // logprob = logit - lse, then one fp32 add
       const size_t pn = (size_t)b * a.beam.nmax + 1 + k + (size_t)(a.beam.step - 1) * k * k + f;
@@ -127,7 +129,7 @@ __global__ __launch_bounds__(256) void row_topk_kernel(RowTopkArgs a) {
   __shared__ uint32_t s_bound[4];
   const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if (a.row_active != nullptr && !a.row_active[row]) return;   // uniform
-  RowEmit emit(a, row);
+  RowEmit<false> emit(a, row);
   const int ngrp_valid = (a.V + 63) >> 6;
   const float* gmax = a.grp_max + (size_t)row * a.ngrp;
   const float* gsum = a.grp_sum + (size_t)row * a.ngrp;
@@ -330,7 +332,7 @@ __global__ __launch_bounds__(kWideRowThreads) void row_topk_wide_kernel(RowTopkA
   __shared__ int s_cnt, s_ng;
   const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if (a.row_active != nullptr && !a.row_active[row]) return;   // uniform
-  RowEmit emit(a, row);
+  RowEmit<true> emit(a, row);
   const int ngrp = (a.V + 63) >> 6, ngrp4 = (ngrp + 3) >> 2;
   float m = -INFINITY, mine_max[2] = {-INFINITY, -INFINITY}, mine_sum[2] = {0.f, 0.f};
 #pragma unroll

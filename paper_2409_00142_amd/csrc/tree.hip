@@ -107,8 +107,9 @@ hipError_t launch_verify_accept(const VerifyArgs& a, hipStream_t stream) {
 // The walk is a chain - which row is next depends on the decision at this one - and a row of 32 000 fp64 exponentials
 // keeps one CU busy for about 8 us, so the two ways of doing it differ in where the rows' sums are made:
 //  * small batches (verify_sample_from_sums): a first launch makes the sums of every row of every tree with the whole
-//    chip (23 us for 62 MB: fp64 issue, 8 cycles an instruction), and the walk that follows looks numbers up: B = 8, V = 32000, 61 nodes,
-//    41 to 65 us a call by the depth of the accepted paths -> 30 us, B = 1 24 to 37 -> 15 us.  It reads m + 1 rows per sequence instead of two or three.
+//    chip (23 us for 62 MB: fp64 issue, 8 cycles an instruction), and the walk that follows looks numbers up: B = 8, V = 32000,
+//    61 nodes, 41 to 65 us a call by the depth of the accepted paths -> 30 us, B = 1 24 to 37 -> 15 us.  It reads m + 1 rows per
+//    sequence instead of two or three.
 //  * beyond that (verify_sample_kernel): one workgroup of 16 waves per sequence makes the sums of the rows it visits.
 // The line lies where the extra rows would cost what they save (rows_from_sums).
 constexpr int kVsWaves = 16;

@@ -89,8 +89,8 @@ __device__ __forceinline__ const u32x4* prompt_chunk(const TreeAttnArgs& a, cons
 // of the step is chunk i = first + ch of the rest: prompt chunks, then the tree's, then nothing.
 // vis: which of the lane's 16 keys of this wave's chunk count for its two queries, bit e as the accumulator registers go.
 template <int NW>
-__device__ __forceinline__ void load_rest(const TreeAttnArgs& a, int first, int c_rest, int n_prompt, int n_rest, int b, int h, int qt,
-                                          int wave, int lane, Operands<NW>& x, uint32_t (&vis)[2]) {
+__device__ __forceinline__ void load_rest(const TreeAttnArgs& a, int first, int c_rest, int n_prompt, int n_rest, int b, int h,
+                                          int qt, int wave, int lane, Operands<NW>& x, uint32_t (&vis)[2]) {
   const int l32 = lane & 31, lh = lane >> 5, db = wave / (NW / 4);
   const u32x4 zero = {0u, 0u, 0u, 0u};
   const int i = first + wave;
@@ -157,8 +157,9 @@ struct QueryState {
 
 // One step.  NEXT: the operands of the next whole step are requested from kn and vn, each as soon as its register has been used.
 template <int NW, bool REST, bool NEXT>
-__device__ __forceinline__ void attend_step(Operands<NW>& x, const u32x4* qlds, u32x4* plds, float* cmax_lds, const uint32_t (&vis)[2],
-                                            const u32x4* kn, const u32x4* vn, int wave, int lane, QueryState<NW>& st) {
+__device__ __forceinline__ void attend_step(Operands<NW>& x, const u32x4* qlds, u32x4* plds, float* cmax_lds,
+                                            const uint32_t (&vis)[2], const u32x4* kn, const u32x4* vn, int wave, int lane,
+                                            QueryState<NW>& st) {
   // scores are kept in units of ln 2: exp(s - m) = exp2(s' - m') with s' = s * log2(e) / sqrt(128)
   const float scale = 0.08838834764831845f * 1.4426950408889634f;
   const int l32 = lane & 31;
@@ -170,7 +171,8 @@ __device__ __forceinline__ void attend_step(Operands<NW>& x, const u32x4* qlds, 
     for (int e = 0; e < 16; ++e) sacc[e] = 0.f;
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
-      sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x.kf[s], __builtin_bit_cast(bf16x8, qlds[(qb * 8 + s) * 64 + lane]), sacc, 0, 0, 0);
+      const bf16x8 qf = __builtin_bit_cast(bf16x8, qlds[(qb * 8 + s) * 64 + lane]);
+      sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x.kf[s], qf, sacc, 0, 0, 0);
       if (NEXT && qb == 1) x.kf[s] = __builtin_bit_cast(bf16x8, kn[s * 64 + lane]);
     }
     // register e of the lane: key c0 + (e>>2)*8 + lh*4 + (e&3), query qb*32 + l32
