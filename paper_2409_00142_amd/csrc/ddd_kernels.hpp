@@ -225,9 +225,10 @@ struct VerifySampleArgs {
   float temperature;
   int B, m, D, V;
   void* rows;                    // null, or scratch of verify_sample_row_bytes() per row of logits: the sums of all rows first
+  int parts;                     // of every row's sums (set by the launcher)
 };
 size_t verify_sample_row_bytes();
-hipError_t launch_verify_sample(const VerifySampleArgs& a, hipStream_t stream);
+hipError_t launch_verify_sample(VerifySampleArgs a, hipStream_t stream);
 
 // Tree attention over the final tree's mask (tree_attn.hip); heads of 128.
 struct TreeAttnArgs {

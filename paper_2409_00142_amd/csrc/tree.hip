@@ -436,6 +436,11 @@ struct VsRow {
   float pad[8];
 };
 static_assert(sizeof(VsRow) == 1152, "whole lines");
+// Parts of a row that hold tokens (eight from 28 673 tokens up to 32 768, one up to 4096); only those are made and count.
+static int vs_parts(int V) {
+  const int cpb = (V + kVsSub * kVsChunk - 1) / (kVsSub * kVsChunk), part = kVsPartSub * cpb * kVsChunk;
+  return (V + part - 1) / part;
+}
 static_assert(kVsWalkThreads >= DDD_MMAX + 1, "a thread per tree index");
 
 size_t verify_sample_row_bytes() { return sizeof(VsRow); }
@@ -505,6 +510,8 @@ __global__ __launch_bounds__(kVsPartWaves * kWave) void verify_row_sums_kernel(V
   }
 }
 
+// ALL: every part of a row holds tokens.
+template <bool ALL>
 __global__ __launch_bounds__(kVsWalkThreads) void verify_sample_from_sums_kernel(VerifySampleArgs a) {
   __shared__ VsTree t;
   __shared__ double s_rem[DDD_MMAX + 1], s_kw[DDD_MMAX + 1];
@@ -514,6 +521,7 @@ __global__ __launch_bounds__(kVsWalkThreads) void verify_sample_from_sums_kernel
   const int T = a.m + 1, V = a.V;
   const int n = min(a.tree.n_sel[b], a.m) + 1;
   const VsRow* rows = static_cast<const VsRow*>(a.rows) + (size_t)b * T;
+  const int parts = ALL ? kVsParts : a.parts;
   const double beta2 = beta2_of(a);
   StatsPre sp{0, 0u};
   if (tid == 0) sp = stats_begin(a.stats, b, a.B);
@@ -528,6 +536,11 @@ __global__ __launch_bounds__(kVsWalkThreads) void verify_sample_from_sums_kernel
     for (int p = 0; p < kVsParts; ++p) {
       pm[p] = rows[tid].pmax[p];
       ps[p] = rows[tid].psum[p];
+    }
+#pragma unroll
+    for (int p = 0; p < kVsParts; ++p) {                                  // what the others hold was never written
+      pm[p] = p < parts ? pm[p] : -__builtin_inff();
+      ps[p] = p < parts ? ps[p] : 0.0;
     }
 #pragma unroll
     for (int p = 0; p < kVsParts; ++p) mx = fmaxf(mx, pm[p]);
@@ -564,10 +577,11 @@ __global__ __launch_bounds__(kVsWalkThreads) void verify_sample_from_sums_kernel
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");                // lane 0's list of rejected tokens
     __builtin_amdgcn_wave_barrier();
     const VsRow& r = rows[cur];
+    const bool held = 2 * lane < kVsPartSub * parts;
     const double scale = weight_of((double)r.pmax[(2 * lane) / kVsPartSub] - (double)s_max[cur], beta2);
-    const int bonus = draw_bonus(t, nrm, a.logits + ((size_t)b * T + cur) * V, (double)s_max[cur], beta2, t.ub[cur] * rem,
-                                 r.sub[2 * lane] * scale, r.sub[2 * lane + 1] * scale, chunks_per_block(V) * kVsChunk, V,
-                                 rows_aligned(a), lane);
+    const double v0 = held ? r.sub[2 * lane] * scale : 0.0, v1 = held ? r.sub[2 * lane + 1] * scale : 0.0;
+    const int bonus = draw_bonus(t, nrm, a.logits + ((size_t)b * T + cur) * V, (double)s_max[cur], beta2, t.ub[cur] * rem, v0, v1,
+                                 chunks_per_block(V) * kVsChunk, V, rows_aligned(a), lane);
     if (lane == 0) {
       s_cur = cur;
       s_nrm = nrm;
@@ -586,11 +600,12 @@ __global__ __launch_bounds__(kVsWalkThreads) void verify_sample_from_sums_kernel
   }
 }
 
-hipError_t launch_verify_sample(const VerifySampleArgs& a, hipStream_t stream) {
+hipError_t launch_verify_sample(VerifySampleArgs a, hipStream_t stream) {
   if (a.m > DDD_MMAX) return hipErrorInvalidValue;      // the kernels keep the tree in LDS
   const int cpb = (a.V + kVsSub * kVsChunk - 1) / (kVsSub * kVsChunk);   // chunks of 256 tokens per block
   if (a.rows != nullptr) {
-    const dim3 grid(kVsParts, a.m + 1, a.B), block(kVsPartWaves * kWave);
+    a.parts = vs_parts(a.V);
+    const dim3 grid(a.parts, a.m + 1, a.B), block(kVsPartWaves * kWave);
     if (cpb == 1)
       hipLaunchKernelGGL((verify_row_sums_kernel<1>), grid, block, 0, stream, a);
     else if (cpb == 2)
@@ -603,7 +618,10 @@ hipError_t launch_verify_sample(const VerifySampleArgs& a, hipStream_t stream) {
       hipLaunchKernelGGL((verify_row_sums_kernel<0>), grid, block, 0, stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(verify_sample_from_sums_kernel, dim3(a.B), dim3(kVsWalkThreads), 0, stream, a);
+    if (a.parts == kVsParts)
+      hipLaunchKernelGGL(verify_sample_from_sums_kernel<true>, dim3(a.B), dim3(kVsWalkThreads), 0, stream, a);
+    else
+      hipLaunchKernelGGL(verify_sample_from_sums_kernel<false>, dim3(a.B), dim3(kVsWalkThreads), 0, stream, a);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(verify_sample_kernel, dim3(a.B), dim3(kVsThreads), 0, stream, a);

@@ -11,13 +11,14 @@ pytestmark = pytest.mark.gpu
 MIN_MARGIN = 1e-10     # relative distance of a decision from its threshold below which fp64 summation order could matter
 
 
-@pytest.mark.parametrize("V", [5, 255, 257, 1024, 32768, 32769, 65537, 98305, 131071, 131076])
+@pytest.mark.parametrize("V", [5, 255, 257, 1024, 4096, 4097, 8193, 32768, 32769, 65537, 98305, 131071, 131076])
 @pytest.mark.parametrize("T", [1.0, 1e-3, 30.0])
 def test_both_routes_agree(V, T):
     import torch
     if not torch.cuda.is_available():
         pytest.fail("GPU tests need a HIP device (an MI355X)")
     import paper_2409_00142_amd as D
+    # up to 4096 tokens a row is one part of eight, from 4097 two, from 32769 a part is twice as long (five of them)
     print(f"[case] verify_sample routes V={V} T={T}", flush=True)
     B, k, Dm, m = 3, 4, 5, 12
     rng = np.random.default_rng(V)
