@@ -333,13 +333,13 @@ hipError_t launch_sum_rows(const SumRowsArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// ---- RoPE + key/value store + tree attention: one workgroup of 8 waves per (row, head) ----------
+// ---- RoPE + key/value store + tree attention: one workgroup of 8 or 16 waves per (row, head) ----------
 // A chain of memory round trips: the first 256 keys and values are in flight while the query is rotated and the ancestors are
 // looked up, sixteen threads read a key or value of 256 bytes together (one key per thread, 64 rows in a wave's
 // load, and 2-byte reads of the values took 15.3 us for ten rows, 32 heads, L = 256, now 9.4).
-constexpr int kAttnThreads = 512;
 constexpr int kAttnKeys = 8;     // keys of a thread in flight
 
+template <int TH>
 __device__ __forceinline__ float block_max_f32(float x, float* red, int tid) {
   x = wave_max_f32(x);
   __syncthreads();              // red may still be read from an earlier reduction
@@ -347,9 +347,10 @@ __device__ __forceinline__ float block_max_f32(float x, float* red, int tid) {
   __syncthreads();
   float m = red[0];
 #pragma unroll
-  for (int w = 1; w < kAttnThreads / 64; ++w) m = fmaxf(m, red[w]);
+  for (int w = 1; w < TH / 64; ++w) m = fmaxf(m, red[w]);
   return m;
 }
+template <int TH>
 __device__ __forceinline__ float block_sum_f32(float x, float* red, int tid) {
   x = wave_sum_f32(x);
   __syncthreads();
@@ -357,7 +358,7 @@ __device__ __forceinline__ float block_sum_f32(float x, float* red, int tid) {
   __syncthreads();
   float s = 0.f;
 #pragma unroll
-  for (int w = 0; w < kAttnThreads / 64; ++w) s += red[w];      // fixed order
+  for (int w = 0; w < TH / 64; ++w) s += red[w];      // fixed order
   return s;
 }
 
@@ -399,12 +400,14 @@ __device__ __forceinline__ void unpack_bf16x8(const u32x4& u, float (&f)[8]) {
   }
 }
 
-constexpr int kAttnLdsFloats = 400 + (kAttnThreads / 64) * kHeadDim;   // in front of the scores
+template <int TH>
+constexpr int kAttnLdsFloats = 400 + (TH / 64) * kHeadDim;   // in front of the scores
 
 // LDS is exchanged, loads from global memory stay in flight (__syncthreads() would wait for them).
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-__global__ __launch_bounds__(kAttnThreads, 4) void body_attention_kernel(BodyAttnArgs a) {
+template <int TH>
+__global__ __launch_bounds__(TH, 4) void body_attention_kernel(BodyAttnArgs a) {
   extern __shared__ __align__(16) float sm[];
   const int nh = a.H / kHeadDim;
   const int r = blockIdx.x / nh, h = blockIdx.x % nh, tid = threadIdx.x;
@@ -413,13 +416,13 @@ __global__ __launch_bounds__(kAttnThreads, 4) void body_attention_kernel(BodyAtt
   float* qs = sm;                  // [128] rotated query
   float* ks = sm + 128;            // [128] own key as stored (bf16 values)
   float* vs = sm + 256;            // [128] own value as stored
-  float* red = sm + 384;           // [8] block reductions
-  float* part = sm + 400;          // [8][128] partial outputs
-  float* sc = sm + kAttnLdsFloats;                                // [n_vis] scores, then weights
+  float* red = sm + 384;           // [TH / 64] block reductions
+  float* part = sm + 400;          // [TH / 64][128] partial outputs
+  float* sc = sm + kAttnLdsFloats<TH>;                                // [n_vis] scores, then weights
   int* anc = reinterpret_cast<int*>(sc + ((n_vis + 3) & ~3));    // [step] row of the ancestor in each earlier call
 
-  // thread (kg, sub): elements sub*8 .. +7 of keys kg, kg + kGroups, ...; the first 256 keys are requested before anything else
-  constexpr int kGroups = kAttnThreads / 16;
+  // thread (kg, sub): elements sub*8 .. +7 of keys kg, kg + kGroups, ...; the first 256 (512) keys are requested before anything else
+  constexpr int kGroups = TH / 16;
   const int kg = tid >> 4, sub = tid & 15;
   const size_t at0 = (size_t)b * a.L * a.H + h * kHeadDim + sub * 8;
   u32x4 kb[kAttnKeys], vb[kAttnKeys];
@@ -510,14 +513,14 @@ __global__ __launch_bounds__(kAttnThreads, 4) void body_attention_kernel(BodyAtt
     }
   }
   score(ke, a.L + kg, kg <= a.step);
-  mx = block_max_f32(mx, red, tid);            // its barriers also publish the scores
+  mx = block_max_f32<TH>(mx, red, tid);            // its barriers also publish the scores
   float sum = 0.f;
-  for (int j = tid; j < n_vis; j += kAttnThreads) {
+  for (int j = tid; j < n_vis; j += TH) {
     const float p = __expf(sc[j] - mx);
     sc[j] = p;
     sum += p;
   }
-  sum = block_sum_f32(sum, red, tid);          // ... and these the weights
+  sum = block_sum_f32<TH>(sum, red, tid);          // ... and these the weights
 
   // values: the thread's eight elements over its keys, then over the groups
   float o[8];
@@ -551,7 +554,7 @@ __global__ __launch_bounds__(kAttnThreads, 4) void body_attention_kernel(BodyAtt
   if (tid < kHeadDim) {
     float t = 0.f;
 #pragma unroll
-    for (int g = 0; g < kAttnThreads / 64; ++g) t += part[g * kHeadDim + tid];   // fixed order
+    for (int g = 0; g < TH / 64; ++g) t += part[g * kHeadDim + tid];   // fixed order
     a.o[(size_t)r * a.H + h * kHeadDim + tid] = f32_to_bf16_rne(t / sum);
   }
 }
@@ -1041,7 +1044,7 @@ static size_t attention_seq_lds(int n_vis) {
          sizeof(float);
 }
 
-hipError_t launch_body_attention(const BodyAttnArgs& a, hipStream_t stream) {
+hipError_t launch_body_attention(const BodyAttnArgs& a, int n_cu, hipStream_t stream) {
   const int n_vis = a.L + a.step + 1;
   // batched rounds with a prompt: one workgroup per (sequence, head), the prompt part on the matrix cores
   if (attention_on_matrix_cores(a.R, a.k, a.L, a.step)) {
@@ -1072,8 +1075,15 @@ hipError_t launch_body_attention(const BodyAttnArgs& a, hipStream_t stream) {
     return hipGetLastError();
   }
   // few rows, wider beams, or a prompt too long for the LDS: one workgroup per (row, head)
-  const size_t lds = (size_t)(kAttnLdsFloats + ((n_vis + 3) & ~3) + 32) * sizeof(float);
-  hipLaunchKernelGGL(body_attention_kernel, dim3(a.R * (a.H / kHeadDim)), dim3(kAttnThreads), lds, stream, a);
+  // Sixteen waves where a prompt does not fit one pass of eight and the launch has no two workgroups for a CU: 512 keys in flight
+  // instead of 256.
+  const int n_wg = a.R * (a.H / kHeadDim), tail = ((n_vis + 3) & ~3) + 32;
+  if (a.L > 256 && n_wg <= n_cu)
+    hipLaunchKernelGGL(body_attention_kernel<1024>, dim3(n_wg), dim3(1024), (size_t)(kAttnLdsFloats<1024> + tail) * sizeof(float),
+                       stream, a);
+  else
+    hipLaunchKernelGGL(body_attention_kernel<512>, dim3(n_wg), dim3(512), (size_t)(kAttnLdsFloats<512> + tail) * sizeof(float),
+                       stream, a);
   return hipGetLastError();
 }
 

@@ -366,7 +366,7 @@ int ddd_body_step(void* user, int32_t step, const ddd_state* st, void* hid_out, 
     if (rc != DDD_OK) return rc;
     t.sums = split_sums(b, R, all, 3 * H, H);
     t.row_pos = all ? nullptr : b->row_pos;
-    BODY_HIP(launch_body_attention(t, s));
+    BODY_HIP(launch_body_attention(t, b->n_cu, s));
     // r1 = r0 + o Wo^T and its norm
     rc = enqueue_gemm_linear(b, R, all, b->w.Wo, H, H, b->xn, nullptr, kGemmPartial, nullptr, 0, s);
     if (rc != DDD_OK) return rc;
@@ -419,7 +419,7 @@ int ddd_body_step(void* user, int32_t step, const ddd_state* st, void* hid_out, 
   rc = enqueue_linear(b, lq, H, s);
   if (rc != DDD_OK) return rc;
 
-  BODY_HIP(launch_body_attention(t, s));
+  BODY_HIP(launch_body_attention(t, b->n_cu, s));
   LinearArgs lo = linear_args(b->w.Wo, H, H, R, act, b->r, H, kLinearAccumulate);   // r1 = r0 + o Wo^T
   lo.rg[0].x = b->xn;
   lo.rg[0].ldx = H;

@@ -96,7 +96,7 @@ struct BodyAttnArgs {
   int H, L, k, step, R;
   int hist_rows;              // rows per call in the histories (B*k)
 };
-hipError_t launch_body_attention(const BodyAttnArgs& a, hipStream_t stream);
+hipError_t launch_body_attention(const BodyAttnArgs& a, int n_cu, hipStream_t stream);
 
 // Input rows of the FC for calls that go through the MFMA GEMM: x0[r] = [E[token of r], feature of r's parent],
 // assembled once (the GEMM gathers whole rows of one matrix).  With row_active the same launch lists the active rows.

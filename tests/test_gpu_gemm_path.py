@@ -135,6 +135,15 @@ def test_split_products_of_the_layer(gpu, B, k, H, F):
     _batch_against_single(gpu, B, k, H, F, 33, sorted({0, 2, B // 2, B - 1}), B + F)
 
 
+# More workgroups than CUs: eight waves each; the sequences alone have sixteen.
+@pytest.mark.parametrize("B,k,L", [(7, 20, 300), (7, 20, 513), (9, 16, 1100)])
+def test_long_prompts_row_by_row(gpu, B, k, L):
+    """Draft layer with one workgroup per row and head and more keys than a pass holds, in a batch and alone.  Tolerance as
+    above."""
+    print(f"[case] long_prompts_row_by_row B={B} k={k} L={L}", flush=True)
+    _batch_against_single(gpu, B, k, 256, 384, L, [0, 2, B - 1], L)
+
+
 def _batch_against_single(gpu, B, k, H, F, L, check, seed):
     torch, D = gpu
     V, calls = 300, 4
