@@ -359,7 +359,10 @@ __device__ __forceinline__ bool tree_select_block(const ddd_state& st, const ddd
   __syncthreads();
 #pragma unroll
   for (int q = 0; q < 2; ++q)
-    if (chosen[q]) sm.e.par[ti[q]] = tidx[my_pn[q]];
+    if (chosen[q]) {
+      const int p = tidx[my_pn[q]];
+      sm.e.par[ti[q]] = p < ti[q] ? p : -1;   // a pool whose parents do not come first must not send the walk below in a circle
+    }
   __syncthreads();
   for (int i = tid; i < T; i += nthr) {
 #pragma unroll

@@ -242,3 +242,34 @@ def test_row_without_candidates(gpu, k, V):
     assert np.all(got["pool_depth"][base:base + kk] == 3)
     assert len(set(got["beam_node"])) == k and got["beam_node"].min() >= base and got["beam_node"].max() < base + kk
     assert np.array_equal(got["beam_parent_slot"], (got["beam_node"] - base) // k)
+
+
+@pytest.mark.parametrize("k,calls", [(10, 3), (10, 6), (100, 2)])
+def test_final_tree_of_a_pool_out_of_order(gpu, k, calls):
+    """A pool in which nodes are their own or each other's parents (a state that no round leaves): the tree is built without
+    those edges, as if the nodes had no parent in it."""
+    torch, D = gpu
+    print(f"[case] tree_out_of_order k={k} calls={calls}", flush=True)
+    n, m = 1 + k + (calls - 1) * k * k, 20
+    score = -np.arange(n, dtype=np.float32)                      # the first m nodes are the tree
+    parent = np.zeros(n, np.int32)
+    parent[0] = -1
+    parent[3], parent[5], parent[6], parent[7] = 3, 6, 5, 9
+    cfg = D.make_config(1, 128, 4000, k, calls, m, 0.0, 0)
+    ctx = D.ddd_create(cfg)
+    try:
+        st, t = D.alloc_state(cfg)
+        tree, tt = D.alloc_tree(cfg)
+        t["pool_score"][0, :n].copy_(torch.from_numpy(score))
+        t["pool_parent"][0, :n].copy_(torch.from_numpy(parent))
+        t["n_nodes"].fill_(n)
+        D.ddd_tree_finalize(ctx, st, tree)
+        torch.cuda.synchronize()
+        got = {x: v.cpu().numpy()[0] for x, v in tt.items()}
+    finally:
+        D.ddd_destroy(ctx)
+    assert np.array_equal(got["sel_node"][:m], np.arange(1, m + 1))
+    want = np.zeros(m + 1, np.int32)
+    want[[0, 3, 5, 7]] = -1
+    want[6] = 5
+    assert np.array_equal(got["parent_idx"], want)
