@@ -316,14 +316,18 @@ __global__ __launch_bounds__(256) void row_topk_kernel(RowTopkArgs a) {
 }
 
 // The same for wide beams (DDD_KMAX < k <= DDD_KWIDE_MAX), where a bound from quad maxima no longer holds k keys: 1024
-// threads rank the group maxima by counting (at most 2048: 32-bit compares against broadcast reads of LDS, several threads
-// per group), and then the candidates at or above the k-th of them.  (Bitonic sorts of both by 256 threads, a block
-// barrier per stage, took 28 us a launch at k = 100, V = 32000, whatever the number of rows; 14.5 us now.)
+// threads rank the group maxima by counting (32-bit compares against broadcast reads of LDS, several threads per group), and
+// then the candidates at or above the k-th of them.  More than 512 groups are folded to the maxima of up to four first: the
+// k-th largest of those is reached by k groups too, only a few more groups pass it (counting all 2000 groups of V = 128000
+// took 60 us).  (Bitonic sorts of both by 256 threads, a block barrier per stage, took 28 us a launch at k = 100,
+// V = 32000, whatever the number of rows; 14 us now.)
 constexpr int kWideRowThreads = 1024;
 constexpr int kWideGroups = 2048;   // V <= 2^17
+constexpr int kWideFold = 512;      // most values that are ranked
+static_assert(kWideGroups == 2 * kWideRowThreads && kWideFold == kWideRowThreads / 2, "a thread's two groups, and its neighbour's");
 
 __global__ __launch_bounds__(kWideRowThreads) void row_topk_wide_kernel(RowTopkArgs a) {
-  __shared__ __align__(16) uint32_t s_gm[kWideGroups];       // group maxima as ordered keys
+  __shared__ __align__(16) uint32_t s_gm[kWideFold];         // (folded) group maxima as ordered keys
   __shared__ int s_num[kWideGroups];                         // work area; later the groups that hold candidates
   __shared__ uint64_t s_cand[kCandMax];
   __shared__ int s_rank[kCandMax];
@@ -333,7 +337,8 @@ __global__ __launch_bounds__(kWideRowThreads) void row_topk_wide_kernel(RowTopkA
   const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if (a.row_active != nullptr && !a.row_active[row]) return;   // uniform
   RowEmit<true> emit(a, row);
-  const int ngrp = (a.V + 63) >> 6, ngrp4 = (ngrp + 3) >> 2;
+  const int ngrp = (a.V + 63) >> 6;
+  uint32_t top = 0u;                                         // the larger of the thread's groups
   float m = -INFINITY, mine_max[2] = {-INFINITY, -INFINITY}, mine_sum[2] = {0.f, 0.f};
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
@@ -341,10 +346,18 @@ __global__ __launch_bounds__(kWideRowThreads) void row_topk_wide_kernel(RowTopkA
     if (g < ngrp) {
       mine_max[u] = a.grp_max[(size_t)row * a.ngrp + g];
       mine_sum[u] = a.grp_sum[(size_t)row * a.ngrp + g];
+      top = umax32(top, ord32(mine_max[u]));
     }
-    if (g < 4 * ngrp4) s_gm[g] = (g < ngrp) ? ord32(mine_max[u]) : 0u;
     m = fmaxf(m, mine_max[u]);
   }
+  const bool fold = ngrp > kWideFold;                        // uniform
+  if (fold) {
+    top = umax32(top, dpp_move_u32<0xB1>(top));              // lane ^ 1
+    if ((tid & 1) == 0) s_gm[tid >> 1] = top;
+  } else if (tid < kWideFold) {
+    s_gm[tid] = top;
+  }
+  const int nval = fold ? (min(ngrp, kWideRowThreads) + 1) >> 1 : ngrp;   // more than k if folded
   if (tid == 0) s_cnt = s_ng = 0;
   for (int i = tid; i < kCandMax; i += kWideRowThreads) s_rank[i] = 0;
   m = wave_max_f32(m);
@@ -359,8 +372,8 @@ __global__ __launch_bounds__(kWideRowThreads) void row_topk_wide_kernel(RowTopkA
     if (tid + u * kWideRowThreads < ngrp) acc += mine_sum[u] * __expf(mine_max[u] - M);
   acc = wave_sum_f32(acc);
   if (lane == 0) s_red[1][wave] = acc;
-  // ---- T = k-th largest group max -----------------------------------------------------------------------------------
-  const uint32_t least = block_kth_largest_u32(s_gm, ngrp, min(a.k, ngrp), s_num, s_min, tid);   // its barriers publish s_red
+  // ---- T = k-th largest (folded) group max --------------------------------------------------------------------------
+  const uint32_t least = block_kth_largest_u32(s_gm, nval, min(a.k, nval), s_num, s_min, tid);   // its barriers publish s_red
   const float T = (ngrp < a.k) ? -INFINITY : unord32(least);
   float total = 0.f;
 #pragma unroll

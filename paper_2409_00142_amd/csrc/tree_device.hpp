@@ -172,10 +172,10 @@ __device__ __forceinline__ void count_larger_keys(const uint64_t* keys, int n, i
 }
 
 // The k-th largest of n values (1 <= k <= n), ties counted: the smallest with fewer than k larger ones.  By a block of 1024
-// threads, n <= 2048; vals: 16-byte aligned LDS, padded with zeros to a multiple of four; cnt: LDS [n], any contents; red:
+// threads, n <= 1024; vals: 16-byte aligned LDS, padded with zeros to a multiple of four; cnt: LDS [n], any contents; red:
 // LDS [16].  32-bit compares against values that the whole wave reads from one address, four at a time (two instructions
-// a compare; 500 values 3.3 us on a CU): one value per P threads up to 1024 values, two per thread above.  The block
-// barriers inside also order the caller's writes of vals before and its reuse of cnt after.
+// a compare; 500 values 3.3 us on a CU), a value per P threads.  The block barriers inside also order the caller's writes of
+// vals before and its reuse of cnt after.
 __device__ __forceinline__ int count_larger4(const uint4& v, uint32_t mine) {
   return (v.x > mine ? 1 : 0) + (v.y > mine ? 1 : 0) + (v.z > mine ? 1 : 0) + (v.w > mine ? 1 : 0);
 }
@@ -183,32 +183,19 @@ __device__ __forceinline__ uint32_t block_kth_largest_u32(const uint32_t* vals, 
   constexpr int kThr = 1024;
   const int n4 = (n + 3) >> 2, lane = tid & 63, wave = tid >> 6;
   const uint4* v4 = reinterpret_cast<const uint4*>(vals);
-  for (int i = tid; i < n; i += kThr) cnt[i] = 0;
+  if (tid < n) cnt[tid] = 0;
   __syncthreads();
-  if (n <= kThr) {                                                // uniform
-    const int P = kThr / n, part = tid / n, i = tid - part * n;
-    if (part < P) {
-      const int chunk = (n4 + P - 1) / P, lo = part * chunk, hi = min(n4, lo + chunk);
-      const uint32_t mine = vals[i];
-      int c = 0;
-      for (int q = lo; q < hi; ++q) c += count_larger4(v4[q], mine);
-      if (c != 0) atomicAdd(&cnt[i], c);
-    }
-  } else {
-    const uint32_t m0 = vals[tid], m1 = (tid + kThr < n) ? vals[tid + kThr] : 0xFFFFFFFFu;
-    int c0 = 0, c1 = 0;
-    for (int q = 0; q < n4; ++q) {
-      const uint4 v = v4[q];
-      c0 += count_larger4(v, m0);
-      c1 += count_larger4(v, m1);
-    }
-    cnt[tid] = c0;
-    if (tid + kThr < n) cnt[tid + kThr] = c1;
+  const int P = kThr / n, part = tid / n, i = tid - part * n;
+  if (part < P) {
+    const int chunk = (n4 + P - 1) / P, lo = part * chunk, hi = min(n4, lo + chunk);
+    const uint32_t mine = vals[i];
+    int c = 0;
+    for (int q = lo; q < hi; ++q) c += count_larger4(v4[q], mine);
+    if (c != 0) atomicAdd(&cnt[i], c);
   }
   __syncthreads();
   uint32_t least = 0xFFFFFFFFu;
-  for (int i = tid; i < n; i += kThr)
-    if (cnt[i] < k) least = min(least, vals[i]);
+  if (tid < n && cnt[tid] < k) least = vals[tid];
   least = ~wave_max_u32(~least);
   if (lane == 0) red[wave] = least;
   __syncthreads();

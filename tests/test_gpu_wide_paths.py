@@ -22,10 +22,10 @@ def _bits(torch, a):
 
 
 @pytest.mark.parametrize("k", [17, 64, 65, 100, 128])
-@pytest.mark.parametrize("V", [128, 2049, 8191, 65536, 65601, 131072])
+@pytest.mark.parametrize("V", [128, 2049, 8191, 32768, 32833, 65536, 65601, 131072])
 def test_wide_row_topk(gpu, k, V):
-    """Fewer groups than beams, up to 1024 groups (several threads per group), more (two groups per thread), ragged last
-    groups, duplicated rows: tokens from a stable sort of the very logits, exactly."""
+    """Fewer groups than beams, up to 512 groups (several threads per group), more (folded by two, from 1025 on by four), ragged
+    last groups, duplicated rows: tokens from a stable sort of the very logits, exactly."""
     torch, D = gpu
     print(f"[case] wide_row_topk k={k} V={V}", flush=True)
     H, R = 128, 5
