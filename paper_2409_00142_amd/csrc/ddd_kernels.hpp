@@ -59,9 +59,9 @@ enum GemmEpilogue {
   kGemmSiluPairs = 3     // rows of W come in (gate_i, up_i) pairs: out16[r][i] = bf16(silu(gate) * up); y unused
 };
 hipError_t prepare_lmhead_gemm();   // once per process: enables the kernels' LDS sizes
-// max_rows: the largest number of rows this call can have (picks the tile shape)
+// max_rows: the largest number of rows this call can have
 hipError_t launch_lmhead_gemm(const GemmArgs& a, int max_rows, int grid, hipStream_t stream);
-// The same kernel for a linear of the draft layer (N = a.V is a few thousand rows, not a vocabulary): the tile is a.split's
+// The same main loop for a linear of the draft layer (N = a.V is a few thousand rows, not a vocabulary): the tile is a.split's
 // (linear_shape, for calls of up to max_rows rows), the column tiles and K ranges are picked on the device.
 SplitShape linear_shape(int N, int K, int max_rows, int grid, int smax, long long cap);
 hipError_t launch_gemm_linear(const GemmArgs& a, int grid, hipStream_t stream);

@@ -50,4 +50,60 @@ __device__ __forceinline__ GemmPlan gemm_plan(const SplitShape& g, int n_act, in
   return p;
 }
 
+// How the LM head's GEMM is cut: row tiles of 128 or 256 rows of W, NT column tiles.
+struct HeadPlan {
+  int bm;    // rows of W per tile
+  int NT;    // column tiles
+  int bpt;   // most blocks of 32 active rows of one
+};
+struct HeadShape {
+  int V, kt, grid;
+  int most;     // most blocks of 32 active rows beside a 256-row tile
+  float row;    // ns in which the whole chip receives a k tile of one row of W (128 bytes) with 128-row tiles,
+  float row2;   // with 256-row tiles
+  HeadPlan known;   // the plan, where the number of rows is known before the launch (bm = 0: it is not)
+};
+// In ns, fitted to launches of 20 to 640 rows with V = 4000 to 128256 and H = 1024 to 4096: a k tile of a unit costs 240 and 22 per
+// 32 x 32 products (block columns in twos: two waves share them), or what its rows of W take to arrive - 1 us per 256 rows, which the
+// column tiles share, or the whole chip's rate -; the unit's ramp and epilogue 500 and 290 or 3500 and 200 per 32 x 32; the
+// workgroups take the units in passes.  Returns 0 where the combination does not exist.
+__host__ __device__ inline float head_price(const HeadShape& h, int n_act, int bm, int NT) {
+  const int nblk = (n_act + 31) >> 5, bpt = (int)((unsigned)(nblk + NT - 1) / (unsigned)NT);
+  if (NT > nblk || bpt > (bm == 256 ? h.most : 10)) return 0.f;                                    // tiles of at most 320 rows
+  const int nmt = bm == 256 ? (h.V + 255) >> 8 : (h.V + 127) >> 7, passes = (int)((unsigned)(nmt * NT + h.grid - 1) / (unsigned)h.grid);
+  const float each = 1.f / (float)NT;
+  const float area = (float)((bm >> 5) * ((bpt + 1) & ~1));
+  const float step = 240.f + 22.f * area, feed = 3.9f * (float)bm * each;
+  const float at_once = fminf((float)nmt, fmaxf((float)h.grid * each, 1.f));                       // row tiles in a pass
+  const float chip = at_once * (float)bm * (bm == 256 ? h.row2 : h.row);
+  return (float)passes * ((bm == 256 ? 3500.f + 200.f * area : 500.f + 290.f * area) + fmaxf(step, fmaxf(feed, chip)) * (float)h.kt);
+}
+inline HeadPlan head_plan_host(const HeadShape& h, int n_act) {
+  const int nblk = (n_act + 31) >> 5, least = (nblk + 9) / 10;
+  HeadPlan p = {0, 0, 0};
+  float best = 0.f;
+  for (int i = 0; i < 64; ++i) {
+    const int bm = i < 32 ? 128 : 256, NT = least + (i & 31);
+    const float price = head_price(h, n_act, bm, NT);
+    if (price > 0.f && (p.bm == 0 || price < best)) {
+      best = price;
+      p = HeadPlan{bm, NT, (nblk + NT - 1) / NT};
+    }
+  }
+  return p;
+}
+// The same by all 64 lanes of a wave, one result in every wave: lanes 0 .. 31 price 128-row tiles, the others 256-row tiles.
+__device__ __forceinline__ HeadPlan head_plan(const HeadShape& h, int n_act, int lane) {
+  if (h.known.bm != 0) return h.known;
+  const int nblk = (n_act + 31) >> 5, bm = lane < 32 ? 128 : 256, NT = (nblk + 9) / 10 + (lane & 31);
+  const float price = head_price(h, n_act, bm, NT);
+  const uint32_t key = price > 0.f ? ~__float_as_uint(price) : 0u;                                 // the order of positive floats
+  const int l = __ffsll((unsigned long long)__ballot(key == wave_max_u32(key))) - 1;
+  HeadPlan p;
+  p.bm = __builtin_amdgcn_readlane(bm, l);
+  p.NT = __builtin_amdgcn_readlane(NT, l);
+  p.bpt = (nblk + p.NT - 1) / p.NT;
+  return p;
+}
+
 }  // namespace ddd

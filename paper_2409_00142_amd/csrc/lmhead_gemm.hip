@@ -5,10 +5,17 @@
 // With hundreds of rows the projection is bound by the matrix cores, not by HBM, and on this chip
 // by what feeds them: a 64 x 64 wave tile needs one 1 KB fragment read per MFMA, which measured
 // LDS-bound at about a quarter of the MFMA peak.  The kernel therefore uses large wave tiles -
-// AB x BB blocks of v_mfma_f32_32x32x16_bf16 per wave, 2 x 2 waves per workgroup, 128 (vocabulary
-// rows) x 320 (hidden rows) per workgroup for hundreds of rows - which leaves no registers for
+// AB x BB blocks of v_mfma_f32_32x32x16_bf16 per wave, 2 x 2 waves per workgroup -, which leaves no registers for
 // per-row top-k lists; the fp32 logits of the active rows are written out (HBM has slack in this
 // regime) and a second kernel reduces each row (row_topk_kernel).
+//
+// Up to 320 hidden rows against a vocabulary whose 128-row tiles are no more than the workgroups: 128 x 320 at most (AB = 2).  More:
+// tiles of 256 rows of W (AB = 4, 128 x 160 per wave) in one pass over the workgroups instead of two, which copy a third less per
+// product and read a third less from LDS.  V = 32000, H = 4096, a ddd_lmhead_topk call: 330 rows 113 -> 100 us, 510 144 -> 131,
+// 640 168 -> 159.  What bounds it there is power: the loop runs at 1.36 PFLOP/s, the rate of a large square product on this card, and
+// the same launch with operands that are mostly zeros takes 25 us less (stores and statistics of the epilogue: 16 us).  Eight waves of 64 x 160
+// on that tile, two per SIMD: 157, but 96 us instead of 92 at 320 rows.  A vocabulary that leaves workgroups without a tile is cut
+// into more column tiles (V = 4000, 320 rows: 72 -> 32 us); how, is priced by head_plan (gemm_plan.hpp).
 //
 // W is the A operand, so an accumulator lane owns one hidden row and four consecutive vocabulary
 // rows per register quad: the output is stored as float4 along V.  Both operands reach LDS by
@@ -49,7 +56,10 @@ __device__ __forceinline__ uint32_t bf16_rne(float x) {   // finite inputs; the 
 template <int AB, int BB>
 struct GemmCfg {
   static constexpr int BM = 32 * AB * kWM, BN = 64 * BB;
-  static constexpr int kSA = (AB >= 3) ? 3 : 4, kSB = (BB >= 4) ? 2 : 3;   // ring depths, kSB <= kSA
+  // 256 rows of W x more than 128 hidden rows: the rings are two or three tiles deep, and a slot's copies are issued as soon as it
+  // is free
+  static constexpr bool kEarly = AB == 4 && BB >= 3;
+  static constexpr int kSA = kEarly && BB >= 5 ? 2 : (AB >= 3) ? 3 : 4, kSB = (BB >= 4 || kEarly) ? 2 : 3;   // ring depths, kSB <= kSA
   static constexpr int kABytes = BM * kRowB, kBBytes = BN * kRowB;
   static constexpr int kLdsBytes = kSA * kABytes + kSB * kBBytes;
   static constexpr int NAP = BM / 32, NBP = BN / 32;   // copy instructions per wave and tile (8 rows each)
@@ -58,6 +68,11 @@ struct GemmCfg {
 
 // Row of the n-th active row of the call.
 __device__ __forceinline__ int row_id(const GemmArgs& a, int n) { return a.row_list != nullptr ? a.row_list[n] : n; }
+
+// a += x y with the accumulators in VGPRs.
+__device__ __forceinline__ void mfma_vgpr(f32x16& a, const bf16x8& x, const bf16x8& y) {
+  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(a) : "v"(x), "v"(y));
+}
 
 // One work unit of one wave.  The column tile starts at active row tile_col0; this wave multiplies
 // NB blocks of 32 rows from block wblk0 of the tile on (0 <= NB <= BB; a wave with NB == 0 still
@@ -141,14 +156,21 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, unsigned char* ldsb
   // cannot issue its next MFMA either.
   constexpr int kLgkm0 = (7 << 4) | (0 << 8);     // lgkmcnt(0), expcnt free; the vmcnt bits are added
   constexpr int NM = AB * NBR;                    // MFMAs of a step
+  // 128 x 160 products of a wave are 320 accumulators: 256 in AGPRs, which is where the compiler keeps all that it allocates, and
+  // the last block column in VGPRs
+  constexpr int kAccCols = AB == 4 ? 4 : NBR;
+#define DDD_NOCOPY(T, STG, i)
 #define DDD_WAIT(VM) __builtin_amdgcn_s_waitcnt(kLgkm0 | ((VM) & 15) | (((VM) >> 4) << 14))
 #define DDD_STEP(AFN, BFN, SA, SB, OK, AFC, BFC, COPY, T, STG, I0, I1)                                         \
   if (NB > 0) {                                                                                                \
     DDD_READ(AFN, BFN, SA, SB, OK);                                                                            \
     __builtin_amdgcn_sched_barrier(0);                                                                         \
     _Pragma("unroll") for (int mi = 0; mi < NM; ++mi) {                                                        \
-      acc[mi % AB][mi / AB] =                                                                                  \
-          __builtin_amdgcn_mfma_f32_32x32x16_bf16(AFC[mi % AB], BFC[mi / AB], acc[mi % AB][mi / AB], 0, 0, 0); \
+      if (mi / AB < kAccCols)                                                                                  \
+        acc[mi % AB][mi / AB] =                                                                                \
+            __builtin_amdgcn_mfma_f32_32x32x16_bf16(AFC[mi % AB], BFC[mi / AB], acc[mi % AB][mi / AB], 0, 0, 0); \
+      else                                                                                                     \
+        mfma_vgpr(acc[mi % AB][mi / AB], AFC[mi % AB], BFC[mi / AB]);                                          \
       _Pragma("unroll") for (int ci = (I0); ci < (I1); ++ci) if (((ci - (I0)) * NM) / ((I1) - (I0)) == mi) {   \
         __builtin_amdgcn_sched_barrier(0);                                                                     \
         COPY(T, STG, ci);                                                                                      \
@@ -161,11 +183,16 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, unsigned char* ldsb
   }
   // Copy schedule.  The barrier of tile kt (in front of its last step) frees the ring slots of
   // tile kt; the hidden rows of tile kt+kSB go there during that last step and the first step of
-  // tile kt+1, the W rows of tile kt+kSA during the two middle steps of tile kt+1.  Behind the
+  // tile kt+1, the W rows of tile kt+kSA during the two middle steps of tile kt+1.  kEarly: one matrix during the last step, the
+  // other during the first one: the hidden rows first, so that a wait for them leaves the younger copies of W in flight, but
+  // W first where the rings are equally deep.  Behind the
   // copies of tile kt+1, which the wait of tile kt needs, each thread then has issued kInFlight more.
-  constexpr int NBa = NBP / 2, NAa = NAP / 2;
-  constexpr int kInFlight = (kSA - 2) * (NAP + NBP) < NAP + (kSB - 2) * (NAP + NBP) ? (kSA - 2) * (NAP + NBP)
-                                                                                      : NAP + (kSB - 2) * (NAP + NBP);
+  constexpr bool kEarly = C::kEarly, kEqual = kSA == kSB;
+  constexpr int P = NAP + NBP;
+  constexpr int NBa = kEarly ? (kEqual ? 0 : NBP) : NBP / 2, NAa = NAP / 2;
+  constexpr int kInFlight = kEarly && kEqual             ? (kSB - 2) * P
+                            : (kSA - 2) * P < NAP + (kSB - 2) * P ? (kSA - 2) * P
+                                                                  : NAP + (kSB - 2) * P;
   static_assert(kInFlight < 64, "vmcnt is a 6-bit counter");
   bf16x8 af0[AB], bf0[NBR], af1[AB], bf1[NBR];
   __syncthreads();            // every wave is done with the LDS tiles of the previous unit
@@ -181,6 +208,10 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, unsigned char* ldsb
   }
 #pragma unroll
   for (int i = 0; i < NBa; ++i) DDD_COPY_B(min(kSB - 1, KT - 1), kSB - 1, i);
+  if (kEarly && kEqual) {
+#pragma unroll
+    for (int i = 0; i < NAP; ++i) DDD_COPY_A(min(kSA - 1, KT - 1), kSA - 1, i);
+  }
   __builtin_amdgcn_s_waitcnt(DDD_VMCNT(0));       // all of it has landed: the static count below holds from tile 0 on
   __builtin_amdgcn_s_barrier();
   if (NB > 0) DDD_READ(af0, bf0, ldsA, ldsB, offk[0]);
@@ -192,18 +223,33 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, unsigned char* ldsb
     const unsigned char* pb = ldsB + sb * C::kBBytes;
     const int sa1 = (sa == kSA - 1) ? 0 : sa + 1, sb1 = (sb == kSB - 1) ? 0 : sb + 1;
     const int tb = min(kt + kSB - 1, KT - 1), ta = min(kt + kSA - 1, KT - 1);   // past the end: the last tile again
-    DDD_STEP(af1, bf1, pa, pb, offk[1], af0, bf0, DDD_COPY_B, tb, sbp, NBa, NBP);
+    if constexpr (kEarly && !kEqual) {
+      DDD_STEP(af1, bf1, pa, pb, offk[1], af0, bf0, DDD_COPY_A, ta, sap, 0, NAP);
+    } else {
+      DDD_STEP(af1, bf1, pa, pb, offk[1], af0, bf0, DDD_COPY_B, tb, sbp, NBa, NBP);
+    }
     DDD_WAIT(63);
-    DDD_STEP(af0, bf0, pa, pb, offk[2], af1, bf1, DDD_COPY_A, ta, sap, 0, NAa);
-    DDD_WAIT(63);
-    DDD_STEP(af1, bf1, pa, pb, offk[3], af0, bf0, DDD_COPY_A, ta, sap, NAa, NAP);
+    if constexpr (kEarly) {
+      DDD_STEP(af0, bf0, pa, pb, offk[2], af1, bf1, DDD_NOCOPY, 0, 0, 0, 0);
+      DDD_WAIT(63);
+      DDD_STEP(af1, bf1, pa, pb, offk[3], af0, bf0, DDD_NOCOPY, 0, 0, 0, 0);
+    } else {
+      DDD_STEP(af0, bf0, pa, pb, offk[2], af1, bf1, DDD_COPY_A, ta, sap, 0, NAa);
+      DDD_WAIT(63);
+      DDD_STEP(af1, bf1, pa, pb, offk[3], af0, bf0, DDD_COPY_A, ta, sap, NAa, NAP);
+    }
     // every read of tile kt is back; this thread's copies of tile kt+1 have landed ...
     DDD_WAIT(kInFlight);
     // ... and everybody's; everybody is done with the slots of tile kt, which the next copies overwrite
     // (a plain barrier: __syncthreads() would wait for every load in flight)
     __builtin_amdgcn_s_barrier();
-    DDD_STEP(af0, bf0, ldsA + sa1 * C::kABytes, ldsB + sb1 * C::kBBytes, offk[0], af1, bf1, DDD_COPY_B,
-             min(kt + kSB, KT - 1), sb, 0, NBa);
+    if constexpr (kEarly && kEqual) {
+      DDD_STEP(af0, bf0, ldsA + sa1 * C::kABytes, ldsB + sb1 * C::kBBytes, offk[0], af1, bf1, DDD_COPY_A,
+               min(kt + kSA, KT - 1), sa, 0, NAP);
+    } else {
+      DDD_STEP(af0, bf0, ldsA + sa1 * C::kABytes, ldsB + sb1 * C::kBBytes, offk[0], af1, bf1, DDD_COPY_B,
+               min(kt + kSB, KT - 1), sb, 0, NBa);
+    }
     DDD_WAIT(63);
     sap = sa;
     sbp = sb;
@@ -211,7 +257,10 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, unsigned char* ldsb
     sb = sb1;
   }
   __builtin_amdgcn_s_waitcnt(DDD_VMCNT(0));   // the copies past the end have landed before the LDS is reused
+  if constexpr (AB == 4 && NBR > kAccCols)    // the last products written in asm have landed before anything reads them
+    asm volatile("s_nop 15\n\ts_nop 15" : "+v"(acc[0][4]), "+v"(acc[1][4]), "+v"(acc[2][4]), "+v"(acc[3][4]));
 #undef DDD_STEP
+#undef DDD_NOCOPY
 #undef DDD_WAIT
 #undef DDD_READ
 #undef DDD_VMCNT
@@ -315,7 +364,7 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, unsigned char* ldsb
   }
 }
 
-// All work units of one workgroup for column tiles of at most 64 * BB rows.  The blocks of 32
+// All work units of one workgroup for column tiles of 64 * BB - 32 or 64 * BB rows, or one block of 32 less.  The blocks of 32
 // active rows are dealt evenly: to the column tiles, and inside a tile to the two waves along the
 // hidden rows, so that 400 active rows cost 7 + 6 blocks in two tiles of (4, 3) and (3, 3) per
 // wave pair instead of 10 + 3 in tiles of (5, 5) and (3, 0).
@@ -331,45 +380,25 @@ __device__ __forceinline__ void gemm_units(const GemmArgs& a, unsigned char* lds
   const int G = gridDim.x;
   const int vg = (blockIdx.x & 7) * (G >> 3) + (blockIdx.x >> 3);   // neighbours on one XCD get neighbouring units
 
+  const int each = bpt * NT == nblk_all ? bpt : bpt - 1, more = nblk_all - each * NT;
   for (int u = vg; u < nunits; u += G) {
-    const int ms = u / NT, nt = u - ms * NT;
+    const int ms = NT == 1 ? u : u / NT, nt = u - ms * NT;
     const int mu = LIN ? ms / S : ms, split = ms - mu * S;
     const int mt = a.reverse ? nmt - 1 - mu : mu;   // consecutive calls walk W in opposite directions (memory-side cache)
-    const int nblk = min(bpt, nblk_all - nt * bpt);  // >= 1
+    const int blk0 = nt * each + min(nt, more), nblk = each + (nt < more ? 1 : 0);   // bpt or bpt - 1, >= 1
     const int h0 = (nblk + 1) >> 1;
-    const int wblk0 = wn ? h0 : 0, nb = wn ? nblk - h0 : h0;   // wave-uniform
-    const int tc0 = nt * bpt * 32;
-    switch (nb) {
-      case 0: gemm_unit<AB, BB, 0, LIN>(a, lds, mt, tc0, wblk0, n_act, split, S, tid, wm, l32, lh); break;
-      case 1: gemm_unit<AB, BB, 1, LIN>(a, lds, mt, tc0, wblk0, n_act, split, S, tid, wm, l32, lh); break;
-      case 2: gemm_unit<AB, BB, (BB >= 2 ? 2 : BB), LIN>(a, lds, mt, tc0, wblk0, n_act, split, S, tid, wm, l32, lh); break;
-      case 3: gemm_unit<AB, BB, (BB >= 3 ? 3 : BB), LIN>(a, lds, mt, tc0, wblk0, n_act, split, S, tid, wm, l32, lh); break;
-      case 4: gemm_unit<AB, BB, (BB >= 4 ? 4 : BB), LIN>(a, lds, mt, tc0, wblk0, n_act, split, S, tid, wm, l32, lh); break;
-      default: gemm_unit<AB, BB, BB, LIN>(a, lds, mt, tc0, wblk0, n_act, split, S, tid, wm, l32, lh); break;
-    }
+    const int wblk0 = wn ? h0 : 0, nb = wn ? nblk - h0 : h0;   // wave-uniform: BB or BB - 1, as bpt is 2 BB or 2 BB - 1
+    if (nb == BB)
+      gemm_unit<AB, BB, BB, LIN>(a, lds, mt, blk0 * 32, wblk0, n_act, split, S, tid, wm, l32, lh);
+    else
+      gemm_unit<AB, BB, BB - 1, LIN>(a, lds, mt, blk0 * 32, wblk0, n_act, split, S, tid, wm, l32, lh);
   }
 }
 
-// BB is the widest column tile the launch may need (64 * BB rows per workgroup).  The number of
-// active rows is only known on the device, so the kernel picks the column tiling itself: as few
-// tiles as BB allows, the blocks dealt evenly to them, and the narrowest tile that holds a share
-// (with 64 active rows a 320-row tile would still copy 320 repeated rows per K tile through LDS).  LIN: a linear of the
-// draft layer (column tiles and K ranges by gemm_plan, the other epilogues) instead of the LM head.
+// The column tiles are as narrow as the largest share of the active rows allows (with 64 active rows a 320-row tile would still
+// copy 320 repeated rows per K tile through LDS), and at most 64 * BB rows.
 template <int AB, int BB, bool LIN>
-__global__ __launch_bounds__(256, 1) void lmhead_gemm_kernel(GemmArgs a) {
-  extern __shared__ __align__(16) unsigned char lds[];     // the two tile rings of the chosen width
-
-  const int n_act = a.row_list != nullptr ? *a.n_act_ptr : a.n_rows;
-  if (n_act <= 0) return;                                  // uniform
-  const int nblk_all = (n_act + 31) >> 5;
-  int NT = (nblk_all + 2 * BB - 1) / (2 * BB), S = 1;
-  int bpt = (nblk_all + NT - 1) / NT;                      // blocks per column tile, <= 2 * BB
-  if (LIN) {
-    const GemmPlan p = gemm_plan(a.split, n_act, threadIdx.x & 63);
-    NT = p.NT;
-    bpt = p.bpt;
-    S = p.S;
-  }
+__device__ __forceinline__ void gemm_widths(const GemmArgs& a, unsigned char* lds, int n_act, int NT, int bpt, int S) {
   const int bb = (bpt + 1) >> 1;                           // blocks per wave, <= BB
   if (BB >= 5 && bb >= 5)
     gemm_units<AB, (BB >= 5 ? 5 : BB), LIN>(a, lds, n_act, NT, bpt, S);
@@ -381,6 +410,32 @@ __global__ __launch_bounds__(256, 1) void lmhead_gemm_kernel(GemmArgs a) {
     gemm_units<AB, (BB >= 2 ? 2 : BB), LIN>(a, lds, n_act, NT, bpt, S);
   else
     gemm_units<AB, 1, LIN>(a, lds, n_act, NT, bpt, S);
+}
+
+// Inside a round the number of active rows is only known on the device, so the kernels pick their tiles themselves.  WIDE: 256-row tiles of W for
+// more than 128 hidden rows may be among them (accumulators in every register of a wave).
+template <bool WIDE>
+__global__ __launch_bounds__(256, 1) void lmhead_gemm_kernel(GemmArgs a, HeadShape h) {
+  extern __shared__ __align__(16) unsigned char lds[];     // the two tile rings of the chosen width
+
+  const int n_act = a.row_list != nullptr ? *a.n_act_ptr : a.n_rows;
+  if (n_act <= 0) return;                                  // uniform
+  const HeadPlan p = head_plan(h, n_act, threadIdx.x & 63);
+  if (p.bm == 256)
+    gemm_widths<4, (WIDE ? 5 : 2), false>(a, lds, n_act, p.NT, p.bpt, 1);
+  else
+    gemm_widths<2, 5, false>(a, lds, n_act, p.NT, p.bpt, 1);
+}
+
+// A linear of the draft layer: column tiles and K ranges by gemm_plan, the other epilogues.
+template <int AB, int BB>
+__global__ __launch_bounds__(256, 1) void linear_gemm_kernel(GemmArgs a) {
+  extern __shared__ __align__(16) unsigned char lds[];
+
+  const int n_act = a.row_list != nullptr ? *a.n_act_ptr : a.n_rows;
+  if (n_act <= 0) return;                                  // uniform
+  const GemmPlan p = gemm_plan(a.split, n_act, threadIdx.x & 63);
+  gemm_widths<AB, BB, true>(a, lds, n_act, p.NT, p.bpt, p.S);
 }
 
 // ---- tile-major copy of W ------------------------------------------------------------------------
@@ -436,40 +491,31 @@ hipError_t launch_build_row_list(const uint8_t* row_active, int n_rows, int32_t*
   return hipGetLastError();
 }
 
-// Tile shape by the largest number of rows the call can have: 128 x 320 for hundreds of rows,
-// smaller column tiles when fewer rows can be active.  (Eight waves on a 256 x 320 tile measured
-// a tenth faster with all 640 rows active, but leave half of the CUs idle once fewer than 321
-// rows are active, which is most draft calls of a round; four waves on that tile spill.)
-// With at most 128 rows and a vocabulary large enough to give every CU a unit, 256 vocabulary rows per
-// workgroup (128 x 64 wave tiles) cut the LDS and L2 traffic per MFMA by a quarter.
-static int pick_shape(int max_rows, int V, int grid) {
-  if (max_rows > 192) return 1;
-  if (max_rows > 128) return 2;
-  return ((V + 255) / 256 >= grid) ? 4 : 3;
-}
-
-template <int AB, int BB, bool LIN>
+template <int AB, int BB>
 static hipError_t prepare_shape() {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&lmhead_gemm_kernel<AB, BB, LIN>),
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&linear_gemm_kernel<AB, BB>),
                              hipFuncAttributeMaxDynamicSharedMemorySize, GemmCfg<AB, BB>::kLdsBytes);
 }
 
+constexpr int kHeadLds = 160 * 1024;
+
 hipError_t prepare_lmhead_gemm() {
-  hipError_t e = prepare_shape<2, 5, false>();
-  if (e == hipSuccess) e = prepare_shape<2, 3, false>();
-  if (e == hipSuccess) e = prepare_shape<2, 2, false>();
-  if (e == hipSuccess) e = prepare_shape<4, 2, false>();
-  if (e == hipSuccess) e = prepare_shape<3, 5, true>();
-  if (e == hipSuccess) e = prepare_shape<2, 5, true>();
-  if (e == hipSuccess) e = prepare_shape<2, 3, true>();
-  if (e == hipSuccess) e = prepare_shape<2, 2, true>();
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&lmhead_gemm_kernel<false>),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, kHeadLds);
+  if (e == hipSuccess)
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&lmhead_gemm_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            kHeadLds);
+  if (e == hipSuccess) e = prepare_shape<3, 5>();
+  if (e == hipSuccess) e = prepare_shape<2, 5>();
+  if (e == hipSuccess) e = prepare_shape<2, 3>();
+  if (e == hipSuccess) e = prepare_shape<2, 2>();
   return e;
 }
 
-template <int AB, int BB, bool LIN>
+template <int AB, int BB>
 static void launch_shape(const GemmArgs& a, int grid, hipStream_t stream) {
   constexpr int lds_bytes = GemmCfg<AB, BB>::kLdsBytes;
-  hipLaunchKernelGGL((lmhead_gemm_kernel<AB, BB, LIN>), dim3(grid), dim3(256), lds_bytes, stream, a);
+  hipLaunchKernelGGL((linear_gemm_kernel<AB, BB>), dim3(grid), dim3(256), lds_bytes, stream, a);
 }
 
 // 128 rows of W per tile, or 192 where that is cheaper: fewer copies and fragment reads per MFMA, and with hundreds of
@@ -494,23 +540,37 @@ SplitShape linear_shape(int N, int K, int max_rows, int grid, int smax, long lon
 
 hipError_t launch_gemm_linear(const GemmArgs& a, int grid, hipStream_t stream) {
   if (a.split.ab == 3)
-    launch_shape<3, 5, true>(a, grid, stream);
+    launch_shape<3, 5>(a, grid, stream);
   else if (a.split.bbmax == 5)
-    launch_shape<2, 5, true>(a, grid, stream);
+    launch_shape<2, 5>(a, grid, stream);
   else if (a.split.bbmax == 3)
-    launch_shape<2, 3, true>(a, grid, stream);
+    launch_shape<2, 3>(a, grid, stream);
   else
-    launch_shape<2, 2, true>(a, grid, stream);
+    launch_shape<2, 2>(a, grid, stream);
   return hipGetLastError();
 }
 
 hipError_t launch_lmhead_gemm(const GemmArgs& a, int max_rows, int grid, hipStream_t stream) {
-  switch (pick_shape(max_rows, a.V, grid)) {
-    case 1: launch_shape<2, 5, false>(a, grid, stream); break;
-    case 2: launch_shape<2, 3, false>(a, grid, stream); break;
-    case 4: launch_shape<4, 2, false>(a, grid, stream); break;
-    default: launch_shape<2, 2, false>(a, grid, stream); break;
-  }
+  HeadShape h;
+  h.V = a.V;
+  h.kt = a.H / kGK;
+  h.grid = grid;
+  // W that the memory-side cache holds in good part, or its tile-major copy, arrives at 6.5 TB/s; rows 8 KB apart from HBM at 3.9, and
+  // 256 of them per tile slower still (V = 128256, H = 4096, 320 rows: 389 us with 128-row tiles, 422 with 256-row tiles)
+  const bool fast = a.Wp != nullptr || (size_t)a.V * a.H * sizeof(uint16_t) <= (size_t)320 << 20;
+  h.row = fast ? 128.f / 6500.f : 128.f / 3900.f;
+  h.row2 = fast ? 128.f / 6500.f : 128.f / 3400.f;
+  h.most = 10;
+  h.known = HeadPlan{0, 0, 0};
+  if (a.row_list == nullptr) h.known = head_plan_host(h, a.n_rows);
+  // Two kernels, because the wide tiles' registers cost every launch of the one that has them 1 us: up to 320 rows it is only taken
+  // where 128-row tiles would need several passes over the workgroups.
+  const bool wide = a.row_list == nullptr ? h.known.bm == 256 && h.known.bpt > 4 : max_rows > 320 || (max_rows > 128 && (a.V + 127) / 128 > grid);
+  if (!wide) h.most = 4;
+  if (!wide)
+    hipLaunchKernelGGL(lmhead_gemm_kernel<false>, dim3(grid), dim3(256), kHeadLds, stream, a, h);
+  else
+    hipLaunchKernelGGL(lmhead_gemm_kernel<true>, dim3(grid), dim3(256), kHeadLds, stream, a, h);
   return hipGetLastError();
 }
 
