@@ -225,7 +225,9 @@ struct VerifySampleArgs {
   float temperature;
   int B, m, D, V;
   void* rows;                    // null, or scratch of verify_sample_row_bytes() per row of logits: the sums of all rows first
-  int parts;                     // of every row's sums (set by the launcher)
+  // set by the launcher:
+  int parts;                     // of every row's sums
+  double beta2, span;            // log2(e) / T, and the difference of two logits whose weights differ by 2^1000
 };
 size_t verify_sample_row_bytes();
 hipError_t launch_verify_sample(VerifySampleArgs a, hipStream_t stream);

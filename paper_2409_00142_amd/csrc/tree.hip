@@ -107,9 +107,10 @@ hipError_t launch_verify_accept(const VerifyArgs& a, hipStream_t stream) {
 // The walk is a chain - which row is next depends on the decision at this one - and a row of 32 000 fp64 exponentials
 // keeps one CU busy for about 8 us, so the two ways of doing it differ in where the rows' sums are made:
 //  * small batches (verify_sample_from_sums): a first launch makes the sums of every row of every tree with the whole
-//    chip (23 us for 62 MB: fp64 issue, 8 cycles an instruction), and the walk that follows looks numbers up: B = 8, V = 32000,
-//    61 nodes, 41 to 65 us a call by the depth of the accepted paths -> 30 us, B = 1 24 to 37 -> 15 us.  It reads m + 1 rows per
-//    sequence instead of two or three.
+//    chip (20 us for 62 MB, of which the memory takes 12; 23 with the long form of the exponential), and the walk that follows
+//    looks numbers up: B = 8, V = 32000, 61 nodes, 41 to 65 us a call by the depth of the accepted paths -> 27 us, B = 1 24 to 37
+//    -> 12.6 us.  It reads m + 1 rows per sequence instead of two or three.  (Workgroups of twice and four times the blocks, which
+//    issue a tenth less per token: 31 and 36 us, because all of the loads then come before all of the arithmetic.)
 //  * beyond that (verify_sample_kernel): one workgroup of 16 waves per sequence makes the sums of the rows it visits.
 // The line lies where the extra rows would cost what they save (rows_from_sums).
 constexpr int kVsWaves = 16;
@@ -141,10 +142,83 @@ __device__ __forceinline__ double weight_of(double d, double beta2) {
   p = fma(p, f, 1.0);
   return ldexp(p, (int)n);
 }
-__device__ __forceinline__ double weight4(const float4& v, double Md, double beta2) {
+// The same for the rows' sums, in 10 fp64 instructions instead of 19: 2^t = 2^(n/128) 2^f with |f| <= 1/256, where adding
+// 1.5 * 2^45 leaves n in the low word, the 128 values of 2^(j/128) sit in LDS and 2^f - 1 is f times a cubic through the Chebyshev
+// nodes (1.5e-16 with the rounding of its coefficients).  f takes one rounding (t is never rounded), so a weight is closer to the
+// exact one than above.  B = 8, V = 32000, 61 nodes: 30.5 -> 27.1 us a call with the constants of T made by the host and the rows'
+// loads in front of the look at the tree's size; B = 16 49.8 -> 42.9.  The high words of the table are less by j << 13, so that adding n << 13 puts the integer part of n / 128 into
+// the exponent field.  For t in (-1021, 0].
+constexpr int kVsExpSize = 128;
+__device__ const unsigned long long kVsExp[kVsExpSize] = {
+    0x3ff0000000000000ull, 0x3feff63da9fb3335ull, 0x3fefec9a3e778061ull, 0x3fefe315e86e7f85ull,
+    0x3fefd9b0d3158574ull, 0x3fefd06b29ddf6deull, 0x3fefc74518759bc8ull, 0x3fefbe3ecac6f383ull,
+    0x3fefb5586cf9890full, 0x3fefac922b7247f7ull, 0x3fefa3ec32d3d1a2ull, 0x3fef9b66affed31bull,
+    0x3fef9301d0125b51ull, 0x3fef8abdc06c31ccull, 0x3fef829aaea92de0ull, 0x3fef7a98c8a58e51ull,
+    0x3fef72b83c7d517bull, 0x3fef6af9388c8deaull, 0x3fef635beb6fcb75ull, 0x3fef5be084045cd4ull,
+    0x3fef54873168b9aaull, 0x3fef4d5022fcd91dull, 0x3fef463b88628cd6ull, 0x3fef3f49917ddc96ull,
+    0x3fef387a6e756238ull, 0x3fef31ce4fb2a63full, 0x3fef2b4565e27cddull, 0x3fef24dfe1f56381ull,
+    0x3fef1e9df51fdee1ull, 0x3fef187fd0dad990ull, 0x3fef1285a6e4030bull, 0x3fef0cafa93e2f56ull,
+    0x3fef06fe0a31b715ull, 0x3fef0170fc4cd831ull, 0x3feefc08b26416ffull, 0x3feef6c55f929ff1ull,
+    0x3feef1a7373aa9cbull, 0x3feeecae6d05d866ull, 0x3feee7db34e59ff7ull, 0x3feee32dc313a8e5ull,
+    0x3feedea64c123422ull, 0x3feeda4504ac801cull, 0x3feed60a21f72e2aull, 0x3feed1f5d950a897ull,
+    0x3feece086061892dull, 0x3feeca41ed1d0057ull, 0x3feec6a2b5c13cd0ull, 0x3feec32af0d7d3deull,
+    0x3feebfdad5362a27ull, 0x3feebcb299fddd0dull, 0x3feeb9b2769d2ca7ull, 0x3feeb6daa2cf6642ull,
+    0x3feeb42b569d4f82ull, 0x3feeb1a4ca5d920full, 0x3feeaf4736b527daull, 0x3feead12d497c7fdull,
+    0x3feeab07dd485429ull, 0x3feea9268a5946b7ull, 0x3feea76f15ad2148ull, 0x3feea5e1b976dc09ull,
+    0x3feea47eb03a5585ull, 0x3feea34634ccc320ull, 0x3feea23882552225ull, 0x3feea155d44ca973ull,
+    0x3feea09e667f3bcdull, 0x3feea012750bdabfull, 0x3fee9fb23c651a2full, 0x3fee9f7df9519484ull,
+    0x3fee9f75e8ec5f74ull, 0x3fee9f9a48a58174ull, 0x3fee9feb564267c9ull, 0x3feea0694fde5d3full,
+    0x3feea11473eb0187ull, 0x3feea1ed0130c132ull, 0x3feea2f336cf4e62ull, 0x3feea427543e1a12ull,
+    0x3feea589994cce13ull, 0x3feea71a4623c7adull, 0x3feea8d99b4492edull, 0x3feeaac7d98a6699ull,
+    0x3feeace5422aa0dbull, 0x3feeaf3216b5448cull, 0x3feeb1ae99157736ull, 0x3feeb45b0b91ffc6ull,
+    0x3feeb737b0cdc5e5ull, 0x3feeba44cbc8520full, 0x3feebd829fde4e50ull, 0x3feec0f170ca07baull,
+    0x3feec49182a3f090ull, 0x3feec86319e32323ull, 0x3feecc667b5de565ull, 0x3feed09bec4a2d33ull,
+    0x3feed503b23e255dull, 0x3feed99e1330b358ull, 0x3feede6b5579fdbfull, 0x3feee36bbfd3f37aull,
+    0x3feee89f995ad3adull, 0x3feeee07298db666ull, 0x3feef3a2b84f15fbull, 0x3feef9728de5593aull,
+    0x3feeff76f2fb5e47ull, 0x3fef05b030a1064aull, 0x3fef0c1e904bc1d2ull, 0x3fef12c25bd71e09ull,
+    0x3fef199bdd85529cull, 0x3fef20ab5fffd07aull, 0x3fef27f12e57d14bull, 0x3fef2f6d9406e7b5ull,
+    0x3fef3720dcef9069ull, 0x3fef3f0b555dc3faull, 0x3fef472d4a07897cull, 0x3fef4f87080d89f2ull,
+    0x3fef5818dcfba487ull, 0x3fef60e316c98398ull, 0x3fef69e603db3285ull, 0x3fef7321f301b460ull,
+    0x3fef7c97337b9b5full, 0x3fef864614f5a129ull, 0x3fef902ee78b3ff6ull, 0x3fef9a51fbc74c83ull,
+    0x3fefa4afa2a490daull, 0x3fefaf482d8e67f1ull, 0x3fefba1bee615a27ull, 0x3fefc52b376bba97ull,
+    0x3fefd0765b6e4540ull, 0x3fefdbfdad9cbe14ull, 0x3fefe7c1819e90d8ull, 0x3feff3c22b8f71f1ull,
+};
+__device__ __forceinline__ void load_exp_table(double* table, int tid) {
+  if (tid < kVsExpSize) table[tid] = __longlong_as_double((long long)kVsExp[tid]);
+}
+__device__ __forceinline__ double add_weight(double acc, double d, double beta2, const double* table) {
+  constexpr double kMagic = 52776558133248.0;   // 1.5 * 2^45: one unit in the last place is 1/128
+  const double s = fma(d, beta2, kMagic);
+  const int n = __double2loint(s);
+  const double base = table[n & (kVsExpSize - 1)];
+  const double f = fma(d, beta2, -(s - kMagic));
+  double p = 0.009618131458021427;
+  p = fma(p, f, 0.05550412901022388);
+  p = fma(p, f, 0.24022650695909623);
+  p = fma(p, f, 0.6931471805599065);
+  p = fma(p, f, 1.0);
+  return fma(__hiloint2double(__double2hiint(base) + (n << 13), __double2loint(base)), p, acc);
+}
+// Logits from which on the short form holds (weights of 2^-1000 and more); NaN, which no logit reaches, below an infinite maximum.
+__device__ __forceinline__ float short_from(double Md, double span) {
+  const double lo = fmax(Md - span, -3.4028234663852886e38);
+  float f = (float)lo;
+  if ((double)f < lo) f = nextafterf(f, __builtin_inff());
+  return f + (float)(Md - Md);
+}
+// acc and the weights of four tokens; by whole waves.
+__device__ __forceinline__ double add_weight4(double acc, const float4& v, double Md, double beta2, float from, const double* table) {
+  if (__ballot(!(v.x >= from && v.y >= from && v.z >= from && v.w >= from)) == 0ull) {
+    acc = add_weight(acc, (double)v.x - Md, beta2, table);
+    acc = add_weight(acc, (double)v.y - Md, beta2, table);
+    acc = add_weight(acc, (double)v.z - Md, beta2, table);
+    return add_weight(acc, (double)v.w - Md, beta2, table);
+  }
+  const float ninf = -__builtin_inff();
+  if (__ballot(v.x != ninf || v.y != ninf || v.z != ninf || v.w != ninf) == 0ull) return acc;   // past the vocabulary
   const double e0 = weight_of((double)v.x - Md, beta2), e1 = weight_of((double)v.y - Md, beta2);
   const double e2 = weight_of((double)v.z - Md, beta2), e3 = weight_of((double)v.w - Md, beta2);
-  return (e0 + e1) + (e2 + e3);
+  return acc + ((e0 + e1) + (e2 + e3));
 }
 
 __device__ __forceinline__ double wave_scan_f64(double x, int lane) {   // inclusive prefix over the lanes
@@ -197,7 +271,7 @@ __device__ __forceinline__ int chunks_per_block(int V) { return (V + kVsSub * kV
 __device__ __forceinline__ bool rows_aligned(const VerifySampleArgs& a) {
   return (a.V & 3) == 0 && (reinterpret_cast<uintptr_t>(a.logits) & 15) == 0;
 }
-__device__ __forceinline__ double beta2_of(const VerifySampleArgs& a) { return 1.4426950408889634 / (double)a.temperature; }
+__device__ __forceinline__ double beta2_of(const VerifySampleArgs& a) { return a.beta2; }
 
 // The sequence's tree, read once, and the tokens rejected at the current node.
 struct VsTree {
@@ -328,13 +402,14 @@ __device__ __forceinline__ int last_resort(const VsTree& t, int nrm, const float
 // ---- one workgroup per sequence makes the sums of the rows it visits --------------------------------------------
 __global__ __launch_bounds__(kVsThreads) void verify_sample_kernel(VerifySampleArgs a) {
   __shared__ float s_max[kVsWaves];
-  __shared__ double s_sub[kVsSub];
+  __shared__ double s_sub[kVsSub], s_exp[kVsExpSize];
   __shared__ VsTree t;
   __shared__ int s_next, s_nrm, s_bonus;
 
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int T = a.m + 1, V = a.V;
   load_tree(a, b, tid, t);
+  load_exp_table(s_exp, tid);
   const int n = min(a.tree.n_sel[b], a.m) + 1;
   StatsPre sp{0, 0u};
   if (tid == 0) sp = stats_begin(a.stats, b, a.B);
@@ -368,6 +443,7 @@ __global__ __launch_bounds__(kVsThreads) void verify_sample_kernel(VerifySampleA
 #pragma unroll
     for (int i = 1; i < kVsWaves; ++i) mx = fmaxf(mx, s_max[i]);
     Md = (double)mx;
+    const float from = short_from(Md, a.span);
     // weights: one sum per block of sb consecutive tokens, in a fixed order
 #pragma unroll 1
     for (int i0 = 0; i0 < kVsSubPerWave; i0 += 4) {
@@ -375,7 +451,8 @@ __global__ __launch_bounds__(kVsThreads) void verify_sample_kernel(VerifySampleA
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         double acc = 0.0;
-        for (int c = 0; c < cpb; ++c) acc += weight4(load_logits4(x, j0 + ((i0 + i) * cpb + c) * kVsChunk, V, vec), Md, beta2);
+        for (int c = 0; c < cpb; ++c)
+          acc = add_weight4(acc, load_logits4(x, j0 + ((i0 + i) * cpb + c) * kVsChunk, V, vec), Md, beta2, from, s_exp);
         sums[i] = acc;
       }
       const double sum = wave_sums_f64<4>(sums, lane);
@@ -450,10 +527,10 @@ size_t verify_sample_row_bytes() { return sizeof(VsRow); }
 template <int CPB>
 __global__ __launch_bounds__(kVsPartWaves * kWave) void verify_row_sums_kernel(VerifySampleArgs a) {
   __shared__ float s_max[kVsPartWaves];
-  __shared__ double s_sub[kVsPartSub];
+  __shared__ double s_sub[kVsPartSub], s_exp[kVsExpSize];
   const int part = blockIdx.x, i = blockIdx.y, b = blockIdx.z, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int T = a.m + 1, V = a.V;
-  if (i > min(a.tree.n_sel[b], a.m)) return;                              // uniform: not a node of the tree
+  const int n_sel = a.tree.n_sel[b];                                      // looked at behind the loads of the row
   const float* x = a.logits + ((size_t)b * T + i) * V;
   VsRow* out = static_cast<VsRow*>(a.rows) + (size_t)b * T + i;
   const int cpb = CPB > 0 ? CPB : chunks_per_block(V);
@@ -469,6 +546,9 @@ __global__ __launch_bounds__(kVsPartWaves * kWave) void verify_row_sums_kernel(V
     for (int q = 0; q < kVsPartPerWave; ++q)
 #pragma unroll
       for (int c = 0; c < kKeep; ++c) xv[q][c] = load_logits4(x, j0 + (q * kKeep + c) * kVsChunk, V, vec);
+  }
+  if (i > min(n_sel, a.m)) return;                                        // uniform: not a node of the tree
+  if (CPB > 0) {
 #pragma unroll
     for (int q = 0; q < kVsPartPerWave; ++q)
 #pragma unroll
@@ -479,19 +559,22 @@ __global__ __launch_bounds__(kVsPartWaves * kWave) void verify_row_sums_kernel(V
   }
   mx = wave_max_f32(mx);
   if (lane == 0) s_max[wv] = mx;
+  load_exp_table(s_exp, tid);
   __syncthreads();
   mx = fmaxf(fmaxf(s_max[0], s_max[1]), fmaxf(s_max[2], s_max[3]));
   const bool none = mx == -__builtin_inff();                              // nothing but -inf, or past the vocabulary: no weight
   const double Md = none ? 0.0 : (double)mx;
+  const float from = short_from(Md, a.span);
   double sums[kVsPartPerWave];
 #pragma unroll
   for (int q = 0; q < kVsPartPerWave; ++q) {
     double acc = 0.0;
     if (CPB > 0) {
 #pragma unroll
-      for (int c = 0; c < kKeep; ++c) acc += weight4(xv[q][c], Md, beta2);
+      for (int c = 0; c < kKeep; ++c) acc = add_weight4(acc, xv[q][c], Md, beta2, from, s_exp);
     } else {
-      for (int c = 0; c < cpb; ++c) acc += weight4(load_logits4(x, j0 + (q * cpb + c) * kVsChunk, V, vec), Md, beta2);
+      for (int c = 0; c < cpb; ++c)
+        acc = add_weight4(acc, load_logits4(x, j0 + (q * cpb + c) * kVsChunk, V, vec), Md, beta2, from, s_exp);
     }
     sums[q] = acc;
   }
@@ -602,6 +685,8 @@ __global__ __launch_bounds__(kVsWalkThreads) void verify_sample_from_sums_kernel
 
 hipError_t launch_verify_sample(VerifySampleArgs a, hipStream_t stream) {
   if (a.m > DDD_MMAX) return hipErrorInvalidValue;      // the kernels keep the tree in LDS
+  a.beta2 = 1.4426950408889634 / (double)a.temperature;
+  a.span = 1000.0 / a.beta2;
   const int cpb = (a.V + kVsSub * kVsChunk - 1) / (kVsSub * kVsChunk);   // chunks of 256 tokens per block
   if (a.rows != nullptr) {
     a.parts = vs_parts(a.V);
