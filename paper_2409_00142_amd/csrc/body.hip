@@ -35,6 +35,16 @@ __device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __uint_as_floa
 typedef u32x4 u32x4_of_halves __attribute__((aligned(2)));   // the caller's prompt values start on any element,
 typedef f32x4 f32x4_of_floats __attribute__((aligned(4)));   // its norm weights on any float
 
+// LDS is exchanged, loads from global memory stay in flight (__syncthreads() would wait for them).
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// Output rows n0 .. n1 - 1 of a weight stream's workgroup: dealt in units of 4.
+__device__ __forceinline__ void slice_rows(int N, int nslice, int slice, int& n0, int& n1) {
+  const int nq = (N + 3) >> 2;
+  n0 = (int)(((long long)slice * nq) / nslice) * 4;
+  n1 = min((int)(((long long)(slice + 1) * nq) / nslice) * 4, N);
+}
+
 // ---- y (+)= x W^T ----------------------------------------------------------------------------
 // MULTI: several K ranges, the last of any number of units; otherwise one whole range, and the input rows stay in registers
 // for the whole kernel.
@@ -44,21 +54,18 @@ __global__ __launch_bounds__(704) void linear_stream_kernel(LinearArgs a) {
   const int NW = a.nw;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
 
-  if (a.row_active != nullptr) {   // uniform
-    const int on = (lane < a.R) ? a.row_active[lane] : 0;
-    if (__ballot(on != 0) == 0ull) return;
-  }
   const int nslice = gridDim.x, slice = blockIdx.x;
   // Output rows are dealt to the workgroups in units of 4 (an epilogue lane's outputs, and whole gate/up
   // pairs), not in tiles of 16: every workgroup streams the same number of weight rows; a slice's last tile
   // is ragged, its missing rows repeat the slice's last row and are not written.
-  const int nq = (a.N + 3) >> 2;
-  const int n0 = (int)(((long long)slice * nq) / nslice) * 4;
-  const int n1 = min((int)(((long long)(slice + 1) * nq) / nslice) * 4, a.N);
+  int n0, n1;
+  slice_rows(a.N, nslice, slice, n0, n1);
   const int nt = (n1 - n0 + 15) >> 4;
 
   float* red = reinterpret_cast<float*>(smem);      // [2][NW][256] fp32 partial tiles
   unsigned char* stage = smem + 2 * NW * 1024;      // [NW][kStageBytes]
+  int* s_src = reinterpret_cast<int*>(stage + NW * kStageBytes);   // [kLinearRanges][16] source rows of the gathered input rows
+  int* s_any = s_src + kLinearRanges * 16;          // whether any row is active
 
   const int NR = a.n_ranges;
   const int total = nt * NR;          // (tile, range) steps of this workgroup, ranges innermost
@@ -90,23 +97,13 @@ __global__ __launch_bounds__(704) void linear_stream_kernel(LinearArgs a) {
           ring[g][i] = *reinterpret_cast<const u32x4*>(wb0 + (size_t)row * a.ldw + g * 128);
         }
     }
-    // source row of input row n in every range
-    int src[kLinearRanges];
-#pragma unroll
-    for (int r = 0; r < kLinearRanges; ++r) {
-      const LinearRange& rg = a.rg[r < NR ? r : 0];
-      const int nr = min(n, a.R - 1);   // operand columns past the last row repeat it: their sums are not written
-      src[r] = nr;
-      if (rg.gather_mode == kGatherIndex) src[r] = rg.gather_idx[nr];
-      else if (rg.gather_mode == kGatherInBlock) src[r] = (nr / a.gather_k) * a.gather_k + rg.gather_idx[nr];
-      else if (rg.gather_mode == kGatherBlock) src[r] = nr / a.gather_k;
-    }
-    auto x_of = [&](int r) {           // this lane's source row in range r, at its first element
+    auto x_of = [&](int r) {           // this lane's source row in range r (operand columns past the last row repeat it), first element
       const LinearRange& rg = a.rg[r];
-      return rg.x + (size_t)(r == 0 ? src[0] : r == 1 ? src[1] : src[2]) * rg.ldx + ks + q * 8;
+      const int src = MULTI && rg.gather_mode != kGatherNone ? s_src[r * 16 + n] : min(n, a.R - 1);
+      return rg.x + (size_t)src * rg.ldx + ks + q * 8;
     };
     bf16x8 bfrag[G][4];
-    {
+    auto load_x = [&]() {
       const uint16_t* xp = x_of(0);
 #pragma unroll
       for (int g = 0; g < G; ++g)
@@ -115,7 +112,13 @@ __global__ __launch_bounds__(704) void linear_stream_kernel(LinearArgs a) {
           if (MULTI && NR == 1 && g >= n_last) continue;
           bfrag[g][j] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(xp + g * 128 + j * 32));
         }
-    }
+    };
+    // What the epilogue wave has looked up arrives through LDS: loads return in order, so a look at the row flags or at an index by
+    // this wave would wait for the whole first tile, and the input rows would be requested behind it.
+    if (!MULTI) load_x();
+    lds_barrier();
+    if (*s_any == 0) return;           // uniform: no row is active (what was requested is dropped)
+    if (MULTI) load_x();
 #pragma unroll 1
     for (int it = 0; it < total; ++it) {
       __builtin_amdgcn_sched_barrier(0);   // the previous step's operands are dead before the next ones are requested
@@ -136,7 +139,32 @@ __global__ __launch_bounds__(704) void linear_stream_kernel(LinearArgs a) {
   } else {
     // epilogue wave: lane = (vb, r) owns outputs 4*vb .. 4*vb+3 of the tile for input row r
     const int r = lane & 15, vb = lane >> 4;
+    const bool active = r < a.R && (a.row_active == nullptr || a.row_active[r] != 0);   // rows of stopped sequences stay untouched
+    if (MULTI) {
+#pragma unroll
+      for (int g = 0; g < kLinearRanges; ++g) {
+        const LinearRange& rg = a.rg[g < NR ? g : 0];
+        const int nr = min(r, a.R - 1);
+        int src = nr;
+        if (rg.gather_mode == kGatherIndex) src = rg.gather_idx[nr];
+        else if (rg.gather_mode == kGatherInBlock) src = (nr / a.gather_k) * a.gather_k + rg.gather_idx[nr];
+        else if (rg.gather_mode == kGatherBlock) src = nr / a.gather_k;
+        if (vb == 0) s_src[g * 16 + r] = src;
+      }
+    }
+    const bool any = __ballot(active) != 0ull;
+    if (lane == 0) *s_any = any ? 1 : 0;
+    lds_barrier();
+    if (!any) return;
     for (int t = 0; t < nt; ++t) {
+      const int v0 = n0 + t * 16 + vb * 4;
+      float* const yp = a.y + (size_t)r * a.ldy + v0;
+      float y0[4] = {0.f, 0.f, 0.f, 0.f};
+      if (a.mode == kLinearAccumulate && active) {   // on their way while the tile is multiplied
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (v0 + e < n1) y0[e] = yp[e];
+      }
       f32x4 s = {0.f, 0.f, 0.f, 0.f};
       for (int rr = 0; rr < NR; ++rr) {
         const int it = t * NR + rr;
@@ -144,8 +172,7 @@ __global__ __launch_bounds__(704) void linear_stream_kernel(LinearArgs a) {
         for (int w = 0; w < NW; ++w)   // fixed order
           s += *reinterpret_cast<const f32x4*>(red + ((it & 1) * NW + w) * 256 + lane * 4);
       }
-      const int v0 = n0 + t * 16 + vb * 4;
-      if (r < a.R && (a.row_active == nullptr || a.row_active[r] != 0)) {   // rows of stopped sequences stay untouched
+      if (active) {
         if (a.mode == kLinearSiluPairs) {   // outputs (v0, v0+1) and (v0+2, v0+3) are (gate, up) pairs
 #pragma unroll
           for (int e = 0; e < 4; e += 2)
@@ -154,11 +181,10 @@ __global__ __launch_bounds__(704) void linear_stream_kernel(LinearArgs a) {
               a.out16[(size_t)r * a.ld16 + ((v0 + e) >> 1)] = f32_to_bf16_rne(g / (1.0f + __expf(-g)) * u);
             }
         } else {
-          float* yp = a.y + (size_t)r * a.ldy + v0;
 #pragma unroll
           for (int e = 0; e < 4; ++e)
             if (v0 + e < n1) {
-              const float y = (a.mode == kLinearAccumulate) ? yp[e] + s[e] : s[e];
+              const float y = (a.mode == kLinearAccumulate) ? y0[e] + s[e] : s[e];
               yp[e] = y;
               if (a.out16 != nullptr) {
                 const uint16_t yb = f32_to_bf16_rne(y);
@@ -175,8 +201,8 @@ __global__ __launch_bounds__(704) void linear_stream_kernel(LinearArgs a) {
 template <int G>
 static hipError_t launch_linear_g(const LinearArgs& a, int nslice, hipStream_t stream) {
   const dim3 grid(nslice), block((a.nw + 1) * 64);
-  const size_t lds = (size_t)2 * a.nw * 1024 + (size_t)a.nw * kStageBytes;
-  if (a.n_ranges > 1 || a.last_units < a.nw * G)
+  const size_t lds = (size_t)2 * a.nw * 1024 + (size_t)a.nw * kStageBytes + (kLinearRanges * 16 + 4) * sizeof(int);
+  if (a.n_ranges > 1 || a.last_units < a.nw * G || a.rg[0].gather_mode != kGatherNone)
     hipLaunchKernelGGL((linear_stream_kernel<G, true>), grid, block, lds, stream, a);
   else
     hipLaunchKernelGGL((linear_stream_kernel<G, false>), grid, block, lds, stream, a);
@@ -192,20 +218,50 @@ hipError_t launch_linear_stream(const LinearArgs& a, int G, int nslice, hipStrea
   }
 }
 
+// ---- weights ahead ----------------------------------------------------------------------------
+// The norms and the attention of a few rows leave most of the chip and all of the memory idle for 5 to 10 us, and the product behind
+// each of them is a weight stream that starts from nothing.  Workgroups beside theirs read what the stream's workgroups start with;
+// workgroup number % 8 is the XCD of both, so the stream finds it in its own L2.
+__device__ __forceinline__ void read_ahead(const WeightsAhead& w, const uint8_t* row_active, int R, int tid, int threads) {
+  if (row_active != nullptr) {   // the stream will not run if every row is inactive
+    const int lane = tid & 63;
+    if (__ballot(lane < R && row_active[min(lane, R - 1)] != 0) == 0ull) return;
+  }
+  int n0, n1;
+  slice_rows(w.N, w.nslice, (int)blockIdx.x % w.nslice, n0, n1);
+  const unsigned char* p = reinterpret_cast<const unsigned char*>(w.W + (size_t)n0 * w.K);
+  const int len = (int)min((long long)w.bytes, (long long)(n1 - n0) * w.K * 2);
+  for (int i0 = tid * 16; i0 < len; i0 += threads * 64) {
+    u32x4 u[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) u[j] = *reinterpret_cast<const u32x4*>(p + min(i0 + j * threads * 16, len - 16));
+#pragma unroll
+    for (int j = 0; j < 4; ++j) asm volatile("" ::"v"(u[j]));
+  }
+}
+
 // ---- rmsnorm ----------------------------------------------------------------------------------
 __global__ __launch_bounds__(1024) void rmsnorm_kernel(RmsNormArgs a) {
   __shared__ float part[16];
   const int r = blockIdx.x, tid = threadIdx.x;
-  if (a.row_active != nullptr && a.row_active[r] == 0) return;   // uniform over the block
+  if (r >= a.R) {                                                // uniform
+    read_ahead(a.ahead, a.row_active, a.R, tid, 1024);
+    return;
+  }
+  // the flag is looked at behind the loads of the row and of the weights: one round trip instead of three
+  const int on = a.row_active != nullptr ? a.row_active[r] : 1;
   const float* x = a.x + (size_t)r * a.H;
-  float xv[8];                                                   // H <= 8192
+  float xv[8], gv[8];                                            // H <= 8192
   float ss = 0.f;
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
     const int i = tid + 1024 * j;
     xv[j] = (i < a.H) ? x[i] : 0.f;
-    ss += xv[j] * xv[j];
+    gv[j] = (i < a.H) ? a.g[i] : 0.f;
   }
+  if (on == 0) return;                                           // uniform over the block
+#pragma unroll
+  for (int j = 0; j < 8; ++j) ss += xv[j] * xv[j];
   ss = wave_sum_f32(ss);
   if ((tid & 63) == 0) part[tid >> 6] = ss;
   __syncthreads();
@@ -216,13 +272,13 @@ __global__ __launch_bounds__(1024) void rmsnorm_kernel(RmsNormArgs a) {
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
     const int i = tid + 1024 * j;
-    if (i < a.H) a.out[(size_t)r * a.H + i] = f32_to_bf16_rne(xv[j] * inv * a.g[i]);
+    if (i < a.H) a.out[(size_t)r * a.H + i] = f32_to_bf16_rne(xv[j] * inv * gv[j]);
   }
 }
 
 hipError_t launch_rmsnorm(const RmsNormArgs& a, hipStream_t stream) {
   if (a.H > 8192) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(rmsnorm_kernel, dim3(a.R), dim3(1024), 0, stream, a);
+  hipLaunchKernelGGL(rmsnorm_kernel, dim3(a.R + (a.ahead.W != nullptr ? a.ahead.nslice : 0)), dim3(1024), 0, stream, a);
   return hipGetLastError();
 }
 
@@ -403,14 +459,15 @@ __device__ __forceinline__ void unpack_bf16x8(const u32x4& u, float (&f)[8]) {
 template <int TH>
 constexpr int kAttnLdsFloats = 400 + (TH / 64) * kHeadDim;   // in front of the scores
 
-// LDS is exchanged, loads from global memory stay in flight (__syncthreads() would wait for them).
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 template <int TH>
 __global__ __launch_bounds__(TH, 4) void body_attention_kernel(BodyAttnArgs a) {
   extern __shared__ __align__(16) float sm[];
   const int nh = a.H / kHeadDim;
   const int r = blockIdx.x / nh, h = blockIdx.x % nh, tid = threadIdx.x;
+  if (r >= a.R) {                  // uniform: workgroups beside the rows'
+    read_ahead(a.ahead, a.row_active, a.R, tid, TH);
+    return;
+  }
   const int b = (a.step == 0) ? r : r / a.k;
   const int n_vis = a.L + a.step + 1;
   float* qs = sm;                  // [128] rotated query
@@ -1077,12 +1134,12 @@ hipError_t launch_body_attention(const BodyAttnArgs& a, int n_cu, hipStream_t st
   // few rows, wider beams, or a prompt too long for the LDS: one workgroup per (row, head)
   // Sixteen waves where a prompt does not fit one pass of eight and the launch has no two workgroups for a CU: 512 keys in flight
   // instead of 256.
-  const int n_wg = a.R * (a.H / kHeadDim), tail = ((n_vis + 3) & ~3) + 32;
+  const int n_wg = a.R * (a.H / kHeadDim), tail = ((n_vis + 3) & ~3) + 32, n_ahead = a.ahead.W != nullptr ? a.ahead.nslice : 0;
   if (a.L > 256 && n_wg <= n_cu)
-    hipLaunchKernelGGL(body_attention_kernel<1024>, dim3(n_wg), dim3(1024), (size_t)(kAttnLdsFloats<1024> + tail) * sizeof(float),
+    hipLaunchKernelGGL(body_attention_kernel<1024>, dim3(n_wg + n_ahead), dim3(1024), (size_t)(kAttnLdsFloats<1024> + tail) * sizeof(float),
                        stream, a);
   else
-    hipLaunchKernelGGL(body_attention_kernel<512>, dim3(n_wg), dim3(512), (size_t)(kAttnLdsFloats<512> + tail) * sizeof(float),
+    hipLaunchKernelGGL(body_attention_kernel<512>, dim3(n_wg + n_ahead), dim3(512), (size_t)(kAttnLdsFloats<512> + tail) * sizeof(float),
                        stream, a);
   return hipGetLastError();
 }

@@ -47,6 +47,12 @@ struct LinearArgs {
 };
 hipError_t launch_linear_stream(const LinearArgs& a, int G, int nslice, hipStream_t stream);
 
+// Weights that the next launch starts with: the first `bytes` of the rows that each of its `nslice` workgroups streams.
+struct WeightsAhead {
+  const uint16_t* W;          // bf16 [N][K], or null
+  int N, K, nslice, bytes;
+};
+
 // out[r] = bf16( x[r] / sqrt(mean(x[r]^2) + eps) * g )
 struct RmsNormArgs {
   const float* x;             // fp32 [R][H]
@@ -54,6 +60,7 @@ struct RmsNormArgs {
   const uint8_t* row_active;
   uint16_t* out;              // bf16 [R][H]
   int H, R;
+  WeightsAhead ahead;
 };
 hipError_t launch_rmsnorm(const RmsNormArgs& a, hipStream_t stream);
 
@@ -95,6 +102,7 @@ struct BodyAttnArgs {
   uint16_t* o;                // bf16 [R][H]
   int H, L, k, step, R;
   int hist_rows;              // rows per call in the histories (B*k)
+  WeightsAhead ahead;         // one workgroup per (row, head) only
 };
 hipError_t launch_body_attention(const BodyAttnArgs& a, int n_cu, hipStream_t stream);
 
