@@ -205,28 +205,71 @@ __device__ __forceinline__ uint32_t block_kth_largest_u32(const uint32_t* vals, 
   return least;
 }
 
+// The largest prefix of an ordered 32-bit key that at least `want` of the wave's keys reach, found bit by bit (a compare and a scalar
+// popcount per slot), and no further than one that exactly `want` reach.
+template <int S>
+__device__ __forceinline__ uint32_t wave_prefix(const uint32_t (&key)[S], int want) {
+  uint32_t T = 0u;
+  for (uint32_t bit = 0x80000000u; bit != 0u; bit >>= 1) {
+    const uint32_t cand = T | bit;
+    int cnt = 0;
+#pragma unroll
+    for (int q = 0; q < S; ++q) cnt += __popcll(__ballot(key[q] >= cand));
+    if (cnt >= want) T = cand;
+    if (cnt == want) break;
+  }
+  return T;
+}
+// By one wave: the tree indices of the `want` best of nodes 1 .. n (n <= 64 S, keys[i] the rerank key of node i + 1), i.e. 1 + the
+// number of taken nodes with a smaller id, to tidx, and their ids to sel.  Of equal scores the lowest ids are taken.
+template <int S>
+__device__ __forceinline__ void wave_take(const uint64_t* keys, int n, int want, int lane, int* tidx, int* sel) {
+  uint32_t key[S];
+#pragma unroll
+  for (int q = 0; q < S; ++q) key[q] = 64 * q + lane < n ? (uint32_t)(keys[64 * q + lane] >> 32) : 0u;
+  const uint32_t T = want < n ? wave_prefix<S>(key, want) : 0u;
+  int above = 0;
+#pragma unroll
+  for (int q = 0; q < S; ++q) above += __popcll(__ballot(key[q] > T));
+  int left = want - above, t0 = 1;         // places for keys equal to T; the next tree index
+  const unsigned long long below = (1ull << lane) - 1ull;
+#pragma unroll
+  for (int q = 0; q < S; ++q) {
+    const bool real = 64 * q + lane < n;
+    const unsigned long long eq = __ballot(real && key[q] == T);
+    const bool in = key[q] > T || (real && key[q] == T && (int)__popcll(eq & below) < left);
+    left -= min(left, (int)__popcll(eq));
+    const unsigned long long bal = __ballot(in);
+    if (in) {
+      const int t = t0 + __popcll(bal & below), id = 64 * q + lane + 1;
+      tidx[id] = t;
+      sel[t] = id;
+    }
+    t0 += __popcll(bal);
+  }
+}
+
 // Pools of up to kSelMax nodes on a block with at least half as many threads: thread t looks after pool nodes
 // t + 1 and t + 1 + nthr from their scores to their lines of the tree, so nothing is searched for and nothing is
-// fetched twice.  One round trip brings a node's score, parent, token and depth.  Selection: the m-th best key
+// fetched twice.  One round trip brings the pool's size and every node's score, parent, token and depth.  Selection, up to kWaveTake
+// nodes: wave 0 alone finds the m-th largest score bit by bit and hands out the tree indices (wave_take), without a barrier; what it
+// costs grows with the nodes per lane.  (Ranking candidates against each other with the whole block, as below, or up to 256 nodes all
+// of them, takes up to ten barriers more; ddd_tree_finalize of one sequence with 211 / 411 / 511 / 690 / 911 nodes: 6.2 / 5.9 / 8.2 /
+// 15.3 / 8.6 us, now 4.9 / 5.3 / 6.6 / 9.5 / 8.4; 64 sequences with 911: 15.3, now 10.6.)  Beyond: the m-th best key
 // among the first kSub nodes is a lower bound of the tree's keys (summed logprobs fall with depth, so the early
 // nodes hold most of the tree and the bound is tight); the nodes at or above it - the candidates, usually little
 // more than m - are ranked among themselves by counting (keys are distinct: the id is part of them), which costs
 // kSub^2 + C^2 comparisons instead of N^2 or a sort's long chain of dependent stages (if more than kSelCand nodes
-// pass the bound, the m-th best of kRefine of them is a tighter one: twice at most); up to kDirect nodes all are
-// ranked at once, which saves the three barriers of the bound (7B shape, k = 10, microseconds inside the stopping
-// call for 111 / 211 / 311 / 411 / 911 nodes: 3.6 / 5.7 / 6.3 / 6.7 / 9.5; ranking every node against all others
-// took 3.5 / 5.2 / 7.8 / 15 / 34, the sort 16 at 911).  Still more than kSelCand candidates after two tightenings:
-// the caller's general path takes over (returns false; nothing has been written to the tree).  The
-// tree index of a selected node is 1 + the number of selected nodes with a smaller id (ballots and popcounts); a
+// pass the bound, the m-th best of kRefine of them is a tighter one: twice at most).  Still more than kSelCand candidates after two
+// tightenings: the caller's general path takes over (returns false; nothing has been written to the tree).  A
 // parent's tree index is read from the node -> index table (a selected node's parent is selected: its score is no
 // smaller and its id is smaller).
-constexpr int kSelMax = 2048, kSub = 128, kSelCand = 384, kDirect = 256, kRefine = 256;
+constexpr int kSelMax = 2048, kSub = 128, kSelCand = 384, kWaveTake = 1024, kRefine = 256;
 static_assert(kRefine >= DDD_MMAX && kRefine <= kSelCand, "the refining sample holds m keys and lies in the candidate list");
-static_assert(kDirect <= kSelCand, "the rank array holds every node of a directly ranked pool");
 static_assert(kSub >= DDD_MMAX, "the subset must hold m keys");
 __device__ __forceinline__ bool tree_select_block(const ddd_state& st, const ddd_tree& tree, int b, int m, int nmax,
-                                                  int tid, int nthr, TreeSmem& sm, int N) {
-  const int m_eff = min(m, N), T = m + 1;
+                                                  int tid, int nthr, TreeSmem& sm, int n_nodes) {
+  const int T = m + 1;
   // the upper half of the key array holds the working set of the selection
   int* tidx = reinterpret_cast<int*>(sm.keys + kSelMax + 2);     // [kSelMax + 1]  tree index of a pool node; -1: not in the tree
   uint64_t* ckey = reinterpret_cast<uint64_t*>(tidx + kSelMax + 2);   // [kSelCand] candidate keys
@@ -244,21 +287,36 @@ __device__ __forceinline__ bool tree_select_block(const ddd_state& st, const ddd
   bool node[2];
   uint64_t my_key[2];
   int my_pn[2], my_tok[2], my_dep[2], root_tok = -1, root_dep = 0;
+  float my_sc[2];
+  const int most = (n_nodes >= 0 ? n_nodes : nmax) - 1;           // the pool's size, if the caller has it not at hand, in the same trip
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
     const int n = tid + q * nthr;                                 // pool node n + 1
-    node[q] = n < N;
-    my_key[q] = 0ull;
+    my_sc[q] = 0.f;
     my_pn[q] = 0;
     my_tok[q] = -1;
     my_dep[q] = 0;
-    if (node[q]) {
-      my_key[q] = rerank_key(psc[n + 1], n + 1);
-      sm.keys[n] = my_key[q];
-      tidx[n + 1] = -1;
+    if (n < most) {
+      my_sc[q] = psc[n + 1];
       my_pn[q] = ppar[n + 1];
       my_tok[q] = ptok[n + 1];
       my_dep[q] = pdep[n + 1];
+    }
+  }
+  if (tid == 0) {
+    root_tok = ptok[0];
+    root_dep = pdep[0];
+  }
+  const int N = (n_nodes >= 0 ? n_nodes : min(st.n_nodes[b], nmax)) - 1, m_eff = min(m, N);
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int n = tid + q * nthr;
+    node[q] = n < N;
+    my_key[q] = 0ull;
+    if (node[q]) {
+      my_key[q] = rerank_key(my_sc[q], n + 1);
+      sm.keys[n] = my_key[q];
+      tidx[n + 1] = -1;
     }
   }
   const int S = min(N, kSub);
@@ -269,16 +327,26 @@ __device__ __forceinline__ bool tree_select_block(const ddd_state& st, const ddd
     misc[0] = 0;
     sm.e.sel[0] = 0;
     sm.e.par[0] = -1;
-    root_tok = ptok[0];
-    root_dep = pdep[0];
   }
   __syncthreads();
-  if (N <= kDirect) {                                             // uniform: few enough nodes to rank them all
-    count_larger_keys(sm.keys, N, rank, tid, nthr);
+  int ti[2] = {-1, -1};
+  if (N <= kWaveTake) {                                           // uniform
+    if (wave == 0) {
+      if (N <= 128)
+        wave_take<2>(sm.keys, N, m_eff, lane, tidx, sm.e.sel);
+      else if (N <= 256)
+        wave_take<4>(sm.keys, N, m_eff, lane, tidx, sm.e.sel);
+      else if (N <= 512)
+        wave_take<8>(sm.keys, N, m_eff, lane, tidx, sm.e.sel);
+      else if (N <= 768)
+        wave_take<12>(sm.keys, N, m_eff, lane, tidx, sm.e.sel);
+      else
+        wave_take<kWaveTake / 64>(sm.keys, N, m_eff, lane, tidx, sm.e.sel);
+    }
     __syncthreads();
-    for (int i = tid; i < N; i += nthr)
-      if (rank[i] < m_eff) tidx[i + 1] = -2;                      // in the tree; its index follows
-    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+      if (node[q]) ti[q] = tidx[tid + q * nthr + 1];
   } else {
     // the bound: first from the early nodes, then - while more than kSelCand nodes pass it (a confident sequence: its
     // deep nodes score as well as the early ones) - from the first kRefine candidates, which lie above the old bound
@@ -320,33 +388,32 @@ __device__ __forceinline__ bool tree_select_block(const ddd_state& st, const ddd
     for (int c = tid; c < C; c += nthr)
       if (rank[c] < m_eff) tidx[cnode[c]] = -2;                     // in the tree; its index follows
     __syncthreads();
-  }
-  bool chosen[2];
-  unsigned long long bal[2];
+    bool chosen[2];
+    unsigned long long bal[2];
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    chosen[q] = node[q] && tidx[tid + q * nthr + 1] == -2;
-    bal[q] = __ballot(chosen[q]);
-    if (lane == 0) wtot[q * 16 + wave] = __popcll(bal[q]);
-  }
-  __syncthreads();
-  int ti[2] = {-1, -1};
-#pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    if (chosen[q]) {
-      int t = 1 + __popcll(bal[q] & ((1ull << lane) - 1ull));
-      for (int w = 0; w < wave; ++w) t += wtot[q * 16 + w];
-      if (q == 1)
-        for (int w = 0; w < nwaves; ++w) t += wtot[w];
-      ti[q] = t;
-      sm.e.sel[t] = tid + q * nthr + 1;
-      tidx[tid + q * nthr + 1] = t;
+    for (int q = 0; q < 2; ++q) {
+      chosen[q] = node[q] && tidx[tid + q * nthr + 1] == -2;
+      bal[q] = __ballot(chosen[q]);
+      if (lane == 0) wtot[q * 16 + wave] = __popcll(bal[q]);
     }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      if (chosen[q]) {
+        int t = 1 + __popcll(bal[q] & ((1ull << lane) - 1ull));
+        for (int w = 0; w < wave; ++w) t += wtot[q * 16 + w];
+        if (q == 1)
+          for (int w = 0; w < nwaves; ++w) t += wtot[w];
+        ti[q] = t;
+        sm.e.sel[t] = tid + q * nthr + 1;
+        tidx[tid + q * nthr + 1] = t;
+      }
+    }
+    __syncthreads();
   }
-  __syncthreads();
 #pragma unroll
   for (int q = 0; q < 2; ++q)
-    if (chosen[q]) {
+    if (ti[q] >= 0) {
       const int p = tidx[my_pn[q]];
       sm.e.par[ti[q]] = p < ti[q] ? p : -1;   // a pool whose parents do not come first must not send the walk below in a circle
     }
@@ -372,7 +439,7 @@ __device__ __forceinline__ bool tree_select_block(const ddd_state& st, const ddd
   for (int i = tid; i < m; i += nthr) tree.sel_node[(size_t)b * m + i] = (i < m_eff) ? sm.e.sel[1 + i] : -1;
 #pragma unroll
   for (int q = 0; q < 2; ++q)
-    if (chosen[q]) {
+    if (ti[q] >= 0) {
       tree.tree_token[(size_t)b * T + ti[q]] = my_tok[q];
       tree.pos[(size_t)b * T + ti[q]] = my_dep[q];
       tree.parent_idx[(size_t)b * T + ti[q]] = sm.e.par[ti[q]];
@@ -396,15 +463,17 @@ __device__ __forceinline__ bool tree_select_block(const ddd_state& st, const ddd
 // n_nodes: the sequence's pool size (st.n_nodes[b]) if the caller has it at hand, else -1.
 __device__ __forceinline__ void tree_finalize_block(const ddd_state& st, const ddd_tree& tree, int b, int m, int nmax,
                                                     int tid, int nthr, TreeSmem& sm, int n_nodes = -1) {
+  const int narrow = nthr <= 1024 ? min(kSelMax, 2 * nthr) : 0;
+  if (n_nodes < 0 && nmax - 1 > narrow) n_nodes = st.n_nodes[b];
+  if ((n_nodes >= 0 ? n_nodes : nmax) - 1 <= narrow) {             // uniform
+    if (tree_select_block(st, tree, b, m, nmax, tid, nthr, sm, n_nodes)) return;
+    __syncthreads();                                              // the general path reuses the key array
+  }
   if (n_nodes < 0) n_nodes = st.n_nodes[b];
   const int N = n_nodes - 1;
   const int m_eff = min(m, N);
   const float* psc = st.pool_score + (size_t)b * nmax;
 
-  if (N >= 1 && N <= kSelMax && N <= 2 * nthr && nthr <= 1024) {   // uniform
-    if (tree_select_block(st, tree, b, m, nmax, tid, nthr, sm, N)) return;
-    __syncthreads();                                              // the general path reuses the key array
-  }
   if (N <= 320) {
     // Small pools on a block much narrower than the pool: rank by counting (the number of larger keys is a node's
     // position in the rerank order); cheaper than the sort's chain of dependent stages up to a few hundred nodes.
