@@ -49,6 +49,7 @@ constexpr float kLazy = 11.0f;  // how far (in powers of two) a score may exceed
 
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef uint32_t u32_of_bytes __attribute__((aligned(1)));   // a row of the mask starts on any byte
 typedef f32x4 f32x4_of_floats __attribute__((aligned(4)));   // the caller's output starts on any float
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 
@@ -85,33 +86,38 @@ __device__ __forceinline__ const u32x4* prompt_chunk(const TreeAttnArgs& a, cons
   return reinterpret_cast<const u32x4*>(base) + (((size_t)b * a.nh + h) * ((a.L + 31) >> 5) + c) * 512;
 }
 
-// A step of prompt keys and tree keys that are not all there (the steps after the whole ones of the prompt).  Chunk ch
-// of the step is chunk i = first + ch of the rest: prompt chunks, then the tree's, then nothing.
-// vis: which of the lane's 16 keys of this wave's chunk count for its two queries, bit e as the accumulator registers go.
-template <int NW>
-__device__ __forceinline__ void load_rest(const TreeAttnArgs& a, int first, int c_rest, int n_prompt, int n_rest, int b, int h,
-                                          int qt, int wave, int lane, Operands<NW>& x, uint32_t (&vis)[2]) {
-  const int l32 = lane & 31, lh = lane >> 5, db = wave / (NW / 4);
-  const u32x4 zero = {0u, 0u, 0u, 0u};
-  const int i = first + wave;
-  vis[0] = vis[1] = 0u;
-  if (i < n_prompt) {
-    const u32x4* kp = prompt_chunk(a, a.k_prompt, c_rest + i, b, h);
+// Keys of chunk c of the prompt, or of chunk i of the tree, for one wave, and which of the lane's 16 keys count for its two queries:
+// bit e of vis as the accumulator registers go.
+__device__ __forceinline__ void load_prompt_keys(const TreeAttnArgs& a, int c, int b, int h, int lane, bf16x8 (&kf)[8], uint32_t (&vis)[2]) {
+  const u32x4* kp = prompt_chunk(a, a.k_prompt, c, b, h);
 #pragma unroll
-    for (int s = 0; s < 8; ++s) x.kf[s] = __builtin_bit_cast(bf16x8, kp[s * 64 + lane]);
+  for (int s = 0; s < 8; ++s) kf[s] = __builtin_bit_cast(bf16x8, kp[s * 64 + lane]);
+  vis[0] = 0u;
 #pragma unroll
-    for (int e = 0; e < 16; ++e)
-      vis[0] |= ((c_rest + i) * 32 + (e >> 2) * 8 + lh * 4 + (e & 3) < a.L) ? (1u << e) : 0u;
-    vis[1] = vis[0];
-  } else if (i < n_rest) {
-    const int c0 = (i - n_prompt) * 32, kj = min(c0 + l32, a.T - 1);
-    const uint16_t* kp = a.k_tree + (((size_t)b * a.T + kj) * a.nh + h) * kAD + lh * 8;
+  for (int e = 0; e < 16; ++e) vis[0] |= (c * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3) < a.L) ? (1u << e) : 0u;
+  vis[1] = vis[0];
+}
+__device__ __forceinline__ void load_tree_keys(const TreeAttnArgs& a, int i, int b, int h, int qt, int lane, bf16x8 (&kf)[8], uint32_t (&vis)[2]) {
+  const int l32 = lane & 31, lh = lane >> 5, c0 = i * 32, kj = min(c0 + l32, a.T - 1);
+  const uint16_t* kp = a.k_tree + (((size_t)b * a.T + kj) * a.nh + h) * kAD + lh * 8;
 #pragma unroll
-    for (int s = 0; s < 8; ++s) x.kf[s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(kp + s * 16));
+  for (int s = 0; s < 8; ++s) kf[s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(kp + s * 16));
 #pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
-      const int qi = qt * kQT + qb * 32 + l32;
-      const uint8_t* mrow = a.mask + ((size_t)b * a.T + min(qi, a.T - 1)) * a.T;
+  for (int qb = 0; qb < 2; ++qb) {
+    const int qi = qt * kQT + qb * 32 + l32;
+    const uint8_t* mrow = a.mask + ((size_t)b * a.T + min(qi, a.T - 1)) * a.T;
+    vis[qb] = 0u;
+    if (a.T >= 4) {                          // four keys a load, the last ones from the row's last four (32 loads of a byte: 1.7 us more)
+      uint32_t w[4];
+#pragma unroll
+      for (int g = 0; g < 4; ++g) w[g] = *reinterpret_cast<const u32_of_bytes*>(mrow + min(c0 + g * 8 + lh * 4, a.T - 4));
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int k0 = c0 + (e >> 2) * 8 + lh * 4, key = k0 + (e & 3);
+        const uint32_t on = (w[e >> 2] >> (8 * ((key - min(k0, a.T - 4)) & 3))) & 0xFFu;
+        vis[qb] |= (key < a.T && qi < a.T && on != 0u) ? (1u << e) : 0u;
+      }
+    } else {
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
         const int key = c0 + (e >> 2) * 8 + lh * 4 + (e & 3);
@@ -119,28 +125,48 @@ __device__ __forceinline__ void load_rest(const TreeAttnArgs& a, int first, int 
         vis[qb] |= (key < a.T && qi < a.T && on != 0) ? (1u << e) : 0u;
       }
     }
+  }
+}
+// Values of chunk c of the prompt, or of chunk i of the tree, for a wave's quarter db of the head.
+__device__ __forceinline__ void load_prompt_values(const TreeAttnArgs& a, int c, int b, int h, int db, int lane, bf16x8 (&vf)[2]) {
+  const u32x4* vp = prompt_chunk(a, a.v_prompt, c, b, h) + db * 128 + lane;
+#pragma unroll
+  for (int t = 0; t < 2; ++t) vf[t] = __builtin_bit_cast(bf16x8, vp[t * 64]);
+}
+__device__ __forceinline__ void load_tree_values(const TreeAttnArgs& a, int i, int b, int h, int db, int lane, bf16x8 (&vf)[2]) {
+  const uint16_t* vp = a.vt_tree + (((size_t)b * a.nh + h) * kAD + db * 32 + (lane & 31)) * a.Tp + (lane >> 5) * 4 + i * 32;
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const u32x2 lo = *reinterpret_cast<const u32x2*>(vp + t * 16), hi = *reinterpret_cast<const u32x2*>(vp + t * 16 + 8);
+    vf[t] = __builtin_bit_cast(bf16x8, u32x4{lo[0], lo[1], hi[0], hi[1]});
+  }
+}
+
+// A step of prompt keys and tree keys that are not all there (the steps after the whole ones of the prompt).  Chunk ch
+// of the step is chunk i = first + ch of the rest: prompt chunks, then the tree's, then nothing.
+template <int NW>
+__device__ __forceinline__ void load_rest(const TreeAttnArgs& a, int first, int c_rest, int n_prompt, int n_rest, int b, int h,
+                                          int qt, int wave, int lane, Operands<NW>& x, uint32_t (&vis)[2]) {
+  const int db = wave / (NW / 4), i = first + wave;
+  const u32x4 zero = {0u, 0u, 0u, 0u};
+  vis[0] = vis[1] = 0u;
+  if (i < n_prompt) {
+    load_prompt_keys(a, c_rest + i, b, h, lane, x.kf, vis);
+  } else if (i < n_rest) {
+    load_tree_keys(a, i - n_prompt, b, h, qt, lane, x.kf, vis);
   } else {
 #pragma unroll
     for (int s = 0; s < 8; ++s) x.kf[s] = __builtin_bit_cast(bf16x8, zero);
   }
-  const uint16_t* vt = a.vt_tree + (((size_t)b * a.nh + h) * kAD + db * 32 + l32) * a.Tp + lh * 4;
 #pragma unroll
   for (int ch = 0; ch < NW; ++ch) {
     const int j = first + ch;                                // uniform
-    if (j < n_prompt) {
-      const u32x4* vp = prompt_chunk(a, a.v_prompt, c_rest + j, b, h) + db * 128 + lane;
-#pragma unroll
-      for (int t = 0; t < 2; ++t) x.vf[ch][t] = __builtin_bit_cast(bf16x8, vp[t * 64]);
-    } else if (j < n_rest) {
-      const uint16_t* vp = vt + (j - n_prompt) * 32;
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const u32x2 lo = *reinterpret_cast<const u32x2*>(vp + t * 16), hi = *reinterpret_cast<const u32x2*>(vp + t * 16 + 8);
-        x.vf[ch][t] = __builtin_bit_cast(bf16x8, u32x4{lo[0], lo[1], hi[0], hi[1]});
-      }
-    } else {
+    if (j < n_prompt)
+      load_prompt_values(a, c_rest + j, b, h, db, lane, x.vf[ch]);
+    else if (j < n_rest)
+      load_tree_values(a, j - n_prompt, b, h, db, lane, x.vf[ch]);
+    else
       x.vf[ch][0] = x.vf[ch][1] = __builtin_bit_cast(bf16x8, zero);
-    }
   }
 }
 
@@ -247,6 +273,16 @@ __device__ __forceinline__ void attend_step(Operands<NW>& x, const u32x4* qlds, 
     }
 }
 
+// Workgroups of one head get numbers that are equal modulo 8, i.e. one XCD: its query tiles read the keys and
+// values through one L2, and the merge finds the partials there (32 heads, L = 1999: one user in one pass 18.9 -> 18.2 us;
+// two query tiles, one user 30.3 -> 27.2, sixteen 199 -> 171; one tile and several steps: 17.7 -> 18.0, so not there).
+__device__ __forceinline__ void head_on_xcd(int& x, int& h) {
+  const int X = gridDim.x, id = x + X * h;
+  if ((gridDim.y & 7) != 0) return;
+  h = (id & 7) + 8 * (id / (8 * X));
+  x = (id >> 3) % X;
+}
+
 template <int NW>
 __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void tree_attn_partial_kernel(TreeAttnArgs a) {
   using C = AttnCfg<NW>;
@@ -257,7 +293,9 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void tree_attn_partial_ke
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, lh = lane >> 5;
   const int db = wave / (NW / 4);
   const int nqt = (a.T + kQT - 1) / kQT;
-  const int split = blockIdx.x / nqt, qt = blockIdx.x - split * nqt, h = blockIdx.y, b = blockIdx.z;
+  int bx = blockIdx.x, h = blockIdx.y;
+  if (nqt > 1) head_on_xcd(bx, h);
+  const int split = bx / nqt, qt = bx - split * nqt, b = blockIdx.z;
   const AttnSteps n = attn_steps(a.L, a.T, NW);
 
   // the first step's operands are on their way while the queries are staged; the workgroup takes steps split, split + nsplit, ...
@@ -360,14 +398,158 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void tree_attn_partial_ke
   }
 }
 
+// Few tiles whose heads are a little more than one step of eight waves per workgroup (one user of 32 heads: 65 chunks of 32 keys for
+// L = 1999 and eight workgroups a head): a second step for the last chunks costs as much as the first, 5 us of loads, barriers and
+// products one after the other.  Here a workgroup takes up to sixteen consecutive chunks in one pass - a wave the scores of two -, so
+// there is one reference, nothing is rescaled, and every load of the pass is on its way before the first product.
+// L = 1999, 32 heads, one user: 24.0 -> 18.9 us with the merge, 1.7 of it by reading the mask four keys at a time.  (Nine workgroups a
+// head instead, two to a CU: 26.3.)
+constexpr int kPassChunks = 16;
+
+__global__ __launch_bounds__(512, 2) void tree_attn_pass_kernel(TreeAttnArgs a, int per) {
+  constexpr int NW = 8, kLdsQ = AttnCfg<NW>::kLdsQ;
+  __shared__ __align__(16) unsigned char lds[(kLdsQ + kPassChunks * 8 * 64) * 16 + NW * kQT * 4];
+  u32x4* qlds = reinterpret_cast<u32x4*>(lds);            // [qb * 8 + s][lane] queries as B operands
+  u32x4* plds = qlds + kLdsQ;                             // [chunk][qb][half][t][lane] weights as B operands
+  float* cmax_lds = reinterpret_cast<float*>(plds + kPassChunks * 8 * 64);   // [wave][query]
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, lh = lane >> 5;
+  const int db = wave >> 1, nqt = (a.T + kQT - 1) / kQT;
+  int bx = blockIdx.x, h = blockIdx.y;
+  head_on_xcd(bx, h);
+  const int split = bx / nqt, qt = bx - split * nqt, b = blockIdx.z;
+  const int n_prompt = (a.L + 31) >> 5, first = split * per, n = min(per, n_prompt + ((a.T + 31) >> 5) - first);   // >= 1 chunks
+
+  bf16x8 kf[2][8], vf[kPassChunks][2];
+  uint32_t vis[2][2] = {{0u, 0u}, {0u, 0u}};
+  auto load_values = [&](int ch) {                        // ch < n is uniform
+    if (ch < n) {
+      if (first + ch < n_prompt)
+        load_prompt_values(a, first + ch, b, h, db, lane, vf[ch]);
+      else
+        load_tree_values(a, first + ch - n_prompt, b, h, db, lane, vf[ch]);
+    }
+  };
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int c = first + wave + NW * u;
+    if (wave + NW * u < n) {                              // wave-uniform
+      if (c < n_prompt)
+        load_prompt_keys(a, c, b, h, lane, kf[u], vis[u]);
+      else
+        load_tree_keys(a, c - n_prompt, b, h, qt, lane, kf[u], vis[u]);
+    }
+  }
+#pragma unroll
+  for (int ch = 0; ch < NW; ++ch) load_values(ch);
+  {
+    // lane (l32, lh) holds d = s*16 + lh*8 .. +7 of query qb*32 + l32
+    u32x4 q[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int f = wave * 2 + i, qi = qt * kQT + (f >> 3) * 32 + l32;
+      q[i] = u32x4{0u, 0u, 0u, 0u};
+      if (qi < a.T) q[i] = *reinterpret_cast<const u32x4*>(a.q + (((size_t)b * a.T + qi) * a.nh + h) * kAD + lh * 8 + (f & 7) * 16);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) qlds[(wave * 2 + i) * 64 + lane] = q[i];
+  }
+  lds_barrier();
+
+  const float scale = 0.08838834764831845f * 1.4426950408889634f;   // scores in units of ln 2
+  float sv[2][2][16], cmax[2] = {-INFINITY, -INFINITY};
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) {
+      if (wave + NW * u >= n) continue;                   // wave-uniform
+      f32x16 acc;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+#pragma unroll
+      for (int s = 0; s < 8; ++s)
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[u][s], __builtin_bit_cast(bf16x8, qlds[(qb * 8 + s) * 64 + lane]), acc, 0, 0, 0);
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        sv[u][qb][e] = ((vis[u][qb] >> e) & 1u) ? acc[e] * scale : -INFINITY;
+        cmax[qb] = fmaxf(cmax[qb], sv[u][qb][e]);
+      }
+    }
+#pragma unroll
+  for (int ch = NW; ch < kPassChunks; ++ch) load_values(ch);   // where the keys were
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb) {
+    const float m = fmaxf(cmax[qb], __shfl_xor(cmax[qb], 32, 64));   // the other half of the query's keys
+    if (lane < 32) cmax_lds[wave * kQT + qb * 32 + l32] = m;
+  }
+  lds_barrier();
+  float m[2], l[2] = {0.f, 0.f};
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb) {
+    m[qb] = cmax_lds[qb * 32 + l32];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) m[qb] = fmaxf(m[qb], cmax_lds[w * kQT + qb * 32 + l32]);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      if (wave + NW * u >= n) continue;
+      // the weights go in as two bf16 halves, hi + lo to 2^-17 relative (attend_step)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        u32x4 hi, lo;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          float p0 = __builtin_amdgcn_exp2f(sv[u][qb][8 * t + 2 * i] - m[qb]), p1 = __builtin_amdgcn_exp2f(sv[u][qb][8 * t + 2 * i + 1] - m[qb]);
+          if (m[qb] == -INFINITY) p0 = p1 = 0.f;          // nothing visible: all weights are zero, not NaN
+          l[qb] += p0 + p1;
+          hi[i] = pack_bf16x2(p0, p1);
+          lo[i] = pack_bf16x2(p0 - __uint_as_float(hi[i] << 16), p1 - __uint_as_float(hi[i] & 0xFFFF0000u));
+        }
+        plds[(((wave + NW * u) * 2 + qb) * 4 + t) * 64 + lane] = hi;
+        plds[(((wave + NW * u) * 2 + qb) * 4 + 2 + t) * 64 + lane] = lo;
+      }
+    }
+  }
+  lds_barrier();                                          // the weights are there, and the maxima have been read
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb) {
+    const float s = l[qb] + __shfl_xor(l[qb], 32, 64);
+    if (lane < 32) cmax_lds[wave * kQT + qb * 32 + l32] = s;
+  }
+  f32x16 o;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) o[e] = 0.f;
+  const int qb = wave & 1, q = qb * 32 + l32;
+#pragma unroll
+  for (int ch = 0; ch < kPassChunks; ++ch) {
+    if (ch >= n) continue;                                // uniform
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int half = 0; half < 2; ++half)
+        o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+            vf[ch][t], __builtin_bit_cast(bf16x8, plds[((ch * 2 + qb) * 4 + half * 2 + t) * 64 + lane]), o, 0, 0, 0);
+  }
+  lds_barrier();
+  float lsum = 0.f;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) lsum += cmax_lds[w * kQT + q];   // fixed order
+  float* part = a.part + ((((size_t)b * a.nh + h) * nqt + qt) * a.nsplit + split) * kPartFloats + q;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) part[(db * 32 + (e >> 2) * 8 + lh * 4 + (e & 3)) * kQT] = o[e];
+  if (db == 0 && lane < 32) {
+    part[kAD * kQT] = qb != 0 ? m[1] : m[0];
+    part[kAD * kQT + kQT] = lsum;
+  }
+}
+
 // Merge of the workgroups' partials: one workgroup per (query tile x eighth of the head, head, sequence).  Every thread asks for
 // its partials eight at a time, the references and sums together with the outputs: one or two memory latencies in all.
 constexpr int kMergeD = 16;   // elements of the head per workgroup
 
 __global__ __launch_bounds__(256) void tree_attn_merge_kernel(TreeAttnArgs a) {
   const int nqt = (a.T + kQT - 1) / kQT;
-  const int qt = blockIdx.x / (kAD / kMergeD), dq0 = (blockIdx.x % (kAD / kMergeD)) * kMergeD, h = blockIdx.y, b = blockIdx.z,
-            tid = threadIdx.x;
+  int bx = blockIdx.x, h = blockIdx.y;
+  head_on_xcd(bx, h);
+  const int qt = bx / (kAD / kMergeD), dq0 = (bx % (kAD / kMergeD)) * kMergeD, b = blockIdx.z, tid = threadIdx.x;
   const float* part = a.part + (((size_t)b * a.nh + h) * nqt + qt) * a.nsplit * kPartFloats;
   const int qx = tid & (kQT - 1), qi = qt * kQT + qx;
   if (qi >= a.T) return;
@@ -458,17 +640,27 @@ size_t tree_attention_part_floats() { return (size_t)kPartFloats; }
 static int attn_waves(long long tiles, int n_cu) { return 2 * tiles <= n_cu ? 8 : 4; }
 static long long attn_tiles(int B, int n_heads, int T) { return (long long)B * n_heads * ((T + kQT - 1) / kQT); }
 
+// Chunks of 32 keys per workgroup where one pass over them takes the place of several steps, or 0.
+static int attn_pass_chunks(int nw, int nsplit, int T, int L) {
+  const int all = (L + 31) / 32 + (T + 31) / 32, per = (all + nsplit - 1) / nsplit;
+  return nw == 8 && nsplit > 1 && per > 8 && per <= kPassChunks ? per : 0;
+}
+
 // Splits of a head's keys over workgroups: one workgroup of eight waves or two of four per CU, a step each at least.
 int tree_attention_splits(int B, int n_heads, int T, int L, int n_cu) {
   const long long tiles = attn_tiles(B, n_heads, T);
   const int nw = attn_waves(tiles, n_cu), most = std::min(attn_steps(L, T, nw).all, 64);
-  return (int)std::min<long long>(std::max<long long>((nw == 8 ? 1 : 2) * n_cu / tiles, 1), most);
+  const int n = (int)std::min<long long>(std::max<long long>((nw == 8 ? 1 : 2) * n_cu / tiles, 1), most);
+  const int per = attn_pass_chunks(nw, n, T, L);
+  return per > 0 ? ((L + 31) / 32 + (T + 31) / 32 + per - 1) / per : n;   // none without a chunk
 }
 
 hipError_t launch_tree_attention(const TreeAttnArgs& a, int n_cu, hipStream_t stream) {
-  const int nqt = (a.T + kQT - 1) / kQT;
+  const int nqt = (a.T + kQT - 1) / kQT, nw = attn_waves(attn_tiles(a.B, a.nh, a.T), n_cu), per = attn_pass_chunks(nw, a.nsplit, a.T, a.L);
   const dim3 grid(a.nsplit * nqt, a.nh, a.B);
-  if (attn_waves(attn_tiles(a.B, a.nh, a.T), n_cu) == 8)
+  if (per > 0)
+    hipLaunchKernelGGL(tree_attn_pass_kernel, grid, dim3(512), 0, stream, a, per);
+  else if (nw == 8)
     hipLaunchKernelGGL(tree_attn_partial_kernel<8>, grid, dim3(64 * 8), 0, stream, a);
   else
     hipLaunchKernelGGL(tree_attn_partial_kernel<4>, grid, dim3(64 * 4), 0, stream, a);
