@@ -316,11 +316,11 @@ __global__ __launch_bounds__(256) void row_topk_kernel(RowTopkArgs a) {
 }
 
 // The same for wide beams (DDD_KMAX < k <= DDD_KWIDE_MAX), where a bound from quad maxima no longer holds k keys: 1024
-// threads rank the group maxima by counting (32-bit compares against broadcast reads of LDS, several threads per group), and
-// then the candidates at or above the k-th of them.  More than 512 groups are folded to the maxima of up to four first: the
+// threads find the k-th largest group maximum (one wave, bit by bit), and rank the candidates at or above it by counting.  More
+// than 512 groups are folded to the maxima of up to four first: the
 // k-th largest of those is reached by k groups too, only a few more groups pass it (counting all 2000 groups of V = 128000
 // took 60 us).  (Bitonic sorts of both by 256 threads, a block barrier per stage, took 28 us a launch at k = 100,
-// V = 32000, whatever the number of rows; 14 us now.)
+// V = 32000, whatever the number of rows; 14 us with the counting, 11 with the k-th group maximum found by one wave.)
 constexpr int kWideRowThreads = 1024;
 constexpr int kWideGroups = 2048;   // V <= 2^17
 constexpr int kWideFold = 512;      // most values that are ranked
@@ -328,14 +328,14 @@ static_assert(kWideGroups == 2 * kWideRowThreads && kWideFold == kWideRowThreads
 
 __global__ __launch_bounds__(kWideRowThreads) void row_topk_wide_kernel(RowTopkArgs a) {
   __shared__ __align__(16) uint32_t s_gm[kWideFold];         // (folded) group maxima as ordered keys
-  __shared__ int s_num[kWideGroups];                         // work area; later the groups that hold candidates
+  __shared__ int s_num[kWideGroups];                         // the groups that hold candidates
   __shared__ uint64_t s_cand[kCandMax];
   __shared__ int s_rank[kCandMax];
   __shared__ float s_red[2][16];
-  __shared__ uint32_t s_min[16];
+  __shared__ uint32_t s_min[1];
   __shared__ int s_cnt, s_ng;
   const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (a.row_active != nullptr && !a.row_active[row]) return;   // uniform
+  const int on = a.row_active != nullptr ? a.row_active[row] : 1;   // looked at behind the loads of the row's groups
   RowEmit<true> emit(a, row);
   const int ngrp = (a.V + 63) >> 6;
   uint32_t top = 0u;                                         // the larger of the thread's groups
@@ -350,6 +350,7 @@ __global__ __launch_bounds__(kWideRowThreads) void row_topk_wide_kernel(RowTopkA
     }
     m = fmaxf(m, mine_max[u]);
   }
+  if (on == 0) return;                                       // uniform
   const bool fold = ngrp > kWideFold;                        // uniform
   if (fold) {
     top = umax32(top, dpp_move_u32<0xB1>(top));              // lane ^ 1
@@ -373,7 +374,7 @@ __global__ __launch_bounds__(kWideRowThreads) void row_topk_wide_kernel(RowTopkA
   acc = wave_sum_f32(acc);
   if (lane == 0) s_red[1][wave] = acc;
   // ---- T = k-th largest (folded) group max --------------------------------------------------------------------------
-  const uint32_t least = block_kth_largest_u32(s_gm, nval, min(a.k, nval), s_num, s_min, tid);   // its barriers publish s_red
+  const uint32_t least = block_kth_largest_u32(s_gm, nval, min(a.k, nval), s_min, tid);   // its barriers publish s_red
   const float T = (ngrp < a.k) ? -INFINITY : unord32(least);
   float total = 0.f;
 #pragma unroll

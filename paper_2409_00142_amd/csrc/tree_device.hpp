@@ -171,40 +171,6 @@ __device__ __forceinline__ void count_larger_keys(const uint64_t* keys, int n, i
   }
 }
 
-// The k-th largest of n values (1 <= k <= n), ties counted: the smallest with fewer than k larger ones.  By a block of 1024
-// threads, n <= 1024; vals: 16-byte aligned LDS, padded with zeros to a multiple of four; cnt: LDS [n], any contents; red:
-// LDS [16].  32-bit compares against values that the whole wave reads from one address, four at a time (two instructions
-// a compare; 500 values 3.3 us on a CU), a value per P threads.  The block barriers inside also order the caller's writes of
-// vals before and its reuse of cnt after.
-__device__ __forceinline__ int count_larger4(const uint4& v, uint32_t mine) {
-  return (v.x > mine ? 1 : 0) + (v.y > mine ? 1 : 0) + (v.z > mine ? 1 : 0) + (v.w > mine ? 1 : 0);
-}
-__device__ __forceinline__ uint32_t block_kth_largest_u32(const uint32_t* vals, int n, int k, int* cnt, uint32_t* red, int tid) {
-  constexpr int kThr = 1024;
-  const int n4 = (n + 3) >> 2, lane = tid & 63, wave = tid >> 6;
-  const uint4* v4 = reinterpret_cast<const uint4*>(vals);
-  if (tid < n) cnt[tid] = 0;
-  __syncthreads();
-  const int P = kThr / n, part = tid / n, i = tid - part * n;
-  if (part < P) {
-    const int chunk = (n4 + P - 1) / P, lo = part * chunk, hi = min(n4, lo + chunk);
-    const uint32_t mine = vals[i];
-    int c = 0;
-    for (int q = lo; q < hi; ++q) c += count_larger4(v4[q], mine);
-    if (c != 0) atomicAdd(&cnt[i], c);
-  }
-  __syncthreads();
-  uint32_t least = 0xFFFFFFFFu;
-  if (tid < n && cnt[tid] < k) least = vals[tid];
-  least = ~wave_max_u32(~least);
-  if (lane == 0) red[wave] = least;
-  __syncthreads();
-  least = red[0];
-#pragma unroll
-  for (int w = 1; w < kThr / 64; ++w) least = min(least, red[w]);
-  return least;
-}
-
 // The largest prefix of an ordered 32-bit key that at least `want` of the wave's keys reach, found bit by bit (a compare and a scalar
 // popcount per slot), and no further than one that exactly `want` reach.
 template <int S>
@@ -220,6 +186,30 @@ __device__ __forceinline__ uint32_t wave_prefix(const uint32_t (&key)[S], int wa
   }
   return T;
 }
+// The k-th largest of n values (1 <= k <= n <= 512), ties counted: the smallest with fewer than k larger ones.  vals: LDS; red: LDS [1].
+// By wave 0 alone; the block barriers also order the caller's writes of vals before and its reuse of them after.  (Counting by the
+// whole block, 32-bit compares against values that a wave reads from one address: 500 values 3.3 us on a CU; now 1.3.)
+template <int S>
+__device__ __forceinline__ uint32_t wave_kth_largest(const uint32_t* vals, int n, int k, int lane) {
+  uint32_t key[S];
+#pragma unroll
+  for (int q = 0; q < S; ++q) key[q] = 64 * q + lane < n ? vals[64 * q + lane] : 0u;
+  const uint32_t T = wave_prefix<S>(key, k);
+  uint32_t least = 0xFFFFFFFFu;            // of the values at or above the prefix
+#pragma unroll
+  for (int q = 0; q < S; ++q) least = (64 * q + lane < n && key[q] >= T) ? min(least, key[q]) : least;
+  return ~wave_max_u32(~least);
+}
+__device__ __forceinline__ uint32_t block_kth_largest_u32(const uint32_t* vals, int n, int k, uint32_t* red, int tid) {
+  __syncthreads();
+  if (tid < 64) {
+    const uint32_t least = n <= 256 ? wave_kth_largest<4>(vals, n, k, tid) : wave_kth_largest<8>(vals, n, k, tid);
+    if (tid == 0) red[0] = least;
+  }
+  __syncthreads();
+  return red[0];
+}
+
 // By one wave: the tree indices of the `want` best of nodes 1 .. n (n <= 64 S, keys[i] the rerank key of node i + 1), i.e. 1 + the
 // number of taken nodes with a smaller id, to tidx, and their ids to sel.  Of equal scores the lowest ids are taken.
 template <int S>

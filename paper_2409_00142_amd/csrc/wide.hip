@@ -8,7 +8,8 @@
 // (8-bit digits from the top: histogram in LDS, the digit holding the wanted rank narrows the prefix).  The final rerank
 // selects the m best pool nodes the same way from the scores in global memory.  At k = 100, V = 32000, B = 1: 31 -> 16 us
 // a call, 73 -> 32 us for the call that builds the final tree (with the candidates formed here and the 64-bit radix
-// select and counting over 512 keys).  Everything else (Eq. 1 in fp64 in index order, parents, ancestor rows, mask) is as
+// select and counting over 512 keys), 14 and 28 with the bound found by one wave, the sample taken from the rows' keys and
+// the keys requested before the sequence's flag is known.  Everything else (Eq. 1 in fp64 in index order, parents, ancestor rows, mask) is as
 // for narrow beams.
 #include "bookkeep_device.hpp"
 #include "tree_device.hpp"
@@ -35,7 +36,7 @@ struct WideSmem {
   float lps_old[kKW];
   int node_old[kKW];
   uint64_t sel[kKW];
-  uint32_t red[16];
+  uint32_t red[1];
   TreeEmitSmem te;
 };
 
@@ -213,22 +214,22 @@ __device__ __forceinline__ void tree_finalize_wide_block(const ddd_state& st, co
   if (m_eff < N && nthr == kWideThreads) {                           // uniform
     constexpr int kFirst = 256;
     static_assert(kFirst >= DDD_MMAX && 2 * kFirst <= 2 * kWSub, "the sample holds m scores and lies in front of the candidates");
-    uint32_t* first = reinterpret_cast<uint32_t*>(work);             // [kFirst + 4]
-    int* cnt = reinterpret_cast<int*>(first + kFirst + 4);           // [kFirst]
+    uint32_t* first = reinterpret_cast<uint32_t*>(work);             // [kFirst]
     const int n_first = min(N, kFirst);
-    for (int i = tid; i < ((n_first + 3) & ~3); i += nthr) first[i] = (i < n_first) ? ord32(psc[i + 1]) : 0u;
+    for (int i = tid; i < n_first; i += nthr) first[i] = ord32(psc[i + 1]);
     for (int i = tid; i < kWCand; i += nthr) rank[i] = 0;
     if (tid == 0) sm.cnt = 0;
     __syncthreads();
     // Compared as ordered bits, a total order: at least the m_eff scores of the sample that made the bound pass it, whatever
     // they are (a NaN, from a row whose largest logit is infinite, would fail every comparison of floats).
-    const uint32_t bound = block_kth_largest_u32(first, n_first, m_eff, cnt, sm.red, tid);
-    for (int i0 = tid; i0 < N; i0 += 16 * kWideThreads) {
-      float x[16];
+    const uint32_t bound = block_kth_largest_u32(first, n_first, m_eff, sm.red, tid);
+    constexpr int kSweep = 16;
+    for (int i0 = tid; i0 < N; i0 += kSweep * kWideThreads) {
+      float x[kSweep];
 #pragma unroll
-      for (int u = 0; u < 16; ++u) x[u] = psc[min(i0 + u * kWideThreads, N - 1) + 1];   // no branch: all in flight
+      for (int u = 0; u < kSweep; ++u) x[u] = psc[min(i0 + u * kWideThreads, N - 1) + 1];   // no branch: all in flight
 #pragma unroll
-      for (int u = 0; u < 16; ++u)
+      for (int u = 0; u < kSweep; ++u)
         if (ord32(x[u]) >= bound && i0 + u * kWideThreads < N) {
           const int p = atomicAdd(&sm.cnt, 1);
           if (p < kWCand) cand[p] = rerank_key(x[u], i0 + u * kWideThreads + 1);
@@ -307,7 +308,25 @@ __device__ __forceinline__ bool step_wide_block(const WideStepArgs& a, unsigned 
   const int b = blockIdx.x, tid = threadIdx.x, nthr = blockDim.x;
   const int k = g.k, step = g.step;
   WideSmem& sm = *reinterpret_cast<WideSmem*>(wsm_raw + wide_front_bytes(k));
-  if (!g.st.active[b]) return false;         // uniform over the workgroup
+  const bool from_keys = (a.part_key != nullptr);
+  const size_t row0 = (step == 0) ? (size_t)b : (size_t)b * k;
+  // The candidates' beam keys that the row reduction has formed, element f = tid + u * 1024, and the rows' first few of them (below):
+  // on their way before the sequence's flag is looked at.
+  constexpr int kPer = kKW * kKW / kWideThreads;
+  uint64_t kv[kPer], mine = 0ull;
+  uint32_t* sample = reinterpret_cast<uint32_t*>(wsm_raw);       // [kWSub]
+  const int per_row = min(k, max(1, 320 / k)), n_sample = k * per_row;
+  const int on_flag = g.st.active[b];
+  if (a.do_select && step > 0 && from_keys) {                    // uniform
+    const int i = tid / per_row;                                 // n_sample <= 320
+    if (tid < n_sample) mine = a.part_key[row0 * k + i * k + (tid - i * per_row)];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int f = u * kWideThreads + tid;
+      kv[u] = (f < k * k) ? a.part_key[row0 * k + f] : 0ull;
+    }
+  }
+  if (!on_flag) return false;                // uniform over the workgroup
 
   float* lps = g.st.logprobsum + (size_t)b * k;
   int32_t* bnode = g.st.beam_node + (size_t)b * k;
@@ -317,8 +336,6 @@ __device__ __forceinline__ bool step_wide_block(const WideStepArgs& a, unsigned 
   int32_t* ppar = g.st.pool_parent + (size_t)b * g.nmax;
   int32_t* pdep = g.st.pool_depth + (size_t)b * g.nmax;
   float* psc = g.st.pool_score + (size_t)b * g.nmax;
-  const bool from_keys = (a.part_key != nullptr);
-  const size_t row0 = (step == 0) ? (size_t)b : (size_t)b * k;
   int steps_done = a.steps_done;
 
   if (a.do_select) {
@@ -355,15 +372,9 @@ __device__ __forceinline__ bool step_wide_block(const WideStepArgs& a, unsigned 
       const int base = 1 + k + (step - 1) * k * k, kk = k * k;
       if (a.lse_dbg != nullptr && from_keys)
         for (int i = tid; i < k; i += nthr) a.lse_dbg[row0 + i] = a.part_lse[row0 + i];
-      // every candidate's beam key, element f = tid + u * 1024: formed by the row reduction, or here from the caller's rows
-      constexpr int kPer = kKW * kKW / kWideThreads;
-      uint64_t kv[kPer];
+      // every candidate's beam key: formed by the row reduction, or here from the caller's rows
       if (from_keys) {
-#pragma unroll
-        for (int u = 0; u < kPer; ++u) {
-          const int f = u * kWideThreads + tid;
-          kv[u] = (f < kk) ? a.part_key[row0 * k + f] : 0ull;
-        }
+        if (tid < n_sample) sample[tid] = (uint32_t)(mine >> 32);
       } else {
         for (int i = tid; i < k; i += nthr) {
           sm.lps_old[i] = lps[i];
@@ -392,6 +403,7 @@ __device__ __forceinline__ bool step_wide_block(const WideStepArgs& a, unsigned 
               pdep[base + f] = step + 1;
               psc[base + f] = sc;
               kv[u0 + u] = wide_beam_key(sc, t[u], f);
+              if (f - i * k < per_row) sample[i * per_row + f - i * k] = (uint32_t)(kv[u0 + u] >> 32);
             }
           }
         }
@@ -399,30 +411,25 @@ __device__ __forceinline__ bool step_wide_block(const WideStepArgs& a, unsigned 
       // The new beam: the k-th best score of the rows' first few candidates is a lower bound of the beam's scores (a row's
       // logprobs fall), the keys at or above it - k and a few more - are ranked by counting.  Three per row at k = 100: the
       // comparisons of a larger sample cost more than the candidates it spares.
-      uint32_t* sample = reinterpret_cast<uint32_t*>(wsm_raw);   // [kWSub]
-      int* cnt = reinterpret_cast<int*>(sample + kWSub);         // [kWSub]
-      uint64_t* cand = reinterpret_cast<uint64_t*>(cnt + kWSub); // [kWCand]
+      uint64_t* cand = reinterpret_cast<uint64_t*>(sample + 2 * kWSub); // [kWCand]
       int* rank = reinterpret_cast<int*>(cand + kWCand);         // [kWCand]
-      const int per_row = min(k, max(1, 320 / k)), n_sample = k * per_row;
-#pragma unroll
-      for (int u = 0; u < kPer; ++u) {
-        const int f = u * kWideThreads + tid, i = f / k, j = f - i * k;
-        if (f < kk && j < per_row) sample[i * per_row + j] = (uint32_t)(kv[u] >> 32);
-      }
-      if (tid < 4) sample[n_sample + tid] = 0u;
       for (int i = tid; i < kWCand; i += nthr) rank[i] = 0;
       if (tid == 0) sm.cnt = 0;
       __syncthreads();
-      const uint32_t bound = block_kth_largest_u32(sample, n_sample, k, cnt, sm.red, tid);
+      const uint32_t bound = block_kth_largest_u32(sample, n_sample, k, sm.red, tid);
+      auto passes = [&](int u) { return kv[u] != 0ull && (uint32_t)(kv[u] >> 32) >= bound; };
+      int at = 0;                                                 // of this wave's candidates: one look at the counter
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) at += __popcll(__ballot(passes(u)));
+      if ((tid & 63) == 0 && at != 0) at = atomicAdd(&sm.cnt, at);
+      at = __builtin_amdgcn_readfirstlane(at);
 #pragma unroll
       for (int u = 0; u < kPer; ++u) {
-        const bool in = kv[u] != 0ull && (uint32_t)(kv[u] >> 32) >= bound;
+        const bool in = passes(u);
         const unsigned long long bal = __ballot(in);
-        if (bal == 0ull) continue;                                // wave-uniform
-        int at = 0;
-        if ((tid & 63) == 0) at = atomicAdd(&sm.cnt, __popcll(bal));
-        const int p = __builtin_amdgcn_readfirstlane(at) + __popcll(bal & ((1ull << (tid & 63)) - 1ull));
+        const int p = at + __popcll(bal & ((1ull << (tid & 63)) - 1ull));
         if (in && p < kWCand) cand[p] = kv[u];
+        at += __popcll(bal);
       }
       __syncthreads();
       const int C = sm.cnt;
