@@ -33,48 +33,16 @@ hipError_t launch_merge(const MergeArgs& a, hipStream_t stream) {
 
 // ---- row reduction of materialised logits (GEMM path) ------------------------------------------
 // One workgroup per row.  The GEMM left, for every group of 64 consecutive vocabulary rows, the
-// group's max and sum of exponentials.  lse follows from those alone.  The k-th largest group max
-// T is a lower bound of the row's k-th largest logit (k distinct elements are >= T), and only the
+// group's max and sum of exponentials.  lse follows from those alone.  The k-th largest of the threads' maxima (of one to eight
+// groups each) is a lower bound T of the row's k-th largest logit (k distinct elements are >= T), and only the
 // groups whose max reaches T - k of them, or a few more - can hold an element >= T: those groups'
 // logits are read (64 values each), the candidates >= T collected, and the exact top-k by (logit
-// desc, token asc) taken among them (a candidate's rank is the number of larger keys).  Massive ties (e.g. constant logits) overflow the lists: with
-// too many candidate groups the whole row is scanned instead, and with too many candidates an
+// desc, token asc) taken among them (a candidate's rank is the number of larger keys).  Massive ties (e.g. constant logits) overflow
+// the lists: with too many candidate groups the whole row is scanned instead, and with too many candidates an
 // exact but slow path takes over: k passes over the row, each finding the largest key below the
 // previous winner.
 constexpr int kCandMax = 2048;
 constexpr int kGrpListMax = 256;   // groups that may hold a candidate; more than that: the row is scanned
-
-// k-th largest of the group maxima as an ordered key (0 if there are fewer than k groups), by one
-// wave: lane holds groups lane, lane + 64, ... (S slots).
-template <int S>
-__device__ __forceinline__ uint32_t kth_largest_group_max(const float* gmax, int ngrp_valid, int k, int lane) {
-  uint32_t loc[S];
-#pragma unroll
-  for (int i = 0; i < S; ++i) {
-    const int g = lane + 64 * i;
-    loc[i] = (g < ngrp_valid) ? ord32(gmax[g]) : 0u;
-  }
-  uint32_t T = 0u;
-  for (int round = 0; round < k; ++round) {
-    uint32_t lm = 0u;
-#pragma unroll
-    for (int i = 0; i < S; ++i) lm = umax32(lm, loc[i]);
-    T = wave_max_u32(lm);
-    if (T == 0u) break;                                    // uniform: fewer than k groups
-    // remove one holder of the maximum (the lowest lane, its lowest slot)
-    const unsigned long long holders = __ballot(lm == T);
-    if (lane == __ffsll((long long)holders) - 1) {
-      bool done = false;
-#pragma unroll
-      for (int i = 0; i < S; ++i)
-        if (!done && loc[i] == T) {
-          loc[i] = 0u;
-          done = true;
-        }
-    }
-  }
-  return T;
-}
 
 // The rank-j key of a row of logits, in the form the launch's caller wants it.  For a wide beam inside a draft call the row
 // also forms its candidates of the beam update (Algorithm 1's next summed logprobs) - with k * k of them per sequence that is
@@ -120,84 +88,57 @@ struct RowEmit {
   }
 };
 
+// S: groups per thread (V <= 64 * 256 * S).  Their statistics are asked for once, all together, and stay in registers: five loops over
+// the groups in memory were five chains of round trips (V = 128256, 128 rows, k = 16: 22.7 us a launch, now 9; V = 32000: 7.5, now 5.8).
+template <int S>
 __global__ __launch_bounds__(256) void row_topk_kernel(RowTopkArgs a) {
   __shared__ uint64_t s_cand[kCandMax];
   __shared__ float s_red[8];
-  __shared__ float s_T;
   __shared__ int s_cnt, s_ng;
   __shared__ int s_glist[kGrpListMax];
-  __shared__ uint32_t s_bound[4];
+  __shared__ uint32_t s_max[256], s_least[1];
   const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (a.row_active != nullptr && !a.row_active[row]) return;   // uniform
+  const int on = a.row_active != nullptr ? a.row_active[row] : 1;   // looked at behind the loads of the row's groups
   RowEmit<false> emit(a, row);
   const int ngrp_valid = (a.V + 63) >> 6;
   const float* gmax = a.grp_max + (size_t)row * a.ngrp;
   const float* gsum = a.grp_sum + (size_t)row * a.ngrp;
+  float gm[S], gs[S];                                          // of groups tid + 256 i; past the last: -inf, 0
+#pragma unroll
+  for (int i = 0; i < S; ++i) {
+    const int g = tid + 256 * i;
+    gm[i] = g < ngrp_valid ? gmax[g] : -INFINITY;
+    gs[i] = g < ngrp_valid ? gsum[g] : 0.f;
+  }
+  if (on == 0) return;                                         // uniform
 
   // ---- row max, lse ---------------------------------------------------------------------------
   float m = -INFINITY;
-  for (int g = tid; g < ngrp_valid; g += 256) m = fmaxf(m, gmax[g]);
+#pragma unroll
+  for (int i = 0; i < S; ++i) m = fmaxf(m, gm[i]);
   m = wave_max_f32(m);
   if (lane == 0) s_red[wave] = m;
   __syncthreads();
   const float M = fmaxf(fmaxf(s_red[0], s_red[1]), fmaxf(s_red[2], s_red[3]));
   float acc = 0.f;
-  for (int g = tid; g < ngrp_valid; g += 256) acc += gsum[g] * __expf(gmax[g] - M);
+#pragma unroll
+  for (int i = 0; i < S; ++i)
+    if (tid + 256 * i < ngrp_valid) acc += gs[i] * __expf(gm[i] - M);
   acc = wave_sum_f32(acc);
   if (lane == 0) s_red[4 + wave] = acc;
-  // ---- T = k-th largest group max (or -inf if there are fewer than k groups): wave 0 -------------
+  // ---- T: the k-th largest of the threads' maxima (or -inf if there are fewer than k), reached by k groups at least ----
+  uint32_t tm = 0u;
+#pragma unroll
+  for (int i = 0; i < S; ++i)
+    if (tid + 256 * i < ngrp_valid) tm = umax32(tm, ord32(gm[i]));
+  s_max[tid] = tm;
   if (tid == 0) {
     s_cnt = 0;
     s_ng = 0;
   }
-  {
-    // Up to 2048 groups (V <= 131072), up to 8 per thread, as ordered keys.  A lower bound first: a quad of lanes
-    // holds 4 to 32 groups, and the k-th largest of a wave's 16 quad maxima is reached by k distinct groups (k <= 16);
-    // the best of the four waves' bounds is taken.  The group maxima at or above it - a few dozen - are ranked by
-    // counting, and the one of rank k - 1 is T.  (k rounds of a wave maximum on one wave took three times as long.)
-    uint32_t tm = 0u;
-    for (int g = tid; g < ngrp_valid; g += 256) tm = umax32(tm, ord32(gmax[g]));
-    uint32_t qm = umax32(tm, dpp_move_u32<0xB1>(tm));
-    qm = umax32(qm, dpp_move_u32<0x4E>(qm));
-    int larger = 0;
-#pragma unroll
-    for (int q = 0; q < 16; ++q) larger += ((uint32_t)__builtin_amdgcn_readlane((int)qm, 4 * q) > qm) ? 1 : 0;
-    const uint32_t bound_w = ~wave_max_u32(~(larger < a.k ? qm : 0xFFFFFFFFu));
-    if (lane == 0) s_bound[wave] = bound_w;
-    __syncthreads();
-    const uint32_t bound = umax32(umax32(s_bound[0], s_bound[1]), umax32(s_bound[2], s_bound[3]));
-    for (int g = tid; g < ngrp_valid; g += 256) {
-      const uint32_t v = ord32(gmax[g]);
-      if (v >= bound) {
-        const int p = atomicAdd(&s_ng, 1);
-        if (p < kCandMax) s_cand[p] = ((uint64_t)v << 32) | (uint32_t)(0xFFFFFFFFu - (uint32_t)g);   // distinct
-      }
-    }
-    __syncthreads();
-    const int ncg = s_ng;
-    __syncthreads();                                             // everybody has the count: the counter is used again below
-    if (ncg <= 256) {                                            // uniform
-      if (tid < ncg) {
-        const uint64_t mine = s_cand[tid];
-        int rank = 0;
-        for (int j = 0; j < ncg; ++j) rank += (s_cand[j] > mine) ? 1 : 0;
-        if (rank == a.k - 1) s_T = unord32((uint32_t)(mine >> 32));
-      }
-      if (tid == 0) {
-        if (ncg < a.k) s_T = -INFINITY;                          // fewer than k groups
-        s_ng = 0;
-      }
-    } else if (wave == 0) {                                      // many equal maxima: the rounds
-      const uint32_t T = (ngrp_valid <= 512)    ? kth_largest_group_max<8>(gmax, ngrp_valid, a.k, lane)
-                         : (ngrp_valid <= 1024) ? kth_largest_group_max<16>(gmax, ngrp_valid, a.k, lane)
-                                                : kth_largest_group_max<32>(gmax, ngrp_valid, a.k, lane);
-      if (lane == 0) {
-        s_T = (T == 0u) ? -INFINITY : unord32(T);
-        s_ng = 0;
-      }
-    }
-  }
-  __syncthreads();
+  const int nval = min(ngrp_valid, 256);
+  const uint32_t least = block_kth_largest_u32(s_max, nval, min(a.k, nval), s_least, tid);   // its barriers publish s_red
+  const float T = nval < a.k ? -INFINITY : unord32(least);
   const float lse = M + __logf(s_red[4] + s_red[5] + s_red[6] + s_red[7]);
   emit.lse = lse;
   if (tid == 0) emit.row_lse();
@@ -206,11 +147,11 @@ __global__ __launch_bounds__(256) void row_topk_kernel(RowTopkArgs a) {
   // Only groups whose max reaches T can hold one: usually k or a few more of them, so the row's
   // logits are read group by group (64 consecutive values, one per lane) rather than scanned.
   const float* x = a.logits + (size_t)row * a.ldl;
-  const float T = s_T;
-  for (int g = tid; g < ngrp_valid; g += 256)
-    if (gmax[g] >= T) {
+#pragma unroll
+  for (int i = 0; i < S; ++i)
+    if (tid + 256 * i < ngrp_valid && gm[i] >= T) {
       const int p = atomicAdd(&s_ng, 1);
-      if (p < kGrpListMax) s_glist[p] = g;
+      if (p < kGrpListMax) s_glist[p] = tid + 256 * i;
     }
   __syncthreads();
   const int ng = s_ng;
@@ -443,8 +384,12 @@ __global__ __launch_bounds__(kWideRowThreads) void row_topk_wide_kernel(RowTopkA
 hipError_t launch_row_topk(const RowTopkArgs& a, hipStream_t stream) {
   if (a.k > DDD_KMAX)
     hipLaunchKernelGGL(row_topk_wide_kernel, dim3(a.n_rows), dim3(kWideRowThreads), 0, stream, a);
+  else if (a.V <= 64 * 256 * 2)
+    hipLaunchKernelGGL(row_topk_kernel<2>, dim3(a.n_rows), dim3(256), 0, stream, a);
+  else if (a.V <= 64 * 256 * 4)
+    hipLaunchKernelGGL(row_topk_kernel<4>, dim3(a.n_rows), dim3(256), 0, stream, a);
   else
-    hipLaunchKernelGGL(row_topk_kernel, dim3(a.n_rows), dim3(256), 0, stream, a);
+    hipLaunchKernelGGL(row_topk_kernel<8>, dim3(a.n_rows), dim3(256), 0, stream, a);
   return hipGetLastError();
 }
 

@@ -82,3 +82,43 @@ def test_products_of_every_tile(V, R, packed):
     for a, b in zip(outs[0], outs[1]):
         assert torch.equal(a[on], b[on])
         assert not bool(b[~on].any())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["random", "equal", "few_groups", "rising"])
+@pytest.mark.parametrize("V,k", [(17, 16), (64, 16), (960, 16), (1024, 16), (16384, 16), (16385, 1), (32768, 16), (32769, 10), (65536, 16),
+                                 (65537, 5), (131072, 16)])
+def test_row_reduction_of_any_vocabulary(V, k, kind):
+    """The reduction's slots per thread and its bound from fewer, as many and more groups than threads and beams: the k best of the
+    logits that the same call writes out (ties to the lower token), and the log-sum-exp in 64 bits to 1e-4.  "equal" and
+    "few_groups": more candidates than the lists hold; "rising": all of the best in the last groups."""
+    import numpy as np
+    import torch
+    import paper_2409_00142_amd as D
+    print(f"[case] row_reduction V={V} k={k} {kind}", flush=True)
+    H, B = 128, (16 + k) // k + 1
+    R = B * k
+    g = torch.Generator(device="cuda")
+    g.manual_seed(V * 3 + k)
+    W = torch.empty(V, H, dtype=torch.bfloat16, device="cuda").normal_(0, 0.1, generator=g)
+    if kind == "equal":
+        W[:] = W[0]
+    if kind == "few_groups":
+        W[: V // 2] = W[0]
+    if kind == "rising":
+        W[:, 1:] = 0
+        W[:, 0] = torch.linspace(0, 8, V, device="cuda").to(torch.bfloat16)
+    hid = torch.empty(R, H, dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=g)
+    if kind == "rising":
+        hid[:, 0] = 1.0
+    ctx = D.ddd_create(D.make_config(B, H, V, k, 3, 10, 0.3))
+    try:
+        o = (torch.full((R, k), -7, dtype=torch.int32, device="cuda"), torch.zeros(R, k, device="cuda"), torch.zeros(R, device="cuda"))
+        dbg = torch.zeros(R, V, device="cuda")
+        D.ddd_lmhead_topk(ctx, W, hid, R, None, *o, dbg)
+        torch.cuda.synchronize()
+    finally:
+        D.ddd_destroy(ctx)
+    logits = dbg.cpu().numpy()
+    assert np.array_equal(o[0].cpu().numpy(), np.argsort(-logits, axis=1, kind="stable")[:, :k])
+    assert float((o[2].double() - torch.logsumexp(dbg.double(), 1)).abs().max()) < 1e-4
