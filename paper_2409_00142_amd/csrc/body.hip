@@ -54,6 +54,14 @@ __global__ __launch_bounds__(704) void linear_stream_kernel(LinearArgs a) {
   const int NW = a.nw;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
 
+  // In front of the first request for W, though that costs each launch that does run a look at the flags: a launch that every row
+  // skips (calls enqueued behind a round's end, most of a captured round's) would read 45 MB for nothing.  Rounds of 3.45 calls with
+  // the check behind the first tile and in front of it: 734 and 706 us paced by the host, 1026 and 811 captured; three calls of
+  // which none is skipped 395 and 402.
+  if (a.row_active != nullptr) {   // uniform
+    const int on = (lane < a.R) ? a.row_active[lane] : 0;
+    if (__ballot(on != 0) == 0ull) return;
+  }
   const int nslice = gridDim.x, slice = blockIdx.x;
   // Output rows are dealt to the workgroups in units of 4 (an epilogue lane's outputs, and whole gate/up
   // pairs), not in tiles of 16: every workgroup streams the same number of weight rows; a slice's last tile
@@ -65,7 +73,6 @@ __global__ __launch_bounds__(704) void linear_stream_kernel(LinearArgs a) {
   float* red = reinterpret_cast<float*>(smem);      // [2][NW][256] fp32 partial tiles
   unsigned char* stage = smem + 2 * NW * 1024;      // [NW][kStageBytes]
   int* s_src = reinterpret_cast<int*>(stage + NW * kStageBytes);   // [kLinearRanges][16] source rows of the gathered input rows
-  int* s_any = s_src + kLinearRanges * 16;          // whether any row is active
 
   const int NR = a.n_ranges;
   const int total = nt * NR;          // (tile, range) steps of this workgroup, ranges innermost
@@ -113,12 +120,10 @@ __global__ __launch_bounds__(704) void linear_stream_kernel(LinearArgs a) {
           bfrag[g][j] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(xp + g * 128 + j * 32));
         }
     };
-    // What the epilogue wave has looked up arrives through LDS: loads return in order, so a look at the row flags or at an index by
-    // this wave would wait for the whole first tile, and the input rows would be requested behind it.
-    if (!MULTI) load_x();
-    lds_barrier();
-    if (*s_any == 0) return;           // uniform: no row is active (what was requested is dropped)
-    if (MULTI) load_x();
+    // What the epilogue wave has looked up arrives through LDS: loads return in order, so a look at an index by this wave would
+    // wait for the whole first tile, and the input rows would be requested behind it.
+    if (MULTI) lds_barrier();
+    load_x();
 #pragma unroll 1
     for (int it = 0; it < total; ++it) {
       __builtin_amdgcn_sched_barrier(0);   // the previous step's operands are dead before the next ones are requested
@@ -152,10 +157,7 @@ __global__ __launch_bounds__(704) void linear_stream_kernel(LinearArgs a) {
         if (vb == 0) s_src[g * 16 + r] = src;
       }
     }
-    const bool any = __ballot(active) != 0ull;
-    if (lane == 0) *s_any = any ? 1 : 0;
-    lds_barrier();
-    if (!any) return;
+    if (MULTI) lds_barrier();
     for (int t = 0; t < nt; ++t) {
       const int v0 = n0 + t * 16 + vb * 4;
       float* const yp = a.y + (size_t)r * a.ldy + v0;
@@ -201,7 +203,7 @@ __global__ __launch_bounds__(704) void linear_stream_kernel(LinearArgs a) {
 template <int G>
 static hipError_t launch_linear_g(const LinearArgs& a, int nslice, hipStream_t stream) {
   const dim3 grid(nslice), block((a.nw + 1) * 64);
-  const size_t lds = (size_t)2 * a.nw * 1024 + (size_t)a.nw * kStageBytes + (kLinearRanges * 16 + 4) * sizeof(int);
+  const size_t lds = (size_t)2 * a.nw * 1024 + (size_t)a.nw * kStageBytes + kLinearRanges * 16 * sizeof(int);
   if (a.n_ranges > 1 || a.last_units < a.nw * G || a.rg[0].gather_mode != kGatherNone)
     hipLaunchKernelGGL((linear_stream_kernel<G, true>), grid, block, lds, stream, a);
   else
