@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "ddd_kernels.hpp"
+#include "tree_attn_plan.hpp"
 
 using namespace ddd;
 
@@ -435,16 +436,11 @@ int ddd_weights_pack(ddd_ctx* c, const void* W, void* stream) {
   return DDD_OK;
 }
 
-namespace {
-int attn_splits(const ddd_ctx* c, int n_heads, int L) {
-  return tree_attention_splits(c->cfg.B, n_heads, c->cfg.m + 1, L, c->n_cu);
-}
-}  // namespace
-
 size_t ddd_tree_attention_workspace(const ddd_ctx* c, int32_t n_heads, int32_t L) {
   if (c == nullptr || n_heads < 1 || L < 0) return 0;
-  const size_t nqt = (size_t)(c->cfg.m + 1 + 63) / 64;
-  return (size_t)c->cfg.B * n_heads * nqt * attn_splits(c, n_heads, L) * tree_attention_part_floats() * sizeof(float);
+  const size_t nqt = (size_t)(c->cfg.m + 1 + kQT - 1) / kQT;
+  const int nsplit = tree_attention_splits(c->cfg.B, n_heads, c->cfg.m + 1, L, c->n_cu);
+  return (size_t)c->cfg.B * n_heads * nqt * nsplit * tree_attention_part_floats() * sizeof(float);
 }
 
 int ddd_kv_pack(ddd_ctx* c, const void* k, const void* v, int32_t L, int32_t n_heads, void* k_packed, void* v_packed,
@@ -481,7 +477,6 @@ int ddd_tree_attention(ddd_ctx* c, const ddd_tree* tree, const void* q, const vo
   a.nh = n_heads;
   a.L = L;
   a.Tp = (a.T + 31) & ~31;
-  a.nsplit = attn_splits(c, n_heads, L);
   DDD_HIP(launch_tree_attention(a, c->n_cu, static_cast<hipStream_t>(stream)));
   return DDD_OK;
 }

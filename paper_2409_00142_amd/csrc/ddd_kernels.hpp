@@ -241,15 +241,15 @@ struct TreeAttnArgs {
   const uint16_t* v_prompt;   // bf16, the same shape: prompt values in fragment order
   const uint8_t* mask;        // [B][T][T]
   const int32_t* n_sel;       // [B]
-  float* part;                // workspace: [B][nh][query tiles][nsplit][tree_attention_part_floats()]
+  float* part;                // workspace: [B][nh][query tiles][nsplit][tree_attention_part_floats()]; room for tree_attention_splits()
   float* out;                 // fp32 [B][T][nh][128]
-  int B, T, nh, L, Tp, nsplit;
+  int B, T, nh, L, Tp;
+  int nsplit;                 // set by the launcher
 };
 // k, v: bf16 [B][L][nh][128] -> the fragment-order cache the attention reads (each ceil(L/32)*32*nh*128*B elements)
 hipError_t launch_kv_pack(const uint16_t* k, const uint16_t* v, uint16_t* kp, uint16_t* vp, int B, int L, int nh,
                           hipStream_t stream);
 size_t tree_attention_part_floats();
-int tree_attention_splits(int B, int n_heads, int T, int L, int n_cu);   // TreeAttnArgs::nsplit
-hipError_t launch_tree_attention(const TreeAttnArgs& a, int n_cu, hipStream_t stream);
+hipError_t launch_tree_attention(TreeAttnArgs a, int n_cu, hipStream_t stream);
 
 }  // namespace ddd

@@ -20,10 +20,9 @@
 // not the 8 consecutive keys a B operand wants; the second product simply contracts over the keys
 // in that order, by loading V^T as two 4-key pieces per operand.
 // Where a head is split over workgroups, a second kernel merges their partials.
-#include <algorithm>
-
 #include "ddd_device.hpp"
 #include "ddd_kernels.hpp"
+#include "tree_attn_plan.hpp"
 
 namespace ddd {
 
@@ -33,7 +32,6 @@ typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
 
 constexpr int kAD = 128;        // head dimension
-constexpr int kQT = 64;         // queries per tile
 constexpr int kPartFloats = kAD * kQT + 2 * kQT;   // one partial: O^T[128][64], m[64], l[64]
 constexpr int kOutPitch = kAD + 4;                 // O[query][d] in LDS at the end: rows padded, 16 bytes aligned
 // Waves of a workgroup = chunks of 32 keys of a step: a wave of four sums a quarter of the head for all 64 queries, one of
@@ -56,19 +54,6 @@ typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {   // round to nearest even (one v_cvt_pk_bf16_f32)
   const f32x2 f = {lo, hi};
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2));
-}
-
-// Steps of a head: the prompt's whole ones, then the rest of its keys and the tree's (chunks of 32, the last of either ragged).
-struct AttnSteps {
-  int full, rest_prompt, rest, all;   // whole steps; chunks of the rest from the prompt, in all; steps in all
-};
-__host__ __device__ __forceinline__ AttnSteps attn_steps(int L, int T, int nw) {
-  AttnSteps n;
-  n.full = L / (32 * nw);
-  n.rest_prompt = (L - n.full * 32 * nw + 31) / 32;
-  n.rest = n.rest_prompt + (T + 31) / 32;
-  n.all = n.full + (n.rest + nw - 1) / nw;
-  return n;
 }
 
 // Operands of one step for one wave.
@@ -404,7 +389,6 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void tree_attn_partial_ke
 // there is one reference, nothing is rescaled, and every load of the pass is on its way before the first product.
 // L = 1999, 32 heads, one user: 24.0 -> 18.9 us with the merge, 1.7 of it by reading the mask four keys at a time.  (Nine workgroups a
 // head instead, two to a CU: 26.3.)
-constexpr int kPassChunks = 16;
 
 __global__ __launch_bounds__(512, 2) void tree_attn_pass_kernel(TreeAttnArgs a, int per) {
   constexpr int NW = 8, kLdsQ = AttnCfg<NW>::kLdsQ;
@@ -632,35 +616,14 @@ hipError_t launch_kv_pack(const uint16_t* k, const uint16_t* v, uint16_t* kp, ui
 
 size_t tree_attention_part_floats() { return (size_t)kPartFloats; }
 
-// Waves per workgroup.  Few tiles (one to four users): eight, one workgroup per CU - a step is 256 keys, so a head needs half as many
-// splits and partials.  Otherwise four: three workgroups fit a CU, and every value is read by one wave instead of two.
-// 32 heads, L = 1999 / 1500 / 700 / 2048 with 1 / 4 / 9 / 64 users, eight against four: 22.8 / 34.9 / 41.9 / 441 us against
-// 24.9 / 35.8 / 32.3 / 426 (27.5 / 49.9 / 57.7 / 493 with a whole output tile per wave and merges through LDS); all without the
-// weights' low halves, which cost one user 1.6 us and 64 users nothing.
-static int attn_waves(long long tiles, int n_cu) { return 2 * tiles <= n_cu ? 8 : 4; }
-static long long attn_tiles(int B, int n_heads, int T) { return (long long)B * n_heads * ((T + kQT - 1) / kQT); }
-
-// Chunks of 32 keys per workgroup where one pass over them takes the place of several steps, or 0.
-static int attn_pass_chunks(int nw, int nsplit, int T, int L) {
-  const int all = (L + 31) / 32 + (T + 31) / 32, per = (all + nsplit - 1) / nsplit;
-  return nw == 8 && nsplit > 1 && per > 8 && per <= kPassChunks ? per : 0;
-}
-
-// Splits of a head's keys over workgroups: one workgroup of eight waves or two of four per CU, a step each at least.
-int tree_attention_splits(int B, int n_heads, int T, int L, int n_cu) {
-  const long long tiles = attn_tiles(B, n_heads, T);
-  const int nw = attn_waves(tiles, n_cu), most = std::min(attn_steps(L, T, nw).all, 64);
-  const int n = (int)std::min<long long>(std::max<long long>((nw == 8 ? 1 : 2) * n_cu / tiles, 1), most);
-  const int per = attn_pass_chunks(nw, n, T, L);
-  return per > 0 ? ((L + 31) / 32 + (T + 31) / 32 + per - 1) / per : n;   // none without a chunk
-}
-
-hipError_t launch_tree_attention(const TreeAttnArgs& a, int n_cu, hipStream_t stream) {
-  const int nqt = (a.T + kQT - 1) / kQT, nw = attn_waves(attn_tiles(a.B, a.nh, a.T), n_cu), per = attn_pass_chunks(nw, a.nsplit, a.T, a.L);
+hipError_t launch_tree_attention(TreeAttnArgs a, int n_cu, hipStream_t stream) {
+  const AttnLaunch p = attn_launch(a.B, a.nh, a.T, a.L, n_cu);
+  a.nsplit = p.nsplit;
+  const int nqt = (a.T + kQT - 1) / kQT;
   const dim3 grid(a.nsplit * nqt, a.nh, a.B);
-  if (per > 0)
-    hipLaunchKernelGGL(tree_attn_pass_kernel, grid, dim3(512), 0, stream, a, per);
-  else if (nw == 8)
+  if (p.per > 0)
+    hipLaunchKernelGGL(tree_attn_pass_kernel, grid, dim3(512), 0, stream, a, p.per);
+  else if (p.nw == 8)
     hipLaunchKernelGGL(tree_attn_partial_kernel<8>, grid, dim3(64 * 8), 0, stream, a);
   else
     hipLaunchKernelGGL(tree_attn_partial_kernel<4>, grid, dim3(64 * 4), 0, stream, a);

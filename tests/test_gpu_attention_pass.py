@@ -58,3 +58,14 @@ def test_heads_of_one_pass(B, nh, m, L):
         want = torch.matmul(torch.softmax(score.masked_fill(~seen, -math.inf), -1), V).permute(1, 0, 2)
         assert float((outs[0][b, :s].double() - want).abs().max()) <= 1e-4
         assert bool((outs[0][b, s:] == 0).all())
+
+
+@pytest.mark.parametrize("nh,m,L", [(24, 60, 2496), (16, 60, 4032), (8, 127, 3968), (4, 60, 16320)])
+def test_workspace_of_a_longer_prompt(nh, m, L):
+    """The workspace never shrinks as the prompt grows, also where the longer prompt takes its chunks in one pass."""
+    import paper_2409_00142_amd as D
+    ctx = D.ddd_create(D.make_config(1, 256, 1000, 4, 4, m, 0.3))
+    try:
+        assert D.ddd_tree_attention_workspace(ctx, nh, L) <= D.ddd_tree_attention_workspace(ctx, nh, L + 1)
+    finally:
+        D.ddd_destroy(ctx)
