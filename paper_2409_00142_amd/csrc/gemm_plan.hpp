@@ -61,22 +61,26 @@ struct HeadShape {
   int most;     // most blocks of 32 active rows beside a 256-row tile
   float row;    // ns in which the whole chip receives a k tile of one row of W (128 bytes) with 128-row tiles,
   float row2;   // with 256-row tiles
+  float once;   // what a cut of one pass costs beside one of several: calls that walk W in opposite directions find in the memory-side
+                // cache what the call before read last, but a single pass reads all rows at once, along k
   HeadPlan known;   // the plan, where the number of rows is known before the launch (bm = 0: it is not)
 };
-// In ns, fitted to launches of 20 to 640 rows with V = 4000 to 128256 and H = 1024 to 4096: a k tile of a unit costs 240 and 22 per
-// 32 x 32 products (block columns in twos: two waves share them), or what its rows of W take to arrive - 1 us per 256 rows, which the
-// column tiles share, or the whole chip's rate -; the unit's ramp and epilogue 500 and 290 or 3500 and 200 per 32 x 32; the
-// workgroups take the units in passes.  Returns 0 where the combination does not exist.
+// In ns, fitted to 900 calls of 20 to 640 rows with V = 4000 to 128256 and H = 1024 to 5120, walking W in one direction and in
+// alternating ones, each with up to ten cuts (the chosen cut is 0.8 % slower than the best one on average; with whole passes at the
+// chip's rate 2 %, and 37 % at most).  Either the workgroups' passes over the units: a unit's ramp and epilogue are 250 and 210 per
+// 32 x 32 products (block columns in twos: two waves share them) or 3600 and 150, a k tile of it 305 and 26 per 32 x 32, or what its
+// rows of W take to arrive, 1 us per 256 rows, which the column tiles share.  Or, if that is longer, the stream of W through the chip,
+// by the rows that there are - a last pass that is nearly empty streams as little -, and nearly once more for each further column
+// tile: 40 rows at V = 100000, H = 4096 take 200 us with one, 227 with two.  Returns 0 where the combination does not exist.
 __host__ __device__ inline float head_price(const HeadShape& h, int n_act, int bm, int NT) {
   const int nblk = (n_act + 31) >> 5, bpt = (int)((unsigned)(nblk + NT - 1) / (unsigned)NT);
   if (NT > nblk || bpt > (bm == 256 ? h.most : 10)) return 0.f;                                    // tiles of at most 320 rows
   const int nmt = bm == 256 ? (h.V + 255) >> 8 : (h.V + 127) >> 7, passes = (int)((unsigned)(nmt * NT + h.grid - 1) / (unsigned)h.grid);
-  const float each = 1.f / (float)NT;
   const float area = (float)((bm >> 5) * ((bpt + 1) & ~1));
-  const float step = 240.f + 22.f * area, feed = 3.9f * (float)bm * each;
-  const float at_once = fminf((float)nmt, fmaxf((float)h.grid * each, 1.f));                       // row tiles in a pass
-  const float chip = at_once * (float)bm * (bm == 256 ? h.row2 : h.row);
-  return (float)passes * ((bm == 256 ? 3500.f + 200.f * area : 500.f + 290.f * area) + fmaxf(step, fmaxf(feed, chip)) * (float)h.kt);
+  const float step = 305.f + 26.f * area, feed = 3.75f * (float)bm / (float)NT;
+  const float unit = (bm == 256 ? 3600.f + 150.f * area : 250.f + 210.f * area) + fmaxf(step, feed) * (float)h.kt;
+  const float stream = (float)(nmt * bm) * (0.1f + 0.9f * (float)NT) * (bm == 256 ? h.row2 : h.row) * (float)h.kt;
+  return fmaxf((float)passes * unit, stream) * (passes == 1 ? h.once : 1.f);
 }
 inline HeadPlan head_plan_host(const HeadShape& h, int n_act) {
   const int nblk = (n_act + 31) >> 5, least = (nblk + 9) / 10;

@@ -555,11 +555,15 @@ hipError_t launch_lmhead_gemm(const GemmArgs& a, int max_rows, int grid, hipStre
   h.V = a.V;
   h.kt = a.H / kGK;
   h.grid = grid;
-  // W that the memory-side cache holds in good part, or its tile-major copy, arrives at 6.5 TB/s; rows 8 KB apart from HBM at 3.9, and
-  // 256 of them per tile slower still (V = 128256, H = 4096, 320 rows: 389 us with 128-row tiles, 422 with 256-row tiles)
-  const bool fast = a.Wp != nullptr || (size_t)a.V * a.H * sizeof(uint16_t) <= (size_t)320 << 20;
-  h.row = fast ? 128.f / 6500.f : 128.f / 3900.f;
-  h.row2 = fast ? 128.f / 6500.f : 128.f / 3400.f;
+  // 256 rows 8 KB apart arrive a little slower from HBM than 128, or than the tile-major copy, which is as fast with either.  (The
+  // rates are the fit's: no ramp, no epilogue.)
+  const size_t bytes = (size_t)a.V * a.H * sizeof(uint16_t);
+  h.row = 0.0171f;
+  h.row2 = a.Wp != nullptr || bytes <= (size_t)320 << 20 ? 0.0171f : 0.0196f;
+  // Calls with a list of rows are those of a round, which alternate.  40 rows, H = 4096, one direction and alternating: V = 40000 with
+  // 128-row tiles (two passes) 94 and 75 us, with 256-row tiles (one pass) 86 and 85; V = 64000 119 and 99, 124 and 122; their
+  // tile-major copies 80 and 74, 85 and 85; 103 and 95, 102 and 102.
+  h.once = a.row_list == nullptr || bytes <= (size_t)256 << 20 ? 1.f : a.Wp != nullptr ? 1.05f : 1.23f;
   h.most = 10;
   h.known = HeadPlan{0, 0, 0};
   if (a.row_list == nullptr) h.known = head_plan_host(h, a.n_rows);

@@ -16,8 +16,8 @@ int main() {
   auto rnd = [&](int lo, int hi) { s = s * 1664525u + 1013904223u; return lo + (int)((s >> 8) % (unsigned)(hi - lo + 1)); };
   int bad = 0, wide = 0, narrow = 0;
   for (int i = 0; i < 100000; ++i) {
-    const float row = rnd(0, 1) ? 0.02f : 0.035f;
-    const HeadShape h = {rnd(1, i % 4 ? 40000 : 131072), 2 * rnd(1, 40), 8 * rnd(1, 32), rnd(0, 1) ? 4 : 10, row, row, {0, 0, 0}};
+    const float row2 = rnd(0, 1) ? 0.0171f : 0.0196f, once = rnd(0, 1) ? 1.f : 1.23f;
+    const HeadShape h = {rnd(1, i % 4 ? 40000 : 131072), 2 * rnd(1, 40), 8 * rnd(1, 32), rnd(0, 1) ? 4 : 10, 0.0171f, row2, once, {0, 0, 0}};
     const int n = rnd(0, 7) ? rnd(1, 700) : rnd(1, 524288), nblk = (n + 31) / 32;
     const HeadPlan p = head_plan_host(h, n);
     // every block of rows has a tile, no tile is empty or wider than its code
@@ -25,7 +25,16 @@ int main() {
       ++bad;
     (p.bm == 256 ? wide : narrow)++;
   }
-  std::printf("bad %d wide %d narrow %d\n", bad, wide, narrow);
+  // a vocabulary whose 128-row tiles are more than the workgroups, against up to 128 rows: W is received once
+  int twice = 0;
+  for (int V = 32769; V <= 131072; V += 61)
+    for (int kt : {32, 64, 80})
+      for (int n = 17; n <= 128; ++n)
+        for (int c = 0; c < 8; ++c) {
+          const HeadShape h = {V, kt, 256, c & 1 ? 4 : 10, 0.0171f, c & 2 ? 0.0171f : 0.0196f, c & 4 ? 1.f : 1.23f, {0, 0, 0}};
+          twice += head_plan_host(h, n).NT > 1;
+        }
+  std::printf("bad %d wide %d narrow %d twice %d\n", bad, wide, narrow, twice);
   return 0;
 }
 """
@@ -38,7 +47,7 @@ def test_every_call_has_a_plan(tmp_path):
     subprocess.run([HIPCC, "-x", "hip", "--offload-host-only", "-O2", "-std=c++17", "-I",
                     os.path.join(ROOT, "paper_2409_00142_amd", "csrc"), str(src), "-o", exe], check=True)
     out = subprocess.run([exe], check=True, capture_output=True, text=True).stdout.split()
-    assert out[1] == "0" and int(out[3]) > 1000 and int(out[5]) > 1000, out
+    assert out[1] == out[7] == "0" and int(out[3]) > 1000 and int(out[5]) > 1000, out
 
 
 @pytest.mark.gpu
