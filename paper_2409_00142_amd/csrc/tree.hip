@@ -274,6 +274,9 @@ __device__ __forceinline__ double wave_sums_f64(double (&v)[N], int lane) {
   return x;
 }
 
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef f32x4 f32x4_of_floats __attribute__((aligned(4)));   // a row of an odd vocabulary starts on any float
+
 // Four consecutive logits starting at token j (a multiple of 4 past the row start); tokens at or
 // beyond lim read as -inf, i.e. weight 0.  vec: the row is 16-byte aligned and V a multiple of 4.
 __device__ __forceinline__ float4 load_logits4(const float* x, int j, int lim, bool vec) {
@@ -551,7 +554,8 @@ __global__ __launch_bounds__(kVsPartWaves * kWave) void verify_row_sums_kernel(V
   const int part = blockIdx.x, i = blockIdx.y, b = blockIdx.z, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int T = a.m + 1, V = a.V;
   // In front of the row's loads: a pool with fewer nodes than m (a round that stopped early) has rows that nobody asks for.  B = 8,
-  // V = 32000: 36 nodes and m = 80 21.1 us a call, 24.3 with all 81 rows read; 10 nodes and m = 60 15.6, 21.2; all of 60 27.2, 26.8.
+  // V = 32000: 36 nodes and m = 80 21.1 us a call, 24.3 with all 81 rows read; 10 nodes and m = 60 15.6, 21.2; all of 60 the look
+  // costs 0.4.
   if (i > min(a.tree.n_sel[b], a.m)) return;                              // uniform: not a node of the tree
   const float* x = a.logits + ((size_t)b * T + i) * V;
   VsRow* out = static_cast<VsRow*>(a.rows) + (size_t)b * T + i;
@@ -564,10 +568,24 @@ __global__ __launch_bounds__(kVsPartWaves * kWave) void verify_row_sums_kernel(V
   float4 xv[kVsPartPerWave][kKeep];
   float mx = -__builtin_inff();
   if (CPB > 0) {
+    // No branch at a load, so all of them are in flight together: 16 bytes wherever the row starts, past its end the row's last four.
+    // What straddles the end, and what lies behind it, is put right afterwards.
+    if (V >= 4) {                                                         // uniform
+#pragma unroll
+      for (int q = 0; q < kVsPartPerWave; ++q)
+#pragma unroll
+        for (int c = 0; c < kKeep; ++c) {
+          const f32x4 v = *reinterpret_cast<const f32x4_of_floats*>(x + min(j0 + (q * kKeep + c) * kVsChunk, V - 4));
+          xv[q][c] = make_float4(v[0], v[1], v[2], v[3]);
+        }
+    }
 #pragma unroll
     for (int q = 0; q < kVsPartPerWave; ++q)
 #pragma unroll
-      for (int c = 0; c < kKeep; ++c) xv[q][c] = load_logits4(x, j0 + (q * kKeep + c) * kVsChunk, V, vec);
+      for (int c = 0; c < kKeep; ++c) {
+        const int j = j0 + (q * kKeep + c) * kVsChunk;
+        if (j + 4 > V) xv[q][c] = load_logits4(x, j, V, false);
+      }
 #pragma unroll
     for (int q = 0; q < kVsPartPerWave; ++q)
 #pragma unroll

@@ -69,3 +69,47 @@ def test_both_routes_agree(V, T):
             continue
         assert (int(got[0][0][b]), int(got[0][2][b])) == (alen, bonus)
         assert np.array_equal(got[0][1][b], path)
+
+
+@pytest.mark.parametrize("V", [2, 3, 4, 6, 7, 1021, 1022, 1023, 32765, 32766, 32767, 65535])
+def test_rows_that_end_anywhere(V):
+    """Rows whose last 16-byte piece is whole or straddles the end, and rows shorter than one: nearly all weight on the last four
+    tokens, so the bonus tells whether each of them counted once, on both routes and against the oracle.  The logits fill their
+    allocation to its last element."""
+    import torch
+    import paper_2409_00142_amd as D
+    print(f"[case] verify_sample row ends V={V}", flush=True)
+    B, k, Dm, m = 16, 2, 3, 4
+    rng = np.random.default_rng(V)
+    lg = rng.standard_normal((B, m + 1, V)).astype(np.float32)
+    lg[..., max(V - 4, 0):] += 14.0
+    ua, ub = np.full((B, m + 1), 0.999999), np.tile(((np.arange(B) + 0.5) / B)[:, None], (1, m + 1))
+    cfg = D.make_config(B, 128, V, k, Dm, m, 0.3)
+    ctx = D.ddd_create(cfg)
+    got = []
+    try:
+        tree, t = D.alloc_tree(cfg)
+        t["n_sel"].zero_()
+        x, a, u = torch.from_numpy(lg).cuda(), torch.from_numpy(ua).cuda(), torch.from_numpy(ub).cuda()
+        other = torch.cuda.Stream()
+        for stream in (torch.cuda.current_stream(), other):
+            out = [torch.full((B,), -7, dtype=torch.int32, device="cuda"),
+                   torch.full((B, Dm + 1), -7, dtype=torch.int32, device="cuda"),
+                   torch.full((B,), -7, dtype=torch.int32, device="cuda")]
+            torch.cuda.synchronize()
+            D.ddd_verify_sample(ctx, tree, x, 1.0, a, u, *out, stream=stream.cuda_stream)
+            torch.cuda.synchronize()
+            got.append([o.cpu().numpy() for o in out])
+    finally:
+        D.ddd_destroy(ctx)
+    for p, q in zip(*got):
+        assert np.array_equal(p, q)
+    none = np.full(m + 1, -1, np.int32)
+    for b in range(B):
+        tr = O.Tree(m=m, n_sel=0, sel_node=none[1:], tree_token=none, pos=np.zeros(m + 1, np.int32), parent_idx=none,
+                    mask=np.zeros((m + 1, m + 1), np.uint8))
+        mg = []
+        alen, _, bonus = verify_sample(tr, lg[b], 1.0, ua[b], ub[b], Dm, margins=mg)
+        if mg and min(mg) <= MIN_MARGIN:
+            continue
+        assert (int(got[0][0][b]), int(got[0][2][b])) == (alen, bonus)
