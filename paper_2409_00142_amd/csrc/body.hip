@@ -221,9 +221,10 @@ hipError_t launch_linear_stream(const LinearArgs& a, int G, int nslice, hipStrea
 }
 
 // ---- weights ahead ----------------------------------------------------------------------------
-// The norms and the attention of a few rows leave most of the chip and all of the memory idle for 5 to 10 us, and the product behind
-// each of them is a weight stream that starts from nothing.  Workgroups beside theirs read what the stream's workgroups start with;
-// workgroup number % 8 is the XCD of both, so the stream finds it in its own L2.
+// The attention of a few rows leaves most of the chip and the memory idle for 5 to 10 us, and the product behind it is a weight stream
+// that starts from nothing.  Workgroups beside its own read what the stream's workgroups start with; workgroup number % 8 is the XCD
+// of both, so the stream finds it in its own L2.  (Beside the norms too: 404.1 -> 403.0 us for three calls of one user with k = 10,
+// L = 256, H = 4096, F = 11008, but every other size tried lost 0.2 to 0.5 %, up to 2 us.)
 __device__ __forceinline__ void read_ahead(const WeightsAhead& w, const uint8_t* row_active, int R, int tid, int threads) {
   if (row_active != nullptr) {   // the stream will not run if every row is inactive
     const int lane = tid & 63;
@@ -246,14 +247,9 @@ __device__ __forceinline__ void read_ahead(const WeightsAhead& w, const uint8_t*
 __global__ __launch_bounds__(1024) void rmsnorm_kernel(RmsNormArgs a) {
   __shared__ float part[16];
   const int r = blockIdx.x, tid = threadIdx.x;
-  if (r >= a.R) {                                                // uniform
-    read_ahead(a.ahead, a.row_active, a.R, tid, 1024);
-    return;
-  }
-  // the flag is looked at behind the loads of the row and of the weights: one round trip instead of three
-  const int on = a.row_active != nullptr ? a.row_active[r] : 1;
+  if (a.row_active != nullptr && a.row_active[r] == 0) return;   // uniform over the block
   const float* x = a.x + (size_t)r * a.H;
-  float xv[8], gv[8];                                            // H <= 8192
+  float xv[8], gv[8];                                            // H <= 8192; the weights arrive with the row
   float ss = 0.f;
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
@@ -261,7 +257,6 @@ __global__ __launch_bounds__(1024) void rmsnorm_kernel(RmsNormArgs a) {
     xv[j] = (i < a.H) ? x[i] : 0.f;
     gv[j] = (i < a.H) ? a.g[i] : 0.f;
   }
-  if (on == 0) return;                                           // uniform over the block
 #pragma unroll
   for (int j = 0; j < 8; ++j) ss += xv[j] * xv[j];
   ss = wave_sum_f32(ss);
@@ -280,7 +275,7 @@ __global__ __launch_bounds__(1024) void rmsnorm_kernel(RmsNormArgs a) {
 
 hipError_t launch_rmsnorm(const RmsNormArgs& a, hipStream_t stream) {
   if (a.H > 8192) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(rmsnorm_kernel, dim3(a.R + (a.ahead.W != nullptr ? a.ahead.nslice : 0)), dim3(1024), 0, stream, a);
+  hipLaunchKernelGGL(rmsnorm_kernel, dim3(a.R), dim3(1024), 0, stream, a);
   return hipGetLastError();
 }
 
@@ -1136,13 +1131,17 @@ hipError_t launch_body_attention(const BodyAttnArgs& a, int n_cu, hipStream_t st
   // few rows, wider beams, or a prompt too long for the LDS: one workgroup per (row, head)
   // Sixteen waves where a prompt does not fit one pass of eight and the launch has no two workgroups for a CU: 512 keys in flight
   // instead of 256.
-  const int n_wg = a.R * (a.H / kHeadDim), tail = ((n_vis + 3) & ~3) + 32, n_ahead = a.ahead.W != nullptr ? a.ahead.nslice : 0;
+  const int n_wg = a.R * (a.H / kHeadDim), tail = ((n_vis + 3) & ~3) + 32;
+  // Weights ahead where the attention takes little of the memory itself.  Three calls of one user without and with them: L = 256, H =
+  // 4096, ten rows (320 workgroups) 407.2 and 404.1 us; L = 8 400.7 and 397.1; H = 5120, five rows (200) 559.4 and 558.3, ten (400)
+  // 584.4 and 585.4; sixteen rows (512) 436.7 and 437.3; sixteen waves, L = 2048, four rows 464.9 and 468.7.
+  const bool ahead = a.ahead.W != nullptr && 4 * n_wg <= 5 * n_cu;
   if (a.L > 256 && n_wg <= n_cu)
-    hipLaunchKernelGGL(body_attention_kernel<1024>, dim3(n_wg + n_ahead), dim3(1024), (size_t)(kAttnLdsFloats<1024> + tail) * sizeof(float),
+    hipLaunchKernelGGL(body_attention_kernel<1024>, dim3(n_wg), dim3(1024), (size_t)(kAttnLdsFloats<1024> + tail) * sizeof(float),
                        stream, a);
   else
-    hipLaunchKernelGGL(body_attention_kernel<512>, dim3(n_wg + n_ahead), dim3(512), (size_t)(kAttnLdsFloats<512> + tail) * sizeof(float),
-                       stream, a);
+    hipLaunchKernelGGL(body_attention_kernel<512>, dim3(n_wg + (ahead ? a.ahead.nslice : 0)), dim3(512),
+                       (size_t)(kAttnLdsFloats<512> + tail) * sizeof(float), stream, a);
   return hipGetLastError();
 }
 

@@ -125,12 +125,11 @@ int enqueue_linear_ranges(const ddd_body* b, LinearArgs a, int K_range, hipStrea
   return DDD_OK;
 }
 
-// The beginning of the next product's weights, for the launch in front of it (body.hip: read_ahead).  Only where the layer's weights
-// are more than the memory-side cache holds: H = 4096, F = 11008 (three calls of one user) 5.5 us of 397 less with 64 KB per workgroup
-// beside the norms and 96 KB beside the attention, the larger the shorter the wait that it fills (32 to 128 KB: within 1 us); with
-// 120 MB of weights in all, H = 2048, 178 -> 180 us.
-constexpr int kAheadNorm = 64 << 10, kAheadAttention = 96 << 10;
-WeightsAhead weights_ahead(const ddd_body* b, const void* W, int N, int K, int bytes) {
+// The beginning of the next product's weights, for the attention in front of it (body.hip: read_ahead).  Only where the layer's weights
+// are more than the memory-side cache holds (with 120 MB of weights in all, H = 2048, 178 -> 180 us); 96 KB per workgroup (32 to 128 KB:
+// within 1 us).
+constexpr int kAheadAttention = 96 << 10;
+WeightsAhead weights_ahead(const ddd_body* b, const void* W, int N, int K) {
   const size_t H = b->cfg.H, layer = 2 * (6 * H * H + 3 * H * (size_t)b->cfg.F);
   const int ntiles = (N + 15) / 16;
   WeightsAhead w;
@@ -138,7 +137,7 @@ WeightsAhead weights_ahead(const ddd_body* b, const void* W, int N, int K, int b
   w.N = N;
   w.K = K;
   w.nslice = ntiles < b->n_cu ? ntiles : b->n_cu;
-  w.bytes = bytes;
+  w.bytes = kAheadAttention;
   return w;
 }
 
@@ -325,7 +324,6 @@ int ddd_body_step(void* user, int32_t step, const ddd_state* st, void* hid_out, 
   n1.out = b->xn;
   n1.H = H;
   n1.R = R;
-  n1.ahead = weights_ahead(b, b->w.Wqkv, 3 * H, H, kAheadNorm);
   BodyAttnArgs t;
   t.qkv = b->qkv;
   t.sums = SplitSums{};
@@ -344,10 +342,9 @@ int ddd_body_step(void* user, int32_t step, const ddd_state* st, void* hid_out, 
   t.step = step;
   t.R = R;
   t.hist_rows = (int)hist_rows;
-  t.ahead = weights_ahead(b, gemm ? nullptr : b->w.Wo, H, H, kAheadAttention);
+  t.ahead = weights_ahead(b, gemm ? nullptr : b->w.Wo, H, H);
   RmsNormArgs n2 = n1;
   n2.g = b->w.g2;
-  n2.ahead = weights_ahead(b, b->w.Wgu, 2 * F, H, kAheadNorm);
 
   if (gemm) {
     // More than kBodyRows rows: the same sequence of operations with every linear on the matrix cores, over the

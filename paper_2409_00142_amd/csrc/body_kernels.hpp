@@ -60,7 +60,6 @@ struct RmsNormArgs {
   const uint8_t* row_active;
   uint16_t* out;              // bf16 [R][H]
   int H, R;
-  WeightsAhead ahead;
 };
 hipError_t launch_rmsnorm(const RmsNormArgs& a, hipStream_t stream);
 

@@ -1,5 +1,5 @@
-"""The draft layer's weight streams with few rows: calls whose rows are all stopped, and gathers by sequence, at a size whose norms
-and attention read the next weights ahead and at one whose do not."""
+"""The draft layer's weight streams with few rows: calls whose rows are all stopped, and gathers by sequence, at a size whose
+attention reads the next weights ahead and at one whose does not."""
 import pytest
 
 pytestmark = pytest.mark.gpu
