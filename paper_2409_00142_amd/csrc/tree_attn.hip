@@ -386,7 +386,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void tree_attn_partial_ke
 // Few tiles whose heads are a little more than one step of eight waves per workgroup (one user of 32 heads: 65 chunks of 32 keys for
 // L = 1999 and eight workgroups a head): a second step for the last chunks costs as much as the first, 5 us of loads, barriers and
 // products one after the other.  Here a workgroup takes up to sixteen consecutive chunks in one pass - a wave the scores of two -, so
-// there is one reference, nothing is rescaled, and every load of the pass is on its way before the first product.
+// there is one reference, and nothing is rescaled.  The keys and the first eight chunks' values are on their way before the first
+// product, the other values where the keys were, behind it; a wave that holds a chunk of the tree waits for the mask's words first.
 // L = 1999, 32 heads, one user: 24.0 -> 18.9 us with the merge, 1.7 of it by reading the mask four keys at a time.  (Nine workgroups a
 // head instead, two to a CU: 26.3.)
 
@@ -529,10 +530,13 @@ __global__ __launch_bounds__(512, 2) void tree_attn_pass_kernel(TreeAttnArgs a, 
 // its partials eight at a time, the references and sums together with the outputs: one or two memory latencies in all.
 constexpr int kMergeD = 16;   // elements of the head per workgroup
 
+// MAPPED: the workgroups of a head on one XCD, where the partials' were (elsewhere it costs 0.2 us: 32 heads, L = 300 to 1500, 17 tree
+// indices 11.4 to 14.4 us against 11.2 to 14.2).
+template <bool MAPPED>
 __global__ __launch_bounds__(256) void tree_attn_merge_kernel(TreeAttnArgs a) {
   const int nqt = (a.T + kQT - 1) / kQT;
   int bx = blockIdx.x, h = blockIdx.y;
-  head_on_xcd(bx, h);
+  if (MAPPED) head_on_xcd(bx, h);
   const int qt = bx / (kAD / kMergeD), dq0 = (bx % (kAD / kMergeD)) * kMergeD, b = blockIdx.z, tid = threadIdx.x;
   const float* part = a.part + (((size_t)b * a.nh + h) * nqt + qt) * a.nsplit * kPartFloats;
   const int qx = tid & (kQT - 1), qi = qt * kQT + qx;
@@ -629,7 +633,11 @@ hipError_t launch_tree_attention(TreeAttnArgs a, int n_cu, hipStream_t stream) {
     hipLaunchKernelGGL(tree_attn_partial_kernel<4>, grid, dim3(64 * 4), 0, stream, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.nsplit == 1) return e;
-  hipLaunchKernelGGL(tree_attn_merge_kernel, dim3(nqt * (kAD / kMergeD), a.nh, a.B), dim3(256), 0, stream, a);
+  const dim3 merge(nqt * (kAD / kMergeD), a.nh, a.B);
+  if (p.per > 0 || nqt > 1)
+    hipLaunchKernelGGL(tree_attn_merge_kernel<true>, merge, dim3(256), 0, stream, a);
+  else
+    hipLaunchKernelGGL(tree_attn_merge_kernel<false>, merge, dim3(256), 0, stream, a);
   return hipGetLastError();
 }
 
