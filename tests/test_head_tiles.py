@@ -94,6 +94,43 @@ def test_products_of_every_tile(V, R, packed):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("packed", [False, True], ids=["rows", "packed"])
+@pytest.mark.parametrize("H", [384, 1024])
+@pytest.mark.parametrize("V,R", [(32003, R) for R in (17, 64, 97, 161, 225, 289, 330, 385, 447, 450, 513, 577, 640)] +
+                         [(17001, R) for R in (200, 257, 330, 450, 577)])
+def test_rings_of_every_tile(V, R, H, packed):
+    """Six and sixteen k tiles: every slot of the rings (two to four tiles deep) is filled again and read again, for every width of
+    the 128-row and 256-row tiles, with as many blocks for each pair of waves and with one less.  W's columns grow with k, so a tile
+    of another k cannot pass for the right one.
+
+    Tolerance: products of bf16 numbers are exact in fp32; H additions round a partial sum of a few units by 2^-24 of it at most, and
+    128 of them stay below 1e-5 (above)."""
+    import torch
+    import paper_2409_00142_amd as D
+    print(f"[case] head_rings V={V} R={R} H={H} packed={packed}", flush=True)
+    k = 5
+    g = torch.Generator(device="cuda")
+    g.manual_seed(V + R + H)
+    W = (torch.empty(V, H, device="cuda").normal_(0, 0.1, generator=g) * torch.linspace(0.5, 1.5, H, device="cuda")).to(torch.bfloat16)
+    hid = torch.empty(R, H, dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=g)
+    ctx = D.ddd_create(D.make_config((R + k - 1) // k, H, V, k, 3, 10, 0.3))
+    try:
+        if packed:
+            D.ddd_weights_pack(ctx, W)
+        o = (torch.zeros(R, k, dtype=torch.int32, device="cuda"), torch.zeros(R, k, device="cuda"), torch.zeros(R, device="cuda"))
+        dbg = [torch.zeros(R, V, device="cuda") for _ in range(2)]
+        for out in dbg:
+            D.ddd_lmhead_topk(ctx, W, hid, R, None, *o, out)
+        torch.cuda.synchronize()
+    finally:
+        D.ddd_destroy(ctx)
+    want = hid.double() @ W.double().T.contiguous()
+    assert torch.equal(dbg[0], dbg[1])
+    assert float((dbg[0].double() - want).abs().max()) < 1e-5 * H / 128
+    assert torch.equal(torch.topk(dbg[0], k, dim=1).values, torch.gather(dbg[0], 1, o[0].long()))
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("kind", ["random", "equal", "few_groups", "rising"])
 @pytest.mark.parametrize("V,k", [(17, 16), (64, 16), (960, 16), (1024, 16), (16384, 16), (16385, 1), (32768, 16), (32769, 10), (65536, 16),
                                  (65537, 5), (131072, 16)])
