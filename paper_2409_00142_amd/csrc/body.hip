@@ -58,9 +58,11 @@ __global__ __launch_bounds__(704) void linear_stream_kernel(LinearArgs a) {
   // skips (calls enqueued behind a round's end, most of a captured round's) would read 45 MB for nothing.  Rounds of 3.45 calls with
   // the check behind the first tile and in front of it: 734 and 706 us paced by the host, 1026 and 811 captured; three calls of
   // which none is skipped 395 and 402.
+  unsigned long long rows_on = ~0ull;
   if (a.row_active != nullptr) {   // uniform
     const int on = (lane < a.R) ? a.row_active[lane] : 0;
-    if (__ballot(on != 0) == 0ull) return;
+    rows_on = __ballot(on != 0);
+    if (rows_on == 0ull) return;
   }
   const int nslice = gridDim.x, slice = blockIdx.x;
   // Output rows are dealt to the workgroups in units of 4 (an epilogue lane's outputs, and whole gate/up
@@ -144,7 +146,7 @@ __global__ __launch_bounds__(704) void linear_stream_kernel(LinearArgs a) {
   } else {
     // epilogue wave: lane = (vb, r) owns outputs 4*vb .. 4*vb+3 of the tile for input row r
     const int r = lane & 15, vb = lane >> 4;
-    const bool active = r < a.R && (a.row_active == nullptr || a.row_active[r] != 0);   // rows of stopped sequences stay untouched
+    const bool active = r < a.R && ((rows_on >> r) & 1ull) != 0;   // rows of stopped sequences stay untouched
     if (MULTI) {
 #pragma unroll
       for (int g = 0; g < kLinearRanges; ++g) {

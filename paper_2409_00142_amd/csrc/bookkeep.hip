@@ -98,7 +98,9 @@ __global__ __launch_bounds__(256) void row_topk_kernel(RowTopkArgs a) {
   __shared__ int s_glist[kGrpListMax];
   __shared__ uint32_t s_max[256], s_least[1];
   const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int on = a.row_active != nullptr ? a.row_active[row] : 1;   // looked at behind the loads of the row's groups
+  // The compiler waits for the flag in front of the row's loads all the same (its load hangs on the null test), but the kernel's
+  // arguments arrive beside it: 0.6 us a launch less than with the return here.
+  const int on = a.row_active != nullptr ? a.row_active[row] : 1;
   RowEmit<false> emit(a, row);
   const int ngrp_valid = (a.V + 63) >> 6;
   const float* gmax = a.grp_max + (size_t)row * a.ngrp;
@@ -266,6 +268,7 @@ constexpr int kWideRowThreads = 1024;
 constexpr int kWideGroups = 2048;   // V <= 2^17
 constexpr int kWideFold = 512;      // most values that are ranked
 static_assert(kWideGroups == 2 * kWideRowThreads && kWideFold == kWideRowThreads / 2, "a thread's two groups, and its neighbour's");
+static_assert(kWideFold <= kKthMost, "one wave ranks them");
 
 __global__ __launch_bounds__(kWideRowThreads) void row_topk_wide_kernel(RowTopkArgs a) {
   __shared__ __align__(16) uint32_t s_gm[kWideFold];         // (folded) group maxima as ordered keys
@@ -276,7 +279,9 @@ __global__ __launch_bounds__(kWideRowThreads) void row_topk_wide_kernel(RowTopkA
   __shared__ uint32_t s_min[1];
   __shared__ int s_cnt, s_ng;
   const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int on = a.row_active != nullptr ? a.row_active[row] : 1;   // looked at behind the loads of the row's groups
+  // The compiler waits for the flag in front of the row's loads all the same (its load hangs on the null test), but the kernel's
+  // arguments arrive beside it: 0.6 us a launch less than with the return here.
+  const int on = a.row_active != nullptr ? a.row_active[row] : 1;
   RowEmit<true> emit(a, row);
   const int ngrp = (a.V + 63) >> 6;
   uint32_t top = 0u;                                         // the larger of the thread's groups

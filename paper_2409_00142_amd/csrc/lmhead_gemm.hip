@@ -171,7 +171,7 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, unsigned char* ldsb
             __builtin_amdgcn_mfma_f32_32x32x16_bf16(AFC[mi % AB], BFC[mi / AB], acc[mi % AB][mi / AB], 0, 0, 0); \
       else                                                                                                     \
         mfma_vgpr(acc[mi % AB][mi / AB], AFC[mi % AB], BFC[mi / AB]);                                          \
-      _Pragma("unroll") for (int ci = (I0); ci < (I1); ++ci) if (((ci - (I0)) * NM) / ((I1) - (I0)) == mi) {   \
+      _Pragma("unroll") for (int ci = (I0); ci < (I1); ++ci) if (((ci - (I0)) * NM) / ((I1) > (I0) ? (I1) - (I0) : 1) == mi) { \
         __builtin_amdgcn_sched_barrier(0);                                                                     \
         COPY(T, STG, ci);                                                                                      \
         __builtin_amdgcn_sched_barrier(0);                                                                     \
@@ -567,8 +567,8 @@ hipError_t launch_lmhead_gemm(const GemmArgs& a, int max_rows, int grid, hipStre
   h.most = 10;
   h.known = HeadPlan{0, 0, 0};
   if (a.row_list == nullptr) h.known = head_plan_host(h, a.n_rows);
-  // Two kernels, because the wide tiles' registers cost every launch of the one that has them 1 us: up to 320 rows it is only taken
-  // where 128-row tiles would need several passes over the workgroups.
+  // Two kernels, because a launch of the one that has the wide tiles, twice the code, takes 1 us longer whatever tiles it uses: up to 320
+  // rows it is only taken where 128-row tiles would need several passes over the workgroups.
   const bool wide = a.row_list == nullptr ? h.known.bm == 256 && h.known.bpt > 4 : max_rows > 320 || (max_rows > 128 && (a.V + 127) / 128 > grid);
   if (!wide) h.most = 4;
   if (!wide)

@@ -186,9 +186,11 @@ __device__ __forceinline__ uint32_t wave_prefix(const uint32_t (&key)[S], int wa
   }
   return T;
 }
-// The k-th largest of n values (1 <= k <= n <= 512), ties counted: the smallest with fewer than k larger ones.  vals: LDS; red: LDS [1].
+// The k-th largest of n values (1 <= k <= n <= kKthMost), ties counted: the smallest with fewer than k larger ones.  vals: LDS; red:
+// LDS [1].
 // By wave 0 alone; the block barriers also order the caller's writes of vals before and its reuse of them after.  (Counting by the
 // whole block, 32-bit compares against values that a wave reads from one address: 500 values 3.3 us on a CU; now 1.3.)
+constexpr int kKthMost = 64 * 8;           // eight values per lane
 template <int S>
 __device__ __forceinline__ uint32_t wave_kth_largest(const uint32_t* vals, int n, int k, int lane) {
   uint32_t key[S];
@@ -203,7 +205,7 @@ __device__ __forceinline__ uint32_t wave_kth_largest(const uint32_t* vals, int n
 __device__ __forceinline__ uint32_t block_kth_largest_u32(const uint32_t* vals, int n, int k, uint32_t* red, int tid) {
   __syncthreads();
   if (tid < 64) {
-    const uint32_t least = n <= 256 ? wave_kth_largest<4>(vals, n, k, tid) : wave_kth_largest<8>(vals, n, k, tid);
+    const uint32_t least = n <= 256 ? wave_kth_largest<4>(vals, n, k, tid) : wave_kth_largest<kKthMost / 64>(vals, n, k, tid);
     if (tid == 0) red[0] = least;
   }
   __syncthreads();

@@ -21,8 +21,10 @@ constexpr int kWideThreads = 1024;
 constexpr int kGlobalChunk = 8;                    // loads in flight per thread when the keys come from global memory
 // final tree of a large pool: sample, candidates and their ranks (tree_finalize_wide_block)
 constexpr int kWSub = 512, kWCand = 1024;
+constexpr int kBeamSample = 320;                   // most candidates that bound a new beam
 constexpr int kWideWorkBytes = kWSub * 8 + kWCand * 8 + kWCand * 4;
 static_assert(kWSub >= DDD_MMAX && kWSub <= kWCand, "the sample holds m keys and lies in the candidate list");
+static_assert(kBeamSample >= kKW && kBeamSample <= kKthMost && kBeamSample <= kWSub, "one of each row at least, ranked by one wave");
 // LDS in front of WideSmem in the step kernel: the k*k candidate keys of a call, later the work area of the final tree
 __host__ __device__ inline size_t wide_front_bytes(int k) {
   const size_t keys = ((size_t)k * k * 8 + 15) & ~(size_t)15;
@@ -213,7 +215,7 @@ __device__ __forceinline__ void tree_finalize_wide_block(const ddd_state& st, co
   // First with 32-bit scores: the m-th best of the first 256 nodes, and one plain sweep over the scores.
   if (m_eff < N && nthr == kWideThreads) {                           // uniform
     constexpr int kFirst = 256;
-    static_assert(kFirst >= DDD_MMAX && 2 * kFirst <= 2 * kWSub, "the sample holds m scores and lies in front of the candidates");
+    static_assert(kFirst >= DDD_MMAX && kFirst <= kKthMost && kFirst <= 2 * kWSub, "the sample holds m scores and lies in front of the candidates");
     uint32_t* first = reinterpret_cast<uint32_t*>(work);             // [kFirst]
     const int n_first = min(N, kFirst);
     for (int i = tid; i < n_first; i += nthr) first[i] = ord32(psc[i + 1]);
@@ -315,10 +317,10 @@ __device__ __forceinline__ bool step_wide_block(const WideStepArgs& a, unsigned 
   constexpr int kPer = kKW * kKW / kWideThreads;
   uint64_t kv[kPer], mine = 0ull;
   uint32_t* sample = reinterpret_cast<uint32_t*>(wsm_raw);       // [kWSub]
-  const int per_row = min(k, max(1, 320 / k)), n_sample = k * per_row;
+  const int per_row = min(k, max(1, kBeamSample / k)), n_sample = k * per_row;
   const int on_flag = g.st.active[b];
   if (a.do_select && step > 0 && from_keys) {                    // uniform
-    const int i = tid / per_row;                                 // n_sample <= 320
+    const int i = tid / per_row;                                 // n_sample <= kBeamSample
     if (tid < n_sample) mine = a.part_key[row0 * k + i * k + (tid - i * per_row)];
 #pragma unroll
     for (int u = 0; u < kPer; ++u) {
@@ -409,8 +411,8 @@ __device__ __forceinline__ bool step_wide_block(const WideStepArgs& a, unsigned 
         }
       }
       // The new beam: the k-th best score of the rows' first few candidates is a lower bound of the beam's scores (a row's
-      // logprobs fall), the keys at or above it - k and a few more - are ranked by counting.  Three per row at k = 100: the
-      // comparisons of a larger sample cost more than the candidates it spares.
+      // logprobs fall), the keys at or above it - k and a few more - are ranked by counting.  Three per row at k = 100: a
+      // size chosen when the bound was found by comparing all pairs, and not tuned again for the one wave that finds it now.
       uint64_t* cand = reinterpret_cast<uint64_t*>(sample + 2 * kWSub); // [kWCand]
       int* rank = reinterpret_cast<int*>(cand + kWCand);         // [kWCand]
       for (int i = tid; i < kWCand; i += nthr) rank[i] = 0;
