@@ -90,11 +90,12 @@ bool pick_split(int H, int* G, int* nw) {
 // Row pitch of the context's own logits: whole 128-byte lines.
 int logits_pitch(int V) { return (V + 31) & ~31; }
 
-// Whether ddd_verify_sample makes the sums of all rows first (tree.hip).  That takes 11 us and 1.4 for a million tokens, whatever
-// is accepted; a walk that makes the sums of its own rows 7.5 and 8.2 for each row of up to 32768 tokens on the batch's
-// longest path.  Sums against walk for longest paths of 0 / 2 / 4 / 6 tokens, V = 32000, 61 nodes: one sequence 13.5 against
-// 15 / 32 / 49 / -, eight 33 against 16 / 32 / 49 / 66, sixteen (the line, 128 MB) 48 against the same - and the more
-// sequences, the longer the longest path: of sixteen it reaches four nineteen times in twenty where 0.65 of the nodes agree.
+// Whether ddd_verify_sample makes the sums of all rows first (tree.hip).  That takes 9.5 us and 0.93 for a million tokens, whatever
+// is accepted; a walk that makes the sums of its own rows 5 and 8.2 for each row of up to 32768 tokens on the batch's longest path
+// (one more than the accepted tokens).  Sums against walk for longest paths of 2 / 4 / 6 tokens, V = 32000, 61 nodes: one sequence 11
+// against 30 / 46 / 62, eight 25 against the same, sixteen (the line, 128 MB) 38 - and the more sequences, the longer the longest path:
+// of sixteen it reaches four nineteen times in twenty where 0.65 of the nodes agree.  With sums this short they would
+// meet a path of four at about 160 MB; the line has not been moved.
 bool rows_from_sums(const ddd_config& c) {
   return (long long)c.B * (c.m + 1) * c.V * 4 <= (128LL << 20) && (long long)c.B * (c.m + 1) <= 8192;
 }

@@ -12,10 +12,10 @@
 // Up to 320 hidden rows against a vocabulary whose 128-row tiles are no more than the workgroups: 128 x 320 at most (AB = 2).  More:
 // tiles of 256 rows of W (AB = 4, 128 x 160 per wave) in one pass over the workgroups instead of two, which copy a third less per
 // product and read a third less from LDS.  V = 32000, H = 4096, a ddd_lmhead_topk call: 330 rows 113 -> 100 us, 510 144 -> 131,
-// 640 168 -> 159.  What bounds it there is power: the loop runs at 1.36 PFLOP/s, the rate of a large square product on this card, and
-// the same launch with operands that are mostly zeros takes 25 us less (stores and statistics of the epilogue: 16 us).  Eight waves of 64 x 160
-// on that tile, two per SIMD: 157, but 96 us instead of 92 at 320 rows.  A vocabulary that leaves workgroups without a tile is cut
-// into more column tiles (V = 4000, 320 rows: 72 -> 32 us); how, is priced by head_plan (gemm_plan.hpp).
+// 640 168 -> 159.  The matrix cores are busy 56 % of that launch's cycles, at 1.87 GHz (the clock under products: with operands that are
+// mostly zeros it takes 25 us less); the rest is the one unit's ramp, the operand feed, and 16 us of stores and statistics.  Eight
+// waves of 64 x 160 on that tile, two per SIMD: 157, but 96 us instead of 92 at 320 rows.  A vocabulary that leaves workgroups without a tile is cut
+// into more column tiles (V = 4000, 320 rows: 72 -> 32 us); how, is priced by head_price (gemm_plan.hpp).
 //
 // W is the A operand, so an accumulator lane owns one hidden row and four consecutive vocabulary
 // rows per register quad: the output is stored as float4 along V.  Both operands reach LDS by

@@ -53,7 +53,7 @@ __device__ __forceinline__ void stats_end(const StatsArgs& s, const StatsPre& p,
 // Section 1 / Section 3.1 (temperature 0): follow the child whose token equals the target's
 // argmax at the current node until there is none; the argmax there is the bonus token.  One wave, one round trip: the whole tree and
 // the target's tokens are in registers (three tree indices per lane) before the walk, whose steps are ballots and one lane read (a
-// load per step: 3.9 us a launch of one sequence, now 2.4; 64 of them 5.7, now 4.1).
+// load per step: 3.9 us a launch of one sequence, now 2.4; 64 of them 5.7, now 3.9).
 constexpr int kVaSlots = (DDD_MMAX + 1 + 63) / 64;
 __global__ __launch_bounds__(64) void verify_accept_kernel(VerifyArgs a) {
   const int b = blockIdx.x, lane = threadIdx.x;
@@ -127,10 +127,11 @@ hipError_t launch_verify_accept(const VerifyArgs& a, hipStream_t stream) {
 // The walk is a chain - which row is next depends on the decision at this one - and a row of 32 000 fp64 exponentials
 // keeps one CU busy for about 8 us, so the two ways of doing it differ in where the rows' sums are made:
 //  * small batches (verify_sample_from_sums): a first launch makes the sums of every row of every tree with the whole
-//    chip (20 us for 62 MB, of which the memory takes 12; 23 with the long form of the exponential), and the walk that follows
-//    looks numbers up: B = 8, V = 32000, 61 nodes, 41 to 65 us a call by the depth of the accepted paths -> 27 us, B = 1 24 to 37
-//    -> 12.6 us.  It reads m + 1 rows per sequence instead of two or three.  (Workgroups of twice and four times the blocks, which
-//    issue a tenth less per token: 31 and 36 us, because all of the loads then come before all of the arithmetic.)
+//    chip (18.3 us for 62 MB, of which the memory takes 12 and the issue of fp64 instructions 9; 19.4 with one load after the other,
+//    23 with the long form of the exponential too), and the walk that follows looks numbers up: B = 8, V = 32000, 61 nodes, 41 to 65
+//    us a call by the depth of the accepted paths -> 25 us, B = 1 24 to 37 -> 11.8 us.  It reads n_sel + 1 rows per sequence instead
+//    of two or three.  (Workgroups of twice and four times the blocks, which issue a tenth less per token: 31 and 36 us, because all of
+//    the loads then come before all of the arithmetic.)
 //  * beyond that (verify_sample_kernel): one workgroup of 16 waves per sequence makes the sums of the rows it visits.
 // The line lies where the extra rows would cost what they save (rows_from_sums).
 constexpr int kVsWaves = 16;
@@ -144,7 +145,7 @@ constexpr int kVsChunk = 4 * kWave;                  // tokens one wave loads pe
 // exact rest, and a polynomial of degree 10 through the Chebyshev nodes of [-1/2, 1/2] (3e-16).  The difference from
 // the row maximum is taken first (exact for the logits that matter), so the weight of the maximum is 1 and the error of
 // the others 2e-15 at T = 1, that of a row's sum 1e-16 (a Taylor polynomial of degree 11 around exp(x / T - max / T), as before:
-// 9e-15 and 5e-16).  19 instructions of fp64 issue per token, most of what the kernels execute.  Exactly 0 for -inf.
+// 9e-15 and 5e-16).  19 fp64 instructions per token.  Exactly 0 for -inf.
 __device__ __forceinline__ double weight_of(double d, double beta2) {
   const double t = fmax(d * beta2, -1200.0);
   const double n = __builtin_rint(t);
@@ -162,12 +163,13 @@ __device__ __forceinline__ double weight_of(double d, double beta2) {
   p = fma(p, f, 1.0);
   return ldexp(p, (int)n);
 }
-// The same for the rows' sums, in 10 fp64 instructions instead of 19: 2^t = 2^(n/128) 2^f with |f| <= 1/256, where adding
-// 1.5 * 2^45 leaves n in the low word, the 128 values of 2^(j/128) sit in LDS and 2^f - 1 is f times a cubic through the Chebyshev
-// nodes (1.5e-16 with the rounding of its coefficients).  f takes one rounding (t is never rounded), so a weight is closer to the
-// exact one than above.  B = 8, V = 32000, 61 nodes: 30.5 -> 27.1 us a call with the constants of T made by the host and the rows'
-// loads in front of the look at the tree's size; B = 16 49.8 -> 42.9.  The high words of the table are less by j << 13, so that adding n << 13 puts the integer part of n / 128 into
-// the exponent field.  For t in (-1021, 0].
+// The same for the rows' sums, in 10 fp64 instructions instead of 19, by a table (the usual table-driven exponential; Tang, "Table-driven
+// implementation of the exponential function in IEEE floating-point arithmetic", ACM TOMS 15, 1989): 2^t = 2^(n/128) 2^f with
+// |f| <= 1/256, where adding 1.5 * 2^45 leaves n in the low word, the 128 values of 2^(j/128), rounded to nearest, sit in LDS and
+// 2^f - 1 is f times a cubic through the Chebyshev nodes (1.5e-16 with the rounding of its coefficients).  f takes one rounding (t is
+// never rounded), so a weight is closer to the exact one than above.  B = 8, V = 32000, 61 nodes: 29.5 -> 26.8 us a call with the
+// constants of T made by the host; B = 16 48.2 -> 43.2.  The high words of the table are less by j << 13, so that adding n << 13 puts
+// the integer part of n / 128 into the exponent field.  For t in (-1021, 0].
 constexpr int kVsExpSize = 128;
 __device__ const unsigned long long kVsExp[kVsExpSize] = {
     0x3ff0000000000000ull, 0x3feff63da9fb3335ull, 0x3fefec9a3e778061ull, 0x3fefe315e86e7f85ull,
