@@ -63,10 +63,11 @@ struct HeadShape {
   float row2;   // with 256-row tiles
   float once;   // what a cut of one pass costs beside one of several: calls that walk W in opposite directions find in the memory-side
                 // cache what the call before read last, but a single pass reads all rows at once, along k
+  int once_most;   // ... in calls of up to so many blocks of 32 rows: with more the products take longer than W
   HeadPlan known;   // the plan, where the number of rows is known before the launch (bm = 0: it is not)
 };
 // In ns, fitted to 900 calls of 20 to 640 rows with V = 4000 to 128256 and H = 1024 to 5120, walking W in one direction and in
-// alternating ones, each with up to ten cuts (the chosen cut is 0.8 % slower than the best one on average; with whole passes at the
+// alternating ones, each with up to ten cuts (the chosen cut is 0.65 % slower than the best one on average; with whole passes at the
 // chip's rate 2 %, and 37 % at most).  Either the workgroups' passes over the units: a unit's ramp and epilogue are 250 and 210 per
 // 32 x 32 products (block columns in twos: two waves share them) or 3600 and 150, a k tile of it 305 and 26 per 32 x 32, or what its
 // rows of W take to arrive, 1 us per 256 rows, which the column tiles share.  Or, if that is longer, the stream of W through the chip,
@@ -80,7 +81,7 @@ __host__ __device__ inline float head_price(const HeadShape& h, int n_act, int b
   const float step = 305.f + 26.f * area, feed = 3.75f * (float)bm / (float)NT;
   const float unit = (bm == 256 ? 3600.f + 150.f * area : 250.f + 210.f * area) + fmaxf(step, feed) * (float)h.kt;
   const float stream = (float)(nmt * bm) * (0.1f + 0.9f * (float)NT) * (bm == 256 ? h.row2 : h.row) * (float)h.kt;
-  return fmaxf((float)passes * unit, stream) * (passes == 1 ? h.once : 1.f);
+  return fmaxf((float)passes * unit, stream) * (passes == 1 && nblk <= h.once_most ? h.once : 1.f);
 }
 inline HeadPlan head_plan_host(const HeadShape& h, int n_act) {
   const int nblk = (n_act + 31) >> 5, least = (nblk + 9) / 10;

@@ -555,15 +555,18 @@ hipError_t launch_lmhead_gemm(const GemmArgs& a, int max_rows, int grid, hipStre
   h.V = a.V;
   h.kt = a.H / kGK;
   h.grid = grid;
-  // 256 rows 8 KB apart arrive a little slower from HBM than 128, or than the tile-major copy, which is as fast with either.  (The
-  // rates are the fit's: no ramp, no epilogue.)
+  // 256 rows apart arrive a little slower from HBM than 128, or than the tile-major copy, which is as fast with either.  (The rates are
+  // the fit's: no ramp, no epilogue.)  Calls with a list of rows are those of a round, which walk W in alternating directions, and
+  // 256 rows that lie whole 8 KB apart are much slower there once the memory-side cache holds little of W: H = 4096, 20 rows, V = 50000
+  // 90 us, V = 56000 114 (89 with the copy).  40 rows, H = 4096, one direction and alternating: V = 40000 with 128-row tiles (two
+  // passes) 94 and 75 us, with 256-row tiles (one pass) 86 and 85; V = 64000 119 and 99, 124 and 122; their tile-major copies 80 and
+  // 74, 85 and 85; 103 and 95, 102 and 102.  200 rows, alternating, V = 50000: 136 and 124.
   const size_t bytes = (size_t)a.V * a.H * sizeof(uint16_t);
+  const bool round = a.row_list != nullptr, rows = a.Wp == nullptr, far = round && rows && bytes > (size_t)430 << 20 && a.H % 4096 == 0;
   h.row = 0.0171f;
-  h.row2 = a.Wp != nullptr || bytes <= (size_t)320 << 20 ? 0.0171f : 0.0196f;
-  // Calls with a list of rows are those of a round, which alternate.  40 rows, H = 4096, one direction and alternating: V = 40000 with
-  // 128-row tiles (two passes) 94 and 75 us, with 256-row tiles (one pass) 86 and 85; V = 64000 119 and 99, 124 and 122; their
-  // tile-major copies 80 and 74, 85 and 85; 103 and 95, 102 and 102.
-  h.once = a.row_list == nullptr || bytes <= (size_t)256 << 20 ? 1.f : a.Wp != nullptr ? 1.05f : 1.23f;
+  h.row2 = far ? 0.030f : rows && bytes > (size_t)320 << 20 ? 0.0196f : 0.0171f;
+  h.once = !round || bytes <= (size_t)256 << 20 ? 1.f : rows ? 1.23f : 1.05f;
+  h.once_most = far ? 1 << 30 : 4;
   h.most = 10;
   h.known = HeadPlan{0, 0, 0};
   if (a.row_list == nullptr) h.known = head_plan_host(h, a.n_rows);
