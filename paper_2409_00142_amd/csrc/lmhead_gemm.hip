@@ -564,7 +564,7 @@ hipError_t launch_lmhead_gemm(const GemmArgs& a, int max_rows, int grid, hipStre
   const size_t bytes = (size_t)a.V * a.H * sizeof(uint16_t);
   const bool round = a.row_list != nullptr, rows = a.Wp == nullptr, far = round && rows && bytes > (size_t)430 << 20 && a.H % 4096 == 0;
   h.row = 0.0171f;
-  h.row2 = far ? 0.030f : rows && bytes > (size_t)320 << 20 ? 0.0196f : 0.0171f;
+  h.row2 = far ? 0.042f : rows && bytes > (size_t)320 << 20 ? 0.0196f : 0.0171f;
   h.once = !round || bytes <= (size_t)256 << 20 ? 1.f : rows ? 1.23f : 1.05f;
   h.once_most = far ? 1 << 30 : 4;
   h.most = 10;
