@@ -110,16 +110,18 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, unsigned char* ldsb
   const bool packed = a.Wp != nullptr;
   const uint32_t a_tile_stride = packed ? 256u * kRowB : (uint32_t)kRowB;
   const unsigned char* Wb = reinterpret_cast<const unsigned char*>(packed ? a.Wp : a.W) + (size_t)kt_lo * a_tile_stride;
+  // Every wave is done with the LDS tiles of the previous unit; that unit's stores stay in flight (__syncthreads() would wait for them).
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
   uint32_t ao[NAP], bo[NBP];
+  int ids[NBP];                 // requested in front of the first copies of W, which do not wait for them
+#pragma unroll
+  for (int i = 0; i < NBP; ++i) ids[i] = row_id(a, min(tile_col0 + (i * 4 + wave) * 8 + prow, n_act - 1));
 #pragma unroll
   for (int i = 0; i < NAP; ++i) {
     const int vrow = mt * C::BM + (i * 4 + wave) * 8 + prow;
     ao[i] = packed ? ((uint32_t)(vrow >> 8) * (uint32_t)KTall * 256u + (uint32_t)(vrow & 255)) * kRowB + pc * 16
                    : ((uint32_t)min(vrow, a.V - 1) * (uint32_t)a.H + pc * 8) * 2u;
   }
-#pragma unroll
-  for (int i = 0; i < NBP; ++i)
-    bo[i] = ((uint32_t)row_id(a, min(tile_col0 + (i * 4 + wave) * 8 + prow, n_act - 1)) * (uint32_t)a.H + pc * 8) * 2u;
   typedef const __attribute__((address_space(1))) void* gptr_t;
   typedef __attribute__((address_space(3))) void* lptr_t;
   const unsigned char* Hb = reinterpret_cast<const unsigned char*>(a.hid) + (size_t)kt_lo * kRowB;
@@ -195,24 +197,33 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, unsigned char* ldsb
                                                                   : NAP + (kSB - 2) * P;
   static_assert(kInFlight < 64, "vmcnt is a 6-bit counter");
   bf16x8 af0[AB], bf0[NBR], af1[AB], bf1[NBR];
-  __syncthreads();            // every wave is done with the LDS tiles of the previous unit
-  // everything the steps before tile 0 would have issued
+  // Everything the steps before tile 0 would have issued, in the order of the tiles: tile 0 is multiplied as soon as it has landed, and
+  // the static count below holds from there on.
+#pragma unroll
+  for (int i = 0; i < NAP; ++i) DDD_COPY_A(0, 0, i);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < NBP; ++i) bo[i] = ((uint32_t)ids[i] * (uint32_t)a.H + pc * 8) * 2u;
 #pragma unroll
   for (int p = 0; p < kSA - 1; ++p) {
+    if (p > 0) {
+#pragma unroll
+      for (int i = 0; i < NAP; ++i) DDD_COPY_A(min(p, KT - 1), p, i);
+    }
     if (p < kSB - 1) {
 #pragma unroll
       for (int i = 0; i < NBP; ++i) DDD_COPY_B(min(p, KT - 1), p, i);
     }
-#pragma unroll
-    for (int i = 0; i < NAP; ++i) DDD_COPY_A(min(p, KT - 1), p, i);
   }
-#pragma unroll
-  for (int i = 0; i < NBa; ++i) DDD_COPY_B(min(kSB - 1, KT - 1), kSB - 1, i);
   if (kEarly && kEqual) {
 #pragma unroll
     for (int i = 0; i < NAP; ++i) DDD_COPY_A(min(kSA - 1, KT - 1), kSA - 1, i);
   }
-  __builtin_amdgcn_s_waitcnt(DDD_VMCNT(0));       // all of it has landed: the static count below holds from tile 0 on
+#pragma unroll
+  for (int i = 0; i < NBa; ++i) DDD_COPY_B(min(kSB - 1, KT - 1), kSB - 1, i);
+  constexpr int kAhead = (kSA - 2) * NAP + (kSB - 2) * NBP + NBa + (kEarly && kEqual ? NAP : 0);   // behind those of tile 0
+  static_assert(kAhead < 64, "vmcnt is a 6-bit counter");
+  __builtin_amdgcn_s_waitcnt(DDD_VMCNT(kAhead));
   __builtin_amdgcn_s_barrier();
   if (NB > 0) DDD_READ(af0, bf0, ldsA, ldsB, offk[0]);
   DDD_WAIT(63);
