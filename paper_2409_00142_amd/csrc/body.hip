@@ -59,6 +59,19 @@ __global__ __launch_bounds__(704) void linear_stream_kernel(LinearArgs a) {
   // the check behind the first tile and in front of it: 734 and 706 us paced by the host, 1026 and 811 captured; three calls of
   // which none is skipped 395 and 402.
   unsigned long long rows_on = ~0ull;
+  // Source row of operand column lane & 15 in each range: on its way with the flags.
+  int src[kLinearRanges];
+  if (MULTI) {
+    const int nr = min(lane & 15, a.R - 1);        // columns past the last row repeat it
+#pragma unroll
+    for (int g = 0; g < kLinearRanges; ++g) {
+      const LinearRange& rg = a.rg[g < a.n_ranges ? g : 0];
+      src[g] = nr;
+      if (rg.gather_mode == kGatherIndex) src[g] = rg.gather_idx[nr];
+      else if (rg.gather_mode == kGatherInBlock) src[g] = (nr / a.gather_k) * a.gather_k + rg.gather_idx[nr];
+      else if (rg.gather_mode == kGatherBlock) src[g] = nr / a.gather_k;
+    }
+  }
   if (a.row_active != nullptr) {   // uniform
     const int on = (lane < a.R) ? a.row_active[lane] : 0;
     rows_on = __ballot(on != 0);
@@ -74,7 +87,6 @@ __global__ __launch_bounds__(704) void linear_stream_kernel(LinearArgs a) {
 
   float* red = reinterpret_cast<float*>(smem);      // [2][NW][256] fp32 partial tiles
   unsigned char* stage = smem + 2 * NW * 1024;      // [NW][kStageBytes]
-  int* s_src = reinterpret_cast<int*>(stage + NW * kStageBytes);   // [kLinearRanges][16] source rows of the gathered input rows
 
   const int NR = a.n_ranges;
   const int total = nt * NR;          // (tile, range) steps of this workgroup, ranges innermost
@@ -100,37 +112,29 @@ __global__ __launch_bounds__(704) void linear_stream_kernel(LinearArgs a) {
     const int n_last = MULTI ? min(max(a.last_units - wave * G, 0), G) : G;
 
     u32x4 ring[G][4];
-    {
-      const int v0 = n0, n_first = (MULTI && range_at(0) == NR - 1) ? n_last : G;
-#pragma unroll
-      for (int g = 0; g < G; ++g)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          if (MULTI && g >= n_first) continue;
-          const int row = min(v0 + i * 4 + lrow, vlast);
-          ring[g][i] = *reinterpret_cast<const u32x4*>(wb0 + (size_t)row * a.ldw + g * 128);
-        }
-    }
-    auto x_of = [&](int r) {           // this lane's source row in range r (operand columns past the last row repeat it), first element
-      const LinearRange& rg = a.rg[r];
-      const int src = MULTI && rg.gather_mode != kGatherNone ? s_src[r * 16 + n] : min(n, a.R - 1);
-      return rg.x + (size_t)src * rg.ldx + ks + q * 8;
-    };
     bf16x8 bfrag[G][4];
-    auto load_x = [&]() {
-      const uint16_t* xp = x_of(range_at(0));
-#pragma unroll
-      for (int g = 0; g < G; ++g)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          if (MULTI && range_at(0) == NR - 1 && g >= n_last) continue;
-          bfrag[g][j] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(xp + g * 128 + j * 32));
-        }
+    auto x_of = [&](int r) {           // this lane's source row in range r, first element
+      const LinearRange& rg = a.rg[r];
+      const int from = !MULTI ? min(n, a.R - 1) : r == 0 ? src[0] : r == 1 ? src[1] : src[2];
+      return rg.x + (size_t)from * rg.ldx + ks + q * 8;
     };
-    // What the epilogue wave has looked up arrives through LDS: loads return in order, so a look at an index by this wave would
-    // wait for the whole first tile, and the input rows would be requested behind it.
-    if (MULTI) lds_barrier();
-    load_x();
+    const int n_first = (MULTI && range_at(0) == NR - 1) ? n_last : G;
+    // Loads return in order, so the input rows of a group follow its weights: the first group can be multiplied, and its weights
+    // of the next tile requested, when an eighth of the tile and rows is there.  With the rows behind the whole tile the memory was
+    // idle until they had come too: three calls of one user 397.5 -> 385.6 us, gate/up of ten rows 38.8 -> 36.4, q/k/v 23.5 -> 22.4.
+    const uint16_t* xp0 = x_of(range_at(0));
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      if (MULTI && g >= n_first) continue;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int row = min(n0 + i * 4 + lrow, vlast);
+        ring[g][i] = *reinterpret_cast<const u32x4*>(wb0 + (size_t)row * a.ldw + g * 128);
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) bfrag[g][j] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(xp0 + g * 128 + j * 32));
+      __builtin_amdgcn_sched_barrier(0);
+    }
 #pragma unroll 1
     for (int it = 0; it < total; ++it) {
       __builtin_amdgcn_sched_barrier(0);   // the previous step's operands are dead before the next ones are requested
@@ -152,19 +156,6 @@ __global__ __launch_bounds__(704) void linear_stream_kernel(LinearArgs a) {
     // epilogue wave: lane = (vb, r) owns outputs 4*vb .. 4*vb+3 of the tile for input row r
     const int r = lane & 15, vb = lane >> 4;
     const bool active = r < a.R && ((rows_on >> r) & 1ull) != 0;   // rows of stopped sequences stay untouched
-    if (MULTI) {
-#pragma unroll
-      for (int g = 0; g < kLinearRanges; ++g) {
-        const LinearRange& rg = a.rg[g < NR ? g : 0];
-        const int nr = min(r, a.R - 1);
-        int src = nr;
-        if (rg.gather_mode == kGatherIndex) src = rg.gather_idx[nr];
-        else if (rg.gather_mode == kGatherInBlock) src = (nr / a.gather_k) * a.gather_k + rg.gather_idx[nr];
-        else if (rg.gather_mode == kGatherBlock) src = nr / a.gather_k;
-        if (vb == 0) s_src[g * 16 + r] = src;
-      }
-    }
-    if (MULTI) lds_barrier();
     for (int t = 0; t < nt; ++t) {
       const int v0 = n0 + t * 16 + vb * 4;
       float* const yp = a.y + (size_t)r * a.ldy + v0;
@@ -210,7 +201,7 @@ __global__ __launch_bounds__(704) void linear_stream_kernel(LinearArgs a) {
 template <int G>
 static hipError_t launch_linear_g(const LinearArgs& a, int nslice, hipStream_t stream) {
   const dim3 grid(nslice), block((a.nw + 1) * 64);
-  const size_t lds = (size_t)2 * a.nw * 1024 + (size_t)a.nw * kStageBytes + kLinearRanges * 16 * sizeof(int);
+  const size_t lds = (size_t)2 * a.nw * 1024 + (size_t)a.nw * kStageBytes;
   if (a.n_ranges > 1 || a.last_units < a.nw * G || a.rg[0].gather_mode != kGatherNone)
     hipLaunchKernelGGL((linear_stream_kernel<G, true>), grid, block, lds, stream, a);
   else
