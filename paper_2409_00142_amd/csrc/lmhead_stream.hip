@@ -75,16 +75,6 @@ __global__ __launch_bounds__(768) void lmhead_stream_kernel(StreamArgs a) {
     // ------------------------------ streaming wave ------------------------------
     const int ks = wave * (128 * G);
     const int n = lane & 15, q = lane >> 4;          // MFMA operand coordinates
-    bf16x8 bfrag[G][4];
-#pragma unroll
-    for (int g = 0; g < G; ++g)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        u32x4 u = {0u, 0u, 0u, 0u};
-        if (n < a.R) u = *reinterpret_cast<const u32x4*>(a.hid + (size_t)n * a.H + ks + g * 128 + j * 32 + q * 8);
-        bfrag[g][j] = __builtin_bit_cast(bf16x8, u);
-      }
-
     const int lrow = lane >> 4, c = lane & 15;       // load coordinates: 4 rows x 16 chunks per instruction
     unsigned char* mystage = stage + wave * kStageBytes;
     const int wr_off = lrow * kStagePitch + c * 16;
@@ -92,15 +82,25 @@ __global__ __launch_bounds__(768) void lmhead_stream_kernel(StreamArgs a) {
     const uint16_t* wbase = a.W + ks + c * 8;
 
     u32x4 ring[G][4];
+    bf16x8 bfrag[G][4];
     {
       const int lo = tile_lo(0), last = tile_hi(0) - 1;   // rows are clamped to the tile
+      // loads return in order: the first group is multiplied, and its next weights requested, when its own operands are there
 #pragma unroll
-      for (int g = 0; g < G; ++g)
+      for (int g = 0; g < G; ++g) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int row = min(lo + i * 4 + lrow, last);
           ring[g][i] = *reinterpret_cast<const u32x4*>(wbase + (size_t)row * a.H + g * 128);
         }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          u32x4 u = {0u, 0u, 0u, 0u};
+          if (n < a.R) u = *reinterpret_cast<const u32x4*>(a.hid + (size_t)n * a.H + ks + g * 128 + j * 32 + q * 8);
+          bfrag[g][j] = __builtin_bit_cast(bf16x8, u);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
     if (check_late) {   // the requests above are simply dropped if nothing is active
       asm volatile("" : "+v"(on_late));   // keeps the compiler from waiting for the flags before the requests are out
