@@ -47,7 +47,7 @@ struct ddd_ctx {
   ddd_round_stats stats;         // caller's statistics arrays (all null: none bound)
   bool stats_on;
   uint32_t* stats_sync;          // device [2]: arrivals and deepest sequence of the verify launch in flight (zero between)
-  // ddd_verify_sample of small batches: the sums of every row (null: the batch is too large for it).  The array belongs to
+  // ddd_verify_sample of small batches: the sums of the rows (null: the batch is too large for it).  The array belongs to
   // the first stream that uses it: calls on one stream are ordered, calls on any other take the kernel without scratch.  (An
   // event behind every walk, for the next call on any stream to wait for, cost 3 of the 29 us of a call: B = 8, V = 32000.)
   void* sample_rows;
@@ -90,14 +90,15 @@ bool pick_split(int H, int* G, int* nw) {
 // Row pitch of the context's own logits: whole 128-byte lines.
 int logits_pitch(int V) { return (V + 31) & ~31; }
 
-// Whether ddd_verify_sample makes the sums of all rows first (tree.hip).  That takes 9.5 us and 0.93 for a million tokens, whatever
-// is accepted; a walk that makes the sums of its own rows 5 and 8.2 for each row of up to 32768 tokens on the batch's longest path
-// (one more than the accepted tokens).  Sums against walk for longest paths of 2 / 4 / 6 tokens, V = 32000, 61 nodes: one sequence 11
-// against 30 / 46 / 62, eight 25 against the same, sixteen (the line, 128 MB) 38 - and the more sequences, the longer the longest path:
-// of sixteen it reaches four nineteen times in twenty where 0.65 of the nodes agree.  With sums this short they would
-// meet a path of four at about 160 MB; the line has not been moved.
+// Whether ddd_verify_sample makes the rows' sums first (tree.hip).  That takes about 13 us and 0.52 for a million tokens of all
+// rows, whatever is accepted; a walk that makes the sums of its own rows 5 and 8.2 for each row of 32768 tokens on the batch's longest path
+// (one more than the accepted tokens), and the more sequences, the longer that is.  Sums against walk where 0.65 of the nodes agree, 61
+// nodes: V = 32000, 24 sequences 36 against 56 us, 32 44 against 57, 32 of 81 nodes (332 MB) 54 against 49 to 70; V = 60001, 32 of 26 nodes 42
+// against 144; V = 128256, 8 sequences 44 against 91, 16 (500 MB) 69 against 98, 32 118 against 118.  By the first figures 64 sequences
+// with V = 32000 (500 MB) would take 78 against 62.
 bool rows_from_sums(const ddd_config& c) {
-  return (long long)c.B * (c.m + 1) * c.V * 4 <= (128LL << 20) && (long long)c.B * (c.m + 1) <= 8192;
+  const long long rows = (long long)c.B * (c.m + 1);
+  return rows <= 1024 || (rows <= 8192 && rows * c.V * 4 <= (288LL << 20));
 }
 
 bool state_ok(const ddd_state* s) {

@@ -224,9 +224,10 @@ struct VerifySampleArgs {
   int32_t* bonus_token;          // [B]
   float temperature;
   int B, m, D, V;
-  void* rows;                    // null, or scratch of verify_sample_row_bytes() per row of logits: the sums of all rows first
+  void* rows;                    // null, or scratch of verify_sample_row_bytes() per row of logits: the sums of the rows first
   // set by the launcher:
   int parts;                     // of every row's sums
+  bool leaves;                   // the sums of leaves too
   double beta2, span;            // log2(e) / T, and the difference of two logits whose weights differ by 2^1000
 };
 size_t verify_sample_row_bytes();

@@ -126,12 +126,13 @@ hipError_t launch_verify_accept(const VerifyArgs& a, hipStream_t stream) {
 //
 // The walk is a chain - which row is next depends on the decision at this one - and a row of 32 000 fp64 exponentials
 // keeps one CU busy for about 8 us, so the two ways of doing it differ in where the rows' sums are made:
-//  * small batches (verify_sample_from_sums): a first launch makes the sums of every row of every tree with the whole
-//    chip (18.3 us for 62 MB, of which the memory takes 12 and the issue of fp64 instructions 9; 19.4 with one load after the other,
-//    23 with the long form of the exponential too), and the walk that follows looks numbers up: B = 8, V = 32000, 61 nodes, 41 to 65
-//    us a call by the depth of the accepted paths -> 25 us, B = 1 24 to 37 -> 11.8 us.  It reads n_sel + 1 rows per sequence instead
-//    of two or three.  (Workgroups of twice and four times the blocks, which issue a tenth less per token: 31 and 36 us, because all of
-//    the loads then come before all of the arithmetic.)
+//  * small batches (verify_sample_from_sums): a first launch makes the sums of the rows of every tree with the whole chip, and the walk
+//    that follows looks numbers up.  It is bound by the rows it reads (62 MB take the memory 12 us, the fp64 instructions 9), so the
+//    rows of leaves, half of a tree's nodes, are left out: a walk tests no children there, and few end there.  Where one does, the
+//    workgroups of the walk's launch make that row's sums between them (4 to 5 us).  With and without the leaves' rows, 61 nodes:
+//    B = 8, V = 32000 24.7 and 18.9 to 21.3 us a call, B = 16 40.4 and 29.2, B = 6 21.5 and 18.9, B = 1 11.9 and 12.3; B = 30, V = 4001,
+//    49 nodes 17.4 and 18.4: what is left out must be worth the leaf of the walk (sums_of_leaves).  (Workgroups of twice and four times
+//    the blocks, which issue a tenth less per token: 31 and 36 us, because all of the loads then come before all of the arithmetic.)
 //  * beyond that (verify_sample_kernel): one workgroup of 16 waves per sequence makes the sums of the rows it visits.
 // The line lies where the extra rows would cost what they save (rows_from_sums).
 constexpr int kVsWaves = 16;
@@ -526,7 +527,7 @@ __global__ __launch_bounds__(kVsThreads) void verify_sample_kernel(VerifySampleA
   }
 }
 
-// ---- small batches: the sums of all rows by the whole chip, then the walk -----------------------------------------
+// ---- small batches: the sums of the rows by the whole chip, then the walk -----------------------------------------
 // A row's 128 blocks belong to kVsParts workgroups of 16 blocks; each takes its weights relative to its own maximum, and
 // the walk scales them by exp((part's maximum - row's maximum) / T).
 constexpr int kVsParts = 8, kVsPartSub = kVsSub / kVsParts, kVsPartWaves = 4, kVsPartPerWave = kVsPartSub / kVsPartWaves;
@@ -535,7 +536,8 @@ struct VsRow {
   double sub[kVsSub];          // block sums, each relative to its part's maximum
   double psum[kVsParts];       // the parts' sums
   float pmax[kVsParts];        // and maxima
-  float pad[8];
+  unsigned arrived;            // of a sequence's first row: the workgroups that have left their part of a leaf's row
+  float pad[7];
 };
 static_assert(sizeof(VsRow) == 1152, "whole lines");
 // Parts of a row that hold tokens (eight from 28 673 tokens up to 32 768, one up to 4096); only those are made and count.
@@ -547,53 +549,39 @@ static_assert(kVsWalkThreads >= DDD_MMAX + 1, "a thread per tree index");
 
 size_t verify_sample_row_bytes() { return sizeof(VsRow); }
 
-// CPB: chunks of 256 tokens per block, kept in registers between the maximum and the weights (1: V <= 32768, 2:
-// V <= 65536 ...); 0: any V, the logits read twice.
+// The 16 block sums of one part of row x, relative to the part's maximum, by a workgroup of four waves.  Returns the maximum; s_sub (LDS)
+// holds the sums, and behind the caller's barrier s_sub[] is complete.  CPB: chunks of 256 tokens per block, kept in registers between the
+// maximum and the weights (1: V <= 32768, 2: V <= 65536 ...); 0: any V, the logits read twice.
 template <int CPB>
-__global__ __launch_bounds__(kVsPartWaves * kWave) void verify_row_sums_kernel(VerifySampleArgs a) {
-  __shared__ float s_max[kVsPartWaves];
-  __shared__ double s_sub[kVsPartSub], s_exp[kVsExpSize];
-  const int part = blockIdx.x, i = blockIdx.y, b = blockIdx.z, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int T = a.m + 1, V = a.V;
-  // In front of the row's loads: a pool with fewer nodes than m (a round that stopped early) has rows that nobody asks for.  B = 8,
-  // V = 32000: 36 nodes and m = 80 21.1 us a call, 24.3 with all 81 rows read; 10 nodes and m = 60 15.6, 21.2; all of 60 the look
-  // costs 0.2 (0.4 with the row's address fetched behind it).
-  const int n_sel = a.tree.n_sel[b];
-  const float* x = a.logits + ((size_t)b * T + i) * V;
-  VsRow* out = static_cast<VsRow*>(a.rows) + (size_t)b * T + i;
-  asm volatile("" ::"s"(x), "s"(out));                                    // the arguments arrive beside the size, not behind it
-  if (i > min(n_sel, a.m)) return;                                        // uniform: not a node of the tree
+__device__ __forceinline__ float part_sums(const VerifySampleArgs& a, const float* x, int part, int tid, float* s_max, double* s_sub,
+                                           double* s_exp) {
+  const int lane = tid & 63, wv = tid >> 6, V = a.V;
   const int cpb = CPB > 0 ? CPB : chunks_per_block(V);
   const int sb = cpb * kVsChunk;
   const int j0 = (part * kVsPartSub + wv * kVsPartPerWave) * sb + 4 * lane;   // may lie beyond V
   const bool vec = rows_aligned(a);
   const double beta2 = beta2_of(a);
   constexpr int kKeep = CPB > 0 ? CPB : 1;
-  float4 xv[kVsPartPerWave][kKeep];
+  constexpr int kHeld = kVsPartPerWave * kKeep;
+  float4 xv[kHeld];
   float mx = -__builtin_inff();
-  if (CPB > 0) {
+  if constexpr (CPB > 0) {
     // No branch at a load, so all of them are in flight together: 16 bytes wherever the row starts, past its end the row's last four.
     // What straddles the end, and what lies behind it, is put right afterwards.
     if (V >= 4) {                                                         // uniform
 #pragma unroll
-      for (int q = 0; q < kVsPartPerWave; ++q)
-#pragma unroll
-        for (int c = 0; c < kKeep; ++c) {
-          const f32x4 v = *reinterpret_cast<const f32x4_of_floats*>(x + min(j0 + (q * kKeep + c) * kVsChunk, V - 4));
-          xv[q][c] = make_float4(v[0], v[1], v[2], v[3]);
-        }
+      for (int c = 0; c < kHeld; ++c) {
+        const f32x4 v = *reinterpret_cast<const f32x4_of_floats*>(x + min(j0 + c * kVsChunk, V - 4));
+        xv[c] = make_float4(v[0], v[1], v[2], v[3]);
+      }
     }
 #pragma unroll
-    for (int q = 0; q < kVsPartPerWave; ++q)
+    for (int c = 0; c < kHeld; ++c) {
+      const int j = j0 + c * kVsChunk;
+      if (j + 4 > V) xv[c] = load_logits4(x, j, V, false);
+    }
 #pragma unroll
-      for (int c = 0; c < kKeep; ++c) {
-        const int j = j0 + (q * kKeep + c) * kVsChunk;
-        if (j + 4 > V) xv[q][c] = load_logits4(x, j, V, false);
-      }
-#pragma unroll
-    for (int q = 0; q < kVsPartPerWave; ++q)
-#pragma unroll
-      for (int c = 0; c < kKeep; ++c) mx = max4(mx, xv[q][c]);
+    for (int c = 0; c < kHeld; ++c) mx = max4(mx, xv[c]);
   } else {
 #pragma unroll 8
     for (int c = 0; c < kVsPartPerWave * cpb; ++c) mx = max4(mx, load_logits4(x, j0 + c * kVsChunk, V, vec));
@@ -606,86 +594,150 @@ __global__ __launch_bounds__(kVsPartWaves * kWave) void verify_row_sums_kernel(V
   const bool none = mx == -__builtin_inff();                              // nothing but -inf, or past the vocabulary: no weight
   const double Md = none ? 0.0 : (double)mx;
   const float from = short_from(Md, a.span);
-  double sums[kVsPartPerWave];
-#pragma unroll
-  for (int q = 0; q < kVsPartPerWave; ++q) {
+  auto block = [&](int q) {
     double acc = 0.0;
-    if (CPB > 0) {
+    if constexpr (CPB > 0) {
 #pragma unroll
-      for (int c = 0; c < kKeep; ++c) acc = add_weight4(acc, xv[q][c], Md, beta2, from, s_exp);
+      for (int c = 0; c < kKeep; ++c) acc = add_weight4(acc, xv[q * kKeep + c], Md, beta2, from, s_exp);
     } else {
       for (int c = 0; c < cpb; ++c)
         acc = add_weight4(acc, load_logits4(x, j0 + (q * cpb + c) * kVsChunk, V, vec), Md, beta2, from, s_exp);
     }
-    sums[q] = acc;
-  }
-  const double sum = wave_sums_f64<kVsPartPerWave>(sums, lane);
+    return acc;
+  };
+  static_assert(kVsPartPerWave == 4, "four blocks");
+  // wave_sums_f64<4>, the values by name: an array of them goes to LDS for CPB > 2
+  auto half = [&](double lo, double hi, int off) {
+    const bool up = (lane & off) != 0;
+    return (up ? hi : lo) + __shfl_xor(up ? lo : hi, off, 64);
+  };
+  const double b0 = block(0), b1 = block(1), b2 = block(2), b3 = block(3);
+  const double h0 = half(b0, b2, 32), h1 = half(b1, b3, 32);
+  double sum = half(h0, h1, 16);
+#pragma unroll
+  for (int o = 8; o >= 1; o >>= 1) sum += __shfl_xor(sum, o, 64);
   constexpr int kLanes = kWave / kVsPartPerWave;                          // lanes that hold the same block's sum
-  if ((lane & (kLanes - 1)) == 0) {
-    out->sub[part * kVsPartSub + wv * kVsPartPerWave + lane / kLanes] = sum;
-    s_sub[wv * kVsPartPerWave + lane / kLanes] = sum;
+  if ((lane & (kLanes - 1)) == 0) s_sub[wv * kVsPartPerWave + lane / kLanes] = sum;
+  return mx;
+}
+// By one thread, behind the barrier: the part's sum, in block order.
+__device__ __forceinline__ double part_total(const double* s_sub) {
+  double total = 0.0;
+  for (int q = 0; q < kVsPartSub; ++q) total += s_sub[q];
+  return total;
+}
+
+template <int CPB>
+__global__ __launch_bounds__(kVsPartWaves * kWave) void verify_row_sums_kernel(VerifySampleArgs a) {
+  __shared__ float s_max[kVsPartWaves];
+  __shared__ double s_sub[kVsPartSub], s_exp[kVsExpSize];
+  const int part = blockIdx.x, i = blockIdx.y, b = blockIdx.z, tid = threadIdx.x, lane = tid & 63;
+  const int T = a.m + 1, V = a.V;
+  // In front of the row's loads: a pool with fewer nodes than m (a round that stopped early) has rows that nobody asks for.  B = 8,
+  // V = 32000: 36 nodes and m = 80 21.1 us a call, 24.3 with all 81 rows read; 10 nodes and m = 60 15.6, 21.2; all of 60 the look
+  // costs 0.2 (0.4 with the row's address fetched behind it).  So has a leaf, unless the walk ends there (verify_sample_from_sums).
+  const int32_t* par = a.tree.parent_idx + (size_t)b * T;
+  int p0 = 0, p1 = 0, p2 = 0;
+  if (!a.leaves) {                                                        // uniform
+    p0 = par[min(lane, T - 1)];
+    p1 = par[min(64 + lane, T - 1)];
+    p2 = par[min(128, T - 1)];
   }
+  static_assert(DDD_MMAX + 1 <= 129, "three parents per lane");
+  const int n = min(a.tree.n_sel[b], a.m) + 1;
+  const float* x = a.logits + ((size_t)b * T + i) * V;
+  VsRow* out = static_cast<VsRow*>(a.rows) + (size_t)b * T + i;
+  asm volatile("" ::"s"(x), "s"(out));                                    // the arguments arrive beside the size, not behind it
+  if (i >= n) return;                                                     // uniform: not a node of the tree
+  if (!a.leaves) {
+    if (i == 0 && part == 0 && tid == 0) out->arrived = 0u;
+    const bool kid = (lane >= 1 && lane < n && p0 == i) || (64 + lane < n && p1 == i) || (128 < n && p2 == i);
+    if (__ballot(kid) == 0ull) return;                                    // uniform: a leaf
+  }
+  const float mx = part_sums<CPB>(a, x, part, tid, s_max, s_sub, s_exp);
   __syncthreads();
+  if (tid < kVsPartSub) out->sub[part * kVsPartSub + tid] = s_sub[tid];
   if (tid == 0) {
-    double total = 0.0;
-    for (int q = 0; q < kVsPartSub; ++q) total += s_sub[q];
-    out->psum[part] = total;
+    out->psum[part] = part_total(s_sub);
     out->pmax[part] = mx;
   }
 }
 
-// ALL: every part of a row holds tokens.
-template <bool ALL>
+// What another workgroup of the launch left in a row: read past this XCD's L2.
+__device__ __forceinline__ double left_f64(const double* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ float left_f32(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// The maximum of a row from its parts', and the row's sum relative to it.
+__device__ __forceinline__ double row_total(const float (&pm)[kVsParts], const double (&ps)[kVsParts], double beta2, float& mx) {
+  mx = -__builtin_inff();
+#pragma unroll
+  for (int p = 0; p < kVsParts; ++p) mx = fmaxf(mx, pm[p]);
+  double rem = 0.0;
+#pragma unroll
+  for (int p = 0; p < kVsParts; ++p) rem += ps[p] * weight_of((double)pm[p] - (double)mx, beta2);
+  return rem;
+}
+
+// The walk over the sums of the rows that have children, by as many workgroups per sequence as a row has parts: all take the same
+// decisions, and where the walk ends at a leaf each makes its part of that row.  The one that arrives last draws the bonus token;
+// nobody waits.  (Elsewhere the first does, and the others are done.)  CPB as above.
+// LEAVES: the leaves' sums are there too, and one workgroup walks.  ALL: every part of a row holds tokens.
+template <int CPB, bool LEAVES, bool ALL>
 __global__ __launch_bounds__(kVsWalkThreads) void verify_sample_from_sums_kernel(VerifySampleArgs a) {
   __shared__ VsTree t;
   __shared__ double s_rem[DDD_MMAX + 1], s_kw[DDD_MMAX + 1];
-  __shared__ float s_max[DDD_MMAX + 1];
-  __shared__ int s_cur, s_nrm, s_bonus;
-  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  __shared__ float s_max[DDD_MMAX + 1], s_pmax[kVsPartWaves];
+  __shared__ double s_sub[kVsPartSub], s_exp[kVsExpSize];
+  __shared__ int s_cur, s_len, s_leaf, s_nrm, s_bonus;
+  const int part = LEAVES ? 0 : blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int T = a.m + 1, V = a.V;
   const int n = min(a.tree.n_sel[b], a.m) + 1;
-  const VsRow* rows = static_cast<const VsRow*>(a.rows) + (size_t)b * T;
+  VsRow* rows = static_cast<VsRow*>(a.rows) + (size_t)b * T;
   const int parts = ALL ? kVsParts : a.parts;
   const double beta2 = beta2_of(a);
   StatsPre sp{0, 0u};
-  if (tid == 0) sp = stats_begin(a.stats, b, a.B);
+  if (tid == 0 && part == 0) sp = stats_begin(a.stats, b, a.B);
   // thread i: the sums of tree index i's row, and its token's logit in its parent's row
   load_tree(a, b, tid, t);
   float kx = 0.0f;
   if (tid >= 1 && tid < n) kx = a.logits[((size_t)b * T + min(max(t.par[tid], 0), T - 1)) * V + t.tok[tid]];
-  if (tid < n) {
-    float pm[kVsParts], mx = -__builtin_inff();
-    double ps[kVsParts], rem = 0.0;
+  if (tid < n) {                                                          // a leaf's were never written, and are not used
+    float pm[kVsParts];
+    double ps[kVsParts];
 #pragma unroll
     for (int p = 0; p < kVsParts; ++p) {
       pm[p] = rows[tid].pmax[p];
       ps[p] = rows[tid].psum[p];
     }
 #pragma unroll
-    for (int p = 0; p < kVsParts; ++p) {                                  // what the others hold was never written
+    for (int p = 0; p < kVsParts; ++p) {                                  // nor were those of parts without tokens
       pm[p] = p < parts ? pm[p] : -__builtin_inff();
       ps[p] = p < parts ? ps[p] : 0.0;
     }
-#pragma unroll
-    for (int p = 0; p < kVsParts; ++p) mx = fmaxf(mx, pm[p]);
-#pragma unroll
-    for (int p = 0; p < kVsParts; ++p) rem += ps[p] * weight_of((double)pm[p] - (double)mx, beta2);
-    s_max[tid] = mx;
-    s_rem[tid] = rem;
+    s_rem[tid] = row_total(pm, ps, beta2, s_max[tid]);
   }
   __syncthreads();
   if (tid >= 1 && tid < n) s_kw[tid] = weight_of((double)kx - (double)s_max[min(max(t.par[tid], 0), T - 1)], beta2);
   __syncthreads();
   int32_t* path = a.accept_path + (size_t)b * (a.D + 1);
   int cur = 0, len = 0, nrm = 0;
+  double rem = 0.0;
   if (wv == 0) {
-    double rem = 0.0;
-    if (lane == 0) path[0] = 0;
+    bool leaf = false;
+    if (lane == 0 && part == 0) path[0] = 0;
     for (int it = 0; it <= a.D; ++it) {
       rem = s_rem[cur];
       nrm = 0;
       int nxt = -1;
-      if (len < a.D)
+      if (!LEAVES) {                                                      // as the first launch has seen it, at the depth limit too
+        bool kids = false;
+        for (int base = 0; base < n; base += kWave) {
+          const int c = base + lane;
+          kids |= __ballot(c >= 1 && c < n && t.par[c] == cur) != 0ull;
+        }
+        leaf = !kids;
+      }
+      if (len < a.D && !leaf)
         nxt = test_children(t, n, lane, rem, nrm, [&](int base, bool& kid, double& kw, double& ku, int& ktok) {
           const int c = base + lane;
           kid = c < n && t.par[c] == cur;
@@ -696,18 +748,73 @@ __global__ __launch_bounds__(kVsWalkThreads) void verify_sample_from_sums_kernel
       if (nxt < 0) break;
       cur = nxt;
       ++len;
-      if (lane == 0) path[len] = cur;
+      if (lane == 0 && part == 0) path[len] = cur;
     }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");                // lane 0's list of rejected tokens
-    __builtin_amdgcn_wave_barrier();
-    const VsRow& r = rows[cur];
-    const bool held = 2 * lane < kVsPartSub * parts;
-    const double scale = weight_of((double)r.pmax[(2 * lane) / kVsPartSub] - (double)s_max[cur], beta2);
-    const double v0 = held ? r.sub[2 * lane] * scale : 0.0, v1 = held ? r.sub[2 * lane + 1] * scale : 0.0;
-    const int bonus = draw_bonus(t, nrm, a.logits + ((size_t)b * T + cur) * V, (double)s_max[cur], beta2, t.ub[cur] * rem, v0, v1,
-                                 chunks_per_block(V) * kVsChunk, V, rows_aligned(a), lane);
     if (lane == 0) {
       s_cur = cur;
+      s_len = len;
+      s_leaf = leaf ? 1 : 0;
+    }
+  }
+  __syncthreads();
+  cur = s_cur;
+  len = s_len;
+  const bool leaf = s_leaf != 0;                                          // the same in every workgroup of the sequence
+  if (part == 0)
+    for (int i = len + 1 + tid; i <= a.D; i += kVsWalkThreads) path[i] = -1;
+  const float* x = a.logits + ((size_t)b * T + cur) * V;
+  VsRow& r = rows[cur];
+  if (!leaf && part != 0) return;                                         // block-uniform
+  if (!LEAVES && leaf) {
+    const float mx = part_sums<CPB>(a, x, part, tid, s_pmax, s_sub, s_exp);
+    __syncthreads();
+    if (wv == 0) {
+      if (lane < kVsPartSub)
+        __hip_atomic_store(&r.sub[part * kVsPartSub + lane], s_sub[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const double total = part_total(s_sub);
+      unsigned before = 0u;
+      if (lane == 0) {
+        __hip_atomic_store(&r.psum[part], total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&r.pmax[part], mx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      // this wave's stores, and the depth that stats_begin has put into the maximum, are there before the arrival is counted
+      asm volatile("s_waitcnt vmcnt(0)" : "+v"(sp.before) : : "memory");
+      if (lane == 0) before = __hip_atomic_fetch_add(&rows[0].arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (lane == 0) s_leaf = before == (unsigned)(parts - 1) ? 2 : 1;
+    }
+    __syncthreads();
+    if (s_leaf != 2) return;                                              // block-uniform
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");                    // lines of this row that this XCD has read before are old
+    if (wv == 0) {
+      float pm[kVsParts], top;
+      double ps[kVsParts];
+#pragma unroll
+      for (int p = 0; p < kVsParts; ++p) {
+        pm[p] = left_f32(&r.pmax[p]);
+        ps[p] = left_f64(&r.psum[p]);
+      }
+#pragma unroll
+      for (int p = 0; p < kVsParts; ++p) {
+        pm[p] = p < parts ? pm[p] : -__builtin_inff();
+        ps[p] = p < parts ? ps[p] : 0.0;
+      }
+      rem = row_total(pm, ps, beta2, top);
+      if (lane == 0) s_max[cur] = top;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    }
+    if (tid == 0 && part != 0 && a.stats.sync != nullptr && a.stats.steps != nullptr) sp.d = min(max(a.stats.steps[b], 0), 31);
+  }
+  if (wv == 0) {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");                // lane 0's list of rejected tokens
+    __builtin_amdgcn_wave_barrier();
+    const bool held = 2 * lane < kVsPartSub * parts;
+    const float pm = LEAVES ? r.pmax[(2 * lane) / kVsPartSub] : left_f32(&r.pmax[(2 * lane) / kVsPartSub]);
+    const double scale = weight_of((double)pm - (double)s_max[cur], beta2);
+    const double u0 = LEAVES ? r.sub[2 * lane] : left_f64(&r.sub[2 * lane]), u1 = LEAVES ? r.sub[2 * lane + 1] : left_f64(&r.sub[2 * lane + 1]);
+    const int bonus = draw_bonus(t, nrm, x, (double)s_max[cur], beta2, t.ub[cur] * rem, held ? u0 * scale : 0.0, held ? u1 * scale : 0.0,
+                                 chunks_per_block(V) * kVsChunk, V, rows_aligned(a), lane);
+    if (lane == 0) {
       s_nrm = nrm;
       s_bonus = bonus;
     }
@@ -715,13 +822,21 @@ __global__ __launch_bounds__(kVsWalkThreads) void verify_sample_from_sums_kernel
   __syncthreads();
   int bonus = s_bonus;
   if (bonus < 0)                                                          // block-uniform
-    bonus = last_resort<kVsWalkWaves>(t, s_nrm, a.logits + ((size_t)b * T + s_cur) * V, (double)s_max[s_cur], a.temperature, V, tid);
+    bonus = last_resort<kVsWalkWaves>(t, s_nrm, x, (double)s_max[cur], a.temperature, V, tid);
   if (tid == 0) {
-    for (int i = len + 1; i <= a.D; ++i) path[i] = -1;
     a.accept_len[b] = len;
     a.bonus_token[b] = bonus;
     stats_end(a.stats, sp, a.B, len);
   }
+}
+
+// Whether the leaves' rows are summed up too.  A walk that ends at a leaf without them takes 4 to 5 us longer, and of a batch's walks one
+// usually does where trees are small.  With them and without, us a call: 8 MB of logits 11.9 and 12.3, 16 MB 14.5 and 14.4, 24 MB in rows of
+// 16 KB 17.4 and 18.4, 23 MB in rows of 128 KB 17.2 and 16.3, 31 MB 20.8 and 19.7, 47 MB 21.3 and 19.0; trees of 26 nodes 53 MB 21.8 and 23.0,
+// of 17 70 MB 24.1 and 23.1.
+static bool sums_of_leaves(const VerifySampleArgs& a) {
+  const long long bytes = (long long)a.B * (a.m + 1) * a.V * 4;
+  return bytes <= 24LL << 20 || (a.m <= 32 && bytes <= 64LL << 20);
 }
 
 hipError_t launch_verify_sample(VerifySampleArgs a, hipStream_t stream) {
@@ -731,6 +846,7 @@ hipError_t launch_verify_sample(VerifySampleArgs a, hipStream_t stream) {
   const int cpb = (a.V + kVsSub * kVsChunk - 1) / (kVsSub * kVsChunk);   // chunks of 256 tokens per block
   if (a.rows != nullptr) {
     a.parts = vs_parts(a.V);
+    a.leaves = sums_of_leaves(a);
     const dim3 grid(a.parts, a.m + 1, a.B), block(kVsPartWaves * kWave);
     if (cpb == 1)
       hipLaunchKernelGGL((verify_row_sums_kernel<1>), grid, block, 0, stream, a);
@@ -744,10 +860,15 @@ hipError_t launch_verify_sample(VerifySampleArgs a, hipStream_t stream) {
       hipLaunchKernelGGL((verify_row_sums_kernel<0>), grid, block, 0, stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (a.parts == kVsParts)
-      hipLaunchKernelGGL(verify_sample_from_sums_kernel<true>, dim3(a.B), dim3(kVsWalkThreads), 0, stream, a);
+    const dim3 walk(a.leaves ? 1 : a.parts, a.B), wg(kVsWalkThreads);
+    if (a.leaves && a.parts == kVsParts)
+      hipLaunchKernelGGL((verify_sample_from_sums_kernel<0, true, true>), walk, wg, 0, stream, a);
+    else if (a.leaves)
+      hipLaunchKernelGGL((verify_sample_from_sums_kernel<0, true, false>), walk, wg, 0, stream, a);
+    else if (cpb == 1)
+      hipLaunchKernelGGL((verify_sample_from_sums_kernel<1, false, false>), walk, wg, 0, stream, a);
     else
-      hipLaunchKernelGGL(verify_sample_from_sums_kernel<false>, dim3(a.B), dim3(kVsWalkThreads), 0, stream, a);
+      hipLaunchKernelGGL((verify_sample_from_sums_kernel<0, false, false>), walk, wg, 0, stream, a);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(verify_sample_kernel, dim3(a.B), dim3(kVsThreads), 0, stream, a);
