@@ -426,17 +426,21 @@ hipError_t launch_depth_continue(const BeamArgs& a, int steps_done, hipStream_t 
 
 // ---- one launch per draft call (rows that came through the GEMM path, or a caller that runs
 // the weight stream separately): one workgroup per sequence ---------------------------------------
+template <bool DENSE>
 __global__ __launch_bounds__(1024) void step_bookkeep_kernel(StepArgs a) {
   __shared__ StepSmem sm;
   const int b = blockIdx.x, tid = threadIdx.x;
   if (a.trace != nullptr && b == 0 && tid == 0) a.trace[0] = (uint64_t)wall_clock64();
-  const bool active = step_bookkeep_block(a, b, tid, blockDim.x, sm);
+  const bool active = step_bookkeep_block<DENSE>(a, b, tid, blockDim.x, sm);
   if (a.trace != nullptr && b == 0 && tid == 0) a.trace[5] = (uint64_t)wall_clock64();
   report_call(a.report, active, b, a.beam.k, tid, blockDim.x);
 }
 
 hipError_t launch_step_bookkeep(const StepArgs& a, hipStream_t stream) {
-  hipLaunchKernelGGL(step_bookkeep_kernel, dim3(a.beam.B), dim3(64 * a.beam.k), 0, stream, a);
+  if (a.nslice == 0)
+    hipLaunchKernelGGL(step_bookkeep_kernel<true>, dim3(a.beam.B), dim3(64 * a.beam.k), 0, stream, a);
+  else
+    hipLaunchKernelGGL(step_bookkeep_kernel<false>, dim3(a.beam.B), dim3(64 * a.beam.k), 0, stream, a);
   return hipGetLastError();
 }
 

@@ -151,7 +151,7 @@ __device__ __forceinline__ void merge_row_count(const uint64_t* __restrict__ pk,
       base += __popcll(bal);
       if (r == 2 && in && k > 3) more = true;
     }
-  if (__ballot(more) != 0ull || base > 64) {                       // uniform
+  if (__builtin_expect(__ballot(more) != 0ull || base > 64, 0)) {  // uniform
     merge_row<HPL>(pk, h, nslice, k, lane, my_key, lse);
     return;
   }
@@ -179,6 +179,24 @@ __device__ __forceinline__ void merge_row_dispatch(const uint64_t* pk, RowHeads&
   merge_row_count<kHPL>(pk, h, nslice, k, lane, my_key, lse, scratch);
 }
 
+// The first beam of a sequence, nodes 1 .. k in rank order: lane j < k passes token and logprob of rank j.  Returns the lane's logprobsum.
+__device__ __forceinline__ float beam_first(const BeamArgs& a, int b, int lane, int t, float s) {
+  const int k = a.k;
+  if (lane < k) {
+    const size_t at = (size_t)b * k + lane, node = (size_t)b * a.nmax + 1 + lane;
+    a.st.pool_token[node] = t;
+    a.st.pool_parent[node] = 0;
+    a.st.pool_depth[node] = 1;
+    a.st.pool_score[node] = s;
+    a.st.beam_node[at] = 1 + lane;
+    a.st.beam_token[at] = t;
+    a.st.beam_parent_slot[at] = 0;
+    a.st.logprobsum[at] = s;
+  }
+  if (lane == 0) a.st.n_nodes[b] = 1 + k;
+  return lane < k ? s : 0.f;
+}
+
 // ---- beam update by one wave (all 64 lanes active) -------------------------------------------
 // tok/lp: rows of k entries with the given row stride (LDS or global).  old_lps / old_node: the
 // current beam as loaded by lane i < k (ignored for step 0).
@@ -197,21 +215,7 @@ __device__ __forceinline__ float beam_update(const BeamArgs& a, int b, int lane,
 
   float new_lps = 0.f;
   if (step == 0) {
-    if (lane < k) {
-      const int nid = 1 + lane;
-      const int t = tok[lane];
-      const float s = lp[lane];
-      ptok[nid] = t;
-      ppar[nid] = 0;
-      pdep[nid] = 1;
-      psc[nid] = s;
-      bnode[lane] = nid;
-      btok[lane] = t;
-      bslot[lane] = 0;
-      lps[lane] = s;
-      new_lps = s;
-    }
-    if (lane == 0) a.st.n_nodes[b] = 1 + k;
+    new_lps = beam_first(a, b, lane, lane < k ? tok[lane] : 0, lane < k ? lp[lane] : 0.f);
   } else {
     const int base = 1 + k + (step - 1) * k * k;
     uint64_t cand[4];
@@ -277,44 +281,37 @@ __device__ __forceinline__ bool stop_test(const BeamArgs& a, int b, int lane, fl
   return cont;
 }
 
-// ---- one draft call of one sequence by one workgroup: merge of the sequence's rows, beam update,
-// stop test, and the final tree as soon as the sequence stops.  Every thread of the block must
-// call it (nthr a multiple of 64, at least 64); the rows are dealt round-robin to the waves.
+// ---- one draft call of one sequence by one workgroup of k waves: merge of the sequence's rows, a wave each, beam update, stop test,
+// and the final tree as soon as the sequence stops.  Every thread of the block must call it.
+// The launch follows a kernel that has streamed the whole LM head through the L2, so its instructions are fetched from behind it: what a
+// call runs lies together, rare ways (a merge by rounds, the tree) at the end, and what it cannot need - the other form of the rows, rows
+// beyond the waves - is not compiled in: 47 -> 21 KB for rows of the weight stream and 15 KB for the GEMM's, no spilled SGPRs.  A call of
+// ten rows 10.9 -> 9.7 us by the profiler; rounds of one user (six calls) 343.9 -> 333.0, of 64 sequences 981 -> 959, with the tree's selection.
 struct StepSmem {
   TreeSmem tsm;
-  int tok[kKM][kKM];
-  float lp[kKM][kKM];
-  uint64_t cand[kKM * kKM];   // beam keys of the k*k candidates (beam update by the whole block)
+  uint64_t cand[kKM * kKM];   // beam keys of the k*k candidates
   int rank[kKM * kKM];        // number of candidates with a larger key
   float newlps[kKM];          // logprobsum of the new beam
   uint64_t mrg[kKM][kMergeWords];   // per wave: candidates of the row merge and its result
   int stopped;
 };
 
-__device__ __forceinline__ void step_publish_row(const StepArgs& a, StepSmem& sm, int rw, size_t row, int lane,
-                                                 uint64_t key, float lse) {
-  if (lane < a.beam.k) {
-    sm.tok[rw][lane] = key_token(key);
-    sm.lp[rw][lane] = key_value(key) - lse;
-  }
-  if (a.lse_dbg != nullptr && lane == 0) a.lse_dbg[row] = lse;
-}
-
+// DENSE: the rows' keys are final (they came through the GEMM path).
 // Returns whether the sequence is still active after this call (the same value in every thread).
+template <bool DENSE>
 __device__ __forceinline__ bool step_bookkeep_block(const StepArgs& a, int b, int tid, int nthr, StepSmem& sm) {
   const BeamArgs& g = a.beam;
-  const int wave = tid >> 6, lane = tid & 63, nwaves = nthr >> 6;
+  const int wave = tid >> 6, lane = tid & 63;
   const int rows = (g.step == 0) ? 1 : g.k;
   const size_t row0 = (g.step == 0) ? (size_t)b : (size_t)b * g.k;
   // Issue every independent load first: the flag, this wave's slice heads, the current beam.
   const uint8_t active = g.st.active[b];
-  const bool dense = (a.nslice == 0);             // keys already final (rows came through the GEMM path)
   const size_t row = row0 + min(wave, rows - 1);
-  const uint64_t* pk = a.part_key + row * (dense ? 1 : a.nslice) * g.k;
+  const uint64_t* pk = a.part_key + row * (DENSE ? 1 : a.nslice) * g.k;
   RowHeads heads;
   uint64_t key = 0ull;
   float lse = 0.f;
-  if (dense) {
+  if (DENSE) {
     key = pk[min(lane, g.k - 1)];
     lse = a.part_sum[row];
   } else {
@@ -327,19 +324,12 @@ __device__ __forceinline__ bool step_bookkeep_block(const StepArgs& a, int b, in
   if (tid == 0) sm.stopped = 0;
   uint64_t* const trace = (a.trace != nullptr && b == 0 && tid == 0) ? a.trace : nullptr;
   if (trace != nullptr) {   // the stamp must follow the arrival of this wave's keys: use one
-    if (!dense && heads.q2[kHPL - 1] == 1ull) trace[7] = 1;       // (never true: keys are never 1)
+    if (!DENSE && heads.q2[kHPL - 1] == 1ull) trace[7] = 1;       // (never true: keys are never 1)
     trace[1] = (uint64_t)wall_clock64();
   }
-  // One wave per row (every call after the prompt call, launched with 64 * k threads): the whole block takes
-  // part in the beam update.  Otherwise (the prompt call's single row; fewer waves than rows) wave 0 does it
-  // from the rows' results in LDS.
-  const bool by_block = g.step >= 1 && nwaves >= rows;
-  if (wave < rows) {
-    if (!dense) merge_row_dispatch(pk, heads, a.nslice, g.k, lane, key, lse, sm.mrg[wave]);
-    if (!by_block) step_publish_row(a, sm, wave, row, lane, key, lse);
-  }
+  if (!DENSE && wave < rows) merge_row_dispatch(pk, heads, a.nslice, g.k, lane, key, lse, sm.mrg[wave]);
   if (trace != nullptr) trace[2] = (uint64_t)wall_clock64();
-  if (by_block) {
+  if (g.step >= 1) {
     // ---- Algorithm 1's beam update by all k waves: wave i holds row i's k candidates in its lanes j < k ------
     const int k = g.k, kk = k * k;
     const int base = 1 + k + (g.step - 1) * kk;
@@ -398,33 +388,17 @@ __device__ __forceinline__ bool step_bookkeep_block(const StepArgs& a, int b, in
       const bool cont = stop_test(g, b, lane, lane < k ? sm.newlps[lane] : 0.f, g.step + 1);
       if (lane == 0 && !cont) sm.stopped = 1;
     }
-  } else {
-  for (int rw = wave + nwaves; rw < rows; rw += nwaves) {   // fewer waves than rows: further passes
-    const size_t row2 = row0 + rw;
-    const uint64_t* pk2 = a.part_key + row2 * (dense ? 1 : a.nslice) * g.k;
-    uint64_t key2;
-    float lse2;
-    if (dense) {
-      key2 = pk2[min(lane, g.k - 1)];
-      lse2 = a.part_sum[row2];
-    } else {
-      RowHeads heads2;
-      merge_load_heads(pk2, a.part_sum + row2 * a.nslice, a.nslice, g.k, lane, heads2);
-      merge_row_dispatch(pk2, heads2, a.nslice, g.k, lane, key2, lse2, sm.mrg[wave]);
-    }
-    step_publish_row(a, sm, rw, row2, lane, key2, lse2);
-  }
-  __syncthreads();
-  if (wave == 0) {
-    const float v = beam_update(g, b, lane, &sm.tok[0][0], &sm.lp[0][0], kKM, old_lps, old_node);
-    const bool cont = stop_test(g, b, lane, v, g.step + 1);
+  } else if (wave == 0) {                         // the prompt call's single row
+    if (a.lse_dbg != nullptr && lane == 0) a.lse_dbg[row] = lse;
+    const float v = beam_first(g, b, lane, key_token(key), key_value(key) - lse);
+    if (lane == 0) g.st.steps[b] = 1;
+    const bool cont = stop_test(g, b, lane, v, 1);
     if (lane == 0 && !cont) sm.stopped = 1;
-  }
   }
   __syncthreads();                                // also orders wave 0's pool writes before the reads below
   if (trace != nullptr) trace[3] = (uint64_t)wall_clock64();
-  if (a.tree.mask != nullptr && sm.stopped)   // pool size after this call: 1 + k + step * k^2 (as beam_update just stored it)
-    tree_finalize_block(g.st, a.tree, b, a.m, g.nmax, tid, nthr, sm.tsm, 1 + g.k + g.step * g.k * g.k);
+  if (__builtin_expect(a.tree.mask != nullptr && sm.stopped, 0))   // pool size after this call: 1 + k + step * k^2, as just stored
+    tree_finalize_block<2>(g.st, a.tree, b, a.m, g.nmax, tid, nthr, sm.tsm, 1 + g.k + g.step * g.k * g.k);
   if (trace != nullptr) trace[4] = (uint64_t)wall_clock64();
   return !sm.stopped;
 }

@@ -7,7 +7,7 @@ namespace ddd {
 
 __global__ __launch_bounds__(1024) void tree_finalize_kernel(FinalizeArgs a) {
   __shared__ TreeSmem sm;
-  tree_finalize_block(a.st, a.tree, blockIdx.x, a.m, a.nmax, threadIdx.x, blockDim.x, sm);
+  tree_finalize_block<4>(a.st, a.tree, blockIdx.x, a.m, a.nmax, threadIdx.x, blockDim.x, sm);
 }
 
 hipError_t launch_tree_finalize(const FinalizeArgs& a, hipStream_t stream) {

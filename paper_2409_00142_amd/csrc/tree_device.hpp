@@ -212,77 +212,61 @@ __device__ __forceinline__ uint32_t block_kth_largest_u32(const uint32_t* vals, 
   return red[0];
 }
 
-// By one wave: the tree indices of the `want` best of nodes 1 .. n (n <= 64 S, keys[i] the rerank key of node i + 1), i.e. 1 + the
-// number of taken nodes with a smaller id, to tidx, and their ids to sel.  Of equal scores the lowest ids are taken.
-template <int S>
-__device__ __forceinline__ void wave_take(const uint64_t* keys, int n, int want, int lane, int* tidx, int* sel) {
-  uint32_t key[S];
-#pragma unroll
-  for (int q = 0; q < S; ++q) key[q] = 64 * q + lane < n ? (uint32_t)(keys[64 * q + lane] >> 32) : 0u;
-  const uint32_t T = want < n ? wave_prefix<S>(key, want) : 0u;
-  int above = 0;
-#pragma unroll
-  for (int q = 0; q < S; ++q) above += __popcll(__ballot(key[q] > T));
-  int left = want - above, t0 = 1;         // places for keys equal to T; the next tree index
-  const unsigned long long below = (1ull << lane) - 1ull;
-#pragma unroll
-  for (int q = 0; q < S; ++q) {
-    const bool real = 64 * q + lane < n;
-    const unsigned long long eq = __ballot(real && key[q] == T);
-    const bool in = key[q] > T || (real && key[q] == T && (int)__popcll(eq & below) < left);
-    left -= min(left, (int)__popcll(eq));
-    const unsigned long long bal = __ballot(in);
-    if (in) {
-      const int t = t0 + __popcll(bal & below), id = 64 * q + lane + 1;
-      tidx[id] = t;
-      sel[t] = id;
-    }
-    t0 += __popcll(bal);
-  }
+// Orders LDS alone: global loads stay in flight.
+__device__ __forceinline__ void tree_lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// Inclusive prefix sums over the first 32 lanes.
+__device__ __forceinline__ uint32_t scan32_u32(uint32_t x, int lane) {
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, true);   // row_shr:1, 2, 4, 8 (0 comes in)
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, true);
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, true);
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, true);
+  const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)x, 15);
+  return lane >= 16 ? x + first : x;
+}
+// Sums over the lanes from this one up to lane 63.
+__device__ __forceinline__ int suffix64_i32(int x, int lane) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x101, 0xf, 0xf, true);                  // row_shl:1, 2, 4, 8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x102, 0xf, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x104, 0xf, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x108, 0xf, 0xf, true);
+  const int r1 = __builtin_amdgcn_readlane(x, 16), r2 = __builtin_amdgcn_readlane(x, 32), r3 = __builtin_amdgcn_readlane(x, 48);
+  return x + (lane < 16 ? r1 + r2 + r3 : lane < 32 ? r2 + r3 : lane < 48 ? r3 : 0);
 }
 
-// Pools of up to kSelMax nodes on a block with at least half as many threads: thread t looks after pool nodes
-// t + 1 and t + 1 + nthr from their scores to their lines of the tree, so nothing is searched for and nothing is
-// fetched twice.  One round trip brings the pool's size and every node's score, parent, token and depth.  Selection, up to kWaveTake
-// nodes: wave 0 alone finds the m-th largest score bit by bit and hands out the tree indices (wave_take), without a barrier; what it
-// costs grows with the nodes per lane.  (Ranking candidates against each other with the whole block, as below, or up to 256 nodes all
-// of them, takes up to ten barriers more; ddd_tree_finalize of one sequence with 211 / 411 / 511 / 690 / 911 nodes: 6.2 / 5.9 / 8.2 /
-// 15.3 / 8.6 us, now 4.9 / 5.3 / 6.6 / 9.5 / 8.4; 64 sequences with 911: 15.3, now 10.6.)  Beyond: the m-th best key
-// among the first kSub nodes is a lower bound of the tree's keys (summed logprobs fall with depth, so the early
-// nodes hold most of the tree and the bound is tight); the nodes at or above it - the candidates, usually little
-// more than m - are ranked among themselves by counting (keys are distinct: the id is part of them), which costs
-// kSub^2 + C^2 comparisons instead of N^2 or a sort's long chain of dependent stages (if more than kSelCand nodes
-// pass the bound, the m-th best of kRefine of them is a tighter one: twice at most).  Still more than kSelCand candidates after two
-// tightenings: the caller's general path takes over (returns false; nothing has been written to the tree).  A
-// parent's tree index is read from the node -> index table (a selected node's parent is selected: its score is no
-// smaller and its id is smaller).
-constexpr int kSelMax = 2048, kSub = 128, kSelCand = 384, kWaveTake = 1024, kRefine = 256;
-static_assert(kRefine >= DDD_MMAX && kRefine <= kSelCand, "the refining sample holds m keys and lies in the candidate list");
-static_assert(kSub >= DDD_MMAX, "the subset must hold m keys");
-__device__ __forceinline__ bool tree_select_block(const ddd_state& st, const ddd_tree& tree, int b, int m, int nmax,
+// Pools of up to Q nodes per thread of the block: thread t looks after pool nodes t + 1, t + 1 + nthr, ... from their scores to their
+// lines of the tree, so nothing is searched for and nothing is fetched twice.  One round trip brings the pool's size and every node's
+// score, parent, token and depth.  Selection: the m-th largest score (ordered bits) is found six bits at a time by the whole block -
+// a wave's 64 digits are counted by ballots, lane d the digit d, the waves' counts meet in LDS behind one barrier, and every wave draws
+// the same conclusion - and no further than a prefix that exactly m nodes reach, three passes as a rule; of equal scores the lowest ids are
+// taken.  The tree index of a selected node is 1 + the number of selected nodes with a smaller id (ballots, and the waves' totals through
+// LDS).  A parent's tree index is read from the node -> index table (a selected node's parent is selected: its score is no smaller and
+// its id is smaller).
+// A launch is latency alone, and small code: behind a stream of weights its instructions come from memory.  ddd_tree_finalize and
+// ddd_verify_accept of one sequence with 811 nodes 11.2 -> 9.2 us (9 is what the host takes for the two), 785 nodes and m = 127 12.4 -> 9.2,
+// 2065 nodes (sorted as a whole before) 36.9 -> 10.7; 64 sequences with 511 nodes 10.4 -> 9.9, 1793 20.0 -> 12.8; up to 511 nodes of one
+// sequence the same 5.4 us on the GPU as with one wave that found the score bit by bit.
+constexpr int kTreeMost = kPoolMax;        // nodes of the largest pool
+constexpr int kTreeDigit = 6, kTreePasses = (32 + kTreeDigit - 1) / kTreeDigit;
+template <int Q>
+__device__ __forceinline__ void tree_select_block(const ddd_state& st, const ddd_tree& tree, int b, int m, int nmax,
                                                   int tid, int nthr, TreeSmem& sm, int n_nodes) {
   const int T = m + 1;
-  // the upper half of the key array holds the working set of the selection
-  int* tidx = reinterpret_cast<int*>(sm.keys + kSelMax + 2);     // [kSelMax + 1]  tree index of a pool node; -1: not in the tree
-  uint64_t* ckey = reinterpret_cast<uint64_t*>(tidx + kSelMax + 2);   // [kSelCand] candidate keys
-  int* cnode = reinterpret_cast<int*>(ckey + kSelCand);          // [kSelCand]     their pool ids
-  int* rank = cnode + kSelCand;                                   // [kSelCand]     larger keys counted
-  int* wtot = rank + kSelCand;                                    // [2][16]        selected nodes per wave and pass
-  int* misc = wtot + 32;                                          // [0] candidates so far
-  uint64_t* bound = reinterpret_cast<uint64_t*>(misc + 2);        // [1] the lower bound
-  static_assert((kSelMax + 2) * 8 + (kSelMax + 2) * 4 + kSelCand * 16 + 34 * 4 + 8 <= (kPoolMax + 2) * 8, "working set");
+  int* tidx = reinterpret_cast<int*>(sm.keys);                    // [kTreeMost + 2]  tree index of a pool node; -1: not in the tree
+  int* hist = tidx + kTreeMost + 2;                               // [kTreePasses][64] nodes per digit
+  uint32_t* wtot = reinterpret_cast<uint32_t*>(hist + kTreePasses * 64);   // [Q][16]  a wave's larger (low half) and equal scores
+  static_assert((kTreeMost + 2 + kTreePasses * 64 + Q * 16) * 4 <= (kPoolMax + 2) * 8, "working set");
+  static_assert(Q == 2 || Q == 4, "totals are scanned 32 at a time");
   const int32_t* ppar = st.pool_parent + (size_t)b * nmax;
   const int32_t* pdep = st.pool_depth + (size_t)b * nmax;
   const int32_t* ptok = st.pool_token + (size_t)b * nmax;
   const float* psc = st.pool_score + (size_t)b * nmax;
-  const int lane = tid & 63, wave = tid >> 6, nwaves = nthr >> 6;
-  bool node[2];
-  uint64_t my_key[2];
-  int my_pn[2], my_tok[2], my_dep[2], root_tok = -1, root_dep = 0;
-  float my_sc[2];
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nwaves = nthr >> 6;
+  int my_pn[Q], my_tok[Q], my_dep[Q], root_tok = -1, root_dep = 0;
+  float my_sc[Q];
   const int most = (n_nodes >= 0 ? n_nodes : nmax) - 1;           // the pool's size, if the caller has it not at hand, in the same trip
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
+  for (int q = 0; q < Q; ++q) {
     const int n = tid + q * nthr;                                 // pool node n + 1
     my_sc[q] = 0.f;
     my_pn[q] = 0;
@@ -300,128 +284,101 @@ __device__ __forceinline__ bool tree_select_block(const ddd_state& st, const ddd
     root_dep = pdep[0];
   }
   const int N = (n_nodes >= 0 ? n_nodes : min(st.n_nodes[b], nmax)) - 1, m_eff = min(m, N);
-#pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const int n = tid + q * nthr;
-    node[q] = n < N;
-    my_key[q] = 0ull;
-    if (node[q]) {
-      my_key[q] = rerank_key(my_sc[q], n + 1);
-      sm.keys[n] = my_key[q];
-      tidx[n + 1] = -1;
-    }
-  }
-  const int S = min(N, kSub);
-  if (tid < kSelCand) rank[tid] = 0;
-  for (int i = tid + nthr; i < kSelCand; i += nthr) rank[i] = 0;
+  for (int i = tid; i < kTreePasses * 64; i += nthr) hist[i] = 0;
+  for (int i = tid; i < Q * 16; i += nthr) wtot[i] = 0u;          // of waves that are not there
   if (tid == 0) {
     tidx[0] = 0;
-    misc[0] = 0;
     sm.e.sel[0] = 0;
     sm.e.par[0] = -1;
   }
-  __syncthreads();
-  int ti[2] = {-1, -1};
-  if (N <= kWaveTake) {                                           // uniform
-    if (wave == 0) {
-      if (N <= 128)
-        wave_take<2>(sm.keys, N, m_eff, lane, tidx, sm.e.sel);
-      else if (N <= 256)
-        wave_take<4>(sm.keys, N, m_eff, lane, tidx, sm.e.sel);
-      else if (N <= 512)
-        wave_take<8>(sm.keys, N, m_eff, lane, tidx, sm.e.sel);
-      else if (N <= 768)
-        wave_take<12>(sm.keys, N, m_eff, lane, tidx, sm.e.sel);
-      else
-        wave_take<kWaveTake / 64>(sm.keys, N, m_eff, lane, tidx, sm.e.sel);
-    }
-    __syncthreads();
+  tree_lds_barrier();
+  uint32_t key[Q];
+  bool real[Q];
 #pragma unroll
-    for (int q = 0; q < 2; ++q)
-      if (node[q]) ti[q] = tidx[tid + q * nthr + 1];
-  } else {
-    // the bound: first from the early nodes, then - while more than kSelCand nodes pass it (a confident sequence: its
-    // deep nodes score as well as the early ones) - from the first kRefine candidates, which lie above the old bound
-    const uint64_t* sample = sm.keys;
-    int n_sample = S, C = 0;
-    for (int attempt = 0;; ++attempt) {
-      count_larger_keys(sample, n_sample, rank, tid, nthr);
-      __syncthreads();
-      for (int i = tid; i < n_sample; i += nthr)
-        if (rank[i] == min(m_eff, n_sample) - 1) bound[0] = sample[i];   // exactly one key has this rank
-      if (tid == 0) misc[0] = 0;
-      __syncthreads();
-      const uint64_t lowest = bound[0];
-      __syncthreads();                                              // everybody has the bound and is done with the ranks and the sample
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        const bool cand = node[q] && my_key[q] >= lowest;
-        const unsigned long long bal = __ballot(cand);
-        int base = 0;
-        if (lane == 0 && bal != 0ull) base = atomicAdd(&misc[0], __popcll(bal));
-        base = __shfl(base, 0, 64);
-        const int pos = base + __popcll(bal & ((1ull << lane) - 1ull));
-        if (cand && pos < kSelCand) {
-          ckey[pos] = my_key[q];
-          cnode[pos] = tid + q * nthr + 1;
-        }
-      }
-      if (tid < kSelCand) rank[tid] = 0;
-      for (int i = tid + nthr; i < kSelCand; i += nthr) rank[i] = 0;
-      __syncthreads();
-      C = misc[0];
-      if (C <= kSelCand) break;                                     // uniform
-      if (attempt == 2) return false;                               // uniform: the general path
-      sample = ckey;
-      n_sample = kRefine;
-    }
-    count_larger_keys(ckey, C, rank, tid, nthr);
-    __syncthreads();
-    for (int c = tid; c < C; c += nthr)
-      if (rank[c] < m_eff) tidx[cnode[c]] = -2;                     // in the tree; its index follows
-    __syncthreads();
-    bool chosen[2];
-    unsigned long long bal[2];
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      chosen[q] = node[q] && tidx[tid + q * nthr + 1] == -2;
-      bal[q] = __ballot(chosen[q]);
-      if (lane == 0) wtot[q * 16 + wave] = __popcll(bal[q]);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      if (chosen[q]) {
-        int t = 1 + __popcll(bal[q] & ((1ull << lane) - 1ull));
-        for (int w = 0; w < wave; ++w) t += wtot[q * 16 + w];
-        if (q == 1)
-          for (int w = 0; w < nwaves; ++w) t += wtot[w];
-        ti[q] = t;
-        sm.e.sel[t] = tid + q * nthr + 1;
-        tidx[tid + q * nthr + 1] = t;
-      }
-    }
-    __syncthreads();
+  for (int q = 0; q < Q; ++q) {
+    real[q] = tid + q * nthr < N;
+    key[q] = ord32(my_sc[q]);
   }
+  // ---- thr: the m_eff-th largest score, or a prefix that exactly m_eff reach ---------------------------------------
+  uint32_t thr = 0u;
+  if (m_eff < N) {                                                // uniform
+    int above = 0;                                                // scores beyond the prefix
+#pragma unroll 1
+    for (int pass = 0; pass < kTreePasses; ++pass) {
+      const int shift = max(32 - kTreeDigit * (pass + 1), 0);
+      const int bits = pass == kTreePasses - 1 ? 32 - kTreeDigit * (kTreePasses - 1) : kTreeDigit;   // of this digit
+      const uint32_t known = pass == 0 ? 0u : ~0u << (shift + bits);
+      int cnt = 0;
 #pragma unroll
-  for (int q = 0; q < 2; ++q)
+      for (int q = 0; q < Q; ++q) {
+        if (wave * 64 + q * nthr >= N) continue;                  // wave-uniform
+        unsigned long long at = __ballot(real[q] && ((key[q] ^ thr) & known) == 0u);   // lanes of this lane's digit
+#pragma unroll
+        for (int i = 0; i < kTreeDigit; ++i) {
+          const unsigned long long set = __ballot(i < bits && ((key[q] >> (shift + i)) & 1u) != 0u);
+          at &= ((lane >> i) & 1) != 0 ? set : ~set;
+        }
+        cnt += __popcll(at);
+      }
+      if (cnt != 0) atomicAdd(&hist[pass * 64 + lane], cnt);
+      __syncthreads();
+      const int from = above + suffix64_i32(hist[pass * 64 + lane], lane);   // scores that reach this lane's digit: falling, lane 0 all
+      const int d = 63 - __clzll((long long)__ballot(from >= m_eff));
+      const int reach = __builtin_amdgcn_readlane(from, d);
+      if (d < 63) above = __builtin_amdgcn_readlane(from, d + 1);
+      thr |= (uint32_t)d << shift;
+      if (reach == m_eff) break;                                  // uniform
+    }
+  }
+  // ---- tree indices --------------------------------------------------------------------------------------------------
+  unsigned long long larger[Q], equal[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    larger[q] = __ballot(real[q] && key[q] > thr);
+    equal[q] = __ballot(real[q] && key[q] == thr);
+    if (lane == 0) wtot[q * 16 + wave] = (uint32_t)__popcll(larger[q]) | (uint32_t)__popcll(equal[q]) << 16;
+  }
+  __syncthreads();
+  int ti[Q];
+  {
+    const unsigned long long below = (1ull << lane) - 1ull;
+    uint32_t own[Q / 2], before[Q / 2], all = 0u;                 // totals of nodes with smaller ids
+#pragma unroll
+    for (int h = 0; h < Q / 2; ++h) {
+      own[h] = lane < 32 ? wtot[h * 32 + lane] : 0u;
+      const uint32_t incl = scan32_u32(own[h], lane);
+      before[h] = all + incl - own[h];
+      all += (uint32_t)__builtin_amdgcn_readlane((int)incl, 31);
+    }
+    const int left = m_eff - (int)(all & 0xFFFFu);                // places for scores equal to thr
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const uint32_t pre = (uint32_t)__builtin_amdgcn_readlane((int)before[q / 2], (q & 1) * 16 + wave);
+      const int gt = (int)(pre & 0xFFFFu) + __popcll(larger[q] & below), eq = (int)(pre >> 16) + __popcll(equal[q] & below);
+      const bool in = real[q] && (key[q] > thr || (key[q] == thr && eq < left));
+      ti[q] = in ? 1 + gt + min(eq, left) : -1;
+      if (real[q]) tidx[tid + q * nthr + 1] = ti[q];
+      if (in) sm.e.sel[ti[q]] = tid + q * nthr + 1;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < Q; ++q)
     if (ti[q] >= 0) {
       const int p = tidx[my_pn[q]];
       sm.e.par[ti[q]] = p < ti[q] ? p : -1;   // a pool whose parents do not come first must not send the walk below in a circle
     }
   __syncthreads();
-  for (int i = tid; i < T; i += nthr) {
+  for (int i = tid; i < T; i += nthr) {                           // ancestor rows
+    uint32_t w[kMaskWords] = {};
+    for (int c = i <= m_eff ? i : -1; c >= 0; c = sm.e.par[c]) {
+      const uint32_t bit = 1u << (c & 31);
 #pragma unroll
-    for (int w = 0; w < kMaskWords; ++w) sm.e.bits[i][w] = 0u;
-    if (i <= m_eff) {
-      int c = i;
-      while (c >= 0) {
-        sm.e.bits[i][c >> 5] |= (1u << (c & 31));
-        c = sm.e.par[c];
-      }
+      for (int x = 0; x < kMaskWords; ++x) w[x] |= (c >> 5) == x ? bit : 0u;
     }
+#pragma unroll
+    for (int x = 0; x < kMaskWords; ++x) sm.e.bits[i][x] = w[x];
   }
-  __syncthreads();
   if (tid == 0) {
     tree.n_sel[b] = m_eff;
     tree.tree_token[(size_t)b * T] = root_tok;
@@ -430,7 +387,7 @@ __device__ __forceinline__ bool tree_select_block(const ddd_state& st, const ddd
   }
   for (int i = tid; i < m; i += nthr) tree.sel_node[(size_t)b * m + i] = (i < m_eff) ? sm.e.sel[1 + i] : -1;
 #pragma unroll
-  for (int q = 0; q < 2; ++q)
+  for (int q = 0; q < Q; ++q)
     if (ti[q] >= 0) {
       tree.tree_token[(size_t)b * T + ti[q]] = my_tok[q];
       tree.pos[(size_t)b * T + ti[q]] = my_dep[q];
@@ -441,25 +398,28 @@ __device__ __forceinline__ bool tree_select_block(const ddd_state& st, const ddd
     tree.pos[(size_t)b * T + i] = 0;
     tree.parent_idx[(size_t)b * T + i] = -1;
   }
+  tree_lds_barrier();
   uint8_t* mask = tree.mask + (size_t)b * T * T;
-  for (int e = tid; e < T * T; e += nthr) {
-    const int i = e / T, j = e - i * T;
-    mask[e] = (uint8_t)((sm.e.bits[i][j >> 5] >> (j & 31)) & 1u);
-  }
-  return true;
+  for (int i = wave; i < T; i += nwaves)                          // a row per wave
+    for (int j = lane; j < T; j += 64) mask[i * T + j] = (uint8_t)((sm.e.bits[i][j >> 5] >> (j & 31)) & 1u);
 }
 
 // Pools of at most DDD_POOL_MAX nodes: the rerank keys sit in LDS (they are distinct: the id is part
 // of the key) and the m_eff largest are kept.
 // Must be called by every thread of the block.
 // n_nodes: the sequence's pool size (st.n_nodes[b]) if the caller has it at hand, else -1.
+template <int QMOST>
 __device__ __forceinline__ void tree_finalize_block(const ddd_state& st, const ddd_tree& tree, int b, int m, int nmax,
                                                     int tid, int nthr, TreeSmem& sm, int n_nodes = -1) {
-  const int narrow = nthr <= 1024 ? min(kSelMax, 2 * nthr) : 0;
-  if (n_nodes < 0 && nmax - 1 > narrow) n_nodes = st.n_nodes[b];
-  if ((n_nodes >= 0 ? n_nodes : nmax) - 1 <= narrow) {             // uniform
-    if (tree_select_block(st, tree, b, m, nmax, tid, nthr, sm, n_nodes)) return;
-    __syncthreads();                                              // the general path reuses the key array
+  if (n_nodes < 0 && nmax - 1 > 2 * nthr) n_nodes = st.n_nodes[b];
+  const int most = (n_nodes >= 0 ? n_nodes : nmax) - 1;
+  if (nthr <= 1024 && most <= 2 * nthr) {                         // uniform
+    tree_select_block<2>(st, tree, b, m, nmax, tid, nthr, sm, n_nodes);
+    return;
+  }
+  if (QMOST >= 4 && nthr <= 1024 && most <= 4 * nthr) {
+    tree_select_block<4>(st, tree, b, m, nmax, tid, nthr, sm, n_nodes);
+    return;
   }
   if (n_nodes < 0) n_nodes = st.n_nodes[b];
   const int N = n_nodes - 1;
