@@ -64,7 +64,7 @@ struct HeadShape {
   float once;   // what a cut of one pass costs beside one of several: calls that walk W in opposite directions find in the memory-side
                 // cache what the call before read last, but a single pass reads all rows at once, along k
   int once_most;   // ... in calls of up to so many blocks of 32 rows: with more the products take longer than W
-  HeadPlan known;   // the plan, where the number of rows is known before the launch (bm = 0: it is not)
+  HeadPlan known;  // the plan, where the host knows the number of rows (bm = 0: it does not, and the kernel makes it)
 };
 // In ns, fitted to 900 calls of 20 to 640 rows with V = 4000 to 128256 and H = 1024 to 5120, walking W in one direction and in
 // alternating ones, each with up to ten cuts (the chosen cut is 0.65 % slower than the best one on average; with whole passes at the
@@ -99,7 +99,6 @@ inline HeadPlan head_plan_host(const HeadShape& h, int n_act) {
 }
 // The same by all 64 lanes of a wave, one result in every wave: lanes 0 .. 31 price 128-row tiles, the others 256-row tiles.
 __device__ __forceinline__ HeadPlan head_plan(const HeadShape& h, int n_act, int lane) {
-  if (h.known.bm != 0) return h.known;
   const int nblk = (n_act + 31) >> 5, bm = lane < 32 ? 128 : 256, NT = (nblk + 9) / 10 + (lane & 31);
   const float price = head_price(h, n_act, bm, NT);
   const uint32_t key = price > 0.f ? ~__float_as_uint(price) : 0u;                                 // the order of positive floats

@@ -423,19 +423,29 @@ __device__ __forceinline__ void gemm_widths(const GemmArgs& a, unsigned char* ld
     gemm_units<AB, 1, LIN>(a, lds, n_act, NT, bpt, S);
 }
 
-// Inside a round the number of active rows is only known on the device, so the kernels pick their tiles themselves.  WIDE: 256-row tiles of W for
+// With flags the number of active rows is only known on the device, so the kernels pick their tiles themselves.  WIDE: 256-row tiles of W for
 // more than 128 hidden rows may be among them (accumulators in every register of a wave).
 template <bool WIDE>
 __global__ __launch_bounds__(256, 1) void lmhead_gemm_kernel(GemmArgs a, HeadShape h) {
   extern __shared__ __align__(16) unsigned char lds[];     // the two tile rings of the chosen width
 
-  const int n_act = a.row_list != nullptr ? *a.n_act_ptr : a.n_rows;
+  const int n_act = *a.n_act_ptr;
   if (n_act <= 0) return;                                  // uniform
   const HeadPlan p = head_plan(h, n_act, threadIdx.x & 63);
   if (p.bm == 256)
     gemm_widths<4, (WIDE ? 5 : 2), false>(a, lds, n_act, p.NT, p.bpt, 1);
   else
     gemm_widths<2, 5, false>(a, lds, n_act, p.NT, p.bpt, 1);
+}
+
+// Where the host knows the number of rows (a call without flags, a round's first call): the one width that the plan takes.  The kernels
+// above hold seven or ten of them with 500 and 1200 spilled SGPRs, this one 40 to 240.  A ddd_lmhead_topk call of 20 rows (V = 8000, H = 1024) 17.1
+// -> 16.4 us, 300 rows (V = 4001) 16.6 -> 15.9, 170 rows (V = 32003, H = 4096) 79.1 -> 78.3, 1024 rows (V = 32000, H = 2048) 152.2 -> 149.3, 128
+// rows (V = 128256) 219.9 -> 217.0.
+template <int AB, int BB>
+__global__ __launch_bounds__(256, 1) void lmhead_gemm_known_kernel(GemmArgs a, HeadPlan p) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  gemm_units<AB, BB, false>(a, lds, a.n_rows, p.NT, p.bpt, 1);
 }
 
 // A linear of the draft layer: column tiles and K ranges by gemm_plan, the other epilogues.
@@ -510,12 +520,32 @@ static hipError_t prepare_shape() {
 
 constexpr int kHeadLds = 160 * 1024;
 
+template <int AB, int BB>
+static hipError_t prepare_known() {
+  hipError_t e = hipSuccess;
+  if constexpr (BB > 1) e = prepare_known<AB, BB - 1>();
+  if (e == hipSuccess)
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&lmhead_gemm_known_kernel<AB, BB>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, GemmCfg<AB, BB>::kLdsBytes);
+  return e;
+}
+// bb: blocks of 32 rows per wave of the widest column tile, 1 <= bb <= BB.
+template <int AB, int BB>
+static void launch_known(const GemmArgs& a, const HeadPlan& p, int bb, int grid, hipStream_t stream) {
+  if constexpr (BB > 1) {
+    if (bb < BB) return launch_known<AB, BB - 1>(a, p, bb, grid, stream);
+  }
+  hipLaunchKernelGGL((lmhead_gemm_known_kernel<AB, BB>), dim3(grid), dim3(256), (GemmCfg<AB, BB>::kLdsBytes), stream, a, p);
+}
+
 hipError_t prepare_lmhead_gemm() {
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&lmhead_gemm_kernel<false>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, kHeadLds);
   if (e == hipSuccess)
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(&lmhead_gemm_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize,
                             kHeadLds);
+  if (e == hipSuccess) e = prepare_known<2, 5>();
+  if (e == hipSuccess) e = prepare_known<4, 5>();
   if (e == hipSuccess) e = prepare_shape<3, 5>();
   if (e == hipSuccess) e = prepare_shape<2, 5>();
   if (e == hipSuccess) e = prepare_shape<2, 3>();
@@ -580,10 +610,19 @@ hipError_t launch_lmhead_gemm(const GemmArgs& a, int max_rows, int grid, hipStre
   h.once_most = far ? 1 << 30 : 4;
   h.most = 10;
   h.known = HeadPlan{0, 0, 0};
-  if (a.row_list == nullptr) h.known = head_plan_host(h, a.n_rows);
+  if (a.row_list == nullptr) {
+    if (a.n_rows <= 0) return hipSuccess;
+    h.known = head_plan_host(h, a.n_rows);
+    const int bb = (h.known.bpt + 1) >> 1;
+    if (h.known.bm == 256)
+      launch_known<4, 5>(a, h.known, bb, grid, stream);
+    else
+      launch_known<2, 5>(a, h.known, bb, grid, stream);
+    return hipGetLastError();
+  }
   // Two kernels, because a launch of the one that has the wide tiles, twice the code, takes 1 us longer whatever tiles it uses: up to 320
   // rows it is only taken where 128-row tiles would need several passes over the workgroups.
-  const bool wide = a.row_list == nullptr ? h.known.bm == 256 && h.known.bpt > 4 : max_rows > 320 || (max_rows > 128 && (a.V + 127) / 128 > grid);
+  const bool wide = max_rows > 320 || (max_rows > 128 && (a.V + 127) / 128 > grid);
   if (!wide) h.most = 4;
   if (!wide)
     hipLaunchKernelGGL(lmhead_gemm_kernel<false>, dim3(grid), dim3(256), kHeadLds, stream, a, h);
