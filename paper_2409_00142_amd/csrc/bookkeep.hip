@@ -157,7 +157,7 @@ __global__ __launch_bounds__(256) void row_topk_kernel(RowTopkArgs a) {
     }
   __syncthreads();
   const int ng = s_ng;
-  if (ng <= kGrpListMax) {                                     // uniform
+  if (__builtin_expect(ng <= kGrpListMax, 1)) {                // uniform
     for (int i0 = wave; i0 < ng; i0 += 16) {
       float xv[4];
       int vv[4];
@@ -210,7 +210,7 @@ __global__ __launch_bounds__(256) void row_topk_kernel(RowTopkArgs a) {
   __syncthreads();
   const int cnt = s_cnt;
 
-  if (cnt <= 256) {                                            // uniform: the usual case, a few more than k candidates
+  if (__builtin_expect(cnt <= 256, 1)) {                       // uniform: the usual case, a few more than k candidates
     // ---- exact top-k among the candidates: a candidate's rank is the number of larger keys (keys are distinct) ---
     if (tid < cnt) {
       const uint64_t mine = s_cand[tid];
@@ -358,7 +358,7 @@ __global__ __launch_bounds__(kWideRowThreads) void row_topk_wide_kernel(RowTopkA
   }
   __syncthreads();
   const int cnt = s_cnt;
-  if (cnt <= kCandMax) {                                        // uniform
+  if (__builtin_expect(cnt <= kCandMax, 1)) {                   // uniform
     count_larger_keys(s_cand, cnt, s_rank, tid, kWideRowThreads);
     __syncthreads();
     for (int i = tid; i < cnt; i += kWideRowThreads)

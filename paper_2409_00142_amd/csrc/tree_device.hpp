@@ -171,32 +171,57 @@ __device__ __forceinline__ void count_larger_keys(const uint64_t* keys, int n, i
   }
 }
 
-// The largest prefix of an ordered 32-bit key that at least `want` of the wave's keys reach, found bit by bit (a compare and a scalar
-// popcount per slot), and no further than one that exactly `want` reach.
-template <int S>
-__device__ __forceinline__ uint32_t wave_prefix(const uint32_t (&key)[S], int want) {
-  uint32_t T = 0u;
-  for (uint32_t bit = 0x80000000u; bit != 0u; bit >>= 1) {
-    const uint32_t cand = T | bit;
-    int cnt = 0;
-#pragma unroll
-    for (int q = 0; q < S; ++q) cnt += __popcll(__ballot(key[q] >= cand));
-    if (cnt >= want) T = cand;
-    if (cnt == want) break;
-  }
-  return T;
+// Sums over the lanes from this one up to lane 63.
+__device__ __forceinline__ int suffix64_i32(int x, int lane) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x101, 0xf, 0xf, true);                  // row_shl:1, 2, 4, 8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x102, 0xf, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x104, 0xf, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x108, 0xf, 0xf, true);
+  const int r1 = __builtin_amdgcn_readlane(x, 16), r2 = __builtin_amdgcn_readlane(x, 32), r3 = __builtin_amdgcn_readlane(x, 48);
+  return x + (lane < 16 ? r1 + r2 + r3 : lane < 32 ? r2 + r3 : lane < 48 ? r3 : 0);
 }
+
 // The k-th largest of n values (1 <= k <= n <= kKthMost), ties counted: the smallest with fewer than k larger ones.  vals: LDS; red:
 // LDS [1].
-// By wave 0 alone; the block barriers also order the caller's writes of vals before and its reuse of them after.  (Counting by the
-// whole block, 32-bit compares against values that a wave reads from one address: 500 values 3.3 us on a CU; now 1.3.)
+// By wave 0 alone; the block barriers also order the caller's writes of vals before and its reuse of them after.  Six bits at a time from
+// the highest one in which any two values differ: the digits are counted in LDS, a lane looks after one of the 64, and the search ends at a
+// prefix that exactly k values reach, after two or three passes.  (Bit by bit, a compare and a popcount per 64 values and bit: row reduction
+// and beam update of a call of 100 beams 10.4 and 14.0 us, now 9.0 and 12.5; the row reduction of 170 rows 5.9, now 5.5; counting by the whole block, 32-bit compares against values that a wave reads from one address: 500 values 3.3 us on a CU.)
 constexpr int kKthMost = 64 * 8;           // eight values per lane
 template <int S>
 __device__ __forceinline__ uint32_t wave_kth_largest(const uint32_t* vals, int n, int k, int lane) {
-  uint32_t key[S];
+  __shared__ int hist[64];
+  uint32_t key[S], lo = 0xFFFFFFFFu, hi = 0u;
 #pragma unroll
-  for (int q = 0; q < S; ++q) key[q] = 64 * q + lane < n ? vals[64 * q + lane] : 0u;
-  const uint32_t T = wave_prefix<S>(key, k);
+  for (int q = 0; q < S; ++q) {
+    const bool real = 64 * q + lane < n;
+    key[q] = real ? vals[64 * q + lane] : 0u;
+    hi = umax32(hi, key[q]);
+    lo = real ? min(lo, key[q]) : lo;
+  }
+  hi = wave_max_u32(hi);
+  lo = ~wave_max_u32(~lo);
+  if (hi == lo) return hi;                                        // uniform, as everything below
+  int end = 32 - __clz((int)(hi ^ lo)), above = 0;                // bits below `end` are open; values beyond the prefix
+  uint32_t T = end == 32 ? 0u : hi >> end << end;
+  while (end > 0) {
+    const int width = min(end, 6), shift = end - width;
+    hist[lane] = 0;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int q = 0; q < S; ++q) {
+      const uint32_t rest = (key[q] - T) >> shift;                // a value of the prefix has a digit here, one beyond it more
+      if (64 * q + lane < n && key[q] >= T && (rest >> width) == 0u) atomicAdd(&hist[rest], 1);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const int from = above + suffix64_i32(hist[lane], lane);      // values that reach this lane's digit: falling, lane 0 all
+    const int d = 63 - __clzll((long long)__ballot(from >= k)), reach = __builtin_amdgcn_readlane(from, d);
+    if (d < 63) above = __builtin_amdgcn_readlane(from, d + 1);
+    T |= (uint32_t)d << shift;
+    end = reach == k ? 0 : shift;
+  }
   uint32_t least = 0xFFFFFFFFu;            // of the values at or above the prefix
 #pragma unroll
   for (int q = 0; q < S; ++q) least = (64 * q + lane < n && key[q] >= T) ? min(least, key[q]) : least;
@@ -224,22 +249,11 @@ __device__ __forceinline__ uint32_t scan32_u32(uint32_t x, int lane) {
   const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)x, 15);
   return lane >= 16 ? x + first : x;
 }
-// Sums over the lanes from this one up to lane 63.
-__device__ __forceinline__ int suffix64_i32(int x, int lane) {
-  x += __builtin_amdgcn_update_dpp(0, x, 0x101, 0xf, 0xf, true);                  // row_shl:1, 2, 4, 8
-  x += __builtin_amdgcn_update_dpp(0, x, 0x102, 0xf, 0xf, true);
-  x += __builtin_amdgcn_update_dpp(0, x, 0x104, 0xf, 0xf, true);
-  x += __builtin_amdgcn_update_dpp(0, x, 0x108, 0xf, 0xf, true);
-  const int r1 = __builtin_amdgcn_readlane(x, 16), r2 = __builtin_amdgcn_readlane(x, 32), r3 = __builtin_amdgcn_readlane(x, 48);
-  return x + (lane < 16 ? r1 + r2 + r3 : lane < 32 ? r2 + r3 : lane < 48 ? r3 : 0);
-}
-
 // Pools of up to Q nodes per thread of the block: thread t looks after pool nodes t + 1, t + 1 + nthr, ... from their scores to their
 // lines of the tree, so nothing is searched for and nothing is fetched twice.  One round trip brings the pool's size and every node's
 // score, parent, token and depth.  Selection: the m-th largest score (ordered bits) is found six bits at a time by the whole block -
-// a wave's 64 digits are counted by ballots, lane d the digit d, the waves' counts meet in LDS behind one barrier, and every wave draws
-// the same conclusion - and no further than a prefix that exactly m nodes reach, three passes as a rule; of equal scores the lowest ids are
-// taken.  The tree index of a selected node is 1 + the number of selected nodes with a smaller id (ballots, and the waves' totals through
+// the 64 digits are counted in LDS, one barrier, and every wave draws the same conclusion, lane d for the digit d - and no further than a
+// prefix that exactly m nodes reach, three passes as a rule; of equal scores the lowest ids are taken.  The tree index of a selected node is 1 + the number of selected nodes with a smaller id (ballots, and the waves' totals through
 // LDS).  A parent's tree index is read from the node -> index table (a selected node's parent is selected: its score is no smaller and
 // its id is smaller).
 // A launch is latency alone, and small code: behind a stream of weights its instructions come from memory.  ddd_tree_finalize and
@@ -306,21 +320,10 @@ __device__ __forceinline__ void tree_select_block(const ddd_state& st, const ddd
 #pragma unroll 1
     for (int pass = 0; pass < kTreePasses; ++pass) {
       const int shift = max(32 - kTreeDigit * (pass + 1), 0);
-      const int bits = pass == kTreePasses - 1 ? 32 - kTreeDigit * (kTreePasses - 1) : kTreeDigit;   // of this digit
-      const uint32_t known = pass == 0 ? 0u : ~0u << (shift + bits);
-      int cnt = 0;
+      const uint32_t known = pass == 0 ? 0u : ~0u << (32 - kTreeDigit * pass);
 #pragma unroll
-      for (int q = 0; q < Q; ++q) {
-        if (wave * 64 + q * nthr >= N) continue;                  // wave-uniform
-        unsigned long long at = __ballot(real[q] && ((key[q] ^ thr) & known) == 0u);   // lanes of this lane's digit
-#pragma unroll
-        for (int i = 0; i < kTreeDigit; ++i) {
-          const unsigned long long set = __ballot(i < bits && ((key[q] >> (shift + i)) & 1u) != 0u);
-          at &= ((lane >> i) & 1) != 0 ? set : ~set;
-        }
-        cnt += __popcll(at);
-      }
-      if (cnt != 0) atomicAdd(&hist[pass * 64 + lane], cnt);
+      for (int q = 0; q < Q; ++q)
+        if (real[q] && ((key[q] ^ thr) & known) == 0u) atomicAdd(&hist[pass * 64 + ((key[q] & ~known) >> shift)], 1);
       __syncthreads();
       const int from = above + suffix64_i32(hist[pass * 64 + lane], lane);   // scores that reach this lane's digit: falling, lane 0 all
       const int d = 63 - __clzll((long long)__ballot(from >= m_eff));

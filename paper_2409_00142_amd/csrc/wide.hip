@@ -239,7 +239,7 @@ __device__ __forceinline__ void tree_finalize_wide_block(const ddd_state& st, co
     }
     __syncthreads();
     const int C = sm.cnt;
-    if (C <= kWCand) {                                               // uniform
+    if (__builtin_expect(C <= kWCand, 1)) {                          // uniform
       count_larger_keys(cand, C, rank, tid, nthr);
       __syncthreads();
       for (int c = tid; c < C; c += nthr)
@@ -248,7 +248,7 @@ __device__ __forceinline__ void tree_finalize_wide_block(const ddd_state& st, co
     }
     __syncthreads();
   }
-  if (!ranked && m_eff < N && nthr == kWideThreads) {                           // uniform
+  if (__builtin_expect(!ranked && m_eff < N && nthr == kWideThreads, 0)) {      // uniform
     int n_sample = min(N, kWSub);
     for (int i = tid; i < n_sample; i += nthr) sample[i] = key_of(i);
     for (int attempt = 0; attempt < 3; ++attempt) {
@@ -287,7 +287,7 @@ __device__ __forceinline__ void tree_finalize_wide_block(const ddd_state& st, co
       __syncthreads();
     }
   }
-  if (!ranked) {
+  if (__builtin_expect(!ranked, 0)) {
     uint64_t kth = 0ull;                       // every key is at least 1
     if (m_eff < N) kth = block_select_kth<kGlobalChunk>(N, m_eff - 1, key_of, sm, tid);
     if (tid == 0) sm.cnt = 0;
@@ -305,12 +305,15 @@ __device__ __forceinline__ void tree_finalize_wide_block(const ddd_state& st, co
 
 // One draft call of one sequence by one workgroup; returns whether the sequence is still active after it
 // (the same value in every thread; true when no stop test is asked for).
+// KEYS: the row reduction has formed the candidates' beam keys (a call of a round, which also selects and tests).
+template <bool KEYS>
 __device__ __forceinline__ bool step_wide_block(const WideStepArgs& a, unsigned char* wsm_raw) {
   const BeamArgs& g = a.beam;
   const int b = blockIdx.x, tid = threadIdx.x, nthr = blockDim.x;
   const int k = g.k, step = g.step;
   WideSmem& sm = *reinterpret_cast<WideSmem*>(wsm_raw + wide_front_bytes(k));
-  const bool from_keys = (a.part_key != nullptr);
+  constexpr bool from_keys = KEYS;
+  const bool do_select = KEYS || a.do_select, do_stop = KEYS || a.do_stop;
   const size_t row0 = (step == 0) ? (size_t)b : (size_t)b * k;
   // The candidates' beam keys that the row reduction has formed, element f = tid + u * 1024, and the rows' first few of them (below):
   // on their way before the sequence's flag is looked at.
@@ -319,7 +322,7 @@ __device__ __forceinline__ bool step_wide_block(const WideStepArgs& a, unsigned 
   uint32_t* sample = reinterpret_cast<uint32_t*>(wsm_raw);       // [kWSub]
   const int per_row = min(k, max(1, kBeamSample / k)), n_sample = k * per_row;
   const int on_flag = g.st.active[b];
-  if (a.do_select && step > 0 && from_keys) {                    // uniform
+  if (do_select && step > 0 && from_keys) {                    // uniform
     const int i = tid / per_row;                                 // n_sample <= kBeamSample
     if (tid < n_sample) mine = a.part_key[row0 * k + i * k + (tid - i * per_row)];
 #pragma unroll
@@ -340,7 +343,7 @@ __device__ __forceinline__ bool step_wide_block(const WideStepArgs& a, unsigned 
   float* psc = g.st.pool_score + (size_t)b * g.nmax;
   int steps_done = a.steps_done;
 
-  if (a.do_select) {
+  if (do_select) {
     steps_done = step + 1;
     if (step == 0) {
       // the prompt call: nodes 1..k in rank order are the first beam
@@ -435,7 +438,7 @@ __device__ __forceinline__ bool step_wide_block(const WideStepArgs& a, unsigned 
       }
       __syncthreads();
       const int C = sm.cnt;
-      if (C <= kWCand) {                                          // uniform
+      if (__builtin_expect(C <= kWCand, 1)) {                     // uniform
         count_larger_keys(cand, C, rank, tid, nthr);
         __syncthreads();
         for (int i = tid; i < C; i += nthr)
@@ -480,7 +483,7 @@ __device__ __forceinline__ bool step_wide_block(const WideStepArgs& a, unsigned 
   }
 
   if (tid == 0) sm.stopped = 0;
-  if (a.do_stop) {
+  if (do_stop) {
     if (tid < 64) {                              // wave 0: lane l holds beam slots l and l + 64
       const double e0 = (tid < k) ? exp((double)lps[tid]) : 0.0, e1 = (tid + 64 < k) ? exp((double)lps[tid + 64]) : 0.0;
       const uint64_t b0 = (uint64_t)__double_as_longlong(e0), b1 = (uint64_t)__double_as_longlong(e1);
@@ -509,14 +512,15 @@ __device__ __forceinline__ bool step_wide_block(const WideStepArgs& a, unsigned 
   }
   __syncthreads();   // also orders the pool writes before the reads below
   const bool stopped = sm.stopped != 0;
-  if (a.tree.mask != nullptr && stopped)   // the candidate keys of the beam update are no longer needed: their LDS is the work area
+  if (__builtin_expect(a.tree.mask != nullptr && stopped, 0))   // the candidate keys of the beam update are no longer needed: their LDS is the work area
     tree_finalize_wide_block(g.st, a.tree, b, a.m, g.nmax, tid, nthr, sm, wsm_raw);
   return !stopped;
 }
 
+template <bool KEYS>
 __global__ __launch_bounds__(kWideThreads) void step_wide_kernel(WideStepArgs a) {
   extern __shared__ __align__(16) unsigned char wsm_raw[];
-  const bool active = step_wide_block(a, wsm_raw);
+  const bool active = step_wide_block<KEYS>(a, wsm_raw);
   report_call(a.report, active, blockIdx.x, a.beam.k, threadIdx.x, blockDim.x);
 }
 
@@ -529,12 +533,19 @@ __global__ __launch_bounds__(kWideThreads) void tree_finalize_wide_kernel(Finali
 static size_t wide_lds_bytes(int k) { return wide_front_bytes(k) + sizeof(WideSmem); }
 
 hipError_t prepare_wide() {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&step_wide_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)wide_lds_bytes(kKW));
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&step_wide_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     (int)wide_lds_bytes(kKW));
+  if (e == hipSuccess)
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&step_wide_kernel<false>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)wide_lds_bytes(kKW));
+  return e;
 }
 
 hipError_t launch_step_wide(const WideStepArgs& a, hipStream_t stream) {
-  hipLaunchKernelGGL(step_wide_kernel, dim3(a.beam.B), dim3(kWideThreads), wide_lds_bytes(a.beam.k), stream, a);
+  if (a.part_key != nullptr && a.do_select && a.do_stop)
+    hipLaunchKernelGGL(step_wide_kernel<true>, dim3(a.beam.B), dim3(kWideThreads), wide_lds_bytes(a.beam.k), stream, a);
+  else
+    hipLaunchKernelGGL(step_wide_kernel<false>, dim3(a.beam.B), dim3(kWideThreads), wide_lds_bytes(a.beam.k), stream, a);
   return hipGetLastError();
 }
 
