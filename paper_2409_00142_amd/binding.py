@@ -138,13 +138,19 @@ def load_library() -> C.CDLL:
     return lib
 
 
+# A call that launches one small kernel is as long as what the host does for it, so the wrappers below keep to the cheapest form of each
+# argument: a structure is passed itself (its argtype is a pointer: ctypes makes the reference, 0.8 us less a call than two byref objects), a
+# tensor is asked for its address before anything else.  ddd_tree_finalize and ddd_verify_accept of one sequence: 9.0 -> 8.4 us.
 def _ptr(t) -> Optional[int]:
     """Device (or host) pointer of a torch tensor / int / None."""
     if t is None:
         return None
-    if isinstance(t, int):
-        return t
-    return t.data_ptr()
+    try:
+        return t.data_ptr()
+    except AttributeError:
+        if isinstance(t, int):
+            return t
+        raise
 
 
 def _check(code: int, where: str) -> None:
@@ -244,59 +250,59 @@ def alloc_tree(cfg: ddd_config, device="cuda") -> Tuple[ddd_tree, Dict[str, "obj
 
 
 def ddd_round_reset(ctx, st: ddd_state, root_token=None, stream=None) -> None:
-    _check(load_library().ddd_round_reset(ctx, C.byref(st), _ptr(root_token),
+    _check((_lib or load_library()).ddd_round_reset(ctx, st, _ptr(root_token),
                                           current_stream() if stream is None else stream), "ddd_round_reset")
 
 
 def ddd_lmhead_topk(ctx, W, hid, n_rows, row_active, topk_token, topk_logprob, lse, logits_dbg=None, stream=None):
-    _check(load_library().ddd_lmhead_topk(ctx, _ptr(W), _ptr(hid), n_rows, _ptr(row_active), _ptr(topk_token),
+    _check((_lib or load_library()).ddd_lmhead_topk(ctx, _ptr(W), _ptr(hid), n_rows, _ptr(row_active), _ptr(topk_token),
                                           _ptr(topk_logprob), _ptr(lse), _ptr(logits_dbg),
                                           current_stream() if stream is None else stream), "ddd_lmhead_topk")
 
 
 def ddd_lmhead_topk_static(cfg: ddd_config, W, hid, n_rows, row_active, topk_token, topk_logprob, lse, stream=None):
     """ddd_lmhead_topk without a context and without any allocation (static device scratch)."""
-    _check(load_library().ddd_lmhead_topk_static(C.byref(cfg), _ptr(W), _ptr(hid), n_rows, _ptr(row_active),
+    _check((_lib or load_library()).ddd_lmhead_topk_static(C.byref(cfg), _ptr(W), _ptr(hid), n_rows, _ptr(row_active),
                                                  _ptr(topk_token), _ptr(topk_logprob), _ptr(lse),
                                                  current_stream() if stream is None else stream),
            "ddd_lmhead_topk_static")
 
 
 def ddd_static_scratch_bytes() -> int:
-    return int(load_library().ddd_static_scratch_bytes())
+    return int((_lib or load_library()).ddd_static_scratch_bytes())
 
 
 def ddd_beam_select(ctx, step, topk_token, topk_logprob, st: ddd_state, stream=None):
-    _check(load_library().ddd_beam_select(ctx, step, _ptr(topk_token), _ptr(topk_logprob), C.byref(st),
+    _check((_lib or load_library()).ddd_beam_select(ctx, step, _ptr(topk_token), _ptr(topk_logprob), st,
                                           current_stream() if stream is None else stream), "ddd_beam_select")
 
 
 def ddd_depth_continue(ctx, steps_done, st: ddd_state, stream=None):
-    _check(load_library().ddd_depth_continue(ctx, steps_done, C.byref(st),
+    _check((_lib or load_library()).ddd_depth_continue(ctx, steps_done, st,
                                              current_stream() if stream is None else stream), "ddd_depth_continue")
 
 
 def ddd_draft_step(ctx, step, W, hid, st: ddd_state, tree: Optional[ddd_tree] = None, logits_dbg=None, lse_dbg=None,
                    stream=None):
-    _check(load_library().ddd_draft_step(ctx, step, _ptr(W), _ptr(hid), C.byref(st),
-                                         C.byref(tree) if tree is not None else None, _ptr(logits_dbg), _ptr(lse_dbg),
+    _check((_lib or load_library()).ddd_draft_step(ctx, step, _ptr(W), _ptr(hid), st,
+                                         tree, _ptr(logits_dbg), _ptr(lse_dbg),
                                          current_stream() if stream is None else stream), "ddd_draft_step")
 
 
 def ddd_tree_finalize(ctx, st: ddd_state, tree: ddd_tree, stream=None):
-    _check(load_library().ddd_tree_finalize(ctx, C.byref(st), C.byref(tree),
+    _check((_lib or load_library()).ddd_tree_finalize(ctx, st, tree,
                                             current_stream() if stream is None else stream), "ddd_tree_finalize")
 
 
 def ddd_verify_accept(ctx, tree: ddd_tree, target_argmax, accept_len, accept_path, bonus_token, stream=None):
-    _check(load_library().ddd_verify_accept(ctx, C.byref(tree), _ptr(target_argmax), _ptr(accept_len),
+    _check((_lib or load_library()).ddd_verify_accept(ctx, tree, _ptr(target_argmax), _ptr(accept_len),
                                             _ptr(accept_path), _ptr(bonus_token),
                                             current_stream() if stream is None else stream), "ddd_verify_accept")
 
 
 def ddd_verify_sample(ctx, tree: ddd_tree, target_logits, temperature, u_accept, u_bonus, accept_len, accept_path,
                       bonus_token, stream=None):
-    _check(load_library().ddd_verify_sample(ctx, C.byref(tree), _ptr(target_logits), float(temperature), _ptr(u_accept),
+    _check((_lib or load_library()).ddd_verify_sample(ctx, tree, _ptr(target_logits), float(temperature), _ptr(u_accept),
                                             _ptr(u_bonus), _ptr(accept_len), _ptr(accept_path), _ptr(bonus_token),
                                             current_stream() if stream is None else stream), "ddd_verify_sample")
 
@@ -311,7 +317,7 @@ def _fn_ptr(fn) -> Optional[int]:
 
 def ddd_round_enqueue(ctx, W, st, tree, root_token, hid_buf, body, body_user, post=None, post_user=None,
                       logits_dbg=None, lse_dbg=None, stream=None):
-    _check(load_library().ddd_round_enqueue(ctx, _ptr(W), C.byref(st), C.byref(tree), _ptr(root_token), _ptr(hid_buf),
+    _check((_lib or load_library()).ddd_round_enqueue(ctx, _ptr(W), st, tree, _ptr(root_token), _ptr(hid_buf),
                                             _fn_ptr(body), body_user, _fn_ptr(post), post_user, _ptr(logits_dbg),
                                             _ptr(lse_dbg), current_stream() if stream is None else stream),
            "ddd_round_enqueue")
@@ -319,7 +325,7 @@ def ddd_round_enqueue(ctx, W, st, tree, root_token, hid_buf, body, body_user, po
 
 def ddd_round_capture(ctx, W, st, tree, root_token, hid_buf, body, body_user, post=None, post_user=None,
                       logits_dbg=None, lse_dbg=None, stream=None):
-    _check(load_library().ddd_round_capture(ctx, _ptr(W), C.byref(st), C.byref(tree), _ptr(root_token), _ptr(hid_buf),
+    _check((_lib or load_library()).ddd_round_capture(ctx, _ptr(W), st, tree, _ptr(root_token), _ptr(hid_buf),
                                             _fn_ptr(body), body_user, _fn_ptr(post), post_user, _ptr(logits_dbg),
                                             _ptr(lse_dbg), current_stream() if stream is None else stream),
            "ddd_round_capture")
@@ -327,7 +333,7 @@ def ddd_round_capture(ctx, W, st, tree, root_token, hid_buf, body, body_user, po
 
 def ddd_round_run(ctx, W, st, tree, root_token, hid_buf, body, body_user, post=None, post_user=None, stream=None) -> int:
     """Host-paced round; returns the number of draft calls queued."""
-    rc = load_library().ddd_round_run(ctx, _ptr(W), C.byref(st), C.byref(tree), _ptr(root_token), _ptr(hid_buf),
+    rc = (_lib or load_library()).ddd_round_run(ctx, _ptr(W), st, tree, _ptr(root_token), _ptr(hid_buf),
                                       _fn_ptr(body), body_user, _fn_ptr(post), post_user,
                                       current_stream() if stream is None else stream)
     if rc < 0:
@@ -338,74 +344,74 @@ def ddd_round_run(ctx, W, st, tree, root_token, hid_buf, body, body_user, post=N
 def ddd_round_run_stats(ctx) -> Dict[str, float]:
     """Counters of ddd_round_run's host waits: rounds, waits, timeouts (waits that ran into their limit), max_wait_us."""
     r, w, t, m = C.c_uint64(), C.c_uint64(), C.c_uint64(), C.c_double()
-    _check(load_library().ddd_round_run_stats(ctx, C.byref(r), C.byref(w), C.byref(t), C.byref(m)), "ddd_round_run_stats")
+    _check((_lib or load_library()).ddd_round_run_stats(ctx, C.byref(r), C.byref(w), C.byref(t), C.byref(m)), "ddd_round_run_stats")
     return {"rounds": r.value, "waits": w.value, "timeouts": t.value, "max_wait_us": m.value}
 
 
 def ddd_round_launch(ctx, stream=None):
-    _check(load_library().ddd_round_launch(ctx, current_stream() if stream is None else stream), "ddd_round_launch")
+    _check((_lib or load_library()).ddd_round_launch(ctx, current_stream() if stream is None else stream), "ddd_round_launch")
 
 
 def ddd_tree_attention_workspace(ctx, n_heads, L) -> int:
-    return int(load_library().ddd_tree_attention_workspace(ctx, n_heads, L))
+    return int((_lib or load_library()).ddd_tree_attention_workspace(ctx, n_heads, L))
 
 
 def ddd_kv_pack(ctx, k, v, L, n_heads, k_packed, v_packed, stream=None):
-    _check(load_library().ddd_kv_pack(ctx, _ptr(k), _ptr(v), L, n_heads, _ptr(k_packed), _ptr(v_packed),
+    _check((_lib or load_library()).ddd_kv_pack(ctx, _ptr(k), _ptr(v), L, n_heads, _ptr(k_packed), _ptr(v_packed),
                                       current_stream() if stream is None else stream), "ddd_kv_pack")
 
 
 def ddd_tree_attention(ctx, tree: ddd_tree, q, k_tree, vt_tree, k_packed, v_packed, L, n_heads, workspace, out,
                        stream=None):
     nbytes = workspace.numel() * workspace.element_size()
-    _check(load_library().ddd_tree_attention(ctx, C.byref(tree), _ptr(q), _ptr(k_tree), _ptr(vt_tree), _ptr(k_packed),
+    _check((_lib or load_library()).ddd_tree_attention(ctx, tree, _ptr(q), _ptr(k_tree), _ptr(vt_tree), _ptr(k_packed),
                                              _ptr(v_packed), L, n_heads, _ptr(workspace), nbytes, _ptr(out),
                                              current_stream() if stream is None else stream), "ddd_tree_attention")
 
 
 def ddd_weights_pack(ctx, W, stream=None):
     """Tile-major copy of W for the GEMM path (W=None forgets it)."""
-    _check(load_library().ddd_weights_pack(ctx, _ptr(W), current_stream() if stream is None else stream),
+    _check((_lib or load_library()).ddd_weights_pack(ctx, _ptr(W), current_stream() if stream is None else stream),
            "ddd_weights_pack")
 
 
 # ---- stand-in draft layer (include/ddd_body.h) -------------------------------------------------
 def ddd_body_create(cfg: ddd_body_config) -> int:
     out = C.c_void_p()
-    _check(load_library().ddd_body_create(C.byref(cfg), C.byref(out)), "ddd_body_create")
+    _check((_lib or load_library()).ddd_body_create(C.byref(cfg), C.byref(out)), "ddd_body_create")
     return out.value
 
 
 def ddd_body_destroy(body: int) -> None:
-    _check(load_library().ddd_body_destroy(body), "ddd_body_destroy")
+    _check((_lib or load_library()).ddd_body_destroy(body), "ddd_body_destroy")
 
 
 def ddd_body_bind(body: int, weights: Dict[str, "object"], prompt: Dict[str, "object"]) -> None:
     """weights / prompt: dicts of device tensors named as the struct fields; the caller keeps them alive."""
     w = ddd_body_weights(*[_ptr(weights[n]) for n, _ in ddd_body_weights._fields_])
     p = ddd_body_prompt(*[_ptr(prompt[n]) for n, _ in ddd_body_prompt._fields_])
-    _check(load_library().ddd_body_bind(body, C.byref(w), C.byref(p)), "ddd_body_bind")
+    _check((_lib or load_library()).ddd_body_bind(body, C.byref(w), C.byref(p)), "ddd_body_bind")
 
 
 def body_step_ptr() -> int:
     """Address of ddd_body_step, usable as the `body` argument of the round calls (user = the body handle)."""
-    return C.cast(load_library().ddd_body_step, C.c_void_p).value
+    return C.cast((_lib or load_library()).ddd_body_step, C.c_void_p).value
 
 
 def ddd_body_step(body: int, step, st: ddd_state, hid_out, stream=None):
-    _check(load_library().ddd_body_step(body, step, C.byref(st), _ptr(hid_out),
+    _check((_lib or load_library()).ddd_body_step(body, step, st, _ptr(hid_out),
                                         current_stream() if stream is None else stream), "ddd_body_step")
 
 
 def ddd_body_linear(body: int, W, N, K, x, R, y, accumulate=False, stream=None):
-    _check(load_library().ddd_body_linear(body, _ptr(W), N, K, _ptr(x), R, _ptr(y), 1 if accumulate else 0,
+    _check((_lib or load_library()).ddd_body_linear(body, _ptr(W), N, K, _ptr(x), R, _ptr(y), 1 if accumulate else 0,
                                           current_stream() if stream is None else stream), "ddd_body_linear")
 
 
 def ddd_profile_lmhead(ctx, W, hid, n_rows, iters, stream=None):
     """(mean_ms, min_ms) per launch of the LM-head kernel alone; synchronises."""
     mean, mn = C.c_float(), C.c_float()
-    _check(load_library().ddd_profile_lmhead(ctx, _ptr(W), _ptr(hid), n_rows, iters, C.byref(mean), C.byref(mn),
+    _check((_lib or load_library()).ddd_profile_lmhead(ctx, _ptr(W), _ptr(hid), n_rows, iters, C.byref(mean), C.byref(mn),
                                                     current_stream() if stream is None else stream),
            "ddd_profile_lmhead")
     return mean.value, mn.value
@@ -415,21 +421,21 @@ def ddd_stats_bind(ctx, rounds=None, depth_hist=None, accept_hist=None, batch_de
     """Binds device statistics arrays (int64; `steps` int32) that the context's verify calls add their rounds to;
     all None unbinds.  The tensors must outlive the binding."""
     if rounds is None and depth_hist is None and accept_hist is None and batch_depth_hist is None:
-        _check(load_library().ddd_stats_bind(ctx, None), "ddd_stats_bind")
+        _check((_lib or load_library()).ddd_stats_bind(ctx, None), "ddd_stats_bind")
         return
     s = ddd_round_stats(_ptr(rounds), _ptr(depth_hist), _ptr(accept_hist), _ptr(batch_depth_hist), _ptr(steps))
-    _check(load_library().ddd_stats_bind(ctx, C.byref(s)), "ddd_stats_bind")
+    _check((_lib or load_library()).ddd_stats_bind(ctx, C.byref(s)), "ddd_stats_bind")
 
 
 def ddd_trace_enable(ctx, on: bool = True) -> None:
-    _check(load_library().ddd_trace_enable(ctx, 1 if on else 0), "ddd_trace_enable")
+    _check((_lib or load_library()).ddd_trace_enable(ctx, 1 if on else 0), "ddd_trace_enable")
 
 
 def ddd_trace_read(ctx):
     """The context's device-timestamp trace as a numpy uint64 array [DDD_DMAX + 1, DDD_TRACE_CALL_WORDS]
     (100 MHz ticks, 0 = not written); synchronises and clears the device buffer."""
     import numpy as np
-    n = int(load_library().ddd_trace_words())
+    n = int((_lib or load_library()).ddd_trace_words())
     out = np.zeros(n, dtype=np.uint64)
-    _check(load_library().ddd_trace_read(ctx, out.ctypes.data, n), "ddd_trace_read")
+    _check((_lib or load_library()).ddd_trace_read(ctx, out.ctypes.data, n), "ddd_trace_read")
     return out.reshape(DDD_DMAX + 1, -1)
