@@ -49,7 +49,7 @@ __device__ __forceinline__ void slice_rows(int N, int nslice, int slice, int& n0
 // MULTI: several K ranges, the last of any number of units; otherwise one whole range, and the input rows stay in registers
 // for the whole kernel.
 template <int G, bool MULTI>
-__global__ __launch_bounds__(704) void linear_stream_kernel(LinearArgs a) {
+__global__ __launch_bounds__((kLinearWaves + 1) * 64) void linear_stream_kernel(LinearArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int NW = a.nw;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -85,14 +85,14 @@ __global__ __launch_bounds__(704) void linear_stream_kernel(LinearArgs a) {
   slice_rows(a.N, nslice, slice, n0, n1);
   const int nt = (n1 - n0 + 15) >> 4;
 
-  float* red = reinterpret_cast<float*>(smem);      // [2][NW][256] fp32 partial tiles
-  unsigned char* stage = smem + 2 * NW * 1024;      // [NW][kStageBytes]
+  const int NR = MULTI ? a.n_ranges : 1;
+  float* red = reinterpret_cast<float*>(smem);      // [2][NR][NW][256] fp32 partial tiles
+  unsigned char* stage = smem + 2 * NR * NW * 1024; // [NW][kStageBytes]
 
-  const int NR = a.n_ranges;
   const int total = nt * NR;          // (tile, range) steps of this workgroup, ranges innermost
   // Neighbours start with different ranges: rows of 16 KB whose first halves every workgroup reads at the same time do not reach the
   // whole memory, and a short last range keeps no workgroup waiting at the same moment.  Three calls of one user (H = 4096, F = 11008)
-  // 404.3 -> 397.5 us; the down product of ten rows 27.5 -> 25.2, the FC of one row 21.0 -> 18.4.
+  // 404.3 -> 397.5 us; the down product of ten rows 27.5 -> 25.2, the FC of one row 21.0 -> 18.4.  The ranges are added up in order.
   const int rot = MULTI ? slice % NR : 0;
   auto range_at = [&](int i) { const int r = i + rot; return r < NR ? r : r - NR; };   // 0 <= i < NR
 
@@ -149,7 +149,7 @@ __global__ __launch_bounds__(704) void linear_stream_kernel(LinearArgs a) {
       } else {
         acc = stream_tile<G, false, MULTI>(ring, bfrag, mystage, wr_off, rd_off, wb0, a.ldw, 0, vlast, n_cur);
       }
-      *reinterpret_cast<f32x4*>(red + ((it & 1) * NW + wave) * 256 + lane * 4) = acc;
+      *reinterpret_cast<f32x4*>(red + ((((it / NR) & 1) * NR + r) * NW + wave) * 256 + lane * 4) = acc;
       __syncthreads();
     }
   } else {
@@ -165,12 +165,15 @@ __global__ __launch_bounds__(704) void linear_stream_kernel(LinearArgs a) {
         for (int e = 0; e < 4; ++e)
           if (v0 + e < n1) y0[e] = yp[e];
       }
+      // The sums run along K whatever range came first, so an output does not depend on the workgroup that makes it: a range is added
+      // when those in front of it have been, the ones that came early (NR - rot of them) behind the tile's last.
       f32x4 s = {0.f, 0.f, 0.f, 0.f};
-      for (int rr = 0; rr < NR; ++rr) {
-        const int it = t * NR + rr;
+      const float* tile = red + (t & 1) * NR * NW * 256 + lane * 4;
+      for (int i = 0; i < NR; ++i) {
         __syncthreads();
-        for (int w = 0; w < NW; ++w)   // fixed order
-          s += *reinterpret_cast<const f32x4*>(red + ((it & 1) * NW + w) * 256 + lane * 4);
+        if (i < NR - rot && rot != 0) continue;
+        const int r0 = range_at(i), r1 = i == NR - 1 ? NR : r0 + 1;
+        for (int w = r0 * NW; w < r1 * NW; ++w) s += *reinterpret_cast<const f32x4*>(tile + w * 256);
       }
       if (active) {
         if (a.mode == kLinearSiluPairs) {   // outputs (v0, v0+1) and (v0+2, v0+3) are (gate, up) pairs
@@ -201,12 +204,24 @@ __global__ __launch_bounds__(704) void linear_stream_kernel(LinearArgs a) {
 template <int G>
 static hipError_t launch_linear_g(const LinearArgs& a, int nslice, hipStream_t stream) {
   const dim3 grid(nslice), block((a.nw + 1) * 64);
-  const size_t lds = (size_t)2 * a.nw * 1024 + (size_t)a.nw * kStageBytes;
+  const size_t lds = (size_t)2 * a.n_ranges * a.nw * 1024 + (size_t)a.nw * kStageBytes;
   if (a.n_ranges > 1 || a.last_units < a.nw * G || a.rg[0].gather_mode != kGatherNone)
     hipLaunchKernelGGL((linear_stream_kernel<G, true>), grid, block, lds, stream, a);
   else
     hipLaunchKernelGGL((linear_stream_kernel<G, false>), grid, block, lds, stream, a);
   return hipGetLastError();
+}
+
+template <int G>
+static hipError_t prepare_linear_g() {
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&linear_stream_kernel<G, true>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                             2 * kLinearRanges * kLinearWaves * 1024 + kLinearWaves * kStageBytes);
+}
+hipError_t prepare_linear_stream() {
+  hipError_t e = prepare_linear_g<1>();
+  if (e == hipSuccess) e = prepare_linear_g<2>();
+  if (e == hipSuccess) e = prepare_linear_g<4>();
+  return e;
 }
 
 hipError_t launch_linear_stream(const LinearArgs& a, int G, int nslice, hipStream_t stream) {

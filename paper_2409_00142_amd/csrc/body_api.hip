@@ -47,7 +47,7 @@ int hip_status(hipError_t e) { return e == hipSuccess ? DDD_OK : DDD_ERR_HIP; }
 bool pick_range(int units, int* G, int* nw) {   // units = remaining K / 128
   int best = 0;
   for (int g = 4; g >= 1; g >>= 1)
-    for (int w = 10; w >= 1; --w)
+    for (int w = kLinearWaves; w >= 1; --w)
       if (g * w <= units && g * w > best) {
         best = g * w;
         *G = g;
@@ -60,7 +60,7 @@ bool pick_range(int units, int* G, int* nw) {   // units = remaining K / 128
 bool fit_range(int units, int* G, int* nw) {
   int best = 0;
   for (int g = 4; g >= 1; g >>= 1)
-    for (int w = 10; w >= 1; --w)
+    for (int w = kLinearWaves; w >= 1; --w)
       if (g * w >= units && (best == 0 || g * w < best)) {
         best = g * w;
         *G = g;
@@ -84,7 +84,7 @@ int enqueue_linear(const ddd_body* b, LinearArgs a, int K, hipStream_t s) {
   int k0 = 0;
   while (k0 < K) {
     const int units = (K - k0) / 128;
-    int G = 4, nw = 10, nr = kLinearRanges;                // what is left does not fit one launch: as much as goes in
+    int G = 4, nw = kLinearWaves, nr = kLinearRanges;                // what is left does not fit one launch: as much as goes in
     for (int n = 1; n <= kLinearRanges; ++n)
       if (fit_range((units + n - 1) / n, &G, &nw)) {       // fewest ranges, each as short as the grid of lengths allows
         nr = n;
@@ -237,6 +237,7 @@ int ddd_body_create(const ddd_body_config* cfg, ddd_body** out) {
   if (e == hipSuccess) e = hipMemset(b->par_hist, 0, D * R * sizeof(int32_t));
   if (e == hipSuccess) e = hipMalloc(&b->row_list, R * sizeof(int32_t));
   if (e == hipSuccess) e = hipMalloc(&b->n_act, sizeof(int32_t));
+  if (e == hipSuccess) e = prepare_linear_stream();
   if (e == hipSuccess && b->rows > kBodyRows) {
     e = hipMalloc(&b->x0, R * 2 * H * sizeof(uint16_t));
     if (e == hipSuccess) e = prepare_lmhead_gemm();

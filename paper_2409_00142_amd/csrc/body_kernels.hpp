@@ -32,7 +32,7 @@ struct LinearRange {
   const int32_t* gather_idx;  // see GatherMode
   int gather_mode, ldx;
 };
-constexpr int kLinearRanges = 3;
+constexpr int kLinearRanges = 3, kLinearWaves = 10;   // at most, of a launch: K ranges, streaming waves
 // One launch covers n_ranges K ranges of the same length 128*G*nw (the last may be shorter) and adds them up in order
 // before the epilogue runs: y (+)= sum_ranges x_range W_range^T.
 struct LinearArgs {
@@ -45,6 +45,7 @@ struct LinearArgs {
   int ldw, ldy, ld16, N, R, ntiles, nw, mode;
   int last_units;             // 128-element units of the last range (fewer than a whole range: the product's K ends there)
 };
+hipError_t prepare_linear_stream();   // once per process: enables the kernels' LDS sizes
 hipError_t launch_linear_stream(const LinearArgs& a, int G, int nslice, hipStream_t stream);
 
 // Weights that the next launch starts with: the first `bytes` of the rows that each of its `nslice` workgroups streams.

@@ -59,3 +59,28 @@ def test_stopped_calls_leave_no_trace(H, F, B, k):
         assert bool(torch.isfinite(a2.float()).all())
     finally:
         D.ddd_body_destroy(body)
+
+
+@pytest.mark.parametrize("N,K", [(4096, 11008), (12292, 8192), (260, 5248), (64, 4096)])
+@pytest.mark.parametrize("R", [1, 10, 16])
+def test_sums_run_along_k(N, K, R):
+    """A product of several K ranges whose weight rows are all alike: every workgroup starts with a range of its own, and yet all
+    outputs of an input row are the same bits."""
+    import torch
+    import paper_2409_00142_amd as D
+    print(f"[case] few_rows sums N={N} K={K} R={R}", flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N + K + R)
+    row = torch.empty(K, device="cuda").normal_(0, K ** -0.5, generator=g).to(torch.bfloat16)
+    W = row.expand(N, K).contiguous()
+    x = torch.empty(R, K, device="cuda").normal_(0, 1, generator=g).to(torch.bfloat16)
+    y = torch.zeros(R, N, device="cuda")
+    body = D.ddd_body_create(D.ddd_body_config(1, 16, 1024, 128, 16, 4, 0))
+    try:
+        D.ddd_body_linear(body, W, N, K, x, R, y)
+        torch.cuda.synchronize()
+        assert torch.equal(y, y[:, :1].expand(R, N))
+        exact = x.double() @ row.double()
+        assert bool((y[:, 0].double() - exact).abs().max() < 1e-4)   # fp32 sums of K products of the size K^-1/2
+    finally:
+        D.ddd_body_destroy(body)
