@@ -253,13 +253,12 @@ __device__ __forceinline__ uint32_t scan32_u32(uint32_t x, int lane) {
 // lines of the tree, so nothing is searched for and nothing is fetched twice.  One round trip brings the pool's size and every node's
 // score, parent, token and depth.  Selection: the m-th largest score (ordered bits) is found six bits at a time by the whole block -
 // the 64 digits are counted in LDS, one barrier, and every wave draws the same conclusion, lane d for the digit d - and no further than a
-// prefix that exactly m nodes reach, three passes as a rule; of equal scores the lowest ids are taken.  The tree index of a selected node is 1 + the number of selected nodes with a smaller id (ballots, and the waves' totals through
-// LDS).  A parent's tree index is read from the node -> index table (a selected node's parent is selected: its score is no smaller and
-// its id is smaller).
-// A launch is latency alone, and small code: behind a stream of weights its instructions come from memory.  ddd_tree_finalize and
-// ddd_verify_accept of one sequence with 811 nodes 11.2 -> 9.2 us (9 is what the host takes for the two), 785 nodes and m = 127 12.4 -> 9.2,
-// 2065 nodes (sorted as a whole before) 36.9 -> 10.7; 64 sequences with 511 nodes 10.4 -> 9.9, 1793 20.0 -> 12.8; up to 511 nodes of one
-// sequence the same 5.4 us on the GPU as with one wave that found the score bit by bit.
+// prefix that exactly m nodes reach, three passes as a rule; of equal scores the lowest ids are taken.  The tree index of a selected node
+// is 1 + the number of selected nodes with a smaller id (ballots, and the waves' totals through LDS).  A parent's tree index is read from
+// the node -> index table (a selected node's parent is selected: its score is no smaller and its id is smaller).
+// A launch is latency alone, and small code: behind a stream of weights its instructions come from memory.  ddd_tree_finalize of one
+// sequence with 211 / 511 / 811 / 1809 / 3857 nodes, m = 60: 5.3 / 5.3 / 5.3 / 6.4 / 8.3 us on the GPU; with one wave that found the score bit
+// by bit up to 1024 nodes, a ranking of candidates up to 2048 and a sort beyond 5.0 / 6.3 / 7.7 / 10.3 / 36.5.
 constexpr int kTreeMost = kPoolMax;        // nodes of the largest pool
 constexpr int kTreeDigit = 6, kTreePasses = (32 + kTreeDigit - 1) / kTreeDigit;
 template <int Q>
@@ -322,8 +321,17 @@ __device__ __forceinline__ void tree_select_block(const ddd_state& st, const ddd
       const int shift = max(32 - kTreeDigit * (pass + 1), 0);
       const uint32_t known = pass == 0 ? 0u : ~0u << (32 - kTreeDigit * pass);
 #pragma unroll
-      for (int q = 0; q < Q; ++q)
-        if (real[q] && ((key[q] ^ thr) & known) == 0u) atomicAdd(&hist[pass * 64 + ((key[q] & ~known) >> shift)], 1);
+      for (int q = 0; q < Q; ++q) {
+        const bool in = real[q] && ((key[q] ^ thr) & known) == 0u;
+        const int digit = (int)((key[q] & ~known) >> shift);
+        const unsigned long long who = __ballot(in);
+        if (who == 0ull) continue;                                // wave-uniform
+        // One addition for all lanes with the digit of the first: the scores' highest digits are alike, and additions to one address
+        // wait for each other.  1809 nodes 7.5 -> 6.4 us, 511 5.45 -> 5.27, 211 5.27 -> 5.34; all scores equal 14.5 -> 7.5, 511 nodes 7.7 -> 6.1.
+        const int first = __ffsll(who) - 1, common = __builtin_amdgcn_readlane(digit, first);
+        const unsigned long long same = __ballot(in && digit == common);
+        if (lane == first || (in && digit != common)) atomicAdd(&hist[pass * 64 + digit], lane == first ? (int)__popcll(same) : 1);
+      }
       __syncthreads();
       const int from = above + suffix64_i32(hist[pass * 64 + lane], lane);   // scores that reach this lane's digit: falling, lane 0 all
       const int d = 63 - __clzll((long long)__ballot(from >= m_eff));
