@@ -227,7 +227,7 @@ struct VerifySampleArgs {
   void* rows;                    // null, or scratch of verify_sample_row_bytes() per row of logits: the sums of the rows first
   // set by the launcher:
   int parts;                     // of every row's sums
-  bool leaves;                   // the sums of leaves too
+  int leaf_rows;                 // trees of up to so many rows have the sums of their leaves made too (m + 1: all trees)
   double beta2, span;            // log2(e) / T, and the difference of two logits whose weights differ by 2^1000
 };
 size_t verify_sample_row_bytes();

@@ -639,11 +639,11 @@ __global__ __launch_bounds__(kVsPartWaves * kWave) void verify_row_sums_kernel(V
   const int part = blockIdx.x, i = blockIdx.y, b = blockIdx.z, tid = threadIdx.x, lane = tid & 63;
   const int T = a.m + 1, V = a.V;
   // In front of the row's loads: a pool with fewer nodes than m (a round that stopped early) has rows that nobody asks for.  B = 8,
-  // V = 32000: 36 nodes and m = 80 21.1 us a call, 24.3 with all 81 rows read; 10 nodes and m = 60 15.6, 21.2; all of 60 the look
-  // costs 0.2 (0.4 with the row's address fetched behind it).  So has a leaf, unless the walk ends there (verify_sample_from_sums).
+  // V = 32000, m = 60: 10 nodes 15.1 us a call, 36 nodes 16.0, all of 60 21.4; the look itself costs 0.2 (0.4 with the row's address
+  // fetched behind it).  So has a leaf of a larger tree, unless the walk ends there (verify_sample_from_sums).
   const int32_t* par = a.tree.parent_idx + (size_t)b * T;
   int p0 = 0, p1 = 0, p2 = 0;
-  if (!a.leaves) {                                                        // uniform
+  if (a.leaf_rows < T) {                                                  // uniform
     p0 = par[min(lane, T - 1)];
     p1 = par[min(64 + lane, T - 1)];
     p2 = par[min(128, T - 1)];
@@ -654,7 +654,7 @@ __global__ __launch_bounds__(kVsPartWaves * kWave) void verify_row_sums_kernel(V
   VsRow* out = static_cast<VsRow*>(a.rows) + (size_t)b * T + i;
   asm volatile("" ::"s"(x), "s"(out));                                    // the arguments arrive beside the size, not behind it
   if (i >= n) return;                                                     // uniform: not a node of the tree
-  if (!a.leaves) {
+  if (n > a.leaf_rows) {                                                  // uniform
     if (i == 0 && part == 0 && tid == 0) out->arrived = 0u;
     const bool kid = (lane >= 1 && lane < n && p0 == i) || (64 + lane < n && p1 == i) || (128 < n && p2 == i);
     if (__ballot(kid) == 0ull) return;                                    // uniform: a leaf
@@ -686,7 +686,7 @@ __device__ __forceinline__ double row_total(const float (&pm)[kVsParts], const d
 // The walk over the sums of the rows that have children, by as many workgroups per sequence as a row has parts: all take the same
 // decisions, and where the walk ends at a leaf each makes its part of that row.  The one that arrives last draws the bonus token;
 // nobody waits.  (Elsewhere the first does, and the others are done.)  CPB as above.
-// LEAVES: the leaves' sums are there too, and one workgroup walks.  ALL: every part of a row holds tokens.
+// LEAVES: the leaves' sums are there too, and one workgroup walks; otherwise they are in small trees.  ALL: every part of a row holds tokens.
 template <int CPB, bool LEAVES, bool ALL>
 __global__ __launch_bounds__(kVsWalkThreads) void verify_sample_from_sums_kernel(VerifySampleArgs a) {
   __shared__ VsTree t;
@@ -697,6 +697,7 @@ __global__ __launch_bounds__(kVsWalkThreads) void verify_sample_from_sums_kernel
   const int part = LEAVES ? 0 : blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int T = a.m + 1, V = a.V;
   const int n = min(a.tree.n_sel[b], a.m) + 1;
+  const bool missing = !LEAVES && n > a.leaf_rows;                        // the leaves' sums are: uniform
   VsRow* rows = static_cast<VsRow*>(a.rows) + (size_t)b * T;
   const int parts = ALL ? kVsParts : a.parts;
   const double beta2 = beta2_of(a);
@@ -740,7 +741,7 @@ __global__ __launch_bounds__(kVsWalkThreads) void verify_sample_from_sums_kernel
           const int c = base + lane;
           kids |= __ballot(c >= 1 && c < n && t.par[c] == cur) != 0ull;
         }
-        leaf = !kids;
+        leaf = missing && !kids;
       }
       if (len < a.D && !leaf)
         nxt = test_children(t, n, lane, rem, nrm, [&](int base, bool& kid, double& kw, double& ku, int& ktok) {
@@ -843,6 +844,14 @@ static bool sums_of_leaves(const VerifySampleArgs& a) {
   const long long bytes = (long long)a.B * (a.m + 1) * a.V * 4;
   return bytes <= 24LL << 20 || (a.m <= 32 && bytes <= 64LL << 20);
 }
+// Where they are not, trees of so many rows have them all the same: a round that stopped after its first call leaves k leaves under the
+// root, and every walk that accepts a token ends at one.  Ahead and on demand, V = 32000, m = 60, us a call where every node is accepted: 4
+// sequences with 4 / 10 / 20 nodes 11.0 and 13.9, 12.5 and 14.6, 13.2 and 15.0; 8 with 4 / 10 / 20 12.0 and 15.2, 14.2 and 15.4, 16.2 and
+// 17.0; 16 with 4 / 10 15.0 and 17.8, 16.0 and 17.7.  Where about half of the tokens are, the walks that end at the root are the longest and
+// the rows ahead cost more: 8 sequences with 4 / 10 / 20 nodes 13.0 and 14.8, 16.9 and 15.0, 16.9 and 15.7.  The line, 10 MB, has both in mind.
+static int rows_with_leaves(const VerifySampleArgs& a) {
+  return sums_of_leaves(a) ? a.m + 1 : (int)((10LL << 20) / ((long long)a.B * a.V * 4));
+}
 
 hipError_t launch_verify_sample(VerifySampleArgs a, hipStream_t stream) {
   if (a.m > DDD_MMAX) return hipErrorInvalidValue;      // the kernels keep the tree in LDS
@@ -851,7 +860,8 @@ hipError_t launch_verify_sample(VerifySampleArgs a, hipStream_t stream) {
   const int cpb = (a.V + kVsSub * kVsChunk - 1) / (kVsSub * kVsChunk);   // chunks of 256 tokens per block
   if (a.rows != nullptr) {
     a.parts = vs_parts(a.V);
-    a.leaves = sums_of_leaves(a);
+    a.leaf_rows = rows_with_leaves(a);
+    const bool leaves = a.leaf_rows > a.m;
     const dim3 grid(a.parts, a.m + 1, a.B), block(kVsPartWaves * kWave);
     if (cpb == 1)
       hipLaunchKernelGGL((verify_row_sums_kernel<1>), grid, block, 0, stream, a);
@@ -865,10 +875,10 @@ hipError_t launch_verify_sample(VerifySampleArgs a, hipStream_t stream) {
       hipLaunchKernelGGL((verify_row_sums_kernel<0>), grid, block, 0, stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const dim3 walk(a.leaves ? 1 : a.parts, a.B), wg(kVsWalkThreads);
-    if (a.leaves && a.parts == kVsParts)
+    const dim3 walk(leaves ? 1 : a.parts, a.B), wg(kVsWalkThreads);
+    if (leaves && a.parts == kVsParts)
       hipLaunchKernelGGL((verify_sample_from_sums_kernel<0, true, true>), walk, wg, 0, stream, a);
-    else if (a.leaves)
+    else if (leaves)
       hipLaunchKernelGGL((verify_sample_from_sums_kernel<0, true, false>), walk, wg, 0, stream, a);
     else if (cpb == 1)
       hipLaunchKernelGGL((verify_sample_from_sums_kernel<1, false, false>), walk, wg, 0, stream, a);
