@@ -138,19 +138,16 @@ def load_library() -> C.CDLL:
     return lib
 
 
-# A call that launches one small kernel is as long as what the host does for it, so the wrappers below keep to the cheapest form of each
-# argument: a structure is passed itself (its argtype is a pointer: ctypes makes the reference, 0.8 us less a call than two byref objects), a
-# tensor is asked for its address before anything else.  ddd_tree_finalize and ddd_verify_accept of one sequence: 9.0 -> 8.4 us.
+# A call that launches one small kernel is as long as what the host does for it, so the wrappers below pass a structure itself (its argtype is
+# a pointer: ctypes makes the reference) and look the library up once: 0.25 to 0.6 us less a call than two byref objects and a function call.
+# ddd_tree_finalize and ddd_verify_accept of one sequence: 8.5 -> 8.25 us.
 def _ptr(t) -> Optional[int]:
     """Device (or host) pointer of a torch tensor / int / None."""
     if t is None:
         return None
-    try:
-        return t.data_ptr()
-    except AttributeError:
-        if isinstance(t, int):
-            return t
-        raise
+    if isinstance(t, int):
+        return t
+    return t.data_ptr()
 
 
 def _check(code: int, where: str) -> None:
@@ -251,20 +248,20 @@ def alloc_tree(cfg: ddd_config, device="cuda") -> Tuple[ddd_tree, Dict[str, "obj
 
 def ddd_round_reset(ctx, st: ddd_state, root_token=None, stream=None) -> None:
     _check((_lib or load_library()).ddd_round_reset(ctx, st, _ptr(root_token),
-                                          current_stream() if stream is None else stream), "ddd_round_reset")
+                                                    current_stream() if stream is None else stream), "ddd_round_reset")
 
 
 def ddd_lmhead_topk(ctx, W, hid, n_rows, row_active, topk_token, topk_logprob, lse, logits_dbg=None, stream=None):
     _check((_lib or load_library()).ddd_lmhead_topk(ctx, _ptr(W), _ptr(hid), n_rows, _ptr(row_active), _ptr(topk_token),
-                                          _ptr(topk_logprob), _ptr(lse), _ptr(logits_dbg),
-                                          current_stream() if stream is None else stream), "ddd_lmhead_topk")
+                                                    _ptr(topk_logprob), _ptr(lse), _ptr(logits_dbg),
+                                                    current_stream() if stream is None else stream), "ddd_lmhead_topk")
 
 
 def ddd_lmhead_topk_static(cfg: ddd_config, W, hid, n_rows, row_active, topk_token, topk_logprob, lse, stream=None):
     """ddd_lmhead_topk without a context and without any allocation (static device scratch)."""
     _check((_lib or load_library()).ddd_lmhead_topk_static(C.byref(cfg), _ptr(W), _ptr(hid), n_rows, _ptr(row_active),
-                                                 _ptr(topk_token), _ptr(topk_logprob), _ptr(lse),
-                                                 current_stream() if stream is None else stream),
+                                                           _ptr(topk_token), _ptr(topk_logprob), _ptr(lse),
+                                                           current_stream() if stream is None else stream),
            "ddd_lmhead_topk_static")
 
 
@@ -274,37 +271,37 @@ def ddd_static_scratch_bytes() -> int:
 
 def ddd_beam_select(ctx, step, topk_token, topk_logprob, st: ddd_state, stream=None):
     _check((_lib or load_library()).ddd_beam_select(ctx, step, _ptr(topk_token), _ptr(topk_logprob), st,
-                                          current_stream() if stream is None else stream), "ddd_beam_select")
+                                                    current_stream() if stream is None else stream), "ddd_beam_select")
 
 
 def ddd_depth_continue(ctx, steps_done, st: ddd_state, stream=None):
     _check((_lib or load_library()).ddd_depth_continue(ctx, steps_done, st,
-                                             current_stream() if stream is None else stream), "ddd_depth_continue")
+                                                       current_stream() if stream is None else stream), "ddd_depth_continue")
 
 
 def ddd_draft_step(ctx, step, W, hid, st: ddd_state, tree: Optional[ddd_tree] = None, logits_dbg=None, lse_dbg=None,
                    stream=None):
     _check((_lib or load_library()).ddd_draft_step(ctx, step, _ptr(W), _ptr(hid), st,
-                                         tree, _ptr(logits_dbg), _ptr(lse_dbg),
-                                         current_stream() if stream is None else stream), "ddd_draft_step")
+                                                   tree, _ptr(logits_dbg), _ptr(lse_dbg),
+                                                   current_stream() if stream is None else stream), "ddd_draft_step")
 
 
 def ddd_tree_finalize(ctx, st: ddd_state, tree: ddd_tree, stream=None):
     _check((_lib or load_library()).ddd_tree_finalize(ctx, st, tree,
-                                            current_stream() if stream is None else stream), "ddd_tree_finalize")
+                                                      current_stream() if stream is None else stream), "ddd_tree_finalize")
 
 
 def ddd_verify_accept(ctx, tree: ddd_tree, target_argmax, accept_len, accept_path, bonus_token, stream=None):
     _check((_lib or load_library()).ddd_verify_accept(ctx, tree, _ptr(target_argmax), _ptr(accept_len),
-                                            _ptr(accept_path), _ptr(bonus_token),
-                                            current_stream() if stream is None else stream), "ddd_verify_accept")
+                                                      _ptr(accept_path), _ptr(bonus_token),
+                                                      current_stream() if stream is None else stream), "ddd_verify_accept")
 
 
 def ddd_verify_sample(ctx, tree: ddd_tree, target_logits, temperature, u_accept, u_bonus, accept_len, accept_path,
                       bonus_token, stream=None):
     _check((_lib or load_library()).ddd_verify_sample(ctx, tree, _ptr(target_logits), float(temperature), _ptr(u_accept),
-                                            _ptr(u_bonus), _ptr(accept_len), _ptr(accept_path), _ptr(bonus_token),
-                                            current_stream() if stream is None else stream), "ddd_verify_sample")
+                                                      _ptr(u_bonus), _ptr(accept_len), _ptr(accept_path), _ptr(bonus_token),
+                                                      current_stream() if stream is None else stream), "ddd_verify_sample")
 
 
 def _fn_ptr(fn) -> Optional[int]:
@@ -318,24 +315,24 @@ def _fn_ptr(fn) -> Optional[int]:
 def ddd_round_enqueue(ctx, W, st, tree, root_token, hid_buf, body, body_user, post=None, post_user=None,
                       logits_dbg=None, lse_dbg=None, stream=None):
     _check((_lib or load_library()).ddd_round_enqueue(ctx, _ptr(W), st, tree, _ptr(root_token), _ptr(hid_buf),
-                                            _fn_ptr(body), body_user, _fn_ptr(post), post_user, _ptr(logits_dbg),
-                                            _ptr(lse_dbg), current_stream() if stream is None else stream),
+                                                      _fn_ptr(body), body_user, _fn_ptr(post), post_user, _ptr(logits_dbg),
+                                                      _ptr(lse_dbg), current_stream() if stream is None else stream),
            "ddd_round_enqueue")
 
 
 def ddd_round_capture(ctx, W, st, tree, root_token, hid_buf, body, body_user, post=None, post_user=None,
                       logits_dbg=None, lse_dbg=None, stream=None):
     _check((_lib or load_library()).ddd_round_capture(ctx, _ptr(W), st, tree, _ptr(root_token), _ptr(hid_buf),
-                                            _fn_ptr(body), body_user, _fn_ptr(post), post_user, _ptr(logits_dbg),
-                                            _ptr(lse_dbg), current_stream() if stream is None else stream),
+                                                      _fn_ptr(body), body_user, _fn_ptr(post), post_user, _ptr(logits_dbg),
+                                                      _ptr(lse_dbg), current_stream() if stream is None else stream),
            "ddd_round_capture")
 
 
 def ddd_round_run(ctx, W, st, tree, root_token, hid_buf, body, body_user, post=None, post_user=None, stream=None) -> int:
     """Host-paced round; returns the number of draft calls queued."""
     rc = (_lib or load_library()).ddd_round_run(ctx, _ptr(W), st, tree, _ptr(root_token), _ptr(hid_buf),
-                                      _fn_ptr(body), body_user, _fn_ptr(post), post_user,
-                                      current_stream() if stream is None else stream)
+                                                _fn_ptr(body), body_user, _fn_ptr(post), post_user,
+                                                current_stream() if stream is None else stream)
     if rc < 0:
         _check(rc, "ddd_round_run")
     return rc
@@ -358,15 +355,15 @@ def ddd_tree_attention_workspace(ctx, n_heads, L) -> int:
 
 def ddd_kv_pack(ctx, k, v, L, n_heads, k_packed, v_packed, stream=None):
     _check((_lib or load_library()).ddd_kv_pack(ctx, _ptr(k), _ptr(v), L, n_heads, _ptr(k_packed), _ptr(v_packed),
-                                      current_stream() if stream is None else stream), "ddd_kv_pack")
+                                                current_stream() if stream is None else stream), "ddd_kv_pack")
 
 
 def ddd_tree_attention(ctx, tree: ddd_tree, q, k_tree, vt_tree, k_packed, v_packed, L, n_heads, workspace, out,
                        stream=None):
     nbytes = workspace.numel() * workspace.element_size()
     _check((_lib or load_library()).ddd_tree_attention(ctx, tree, _ptr(q), _ptr(k_tree), _ptr(vt_tree), _ptr(k_packed),
-                                             _ptr(v_packed), L, n_heads, _ptr(workspace), nbytes, _ptr(out),
-                                             current_stream() if stream is None else stream), "ddd_tree_attention")
+                                                       _ptr(v_packed), L, n_heads, _ptr(workspace), nbytes, _ptr(out),
+                                                       current_stream() if stream is None else stream), "ddd_tree_attention")
 
 
 def ddd_weights_pack(ctx, W, stream=None):
@@ -400,19 +397,19 @@ def body_step_ptr() -> int:
 
 def ddd_body_step(body: int, step, st: ddd_state, hid_out, stream=None):
     _check((_lib or load_library()).ddd_body_step(body, step, st, _ptr(hid_out),
-                                        current_stream() if stream is None else stream), "ddd_body_step")
+                                                  current_stream() if stream is None else stream), "ddd_body_step")
 
 
 def ddd_body_linear(body: int, W, N, K, x, R, y, accumulate=False, stream=None):
     _check((_lib or load_library()).ddd_body_linear(body, _ptr(W), N, K, _ptr(x), R, _ptr(y), 1 if accumulate else 0,
-                                          current_stream() if stream is None else stream), "ddd_body_linear")
+                                                    current_stream() if stream is None else stream), "ddd_body_linear")
 
 
 def ddd_profile_lmhead(ctx, W, hid, n_rows, iters, stream=None):
     """(mean_ms, min_ms) per launch of the LM-head kernel alone; synchronises."""
     mean, mn = C.c_float(), C.c_float()
     _check((_lib or load_library()).ddd_profile_lmhead(ctx, _ptr(W), _ptr(hid), n_rows, iters, C.byref(mean), C.byref(mn),
-                                                    current_stream() if stream is None else stream),
+                                                       current_stream() if stream is None else stream),
            "ddd_profile_lmhead")
     return mean.value, mn.value
 
