@@ -100,7 +100,6 @@ __global__ __launch_bounds__((kLinearWaves + 1) * 64) void linear_stream_kernel(
     // streaming wave: K-slice [wave*128*G, +128*G) of every range, its share of x resident as B operands
     const int ks = wave * (128 * G);
     const int n = lane & 15, q = lane >> 4;
-    // the first tile of W is requested before anything else: it flies while the input rows are prepared
     const int lrow = lane >> 4, c = lane & 15;
     unsigned char* mystage = stage + wave * kStageBytes;
     const int wr_off = lrow * kStagePitch + c * 16;
@@ -120,8 +119,9 @@ __global__ __launch_bounds__((kLinearWaves + 1) * 64) void linear_stream_kernel(
     };
     const int n_first = (MULTI && range_at(0) == NR - 1) ? n_last : G;
     // Loads return in order, so the input rows of a group follow its weights: the first group can be multiplied, and its weights
-    // of the next tile requested, when an eighth of the tile and rows is there.  With the rows behind the whole tile the memory was
-    // idle until they had come too: three calls of one user 397.5 -> 385.6 us, gate/up of ten rows 38.8 -> 36.4, q/k/v 23.5 -> 22.4.
+    // of the next tile requested, when its own share of the tile and rows (a quarter of them with G = 4) is there.  With the rows behind
+    // the whole tile the memory was idle until they had come too: three calls of one user 397.5 -> 385.6 us, gate/up of ten rows 38.8 ->
+    // 36.4, q/k/v 23.5 -> 22.4.
     const uint16_t* xp0 = x_of(range_at(0));
 #pragma unroll
     for (int g = 0; g < G; ++g) {

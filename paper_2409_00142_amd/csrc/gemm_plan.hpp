@@ -64,7 +64,6 @@ struct HeadShape {
   float once;   // what a cut of one pass costs beside one of several: calls that walk W in opposite directions find in the memory-side
                 // cache what the call before read last, but a single pass reads all rows at once, along k
   int once_most;   // ... in calls of up to so many blocks of 32 rows: with more the products take longer than W
-  HeadPlan known;  // the plan, where the host knows the number of rows (bm = 0: it does not, and the kernel makes it)
 };
 // In ns, fitted to 900 calls of 20 to 640 rows with V = 4000 to 128256 and H = 1024 to 5120, walking W in one direction and in
 // alternating ones, each with up to ten cuts (the chosen cut is 0.65 % slower than the best one on average; with whole passes at the

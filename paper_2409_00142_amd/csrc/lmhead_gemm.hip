@@ -609,15 +609,14 @@ hipError_t launch_lmhead_gemm(const GemmArgs& a, int max_rows, int grid, hipStre
   h.once = !round || bytes <= (size_t)256 << 20 ? 1.f : rows ? 1.23f : 1.05f;
   h.once_most = far ? 1 << 30 : 4;
   h.most = 10;
-  h.known = HeadPlan{0, 0, 0};
   if (a.row_list == nullptr) {
     if (a.n_rows <= 0) return hipSuccess;
-    h.known = head_plan_host(h, a.n_rows);
-    const int bb = (h.known.bpt + 1) >> 1;
-    if (h.known.bm == 256)
-      launch_known<4, 5>(a, h.known, bb, grid, stream);
+    const HeadPlan known = head_plan_host(h, a.n_rows);
+    const int bb = (known.bpt + 1) >> 1;
+    if (known.bm == 256)
+      launch_known<4, 5>(a, known, bb, grid, stream);
     else
-      launch_known<2, 5>(a, h.known, bb, grid, stream);
+      launch_known<2, 5>(a, known, bb, grid, stream);
     return hipGetLastError();
   }
   // Two kernels, because a launch of the one that has the wide tiles, twice the code, takes 1 us longer whatever tiles it uses: up to 320

@@ -16,6 +16,7 @@ hipError_t launch_tree_finalize(const FinalizeArgs& a, hipStream_t stream) {
   // eight 5.3 and 5.9, 5.7 and 6.2, 5.99 and 6.09; 64 5.55 and 6.1, 5.9 and 6.3, 6.3 and 6.6.  A wider mask keeps sixteen waves busy: 511
   // nodes and m = 64 5.72 and 5.81, m = 80 5.88 and 5.85.
   const int threads = a.nmax <= 1025 && a.m <= 64 ? 512 : 1024;
+  static_assert(DDD_POOL_MAX <= 4 * 1024 + 1, "a thread for every four nodes");
   hipLaunchKernelGGL(tree_finalize_kernel, dim3(a.B), dim3(threads), 0, stream, a);
   return hipGetLastError();
 }

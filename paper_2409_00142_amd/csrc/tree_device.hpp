@@ -186,7 +186,8 @@ __device__ __forceinline__ int suffix64_i32(int x, int lane) {
 // By wave 0 alone; the block barriers also order the caller's writes of vals before and its reuse of them after.  Six bits at a time from
 // the highest one in which any two values differ: the digits are counted in LDS, a lane looks after one of the 64, and the search ends at a
 // prefix that exactly k values reach, after two or three passes.  (Bit by bit, a compare and a popcount per 64 values and bit: row reduction
-// and beam update of a call of 100 beams 10.4 and 14.0 us, now 9.0 and 12.5; the row reduction of 170 rows 5.9, now 5.5; counting by the whole block, 32-bit compares against values that a wave reads from one address: 500 values 3.3 us on a CU.)
+// and beam update of a call of 100 beams 10.4 and 14.0 us, now 9.0 and 12.5; the row reduction of 170 rows 5.9, now 5.5; counting by the
+// whole block, 32-bit compares against values that a wave reads from one address: 500 values 3.3 us on a CU.)
 constexpr int kKthMost = 64 * 8;           // eight values per lane
 template <int S>
 __device__ __forceinline__ uint32_t wave_kth_largest(const uint32_t* vals, int n, int k, int lane) {
@@ -415,53 +416,33 @@ __device__ __forceinline__ void tree_select_block(const ddd_state& st, const ddd
     for (int j = lane; j < T; j += 64) mask[i * T + j] = (uint8_t)((sm.e.bits[i][j >> 5] >> (j & 31)) & 1u);
 }
 
-// Pools of at most DDD_POOL_MAX nodes: the rerank keys sit in LDS (they are distinct: the id is part
-// of the key) and the m_eff largest are kept.
-// Must be called by every thread of the block.
+// The final tree of a pool of at most DDD_POOL_MAX nodes.  Must be called by every thread of the block, at most 1024.
 // n_nodes: the sequence's pool size (st.n_nodes[b]) if the caller has it at hand, else -1.
+// QMOST = 4: the block has a thread for every four nodes.  QMOST = 2: a block of 64 k threads inside the bookkeeping, where pools beyond two
+// nodes a thread (k = 16 from nine calls on, k = 10 from fourteen) have their rerank keys sorted in LDS (they are distinct: the id is part of
+// the key).
 template <int QMOST>
 __device__ __forceinline__ void tree_finalize_block(const ddd_state& st, const ddd_tree& tree, int b, int m, int nmax,
                                                     int tid, int nthr, TreeSmem& sm, int n_nodes = -1) {
-  if (n_nodes < 0 && nmax - 1 > 2 * nthr) n_nodes = st.n_nodes[b];
+  static_assert(QMOST == 2 || QMOST == 4, "nodes per thread");
+  if (n_nodes < 0 && nmax - 1 > 2 * nthr) n_nodes = min(st.n_nodes[b], nmax);
   const int most = (n_nodes >= 0 ? n_nodes : nmax) - 1;
-  if (nthr <= 1024 && most <= 2 * nthr) {                         // uniform
+  if (most <= 2 * nthr) {                                         // uniform
     tree_select_block<2>(st, tree, b, m, nmax, tid, nthr, sm, n_nodes);
-    return;
-  }
-  if (QMOST >= 4 && nthr <= 1024 && most <= 4 * nthr) {
+  } else if constexpr (QMOST == 4) {
     tree_select_block<4>(st, tree, b, m, nmax, tid, nthr, sm, n_nodes);
-    return;
-  }
-  if (n_nodes < 0) n_nodes = st.n_nodes[b];
-  const int N = n_nodes - 1;
-  const int m_eff = min(m, N);
-  const float* psc = st.pool_score + (size_t)b * nmax;
-
-  if (N <= 320) {
-    // Small pools on a block much narrower than the pool: rank by counting (the number of larger keys is a node's
-    // position in the rerank order); cheaper than the sort's chain of dependent stages up to a few hundred nodes.
-    for (int i = tid; i < N; i += nthr) sm.keys[i] = rerank_key(psc[i + 1], i + 1);
-    if (tid == 0) sm.keys[N] = 0ull;   // pad: the counting loop reads keys in pairs
-    __syncthreads();
-    for (int i = tid; i < N; i += nthr) {
-      const uint64_t mine = sm.keys[i];
-      int rank = 0;
-      for (int j = 0; j < N; j += 2) {
-        const uint64_t x = sm.keys[j], y = sm.keys[j + 1];
-        rank += (x > mine ? 1 : 0) + (y > mine ? 1 : 0);
-      }
-      if (rank < m_eff) sm.e.pick[rank] = i + 1;
-    }
   } else {
+    const int N = most, m_eff = min(m, N);
+    const float* psc = st.pool_score + (size_t)b * nmax;
     int n2 = 2;
     while (n2 < N) n2 <<= 1;
     for (int i = tid; i < n2; i += nthr) sm.keys[i] = (i < N) ? rerank_key(psc[i + 1], i + 1) : 0ull;   // 0: below every key
     __syncthreads();
     bitonic_sort_desc(sm.keys, n2, tid, nthr);
     for (int i = tid; i < m_eff; i += nthr) sm.e.pick[i] = (int)(0xFFFFFFFFu - (uint32_t)sm.keys[i]);
+    __syncthreads();
+    tree_emit_block(st, tree, b, m, m_eff, nmax, tid, nthr, sm.e);
   }
-  __syncthreads();
-  tree_emit_block(st, tree, b, m, m_eff, nmax, tid, nthr, sm.e);
 }
 
 }  // namespace ddd

@@ -17,7 +17,7 @@ int main() {
   int bad = 0, wide = 0, narrow = 0;
   for (int i = 0; i < 100000; ++i) {
     const float row2 = rnd(0, 1) ? 0.0171f : rnd(0, 1) ? 0.0196f : 0.042f, once = rnd(0, 1) ? 1.f : 1.23f;
-    const HeadShape h = {rnd(1, i % 4 ? 40000 : 131072), 2 * rnd(1, 40), 8 * rnd(1, 32), rnd(0, 1) ? 4 : 10, 0.0171f, row2, once, rnd(0, 1) ? 4 : 1 << 30, {0, 0, 0}};
+    const HeadShape h = {rnd(1, i % 4 ? 40000 : 131072), 2 * rnd(1, 40), 8 * rnd(1, 32), rnd(0, 1) ? 4 : 10, 0.0171f, row2, once, rnd(0, 1) ? 4 : 1 << 30};
     const int n = rnd(0, 7) ? rnd(1, 700) : rnd(1, 524288), nblk = (n + 31) / 32;
     const HeadPlan p = head_plan_host(h, n);
     // every block of rows has a tile, no tile is empty or wider than its code
@@ -31,7 +31,7 @@ int main() {
     for (int kt : {32, 64, 80})
       for (int n = 17; n <= 128; ++n)
         for (int c = 0; c < 16; ++c) {
-          const HeadShape h = {V, kt, 256, c & 1 ? 4 : 10, 0.0171f, c & 2 ? 0.0171f : c & 8 ? 0.0196f : 0.042f, c & 4 ? 1.f : 1.23f, 4, {0, 0, 0}};
+          const HeadShape h = {V, kt, 256, c & 1 ? 4 : 10, 0.0171f, c & 2 ? 0.0171f : c & 8 ? 0.0196f : 0.042f, c & 4 ? 1.f : 1.23f, 4};
           twice += head_plan_host(h, n).NT > 1;
         }
   std::printf("bad %d wide %d narrow %d twice %d\n", bad, wide, narrow, twice);
