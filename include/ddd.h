@@ -236,7 +236,7 @@ int ddd_stats_bind(ddd_ctx* ctx, const ddd_round_stats* stats);
  *   u_accept      device fp64 [B, m+1] uniforms in [0,1), entry i drives the test of tree index i
  *   u_bonus       device fp64 [B, m+1] uniforms in [0,1), entry i drives the bonus draw at tree index i
  *   outputs as for ddd_verify_accept.  Only the logit rows of the accepted path have a say; with small batches (up to
- *   288 MiB of logits, or 1024 rows) the rows of the tree's other nodes (tree indices 0 .. n_sel) are read too.
+ *   288 MiB of logits, or 1024 rows) rows of the tree's other nodes (tree indices 0 .. n_sel) are read too.
  * The first stream a context's calls come on keeps the context's scratch for small batches, for the context's life (make the
  * first call on the stream that serves, not on one that warms up); calls on other streams and captured calls use none and take
  * longer, so calls on different streams may overlap.  That stream must not be destroyed before its calls have finished: a

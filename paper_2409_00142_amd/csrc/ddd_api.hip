@@ -51,6 +51,7 @@ struct ddd_ctx {
   // the first stream that uses it: calls on one stream are ordered, calls on any other take the kernel without scratch.  (An
   // event behind every walk, for the next call on any stream to wait for, cost 3 of the 29 us of a call: B = 8, V = 32000.)
   void* sample_rows;
+  uint32_t* sample_asked;        // device [B], zero between calls
   bool sample_owned;
   hipStream_t sample_stream;
   std::mutex sample_mutex;       // held over the two launches, so that two threads' calls do not interleave on the stream
@@ -90,12 +91,12 @@ bool pick_split(int H, int* G, int* nw) {
 // Row pitch of the context's own logits: whole 128-byte lines.
 int logits_pitch(int V) { return (V + 31) & ~31; }
 
-// Whether ddd_verify_sample makes the rows' sums first (tree.hip).  That takes about 13 us and 0.52 for a million tokens of all
-// rows, whatever is accepted; a walk that makes the sums of its own rows 5 and 8.2 for each row of 32768 tokens on the batch's longest path
-// (one more than the accepted tokens), and the more sequences, the longer that is.  Sums against walk where 0.65 of the nodes agree, 61
-// nodes: V = 32000, 24 sequences 36 against 56 us, 32 44 against 57, 32 of 81 nodes (332 MB) 54 against 49 to 70; V = 60001, 32 of 26 nodes 42
-// against 144; V = 128256, 8 sequences 44 against 91, 16 (500 MB) 69 against 98, 32 118 against 118.  By the first figures 64 sequences
-// with V = 32000 (500 MB) would take 78 against 62.
+// Whether ddd_verify_sample makes the rows' sums first (tree.hip).  A walk that makes the sums of its own rows takes 5 us and 8.2 for each
+// row of 32768 tokens on the batch's longest path (one more than the accepted tokens), and the more sequences, the longer that is.  Sums against
+// walk by the longest path, one row / two / as long as it gets where 0.65 of the nodes agree, 61 nodes, us a call: V = 32000, 18 sequences 20
+// against 16 / 26 against 24 / 30 against 55, 32 22 against 16 / 28 against 24 / 34 against 55, 37 22 against 16 / 29 against 24 / 35 against
+// 47; V = 60001, 32 of 26 nodes 25 against 36 / 29 against 62 / 42 against 171; V = 128256, 8 sequences 27 against 35 / 38 against 60 / 38 against
+// 106, 16 (478 MiB) 30 against 36 / 36 against 58 / 47 against 83.
 bool rows_from_sums(const ddd_config& c) {
   const long long rows = (long long)c.B * (c.m + 1);
   return rows <= 1024 || (rows <= 8192 && rows * c.V * 4 <= (288LL << 20));
@@ -348,6 +349,7 @@ int ddd_create(const ddd_config* cfg, ddd_ctx** out) {
   c->stats_sync = nullptr;
   c->stats_on = false;
   c->sample_rows = nullptr;
+  c->sample_asked = nullptr;
   c->sample_owned = false;
   c->sample_stream = nullptr;
   c->stats = ddd_round_stats{nullptr, nullptr, nullptr, nullptr, nullptr};
@@ -362,7 +364,8 @@ int ddd_create(const ddd_config* cfg, ddd_ctx** out) {
   {
     auto aligned = [](size_t n) { return (n + 255) & ~(size_t)255; };
     const size_t o_mask = aligned((DDD_DMAX + 1) * sizeof(uint32_t)), o_sync = o_mask + aligned((DDD_BMAX / 64) * sizeof(uint64_t));
-    const size_t o_act = o_sync + aligned(2 * sizeof(uint32_t)), o_list = o_act + aligned(sizeof(int32_t));
+    const size_t o_asked = o_sync + aligned(2 * sizeof(uint32_t)), o_act = o_asked + aligned((size_t)cfg->B * sizeof(uint32_t));
+    const size_t o_list = o_act + aligned(sizeof(int32_t));
     const size_t o_rows = o_list + aligned(rows * sizeof(int32_t));
     const size_t n_rows = rows_from_sums(*cfg) ? (size_t)cfg->B * (cfg->m + 1) * verify_sample_row_bytes() : 0;
     const size_t o_sum = o_rows + aligned(n_rows), o_gmax = o_sum + aligned(c->part_sum_bytes);
@@ -374,6 +377,7 @@ int ddd_create(const ddd_config* cfg, ddd_ctx** out) {
       c->call_count = reinterpret_cast<uint32_t*>(p);
       c->active_mask = reinterpret_cast<uint64_t*>(p + o_mask);
       c->stats_sync = reinterpret_cast<uint32_t*>(p + o_sync);
+      c->sample_asked = reinterpret_cast<uint32_t*>(p + o_asked);
       c->n_act = reinterpret_cast<int32_t*>(p + o_act);
       c->row_list = reinterpret_cast<int32_t*>(p + o_list);
       if (n_rows) c->sample_rows = p + o_rows;
@@ -782,6 +786,7 @@ int ddd_verify_sample(ddd_ctx* c, const ddd_tree* tree, const float* target_logi
   a.D = c->cfg.max_depth;
   a.V = c->cfg.V;
   a.rows = nullptr;
+  a.asked = c->sample_asked;
   a.parts = 0;
   hipStream_t s = static_cast<hipStream_t>(stream);
   std::unique_lock<std::mutex> lock(c->sample_mutex, std::defer_lock);

@@ -139,6 +139,8 @@ hipError_t launch_verify_accept(const VerifyArgs& a, hipStream_t stream) {
 //    B = 8, V = 32000 24.7 and 18.9 to 21.3 us a call, B = 16 40.4 and 29.2, B = 6 21.5 and 18.9, B = 1 11.9 and 12.3; B = 30, V = 4001,
 //    49 nodes 17.4 and 18.4: what is left out must be worth the leaf of the walk (sums_of_leaves).  (Workgroups of twice and four times
 //    the blocks, which issue a tenth less per token: 31 and 36 us, because all of the loads then come before all of the arithmetic.)
+//    Above 128 MiB of logits the rows are still more than a walk needs if it ends early, so a launch in front makes the roots' sums and
+//    decides there, and only rows below the accepted child are summed up (roots_first).
 //  * beyond that (verify_sample_kernel): one workgroup of 16 waves per sequence makes the sums of the rows it visits.
 // The line lies where the extra rows would cost what they save (rows_from_sums).
 constexpr int kVsWaves = 16;
@@ -542,8 +544,10 @@ struct VsRow {
   double sub[kVsSub];          // block sums, each relative to its part's maximum
   double psum[kVsParts];       // the parts' sums
   float pmax[kVsParts];        // and maxima
-  unsigned arrived;            // of a sequence's first row: the workgroups that have left their part of a leaf's row
-  float pad[7];
+  // of a sequence's first row:
+  uint64_t reach[3];           // bit i: row i's sums are needed if the walk leaves the root (verify_root_kernel)
+  unsigned arrived;            // the workgroups that have left their part of a leaf's row
+  unsigned pad;
 };
 static_assert(sizeof(VsRow) == 1152, "whole lines");
 // Parts of a row that hold tokens (eight from 28 673 tokens up to 32 768, one up to 4096); only those are made and count.
@@ -633,6 +637,108 @@ __device__ __forceinline__ double part_total(const double* s_sub) {
   return total;
 }
 
+// What another workgroup of the launch left in a row: read past this XCD's L2.
+__device__ __forceinline__ double left_f64(const double* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ float left_f32(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// The maximum of a row from its parts', and the row's sum relative to it; parts without tokens were never written.
+__device__ __forceinline__ double row_total(float (&pm)[kVsParts], double (&ps)[kVsParts], int parts, double beta2, float& mx) {
+#pragma unroll
+  for (int p = 0; p < kVsParts; ++p) {
+    pm[p] = p < parts ? pm[p] : -__builtin_inff();
+    ps[p] = p < parts ? ps[p] : 0.0;
+  }
+  mx = -__builtin_inff();
+#pragma unroll
+  for (int p = 0; p < kVsParts; ++p) mx = fmaxf(mx, pm[p]);
+  double rem = 0.0;
+#pragma unroll
+  for (int p = 0; p < kVsParts; ++p) rem = fma(ps[p], weight_of((double)pm[p] - (double)mx, beta2), rem);
+  return rem;
+}
+
+// By one wave: a part's sums (LDS) and maximum are left to the other workgroups of the launch, then this one is counted; the number of
+// those before it, in lane 0.  keep: what else has to be there when it is counted.
+__device__ __forceinline__ unsigned leave_part(VsRow& r, int part, const double* s_sub, float mx, unsigned* count, unsigned& keep, int lane) {
+  if (lane < kVsPartSub)
+    __hip_atomic_store(&r.sub[part * kVsPartSub + lane], s_sub[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const double total = part_total(s_sub);
+  if (lane == 0) {
+    __hip_atomic_store(&r.psum[part], total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&r.pmax[part], mx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  asm volatile("s_waitcnt vmcnt(0)" : "+v"(keep) : : "memory");           // this wave's stores
+  return lane == 0 ? __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+}
+// By the workgroup that was counted last.
+__device__ __forceinline__ double left_total(const VsRow& r, int parts, double beta2, float& mx) {
+  float pm[kVsParts];
+  double ps[kVsParts];
+#pragma unroll
+  for (int p = 0; p < kVsParts; ++p) {
+    pm[p] = left_f32(&r.pmax[p]);
+    ps[p] = left_f64(&r.psum[p]);
+  }
+  return row_total(pm, ps, parts, beta2, mx);
+}
+
+// The sums of the roots' rows alone, a workgroup per part; the one that is counted last tests the root's children and names the rows that
+// the walk can ask for below the one it accepts, for the next launch.
+template <int CPB>
+__global__ __launch_bounds__(kVsPartWaves * kWave) void verify_root_kernel(VerifySampleArgs a) {
+  __shared__ VsTree t;
+  __shared__ float s_max[kVsPartWaves];
+  __shared__ double s_sub[kVsPartSub], s_exp[kVsExpSize], s_kw[DDD_MMAX + 1];
+  __shared__ int s_last, s_child;
+  __shared__ bool s_kids[DDD_MMAX + 1];
+  const int part = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int T = a.m + 1;
+  const int n = min(a.tree.n_sel[b], a.m) + 1;
+  const float* x = a.logits + (size_t)b * T * a.V;
+  VsRow& r = static_cast<VsRow*>(a.rows)[(size_t)b * T];
+  const double beta2 = beta2_of(a);
+  load_tree(a, b, tid, t);
+  const float kx = tid < T ? x[t.tok[tid]] : 0.0f;                        // of the thread's own index: no barrier
+  const float mx = part_sums<CPB>(a, x, part, tid, s_max, s_sub, s_exp);
+  __syncthreads();
+  if (wv == 0) {
+    unsigned none = 0u;
+    const unsigned before = leave_part(r, part, s_sub, mx, a.asked + b, none, lane);
+    if (lane == 0) s_last = before == (unsigned)(a.parts - 1);
+  }
+  __syncthreads();
+  if (!s_last) return;                                                    // block-uniform
+  float top;   // no line of the row's sums has been read before in this launch: no fence, which would cost 1 to 4 us while others stream
+  double rem = left_total(r, a.parts, beta2, top);
+  if (tid < T) {
+    s_kw[tid] = weight_of((double)kx - (double)top, beta2);
+    s_kids[tid] = n <= a.leaf_rows;                                       // then a leaf's sums are made too
+  }
+  __syncthreads();
+  if (tid >= 1 && tid < n && t.par[tid] >= 0 && t.par[tid] < n) s_kids[t.par[tid]] = true;
+  if (wv == 0) {
+    int nrm = 0;
+    const int child = test_children(t, n, lane, rem, nrm, [&](int base, bool& kid, double& kw, double& ku, int& ktok) {
+      const int c = base + lane;
+      kid = c < n && t.par[c] == 0;
+      ktok = c < n ? t.tok[c] : 0;
+      ku = c < n ? t.ua[c] : 0.0;
+      kw = c < n ? s_kw[c] : 0.0;
+    });
+    if (lane == 0) s_child = child;
+  }
+  __syncthreads();
+  const int child = s_child;
+  bool on = false;                                                        // a node is that child, or below it by no more than the walk goes
+  for (int c = tid < n ? tid : -1, d = 0; child > 0 && c > 0 && c < n && d < a.D; c = t.par[c], ++d) on |= c == child;
+  const uint64_t bits = __ballot(on && s_kids[tid]);
+  if (lane == 0 && wv < 3) r.reach[wv] = bits;
+  if (tid == 0) {
+    r.arrived = 0u;
+    a.asked[b] = 0u;
+  }
+}
+
 template <int CPB>
 __global__ __launch_bounds__(kVsPartWaves * kWave) void verify_row_sums_kernel(VerifySampleArgs a) {
   __shared__ float s_max[kVsPartWaves];
@@ -669,19 +775,32 @@ __global__ __launch_bounds__(kVsPartWaves * kWave) void verify_row_sums_kernel(V
   }
 }
 
-// What another workgroup of the launch left in a row: read past this XCD's L2.
-__device__ __forceinline__ double left_f64(const double* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ float left_f32(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-
-// The maximum of a row from its parts', and the row's sum relative to it.
-__device__ __forceinline__ double row_total(const float (&pm)[kVsParts], const double (&ps)[kVsParts], double beta2, float& mx) {
-  mx = -__builtin_inff();
+// The same for the rows that verify_root_kernel has named, dealt to gridDim.y workgroups per part.  Most rows of a tree are not named, and a
+// workgroup for each costs as much where nothing is: 37 sequences, V = 32000, m = 60, nothing / all that 0.65 of the nodes ask for 27.1 and
+// 36.4 us a call with 61 workgroups per part, 22.1 and 34.9 with 16; 8 20.1 and 36.1, and 8 sequences with V = 128256 37.9 with 16 and 49.5.
+constexpr int kVsReached = 16;
+template <int CPB>
+__global__ __launch_bounds__(kVsPartWaves * kWave) void verify_reached_sums_kernel(VerifySampleArgs a) {
+  __shared__ float s_max[kVsPartWaves];
+  __shared__ double s_sub[kVsPartSub], s_exp[kVsExpSize];
+  const int part = blockIdx.x, b = blockIdx.z, tid = threadIdx.x, T = a.m + 1;
+  VsRow* rows = static_cast<VsRow*>(a.rows) + (size_t)b * T;
+  const uint64_t reach[3] = {rows->reach[0], rows->reach[1], rows->reach[2]};
+  int turn = blockIdx.y;                                                  // needed rows in front of this workgroup's next one
 #pragma unroll
-  for (int p = 0; p < kVsParts; ++p) mx = fmaxf(mx, pm[p]);
-  double rem = 0.0;
-#pragma unroll
-  for (int p = 0; p < kVsParts; ++p) rem += ps[p] * weight_of((double)pm[p] - (double)mx, beta2);
-  return rem;
+  for (int w = 0; w < 3; ++w)
+    for (uint64_t left = reach[w]; left != 0ull; left &= left - 1ull) {   // uniform
+      if (turn-- != 0) continue;
+      turn = gridDim.y - 1;
+      const int i = 64 * w + __ffsll((unsigned long long)left) - 1;
+      const float mx = part_sums<CPB>(a, a.logits + ((size_t)b * T + i) * a.V, part, tid, s_max, s_sub, s_exp);
+      __syncthreads();
+      if (tid < kVsPartSub) rows[i].sub[part * kVsPartSub + tid] = s_sub[tid];
+      if (tid == 0) {
+        rows[i].psum[part] = part_total(s_sub);
+        rows[i].pmax[part] = mx;
+      }
+    }
 }
 
 // The walk over the sums of the rows that have children, by as many workgroups per sequence as a row has parts: all take the same
@@ -708,7 +827,7 @@ __global__ __launch_bounds__(kVsWalkThreads) void verify_sample_from_sums_kernel
   load_tree(a, b, tid, t);
   float kx = 0.0f;
   if (tid >= 1 && tid < n) kx = a.logits[((size_t)b * T + min(max(t.par[tid], 0), T - 1)) * V + t.tok[tid]];
-  if (tid < n) {                                                          // a leaf's were never written, and are not used
+  if (tid < n) {                                                          // a leaf's (or what is out of reach) were never written, and are not used
     float pm[kVsParts];
     double ps[kVsParts];
 #pragma unroll
@@ -716,12 +835,7 @@ __global__ __launch_bounds__(kVsWalkThreads) void verify_sample_from_sums_kernel
       pm[p] = rows[tid].pmax[p];
       ps[p] = rows[tid].psum[p];
     }
-#pragma unroll
-    for (int p = 0; p < kVsParts; ++p) {                                  // nor were those of parts without tokens
-      pm[p] = p < parts ? pm[p] : -__builtin_inff();
-      ps[p] = p < parts ? ps[p] : 0.0;
-    }
-    s_rem[tid] = row_total(pm, ps, beta2, s_max[tid]);
+    s_rem[tid] = row_total(pm, ps, parts, beta2, s_max[tid]);
   }
   __syncthreads();
   if (tid >= 1 && tid < n) s_kw[tid] = weight_of((double)kx - (double)s_max[min(max(t.par[tid], 0), T - 1)], beta2);
@@ -776,36 +890,16 @@ __global__ __launch_bounds__(kVsWalkThreads) void verify_sample_from_sums_kernel
     const float mx = part_sums<CPB>(a, x, part, tid, s_pmax, s_sub, s_exp);
     __syncthreads();
     if (wv == 0) {
-      if (lane < kVsPartSub)
-        __hip_atomic_store(&r.sub[part * kVsPartSub + lane], s_sub[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const double total = part_total(s_sub);
-      unsigned before = 0u;
-      if (lane == 0) {
-        __hip_atomic_store(&r.psum[part], total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(&r.pmax[part], mx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-      // this wave's stores, and the depth that stats_begin has put into the maximum, are there before the arrival is counted
-      asm volatile("s_waitcnt vmcnt(0)" : "+v"(sp.before) : : "memory");
-      if (lane == 0) before = __hip_atomic_fetch_add(&rows[0].arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      // sp: the depth that stats_begin has put into the maximum
+      const unsigned before = leave_part(r, part, s_sub, mx, &rows[0].arrived, sp.before, lane);
       if (lane == 0) s_leaf = before == (unsigned)(parts - 1) ? 2 : 1;
     }
     __syncthreads();
     if (s_leaf != 2) return;                                              // block-uniform
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");                    // lines of this row that this XCD has read before are old
     if (wv == 0) {
-      float pm[kVsParts], top;
-      double ps[kVsParts];
-#pragma unroll
-      for (int p = 0; p < kVsParts; ++p) {
-        pm[p] = left_f32(&r.pmax[p]);
-        ps[p] = left_f64(&r.psum[p]);
-      }
-#pragma unroll
-      for (int p = 0; p < kVsParts; ++p) {
-        pm[p] = p < parts ? pm[p] : -__builtin_inff();
-        ps[p] = p < parts ? ps[p] : 0.0;
-      }
-      rem = row_total(pm, ps, beta2, top);
+      float top;
+      rem = left_total(r, parts, beta2, top);
       if (lane == 0) s_max[cur] = top;
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
@@ -854,6 +948,28 @@ static int rows_with_leaves(const VerifySampleArgs& a) {
   return sums_of_leaves(a) ? a.m + 1 : (int)((10LL << 20) / ((long long)a.B * a.V * 4));
 }
 
+// Whether the roots are decided by a launch of their own.  It takes 8 us and leaves the next one half of the rows where 0.65 of the nodes
+// agree and none where the root rejects all its children.  With it and without, 61 nodes, us a call, root alone / one or two rows more / 0.65 of
+// the nodes: V = 32000, 18 sequences (134 MiB) 20.3 and 29.5 / 25.6 and 29.3 / 30.1 and 29.9, 32 21.6 and 40.9 / 28.2 and 41.0 / 33.8 and 40.7, 37
+// 22.1 and 45.1 / 28.6 and 44.9 / 34.9 and 45.3; V = 128256, 8 26.6 and 41.9 / 38.4 and 41.8 / 37.9 and 40.8.  Below the line two launches are
+// as fast where nodes agree (119 MiB 27.7).
+static bool roots_first(const VerifySampleArgs& a) { return (long long)a.B * (a.m + 1) * a.V * 4 > 128LL << 20; }
+
+// The launches in front of the walk.
+template <int CPB>
+static hipError_t launch_sums(const VerifySampleArgs& a, hipStream_t stream) {
+  const dim3 wg(kVsPartWaves * kWave);
+  if (!roots_first(a)) {
+    hipLaunchKernelGGL((verify_row_sums_kernel<CPB>), dim3(a.parts, a.m + 1, a.B), wg, 0, stream, a);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL((verify_root_kernel<CPB>), dim3(a.parts, a.B), wg, 0, stream, a);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((verify_reached_sums_kernel<CPB>), dim3(a.parts, kVsReached, a.B), wg, 0, stream, a);
+  return hipGetLastError();
+}
+
 hipError_t launch_verify_sample(VerifySampleArgs a, hipStream_t stream) {
   if (a.m > DDD_MMAX) return hipErrorInvalidValue;      // the kernels keep the tree in LDS
   a.beta2 = 1.4426950408889634 / (double)a.temperature;
@@ -863,18 +979,17 @@ hipError_t launch_verify_sample(VerifySampleArgs a, hipStream_t stream) {
     a.parts = vs_parts(a.V);
     a.leaf_rows = rows_with_leaves(a);
     const bool leaves = a.leaf_rows > a.m;
-    const dim3 grid(a.parts, a.m + 1, a.B), block(kVsPartWaves * kWave);
+    hipError_t e = hipSuccess;
     if (cpb == 1)
-      hipLaunchKernelGGL((verify_row_sums_kernel<1>), grid, block, 0, stream, a);
+      e = launch_sums<1>(a, stream);
     else if (cpb == 2)
-      hipLaunchKernelGGL((verify_row_sums_kernel<2>), grid, block, 0, stream, a);
+      e = launch_sums<2>(a, stream);
     else if (cpb == 3)
-      hipLaunchKernelGGL((verify_row_sums_kernel<3>), grid, block, 0, stream, a);
+      e = launch_sums<3>(a, stream);
     else if (cpb == 4)
-      hipLaunchKernelGGL((verify_row_sums_kernel<4>), grid, block, 0, stream, a);
+      e = launch_sums<4>(a, stream);
     else
-      hipLaunchKernelGGL((verify_row_sums_kernel<0>), grid, block, 0, stream, a);
-    hipError_t e = hipGetLastError();
+      e = launch_sums<0>(a, stream);
     if (e != hipSuccess) return e;
     const dim3 walk(leaves ? 1 : a.parts, a.B), wg(kVsWalkThreads);
     if (leaves && a.parts == kVsParts)
