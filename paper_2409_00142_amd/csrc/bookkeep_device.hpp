@@ -285,8 +285,8 @@ __device__ __forceinline__ bool stop_test(const BeamArgs& a, int b, int lane, fl
 // and the final tree as soon as the sequence stops.  Every thread of the block must call it.
 // The launch follows a kernel that has streamed the whole LM head through the L2, so its instructions are fetched from behind it: what a
 // call runs lies together, rare ways (a merge by rounds, the tree) at the end, and what it cannot need - the other form of the rows, rows
-// beyond the waves - is not compiled in: 47 -> 21 KB for rows of the weight stream and 15 KB for the GEMM's, no spilled SGPRs.  A call of
-// ten rows 10.9 -> 9.7 us by the profiler; rounds of one user (six calls) 343.9 -> 333.0, of 64 sequences 981 -> 959, with the tree's selection.
+// beyond the waves - is not compiled in: 47 -> 19 KB for rows of the weight stream and 14 KB for the GEMM's, no spilled SGPRs.  Calls of
+// ten rows 10.6 -> 7.7 us by the profiler (ten calls a round, the last with the final tree); rounds of one user (six calls) 343.9 -> 333.0, of 64 sequences 981 -> 959, with the tree's selection.
 struct StepSmem {
   TreeSmem tsm;
   uint64_t cand[kKM * kKM];   // beam keys of the k*k candidates

@@ -787,6 +787,7 @@ __global__ __launch_bounds__(kVsPartWaves * kWave) void verify_reached_sums_kern
   VsRow* rows = static_cast<VsRow*>(a.rows) + (size_t)b * T;
   const uint64_t reach[3] = {rows->reach[0], rows->reach[1], rows->reach[2]};
   int turn = blockIdx.y;                                                  // needed rows in front of this workgroup's next one
+  // Three copies of the sums: one loop over all bits, half the code, took 0.3 to 1 us longer (32 sequences, V = 32000 33.7 and 34.7).
 #pragma unroll
   for (int w = 0; w < 3; ++w)
     for (uint64_t left = reach[w]; left != 0ull; left &= left - 1ull) {   // uniform
