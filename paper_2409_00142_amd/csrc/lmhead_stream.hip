@@ -83,9 +83,25 @@ __global__ __launch_bounds__(768) void lmhead_stream_kernel(StreamArgs a) {
 
     u32x4 ring[G][4];
     bf16x8 bfrag[G][4];
+    auto load_x = [&](int g) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        u32x4 u = {0u, 0u, 0u, 0u};
+        if (n < a.R) u = *reinterpret_cast<const u32x4*>(a.hid + (size_t)n * a.H + ks + g * 128 + j * 32 + q * 8);
+        bfrag[g][j] = __builtin_bit_cast(bf16x8, u);
+      }
+    };
+    // Loads return in order.  With four groups the first one is multiplied, and its next weights requested, when its own operands are
+    // there.  With one or two that is hardly earlier than when all are, and the hidden rows go first, on their way while the tile is found.
+    // Rows first against rows behind each group, us a call: ten rows, V = 32000 H = 1024 24.4 and 24.7, H = 4096 46.2 and 45.6, V = 12001 H = 2048
+    // 16.5 and 16.8, H = 4096 24.5 and 24.0; fifteen rows, V = 4000, H = 2048 10.4 and 10.7; ten, V = 4000, H = 5120 15.9 and 14.9.
+    constexpr bool kRowsFirst = G < 4;
+    if constexpr (kRowsFirst) {
+#pragma unroll
+      for (int g = 0; g < G; ++g) load_x(g);
+    }
     {
       const int lo = tile_lo(0), last = tile_hi(0) - 1;   // rows are clamped to the tile
-      // loads return in order: the first group is multiplied, and its next weights requested, when its own operands are there
 #pragma unroll
       for (int g = 0; g < G; ++g) {
 #pragma unroll
@@ -93,13 +109,10 @@ __global__ __launch_bounds__(768) void lmhead_stream_kernel(StreamArgs a) {
           const int row = min(lo + i * 4 + lrow, last);
           ring[g][i] = *reinterpret_cast<const u32x4*>(wbase + (size_t)row * a.H + g * 128);
         }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          u32x4 u = {0u, 0u, 0u, 0u};
-          if (n < a.R) u = *reinterpret_cast<const u32x4*>(a.hid + (size_t)n * a.H + ks + g * 128 + j * 32 + q * 8);
-          bfrag[g][j] = __builtin_bit_cast(bf16x8, u);
+        if constexpr (!kRowsFirst) {
+          load_x(g);
+          __builtin_amdgcn_sched_barrier(0);
         }
-        __builtin_amdgcn_sched_barrier(0);
       }
     }
     if (check_late) {   // the requests above are simply dropped if nothing is active
