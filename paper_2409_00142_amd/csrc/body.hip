@@ -92,8 +92,9 @@ __global__ __launch_bounds__((kLinearWaves + 1) * 64) void linear_stream_kernel(
   const int total = nt * NR;          // (tile, range) steps of this workgroup, ranges innermost
   // Neighbours start with different ranges: rows of 16 KB whose first halves every workgroup reads at the same time do not reach the
   // whole memory, and a short last range keeps no workgroup waiting at the same moment.  Three calls of one user (H = 4096, F = 11008)
-  // 404.3 -> 397.5 us; the down product of ten rows 27.5 -> 25.2, the FC of one row 21.0 -> 18.4.  The ranges are added up in order.
-  const int rot = MULTI ? slice % NR : 0;
+  // 404.3 -> 397.5 us; the down product of ten rows 27.5 -> 25.2.  The ranges are added up in order, which few workgroups, far from the memory's
+  // limit, only wait for: 64 of them (N = 1024, K = 11008, ten rows) 13.1 us and 13.9 rotated, 128 (N = 2048, K = 5632) 8.5 both.
+  const int rot = MULTI && nslice >= 192 ? slice % NR : 0;
   auto range_at = [&](int i) { const int r = i + rot; return r < NR ? r : r - NR; };   // 0 <= i < NR
 
   if (wave < NW) {
@@ -173,6 +174,7 @@ __global__ __launch_bounds__((kLinearWaves + 1) * 64) void linear_stream_kernel(
         __syncthreads();
         if (i < NR - rot && rot != 0) continue;
         const int r0 = range_at(i), r1 = i == NR - 1 ? NR : r0 + 1;
+#pragma unroll 5   // reads in flight together: down of ten rows 0.4 us
         for (int w = r0 * NW; w < r1 * NW; ++w) s += *reinterpret_cast<const f32x4*>(tile + w * 256);
       }
       if (active) {
