@@ -51,7 +51,6 @@ struct ddd_ctx {
   // the first stream that uses it: calls on one stream are ordered, calls on any other take the kernel without scratch.  (An
   // event behind every walk, for the next call on any stream to wait for, cost 3 of the 29 us of a call: B = 8, V = 32000.)
   void* sample_rows;
-  uint32_t* sample_asked;        // device [B], zero between calls
   bool sample_owned;
   hipStream_t sample_stream;
   std::mutex sample_mutex;       // held over the two launches, so that two threads' calls do not interleave on the stream
@@ -349,7 +348,6 @@ int ddd_create(const ddd_config* cfg, ddd_ctx** out) {
   c->stats_sync = nullptr;
   c->stats_on = false;
   c->sample_rows = nullptr;
-  c->sample_asked = nullptr;
   c->sample_owned = false;
   c->sample_stream = nullptr;
   c->stats = ddd_round_stats{nullptr, nullptr, nullptr, nullptr, nullptr};
@@ -364,20 +362,20 @@ int ddd_create(const ddd_config* cfg, ddd_ctx** out) {
   {
     auto aligned = [](size_t n) { return (n + 255) & ~(size_t)255; };
     const size_t o_mask = aligned((DDD_DMAX + 1) * sizeof(uint32_t)), o_sync = o_mask + aligned((DDD_BMAX / 64) * sizeof(uint64_t));
-    const size_t o_asked = o_sync + aligned(2 * sizeof(uint32_t)), o_act = o_asked + aligned((size_t)cfg->B * sizeof(uint32_t));
-    const size_t o_list = o_act + aligned(sizeof(int32_t));
+    const size_t o_act = o_sync + aligned(2 * sizeof(uint32_t)), o_list = o_act + aligned(sizeof(int32_t));
     const size_t o_rows = o_list + aligned(rows * sizeof(int32_t));
     const size_t n_rows = rows_from_sums(*cfg) ? (size_t)cfg->B * (cfg->m + 1) * verify_sample_row_bytes() : 0;
-    const size_t o_sum = o_rows + aligned(n_rows), o_gmax = o_sum + aligned(c->part_sum_bytes);
+    const size_t n_asked = n_rows ? cfg->B * sizeof(uint32_t) : 0;
+    const size_t o_sum = o_rows + aligned(n_rows + n_asked), o_gmax = o_sum + aligned(c->part_sum_bytes);
     const size_t o_gsum = o_gmax + aligned(c->grp_bytes);
     if (e == hipSuccess) e = hipMalloc(&c->small, o_gsum + aligned(c->grp_bytes));
     if (e == hipSuccess) e = hipMemset(c->small, 0, o_act);
+    if (e == hipSuccess && n_asked) e = hipMemset(static_cast<unsigned char*>(c->small) + o_rows + n_rows, 0, n_asked);
     if (e == hipSuccess) {
       unsigned char* p = static_cast<unsigned char*>(c->small);
       c->call_count = reinterpret_cast<uint32_t*>(p);
       c->active_mask = reinterpret_cast<uint64_t*>(p + o_mask);
       c->stats_sync = reinterpret_cast<uint32_t*>(p + o_sync);
-      c->sample_asked = reinterpret_cast<uint32_t*>(p + o_asked);
       c->n_act = reinterpret_cast<int32_t*>(p + o_act);
       c->row_list = reinterpret_cast<int32_t*>(p + o_list);
       if (n_rows) c->sample_rows = p + o_rows;
@@ -786,7 +784,6 @@ int ddd_verify_sample(ddd_ctx* c, const ddd_tree* tree, const float* target_logi
   a.D = c->cfg.max_depth;
   a.V = c->cfg.V;
   a.rows = nullptr;
-  a.asked = c->sample_asked;
   a.parts = 0;
   hipStream_t s = static_cast<hipStream_t>(stream);
   std::unique_lock<std::mutex> lock(c->sample_mutex, std::defer_lock);

@@ -224,8 +224,9 @@ struct VerifySampleArgs {
   int32_t* bonus_token;          // [B]
   float temperature;
   int B, m, D, V;
-  void* rows;                    // null, or scratch of verify_sample_row_bytes() per row of logits: the sums of the rows first
-  uint32_t* asked;               // with rows: device [B], zero between calls: the workgroups that have made their part of the root's row
+  // null, or scratch of verify_sample_row_bytes() per row of logits (the sums of the rows first) and, behind them, one word per sequence that is
+  // zero between calls (the workgroups that have made their part of the root's row)
+  void* rows;
   // set by the launcher:
   int parts;                     // of every row's sums
   int leaf_rows;                 // trees of up to so many rows have the sums of their leaves made too (m + 1: all trees)

@@ -696,6 +696,7 @@ __global__ __launch_bounds__(kVsPartWaves * kWave) void verify_root_kernel(Verif
   const int n = min(a.tree.n_sel[b], a.m) + 1;
   const float* x = a.logits + (size_t)b * T * a.V;
   VsRow& r = static_cast<VsRow*>(a.rows)[(size_t)b * T];
+  unsigned* const asked = reinterpret_cast<unsigned*>(static_cast<VsRow*>(a.rows) + (size_t)a.B * T) + b;
   const double beta2 = beta2_of(a);
   load_tree(a, b, tid, t);
   const float kx = tid < T ? x[t.tok[tid]] : 0.0f;                        // of the thread's own index: no barrier
@@ -703,7 +704,7 @@ __global__ __launch_bounds__(kVsPartWaves * kWave) void verify_root_kernel(Verif
   __syncthreads();
   if (wv == 0) {
     unsigned none = 0u;
-    const unsigned before = leave_part(r, part, s_sub, mx, a.asked + b, none, lane);
+    const unsigned before = leave_part(r, part, s_sub, mx, asked, none, lane);
     if (lane == 0) s_last = before == (unsigned)(a.parts - 1);
   }
   __syncthreads();
@@ -735,7 +736,7 @@ __global__ __launch_bounds__(kVsPartWaves * kWave) void verify_root_kernel(Verif
   if (lane == 0 && wv < 3) r.reach[wv] = bits;
   if (tid == 0) {
     r.arrived = 0u;
-    a.asked[b] = 0u;
+    *asked = 0u;
   }
 }
 
