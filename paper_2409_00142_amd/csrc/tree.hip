@@ -12,8 +12,8 @@ __global__ __launch_bounds__(1024) void tree_finalize_kernel(FinalizeArgs a) {
 
 hipError_t launch_tree_finalize(const FinalizeArgs& a, hipStream_t stream) {
   // Half the waves, two nodes a thread, where neither the pool nor the mask keeps them busy: barriers and the conclusions that every wave
-  // draws cost less.  512 against 1024 threads, m = 60: one sequence with 211 / 511 / 811 nodes 5.34 and 5.9 us, 5.27 and 5.57, 5.26 and 5.41;
-  // eight 5.3 and 5.9, 5.7 and 6.2, 5.99 and 6.09; 64 5.55 and 6.1, 5.9 and 6.3, 6.3 and 6.6.  A wider mask keeps sixteen waves busy: 511
+  // draws cost less.  512 against 1024 threads, m = 60: one sequence with 511 / 811 nodes 5.27 and 5.57 us, 5.26 and 5.41; eight
+  // 5.7 and 6.2, 5.99 and 6.09; 64 5.9 and 6.3, 6.3 and 6.6.  A wider mask keeps sixteen waves busy: 511
   // nodes and m = 64 5.72 and 5.81, m = 80 5.88 and 5.85.
   const int threads = a.nmax <= 1025 && a.m <= 64 ? 512 : 1024;
   static_assert(DDD_POOL_MAX <= 4 * 1024 + 1, "a thread for every four nodes");

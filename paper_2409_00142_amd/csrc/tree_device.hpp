@@ -250,17 +250,58 @@ __device__ __forceinline__ uint32_t scan32_u32(uint32_t x, int lane) {
   const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)x, 15);
   return lane >= 16 ? x + first : x;
 }
+// By one wave: the tree indices of the `want` best of nodes 1 .. n (n <= 64 S, sc[h] the score of node 64 h + lane + 1), i.e. 1 + the number
+// of taken nodes with a smaller id, to tidx, and their ids to sel.  The prefix is found bit by bit, a compare and a scalar popcount per 64
+// nodes, and no further than one that exactly `want` reach; of equal scores the lowest ids are taken.
+template <int S>
+__device__ __forceinline__ void wave_take(const float* sc, int n, int want, int lane, int* tidx, int* sel) {
+  uint32_t key[S], thr = 0u;
+  bool real[S];
+#pragma unroll
+  for (int h = 0; h < S; ++h) {
+    real[h] = 64 * h + lane < n;
+    key[h] = real[h] ? ord32(sc[h]) : 0u;
+  }
+  if (want < n)                                                   // uniform
+    for (uint32_t bit = 0x80000000u; bit != 0u; bit >>= 1) {
+      const uint32_t cand = thr | bit;
+      int cnt = 0;
+#pragma unroll
+      for (int h = 0; h < S; ++h) cnt += __popcll(__ballot(key[h] >= cand));
+      if (cnt >= want) thr = cand;
+      if (cnt == want) break;
+    }
+  int left = want;                                                // places for scores equal to thr
+#pragma unroll
+  for (int h = 0; h < S; ++h) left -= __popcll(__ballot(real[h] && key[h] > thr));
+  const unsigned long long below = (1ull << lane) - 1ull;
+  int over = 0, same = 0;                                         // of smaller ids
+#pragma unroll
+  for (int h = 0; h < S; ++h) {
+    const unsigned long long gt = __ballot(real[h] && key[h] > thr), eq = __ballot(real[h] && key[h] == thr);
+    const int o = over + __popcll(gt & below), e = same + __popcll(eq & below);
+    const bool in = real[h] && (key[h] > thr || (key[h] == thr && e < left));
+    const int t = 1 + o + min(e, left), id = 64 * h + lane + 1;
+    if (real[h]) tidx[id] = in ? t : -1;
+    if (in) sel[t] = id;
+    over += __popcll(gt);
+    same += __popcll(eq);
+  }
+}
 // Pools of up to Q nodes per thread of the block: thread t looks after pool nodes t + 1, t + 1 + nthr, ... from their scores to their
 // lines of the tree, so nothing is searched for and nothing is fetched twice.  One round trip brings the pool's size and every node's
 // score, parent, token and depth.  Selection: the m-th largest score (ordered bits) is found six bits at a time by the whole block -
 // the 64 digits are counted in LDS, one barrier, and every wave draws the same conclusion, lane d for the digit d - and no further than a
-// prefix that exactly m nodes reach, three passes as a rule; of equal scores the lowest ids are taken.  The tree index of a selected node
+// prefix that exactly m nodes reach, three passes as a rule; of equal scores the lowest ids are taken.  Pools of up to 256 nodes are left to
+// one wave (wave_take; 37 nodes and m = 16 4.2 -> 3.6 us, 131 and m = 48 5.1 -> 4.2, 211 and m = 60 5.2 -> 5.0; a wave that selects
+// for itself in every wave: 4.1, 4.9).  The tree index of a selected node
 // is 1 + the number of selected nodes with a smaller id (ballots, and the waves' totals through LDS).  A parent's tree index is read from
 // the node -> index table (a selected node's parent is selected: its score is no smaller and its id is smaller).
 // A launch is latency alone, and small code: behind a stream of weights its instructions come from memory.  ddd_tree_finalize of one
-// sequence with 211 / 511 / 811 / 1809 / 3857 nodes, m = 60: 5.3 / 5.3 / 5.3 / 6.4 / 8.3 us on the GPU; with one wave that found the score bit
+// sequence with 211 / 511 / 811 / 1809 / 3857 nodes, m = 60: 5.0 / 5.3 / 5.3 / 6.4 / 8.3 us on the GPU; with one wave that found the score bit
 // by bit up to 1024 nodes, a ranking of candidates up to 2048 and a sort beyond 5.0 / 6.3 / 7.7 / 10.3 / 36.5.
 constexpr int kTreeMost = kPoolMax;        // nodes of the largest pool
+constexpr int kTreeFew = 256;              // nodes up to which one wave selects
 constexpr int kTreeDigit = 6, kTreePasses = (32 + kTreeDigit - 1) / kTreeDigit;
 template <int Q>
 __device__ __forceinline__ void tree_select_block(const ddd_state& st, const ddd_tree& tree, int b, int m, int nmax,
@@ -293,19 +334,23 @@ __device__ __forceinline__ void tree_select_block(const ddd_state& st, const ddd
       my_dep[q] = pdep[n + 1];
     }
   }
+  const bool few = Q == 2 && most <= kTreeFew;                     // uniform
+  float few_sc[kTreeFew / 64] = {};
+  if (few && wave == 0) {
+#pragma unroll
+    for (int h = 0; h < kTreeFew / 64; ++h)
+      if (64 * h + lane < most) few_sc[h] = psc[64 * h + lane + 1];
+  }
   if (tid == 0) {
     root_tok = ptok[0];
     root_dep = pdep[0];
   }
   const int N = (n_nodes >= 0 ? n_nodes : min(st.n_nodes[b], nmax)) - 1, m_eff = min(m, N);
-  for (int i = tid; i < kTreePasses * 64; i += nthr) hist[i] = 0;
-  for (int i = tid; i < Q * 16; i += nthr) wtot[i] = 0u;          // of waves that are not there
   if (tid == 0) {
     tidx[0] = 0;
     sm.e.sel[0] = 0;
     sm.e.par[0] = -1;
   }
-  tree_lds_barrier();
   uint32_t key[Q];
   bool real[Q];
 #pragma unroll
@@ -313,67 +358,83 @@ __device__ __forceinline__ void tree_select_block(const ddd_state& st, const ddd
     real[q] = tid + q * nthr < N;
     key[q] = ord32(my_sc[q]);
   }
-  // ---- thr: the m_eff-th largest score, or a prefix that exactly m_eff reach ---------------------------------------
-  uint32_t thr = 0u;
-  if (m_eff < N) {                                                // uniform
-    int above = 0;                                                // scores beyond the prefix
-#pragma unroll 1
-    for (int pass = 0; pass < kTreePasses; ++pass) {
-      const int shift = max(32 - kTreeDigit * (pass + 1), 0);
-      const uint32_t known = pass == 0 ? 0u : ~0u << (32 - kTreeDigit * pass);
-#pragma unroll
-      for (int q = 0; q < Q; ++q) {
-        const bool in = real[q] && ((key[q] ^ thr) & known) == 0u;
-        const int digit = (int)((key[q] & ~known) >> shift);
-        const unsigned long long who = __ballot(in);
-        if (who == 0ull) continue;                                // wave-uniform
-        // One addition for all lanes with the digit of the first: the scores' highest digits are alike, and additions to one address
-        // wait for each other.  1809 nodes 7.5 -> 6.4 us, 511 5.45 -> 5.27, 211 5.27 -> 5.34; all scores equal 14.5 -> 7.5, 511 nodes 7.7 -> 6.1.
-        const int first = __ffsll(who) - 1, common = __builtin_amdgcn_readlane(digit, first);
-        const unsigned long long same = __ballot(in && digit == common);
-        if (lane == first || (in && digit != common)) atomicAdd(&hist[pass * 64 + digit], lane == first ? (int)__popcll(same) : 1);
-      }
-      __syncthreads();
-      const int from = above + suffix64_i32(hist[pass * 64 + lane], lane);   // scores that reach this lane's digit: falling, lane 0 all
-      const int d = 63 - __clzll((long long)__ballot(from >= m_eff));
-      const int reach = __builtin_amdgcn_readlane(from, d);
-      if (d < 63) above = __builtin_amdgcn_readlane(from, d + 1);
-      thr |= (uint32_t)d << shift;
-      if (reach == m_eff) break;                                  // uniform
-    }
-  }
-  // ---- tree indices --------------------------------------------------------------------------------------------------
-  unsigned long long larger[Q], equal[Q];
-#pragma unroll
-  for (int q = 0; q < Q; ++q) {
-    larger[q] = __ballot(real[q] && key[q] > thr);
-    equal[q] = __ballot(real[q] && key[q] == thr);
-    if (lane == 0) wtot[q * 16 + wave] = (uint32_t)__popcll(larger[q]) | (uint32_t)__popcll(equal[q]) << 16;
-  }
-  __syncthreads();
   int ti[Q];
-  {
-    const unsigned long long below = (1ull << lane) - 1ull;
-    uint32_t own[Q / 2], before[Q / 2], all = 0u;                 // totals of nodes with smaller ids
-#pragma unroll
-    for (int h = 0; h < Q / 2; ++h) {
-      own[h] = lane < 32 ? wtot[h * 32 + lane] : 0u;
-      const uint32_t incl = scan32_u32(own[h], lane);
-      before[h] = all + incl - own[h];
-      all += (uint32_t)__builtin_amdgcn_readlane((int)incl, 31);
+  const unsigned long long below = (1ull << lane) - 1ull;
+  if (few) {
+    if (wave == 0) {
+      if (most <= 128)                                            // uniform
+        wave_take<2>(few_sc, N, m_eff, lane, tidx, sm.e.sel);
+      else
+        wave_take<4>(few_sc, N, m_eff, lane, tidx, sm.e.sel);
     }
-    const int left = m_eff - (int)(all & 0xFFFFu);                // places for scores equal to thr
+  } else {
+    for (int i = tid; i < kTreePasses * 64; i += nthr) hist[i] = 0;
+    for (int i = tid; i < Q * 16; i += nthr) wtot[i] = 0u;          // of waves that are not there
+    tree_lds_barrier();
+    // ---- thr: the m_eff-th largest score, or a prefix that exactly m_eff reach ---------------------------------------
+    uint32_t thr = 0u;
+    if (m_eff < N) {                                                // uniform
+      int above = 0;                                                // scores beyond the prefix
+#pragma unroll 1
+      for (int pass = 0; pass < kTreePasses; ++pass) {
+        const int shift = max(32 - kTreeDigit * (pass + 1), 0);
+        const uint32_t known = pass == 0 ? 0u : ~0u << (32 - kTreeDigit * pass);
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+          const bool in = real[q] && ((key[q] ^ thr) & known) == 0u;
+          const int digit = (int)((key[q] & ~known) >> shift);
+          const unsigned long long who = __ballot(in);
+          if (who == 0ull) continue;                                // wave-uniform
+          // One addition for all lanes with the digit of the first: the scores' highest digits are alike, and additions to one address
+          // wait for each other.  1809 nodes 7.5 -> 6.4 us, 511 5.45 -> 5.27; all scores equal 14.5 -> 7.5, 511 nodes 7.7 -> 6.1.
+          const int first = __ffsll(who) - 1, common = __builtin_amdgcn_readlane(digit, first);
+          const unsigned long long same = __ballot(in && digit == common);
+          if (lane == first || (in && digit != common)) atomicAdd(&hist[pass * 64 + digit], lane == first ? (int)__popcll(same) : 1);
+        }
+        __syncthreads();
+        const int from = above + suffix64_i32(hist[pass * 64 + lane], lane);   // scores that reach this lane's digit: falling, lane 0 all
+        const int d = 63 - __clzll((long long)__ballot(from >= m_eff));
+        const int reach = __builtin_amdgcn_readlane(from, d);
+        if (d < 63) above = __builtin_amdgcn_readlane(from, d + 1);
+        thr |= (uint32_t)d << shift;
+        if (reach == m_eff) break;                                  // uniform
+      }
+    }
+    // ---- tree indices --------------------------------------------------------------------------------------------------
+    unsigned long long larger[Q], equal[Q];
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-      const uint32_t pre = (uint32_t)__builtin_amdgcn_readlane((int)before[q / 2], (q & 1) * 16 + wave);
-      const int gt = (int)(pre & 0xFFFFu) + __popcll(larger[q] & below), eq = (int)(pre >> 16) + __popcll(equal[q] & below);
-      const bool in = real[q] && (key[q] > thr || (key[q] == thr && eq < left));
-      ti[q] = in ? 1 + gt + min(eq, left) : -1;
-      if (real[q]) tidx[tid + q * nthr + 1] = ti[q];
-      if (in) sm.e.sel[ti[q]] = tid + q * nthr + 1;
+      larger[q] = __ballot(real[q] && key[q] > thr);
+      equal[q] = __ballot(real[q] && key[q] == thr);
+      if (lane == 0) wtot[q * 16 + wave] = (uint32_t)__popcll(larger[q]) | (uint32_t)__popcll(equal[q]) << 16;
+    }
+    __syncthreads();
+    {
+      uint32_t own[Q / 2], before[Q / 2], all = 0u;                 // totals of nodes with smaller ids
+#pragma unroll
+      for (int h = 0; h < Q / 2; ++h) {
+        own[h] = lane < 32 ? wtot[h * 32 + lane] : 0u;
+        const uint32_t incl = scan32_u32(own[h], lane);
+        before[h] = all + incl - own[h];
+        all += (uint32_t)__builtin_amdgcn_readlane((int)incl, 31);
+      }
+      const int left = m_eff - (int)(all & 0xFFFFu);                // places for scores equal to thr
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        const uint32_t pre = (uint32_t)__builtin_amdgcn_readlane((int)before[q / 2], (q & 1) * 16 + wave);
+        const int gt = (int)(pre & 0xFFFFu) + __popcll(larger[q] & below), eq = (int)(pre >> 16) + __popcll(equal[q] & below);
+        const bool in = real[q] && (key[q] > thr || (key[q] == thr && eq < left));
+        ti[q] = in ? 1 + gt + min(eq, left) : -1;
+        if (real[q]) tidx[tid + q * nthr + 1] = ti[q];
+        if (in) sm.e.sel[ti[q]] = tid + q * nthr + 1;
+      }
     }
   }
   __syncthreads();
+  if (few) {
+#pragma unroll
+    for (int q = 0; q < Q; ++q) ti[q] = real[q] ? tidx[tid + q * nthr + 1] : -1;
+  }
 #pragma unroll
   for (int q = 0; q < Q; ++q)
     if (ti[q] >= 0) {
@@ -412,8 +473,15 @@ __device__ __forceinline__ void tree_select_block(const ddd_state& st, const ddd
   }
   tree_lds_barrier();
   uint8_t* mask = tree.mask + (size_t)b * T * T;
-  for (int i = wave; i < T; i += nwaves)                          // a row per wave
-    for (int j = lane; j < T; j += 64) mask[i * T + j] = (uint8_t)((sm.e.bits[i][j >> 5] >> (j & 31)) & 1u);
+  if (T <= 52) {                                                  // rows would leave lanes idle: 17 rows 0.2 us
+    for (int e = tid; e < T * T; e += nthr) {
+      const int i = e / T, j = e - i * T;
+      mask[e] = (uint8_t)((sm.e.bits[i][j >> 5] >> (j & 31)) & 1u);
+    }
+  } else {
+    for (int i = wave; i < T; i += nwaves)                        // a row per wave
+      for (int j = lane; j < T; j += 64) mask[i * T + j] = (uint8_t)((sm.e.bits[i][j >> 5] >> (j & 31)) & 1u);
+  }
 }
 
 // The final tree of a pool of at most DDD_POOL_MAX nodes.  Must be called by every thread of the block, at most 1024.
