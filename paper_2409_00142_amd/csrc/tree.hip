@@ -936,10 +936,11 @@ __global__ __launch_bounds__(kVsWalkThreads) void verify_sample_from_sums_kernel
 // Whether the leaves' rows are summed up too.  A walk that ends at a leaf without them takes 4 to 5 us longer, and of a batch's walks one
 // usually does where trees are small.  With them and without, us a call: 8 MB of logits 11.9 and 12.3, 16 MB 14.5 and 14.4, 24 MB in rows of
 // 16 KB 17.4 and 18.4, 23 MB in rows of 128 KB 17.2 and 16.3, 31 MB 20.8 and 19.7, 47 MB 21.3 and 19.0; trees of 26 nodes 53 MB 21.8 and 23.0,
-// of 17 70 MB 24.1 and 23.1.
+// of 17 70 MB 24.1 and 23.1.  The more sequences, the surer: from 24 on, 25 MB 17.5 and 19.4, 33 MB 18.9 and 20.5 (25.2 and 26.3 at V = 5000), 38
+// MB 20.5 and 21.0, 44 MB 22.3 and 21.5; with fewer about as often the one as the other.
 static bool sums_of_leaves(const VerifySampleArgs& a) {
   const long long bytes = (long long)a.B * (a.m + 1) * a.V * 4;
-  return bytes <= 24LL << 20 || (a.m <= 32 && bytes <= 64LL << 20);
+  return bytes <= 24LL << 20 || (a.B >= 24 && bytes <= 38LL << 20) || (a.m <= 32 && bytes <= 64LL << 20);
 }
 // Where they are not, trees of so many rows have them all the same: a round that stopped after its first call leaves k leaves under the
 // root, and every walk that accepts a token ends at one.  Ahead and on demand, V = 32000, m = 60, us a call where every node is accepted: 4

@@ -17,11 +17,11 @@ MB = 1 << 20
 def _leaves_ahead(B, V, m):
     """Rows up to which a tree's leaves are summed ahead."""
     total = B * (m + 1) * V * 4
-    return m + 1 if total <= 24 * MB or (m <= 32 and total <= 64 * MB) else 10 * MB // (B * V * 4)
+    return m + 1 if total <= 24 * MB or (B >= 24 and total <= 38 * MB) or (m <= 32 and total <= 64 * MB) else 10 * MB // (B * V * 4)
 
 
 @pytest.mark.parametrize("B,V,m,ahead", [
-    (6, 3, 2, True), (6, 300, 20, True), (6, 4096, 60, True), (6, 98304, 12, True),          # every leaf ahead
+    (6, 3, 2, True), (6, 300, 20, True), (6, 4096, 60, True), (6, 98304, 12, True), (24, 5001, 70, True),   # every leaf ahead
     (13, 4096, 128, False), (13, 4097, 128, False), (16, 10000, 60, False),                  # one, two and three parts
     (8, 28672, 48, False), (8, 28673, 48, False), (8, 32000, 65, False),                     # seven and eight
     (8, 32769, 40, False), (8, 65537, 33, False), (8, 98305, 33, False), (8, 131071, 33, False)])   # two, three, four chunks a block, five parts
