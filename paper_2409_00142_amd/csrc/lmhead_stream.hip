@@ -75,21 +75,11 @@ __global__ __launch_bounds__(768) void lmhead_stream_kernel(StreamArgs a) {
     // ------------------------------ streaming wave ------------------------------
     const int ks = wave * (128 * G);
     const int n = lane & 15, q = lane >> 4;          // MFMA operand coordinates
-    const int lrow = lane >> 4, c = lane & 15;       // load coordinates: 4 rows x 16 chunks per instruction
-    unsigned char* mystage = stage + wave * kStageBytes;
-    const int wr_off = lrow * kStagePitch + c * 16;
-    const int rd_off = n * kStagePitch + q * 16;
-    const uint16_t* wbase = a.W + ks + c * 8;
-
-    u32x4 ring[G][4];
     bf16x8 bfrag[G][4];
-    auto load_x = [&](int g) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        u32x4 u = {0u, 0u, 0u, 0u};
-        if (n < a.R) u = *reinterpret_cast<const u32x4*>(a.hid + (size_t)n * a.H + ks + g * 128 + j * 32 + q * 8);
-        bfrag[g][j] = __builtin_bit_cast(bf16x8, u);
-      }
+    auto load_x = [&](int g, int j) {
+      u32x4 u = {0u, 0u, 0u, 0u};
+      if (n < a.R) u = *reinterpret_cast<const u32x4*>(a.hid + (size_t)n * a.H + ks + g * 128 + j * 32 + q * 8);
+      bfrag[g][j] = __builtin_bit_cast(bf16x8, u);
     };
     // Loads return in order.  With four groups the first one is multiplied, and its next weights requested, when its own operands are
     // there.  With one or two that is hardly earlier than when all are, and the hidden rows go first, on their way while the tile is found.
@@ -98,8 +88,17 @@ __global__ __launch_bounds__(768) void lmhead_stream_kernel(StreamArgs a) {
     constexpr bool kRowsFirst = G < 4;
     if constexpr (kRowsFirst) {
 #pragma unroll
-      for (int g = 0; g < G; ++g) load_x(g);
+      for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) load_x(g, j);
     }
+    const int lrow = lane >> 4, c = lane & 15;       // load coordinates: 4 rows x 16 chunks per instruction
+    unsigned char* mystage = stage + wave * kStageBytes;
+    const int wr_off = lrow * kStagePitch + c * 16;
+    const int rd_off = n * kStagePitch + q * 16;
+    const uint16_t* wbase = a.W + ks + c * 8;
+
+    u32x4 ring[G][4];
     {
       const int lo = tile_lo(0), last = tile_hi(0) - 1;   // rows are clamped to the tile
 #pragma unroll
@@ -110,7 +109,8 @@ __global__ __launch_bounds__(768) void lmhead_stream_kernel(StreamArgs a) {
           ring[g][i] = *reinterpret_cast<const u32x4*>(wbase + (size_t)row * a.H + g * 128);
         }
         if constexpr (!kRowsFirst) {
-          load_x(g);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) load_x(g, j);
           __builtin_amdgcn_sched_barrier(0);
         }
       }
