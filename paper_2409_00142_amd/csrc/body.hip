@@ -94,7 +94,8 @@ __global__ __launch_bounds__((kLinearWaves + 1) * 64) void linear_stream_kernel(
   // whole memory, and a short last range keeps no workgroup waiting at the same moment.  Three calls of one user (H = 4096, F = 11008)
   // 404.3 -> 397.5 us; the down product of ten rows 27.5 -> 25.2.  The ranges are added up in order, which few workgroups, far from the memory's
   // limit, only wait for: 64 of them (N = 1024, K = 11008, ten rows) 13.1 us and 13.9 rotated, 128 (N = 2048, K = 5632) 8.5 both.
-  const int rot = MULTI && nslice >= 192 ? slice % NR : 0;
+  const bool late = MULTI && a.late_rows;
+  const int rot = MULTI && nslice >= 192 && !late ? slice % NR : 0;
   auto range_at = [&](int i) { const int r = i + rot; return r < NR ? r : r - NR; };   // 0 <= i < NR
 
   if (wave < NW) {
@@ -122,8 +123,12 @@ __global__ __launch_bounds__((kLinearWaves + 1) * 64) void linear_stream_kernel(
     // Loads return in order, so the input rows of a group follow its weights: the first group can be multiplied, and its weights
     // of the next tile requested, when its own share of the tile and rows (a quarter of them with G = 4) is there.  With the rows behind
     // the whole tile the memory was idle until they had come too: three calls of one user 397.5 -> 385.6 us, gate/up of ten rows 38.8 ->
-    // 36.4, q/k/v 23.5 -> 22.4.
+    // 36.4, q/k/v 23.5 -> 22.4.  (late: see the launch.)
     const uint16_t* xp0 = x_of(range_at(0));
+    auto load_x = [&](int g) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) bfrag[g][j] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(xp0 + g * 128 + j * 32));
+    };
 #pragma unroll
     for (int g = 0; g < G; ++g) {
       if (MULTI && g >= n_first) continue;
@@ -132,9 +137,16 @@ __global__ __launch_bounds__((kLinearWaves + 1) * 64) void linear_stream_kernel(
         const int row = min(n0 + i * 4 + lrow, vlast);
         ring[g][i] = *reinterpret_cast<const u32x4*>(wb0 + (size_t)row * a.ldw + g * 128);
       }
-#pragma unroll
-      for (int j = 0; j < 4; ++j) bfrag[g][j] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(xp0 + g * 128 + j * 32));
+      if (!late) load_x(g);
       __builtin_amdgcn_sched_barrier(0);
+    }
+    if (late) {
+      lds_barrier();
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        if (MULTI && g >= n_first) continue;
+        load_x(g);
+      }
     }
 #pragma unroll 1
     for (int it = 0; it < total; ++it) {
@@ -157,6 +169,7 @@ __global__ __launch_bounds__((kLinearWaves + 1) * 64) void linear_stream_kernel(
     // epilogue wave: lane = (vb, r) owns outputs 4*vb .. 4*vb+3 of the tile for input row r
     const int r = lane & 15, vb = lane >> 4;
     const bool active = r < a.R && ((rows_on >> r) & 1ull) != 0;   // rows of stopped sequences stay untouched
+    if (late) lds_barrier();
     for (int t = 0; t < nt; ++t) {
       const int v0 = n0 + t * 16 + vb * 4;
       float* const yp = a.y + (size_t)r * a.ldy + v0;
@@ -204,7 +217,11 @@ __global__ __launch_bounds__((kLinearWaves + 1) * 64) void linear_stream_kernel(
 }
 
 template <int G>
-static hipError_t launch_linear_g(const LinearArgs& a, int nslice, hipStream_t stream) {
+static hipError_t launch_linear_g(LinearArgs a, int nslice, hipStream_t stream) {
+  // Rows of W whole 16 KB apart and few input rows: these behind all of the first tile, requested when every wave's weights have been, and no
+  // rotation.  Late against behind each group, N = 4096, K = 8192, weights from HBM, us: one row 18.5 and 19.7, four 19.0 and 19.8, five 19.1 and
+  // 19.75, eight 19.95 and 19.8, ten 20.5 and 19.8; at other pitches late rows are the slower ones (K = 6144, ten rows 15.1 and 14.4).
+  a.late_rows = (a.ldw & 8191) == 0 && a.R <= 6;
   const dim3 grid(nslice), block((a.nw + 1) * 64);
   const size_t lds = (size_t)2 * a.n_ranges * a.nw * 1024 + (size_t)a.nw * kStageBytes;
   if (a.n_ranges > 1 || a.last_units < a.nw * G || a.rg[0].gather_mode != kGatherNone)

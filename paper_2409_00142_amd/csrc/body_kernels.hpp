@@ -43,6 +43,7 @@ struct LinearArgs {
   uint16_t* out16;            // null, or bf16 [R] with row pitch ld16: the rounded result (modes 0/1), the activations (mode 2)
   uint16_t* out16b;           // null, or a second copy of out16 (same pitch)
   int ldw, ldy, ld16, N, R, ntiles, nw, mode;
+  bool late_rows;             // set by the launcher: input rows are requested behind all of a workgroup's first tile
   int last_units;             // 128-element units of the last range (fewer than a whole range: the product's K ends there)
 };
 hipError_t prepare_linear_stream();   // once per process: enables the kernels' LDS sizes
