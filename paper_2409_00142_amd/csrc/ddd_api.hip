@@ -362,15 +362,13 @@ int ddd_create(const ddd_config* cfg, ddd_ctx** out) {
   {
     auto aligned = [](size_t n) { return (n + 255) & ~(size_t)255; };
     const size_t o_mask = aligned((DDD_DMAX + 1) * sizeof(uint32_t)), o_sync = o_mask + aligned((DDD_BMAX / 64) * sizeof(uint64_t));
-    const size_t o_act = o_sync + aligned(2 * sizeof(uint32_t)), o_list = o_act + aligned(sizeof(int32_t));
-    const size_t o_rows = o_list + aligned(rows * sizeof(int32_t));
+    const size_t o_rows = o_sync + aligned(2 * sizeof(uint32_t)) + aligned(cfg->B * sizeof(uint32_t));   // words in front of it too
     const size_t n_rows = rows_from_sums(*cfg) ? (size_t)cfg->B * (cfg->m + 1) * verify_sample_row_bytes() : 0;
-    const size_t n_asked = n_rows ? cfg->B * sizeof(uint32_t) : 0;
-    const size_t o_sum = o_rows + aligned(n_rows + n_asked), o_gmax = o_sum + aligned(c->part_sum_bytes);
+    const size_t o_act = o_rows + aligned(n_rows), o_list = o_act + aligned(sizeof(int32_t));
+    const size_t o_sum = o_list + aligned(rows * sizeof(int32_t)), o_gmax = o_sum + aligned(c->part_sum_bytes);
     const size_t o_gsum = o_gmax + aligned(c->grp_bytes);
     if (e == hipSuccess) e = hipMalloc(&c->small, o_gsum + aligned(c->grp_bytes));
-    if (e == hipSuccess) e = hipMemset(c->small, 0, o_act);
-    if (e == hipSuccess && n_asked) e = hipMemset(static_cast<unsigned char*>(c->small) + o_rows + n_rows, 0, n_asked);
+    if (e == hipSuccess) e = hipMemset(c->small, 0, o_rows);
     if (e == hipSuccess) {
       unsigned char* p = static_cast<unsigned char*>(c->small);
       c->call_count = reinterpret_cast<uint32_t*>(p);

@@ -224,7 +224,7 @@ struct VerifySampleArgs {
   int32_t* bonus_token;          // [B]
   float temperature;
   int B, m, D, V;
-  // null, or scratch of verify_sample_row_bytes() per row of logits (the sums of the rows first) and, behind them, one word per sequence that is
+  // null, or scratch of verify_sample_row_bytes() per row of logits (the sums of the rows first); in front of it one word per sequence that is
   // zero between calls (the workgroups that have made their part of the root's row)
   void* rows;
   // set by the launcher:

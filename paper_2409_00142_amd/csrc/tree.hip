@@ -696,7 +696,7 @@ __global__ __launch_bounds__(kVsPartWaves * kWave) void verify_root_kernel(Verif
   const int n = min(a.tree.n_sel[b], a.m) + 1;
   const float* x = a.logits + (size_t)b * T * a.V;
   VsRow& r = static_cast<VsRow*>(a.rows)[(size_t)b * T];
-  unsigned* const asked = reinterpret_cast<unsigned*>(static_cast<VsRow*>(a.rows) + (size_t)a.B * T) + b;
+  unsigned* const asked = static_cast<unsigned*>(a.rows) - a.B + b;
   const double beta2 = beta2_of(a);
   load_tree(a, b, tid, t);
   const float kx = tid < T ? x[t.tok[tid]] : 0.0f;                        // of the thread's own index: no barrier
