@@ -84,3 +84,28 @@ def test_sums_run_along_k(N, K, R):
         assert bool((y[:, 0].double() - exact).abs().max() < 1e-4)   # fp32 sums of K products of the size K^-1/2
     finally:
         D.ddd_body_destroy(body)
+
+
+@pytest.mark.parametrize("N,K", [(4096, 8192), (516, 16384), (12, 24576)])   # two ranges; two launches, the second with one or two
+@pytest.mark.parametrize("R", [1, 6, 7])
+def test_input_rows_behind_the_whole_tile(N, K, R):
+    """Weight rows whole 16 KB apart, on either side of the number of input rows up to which these are requested behind all of the first
+    tile.  Against 64 bits, and twice with the same bits whatever the result held."""
+    import torch
+    import paper_2409_00142_amd as D
+    print(f"[case] few_rows late N={N} K={K} R={R}", flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N + K + R)
+    W = torch.empty(N, K, device="cuda").normal_(0, K ** -0.5, generator=g).to(torch.bfloat16)
+    x = torch.empty(R, K, device="cuda").normal_(0, 1, generator=g).to(torch.bfloat16)
+    y = torch.full((R, N), -7.0, device="cuda")
+    again = torch.full((R, N), -7.0, device="cuda")
+    body = D.ddd_body_create(D.ddd_body_config(1, 16, 1024, 128, 16, 4, 0))
+    try:
+        D.ddd_body_linear(body, W, N, K, x, R, y)
+        D.ddd_body_linear(body, W, N, K, x, R, again)
+        torch.cuda.synchronize()
+    finally:
+        D.ddd_body_destroy(body)
+    assert torch.equal(y, again)
+    assert bool((y.double() - x.double() @ W.double().T).abs().max() < 1e-4)   # fp32 sums of K products of the size K^-1/2
