@@ -292,9 +292,10 @@ __device__ __forceinline__ void wave_take(const float* sc, int n, int want, int 
 // lines of the tree, so nothing is searched for and nothing is fetched twice.  One round trip brings the pool's size and every node's
 // score, parent, token and depth.  Selection: the m-th largest score (ordered bits) is found six bits at a time by the whole block -
 // the 64 digits are counted in LDS, one barrier, and every wave draws the same conclusion, lane d for the digit d - and no further than a
-// prefix that exactly m nodes reach, three passes as a rule; of equal scores the lowest ids are taken.  Pools of up to 256 nodes are left to
-// one wave (wave_take; 37 nodes and m = 16 4.2 -> 3.6 us, 131 and m = 48 5.1 -> 4.2, 211 and m = 60 5.2 -> 5.0; a wave that selects
-// for itself in every wave: 4.1, 4.9).  The tree index of a selected node
+// prefix that exactly m nodes reach, three passes as a rule; of equal scores the lowest ids are taken.  FEW: pools of up to 256 nodes are
+// left to one wave (wave_take; 37 nodes and m = 16 4.2 -> 3.6 us, 131 and m = 48 5.1 -> 4.2, 211 and m = 60 5.2 -> 5.0; a wave that selects
+// for itself in every wave: 4.1, 4.9); not in the bookkeeping, of whose calls most make no tree: the code alone takes each call 0.15 us (ten
+// calls with the tree of 911 nodes 7.87 and 7.69 us a call, three with one of 211 7.92 and 7.83).  The tree index of a selected node
 // is 1 + the number of selected nodes with a smaller id (ballots, and the waves' totals through LDS).  A parent's tree index is read from
 // the node -> index table (a selected node's parent is selected: its score is no smaller and its id is smaller).
 // A launch is latency alone, and small code: behind a stream of weights its instructions come from memory.  ddd_tree_finalize of one
@@ -303,7 +304,7 @@ __device__ __forceinline__ void wave_take(const float* sc, int n, int want, int 
 constexpr int kTreeMost = kPoolMax;        // nodes of the largest pool
 constexpr int kTreeFew = 256;              // nodes up to which one wave selects
 constexpr int kTreeDigit = 6, kTreePasses = (32 + kTreeDigit - 1) / kTreeDigit;
-template <int Q>
+template <int Q, bool FEW>
 __device__ __forceinline__ void tree_select_block(const ddd_state& st, const ddd_tree& tree, int b, int m, int nmax,
                                                   int tid, int nthr, TreeSmem& sm, int n_nodes) {
   const int T = m + 1;
@@ -334,7 +335,7 @@ __device__ __forceinline__ void tree_select_block(const ddd_state& st, const ddd
       my_dep[q] = pdep[n + 1];
     }
   }
-  const bool few = Q == 2 && most <= kTreeFew;                     // uniform
+  const bool few = FEW && most <= kTreeFew;                     // uniform
   float few_sc[kTreeFew / 64] = {};
   if (few && wave == 0) {
 #pragma unroll
@@ -496,9 +497,9 @@ __device__ __forceinline__ void tree_finalize_block(const ddd_state& st, const d
   if (n_nodes < 0 && nmax - 1 > 2 * nthr) n_nodes = min(st.n_nodes[b], nmax);
   const int most = (n_nodes >= 0 ? n_nodes : nmax) - 1;
   if (most <= 2 * nthr) {                                         // uniform
-    tree_select_block<2>(st, tree, b, m, nmax, tid, nthr, sm, n_nodes);
+    tree_select_block<2, QMOST == 4>(st, tree, b, m, nmax, tid, nthr, sm, n_nodes);
   } else if constexpr (QMOST == 4) {
-    tree_select_block<4>(st, tree, b, m, nmax, tid, nthr, sm, n_nodes);
+    tree_select_block<4, false>(st, tree, b, m, nmax, tid, nthr, sm, n_nodes);
   } else {
     const int N = most, m_eff = min(m, N);
     const float* psc = st.pool_score + (size_t)b * nmax;
